@@ -353,6 +353,25 @@ int iconv2d_twin_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_p
                        const icnn_conv_desc *cb, const void *wb_packed, const int32_t *bias_b, void *yb, void *stream);
 
 /*
+ * A run of 3x3 layers as one launch: the body of a picture-to-picture network (Section 3.1 for each layer).  Result: exactly
+ * that of
+ *     iconv2d_brelu(descs[0], x,  w_packed[0], bias[0], NULL, t0, ...);
+ *     iconv2d_brelu(descs[1], t0, w_packed[1], bias[1], NULL, t1, ...);    ...    the last one writing y
+ * without the middle tensors ever existing (every workgroup takes a tile of the picture through all layers and recomputes
+ * the borders it needs).  The arrays are host memory holding host pointers to descriptors and device pointers to the
+ * layers' packed weights and biases; y must not overlap x.  Shapes it takes: 1 to 6 layers, all 3x3 / stride 1 / padding 1 with
+ * 64 input and 64 output channels, unsigned inputs (up to 127, or full range), unsigned 8-bit outputs, no skip operands;
+ * x, y and their pitches 16-byte aligned; tensors below 2 GiB.  The pitches and offsets of the middle tensors are not used.  Anything
+ * else returns ICNN_E_UNSUPPORTED having launched nothing, and the caller issues the layers separately.
+ *
+ * iconv2d_chain_split (host only) cuts a run of n_layers such layers into launches: lengths[i] (room for n_layers entries) is the number
+ * of layers of launch i, *n_launches their count.  More layers per launch recompute more border, fewer cost more launches.
+ */
+int iconv2d_chain_brelu(int32_t n_layers, const icnn_conv_desc *const *descs, const void *x, const void *const *w_packed,
+                        const int32_t *const *bias, void *y, void *stream);
+int iconv2d_chain_split(int32_t n_layers, const icnn_conv_desc *const *descs, int32_t *lengths, int32_t *n_launches);
+
+/*
  * Rescaled feature-map addition (ratio synchronisation between feature maps,
  * Sections 3.4.2 and 4.1), as a stand-alone pass over memory:
  *   T   = sat32(a + [b * b_mul / 2^b_shift])

@@ -73,6 +73,9 @@ _lib.iconv2d_bottleneck_dual_brelu.argtypes = [C.POINTER(icnn_conv_desc), _vp, _
                                                C.POINTER(icnn_conv_desc), _vp, _vp, C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _vp]
 _lib.iconv2d_pair_brelu.argtypes = [C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _vp, _vp, C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _vp]
 _lib.iconv2d_twin_brelu.argtypes = [C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _vp, C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _vp]
+_descp = C.POINTER(icnn_conv_desc)
+_lib.iconv2d_chain_brelu.argtypes = [_i32, C.POINTER(_descp), _vp, C.POINTER(_vp), C.POINTER(_vp), _vp, _vp]
+_lib.iconv2d_chain_split.argtypes = [_i32, C.POINTER(_descp), C.POINTER(_i32), C.POINTER(_i32)]
 _lib.iadd_rescale.argtypes = [C.POINTER(icnn_add_desc), _vp, _vp, _vp, _vp]
 _lib.iconcat.argtypes = [_i32, C.POINTER(_vp), C.POINTER(_i32), C.POINTER(_i32), C.POINTER(_i32),
                          C.POINTER(_i32), _i32, _i64, _vp, _i32, _vp]
@@ -85,7 +88,7 @@ _lib.icnn_peak_copy.argtypes = [_vp, _vp, C.c_size_t, _vp]
 EXPORTS = ["icnn_version", "icnn_last_error", "icnn_set_tuning", "iconv2d_validate", "iconv2d_out_hw",
            "iconv2d_workspace_bytes", "iconv2d_packed_weight_bytes", "iconv2d_prepack_weights",
            "iconv2d_brelu", "iconv2d_brelu_static_ws", "iconv2d_packed_channel_params_bytes", "iconv2d_prepack_channel_params", "iconv2d_brelu_pc",
-           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_twin_brelu", "iconv2d_maxpool_brelu", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
+           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_twin_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
            "irenormalize_u8", "icnn_peak_mfma_i8", "icnn_peak_copy"]
 
 
@@ -248,6 +251,23 @@ def iconv2d_pair_brelu(c3, t, w3_packed, bias3, res, y, c1, w1_packed, bias1, z,
 def iconv2d_twin_brelu(ca, x, wa_packed, bias_a, ya, cb, wb_packed, bias_b, yb, stream=None):
     return _check(_lib.iconv2d_twin_brelu(C.byref(ca), _ptr(x), _ptr(wa_packed), _ptr(bias_a), _ptr(ya), C.byref(cb),
                                           _ptr(wb_packed), _ptr(bias_b), _ptr(yb), _stream(stream)))
+
+
+def iconv2d_chain_brelu(descs, x, w_packed, bias, y, stream=None):
+    n = len(descs)
+    dp = (_descp * n)(*[C.pointer(d) for d in descs])
+    wp = (_vp * n)(*[_ptr(t) for t in w_packed])
+    bp = (_vp * n)(*[_ptr(t) for t in bias])
+    return _check(_lib.iconv2d_chain_brelu(n, dp, _ptr(x), wp, bp, _ptr(y), _stream(stream)))
+
+
+def iconv2d_chain_split(descs):
+    """Layers per launch for a run of chainable layers."""
+    n = len(descs)
+    dp = (_descp * n)(*[C.pointer(d) for d in descs])
+    lens, k = (_i32 * n)(), _i32()
+    _check(_lib.iconv2d_chain_split(n, dp, lens, C.byref(k)))
+    return list(lens[:k.value])
 
 
 def iadd_rescale(desc, a, b, out, stream=None):

@@ -749,6 +749,67 @@ int iconv2d_twin_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_p
     return launched(launch_conv_plane_twin(a, b, (hipStream_t)stream), "iconv2d_twin_brelu");
 }
 
+// What every layer of a chain has to be; g: its geometry
+static int chain_layer_ok(const icnn_conv_desc *d, const icnn_conv_desc *first)
+{
+    if (d->n != first->n || d->h != first->h || d->w != first->w) return fail(ICNN_E_SHAPE, "the layers of a chain must share n, h, w");
+    if (d->kh != 3 || d->kw != 3 || d->stride_h != 1 || d->stride_w != 1 || d->pad_h != 1 || d->pad_w != 1 || d->cin != 64 || d->cout != 64)
+        return fail(ICNN_E_UNSUPPORTED, "a chain takes 3x3 layers of 64 channels, stride 1, padding 1");
+    if ((d->in_signed != ICNN_IN_U8_LE127 && d->in_signed != ICNN_IN_U8_FULL) || d->in_sub128)
+        return fail(ICNN_E_UNSUPPORTED, "a chain takes unsigned inputs");
+    if ((d->out_mode != ICNN_OUT_BRELU_U8 && d->out_mode != ICNN_OUT_CLAMP_U8) || d->res_mode != ICNN_RES_NONE)
+        return fail(ICNN_E_UNSUPPORTED, "the layers of a chain store unsigned bytes and take no skip operand");
+    return ICNN_OK;
+}
+
+int iconv2d_chain_split(int32_t n_layers, const icnn_conv_desc *const *descs, int32_t *lengths, int32_t *n_launches)
+{
+    if (!descs || !lengths || !n_launches) return fail(ICNN_E_NULL, "descs, lengths and n_launches must not be NULL");
+    if (n_layers < 1 || n_layers > 256) return fail(ICNN_E_SHAPE, "a chain has 1 to 256 layers");
+    for (int i = 0; i < n_layers; ++i) {
+        int rc = check_conv(descs[i], nullptr);
+        if (rc || (rc = chain_layer_ok(descs[i], descs[0]))) return rc;
+    }
+    *n_launches = conv_chain_split(descs[0]->n, descs[0]->h, descs[0]->w, n_layers, lengths);
+    return ICNN_OK;
+}
+
+int iconv2d_chain_brelu(int32_t n_layers, const icnn_conv_desc *const *descs, const void *x, const void *const *w_packed,
+                        const int32_t *const *bias, void *y, void *stream)
+{
+    if (!descs || !w_packed || !bias) return fail(ICNN_E_NULL, "an argument array is NULL");
+    if (n_layers < 1) return fail(ICNN_E_SHAPE, "a chain has at least one layer");
+    if (n_layers > kChainMaxLayers) return fail(ICNN_E_UNSUPPORTED, "one launch takes at most %d layers (iconv2d_chain_split)", kChainMaxLayers);
+    ChainArgs c;
+    for (int i = 0; i < n_layers; ++i) {
+        const icnn_conv_desc *d = descs[i];
+        ConvGeom g;
+        int rc = check_conv(d, &g);
+        if (rc || (rc = chain_layer_ok(d, descs[0]))) return rc;
+        if (i > 0 && d->in_signed == ICNN_IN_U8_LE127 && (descs[i - 1]->out_mode == ICNN_OUT_BRELU_U8 ? descs[i - 1]->bound_q : descs[i - 1]->hi) > 127)
+            return fail(ICNN_E_PARAM, "layer %d declares inputs up to 127, layer %d stores more", i, i - 1);
+        ConvArgs a;
+        int32_t dummy = 0;               // the middle outputs never reach memory
+        if ((rc = fill_conv_args(d, g, i == 0 ? x : (const void *)&dummy, w_packed[i], bias[i], nullptr, i + 1 == n_layers ? y : &dummy, a))) return rc;
+        if (i == 0) {
+            if (!aligned16(x) || d->in_c_stride % 16) return fail(ICNN_E_UNSUPPORTED, "a chain needs a 16-byte aligned input");
+            if (a.x_bytes >= 0x7fffff00u || g.M > 0x7fffffffLL) return fail(ICNN_E_UNSUPPORTED, "a chain needs tensors below 2 GiB");
+            c.x = a.x; c.x_bytes = a.x_bytes; c.in_cs = d->in_c_stride;
+            c.N = d->n; c.H = d->h; c.W = d->w; c.L = n_layers;
+        }
+        if (i + 1 == n_layers) {
+            if (!a.vec_out) return fail(ICNN_E_UNSUPPORTED, "a chain needs a 16-byte aligned output");
+            c.out = (uint8_t *)y; c.out_cs = d->out_c_stride; c.out_co = d->out_c_offset;
+        }
+        ChainLayer &l = c.l[i];
+        l.wp = a.wp; l.bias = a.bias; l.wsum = a.wsum; l.xin = a.frag_xor;
+        l.mul = a.mul; l.shift = a.shift; l.lo = a.lo; l.hi = a.hi; l.rq_fast = a.rq_fast; l.mul_hi = a.mul_hi;
+        l.rq24 = a.rq24; l.t_hi = a.t_hi; l.rnd = a.rnd;
+    }
+    for (int i = n_layers; i < kChainMaxLayers; ++i) c.l[i] = c.l[n_layers - 1];
+    return launched(launch_conv_chain(c, (hipStream_t)stream), "iconv2d_chain_brelu");
+}
+
 int iadd_rescale(const icnn_add_desc *d, const void *a, const void *b, void *out, void *stream)
 {
     if (!d) return fail(ICNN_E_NULL, "add descriptor is NULL");

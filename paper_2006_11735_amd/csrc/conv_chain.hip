@@ -1,0 +1,311 @@
+// A run of 3x3 / stride 1 / padding 1 layers of 64 channels (the body of the super-resolution network) as ONE launch:
+// a workgroup takes a spatial tile of the picture through up to six layers with the middle tensors only in LDS.
+//
+// One such layer on a 256 x 256 plane is 1 us of matrix-core time behind a launch that costs 6 us (launch gap, cold
+// weights, first patch).  Here a workgroup computes TH x TW pixels of the last of L layers and, before them, what those
+// need of every earlier layer: layer l's region is TH + 2 (L - 1 - l) by TW + 2 (L - 1 - l) pixels.  The recomputed border
+// costs matrix time (1.28 x for three layers on 16 x 16 tiles), and saves L - 1 launches; conv_chain_split() weighs the
+// two and cuts a run of layers into launches.
+//
+//   buffers  two activation buffers in LDS, rows of 24 pixels, 80 bytes per pixel (64 channels and 16 bytes of padding:
+//            sixteen consecutive pixels hit every bank once, and every tap of a fragment read is an immediate offset
+//            from one address per lane).  Layer 0 reads the patch copied straight from memory, every later layer what the
+//            layer before wrote; pixels outside the picture are stored as zeros = the next layer's padding.
+//   weights  36 KiB per layer, double-buffered: the next layer's travel while this one is multiplied.  A wave multiplies one
+//            32-channel chunk (wave & 1) and keeps its 18 weight fragments in registers for the layer, so the K loop
+//            reads one activation fragment (1 KiB of LDS) per matrix instruction.
+//   work     layer l's pixels in groups of 32 (row-major over the region); wave w takes groups (w >> 1), + 4, ...
+//   barrier  one per layer
+#include "conv_common.h"
+
+#include <type_traits>
+
+namespace icnn {
+
+constexpr int kChainRP = 24;                       // pixels per buffer row
+constexpr int kChainPix = 80;                      // bytes per pixel in LDS
+constexpr int kChainRow = kChainRP * kChainPix;
+constexpr int kChainF = 18;                        // K fragments of 32 (9 taps x 64 channels)
+constexpr int kChainWBytes = 2 * kChainF * 1024;   // packed weights of one layer
+constexpr int kChainA = kChainRP * kChainRow;      // the first layer's input, up to 24 rows
+constexpr int kChainB = (kChainRP - 2) * kChainRow;
+constexpr int kChainLds = 2 * kChainWBytes + kChainA + kChainB + kChainMaxLayers * 64 * 4;
+static_assert(kChainLds <= 160 * 1024, "LDS");
+
+// PIPE: every layer has the 32-bit requantisation form (ConvArgs::rq24; the host checks).  A wave then deals the requantisation of
+// its previous pixel group out between the matrix instructions of the next: the barrier per layer keeps the two waves of a SIMD in
+// step, so both multiplied and then both requantised (a round of groups took 2.3 k clocks for 1.15 k of matrix work).
+template <bool PIPE>
+__global__ __launch_bounds__(512, 1) void conv_chain_kernel(const ChainArgs g)
+{
+#if defined(__HIP_DEVICE_COMPILE__)   // the buffer-resource type exists in the device pass only
+    constexpr unsigned OOB = 0x80000000u;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    uint8_t *const wbuf = lds;
+    uint8_t *const bufA = lds + 2 * kChainWBytes;
+    uint8_t *const bufB = bufA + kChainA;
+    int32_t *const btab = (int32_t *)(bufB + kChainB);
+
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int chunk = wave & 1;
+
+    // the workgroups of an XCD (dealt round-robin) take a contiguous range of tiles: shared patch borders meet in one L2
+    const int t = (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3);
+    if (t >= g.n_tiles) return;
+    const int n = fast_div(t, g.div_tpi);
+    const int r = t - n * g.tiles_per_img;
+    const int ty = fast_div(r, g.div_tx);
+    const int y0 = ty * g.TH, x0 = (r - ty * g.tiles_x) * g.TW;
+    const int L = g.L;
+
+    auto issue_weights = [&](int l) {
+        const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)g.l[l].wp, 0, kChainWBytes, 0x00020000);
+        uint8_t *const dst = wbuf + (l & 1) * kChainWBytes;
+#pragma unroll
+        for (int i = 0; i < (kChainWBytes / 1024 + 7) / 8; ++i) {
+            const int e = wave + 8 * i;
+            if (e < kChainWBytes / 1024)            // wave-uniform
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, (__attribute__((address_space(3))) void *)(dst + e * 1024), 16,
+                                                         (unsigned)(e * 1024 + lane * 16), 0, 0, 0);
+        }
+    };
+
+    // the first layer's patch: LDS piece q (16 bytes) is slot q % 5 of buffer pixel q / 5; slot 4 is the pixel's padding
+    const int ph = g.TH + 2 * L, pw = g.TW + 2 * L;
+    const int ncopy = (ph * kChainRow + 1023) / 1024;
+    constexpr int CPW = (kChainA / 1024 + 7) / 8;
+    {
+        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)g.x, 0, g.x_bytes, 0x00020000);
+#pragma unroll
+        for (int i = 0; i < CPW; ++i) {
+            const int e = wave + 8 * i;
+            const int q = e * 64 + lane;
+            const int pix = q / 5, slot = q - pix * 5;
+            const int py = pix / kChainRP, px = pix - py * kChainRP;
+            const int iy = y0 - L + py, ix = x0 - L + px;
+            const bool ok = slot < 4 && py < ph && px < pw && (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
+            const unsigned off = ok ? (unsigned)(((n * g.H + iy) * g.W + ix) * g.in_cs + slot * 16) : OOB;
+            if (e < ncopy)                          // wave-uniform
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(bufA + e * 1024), 16, off, 0, 0, 0);
+        }
+    }
+    issue_weights(0);
+    if (wave < L) {                                 // wave l: layer l's biases (and what inputs up to 255 add to them)
+        int b = g.l[wave].bias[lane];
+        if (g.l[wave].xin) b += 128 * g.l[wave].wsum[lane];
+        btab[wave * 64 + lane] = b;
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070);             // vmcnt(0), lgkmcnt(0)
+    asm volatile("" ::: "memory");
+    if (g.l[0].xin) {
+        // inputs up to 255: the matrix cores take x - 128 (see ConvArgs::frag_xor); every lane flips the pieces it fetched
+#pragma unroll
+        for (int i = 0; i < CPW; ++i) {
+            const int e = wave + 8 * i;
+            if (e < ncopy) {
+                v4i *p = (v4i *)(bufA + e * 1024 + lane * 16);
+                *p = *p ^ (int)g.l[0].xin;
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);         // lgkmcnt(0)
+    }
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    for (int l = 0; l < L; ++l) {
+        const ChainLayer &a = g.l[l];
+        const bool last = l + 1 == L;
+        if (!last) issue_weights(l + 1);
+        const uint8_t *const src = (l & 1) ? bufB : bufA;
+        uint8_t *const dst = (l & 1) ? bufA : bufB;
+        v4i w[kChainF];
+#pragma unroll
+        for (int f = 0; f < kChainF; ++f) w[f] = *(const v4i *)(wbuf + (l & 1) * kChainWBytes + (chunk * kChainF + f) * 1024 + lane * 16);
+        const v16i bias = bias16(btab + l * 64 + chunk * 32 + half * 16);
+        const int border = L - 1 - l;               // this layer's region reaches so far beyond the tile
+        const int rw = g.TW + 2 * border, cnt = rw * (g.TH + 2 * border);
+        const int ng = (cnt + 31) >> 5;
+        const uint32_t xout = last ? 0u : g.l[l + 1].xin;
+
+        // pixel of this lane in group gr
+        auto locate = [&](int gr, int &oy, int &ox) {
+            const int idx = min(gr * 32 + col, cnt - 1);
+            oy = (int)((unsigned)idx * g.inv[l] >> 16);
+            ox = idx - oy * rw;
+        };
+        constexpr int RING = 6;
+        v4i bf[RING];
+        const uint8_t *p = src;
+        auto fetch = [&](auto f_tag) {
+            constexpr int f = decltype(f_tag)::value, T = f / 2;
+            bf[f % RING] = *(const v4i *)(p + (T / 3) * kChainRow + (T % 3) * kChainPix + (f & 1) * 32);
+        };
+        // group gr's place, and its first fragments on their way
+        auto start = [&](int gr, int &oy, int &ox) {
+            locate(gr, oy, ox);
+            p = src + oy * kChainRow + ox * kChainPix + half * 16;
+            static_for<RING - 1>([&](auto f_tag) { fetch(f_tag); });
+        };
+        auto store = [&](int gr, int oy, int ox, v4i o) {
+            const int iy = y0 - border + oy, ix = x0 - border + ox;
+            const bool valid = gr * 32 + col < cnt;
+            const bool inside = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
+            if (last) {
+                if (valid && inside)
+                    *(v4i *)(g.out + (size_t)((n * g.H + iy) * g.W + ix) * g.out_cs + g.out_co + chunk * 32 + half * 16) = o;
+            } else if (valid) {
+                if (!inside) o = v4i{0, 0, 0, 0};
+                *(v4i *)(dst + oy * kChainRow + ox * kChainPix + chunk * 32 + half * 16) = o ^ (int)xout;
+            }
+        };
+        auto finish = [&](int gr, int oy, int ox, const v16i &acc) {
+            int tv[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) tv[q] = acc[q];
+            store(gr, oy, ox, PIPE ? requant16<3>(a, tv) : requant16_any(a, tv));
+        };
+        // Multiplies group gr, whose first fragments are on their way, into acc; then starts the group after it.  PREV: group
+        // gr - 4, whose sums are in old, is requantised in slices between the matrix instructions and stored.
+        auto step = [&](auto prev_tag, int gr, int &oy, int &ox, v16i &acc, const v16i &old, int old_y, int old_x) {
+            constexpr bool PREV = decltype(prev_tag)::value;
+            [[maybe_unused]] int ow[4] = {0, 0, 0, 0};
+            static_for<kChainF>([&](auto f_tag) {
+                constexpr int f = decltype(f_tag)::value;
+                if constexpr (f + RING - 1 < kChainF) fetch(std::integral_constant<int, f + RING - 1>{});
+                if constexpr (f == 0) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[f], bf[f % RING], bias, 0, 0, 0);
+                else acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[f], bf[f % RING], acc, 0, 0, 0);
+                if constexpr (PREV && f >= 1 && f < 17) {
+                    epilogue_rq24_slice<0, f - 1, 1>(a, old, v4i{0, 0, 0, 0}, ow);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            });
+            int ny = 0, nx = 0;
+            if (gr + 4 < ng) start(gr + 4, ny, nx);
+            if constexpr (PREV) store(gr - 4, old_y, old_x, v4i{ow[0], ow[1], ow[2], ow[3]});
+            mfma_drain(acc);
+            oy = ny;
+            ox = nx;
+        };
+        const int gr0 = wave >> 1;
+        int oy = 0, ox = 0;
+        if (gr0 < ng) {
+            start(gr0, oy, ox);
+            v16i acc0 = bias, acc1 = bias;
+            if constexpr (PIPE) {
+                int py = oy, px = ox, gr = gr0;
+                step(std::false_type{}, gr, oy, ox, acc0, acc1, 0, 0);
+                for (;;) {
+                    gr += 4;
+                    if (gr >= ng) { finish(gr - 4, py, px, acc0); break; }
+                    int cy = oy, cx = ox;
+                    step(std::true_type{}, gr, oy, ox, acc1, acc0, py, px);
+                    py = cy; px = cx;
+                    gr += 4;
+                    if (gr >= ng) { finish(gr - 4, py, px, acc1); break; }
+                    cy = oy; cx = ox;
+                    step(std::true_type{}, gr, oy, ox, acc0, acc1, py, px);
+                    py = cy; px = cx;
+                }
+            } else {
+                for (int gr = gr0; gr < ng; gr += 4) {
+                    const int cy = oy, cx = ox;
+                    step(std::false_type{}, gr, oy, ox, acc0, acc1, 0, 0);
+                    finish(gr, cy, cx, acc0);
+                }
+            }
+        }
+        if (!last) {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_waitcnt(0x0070);     // the next layer's weights have landed; this wave's pixels are in LDS
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+    }
+#endif
+}
+
+// ------------------------------------------------------------------ dispatch
+// Estimated microseconds of a launch of L layers on TH x TW tiles: the launch itself, then per round of workgroups (one per
+// compute unit) a prologue and, per layer, rounds of four pixel groups and what a layer costs whatever its size (weights
+// to registers, barrier, latencies).  Fitted to 1 to 6 layers on planes of 96 x 96 to 384 x 384 (256 x 256: 5.7, 8.9, 12.2
+// and 16.5 us for 1 to 4 layers).
+static double chain_cost(long long tiles, int L, int th, int tw)
+{
+    double per_tile = 1.5;
+    for (int b = 0; b < L; ++b) {
+        const int ng = ((th + 2 * b) * (tw + 2 * b) + 31) / 32;
+        per_tile += 0.65 * ((ng + 3) / 4) + 1.0;
+    }
+    return 2.0 + per_tile * (double)((tiles + 255) / 256);
+}
+
+// best tile for L layers
+static double chain_tile(int N, int H, int W, int L, int &th, int &tw)
+{
+    const int most = kChainRP - 2 * L;
+    double best = 1e300;
+    for (int ny = (H + most - 1) / most, iy = 0; iy < 6 && ny <= H; ++ny, ++iy)
+        for (int nx = (W + most - 1) / most, ix = 0; ix < 6 && nx <= W; ++nx, ++ix) {
+            const int h = (H + ny - 1) / ny, w = (W + nx - 1) / nx;
+            const double c = chain_cost((long long)N * ny * nx, L, h, w);
+            if (c < best) { best = c; th = h; tw = w; }
+        }
+    return best;
+}
+
+// Cuts n layers into launches of len[0], len[1], ... layers (at most n entries); returns their number.
+int conv_chain_split(int N, int H, int W, int n, int *len)
+{
+    double cost[kChainMaxLayers + 1];
+    int th, tw;
+    for (int L = 1; L <= kChainMaxLayers; ++L) cost[L] = chain_tile(N, H, W, L, th, tw);
+    // shortest path over the number of layers done
+    double best[257];
+    int from[257];
+    best[0] = 0;
+    for (int i = 1; i <= n; ++i) {
+        best[i] = 1e300;
+        for (int L = 1; L <= kChainMaxLayers && L <= i; ++L)
+            if (best[i - L] + cost[L] < best[i]) { best[i] = best[i - L] + cost[L]; from[i] = L; }
+    }
+    int k = 0;
+    for (int i = n; i > 0; i -= from[i]) len[k++] = from[i];
+    return k;
+}
+
+hipError_t launch_conv_chain(ChainArgs &g, hipStream_t st)
+{
+    struct Plan { int N, H, W, L, th, tw; };
+    static thread_local Plan plan = {0, 0, 0, 0, 0, 0};     // host arithmetic only: the last tile choice of this thread
+    if (plan.N != g.N || plan.H != g.H || plan.W != g.W || plan.L != g.L) {
+        plan = {g.N, g.H, g.W, g.L, 1, 1};
+        chain_tile(g.N, g.H, g.W, g.L, plan.th, plan.tw);
+    }
+    g.TH = plan.th;
+    g.TW = plan.tw;
+    if (g.L < 1 || g.L > kChainMaxLayers || g.TH < 1 || g.TW < 1 || g.TH + 2 * g.L > kChainRP || g.TW + 2 * g.L > kChainRP)
+        return hipErrorInvalidValue;
+    g.tiles_x = (g.W + g.TW - 1) / g.TW;
+    g.tiles_per_img = g.tiles_x * ((g.H + g.TH - 1) / g.TH);
+    const long long tiles = (long long)g.tiles_per_img * g.N;
+    if (tiles < 1 || tiles > 0x7ffffff0LL / 8) return hipErrorInvalidValue;
+    g.n_tiles = (int)tiles;
+    g.per_xcd = (int)((tiles + 7) / 8);
+    g.div_tpi = make_fast_div((unsigned)g.tiles_per_img);
+    g.div_tx = make_fast_div((unsigned)g.tiles_x);
+    for (int l = 0; l < g.L; ++l) {
+        const unsigned rw = (unsigned)(g.TW + 2 * (g.L - 1 - l));
+        g.inv[l] = (65536 + rw - 1) / rw;           // idx * inv >> 16 = idx / rw: idx < 22 * 22 and inv * rw - 65536 < 24
+    }
+    bool pipe = true;
+    for (int l = 0; l < g.L; ++l) pipe = pipe && g.l[l].rq24;
+    const auto kernel = pipe ? conv_chain_kernel<true> : conv_chain_kernel<false>;
+    const hipError_t e = allow_large_lds((const void *)kernel);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * g.per_xcd)), dim3(512), kChainLds, st, g);
+    return hipGetLastError();
+}
+
+}  // namespace icnn

@@ -116,8 +116,9 @@ __device__ __forceinline__ void shift_into_byte(int &w, uint32_t x, int sh_v, in
 // Sixteen values t (bias and skip operand already in) -> sixteen requantised, clamped bytes as four words
 // (Section 3.2.1).  RQ as in epilogue_vec: 1 one 32x32->64 multiply-add whose high word is the result;
 // 2 general 64-bit multiply, add, shift; 3 in 32 bits after clamping t to [0, t_hi] (see ConvArgs::rq24).
-template <int RQ>
-__device__ __forceinline__ v4i requant16(const ConvArgs &a, const int (&t)[16])
+// (P: ConvArgs, or any struct with the same requantisation fields)
+template <int RQ, class P>
+__device__ __forceinline__ v4i requant16(const P &a, const int (&t)[16])
 {
     if (RQ == 3) {
         // clamp, multiply-add, then the shift writes its byte of the output word: three instructions per value
@@ -148,7 +149,8 @@ __device__ __forceinline__ v4i requant16(const ConvArgs &a, const int (&t)[16])
                pack_low_bytes(v[8], v[9], v[10], v[11]), pack_low_bytes(v[12], v[13], v[14], v[15])};
 }
 // the cheapest exact form the layer's parameters allow (wave-uniform choice)
-__device__ __forceinline__ v4i requant16_any(const ConvArgs &a, const int (&t)[16])
+template <class P>
+__device__ __forceinline__ v4i requant16_any(const P &a, const int (&t)[16])
 {
     if (a.rq24) return requant16<3>(a, t);
     if (a.rq_fast) return requant16<1>(a, t);
@@ -495,16 +497,16 @@ __device__ __forceinline__ v4i epilogue_bytes16(const ConvArgs &a, const v16i &a
 // Outputs R0 .. R0 + N - 1 of epilogue_bytes16<RES, 3> (the 32-bit requantisation form, a.rq24): their bytes go into
 // the words w[R0 / 4 ..], which the caller collects over the sixteen outputs.  For callers that deal the epilogue out
 // in slices between matrix instructions.  R0 and N are multiples of... any; a word is started by its output 4 q.
-template <int RES, int R0, int N>
-__device__ __forceinline__ void epilogue_rq24_slice(const ConvArgs &a, const v16i &acc, const v4i &res8, int (&w)[4])
+template <int RES, int R0, int N, class P>
+__device__ __forceinline__ void epilogue_rq24_slice(const P &a, const v16i &acc, const v4i &res8, int (&w)[4])
 {
     const int wd[4] = {res8.x, res8.y, res8.z, res8.w};
-    const int half = (1 << a.res_shift) >> 1;
     const int sh_v = a.shift;
 #pragma unroll
     for (int r = R0; r < R0 + N; ++r) {
         int t = acc[r];
-        if (RES == 1) {
+        if constexpr (RES == 1) {
+            const int half = (1 << a.res_shift) >> 1;
             const uint32_t b8 = ((uint32_t)wd[r >> 2] >> ((r & 3) * 8)) & 0xffu;
             t = __builtin_elementwise_add_sat(t, (int)((__umul24(b8, (uint32_t)a.res_mul) + (uint32_t)half) >> a.res_shift));
         }

@@ -122,6 +122,27 @@ struct BlockArgs {
     int nchunk3;                  // output channel chunks of the last layer: C / MID
 };
 
+// A run of 3x3 layers of 64 channels as one launch (see conv_chain.hip)
+constexpr int kChainMaxLayers = 6;
+struct ChainLayer {
+    const uint8_t *wp;
+    const int32_t *bias, *wsum;
+    uint32_t xin;                 // 0x80808080: the layer's inputs go up to 255 (ConvArgs::frag_xor)
+    int mul, shift, lo, hi, rq_fast, mul_hi, rq24, t_hi, rnd;   // as in ConvArgs
+};
+struct ChainArgs {
+    const uint8_t *x;
+    uint8_t *out;
+    unsigned x_bytes;
+    int in_cs, out_cs, out_co;
+    int N, H, W, L;
+    int TH, TW;                   // output tile
+    int tiles_x, tiles_per_img, n_tiles, per_xcd;
+    FastDiv div_tpi, div_tx;
+    unsigned inv[kChainMaxLayers];   // division by a layer's region width
+    ChainLayer l[kChainMaxLayers];
+};
+
 // bytewise maximum of two words: even and odd bytes as 16-bit lanes
 __device__ __forceinline__ uint32_t max_bytes(uint32_t x, uint32_t y)
 {
@@ -196,6 +217,8 @@ bool conv_plane_twin_ok(const ConvArgs &a, const ConvArgs &b);
 hipError_t launch_conv_plane_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st);
 bool conv_deep_applies(const ConvArgs &a);
 hipError_t launch_conv_deep(const ConvArgs &a, hipStream_t st);
+int conv_chain_split(int N, int H, int W, int n, int *len);
+hipError_t launch_conv_chain(ChainArgs &g, hipStream_t st);
 hipError_t launch_conv_pic(const ConvArgs &a, hipStream_t st);
 hipError_t launch_conv_stem_pool(const ConvArgs &a, int hp, int wp, hipStream_t st);
 bool conv_block_tile(int H, int W, BlockArgs &g);

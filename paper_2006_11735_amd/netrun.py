@@ -42,6 +42,7 @@ class GpuNet:
         self.fused_pool = {}                # first conv name -> the max-pool op fused into its launch
         self.fused_pair = {}                # block-closing conv name -> the next block's opening conv op in its launch
         self.fused_twin = {}                # branch name -> the other branch's op in its launch
+        self.fused_chain = {}               # last conv name -> the conv ops before it in its launch
         self.fused_projblock = {}           # last conv name -> (first, middle, projection) conv ops fused into its launch
         pending = {}                        # skip buffer name -> prepared projection step
         for op in net["ops"]:
@@ -78,16 +79,13 @@ class GpuNet:
             self._fuse_first_layer()
             self._fuse_pairs()
             self._fuse_twins()
+            self._fuse_chains()
         torch.cuda.synchronize(self.device)
 
     def _fuse_first_layer(self):
         """A picture convolution followed by the max-pool of its output, nothing else reading that output: one
         iconv2d_maxpool_brelu launch where the library accepts it (the convolution's buffer then stays untouched)."""
-        readers = {}
-        for op in self.net["ops"]:
-            readers.setdefault(op["src"], []).append(op)
-            if op.get("res") is not None:
-                readers.setdefault(op["res"], []).append(op)
+        readers = self._readers()
         steps, i = [], 0
         while i < len(self.steps):
             pair = self.steps[i:i + 2]
@@ -181,15 +179,74 @@ class GpuNet:
             i += 1
         self.steps = steps
 
-    def _fuse_projection_blocks(self):
-        """A stage's opening bottleneck block whose last layer already runs with its projection as one dual step: the
-        two layers before it join that launch (iconv2d_bottleneck_dual_brelu) where the library accepts it; the block's
-        two middle buffers then stay untouched as well."""
+    # A chain's launches recompute borders to save launches; on pictures smaller than a few tiles there is nothing to gain
+    # over the layers, which cost a launch each either way.
+    CHAIN_MIN_PIXELS = 64 * 64
+
+    def _fuse_chains(self):
+        """Runs of convolutions that feed each other and nothing else: as few iconv2d_chain_brelu launches as the library
+        advises, where it accepts them (the tensors between the layers of a launch then stay untouched)."""
+        readers = self._readers()
+        steps, i = [], 0
+        while i < len(self.steps):
+            run = [self.steps[i]]
+            while i + len(run) < len(self.steps):
+                a, b = run[-1], self.steps[i + len(run)]
+                if (a[0] != "conv" or b[0] != "conv" or b[1]["src"] != a[1]["dst"] or readers.get(a[1]["dst"]) != [b[1]] or
+                        a[1]["dst"] in self.net["outputs"]):
+                    break
+                run.append(b)
+            run = self._chain_part(run)
+            if run is None:
+                steps.append(self.steps[i])
+                i += 1
+                continue
+            at = 0
+            for n in B.iconv2d_chain_split([st[2][0] for st in run]):
+                part, at = run[at:at + n], at + n
+                if n == 1:
+                    steps.append(part[0])
+                    continue
+                args = ([st[2][0] for st in part], part[0][2][1], [st[2][2] for st in part], [st[2][3] for st in part], part[-1][2][5])
+                B.iconv2d_chain_brelu(*args)                       # also a warm-up launch
+                self.fused += [st[1]["dst"] for st in part[:-1]]
+                self.fused_chain[part[-1][1]["name"]] = [st[1] for st in part[:-1]]
+                steps.append(("chain", part[-1][1], args))
+            i += len(run)
+        self.steps = steps
+
+    def _chain_part(self, run):
+        """The leading layers of a run that one chain can hold, or None."""
+        if run[0][0] != "conv":
+            return None
+        d = run[0][2][0]
+        if d.n * d.h * d.w < self.CHAIN_MIN_PIXELS:
+            return None
+        n = 0
+        while n < len(run):
+            try:
+                B.iconv2d_chain_split([st[2][0] for st in run[:n + 1]])
+            except B.IcnnError as e:
+                if e.code not in (B.ICNN_E_UNSUPPORTED, B.ICNN_E_SHAPE):
+                    raise
+                break
+            n += 1
+        return run[:n] if n > 1 else None
+
+    def _readers(self):
+        """buffer name -> the ops that read it"""
         readers = {}
         for op in self.net["ops"]:
             readers.setdefault(op["src"], []).append(op)
             if op.get("res") is not None:
                 readers.setdefault(op["res"], []).append(op)
+        return readers
+
+    def _fuse_projection_blocks(self):
+        """A stage's opening bottleneck block whose last layer already runs with its projection as one dual step: the
+        two layers before it join that launch (iconv2d_bottleneck_dual_brelu) where the library accepts it; the block's
+        two middle buffers then stay untouched as well."""
+        readers = self._readers()
         steps, i = [], 0
         while i < len(self.steps):
             trio = self.steps[i:i + 3]
@@ -221,11 +278,7 @@ class GpuNet:
 
     def _fuse_blocks(self):
         """Replaces every run of three per-layer conv steps that forms an identity bottleneck block by one fused step."""
-        readers = {}
-        for op in self.net["ops"]:
-            readers.setdefault(op["src"], []).append(op)
-            if op.get("res") is not None:
-                readers.setdefault(op["res"], []).append(op)
+        readers = self._readers()
         steps, i = [], 0
         while i < len(self.steps):
             trio = self.steps[i:i + 3]
@@ -346,6 +399,8 @@ class GpuNet:
             B.iconv2d_pair_brelu(*args, stream=stream)
         elif kind == "twin":
             B.iconv2d_twin_brelu(*args, stream=stream)
+        elif kind == "chain":
+            B.iconv2d_chain_brelu(*args, stream=stream)
         elif kind == "projblock":
             B.iconv2d_bottleneck_dual_brelu(*args, stream=stream)
         elif kind == "block":

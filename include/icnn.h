@@ -372,6 +372,26 @@ int iconv2d_chain_brelu(int32_t n_layers, const icnn_conv_desc *const *descs, co
 int iconv2d_chain_split(int32_t n_layers, const icnn_conv_desc *const *descs, int32_t *lengths, int32_t *n_launches);
 
 /*
+/*
+ * A program's calls in one: the `n` calls are issued in order on the stream, each with the checks, the result and the errors of the
+ * entry point that its kind names (the first error ends the list and is returned).  For programs that issue the same calls again
+ * and again, whose cost on the host is then one call's marshalling and not n.  Which fields a kind reads, in the order of
+ * the entry point's own arguments: d its descriptors, i its integers, p its device pointers (absent ones NULL);
+ * ICNN_CALL_CHAIN: i[0] layers, list[0..2] the host arrays descs, w_packed and bias, p[0] = x, p[1] = y.
+ */
+typedef enum {
+    ICNN_CALL_CONV = 0, ICNN_CALL_CONV_PC = 1, ICNN_CALL_DUAL = 2, ICNN_CALL_DUAL_PC = 3, ICNN_CALL_CONV_MAXPOOL = 4, ICNN_CALL_BOTTLENECK = 5,
+    ICNN_CALL_BOTTLENECK_DUAL = 6, ICNN_CALL_PAIR = 7, ICNN_CALL_TWIN = 8, ICNN_CALL_CHAIN = 9, ICNN_CALL_MAXPOOL = 10, ICNN_CALL_AVGPOOL = 11
+} icnn_call_kind;
+typedef struct {
+    int32_t kind;                  /* icnn_call_kind */
+    int32_t i[7];
+    const icnn_conv_desc *d[4];
+    const void *p[12];
+    const void *list[3];
+} icnn_call;
+int icnn_run_calls(int32_t n, const icnn_call *calls, void *stream);
+
  * Rescaled feature-map addition (ratio synchronisation between feature maps,
  * Sections 3.4.2 and 4.1), as a stand-alone pass over memory:
  *   T   = sat32(a + [b * b_mul / 2^b_shift])

@@ -37,6 +37,15 @@ class icnn_channel_params(C.Structure):
     _fields_ = [(k, C.c_void_p) for k in ("mul", "shift", "res_mul", "res_shift")]
 
 
+class icnn_call(C.Structure):
+    _fields_ = [("kind", C.c_int32), ("i", C.c_int32 * 7), ("d", C.POINTER(icnn_conv_desc) * 4), ("p", C.c_void_p * 12),
+                ("list", C.c_void_p * 3)]
+
+
+(ICNN_CALL_CONV, ICNN_CALL_CONV_PC, ICNN_CALL_DUAL, ICNN_CALL_DUAL_PC, ICNN_CALL_CONV_MAXPOOL, ICNN_CALL_BOTTLENECK, ICNN_CALL_BOTTLENECK_DUAL,
+ ICNN_CALL_PAIR, ICNN_CALL_TWIN, ICNN_CALL_CHAIN, ICNN_CALL_MAXPOOL, ICNN_CALL_AVGPOOL) = range(12)
+
+
 class IcnnError(RuntimeError):
     def __init__(self, code, msg):
         super().__init__("icnn error %d: %s" % (code, msg))
@@ -76,6 +85,7 @@ _lib.iconv2d_twin_brelu.argtypes = [C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _v
 _descp = C.POINTER(icnn_conv_desc)
 _lib.iconv2d_chain_brelu.argtypes = [_i32, C.POINTER(_descp), _vp, C.POINTER(_vp), C.POINTER(_vp), _vp, _vp]
 _lib.iconv2d_chain_split.argtypes = [_i32, C.POINTER(_descp), C.POINTER(_i32), C.POINTER(_i32)]
+_lib.icnn_run_calls.argtypes = [_i32, C.POINTER(icnn_call), _vp]
 _lib.iadd_rescale.argtypes = [C.POINTER(icnn_add_desc), _vp, _vp, _vp, _vp]
 _lib.iconcat.argtypes = [_i32, C.POINTER(_vp), C.POINTER(_i32), C.POINTER(_i32), C.POINTER(_i32),
                          C.POINTER(_i32), _i32, _i64, _vp, _i32, _vp]
@@ -88,7 +98,7 @@ _lib.icnn_peak_copy.argtypes = [_vp, _vp, C.c_size_t, _vp]
 EXPORTS = ["icnn_version", "icnn_last_error", "icnn_set_tuning", "iconv2d_validate", "iconv2d_out_hw",
            "iconv2d_workspace_bytes", "iconv2d_packed_weight_bytes", "iconv2d_prepack_weights",
            "iconv2d_brelu", "iconv2d_brelu_static_ws", "iconv2d_packed_channel_params_bytes", "iconv2d_prepack_channel_params", "iconv2d_brelu_pc",
-           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_twin_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
+           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_twin_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "icnn_run_calls", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
            "irenormalize_u8", "icnn_peak_mfma_i8", "icnn_peak_copy"]
 
 
@@ -101,10 +111,14 @@ def _ptr(t):
     return t.data_ptr()
 
 
+_raw_stream, _current_device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        # (the handle of torch's current stream on its current device; building a Stream object around it costs 2.7 us of host time
+        # more, as much as a launch)
+        return _raw_stream(_current_device())
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -268,6 +282,53 @@ def iconv2d_chain_split(descs):
     lens, k = (_i32 * n)(), _i32()
     _check(_lib.iconv2d_chain_split(n, dp, lens, C.byref(k)))
     return list(lens[:k.value])
+
+
+class Calls:
+    """A list of calls issued by one icnn_run_calls: (kind name, arguments of the binding's function of that kind), as netrun has them."""
+
+    def __init__(self, calls):
+        self._keep = [args for _, args in calls]                  # tensors and descriptors the list points to
+        self._arr = (icnn_call * max(1, len(calls)))()
+        for c, (kind, args) in zip(self._arr, calls):
+            self._fill(c, kind, args)
+        self.n = len(calls)
+
+    def _fill(self, c, kind, args):
+        if kind == "chain":
+            descs, x, w_packed, bias, y = args
+            n = len(descs)
+            dp = (_descp * n)(*[C.pointer(d) for d in descs])
+            wp = (_vp * n)(*[_ptr(t) for t in w_packed])
+            bp = (_vp * n)(*[_ptr(t) for t in bias])
+            self._keep.append((dp, wp, bp))
+            c.kind, c.i[0] = ICNN_CALL_CHAIN, n
+            c.list[0], c.list[1], c.list[2] = C.addressof(dp), C.addressof(wp), C.addressof(bp)
+            c.p[0], c.p[1] = _ptr(x), _ptr(y)
+            return
+        # (kind, integers in the argument list before the first pointer or after the first descriptor)
+        c.kind, ints = {"conv": (ICNN_CALL_CONV, 0), "conv_pc": (ICNN_CALL_CONV_PC, 0), "dual": (ICNN_CALL_DUAL, 0),
+                        "dual_pc": (ICNN_CALL_DUAL_PC, 0), "convpool": (ICNN_CALL_CONV_MAXPOOL, 3), "block": (ICNN_CALL_BOTTLENECK, 0),
+                        "projblock": (ICNN_CALL_BOTTLENECK_DUAL, 0), "pair": (ICNN_CALL_PAIR, 0), "twin": (ICNN_CALL_TWIN, 0),
+                        "maxpool": (ICNN_CALL_MAXPOOL, 7), "avgpool": (ICNN_CALL_AVGPOOL, 7)}[kind]
+        args = list(args)
+        if ints:
+            at = 1 if isinstance(args[0], icnn_conv_desc) else 0
+            for k in range(ints):
+                c.i[k] = int(args.pop(at))
+        nd = 0
+        ptrs = []
+        for a in args:
+            if isinstance(a, icnn_conv_desc):
+                c.d[nd] = C.pointer(a)
+                nd += 1
+            else:
+                ptrs.append(a)
+        for k, t in enumerate(ptrs):
+            c.p[k] = _ptr(t)
+
+    def run(self, stream=None):
+        return _check(_lib.icnn_run_calls(self.n, self._arr, _stream(stream)))
 
 
 def iadd_rescale(desc, a, b, out, stream=None):

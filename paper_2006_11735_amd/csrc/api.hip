@@ -945,6 +945,45 @@ int irenormalize_u8(int64_t count, const void *x, void *out, void *stream)
                     "irenormalize_u8");
 }
 
+int icnn_run_calls(int32_t n, const icnn_call *calls, void *stream)
+{
+    if (n < 0) return fail(ICNN_E_SHAPE, "n must be >= 0");
+    if (n && !calls) return fail(ICNN_E_NULL, "calls is NULL");
+    for (int32_t k = 0; k < n; ++k) {
+        const icnn_call &c = calls[k];
+        const void *const *p = c.p;
+        const icnn_conv_desc *const *d = c.d;
+        const int32_t *i = c.i;
+        auto b = [&](int q) { return (const int32_t *)p[q]; };
+        auto o = [&](int q) { return const_cast<void *>(p[q]); };
+        int rc;
+        switch (c.kind) {
+        case ICNN_CALL_CONV: rc = iconv2d_brelu(d[0], p[0], p[1], b(2), p[3], o(4), o(5), stream); break;
+        case ICNN_CALL_CONV_PC: rc = iconv2d_brelu_pc(d[0], p[0], p[1], b(2), p[3], p[4], o(5), o(6), stream); break;
+        case ICNN_CALL_DUAL: rc = iconv2d_dual_brelu(d[0], p[0], p[1], b(2), d[1], p[3], p[4], b(5), o(6), stream); break;
+        case ICNN_CALL_DUAL_PC: rc = iconv2d_dual_brelu_pc(d[0], p[0], p[1], b(2), p[3], d[1], p[4], p[5], b(6), o(7), stream); break;
+        case ICNN_CALL_CONV_MAXPOOL: rc = iconv2d_maxpool_brelu(d[0], i[0], i[1], i[2], p[0], p[1], b(2), o(3), stream); break;
+        case ICNN_CALL_BOTTLENECK:
+            rc = iconv2d_bottleneck_brelu(d[0], p[0], p[1], b(2), d[1], p[3], b(4), d[2], p[5], b(6), p[7], o(8), stream);
+            break;
+        case ICNN_CALL_BOTTLENECK_DUAL:
+            rc = iconv2d_bottleneck_dual_brelu(d[0], p[0], p[1], b(2), d[1], p[3], b(4), d[2], p[5], b(6), d[3], p[7], b(8), o(9), stream);
+            break;
+        case ICNN_CALL_PAIR: rc = iconv2d_pair_brelu(d[0], p[0], p[1], b(2), p[3], o(4), d[1], p[5], b(6), o(7), stream); break;
+        case ICNN_CALL_TWIN: rc = iconv2d_twin_brelu(d[0], p[0], p[1], b(2), o(3), d[1], p[4], b(5), o(6), stream); break;
+        case ICNN_CALL_CHAIN:
+            rc = iconv2d_chain_brelu(i[0], (const icnn_conv_desc *const *)c.list[0], p[0], (const void *const *)c.list[1],
+                                     (const int32_t *const *)c.list[2], o(1), stream);
+            break;
+        case ICNN_CALL_MAXPOOL: rc = imaxpool2d_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
+        case ICNN_CALL_AVGPOOL: rc = iavgpool_global_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
+        default: rc = fail(ICNN_E_PARAM, "call %d: unknown kind %d", k, c.kind);
+        }
+        if (rc) return rc;
+    }
+    return ICNN_OK;
+}
+
 int icnn_peak_mfma_i8(int32_t blocks, int32_t iters, void *sink, void *stream)
 {
     if (blocks < 1 || blocks > (1 << 20) || iters < 1) return fail(ICNN_E_SHAPE, "blocks must be in [1, 2^20] and iters >= 1");

@@ -80,6 +80,7 @@ class GpuNet:
             self._fuse_pairs()
             self._fuse_twins()
             self._fuse_chains()
+        self._calls = B.Calls([(kind, args) for kind, _, args in self.steps])
         torch.cuda.synchronize(self.device)
 
     def _fuse_first_layer(self):
@@ -382,8 +383,7 @@ class GpuNet:
         self.buf["raw"].copy_(torch.from_numpy(np.ascontiguousarray(x_raw)).to(self.device))
 
     def run(self, stream=None):
-        for i in range(len(self.steps)):
-            self.run_step(i, stream)
+        self._calls.run(stream)
 
     def run_step(self, i, stream=None):
         kind, _, args = self.steps[i]

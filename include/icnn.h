@@ -124,7 +124,8 @@ const char *icnn_last_error(void);
  * synchronised: set it while no other thread is inside the library.  `name` (host string) and the values it takes:
  *   "tile"        -1 library's choice; 0..4 force that tile shape of the tap-by-tap convolution kernel
  *   "stages"      0 library's choice; 2..6 LDS ring depth of that kernel
- *   "no_narrow", "no_fc", "no_halo", "no_stream", "no_block64", "no_deep", "no_plane", "no_pic"   1 keeps layers off the respective special kernel
+ *   "no_narrow", "no_lat", "no_halo", "no_stream", "no_block64", "no_deep", "no_plane", "no_pic"   1 keeps layers off the respective special kernel
+ *   "lat"         1 lets the kernel for few pixels (waves split K straight from global memory) take every layer whose shape it accepts
  *   "halo_tile"   0 library's choice; 1 = 128 x 128, 2 = 64 x 256 tiles of the patch-resident 3x3 kernel
  *   "halo_always" 1 lets the patch-resident kernel take layers with several tiles per workgroup
  *   "block_any_form" 1 keeps fused bottleneck blocks on the instantiation that holds every epilogue form
@@ -132,7 +133,7 @@ const char *icnn_last_error(void);
  *   "plane_always" 1 lets the kernel with two-dimensional tiles (few channels, large pictures) take every layer it accepts
  *   "deep_always" 1 lets the 3x3 kernel whose waves split the K axis take every layer whose shape it accepts
  *   "deep_plain_walk" 1 gives that kernel the tile order of the other kernels (pixel tiles, not channel tiles, per XCD)
- *   "ksplit"      0 library's choice; 1 never split the K axis over workgroups; 2..8 that split where it divides the K steps
+ *   "ksplit"      0, 1 never split the K axis over workgroups (the library's choice); 2..8 that split where it divides the K steps
  *   "reset"       (value ignored) back to the library's choices
  * Unknown names and values outside these ranges return ICNN_E_PARAM and change nothing. */
 int icnn_set_tuning(const char *name, int32_t value);
@@ -372,7 +373,6 @@ int iconv2d_chain_brelu(int32_t n_layers, const icnn_conv_desc *const *descs, co
 int iconv2d_chain_split(int32_t n_layers, const icnn_conv_desc *const *descs, int32_t *lengths, int32_t *n_launches);
 
 /*
-/*
  * A program's calls in one: the `n` calls are issued in order on the stream, each with the checks, the result and the errors of the
  * entry point that its kind names (the first error ends the list and is returned).  For programs that issue the same calls again
  * and again, whose cost on the host is then one call's marshalling and not n.  Which fields a kind reads, in the order of
@@ -392,6 +392,7 @@ typedef struct {
 } icnn_call;
 int icnn_run_calls(int32_t n, const icnn_call *calls, void *stream);
 
+/*
  * Rescaled feature-map addition (ratio synchronisation between feature maps,
  * Sections 3.4.2 and 4.1), as a stand-alone pass over memory:
  *   T   = sat32(a + [b * b_mul / 2^b_shift])

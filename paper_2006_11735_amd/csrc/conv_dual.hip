@@ -308,6 +308,7 @@ static hipError_t launch_dual_cfg(const ConvArgs &a0, const ProjArgs &q, hipStre
 
 hipError_t launch_conv_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st)
 {
+    if (conv_lat_dual_applies(a, q)) return launch_conv_lat_dual(a, q, st);
     // narrow pixel tiles when the wide ones would leave most CUs without work
     const long long wide = (long long)((a.Cout + 127) / 128) * ((a.M + 127) / 128);
     if (a.pc) {

@@ -728,12 +728,12 @@ static hipError_t launch_tile(int t, const ConvArgs &a, int ksplit, hipStream_t 
     }
 }
 
-// Estimated cycles of a launch with tile shape c and the K axis cut into ksplit ranges: rounds of resident
+// Estimated cycles of a launch with tile shape c: rounds of resident
 // workgroups times the time of one work unit, whose K loop is bound either by the matrix cores or by the
 // L2 -> LDS traffic of its tiles (bytes per step = 64 * (bm + bp)).
-static double tile_cost(const TileCfg &c, const ConvArgs &a, int ksplit)
+static double tile_cost(const TileCfg &c, const ConvArgs &a)
 {
-    const double tiles = (double)((a.Cout + c.bm - 1) / c.bm) * (double)((a.M + c.bp - 1) / c.bp) * ksplit;
+    const double tiles = (double)((a.Cout + c.bm - 1) / c.bm) * (double)((a.M + c.bp - 1) / c.bp);
     const double slots = 256.0 * c.per_cu;
     const double rounds = (double)(long long)((tiles + slots - 1) / slots);
     const double resident = tiles < slots ? (tiles / 256.0 > 1 ? tiles / 256.0 : 1) : c.per_cu;   // per CU
@@ -743,21 +743,16 @@ static double tile_cost(const TileCfg &c, const ConvArgs &a, int ksplit)
     const bool pointwise = a.KH == 1 && a.KW == 1 && a.sh == 1 && a.sw == 1;
     const double l2 = 64.0 * (c.bm + (pointwise ? 1.0 : 1.1) * c.bp) / 24.0;
     const double step = resident * (mfma > l2 ? mfma : l2) + 150;
-    double fixed = 2500 + 1.5 * c.bm * c.bp / 256 * 6;                     // prologue + epilogue
-    // partial sums out, their arrival, the counter's round trip, partial sums in: measured 5 to 8 us on layers of
-    // 10 us (64 x 7 x 7 x 2048 -> 512: 16.5 us split in two against 10.8 whole; 64 x 14 x 14 x 256 -> 256 3x3 / 2:
-    // 23.6 against 12.7), whether the sums travel through memory or stay in L2: a chain of memory latencies at the
-    // end of the launch, not bandwidth
-    if (ksplit > 1) fixed += 15000;
-    return rounds * (a.ksteps / ksplit * step + fixed);
+    const double fixed = 2500 + 1.5 * c.bm * c.bp / 256 * 6;                     // prologue + epilogue
+    return rounds * (a.ksteps * step + fixed);
 }
 
 // Splits of the K axis the kernel can run for this layer with tile shape c: 128-channel tiles, pointwise and
 // 64-channel-aligned layers only (the other addressing modes track taps per lane), even ranges of at least 8 steps, at most one unit per
-// compute unit.  Layers with few tiles and a long K loop leave most compute units idle otherwise (a 7 x 7 x
-// 512-channel layer at batch 64 has 100 tiles of 128 x 128 for 256 units); whether a split pays is the cost model's
-// business (at the workloads' sizes it does not: see tile_cost).
-static bool split_allowed(const TileCfg &c, const ConvArgs &a, int s, bool forced)
+// compute unit.  The library never splits by itself: partial sums out, their arrival, the counter's round trip, partial sums in are a
+// chain of memory latencies at the end of the launch (14 x 14 x 512 -> 512 3x3 / 2 on 16, 32 and 64 images: 41.9, 27.4 and 24.5 us
+// split, 18.6, 18.5 and 19.4 whole; 28 x 28 x 256 -> 256 3x3 / 2 on 16: 24.5 and 12.0).  Kept for the "ksplit" override.
+static bool split_allowed(const TileCfg &c, const ConvArgs &a, int s)
 {
     if (s == 1) return true;
     // (the padded copy of a 1x1 small-cin layer is wider than the output: its pixels are not the output's pixels)
@@ -765,7 +760,7 @@ static bool split_allowed(const TileCfg &c, const ConvArgs &a, int s, bool force
     if (!(pw || (a.Cin % 64 == 0 && a.KH * a.KW <= 32)) || a.K % kStepK != 0 || a.ksteps % s != 0 || c.bm != 128) return false;
     const long long tiles = (long long)((a.Cout + c.bm - 1) / c.bm) * ((a.M + c.bp - 1) / c.bp);
     if (tiles > kWsMaxSplitTiles) return false;
-    return forced ? a.ksteps / s >= 2 : (a.ksteps / s >= 8 && tiles * s <= 256);
+    return a.ksteps / s >= 2;
 }
 
 // Tile shape and K split of the direct-to-LDS kernel for a layer: the cheapest by the cost model, or what the tuning
@@ -775,18 +770,13 @@ static void choose_plan(const ConvArgs &a, bool may_split, int &tile, int &kspli
     tile = -1;
     ksplit = 1;
     double best_cost = 0;
-    const int s_lo = !may_split || g_tuning.ksplit == 1 ? 1 : (g_tuning.ksplit > 1 ? g_tuning.ksplit : 1);
-    const int s_hi = !may_split || g_tuning.ksplit == 1 ? 1 : (g_tuning.ksplit > 1 ? g_tuning.ksplit : 8);
+    const int forced = may_split && g_tuning.ksplit > 1 ? g_tuning.ksplit : 1;
     for (int t = 0; t < kNumTiles; ++t) {
         if (g_tuning.tile >= 0 && g_tuning.tile < kNumTiles ? t != g_tuning.tile : (kTiles[t].bm / 2 >= a.Cout && t != 0))
             continue;                                                      // forced shape; or more than half the cout tile empty
-        for (int s = 1; s <= s_hi; ++s) {
-            if (s > 1 && s < s_lo) continue;
-            if (!split_allowed(kTiles[t], a, s, g_tuning.ksplit > 1)) continue;
-            double c = tile_cost(kTiles[t], a, s);
-            if (s > 1 && g_tuning.ksplit > 1) c = 0;                       // a forced split wins wherever it is possible
-            if (tile < 0 || c < best_cost) { tile = t; ksplit = s; best_cost = c; }
-        }
+        const int s = split_allowed(kTiles[t], a, forced) ? forced : 1;    // a forced split wins wherever it is possible
+        const double c = s > 1 ? 0 : tile_cost(kTiles[t], a);
+        if (tile < 0 || c < best_cost) { tile = t; ksplit = s; best_cost = c; }
     }
 }
 
@@ -799,8 +789,8 @@ static bool takes_direct(const ConvArgs &a, bool direct_ok)
 size_t conv_split_bytes(const ConvArgs &a, bool direct_ok)
 {
     if (direct_ok && conv_narrow_applies(a) && !g_tuning.no_narrow) return 0;
-    if (direct_ok && conv_fc_applies(a) && !g_tuning.no_fc) return 0;
     if (!takes_direct(a, direct_ok)) return 0;
+    if (conv_lat_applies(a)) return 0;
     if (!g_tuning.no_plane && g_tuning.tile < 0 && conv_plane_applies(a)) return 0;
     if (!g_tuning.no_deep && g_tuning.tile < 0 && conv_deep_applies(a)) return 0;
     if (!g_tuning.no_halo && g_tuning.tile < 0 && conv_halo_applies(a)) return 0;
@@ -817,8 +807,8 @@ hipError_t launch_conv(const ConvArgs &a, bool vec_in, bool direct_ok, hipStream
     // one to four output channels: a lane per pixel and dot products beat tiles that are 7/8 padding
     if (direct_ok && conv_narrow_applies(a) && !g_tuning.no_narrow)
         return launch_conv_narrow(a, st);
-    // the classifier: a few pixels, long K
-    if (direct_ok && conv_fc_applies(a) && !g_tuning.no_fc) return launch_conv_fc(a, st);
+    // few pixels: the waves split the K axis straight from global memory
+    if (direct && conv_lat_applies(a)) return launch_conv_lat(a, st);
     // few channels on a large picture: two-dimensional tiles, patch and weights resident in LDS
     if (direct && !g_tuning.no_plane && g_tuning.tile < 0 && conv_plane_applies(a)) return launch_conv_plane(a, st);
     // 3x3 / stride 1 / padding 1 with cin % 256 == 0 on few pixels: the waves of a workgroup split the K axis

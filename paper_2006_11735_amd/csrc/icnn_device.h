@@ -182,7 +182,8 @@ struct Tuning {
     int tile = -1;         // force tile shape 0..4 of the direct-to-LDS kernel (also keeps 3x3 layers off the patch kernel)
     int stages = 0;        // force the LDS ring depth of the direct-to-LDS kernel (2..6)
     int no_narrow = 0;     // keep one-to-four-channel layers on the tile kernels
-    int no_fc = 0;         // keep few-pixel pointwise layers on the tile kernels
+    int lat = 0;           // few-pixel kernel for every layer whose shape it accepts
+    int no_lat = 0;        // keep layers on few pixels off the kernel whose waves split the K axis straight from global memory
     int no_halo = 0;       // keep 3x3 layers on the tap-by-tap kernel
     int halo_tile = 0;     // patch-resident kernel: 1 = 128 x 128, 2 = 64 x 256
     int halo_always = 0;   // patch-resident kernel also with several tiles per workgroup and short K loops
@@ -207,8 +208,10 @@ hipError_t launch_conv(const ConvArgs &a, bool vec_in, bool direct_ok, hipStream
 size_t conv_split_bytes(const ConvArgs &a, bool direct_ok);
 hipError_t launch_conv_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st);
 hipError_t allow_large_lds(const void *kernel);   // > 64 KiB of dynamic LDS, once per kernel function
-bool conv_fc_applies(const ConvArgs &a);
-hipError_t launch_conv_fc(const ConvArgs &a, hipStream_t st);
+bool conv_lat_applies(const ConvArgs &a);
+hipError_t launch_conv_lat(const ConvArgs &a, hipStream_t st);
+bool conv_lat_dual_applies(const ConvArgs &a, const ProjArgs &q);
+hipError_t launch_conv_lat_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st);
 bool conv_halo_applies(const ConvArgs &a);
 hipError_t launch_conv_halo(const ConvArgs &a, hipStream_t st);
 bool conv_plane_applies(const ConvArgs &a);

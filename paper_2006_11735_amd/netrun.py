@@ -117,6 +117,9 @@ class GpuNet:
     # fit the chip in about one round and the wide tensor is at most 1024 channels (measured at batch 64: 17.6 us
     # against 23.8 us for 12544 pixels of 256 -> 1024 -> 256; level at 50176 pixels of 128 -> 512 -> 128; a loss,
     # 22.9 us against 19.0 us, at 3136 pixels of 512 -> 2048 -> 512).
+    # Below the other bound the two layers by themselves are the faster choice (a few tiles of 64 pixels against work units all over
+    # the chip: one image of 256 -> 1024 -> 256 takes 13.2 us fused and 8.5 us in two launches, nine 13.7 and 13.1 us).
+    PAIR_MIN_PIXELS = 1800
     PAIR_MAX_PIXELS = 64 * 512
     PAIR_MAX_WIDE = 1024
 
@@ -132,7 +135,7 @@ class GpuNet:
                 (d3, t, w3, b3, res, y, _ws3), (d1, _y, w1, b1, _r1, z, _ws1) = two[0][2], two[1][2]
                 if (o1["src"] == o3["dst"] and o3["kh"] == 1 and o1["kh"] == 1 and o3["dst_c_offset"] == 0 and
                         o1["cout"] == o3["cin"] and o1["cin"] == o3["cout"] and
-                        d3.n * d3.h * d3.w <= self.PAIR_MAX_PIXELS and o3["cout"] <= self.PAIR_MAX_WIDE):
+                        self.PAIR_MIN_PIXELS <= d3.n * d3.h * d3.w <= self.PAIR_MAX_PIXELS and o3["cout"] <= self.PAIR_MAX_WIDE):
                     args = (d3, t, w3, b3, res, y, d1, w1, b1, z)
                     try:
                         B.iconv2d_pair_brelu(*args)                # also a warm-up launch
@@ -277,6 +280,10 @@ class GpuNet:
             i += 1
         self.steps = steps
 
+    # With 128 middle channels a block is a chain of 22 us whatever its tiles are fewer than the compute units; its three layers
+    # spread over the chip instead (one image: 12.7 us, four 17.6, nine 21).  64 middle channels stay fused: 10.6 us for one image.
+    BLOCK128_MIN_PIXELS = 7100
+
     def _fuse_blocks(self):
         """Replaces every run of three per-layer conv steps that forms an identity bottleneck block by one fused step."""
         readers = self._readers()
@@ -289,7 +296,8 @@ class GpuNet:
                          readers.get(o1["dst"]) == [o2] and readers.get(o2["dst"]) == [o3] and
                          o1["dst"] not in self.net["outputs"] and o2["dst"] not in self.net["outputs"] and
                          o1["dst_c_offset"] == 0 and o2["dst_c_offset"] == 0)
-                if chain:
+                d1 = trio[0][2][0]
+                if chain and (o1["cout"] != 128 or d1.n * d1.h * d1.w >= self.BLOCK128_MIN_PIXELS):
                     (d1, x, w1, b1, _r1, _y1, _ws1), (d2, _x2, w2, b2, _r2, _y2, _ws2), (d3, _x3, w3, b3, res, y, _ws3) = (
                         st[2] for st in trio)
                     args = (d1, x, w1, b1, d2, w2, b2, d3, w3, b3, res, y)

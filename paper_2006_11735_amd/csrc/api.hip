@@ -294,13 +294,19 @@ static int fill_conv_args(const icnn_conv_desc *d, const ConvGeom &g, const void
         a.rq_fast = 1;
         a.mul_hi = (int)((long long)a.mul << (32 - a.shift));
     }
-    a.rq24 = a.t_hi = a.rnd = 0;
-    if (d->out_mode != ICNN_OUT_RAW_S32 && a.lo == 0 && a.hi >= 0 && a.shift >= 1 && a.shift <= 31 && a.mul >= 1 &&
+    a.rq24 = a.t_hi = a.rnd = a.rqh = 0;
+    if (d->out_mode != ICNN_OUT_RAW_S32 && a.lo == 0 && a.hi >= 0 && a.shift >= 1 && a.shift <= 33 && a.mul >= 1 &&
         a.mul < (1 << 24)) {
         const long long half = 1LL << (a.shift - 1);
         const long long num = ((long long)a.hi << a.shift) - half;
         const long long t_hi = num <= 0 ? 0 : (num + a.mul - 1) / a.mul;
-        if (t_hi < (1 << 24) && t_hi * a.mul + half <= 0xffffffffLL && ((t_hi * a.mul + half) >> a.shift) == a.hi) {
+        const long long m = (long long)a.mul << (33 - a.shift);
+        if (t_hi < (1 << 24) && m < (1 << 24) && ((t_hi * a.mul + half) >> a.shift) == a.hi) {
+            // floor((t m / 2^31 + 1) / 2) with t m / 2^31 floored first: the floor of a floor
+            a.rqh = (int)m;
+            a.t_hi = (int)t_hi;
+        }
+        if (a.shift <= 31 && t_hi < (1 << 24) && t_hi * a.mul + half <= 0xffffffffLL && ((t_hi * a.mul + half) >> a.shift) == a.hi) {
             a.rq24 = 1;
             a.t_hi = (int)t_hi;
             a.rnd = (int)half;
@@ -804,7 +810,7 @@ int iconv2d_chain_brelu(int32_t n_layers, const icnn_conv_desc *const *descs, co
         ChainLayer &l = c.l[i];
         l.wp = a.wp; l.bias = a.bias; l.wsum = a.wsum; l.xin = a.frag_xor;
         l.mul = a.mul; l.shift = a.shift; l.lo = a.lo; l.hi = a.hi; l.rq_fast = a.rq_fast; l.mul_hi = a.mul_hi;
-        l.rq24 = a.rq24; l.t_hi = a.t_hi; l.rnd = a.rnd;
+        l.rq24 = a.rq24; l.t_hi = a.t_hi; l.rnd = a.rnd; l.rqh = a.rqh;
     }
     for (int i = n_layers; i < kChainMaxLayers; ++i) c.l[i] = c.l[n_layers - 1];
     return launched(launch_conv_chain(c, (hipStream_t)stream), "iconv2d_chain_brelu");

@@ -99,6 +99,14 @@ __device__ __forceinline__ int pack_low_bytes(int v0, int v1, int v2, int v3)
     return (int)__builtin_amdgcn_perm(hi, lo, 0x05040100u);
 }
 
+// t clamped to [0, t_hi], times m, the high 32 bits of it: t_hi and m (scalars) below 2^24.  Plain arithmetic that the compiler turns
+// into two clamps and v_mul_hi_u32_u24: around hand-written instructions it puts wait states.
+__device__ __forceinline__ uint32_t clamp_mul_hi_u24(int t, int t_hi, int m)
+{
+    const uint32_t x = (uint32_t)min(max(t, 0), t_hi & 0xffffff);
+    return (uint32_t)(((uint64_t)(x & 0xffffff) * (uint64_t)((uint32_t)m & 0xffffff)) >> 32);
+}
+
 // byte `pos` (1..3) of w = low byte of x >> sh; the other bytes of w are kept
 __device__ __forceinline__ void shift_into_byte(int &w, uint32_t x, int sh_v, int pos)
 {
@@ -115,7 +123,9 @@ __device__ __forceinline__ void shift_into_byte(int &w, uint32_t x, int sh_v, in
 
 // Sixteen values t (bias and skip operand already in) -> sixteen requantised, clamped bytes as four words
 // (Section 3.2.1).  RQ as in epilogue_vec: 1 one 32x32->64 multiply-add whose high word is the result;
-// 2 general 64-bit multiply, add, shift; 3 in 32 bits after clamping t to [0, t_hi] (see ConvArgs::rq24).
+// 2 general 64-bit multiply, add, shift; 3 in 32 bits after clamping t to [0, t_hi] (see ConvArgs::rq24); 4 likewise with the
+// high half of a 24-bit product (see ConvArgs::rqh).  (Form 4 in place of form 1 in every kernel measured slower, the nine-image
+// network 341 -> 354 us; it serves kernels that deal an epilogue out between matrix instructions, where form 1's word pairs do not fit.)
 // (P: ConvArgs, or any struct with the same requantisation fields)
 template <int RQ, class P>
 __device__ __forceinline__ v4i requant16(const P &a, const int (&t)[16])
@@ -130,6 +140,17 @@ __device__ __forceinline__ v4i requant16(const P &a, const int (&t)[16])
             const uint32_t x = __umul24(tc, (uint32_t)a.mul) + (uint32_t)a.rnd;
             if ((r & 3) == 0) w[r >> 2] = (int)(x >> a.shift);
             else shift_into_byte(w[r >> 2], x, sh_v, r & 3);
+        }
+        return v4i{w[0], w[1], w[2], w[3]};
+    }
+    if (RQ == 4) {
+        int w[4];
+        const int one_v = 1;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const uint32_t x = clamp_mul_hi_u24(t[r], a.t_hi, a.rqh) + 1u;
+            if ((r & 3) == 0) w[r >> 2] = (int)(x >> 1);
+            else shift_into_byte(w[r >> 2], x, one_v, r & 3);
         }
         return v4i{w[0], w[1], w[2], w[3]};
     }
@@ -497,7 +518,8 @@ __device__ __forceinline__ v4i epilogue_bytes16(const ConvArgs &a, const v16i &a
 // Outputs R0 .. R0 + N - 1 of epilogue_bytes16<RES, 3> (the 32-bit requantisation form, a.rq24): their bytes go into
 // the words w[R0 / 4 ..], which the caller collects over the sixteen outputs.  For callers that deal the epilogue out
 // in slices between matrix instructions.  R0 and N are multiples of... any; a word is started by its output 4 q.
-template <int RES, int R0, int N, class P>
+// FORM: 3 (a.rq24) or 4 (a.rqh), as in requant16.
+template <int RES, int R0, int N, int FORM = 3, class P>
 __device__ __forceinline__ void epilogue_rq24_slice(const P &a, const v16i &acc, const v4i &res8, int (&w)[4])
 {
     const int wd[4] = {res8.x, res8.y, res8.z, res8.w};
@@ -510,10 +532,9 @@ __device__ __forceinline__ void epilogue_rq24_slice(const P &a, const v16i &acc,
             const uint32_t b8 = ((uint32_t)wd[r >> 2] >> ((r & 3) * 8)) & 0xffu;
             t = __builtin_elementwise_add_sat(t, (int)((__umul24(b8, (uint32_t)a.res_mul) + (uint32_t)half) >> a.res_shift));
         }
-        const uint32_t tc = (uint32_t)med3_v0s(t, a.t_hi);
-        const uint32_t x = __umul24(tc, (uint32_t)a.mul) + (uint32_t)a.rnd;
-        if ((r & 3) == 0) w[r >> 2] = (int)(x >> a.shift);
-        else shift_into_byte(w[r >> 2], x, sh_v, r & 3);
+        const uint32_t x = FORM == 4 ? clamp_mul_hi_u24(t, a.t_hi, a.rqh) + 1u : __umul24((uint32_t)med3_v0s(t, a.t_hi), (uint32_t)a.mul) + (uint32_t)a.rnd;
+        if ((r & 3) == 0) w[r >> 2] = (int)(x >> (FORM == 4 ? 1 : a.shift));
+        else shift_into_byte(w[r >> 2], x, FORM == 4 ? 1 : sh_v, r & 3);
     }
 }
 // Between the last v_mfma of an accumulation and the first instruction that reads the accumulator.  The compiler's

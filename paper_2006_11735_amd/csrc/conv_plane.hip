@@ -558,6 +558,8 @@ bool conv_plane_twin_ok(const ConvArgs &a, const ConvArgs &b)
 hipError_t launch_conv_plane_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st)
 {
     if (!conv_plane_twin_ok(a, b)) return hipErrorInvalidValue;
+    // (one wave per SIMD with all its registers: conv_rows.hip)
+    if (conv_rows_twin_applies(a, b)) return launch_conv_rows_twin(a, b, st);
     if (a.KH == 5) return launch_plane<5, 64, 1, 1>(a, b, st);
     if (a.Cin == 48 && plane_pipe_ok(a) && plane_pipe_ok(b)) return launch_plane<3, 48, 1, 1, 2, true>(a, b, st);
     return a.Cin == 64 ? launch_plane<3, 64, 1, 1>(a, b, st) : launch_plane<3, 48, 1, 1>(a, b, st);

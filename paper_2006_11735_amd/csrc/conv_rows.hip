@@ -1,0 +1,276 @@
+// The two-branch layer of the restoration network on large pictures: a 5x5 layer of 64 channels and, in the same launch, the 3x3 layer
+// of the same input (at most 32 output channels each, stride 1, "same" padding, unsigned bytes by one of the 24-bit requantisation forms).
+//
+// conv_plane.hip runs it with two waves per SIMD that own two tile rows each: 51 % of the matrix cores' rate, because every
+// product needs a fresh fragment from LDS (1.34 MB per tile, 7.5 k clocks of LDS against 8.7 k of matrix work), and because the barrier
+// per tile keeps the two waves in step, so that both multiply and then both requantise.  Here a SIMD has ONE wave with all of its registers:
+//
+//   tile     16 rows x 32 columns; wave w owns rows 4 w .. 4 w + 3 (a pixel group of 32 = one tile row), for both layers: eight
+//            accumulator tiles
+//   K loop   outermost the kernel column and the channel half (ten steps), then the eight input rows under the wave's four output rows:
+//            one activation fragment of an input row is multiplied into every output row it reaches (up to five, and three of the
+//            twin), with the step's five (+ three) weight fragments in registers.  0.6 KiB of LDS per matrix instruction instead of 1.2.
+//   epilogue of the tile before, dealt out between this tile's matrix instructions (two sets of accumulators, used in turn)
+//   patch, weights, copies, tile walk: as in conv_plane.hip
+//
+// Straight-line code for a tile: 272 matrix instructions per wave, everything else in their shadow.
+// Measured on 2560 x 1600, 64 -> 32 + 16: see launch_conv_rows_twin().
+#include "conv_common.h"
+
+#include <type_traits>
+
+namespace icnn {
+
+constexpr int kRowsTW = 32, kRowsTH = 16;
+
+struct RowsArgs {
+    int tiles_x, tiles_per_img, n_tiles;
+    int per_xcd;                // tiles handed to each of the 8 XCDs
+    FastDiv div_tpi, div_tx;    // / tiles_per_img, / tiles_x
+};
+
+// Matrix instructions of a tile before product dy of fragment i (step i / 8, input row i % 8): the order of the loop below
+constexpr int rows_products_before(int i, int dy)
+{
+    int m = 0;
+    for (int f = 0; f <= i; ++f)
+        for (int d = 0; d < 5; ++d) {
+            if (f == i && d == dy) return m;
+            const int r = f % 8, dx = f / 16;
+            if (r - d >= 0 && r - d < 4) m += dx >= 1 && dx <= 3 && d >= 1 && d <= 3 ? 2 : 1;
+        }
+    return m;
+}
+constexpr int kRowsProducts = rows_products_before(80, 0);
+static_assert(kRowsProducts == 4 * (50 + 18), "products of four rows");
+
+// FORM: the requantisation form of both layers, 3 or 4 of requant16
+template <int FORM>
+__global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a, const ConvArgs b, const RowsArgs g)
+{
+#if defined(__HIP_DEVICE_COMPILE__)   // the buffer-resource type exists in the device pass only
+    constexpr unsigned OOB = 0x80000000u;            // beyond any buffer this kernel accepts (< 2 GiB)
+    constexpr int KS = 5, KSB = 3, CIN = 64, PAD = 2, RPW = 4;
+    constexpr int PH = kRowsTH + KS - 1, PW = kRowsTW + KS - 1, PPT = CIN / 16, ROWB = PW * CIN;
+    constexpr int F = KS * KS * 2, FB = KSB * KSB * 2;                   // weight fragments of 32 k-values
+    constexpr int PIECES = PH * PW * PPT, NCOPY = (PIECES + 63) / 64, CPW = (NCOPY + 3) / 4, PATCH = NCOPY * 1024;
+    constexpr int WBYTES = F * 1024, WBYTESB = FB * 1024;
+    static_assert(PW % 4 == 0, "patch rows are whole groups of four pixels");
+    static_assert(WBYTES + WBYTESB + 2 * PATCH <= 160 * 1024, "LDS");
+
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    uint8_t *const wbuf = lds;
+    uint8_t *const wbufB = lds + WBYTES;
+    uint8_t *const pbuf = lds + WBYTES + WBYTESB;
+
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.x_bytes, 0x00020000);
+
+    auto tile_of = [&](int v) { return (v & 7) * g.per_xcd + (v >> 3); };
+    auto valid = [&](int v) { return (v >> 3) < g.per_xcd && tile_of(v) < g.n_tiles; };
+    auto tile_origin = [&](int v, int &n, int &y0, int &x0) {
+        const int t = tile_of(v);
+        n = fast_div(t, g.div_tpi);
+        const int r = t - n * g.tiles_per_img;
+        const int ty = fast_div(r, g.div_tx);
+        y0 = ty * kRowsTH;
+        x0 = (r - ty * g.tiles_x) * kRowsTW;
+    };
+    // (patch layout and copies: see conv_plane.hip)
+    int p_rel[CPW], p_yx[CPW];
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+        const int q = (wave + 4 * i) * 64 + lane;
+        const int pix = q / PPT, slot = q - pix * PPT;
+        const int py = pix / PW, px = pix - py * PW;
+        p_rel[i] = (py * a.W + px) * a.in_cs + (slot ^ ((px >> 2) & 3)) * 16;
+        p_yx[i] = ((q < PIECES ? py : 0x7fff) << 16) | px;
+    }
+    auto issue_copy = [&](auto i_tag, int base, int y0, int x0, int buf) {
+        constexpr int i = decltype(i_tag)::value;
+        const int e = wave + 4 * i;
+        if (e < NCOPY) {                             // wave-uniform
+            const int iy = y0 - PAD + (p_yx[i] >> 16), ix = x0 - PAD + (p_yx[i] & 0xffff);
+            const bool ok = ((unsigned)iy < (unsigned)a.H) & ((unsigned)ix < (unsigned)a.W);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(pbuf + buf * PATCH + e * 1024), 16,
+                                                     ok ? (unsigned)(base + p_rel[i]) : OOB, 0, 0, 0);
+        }
+    };
+    auto patch_base = [&](int n, int y0, int x0) { return ((n * a.H + y0 - PAD) * a.W + x0 - PAD) * a.in_cs; };
+
+    const int v0 = blockIdx.x;
+    if (!valid(v0)) return;                          // (the whole workgroup: it has no tile at all)
+    {
+        int n, y0, x0;
+        tile_origin(v0, n, y0, x0);
+        const int base = patch_base(n, y0, x0);
+        static_for<CPW>([&](auto i_tag) { issue_copy(i_tag, base, y0, x0, 0); });
+        const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)a.wp, 0, a.wp_bytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rs_wb = __builtin_amdgcn_make_buffer_rsrc((void *)b.wp, 0, b.wp_bytes, 0x00020000);
+        for (int e = wave; e < F; e += 4)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, (__attribute__((address_space(3))) void *)(wbuf + e * 1024), 16, (unsigned)(e * 1024 + lane * 16), 0, 0, 0);
+        for (int e = wave; e < FB; e += 4)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_wb, (__attribute__((address_space(3))) void *)(wbufB + e * 1024), 16, (unsigned)(e * 1024 + lane * 16), 0, 0, 0);
+    }
+    v16i bias[1], biasB[1];
+    load_bias_rows<1>(a, 0, half, bias);
+    load_bias_rows<1>(b, 0, half, biasB);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0070);              // vmcnt(0), lgkmcnt(0): the first patch and the weights are in LDS
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    const uint8_t *const wlane = wbuf + lane * 16, *const wlaneB = wbufB + lane * 16;
+    int ex[KS][2];                                   // this lane's offset in the wave's first patch row, per kernel column and channel half
+#pragma unroll
+    for (int dx = 0; dx < KS; ++dx)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) ex[dx][k] = (RPW * wave) * ROWB + (col + dx) * 64 + (((2 * k + half) ^ (((col + dx) >> 2) & 3)) << 4);
+    const bool storeA = half * 16 < a.Cout, storeB = half * 16 < b.Cout;
+
+    struct Done {                                    // where a finished tile's outputs go
+        int pix;                                     // this lane's pixel in the wave's first row
+        int rows;                                    // rows of it inside the picture (0: this lane's column is outside)
+    };
+    // one tile: multiplies into acc / accB; the tile before (sums in old / oldB, place in was) is requantised and stored meanwhile
+    auto tile = [&](auto prev_tag, int v, int buf, v16i (&acc)[RPW], v16i (&accB)[RPW], const v16i (&old)[RPW], const v16i (&oldB)[RPW], const Done &was, Done &now) {
+        constexpr bool PREV = decltype(prev_tag)::value;
+        int n, y0, x0;
+        tile_origin(v, n, y0, x0);
+        now.pix = (n * a.H + y0 + RPW * wave) * a.W + x0 + col;
+        now.rows = x0 + col < a.W ? min(RPW, a.H - y0 - RPW * wave) : 0;
+        const bool more = valid(v + (int)gridDim.x);
+        int nn = 0, ny0 = 0, nx0 = 0;
+        if (more) tile_origin(v + (int)gridDim.x, nn, ny0, nx0);
+        const int nbase = patch_base(nn, ny0, nx0);
+        const uint8_t *const P = pbuf + buf * PATCH;
+
+        constexpr int ROWS = RPW + KS - 1;           // input rows under the wave's output rows
+        constexpr int STEPS = KS * 2;
+        constexpr int RING = 4;
+        v4i A[2][KS], AB[2][KSB], B[RING];
+        [[maybe_unused]] int wd[4] = {0, 0, 0, 0};
+        auto fetch_a = [&](auto s_tag, auto q_tag) {             // weight fragment q of step s (q >= KS: the twin's)
+            constexpr int s = decltype(s_tag)::value, q = decltype(q_tag)::value, DX = s >> 1, KK = s & 1;
+            if constexpr (q < KS) A[s & 1][q] = *(const v4i *)(wlane + ((q * KS + DX) * 2 + KK) * 1024);
+            else if constexpr (DX >= 1 && DX <= KSB) AB[s & 1][q - KS] = *(const v4i *)(wlaneB + (((q - KS) * KSB + DX - 1) * 2 + KK) * 1024);
+        };
+        auto fetch_b = [&](auto i_tag) {                         // activation fragment i = step * ROWS + input row
+            constexpr int i = decltype(i_tag)::value, s = i / ROWS, r = i % ROWS;
+            B[i % RING] = *(const v4i *)(P + ex[s >> 1][s & 1] + r * ROWB);
+        };
+        // the part of the tile before that goes behind matrix instruction m of this one
+        auto deal = [&](auto m_tag) {
+            constexpr int m = decltype(m_tag)::value;
+            if constexpr (PREV) {
+                // outputs [LO, HI): row o / 32, then 16 of the layer and 16 of its twin
+                constexpr int NOUT = RPW * 32, LO = m * NOUT / kRowsProducts, HI = (m + 1) * NOUT / kRowsProducts;
+                static_for<HI - LO>([&](auto q_tag) {
+                    constexpr int o = LO + decltype(q_tag)::value, j = o / 32, k = o % 16;
+                    constexpr bool twin = (o % 32) >= 16;
+                    epilogue_rq24_slice<0, k, 1, FORM>(twin ? b : a, twin ? oldB[j] : old[j], v4i{0, 0, 0, 0}, wd);
+                    if constexpr (k == 15) {
+                        const ConvArgs &c = twin ? b : a;
+                        if (j < was.rows && (twin ? storeB : storeA))
+                            *(v4i *)((uint8_t *)c.out + (size_t)(was.pix + j * a.W) * c.out_cs + c.out_co + half * 16) = v4i{wd[0], wd[1], wd[2], wd[3]};
+                    }
+                });
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        static_for<KS + KSB>([&](auto q_tag) { fetch_a(std::integral_constant<int, 0>{}, q_tag); });
+        static_for<RING - 1>([&](auto i_tag) { fetch_b(i_tag); });
+        static_for<STEPS * ROWS>([&](auto i_tag) {
+            constexpr int i = decltype(i_tag)::value, s = i / ROWS, r = i % ROWS, DX = s >> 1;
+            if constexpr (i + RING - 1 < STEPS * ROWS) fetch_b(std::integral_constant<int, i + RING - 1>{});
+            if constexpr (s + 1 < STEPS && r < KS + KSB) fetch_a(std::integral_constant<int, s + 1>{}, std::integral_constant<int, r>{});
+            constexpr int EVERY = STEPS * ROWS / CPW;            // a copy of the next patch every so many fragments
+            if constexpr (i % EVERY == 0 && i / EVERY < CPW) {
+                if (more) issue_copy(std::integral_constant<int, i / EVERY>{}, nbase, ny0, nx0, buf ^ 1);
+            }
+            // this fragment's products, each followed by its share of the tile before: outputs are dealt out evenly over the matrix
+            // instructions (between two of them there is room for seven vector instructions)
+            static_for<KS>([&](auto dy_tag) {
+                constexpr int dy = decltype(dy_tag)::value, j = r - dy;
+                if constexpr (j >= 0 && j < RPW) {
+                    constexpr bool TWIN = DX >= 1 && DX <= KSB && dy >= 1 && dy <= KSB;
+                    constexpr int m = rows_products_before(i, dy);
+                    if constexpr (s == 0 && dy == 0) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[0][0], B[i % RING], bias[0], 0, 0, 0);
+                    else acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(A[s & 1][dy], B[i % RING], acc[j], 0, 0, 0);
+                    deal(std::integral_constant<int, m>{});
+                    if constexpr (TWIN) {
+                        if constexpr (s == 2 && dy == 1) accB[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(AB[0][0], B[i % RING], biasB[0], 0, 0, 0);
+                        else accB[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(AB[s & 1][dy - 1], B[i % RING], accB[j], 0, 0, 0);
+                        deal(std::integral_constant<int, m + 1>{});
+                    }
+                }
+            });
+        });
+        mfma_drain(acc);
+        mfma_drain(accB);
+        asm volatile("" ::: "memory");
+        ICNN_WAIT_VMCNT(0);                          // the next tile's patch has landed (this wave's copies of it)
+        __builtin_amdgcn_s_waitcnt(0xC07F);          // and this wave has read the last of this tile's patch
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    auto finish = [&](const v16i (&acc)[RPW], const v16i (&accB)[RPW], const Done &was) {
+        static_for<RPW>([&](auto j_tag) {
+            constexpr int j = decltype(j_tag)::value;
+            if (j >= was.rows) return;
+            const size_t p = (size_t)(was.pix + j * a.W);
+            if (storeA) *(v4i *)((uint8_t *)a.out + p * a.out_cs + a.out_co + half * 16) = epilogue_bytes16<0, FORM>(a, acc[j], v4i{0, 0, 0, 0});
+            if (storeB) *(v4i *)((uint8_t *)b.out + p * b.out_cs + b.out_co + half * 16) = epilogue_bytes16<0, FORM>(b, accB[j], v4i{0, 0, 0, 0});
+        });
+    };
+
+    v16i acc0[RPW], acc1[RPW], accB0[RPW], accB1[RPW];
+#pragma unroll
+    for (int j = 0; j < RPW; ++j) { acc0[j] = acc1[j] = bias[0]; accB0[j] = accB1[j] = biasB[0]; }
+    Done d0 = {0, 0}, d1 = {0, 0};
+    int v = v0;
+    tile(std::false_type{}, v, 0, acc0, accB0, acc1, accB1, d1, d0);
+    for (;;) {
+        v += gridDim.x;
+        if (!valid(v)) { finish(acc0, accB0, d0); break; }
+        tile(std::true_type{}, v, 1, acc1, accB1, acc0, accB0, d0, d1);
+        v += gridDim.x;
+        if (!valid(v)) { finish(acc1, accB1, d1); break; }
+        tile(std::true_type{}, v, 0, acc0, accB0, acc1, accB1, d1, d0);
+    }
+#endif
+}
+
+// ------------------------------------------------------------------ dispatch
+// what the kernel assumes of a layer beyond its shape (conv_plane_twin_ok)
+static bool rows_layer_ok(const ConvArgs &a)
+{
+    return a.epi_vec && a.out_mode <= 1 && a.res_mode == 0 && (a.Cout & 15) == 0 && a.Cout <= 32;
+}
+bool conv_rows_twin_applies(const ConvArgs &a, const ConvArgs &b)
+{
+    return a.KH == 5 && a.Cin == 64 && rows_layer_ok(a) && rows_layer_ok(b) && ((a.rqh && b.rqh) || (a.rq24 && b.rq24)) && !g_tuning.plane_no_pipe;
+}
+
+hipError_t launch_conv_rows_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st)
+{
+    RowsArgs g;
+    g.tiles_x = (a.W + kRowsTW - 1) / kRowsTW;
+    g.tiles_per_img = g.tiles_x * ((a.H + kRowsTH - 1) / kRowsTH);
+    const long long tiles = (long long)g.tiles_per_img * a.N;
+    if (tiles < 1 || tiles > 0x7ffffff0LL / 8) return hipErrorInvalidValue;
+    g.n_tiles = (int)tiles;
+    g.per_xcd = (int)((tiles + 7) / 8);
+    g.div_tpi = make_fast_div((unsigned)g.tiles_per_img);
+    g.div_tx = make_fast_div((unsigned)g.tiles_x);
+    constexpr int NCOPY = ((kRowsTH + 4) * (kRowsTW + 4) * 4 + 63) / 64;
+    constexpr size_t lds_bytes = (50 + 18) * 1024 + 2 * (size_t)NCOPY * 1024;
+    const auto kernel = a.rqh && b.rqh ? conv_rows_twin_kernel<4> : conv_rows_twin_kernel<3>;
+    const hipError_t e = allow_large_lds((const void *)kernel);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * g.per_xcd < 256 ? 8 * g.per_xcd : 256)), dim3(256), lds_bytes, st, a, b, g);
+    return hipGetLastError();
+}
+
+}  // namespace icnn

@@ -62,6 +62,9 @@ struct ConvArgs {
     // hi) leaves the result unchanged, and then t * mul + 2^(shift-1) fits 32 bits unsigned with both factors
     // below 2^24, so one full-rate multiply-add and a shift finish it and no clamp of the result is needed
     int rq24, t_hi, rnd;
+    // the same with the high half of a 24-bit product, for shifts whose product does not fit 32 bits: with rqh = mul << (33 - shift) < 2^24
+    // (and t limited to t_hi < 2^24) the result is (high 32 bits of t * rqh, plus 1) >> 1.  0: does not apply.
+    int rqh;
     int res_fast; // unsigned 8-bit skip operand whose rescale fits 32 bits
     int epi_vec;  // output (and skip operand) allow 16-byte accesses
     int epi_mode; // 4 * RES + RQ of the vector epilogue
@@ -128,7 +131,7 @@ struct ChainLayer {
     const uint8_t *wp;
     const int32_t *bias, *wsum;
     uint32_t xin;                 // 0x80808080: the layer's inputs go up to 255 (ConvArgs::frag_xor)
-    int mul, shift, lo, hi, rq_fast, mul_hi, rq24, t_hi, rnd;   // as in ConvArgs
+    int mul, shift, lo, hi, rq_fast, mul_hi, rq24, t_hi, rnd, rqh;   // as in ConvArgs
 };
 struct ChainArgs {
     const uint8_t *x;
@@ -214,6 +217,8 @@ bool conv_lat_dual_applies(const ConvArgs &a, const ProjArgs &q);
 hipError_t launch_conv_lat_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st);
 bool conv_halo_applies(const ConvArgs &a);
 hipError_t launch_conv_halo(const ConvArgs &a, hipStream_t st);
+bool conv_rows_twin_applies(const ConvArgs &a, const ConvArgs &b);
+hipError_t launch_conv_rows_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st);
 bool conv_plane_applies(const ConvArgs &a);
 hipError_t launch_conv_plane(const ConvArgs &a, hipStream_t st);
 bool conv_plane_twin_ok(const ConvArgs &a, const ConvArgs &b);

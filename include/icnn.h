@@ -393,6 +393,19 @@ typedef struct {
 int icnn_run_calls(int32_t n, const icnn_call *calls, void *stream);
 
 /*
+ * Several independent lists of calls (the parts of a batch) side by side: list 0 on `stream`, every other list on a stream of its own
+ * that `lanes` holds, issued in turn, one call of each.  Ordered like one call on `stream`: the lists start after what the stream held
+ * before, and what follows on the stream waits for all of them (also while the stream is being captured into a graph).  On an error
+ * nothing more is issued, the stream still waits for what was, and the error is returned.
+ *
+ * icnn_lanes_create makes the streams (default priority) and events for up to `lists` lists on the current device; they serve one
+ * icnn_run_lanes at a time.  icnn_lanes_destroy gives them back; work issued on them is completed all the same.
+ */
+int icnn_lanes_create(int32_t lists, void **lanes);
+void icnn_lanes_destroy(void *lanes);
+int icnn_run_lanes(void *lanes, int32_t lists, const int32_t *n, const icnn_call *const *calls, void *stream);
+
+/*
  * Rescaled feature-map addition (ratio synchronisation between feature maps,
  * Sections 3.4.2 and 4.1), as a stand-alone pass over memory:
  *   T   = sat32(a + [b * b_mul / 2^b_shift])

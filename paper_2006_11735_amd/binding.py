@@ -86,6 +86,9 @@ _descp = C.POINTER(icnn_conv_desc)
 _lib.iconv2d_chain_brelu.argtypes = [_i32, C.POINTER(_descp), _vp, C.POINTER(_vp), C.POINTER(_vp), _vp, _vp]
 _lib.iconv2d_chain_split.argtypes = [_i32, C.POINTER(_descp), C.POINTER(_i32), C.POINTER(_i32)]
 _lib.icnn_run_calls.argtypes = [_i32, C.POINTER(icnn_call), _vp]
+_lib.icnn_lanes_create.argtypes = [_i32, C.POINTER(_vp)]
+_lib.icnn_lanes_destroy.argtypes, _lib.icnn_lanes_destroy.restype = [_vp], None
+_lib.icnn_run_lanes.argtypes = [_vp, _i32, C.POINTER(_i32), C.POINTER(C.POINTER(icnn_call)), _vp]
 _lib.iadd_rescale.argtypes = [C.POINTER(icnn_add_desc), _vp, _vp, _vp, _vp]
 _lib.iconcat.argtypes = [_i32, C.POINTER(_vp), C.POINTER(_i32), C.POINTER(_i32), C.POINTER(_i32),
                          C.POINTER(_i32), _i32, _i64, _vp, _i32, _vp]
@@ -98,7 +101,7 @@ _lib.icnn_peak_copy.argtypes = [_vp, _vp, C.c_size_t, _vp]
 EXPORTS = ["icnn_version", "icnn_last_error", "icnn_set_tuning", "iconv2d_validate", "iconv2d_out_hw",
            "iconv2d_workspace_bytes", "iconv2d_packed_weight_bytes", "iconv2d_prepack_weights",
            "iconv2d_brelu", "iconv2d_brelu_static_ws", "iconv2d_packed_channel_params_bytes", "iconv2d_prepack_channel_params", "iconv2d_brelu_pc",
-           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_twin_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "icnn_run_calls", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
+           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_twin_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "icnn_run_calls", "icnn_lanes_create", "icnn_lanes_destroy", "icnn_run_lanes", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
            "irenormalize_u8", "icnn_peak_mfma_i8", "icnn_peak_copy"]
 
 
@@ -329,6 +332,27 @@ class Calls:
 
     def run(self, stream=None):
         return _check(_lib.icnn_run_calls(self.n, self._arr, _stream(stream)))
+
+
+class Lanes:
+    """Several Calls lists side by side (icnn_run_lanes): the first on the caller's stream, the others on streams of their own; ordered
+    like one call on the caller's stream.  Made on the current device."""
+
+    def __init__(self, lists):
+        self._lists = list(lists)
+        n = len(self._lists)
+        self._n = (_i32 * n)(*[c.n for c in self._lists])
+        self._arr = (C.POINTER(icnn_call) * n)(*[C.cast(c._arr, C.POINTER(icnn_call)) for c in self._lists])
+        h = _vp()
+        _check(_lib.icnn_lanes_create(n, C.byref(h)))
+        self._handle = h
+
+    def run(self, stream=None):
+        return _check(_lib.icnn_run_lanes(self._handle, len(self._lists), self._n, self._arr, _stream(stream)))
+
+    def __del__(self):
+        if getattr(self, "_handle", None):
+            _lib.icnn_lanes_destroy(self._handle)
 
 
 def iadd_rescale(desc, a, b, out, stream=None):

@@ -6,6 +6,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
+#include <vector>
 
 using namespace icnn;
 
@@ -951,43 +952,115 @@ int irenormalize_u8(int64_t count, const void *x, void *out, void *stream)
                     "irenormalize_u8");
 }
 
+static int run_call(int32_t k, const icnn_call &c, void *stream)
+{
+    const void *const *p = c.p;
+    const icnn_conv_desc *const *d = c.d;
+    const int32_t *i = c.i;
+    auto b = [&](int q) { return (const int32_t *)p[q]; };
+    auto o = [&](int q) { return const_cast<void *>(p[q]); };
+    int rc;
+    switch (c.kind) {
+    case ICNN_CALL_CONV: rc = iconv2d_brelu(d[0], p[0], p[1], b(2), p[3], o(4), o(5), stream); break;
+    case ICNN_CALL_CONV_PC: rc = iconv2d_brelu_pc(d[0], p[0], p[1], b(2), p[3], p[4], o(5), o(6), stream); break;
+    case ICNN_CALL_DUAL: rc = iconv2d_dual_brelu(d[0], p[0], p[1], b(2), d[1], p[3], p[4], b(5), o(6), stream); break;
+    case ICNN_CALL_DUAL_PC: rc = iconv2d_dual_brelu_pc(d[0], p[0], p[1], b(2), p[3], d[1], p[4], p[5], b(6), o(7), stream); break;
+    case ICNN_CALL_CONV_MAXPOOL: rc = iconv2d_maxpool_brelu(d[0], i[0], i[1], i[2], p[0], p[1], b(2), o(3), stream); break;
+    case ICNN_CALL_BOTTLENECK:
+        rc = iconv2d_bottleneck_brelu(d[0], p[0], p[1], b(2), d[1], p[3], b(4), d[2], p[5], b(6), p[7], o(8), stream);
+        break;
+    case ICNN_CALL_BOTTLENECK_DUAL:
+        rc = iconv2d_bottleneck_dual_brelu(d[0], p[0], p[1], b(2), d[1], p[3], b(4), d[2], p[5], b(6), d[3], p[7], b(8), o(9), stream);
+        break;
+    case ICNN_CALL_PAIR: rc = iconv2d_pair_brelu(d[0], p[0], p[1], b(2), p[3], o(4), d[1], p[5], b(6), o(7), stream); break;
+    case ICNN_CALL_TWIN: rc = iconv2d_twin_brelu(d[0], p[0], p[1], b(2), o(3), d[1], p[4], b(5), o(6), stream); break;
+    case ICNN_CALL_CHAIN:
+        rc = iconv2d_chain_brelu(i[0], (const icnn_conv_desc *const *)c.list[0], p[0], (const void *const *)c.list[1],
+                                 (const int32_t *const *)c.list[2], o(1), stream);
+        break;
+    case ICNN_CALL_MAXPOOL: rc = imaxpool2d_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
+    case ICNN_CALL_AVGPOOL: rc = iavgpool_global_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
+    default: rc = fail(ICNN_E_PARAM, "call %d: unknown kind %d", k, c.kind);
+    }
+    return rc;
+}
+
 int icnn_run_calls(int32_t n, const icnn_call *calls, void *stream)
 {
     if (n < 0) return fail(ICNN_E_SHAPE, "n must be >= 0");
     if (n && !calls) return fail(ICNN_E_NULL, "calls is NULL");
     for (int32_t k = 0; k < n; ++k) {
-        const icnn_call &c = calls[k];
-        const void *const *p = c.p;
-        const icnn_conv_desc *const *d = c.d;
-        const int32_t *i = c.i;
-        auto b = [&](int q) { return (const int32_t *)p[q]; };
-        auto o = [&](int q) { return const_cast<void *>(p[q]); };
-        int rc;
-        switch (c.kind) {
-        case ICNN_CALL_CONV: rc = iconv2d_brelu(d[0], p[0], p[1], b(2), p[3], o(4), o(5), stream); break;
-        case ICNN_CALL_CONV_PC: rc = iconv2d_brelu_pc(d[0], p[0], p[1], b(2), p[3], p[4], o(5), o(6), stream); break;
-        case ICNN_CALL_DUAL: rc = iconv2d_dual_brelu(d[0], p[0], p[1], b(2), d[1], p[3], p[4], b(5), o(6), stream); break;
-        case ICNN_CALL_DUAL_PC: rc = iconv2d_dual_brelu_pc(d[0], p[0], p[1], b(2), p[3], d[1], p[4], p[5], b(6), o(7), stream); break;
-        case ICNN_CALL_CONV_MAXPOOL: rc = iconv2d_maxpool_brelu(d[0], i[0], i[1], i[2], p[0], p[1], b(2), o(3), stream); break;
-        case ICNN_CALL_BOTTLENECK:
-            rc = iconv2d_bottleneck_brelu(d[0], p[0], p[1], b(2), d[1], p[3], b(4), d[2], p[5], b(6), p[7], o(8), stream);
-            break;
-        case ICNN_CALL_BOTTLENECK_DUAL:
-            rc = iconv2d_bottleneck_dual_brelu(d[0], p[0], p[1], b(2), d[1], p[3], b(4), d[2], p[5], b(6), d[3], p[7], b(8), o(9), stream);
-            break;
-        case ICNN_CALL_PAIR: rc = iconv2d_pair_brelu(d[0], p[0], p[1], b(2), p[3], o(4), d[1], p[5], b(6), o(7), stream); break;
-        case ICNN_CALL_TWIN: rc = iconv2d_twin_brelu(d[0], p[0], p[1], b(2), o(3), d[1], p[4], b(5), o(6), stream); break;
-        case ICNN_CALL_CHAIN:
-            rc = iconv2d_chain_brelu(i[0], (const icnn_conv_desc *const *)c.list[0], p[0], (const void *const *)c.list[1],
-                                     (const int32_t *const *)c.list[2], o(1), stream);
-            break;
-        case ICNN_CALL_MAXPOOL: rc = imaxpool2d_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
-        case ICNN_CALL_AVGPOOL: rc = iavgpool_global_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
-        default: rc = fail(ICNN_E_PARAM, "call %d: unknown kind %d", k, c.kind);
-        }
+        const int rc = run_call(k, calls[k], stream);
         if (rc) return rc;
     }
     return ICNN_OK;
+}
+
+namespace {
+struct Lanes {
+    std::vector<hipStream_t> streams;       // of lists 1, 2, ...
+    std::vector<hipEvent_t> done;           // a list's last call
+    hipEvent_t start = nullptr;
+};
+}  // namespace
+
+void icnn_lanes_destroy(void *lanes)
+{
+    Lanes *const l = (Lanes *)lanes;
+    if (!l) return;
+    for (hipEvent_t e : l->done) (void)hipEventDestroy(e);
+    for (hipStream_t s : l->streams) (void)hipStreamDestroy(s);
+    if (l->start) (void)hipEventDestroy(l->start);
+    delete l;
+}
+
+int icnn_lanes_create(int32_t lists, void **lanes)
+{
+    if (lists < 1 || lists > 16) return fail(ICNN_E_SHAPE, "lists must be in [1, 16]");
+    if (!lanes) return fail(ICNN_E_NULL, "lanes is NULL");
+    Lanes *const l = new Lanes;
+    hipError_t e = hipEventCreateWithFlags(&l->start, hipEventDisableTiming);
+    for (int32_t k = 1; k < lists && e == hipSuccess; ++k) {
+        hipStream_t s;
+        e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+        if (e != hipSuccess) break;
+        l->streams.push_back(s);
+        hipEvent_t d;
+        e = hipEventCreateWithFlags(&d, hipEventDisableTiming);
+        if (e == hipSuccess) l->done.push_back(d);
+    }
+    if (e != hipSuccess) {
+        icnn_lanes_destroy(l);
+        return launched(e, "icnn_lanes_create");
+    }
+    *lanes = l;
+    return ICNN_OK;
+}
+
+int icnn_run_lanes(void *lanes, int32_t lists, const int32_t *n, const icnn_call *const *calls, void *stream)
+{
+    Lanes *const l = (Lanes *)lanes;
+    if (!l || !n || !calls) return fail(ICNN_E_NULL, "lanes, n and calls must not be NULL");
+    if (lists < 1 || lists > (int32_t)l->streams.size() + 1) return fail(ICNN_E_SHAPE, "%d lists: the lanes hold %d", lists, (int)l->streams.size() + 1);
+    int32_t most = 0;
+    for (int32_t q = 0; q < lists; ++q) {
+        if (n[q] < 0) return fail(ICNN_E_SHAPE, "n must be >= 0");
+        if (n[q] && !calls[q]) return fail(ICNN_E_NULL, "calls[%d] is NULL", q);
+        most = n[q] > most ? n[q] : most;
+    }
+    hipError_t e = hipEventRecord(l->start, (hipStream_t)stream);
+    for (int32_t q = 1; q < lists && e == hipSuccess; ++q) e = hipStreamWaitEvent(l->streams[q - 1], l->start, 0);
+    if (e != hipSuccess) return launched(e, "icnn_run_lanes");
+    int rc = ICNN_OK;
+    for (int32_t k = 0; k < most && !rc; ++k)
+        for (int32_t q = 0; q < lists && !rc; ++q)
+            if (k < n[q]) rc = run_call(k, calls[q][k], q ? (void *)l->streams[q - 1] : stream);
+    for (int32_t q = 1; q < lists; ++q) {
+        e = hipEventRecord(l->done[q - 1], l->streams[q - 1]);
+        if (e == hipSuccess) e = hipStreamWaitEvent((hipStream_t)stream, l->done[q - 1], 0);
+        if (e != hipSuccess && !rc) rc = launched(e, "icnn_run_lanes");
+    }
+    return rc;
 }
 
 int icnn_peak_mfma_i8(int32_t blocks, int32_t iters, void *sink, void *stream)

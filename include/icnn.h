@@ -280,6 +280,9 @@ int iconv2d_dual_brelu_pc(const icnn_conv_desc *main_desc, const void *x_main,
  */
 int iconv2d_maxpool_brelu(const icnn_conv_desc *desc, int32_t pool_k, int32_t pool_stride, int32_t pool_pad,
                           const void *x, const void *w_packed, const int32_t *bias, void *y, void *stream);
+/* ... with requantisation per output channel, as iconv2d_brelu_pc */
+int iconv2d_maxpool_brelu_pc(const icnn_conv_desc *desc, int32_t pool_k, int32_t pool_stride, int32_t pool_pad,
+                             const void *x, const void *w_packed, const int32_t *bias, const void *pc_packed, void *y, void *stream);
 
 /*
  * A whole identity bottleneck block of a residual network as one launch (Section 4.1: the block's layers with the
@@ -300,6 +303,12 @@ int iconv2d_bottleneck_brelu(const icnn_conv_desc *c1, const void *x, const void
                              const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2,
                              const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *res,
                              void *y, void *stream);
+/* ... with every layer's requantisation and skip rescale per output channel, as three iconv2d_brelu_pc calls.  Shapes it takes of those
+ * above: c1->cout = 64; c1->cin = c3->cout in {64, 128, 256}; c3 stores 8 bits; res = x (unsigned, joined before requantisation) or none. */
+int iconv2d_bottleneck_brelu_pc(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1, const void *pc1_packed,
+                                const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2, const void *pc2_packed,
+                                const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3_packed,
+                                const void *res, void *y, void *stream);
 
 /*
  * The bottleneck block that opens a stage, projection skip included, as one launch (Section 4.1, the skip connection
@@ -317,6 +326,11 @@ int iconv2d_bottleneck_dual_brelu(const icnn_conv_desc *c1, const void *x, const
                                   const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2,
                                   const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3,
                                   const icnn_conv_desc *cp, const void *wp_packed, const int32_t *biasp, void *y, void *stream);
+/* ... per output channel: c3 and cp as for iconv2d_dual_brelu_pc (c3's own res_mul / res_shift bound the per-channel ratios) */
+int iconv2d_bottleneck_dual_brelu_pc(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1, const void *pc1_packed,
+                                     const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2, const void *pc2_packed,
+                                     const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3_packed,
+                                     const icnn_conv_desc *cp, const void *wp_packed, const int32_t *biasp, void *y, void *stream);
 
 /*
  * Two pointwise layers as one launch: the 1x1 convolution that closes a residual block, skip operand merged in its
@@ -335,6 +349,10 @@ int iconv2d_bottleneck_dual_brelu(const icnn_conv_desc *c1, const void *x, const
 int iconv2d_pair_brelu(const icnn_conv_desc *c3, const void *t, const void *w3_packed, const int32_t *bias3, const void *res,
                        void *y, const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, void *z,
                        void *stream);
+/* ... per output channel, as two iconv2d_brelu_pc calls (an unsigned 8-bit skip operand may have any rescale; c3->cout up to 1024 fits) */
+int iconv2d_pair_brelu_pc(const icnn_conv_desc *c3, const void *t, const void *w3_packed, const int32_t *bias3, const void *pc3_packed,
+                          const void *res, void *y, const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1,
+                          const void *pc1_packed, void *z, void *stream);
 
 /*
  * Two branches of one input as one launch: the layers of different kernel sizes whose outputs are concatenated
@@ -381,13 +399,14 @@ int iconv2d_chain_split(int32_t n_layers, const icnn_conv_desc *const *descs, in
  */
 typedef enum {
     ICNN_CALL_CONV = 0, ICNN_CALL_CONV_PC = 1, ICNN_CALL_DUAL = 2, ICNN_CALL_DUAL_PC = 3, ICNN_CALL_CONV_MAXPOOL = 4, ICNN_CALL_BOTTLENECK = 5,
-    ICNN_CALL_BOTTLENECK_DUAL = 6, ICNN_CALL_PAIR = 7, ICNN_CALL_TWIN = 8, ICNN_CALL_CHAIN = 9, ICNN_CALL_MAXPOOL = 10, ICNN_CALL_AVGPOOL = 11
+    ICNN_CALL_BOTTLENECK_DUAL = 6, ICNN_CALL_PAIR = 7, ICNN_CALL_TWIN = 8, ICNN_CALL_CHAIN = 9, ICNN_CALL_MAXPOOL = 10, ICNN_CALL_AVGPOOL = 11,
+    ICNN_CALL_CONV_MAXPOOL_PC = 12, ICNN_CALL_BOTTLENECK_PC = 13, ICNN_CALL_BOTTLENECK_DUAL_PC = 14, ICNN_CALL_PAIR_PC = 15
 } icnn_call_kind;
 typedef struct {
     int32_t kind;                  /* icnn_call_kind */
     int32_t i[7];
     const icnn_conv_desc *d[4];
-    const void *p[12];
+    const void *p[13];
     const void *list[3];
 } icnn_call;
 int icnn_run_calls(int32_t n, const icnn_call *calls, void *stream);

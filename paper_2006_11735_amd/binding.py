@@ -38,12 +38,13 @@ class icnn_channel_params(C.Structure):
 
 
 class icnn_call(C.Structure):
-    _fields_ = [("kind", C.c_int32), ("i", C.c_int32 * 7), ("d", C.POINTER(icnn_conv_desc) * 4), ("p", C.c_void_p * 12),
+    _fields_ = [("kind", C.c_int32), ("i", C.c_int32 * 7), ("d", C.POINTER(icnn_conv_desc) * 4), ("p", C.c_void_p * 13),
                 ("list", C.c_void_p * 3)]
 
 
 (ICNN_CALL_CONV, ICNN_CALL_CONV_PC, ICNN_CALL_DUAL, ICNN_CALL_DUAL_PC, ICNN_CALL_CONV_MAXPOOL, ICNN_CALL_BOTTLENECK, ICNN_CALL_BOTTLENECK_DUAL,
- ICNN_CALL_PAIR, ICNN_CALL_TWIN, ICNN_CALL_CHAIN, ICNN_CALL_MAXPOOL, ICNN_CALL_AVGPOOL) = range(12)
+ ICNN_CALL_PAIR, ICNN_CALL_TWIN, ICNN_CALL_CHAIN, ICNN_CALL_MAXPOOL, ICNN_CALL_AVGPOOL, ICNN_CALL_CONV_MAXPOOL_PC, ICNN_CALL_BOTTLENECK_PC,
+ ICNN_CALL_BOTTLENECK_DUAL_PC, ICNN_CALL_PAIR_PC) = range(16)
 
 
 class IcnnError(RuntimeError):
@@ -83,6 +84,10 @@ _lib.iconv2d_bottleneck_dual_brelu.argtypes = [C.POINTER(icnn_conv_desc), _vp, _
 _lib.iconv2d_pair_brelu.argtypes = [C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _vp, _vp, C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _vp]
 _lib.iconv2d_twin_brelu.argtypes = [C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _vp, C.POINTER(icnn_conv_desc), _vp, _vp, _vp, _vp]
 _descp = C.POINTER(icnn_conv_desc)
+_lib.iconv2d_maxpool_brelu_pc.argtypes = [_descp, _i32, _i32, _i32, _vp, _vp, _vp, _vp, _vp, _vp]
+_lib.iconv2d_bottleneck_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp] + [_descp, _vp, _vp, _vp] * 2 + [_vp, _vp, _vp]
+_lib.iconv2d_bottleneck_dual_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp] + [_descp, _vp, _vp, _vp] * 2 + [_descp, _vp, _vp, _vp, _vp]
+_lib.iconv2d_pair_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp, _vp, _vp, _descp, _vp, _vp, _vp, _vp, _vp]
 _lib.iconv2d_chain_brelu.argtypes = [_i32, C.POINTER(_descp), _vp, C.POINTER(_vp), C.POINTER(_vp), _vp, _vp]
 _lib.iconv2d_chain_split.argtypes = [_i32, C.POINTER(_descp), C.POINTER(_i32), C.POINTER(_i32)]
 _lib.icnn_run_calls.argtypes = [_i32, C.POINTER(icnn_call), _vp]
@@ -101,7 +106,7 @@ _lib.icnn_peak_copy.argtypes = [_vp, _vp, C.c_size_t, _vp]
 EXPORTS = ["icnn_version", "icnn_last_error", "icnn_set_tuning", "iconv2d_validate", "iconv2d_out_hw",
            "iconv2d_workspace_bytes", "iconv2d_packed_weight_bytes", "iconv2d_prepack_weights",
            "iconv2d_brelu", "iconv2d_brelu_static_ws", "iconv2d_packed_channel_params_bytes", "iconv2d_prepack_channel_params", "iconv2d_brelu_pc",
-           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_twin_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "icnn_run_calls", "icnn_lanes_create", "icnn_lanes_destroy", "icnn_run_lanes", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
+           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_maxpool_brelu_pc", "iconv2d_bottleneck_brelu_pc", "iconv2d_bottleneck_dual_brelu_pc", "iconv2d_pair_brelu_pc", "iconv2d_twin_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "icnn_run_calls", "icnn_lanes_create", "icnn_lanes_destroy", "icnn_run_lanes", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
            "irenormalize_u8", "icnn_peak_mfma_i8", "icnn_peak_copy"]
 
 
@@ -265,6 +270,29 @@ def iconv2d_pair_brelu(c3, t, w3_packed, bias3, res, y, c1, w1_packed, bias1, z,
                                           _ptr(w1_packed), _ptr(bias1), _ptr(z), _stream(stream)))
 
 
+def iconv2d_maxpool_brelu_pc(desc, pool_k, pool_stride, pool_pad, x, w_packed, bias, pc, y, stream=None):
+    return _check(_lib.iconv2d_maxpool_brelu_pc(C.byref(desc), pool_k, pool_stride, pool_pad, _ptr(x), _ptr(w_packed), _ptr(bias), _ptr(pc),
+                                                _ptr(y), _stream(stream)))
+
+
+def iconv2d_bottleneck_brelu_pc(c1, x, w1_packed, bias1, pc1, c2, w2_packed, bias2, pc2, c3, w3_packed, bias3, pc3, res, y, stream=None):
+    return _check(_lib.iconv2d_bottleneck_brelu_pc(C.byref(c1), _ptr(x), _ptr(w1_packed), _ptr(bias1), _ptr(pc1), C.byref(c2),
+                                                   _ptr(w2_packed), _ptr(bias2), _ptr(pc2), C.byref(c3), _ptr(w3_packed), _ptr(bias3),
+                                                   _ptr(pc3), _ptr(res), _ptr(y), _stream(stream)))
+
+
+def iconv2d_bottleneck_dual_brelu_pc(c1, x, w1_packed, bias1, pc1, c2, w2_packed, bias2, pc2, c3, w3_packed, bias3, pc3, cp, wp_packed, biasp, y,
+                                     stream=None):
+    return _check(_lib.iconv2d_bottleneck_dual_brelu_pc(C.byref(c1), _ptr(x), _ptr(w1_packed), _ptr(bias1), _ptr(pc1), C.byref(c2),
+                                                        _ptr(w2_packed), _ptr(bias2), _ptr(pc2), C.byref(c3), _ptr(w3_packed), _ptr(bias3),
+                                                        _ptr(pc3), C.byref(cp), _ptr(wp_packed), _ptr(biasp), _ptr(y), _stream(stream)))
+
+
+def iconv2d_pair_brelu_pc(c3, t, w3_packed, bias3, pc3, res, y, c1, w1_packed, bias1, pc1, z, stream=None):
+    return _check(_lib.iconv2d_pair_brelu_pc(C.byref(c3), _ptr(t), _ptr(w3_packed), _ptr(bias3), _ptr(pc3), _ptr(res), _ptr(y), C.byref(c1),
+                                             _ptr(w1_packed), _ptr(bias1), _ptr(pc1), _ptr(z), _stream(stream)))
+
+
 def iconv2d_twin_brelu(ca, x, wa_packed, bias_a, ya, cb, wb_packed, bias_b, yb, stream=None):
     return _check(_lib.iconv2d_twin_brelu(C.byref(ca), _ptr(x), _ptr(wa_packed), _ptr(bias_a), _ptr(ya), C.byref(cb),
                                           _ptr(wb_packed), _ptr(bias_b), _ptr(yb), _stream(stream)))
@@ -313,6 +341,8 @@ class Calls:
         c.kind, ints = {"conv": (ICNN_CALL_CONV, 0), "conv_pc": (ICNN_CALL_CONV_PC, 0), "dual": (ICNN_CALL_DUAL, 0),
                         "dual_pc": (ICNN_CALL_DUAL_PC, 0), "convpool": (ICNN_CALL_CONV_MAXPOOL, 3), "block": (ICNN_CALL_BOTTLENECK, 0),
                         "projblock": (ICNN_CALL_BOTTLENECK_DUAL, 0), "pair": (ICNN_CALL_PAIR, 0), "twin": (ICNN_CALL_TWIN, 0),
+                        "convpool_pc": (ICNN_CALL_CONV_MAXPOOL_PC, 3), "block_pc": (ICNN_CALL_BOTTLENECK_PC, 0),
+                        "projblock_pc": (ICNN_CALL_BOTTLENECK_DUAL_PC, 0), "pair_pc": (ICNN_CALL_PAIR_PC, 0),
                         "maxpool": (ICNN_CALL_MAXPOOL, 7), "avgpool": (ICNN_CALL_AVGPOOL, 7)}[kind]
         args = list(args)
         if ints:

@@ -542,8 +542,16 @@ int iconv2d_dual_brelu_pc(const icnn_conv_desc *m, const void *x_main, const voi
                       "iconv2d_dual_brelu_pc");
 }
 
-int iconv2d_maxpool_brelu(const icnn_conv_desc *d, int32_t pool_k, int32_t pool_stride, int32_t pool_pad, const void *x,
-                          const void *w_packed, const int32_t *bias, void *y, void *stream)
+// The packed per-channel parameters of a fused launch's layer (null: one pair per layer)
+static int take_pc(ConvArgs &a, const void *pc)
+{
+    if (pc && !aligned16(pc)) return fail(ICNN_E_ALIGN, "packed channel parameters must be 16-byte aligned");
+    a.pc = (const int32_t *)pc;
+    return ICNN_OK;
+}
+
+static int maxpool_layer(const icnn_conv_desc *d, int32_t pool_k, int32_t pool_stride, int32_t pool_pad, const void *x,
+                         const void *w_packed, const int32_t *bias, const void *pc, void *y, void *stream, const char *what)
 {
     ConvGeom g;
     int rc = check_conv(d, &g);
@@ -561,18 +569,32 @@ int iconv2d_maxpool_brelu(const icnn_conv_desc *d, int32_t pool_k, int32_t pool_
         return fail(ICNN_E_UNSUPPORTED, "fused first layer needs a lower clamp of 0 (the pool's padding is zero)");
     ConvArgs a;
     if ((rc = fill_conv_args(d, g, x, w_packed, bias, nullptr, y, a))) return rc;
+    if ((rc = take_pc(a, pc))) return rc;
     if (!a.vec_out || !a.vec_bias) return fail(ICNN_E_UNSUPPORTED, "fused first layer needs 16-byte aligned output and bias");
     const unsigned long long xb = ((unsigned long long)d->n * d->h * d->w - 1) * d->in_c_stride + d->cin;
     if (xb > 0x7fffffffull || g.M > 0x7fffffffLL) return fail(ICNN_E_UNSUPPORTED, "fused first layer needs tensors below 2 GiB");
     if (xb < 4) return fail(ICNN_E_UNSUPPORTED, "fused first layer reads the picture four bytes at a time: it needs at least four");
     const int hp = (g.ho + 2 * pool_pad - pool_k) / pool_stride + 1, wp = (g.wo + 2 * pool_pad - pool_k) / pool_stride + 1;
-    return launched(launch_conv_stem_pool(a, hp, wp, (hipStream_t)stream), "iconv2d_maxpool_brelu");
+    return launched(launch_conv_stem_pool(a, hp, wp, (hipStream_t)stream), what);
 }
 
-int iconv2d_bottleneck_brelu(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1,
-                             const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2,
-                             const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *res,
-                             void *y, void *stream)
+int iconv2d_maxpool_brelu(const icnn_conv_desc *d, int32_t pool_k, int32_t pool_stride, int32_t pool_pad, const void *x,
+                          const void *w_packed, const int32_t *bias, void *y, void *stream)
+{
+    return maxpool_layer(d, pool_k, pool_stride, pool_pad, x, w_packed, bias, nullptr, y, stream, "iconv2d_maxpool_brelu");
+}
+
+int iconv2d_maxpool_brelu_pc(const icnn_conv_desc *d, int32_t pool_k, int32_t pool_stride, int32_t pool_pad, const void *x,
+                             const void *w_packed, const int32_t *bias, const void *pc_packed, void *y, void *stream)
+{
+    if (!pc_packed) return fail(ICNN_E_NULL, "packed channel parameters are NULL");
+    return maxpool_layer(d, pool_k, pool_stride, pool_pad, x, w_packed, bias, pc_packed, y, stream, "iconv2d_maxpool_brelu_pc");
+}
+
+static int bottleneck(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1, const void *pc1,
+                      const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2, const void *pc2,
+                      const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3, const void *res,
+                      void *y, void *stream, const char *what)
 {
     ConvGeom g1, g2, g3;
     int rc = check_conv(c1, &g1);
@@ -607,6 +629,7 @@ int iconv2d_bottleneck_brelu(const icnn_conv_desc *c1, const void *x, const void
     if ((rc = fill_conv_args(c1, g1, x, w1_packed, bias1, nullptr, &dummy, a1))) return rc;
     if ((rc = fill_conv_args(c2, g2, x, w2_packed, bias2, nullptr, &dummy, a2))) return rc;
     if ((rc = fill_conv_args(c3, g3, x, w3_packed, bias3, res, y, a3))) return rc;
+    if ((rc = take_pc(a1, pc1)) || (rc = take_pc(a2, pc2)) || (rc = take_pc(a3, pc3))) return rc;
     if (!a3.epi_vec) return fail(ICNN_E_UNSUPPORTED, "fused block needs 16-byte aligned output and skip tensors");
     if (!a1.vec_bias || !a2.vec_bias || !a3.vec_bias) return fail(ICNN_E_UNSUPPORTED, "fused block needs 16-byte aligned bias arrays");
     if (a1.x_bytes >= 0x7fffff00u || a1.wp_bytes >= 0x7fffff00u || a2.wp_bytes >= 0x7fffff00u || a3.wp_bytes >= 0x7fffff00u)
@@ -621,15 +644,35 @@ int iconv2d_bottleneck_brelu(const icnn_conv_desc *c1, const void *x, const void
     b.per_xcd = 0;              // set by the launcher
     b.k1 = c / 64;
     b.nchunk3 = c3->cout / mid;
-    if (!g_tuning.no_block64 && conv_block64_takes(b, a1, a3) && conv_block64_lds_bytes(c, c, false) <= 160 * 1024)
-        return launched(launch_conv_block64(b, a1, a2, a3, nullptr, (hipStream_t)stream), "iconv2d_bottleneck_brelu");
-    return launched(launch_conv_block(b, a1, a2, a3, (hipStream_t)stream), "iconv2d_bottleneck_brelu");
+    if ((pc3 || !g_tuning.no_block64) && conv_block64_takes(b, a1, a3) && conv_block64_lds_bytes(c, c, false, pc3 != nullptr) <= 160 * 1024)
+        return launched(launch_conv_block64(b, a1, a2, a3, nullptr, (hipStream_t)stream), what);
+    if (pc3) return fail(ICNN_E_UNSUPPORTED, "fused block with channel parameters needs a middle width of 64, outer widths of 64, 128 or 256, an 8-bit output and the block input as skip operand");
+    return launched(launch_conv_block(b, a1, a2, a3, (hipStream_t)stream), what);
 }
 
-int iconv2d_bottleneck_dual_brelu(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1,
-                                  const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2,
-                                  const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3,
-                                  const icnn_conv_desc *cp, const void *wp_packed, const int32_t *biasp, void *y, void *stream)
+int iconv2d_bottleneck_brelu(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1,
+                             const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2,
+                             const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *res,
+                             void *y, void *stream)
+{
+    return bottleneck(c1, x, w1_packed, bias1, nullptr, c2, w2_packed, bias2, nullptr, c3, w3_packed, bias3, nullptr, res, y, stream,
+                      "iconv2d_bottleneck_brelu");
+}
+
+int iconv2d_bottleneck_brelu_pc(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1, const void *pc1_packed,
+                                const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2, const void *pc2_packed,
+                                const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3_packed,
+                                const void *res, void *y, void *stream)
+{
+    if (!pc1_packed || !pc2_packed || !pc3_packed) return fail(ICNN_E_NULL, "packed channel parameters are NULL");
+    return bottleneck(c1, x, w1_packed, bias1, pc1_packed, c2, w2_packed, bias2, pc2_packed, c3, w3_packed, bias3, pc3_packed, res, y, stream,
+                      "iconv2d_bottleneck_brelu_pc");
+}
+
+static int bottleneck_dual(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1, const void *pc1,
+                           const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2, const void *pc2,
+                           const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3,
+                           const icnn_conv_desc *cp, const void *wp_packed, const int32_t *biasp, void *y, void *stream, const char *what)
 {
     ConvGeom g1, g2, g3, gp;
     int rc = check_conv(c1, &g1);
@@ -672,6 +715,7 @@ int iconv2d_bottleneck_dual_brelu(const icnn_conv_desc *c1, const void *x, const
     if ((rc = fill_conv_args(c2, g2, x, w2_packed, bias2, nullptr, &dummy, a2))) return rc;
     if ((rc = fill_conv_args(&m0, g3, x, w3_packed, bias3, nullptr, y, a3))) return rc;
     if ((rc = fill_conv_args(cp, gp, x, wp_packed, biasp, nullptr, &dummy, ap))) return rc;
+    if ((rc = take_pc(a1, pc1)) || (rc = take_pc(a2, pc2)) || (rc = take_pc(a3, pc3))) return rc;
     if (!a3.epi_vec) return fail(ICNN_E_UNSUPPORTED, "fused block needs a 16-byte aligned output");
     if (!a1.vec_bias || !a2.vec_bias || !a3.vec_bias || !ap.vec_bias) return fail(ICNN_E_UNSUPPORTED, "fused block needs 16-byte aligned bias arrays");
     if (a1.x_bytes >= 0x7fffff00u || g1.M > 0x7fffffffLL) return fail(ICNN_E_UNSUPPORTED, "fused block needs tensors below 2 GiB");
@@ -691,11 +735,31 @@ int iconv2d_bottleneck_dual_brelu(const icnn_conv_desc *c1, const void *x, const
     b.k1 = 1;
     b.nchunk3 = 4;
     if (!conv_block64_proj_takes(a1, a3, q)) return fail(ICNN_E_UNSUPPORTED, "fused projection block does not take these layers");
-    return launched(launch_conv_block64(b, a1, a2, a3, &q, (hipStream_t)stream), "iconv2d_bottleneck_dual_brelu");
+    return launched(launch_conv_block64(b, a1, a2, a3, &q, (hipStream_t)stream), what);
 }
 
-int iconv2d_pair_brelu(const icnn_conv_desc *c3, const void *t, const void *w3_packed, const int32_t *bias3, const void *res,
-                       void *y, const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, void *z, void *stream)
+int iconv2d_bottleneck_dual_brelu(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1,
+                                  const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2,
+                                  const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3,
+                                  const icnn_conv_desc *cp, const void *wp_packed, const int32_t *biasp, void *y, void *stream)
+{
+    return bottleneck_dual(c1, x, w1_packed, bias1, nullptr, c2, w2_packed, bias2, nullptr, c3, w3_packed, bias3, nullptr, cp, wp_packed, biasp, y,
+                           stream, "iconv2d_bottleneck_dual_brelu");
+}
+
+int iconv2d_bottleneck_dual_brelu_pc(const icnn_conv_desc *c1, const void *x, const void *w1_packed, const int32_t *bias1, const void *pc1_packed,
+                                     const icnn_conv_desc *c2, const void *w2_packed, const int32_t *bias2, const void *pc2_packed,
+                                     const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3_packed,
+                                     const icnn_conv_desc *cp, const void *wp_packed, const int32_t *biasp, void *y, void *stream)
+{
+    if (!pc1_packed || !pc2_packed || !pc3_packed) return fail(ICNN_E_NULL, "packed channel parameters are NULL");
+    return bottleneck_dual(c1, x, w1_packed, bias1, pc1_packed, c2, w2_packed, bias2, pc2_packed, c3, w3_packed, bias3, pc3_packed, cp, wp_packed,
+                           biasp, y, stream, "iconv2d_bottleneck_dual_brelu_pc");
+}
+
+static int pair_layers(const icnn_conv_desc *c3, const void *t, const void *w3_packed, const int32_t *bias3, const void *pc3, const void *res,
+                       void *y, const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, const void *pc1, void *z, void *stream,
+                       const char *what)
 {
     ConvGeom g3, g1;
     int rc = check_conv(c3, &g3);
@@ -721,16 +785,33 @@ int iconv2d_pair_brelu(const icnn_conv_desc *c3, const void *t, const void *w3_p
     ConvArgs a3, a1;
     if ((rc = fill_conv_args(c3, g3, t, w3_packed, bias3, res, y, a3))) return rc;
     if ((rc = fill_conv_args(c1, g1, y, w1_packed, bias1, nullptr, z, a1))) return rc;
+    if ((rc = take_pc(a3, pc3)) || (rc = take_pc(a1, pc1))) return rc;
     if (!a3.epi_vec || !a1.epi_vec) return fail(ICNN_E_UNSUPPORTED, "fused pair needs 16-byte aligned output and skip tensors");
     if (!a3.vec_bias || !a1.vec_bias) return fail(ICNN_E_UNSUPPORTED, "fused pair needs 16-byte aligned bias arrays");
     // skip operand kinds the byte epilogue covers: none, or unsigned 8-bit joined before requantisation in 32 bits
-    if (a3.epi_mode / 4 == 2) return fail(ICNN_E_UNSUPPORTED, "fused pair takes an unsigned 8-bit skip operand joined before requantisation");
+    // (per channel the rescale may be any: the kernel looks at the parameters)
+    if (pc3 ? c3->res_mode == ICNN_RES_POST || (c3->res_mode == ICNN_RES_PRE && c3->res_dtype != ICNN_U8) : a3.epi_mode / 4 == 2)
+        return fail(ICNN_E_UNSUPPORTED, "fused pair takes an unsigned 8-bit skip operand joined before requantisation");
     if (a3.x_bytes >= 0x7fffff00u || g3.M > 0x7fffffffLL - 64 ||
         (unsigned long long)g3.M * c3->out_c_stride >= 0x7fffff00ull ||
         (c3->res_mode != ICNN_RES_NONE && (unsigned long long)g3.M * c3->res_c_stride >= 0x7fffff00ull))
         return fail(ICNN_E_UNSUPPORTED, "fused pair needs tensors below 2 GiB");
-    if (conv_pair_lds_bytes(c3->cout, c1->cout) > 160 * 1024) return fail(ICNN_E_UNSUPPORTED, "the tile of the wide tensor does not fit the on-chip memory");
-    return launched(launch_conv_pair(a3, a1, g3.M, (hipStream_t)stream), "iconv2d_pair_brelu");
+    if (conv_pair_lds_bytes(c3->cout, c1->cout, pc3 != nullptr) > 160 * 1024) return fail(ICNN_E_UNSUPPORTED, "the tile of the wide tensor does not fit the on-chip memory");
+    return launched(launch_conv_pair(a3, a1, g3.M, (hipStream_t)stream), what);
+}
+
+int iconv2d_pair_brelu(const icnn_conv_desc *c3, const void *t, const void *w3_packed, const int32_t *bias3, const void *res,
+                       void *y, const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, void *z, void *stream)
+{
+    return pair_layers(c3, t, w3_packed, bias3, nullptr, res, y, c1, w1_packed, bias1, nullptr, z, stream, "iconv2d_pair_brelu");
+}
+
+int iconv2d_pair_brelu_pc(const icnn_conv_desc *c3, const void *t, const void *w3_packed, const int32_t *bias3, const void *pc3_packed,
+                          const void *res, void *y, const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1,
+                          const void *pc1_packed, void *z, void *stream)
+{
+    if (!pc3_packed || !pc1_packed) return fail(ICNN_E_NULL, "packed channel parameters are NULL");
+    return pair_layers(c3, t, w3_packed, bias3, pc3_packed, res, y, c1, w1_packed, bias1, pc1_packed, z, stream, "iconv2d_pair_brelu_pc");
 }
 
 int iconv2d_twin_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_packed, const int32_t *bias_a, void *ya,
@@ -978,6 +1059,15 @@ static int run_call(int32_t k, const icnn_call &c, void *stream)
         rc = iconv2d_chain_brelu(i[0], (const icnn_conv_desc *const *)c.list[0], p[0], (const void *const *)c.list[1],
                                  (const int32_t *const *)c.list[2], o(1), stream);
         break;
+    case ICNN_CALL_CONV_MAXPOOL_PC: rc = iconv2d_maxpool_brelu_pc(d[0], i[0], i[1], i[2], p[0], p[1], b(2), p[3], o(4), stream); break;
+    case ICNN_CALL_BOTTLENECK_PC:
+        rc = iconv2d_bottleneck_brelu_pc(d[0], p[0], p[1], b(2), p[3], d[1], p[4], b(5), p[6], d[2], p[7], b(8), p[9], p[10], o(11), stream);
+        break;
+    case ICNN_CALL_BOTTLENECK_DUAL_PC:
+        rc = iconv2d_bottleneck_dual_brelu_pc(d[0], p[0], p[1], b(2), p[3], d[1], p[4], b(5), p[6], d[2], p[7], b(8), p[9], d[3], p[10], b(11), o(12),
+                                              stream);
+        break;
+    case ICNN_CALL_PAIR_PC: rc = iconv2d_pair_brelu_pc(d[0], p[0], p[1], b(2), p[3], p[4], o(5), d[1], p[6], b(7), p[8], o(9), stream); break;
     case ICNN_CALL_MAXPOOL: rc = imaxpool2d_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
     case ICNN_CALL_AVGPOOL: rc = iavgpool_global_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
     default: rc = fail(ICNN_E_PARAM, "call %d: unknown kind %d", k, c.kind);

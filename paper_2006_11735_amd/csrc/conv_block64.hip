@@ -39,7 +39,8 @@ __device__ unsigned long long g_b64_trace[512];
 
 constexpr int kB64Rows = 160;        // patch rows: five pixel groups of 32 (output pixel slots of a tile: 128, four groups)
 
-template <int K1, int NCH3, bool PROJ>       // input channels / 64 (1, 2 or 4); output channels / 32 (2, 4 or 8); projection skip
+// PC: requantisation and skip rescale per output channel (packed parameters of the three layers, copied to LDS once)
+template <int K1, int NCH3, bool PROJ, bool PC>       // input channels / 64 (1, 2 or 4); output channels / 32 (2, 4 or 8); projection skip
 __global__ __launch_bounds__(512, 2) void conv_block64_kernel(const BlockArgs g, const ConvArgs a1, const ConvArgs a2, const ConvArgs a3,
                                                               const ProjArgs pj)
 {
@@ -57,6 +58,9 @@ __global__ __launch_bounds__(512, 2) void conv_block64_kernel(const BlockArgs g,
     uint8_t *const abuf = lds + 2 * PATCH;
     uint8_t *const bbuf = abuf;                      // b overwrites a once every wave has left phase 2
     int32_t *const btab = (int32_t *)(abuf + SLICE);
+    // PC: the channel groups of layers 1 (four), 2 (four) and 3; this lane's group of chunk c is 2 c + half
+    int32_t *const pct = btab + 128 + (PROJ ? 2 : 1) * CO;
+    auto group = [&](int first, int chunk) { return pct + (first + 2 * chunk + ((threadIdx.x >> 5) & 1)) * kPcGroupInts; };
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -138,6 +142,12 @@ __global__ __launch_bounds__(512, 2) void conv_block64_kernel(const BlockArgs g,
     for (int i = tid; i < 128 + (PROJ ? 2 : 1) * CO; i += 512)
         btab[i] = i < 64 ? a1.bias[i] : (i < 128 ? a2.bias[i - 64] : (i < 128 + CO ? a3.bias[i - 128] : pj.bias[i - 128 - CO]));
 
+    if constexpr (PC) {
+        copy_pc_groups<512>(pct, a1.pc, 4, tid);
+        copy_pc_groups<512>(pct + 4 * kPcGroupInts, a2.pc, 4, tid);
+        copy_pc_groups<512>(pct + 8 * kPcGroupInts, a3.pc, CO / 16, tid);
+    }
+
     // tile-invariant positions of phase 2: output slot q = 32 pg12 + col is tile pixel (q / TW, q % TW), whose centre
     // tap is patch row (ty + 1) * PW + tx + 1; slots beyond the tile compute on row PW + 1 and are never stored
     int rel2;
@@ -184,10 +194,9 @@ __global__ __launch_bounds__(512, 2) void conv_block64_kernel(const BlockArgs g,
                 const int px = row - py * g.PW;
                 const int iy = y0 - 1 + py, ix = x0 - 1 + px;
                 const bool ok = py < g.TH + 2 && (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
-                int t[16];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) t[r] = acc[r];
-                v4i w = requant16_any(a1, t);
+                v4i w;
+                if constexpr (PC) w = epilogue_pc_bytes16<0>(a1, acc, v4i{0, 0, 0, 0}, group(0, c12));
+                else w = epilogue_bytes16<0>(a1, acc, v4i{0, 0, 0, 0});
                 if (!ok) w = v4i{0, 0, 0, 0};        // outside the image: the next layer's zero padding
                 *(v4i *)(abuf + b_slot_offset(row, c12 * 2 + half)) = w;
                 B64_TR(4);
@@ -210,10 +219,9 @@ __global__ __launch_bounds__(512, 2) void conv_block64_kernel(const BlockArgs g,
             sync();                                  // every wave has its last fragments of a: b may overwrite it
             mfma_drain(acc);
             B64_TR(7);
-            int t[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) t[r] = acc[r];
-            const v4i w = requant16_any(a2, t);      // slots beyond the tile hold values nobody stores
+            v4i w;                                   // slots beyond the tile hold values nobody stores
+            if constexpr (PC) w = epilogue_pc_bytes16<0>(a2, acc, v4i{0, 0, 0, 0}, group(4, c12));
+            else w = epilogue_bytes16<0>(a2, acc, v4i{0, 0, 0, 0});
             *(v4i *)(bbuf + b_slot_offset(32 * pg12 + col, c12 * 2 + half)) = w;
             B64_TR(8);
         }
@@ -242,6 +250,11 @@ __global__ __launch_bounds__(512, 2) void conv_block64_kernel(const BlockArgs g,
                                                                 acc, 0, 0, 0);
                 mfma_drain(acc);
                 const v16i b3 = bias16(btab + 128 + co);
+                if constexpr (PC) {
+                    const int32_t *gp = group(8, ch3);
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[r] = (int)rsr64((int64_t)acc[r] * gp[kPcResMul + r], gp[kPcResShift + r] & 63) + b3[r];
+                } else
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[r] = (int)rsr64((int64_t)acc[r] * pj.res_mul, pj.res_shift) + b3[r];
             } else {
@@ -253,11 +266,13 @@ __global__ __launch_bounds__(512, 2) void conv_block64_kernel(const BlockArgs g,
             mfma_drain(acc);
             v4i w;
             if constexpr (PROJ) {
-                w = epilogue_bytes16<0>(a3, acc, v4i{0, 0, 0, 0});
+                if constexpr (PC) w = epilogue_pc_bytes16<0>(a3, acc, v4i{0, 0, 0, 0}, group(8, ch3));
+                else w = epilogue_bytes16<0>(a3, acc, v4i{0, 0, 0, 0});
             } else {
                 // the skip operand: channels co .. co + 16 of the pixel's own patch row
                 const v4i r8 = *(const v4i *)(xb + (co >> 6) * SLICE + b_slot_offset(prow, (co & 63) >> 4));
-                w = has_res ? epilogue_bytes16<1>(a3, acc, r8) : epilogue_bytes16<0>(a3, acc, r8);
+                if constexpr (PC) w = has_res ? epilogue_pc_bytes16<1>(a3, acc, r8, group(8, ch3)) : epilogue_pc_bytes16<0>(a3, acc, r8, group(8, ch3));
+                else w = has_res ? epilogue_bytes16<1>(a3, acc, r8) : epilogue_bytes16<0>(a3, acc, r8);
             }
             if (ok) *(v4i *)((uint8_t *)a3.out + (size_t)((n * g.H + oy) * g.W + ox) * a3.out_cs + a3.out_co + co) = w;
             B64_TR(10);
@@ -272,9 +287,9 @@ __global__ __launch_bounds__(512, 2) void conv_block64_kernel(const BlockArgs g,
 }
 
 // ------------------------------------------------------------------ dispatch
-size_t conv_block64_lds_bytes(int c_in, int c_out, bool proj)
+size_t conv_block64_lds_bytes(int c_in, int c_out, bool proj, bool pc)
 {
-    return (size_t)(2 * (c_in / 64) + 1) * kB64Rows * 64 + (size_t)(128 + (proj ? 2 : 1) * c_out) * 4;
+    return (size_t)(2 * (c_in / 64) + 1) * kB64Rows * 64 + (size_t)(128 + (proj ? 2 : 1) * c_out) * 4 + (pc ? (size_t)(8 + c_out / 16) * kPcGroupInts * 4 : 0);
 }
 
 // true when the register-resident kernel takes the block: 64 middle channels, 64, 128 or 256 outer channels, an
@@ -284,7 +299,9 @@ bool conv_block64_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &
 {
     const int c = a1.Cin;
     if (a1.Cout != 64 || a3.Cout != c || (c != 64 && c != 128 && c != 256)) return false;
-    if (a3.out_mode == 3 || a3.epi_mode / 4 == 2 || !a3.epi_vec) return false;
+    if (a3.out_mode == 3 || !a3.epi_vec) return false;
+    // (per channel, the rescale of an unsigned 8-bit skip operand may be any: the kernel looks at the parameters)
+    if (a3.pc ? a3.res_mode == 2 || (a3.res_mode == 1 && a3.res_dtype != 0) : a3.epi_mode / 4 == 2) return false;
     if (a3.res_mode != 0 && ((const uint8_t *)a3.res != g.x || a3.res_cs != g.x_cs)) return false;
     return true;
 }
@@ -301,7 +318,8 @@ hipError_t launch_conv_block64(const BlockArgs &g, const ConvArgs &a1, const Con
                                hipStream_t st)
 {
     const int c = a1.Cin;
-    const size_t lds_bytes = conv_block64_lds_bytes(c, a3.Cout, pj != nullptr);
+    const size_t lds_bytes = conv_block64_lds_bytes(c, a3.Cout, pj != nullptr, a3.pc != nullptr);
+    if ((a1.pc != nullptr) != (a3.pc != nullptr) || (a2.pc != nullptr) != (a3.pc != nullptr)) return hipErrorInvalidValue;
     if (!(pj ? conv_block64_proj_takes(a1, a3, *pj) : conv_block64_takes(g, a1, a3)) || lds_bytes > 160 * 1024 || g.n_tiles < 1)
         return hipErrorInvalidValue;
     BlockArgs gx = g;
@@ -316,8 +334,12 @@ hipError_t launch_conv_block64(const BlockArgs &g, const ConvArgs &a1, const Con
         hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, gx, a1, a2, a3, pj ? *pj : none);
         return hipGetLastError();
     };
-    if (pj) return go(conv_block64_kernel<1, 8, true>);
-    return c == 64 ? go(conv_block64_kernel<1, 2, false>) : c == 128 ? go(conv_block64_kernel<2, 4, false>) : go(conv_block64_kernel<4, 8, false>);
+    if (a3.pc) {
+        if (pj) return go(conv_block64_kernel<1, 8, true, true>);
+        return c == 64 ? go(conv_block64_kernel<1, 2, false, true>) : c == 128 ? go(conv_block64_kernel<2, 4, false, true>) : go(conv_block64_kernel<4, 8, false, true>);
+    }
+    if (pj) return go(conv_block64_kernel<1, 8, true, false>);
+    return c == 64 ? go(conv_block64_kernel<1, 2, false, false>) : c == 128 ? go(conv_block64_kernel<2, 4, false, false>) : go(conv_block64_kernel<4, 8, false, false>);
 }
 
 #ifdef ICNN_B64_TRACE

@@ -515,6 +515,57 @@ __device__ __forceinline__ v4i epilogue_bytes16(const ConvArgs &a, const v16i &a
     if constexpr (RQ == 0) return requant16_any(a, t);
     else return requant16<RQ>(a, t);
 }
+// epilogue_bytes16 with per-channel parameters (g: those of the lane's group of 16, see kPcGroupInts; in LDS, the lanes of a half read the same
+// ones): unsigned bytes, skip operand as there.  The forms are those of epilogue_pc_row and, where a skip rescale does not fit 32 bits,
+// of epilogue_pc_slow; which one is decided for the whole wave.
+template <int RES>
+__device__ __forceinline__ v4i epilogue_pc_bytes16(const ConvArgs &a, const v16i &acc, const v4i &res8, const int32_t *g)
+{
+    const int flags = g[kPcFlags];
+    const bool plain = __builtin_amdgcn_ballot_w64(!(flags & 2)) == 0;
+    const bool res32 = RES == 0 || __builtin_amdgcn_ballot_w64(!(flags & 1)) == 0;
+    const int lo_v = a.lo;
+    v4i w;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+        int t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = acc[4 * q4 + e];
+        if (RES == 1) {
+            const v4i rmu = *(const v4i *)(g + kPcResMul + 4 * q4), rsf = *(const v4i *)(g + kPcResShift + 4 * q4);
+            const uint32_t w4 = (uint32_t)res8[q4];
+            if (res32) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    t[e] = __builtin_elementwise_add_sat(t[e], (int)((__umul24((w4 >> (8 * e)) & 0xffu, (uint32_t)rmu[e]) + ((1u << rsf[e]) >> 1)) >> rsf[e]));
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) t[e] = sat32((int64_t)t[e] + rsr64((int64_t)((w4 >> (8 * e)) & 0xffu) * rmu[e], rsf[e] & 63));
+            }
+        }
+        const v4i A = *(const v4i *)(g + kPcA + 4 * q4);
+        int v[4];
+        if (plain) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = med3_vvs((int)(((int64_t)t[e] * A[e] + 0x80000000LL) >> 32), lo_v, a.hi);
+        } else {
+            const v4i L = *(const v4i *)(g + kPcL + 4 * q4), T = *(const v4i *)(g + kPcT + 4 * q4), C = *(const v4i *)(g + kPcC + 4 * q4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int tc = min(max(t[e], ~T[e]), T[e]) << L[e];
+                v[e] = med3_vvs((int)(((int64_t)tc * A[e] + ((int64_t)1 << (31 + C[e]))) >> 32) >> C[e], lo_v, a.hi);
+            }
+        }
+        w[q4] = pack_low_bytes(v[0], v[1], v[2], v[3]);
+    }
+    return w;
+}
+// The parameters of n_groups groups from memory to LDS (16-byte pieces, dealt over the workgroup's threads)
+template <int THREADS>
+__device__ __forceinline__ void copy_pc_groups(int32_t *dst, const int32_t *src, int n_groups, int tid)
+{
+    for (int i = tid; i < n_groups * (kPcGroupInts / 4); i += THREADS) ((v4i *)dst)[i] = ((const v4i *)src)[i];
+}
 // Outputs R0 .. R0 + N - 1 of epilogue_bytes16<RES, 3> (the 32-bit requantisation form, a.rq24): their bytes go into
 // the words w[R0 / 4 ..], which the caller collects over the sixteen outputs.  For callers that deal the epilogue out
 // in slices between matrix instructions.  R0 and N are multiples of... any; a word is started by its output 4 q.

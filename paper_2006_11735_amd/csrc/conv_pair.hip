@@ -56,8 +56,9 @@ struct PairArgs {
 };
 
 // K3 / 32 (fragments of the first layer's K), MID2 / 32 (chunks of the second's outputs); PIPE: the first layer's
-// requantisation has the 32-bit form (a3.rq24) and its epilogue is dealt out between the matrix instructions
-template <int KF, int MG2, bool PIPE>
+// requantisation has the 32-bit form (a3.rq24) and its epilogue is dealt out between the matrix instructions; PC: requantisation and skip
+// rescale of both layers per output channel (packed parameters, copied to LDS; PIPE is false then)
+template <int KF, int MG2, bool PIPE, bool PC>
 __global__ __launch_bounds__(512, KF == 8 ? 1 : 2) void conv_pair_kernel(const ConvArgs a3, const ConvArgs a1, const PairArgs g)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -94,6 +95,7 @@ __global__ __launch_bounds__(512, KF == 8 ? 1 : 2) void conv_pair_kernel(const C
     // the tile of t goes through LDS once (every wave needs all of it): 16-byte pieces, rows padded like y's
     constexpr int K3 = KF * 32, TPITCH = K3 + 16, TPIECES = kPairPix * K3 / 16, TQ = (TPIECES + 511) / 512;
     uint8_t *const tbuf = (uint8_t *)(btab + C + MG2 * 32);
+    [[maybe_unused]] int32_t *const pct = (int32_t *)(tbuf + kPairPix * TPITCH);     // PC: [C / 16] groups of the first layer, [MID2 / 16] of the second
     v4i tv[TQ];
     {
         const __amdgpu_buffer_rsrc_t rs_t = __builtin_amdgcn_make_buffer_rsrc((void *)a3.x, 0, a3.x_bytes, 0x00020000);
@@ -148,7 +150,13 @@ __global__ __launch_bounds__(512, KF == 8 ? 1 : 2) void conv_pair_kernel(const C
     // ... and its epilogue: sixteen requantised bytes into the pixel's row of y in LDS.  RQ as in epilogue_bytes16.
     auto fin_tile = [&](auto j_tag, auto rq_tag, const v16i &acc, const v4i &r, int chunk) __attribute__((always_inline)) {
         constexpr int J = decltype(j_tag)::value, RQ = decltype(rq_tag)::value;
-        const v4i w = has_res ? epilogue_bytes16<1, RQ>(a3, acc, r) : epilogue_bytes16<0, RQ>(a3, acc, r);
+        v4i w;
+        if constexpr (PC) {
+            const int32_t *g16 = pct + (2 * chunk + half) * kPcGroupInts;
+            w = has_res ? epilogue_pc_bytes16<1>(a3, acc, r, g16) : epilogue_pc_bytes16<0>(a3, acc, r, g16);
+        } else {
+            w = has_res ? epilogue_bytes16<1, RQ>(a3, acc, r) : epilogue_bytes16<0, RQ>(a3, acc, r);
+        }
         *(v4i *)(ybuf + (32 * J + col) * pitch + chunk * 32 + half * 16) = w;
     };
     // One step of the software pipeline: a tile's matrix instructions and the previous tile's epilogue are independent.
@@ -199,6 +207,10 @@ __global__ __launch_bounds__(512, KF == 8 ? 1 : 2) void conv_pair_kernel(const C
         for (int q = 0; q < TQ; ++q) {
             const int e = tid + q * 512;
             if (e < TPIECES) *(v4i *)(tbuf + (e / (K3 / 16)) * TPITCH + (e % (K3 / 16)) * 16) = tv[q];
+        }
+        if constexpr (PC) {
+            copy_pc_groups<512>(pct, a3.pc, C >> 4, tid);
+            copy_pc_groups<512>(pct + (C >> 4) * kPcGroupInts, a1.pc, MG2 * 2, tid);
         }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_waitcnt(0xC07F);
@@ -319,7 +331,9 @@ __global__ __launch_bounds__(512, KF == 8 ? 1 : 2) void conv_pair_kernel(const C
     static_for<NJ2>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
         const int pz = p0 + 32 * (pg + j) + col;
-        const v4i w = epilogue_bytes16<0>(a1, acc[j], v4i{0, 0, 0, 0});
+        v4i w;
+        if constexpr (PC) w = epilogue_pc_bytes16<0>(a1, acc[j], v4i{0, 0, 0, 0}, pct + ((C >> 4) + 2 * c2 + half) * kPcGroupInts);
+        else w = epilogue_bytes16<0>(a1, acc[j], v4i{0, 0, 0, 0});
         if (pz < P) *(v4i *)((uint8_t *)a1.out + (size_t)pz * a1.out_cs + a1.out_co + c2 * 32 + half * 16) = w;
     });
     PAIR_TR(8);
@@ -328,17 +342,17 @@ __global__ __launch_bounds__(512, KF == 8 ? 1 : 2) void conv_pair_kernel(const C
 }
 
 // ------------------------------------------------------------------ dispatch
-size_t conv_pair_lds_bytes(int c, int mid2)
+size_t conv_pair_lds_bytes(int c, int mid2, bool pc)
 {
-    return (size_t)kPairPix * (c + 16) + (size_t)(c + mid2) * 4 + (size_t)kPairPix * (mid2 + 16);
+    return (size_t)kPairPix * (c + 16) + (size_t)(c + mid2) * 4 + (size_t)kPairPix * (mid2 + 16) + (pc ? (size_t)(c + mid2) / 16 * kPcGroupInts * 4 : 0);
 }
 
 hipError_t launch_conv_pair(const ConvArgs &a3, const ConvArgs &a1, long long pixels, hipStream_t st)
 {
     const int kf = a3.Cin / 32, mg2 = a1.Cout / 32;
-    const size_t lds_bytes = conv_pair_lds_bytes(a3.Cout, a1.Cout);
+    const size_t lds_bytes = conv_pair_lds_bytes(a3.Cout, a1.Cout, a3.pc != nullptr);
     if (a3.Cin % 64 || a1.Cout % 32 || kf != mg2 || (kf != 2 && kf != 4 && kf != 8) || a3.Cout % 256 || a1.Cin != a3.Cout ||
-        lds_bytes > 160 * 1024 || pixels < 1 || pixels > 0x7fffffffLL - kPairPix)
+        lds_bytes > 160 * 1024 || (a1.pc != nullptr) != (a3.pc != nullptr) || pixels < 1 || pixels > 0x7fffffffLL - kPairPix)
         return hipErrorInvalidValue;
     // byte extents of the skip operand and of y up to the end of the last pixel's channels, for the descriptors
     const unsigned long long rb = a3.res_mode ? (unsigned long long)(pixels - 1) * a3.res_cs + a3.Cout : 0;
@@ -367,9 +381,11 @@ hipError_t launch_conv_pair(const ConvArgs &a3, const ConvArgs &a1, long long pi
         hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, b3, a1, g);
         return hipGetLastError();
     };
+    if (a3.pc)
+        return kf == 2 ? go(conv_pair_kernel<2, 2, false, true>) : kf == 4 ? go(conv_pair_kernel<4, 4, false, true>) : go(conv_pair_kernel<8, 8, false, true>);
     if (a3.rq24 && (!a3.res_mode || a3.res_fast))
-        return kf == 2 ? go3(conv_pair_kernel<2, 2, true>) : kf == 4 ? go3(conv_pair_kernel<4, 4, true>) : go3(conv_pair_kernel<8, 8, true>);
-    return kf == 2 ? go(conv_pair_kernel<2, 2, false>) : kf == 4 ? go(conv_pair_kernel<4, 4, false>) : go(conv_pair_kernel<8, 8, false>);
+        return kf == 2 ? go3(conv_pair_kernel<2, 2, true, false>) : kf == 4 ? go3(conv_pair_kernel<4, 4, true, false>) : go3(conv_pair_kernel<8, 8, true, false>);
+    return kf == 2 ? go(conv_pair_kernel<2, 2, false, false>) : kf == 4 ? go(conv_pair_kernel<4, 4, false, false>) : go(conv_pair_kernel<8, 8, false, false>);
 }
 
 #ifdef ICNN_PAIR_TRACE

@@ -49,7 +49,7 @@ __device__ __forceinline__ void stem_static_for(F &&fn)
     }
 }
 
-template <int CG>           // cout / 32: 1 or 2
+template <int CG, bool PC>  // cout / 32: 1 or 2; requantisation per output channel (the packed parameters stay in LDS)
 __global__ __launch_bounds__(256, 3) void conv_stem_pool_kernel(const ConvArgs a, const StemArgs g)
 {
     constexpr int TPX = kStemGroups / 4;             // pixel groups of a wave
@@ -75,6 +75,8 @@ __global__ __launch_bounds__(256, 3) void conv_stem_pool_kernel(const ConvArgs a
     // biases in LDS (read again for every tile: the registers are needed elsewhere)
     int32_t *const btab = (int32_t *)(cbuf + kStemGroups * 32 * ROW_PITCH);
     for (int i = tid; i < CG * 32; i += 256) btab[i] = a.bias[i];
+    int32_t *const pct = btab + CG * 32;
+    if constexpr (PC) copy_pc_groups<256>(pct, a.pc, CG * 2, tid);
 
     // Workgroups go to the eight XCDs round-robin and every XCD has an L2 of its own: the workgroups of XCD x walk the
     // contiguous tile range [x * per_xcd, (x + 1) * per_xcd), so that the picture rows neighbouring tiles share meet in
@@ -211,10 +213,9 @@ __global__ __launch_bounds__(256, 3) void conv_stem_pool_kernel(const ConvArgs a
             const int q = 32 * (pg0 + j) + col;
             stem_static_for<CG>([&](auto cc) {
                 constexpr int c = decltype(cc)::value;
-                int t[16];
-#pragma unroll
-                for (int r = 0; r < 16; ++r) t[r] = acc[c][j][r];
-                v4i w = requant16_any(a, t);
+                v4i w;
+                if constexpr (PC) w = epilogue_pc_bytes16<0>(a, acc[c][j], v4i{0, 0, 0, 0}, pct + (2 * c + half) * kPcGroupInts);
+                else w = epilogue_bytes16<0>(a, acc[c][j], v4i{0, 0, 0, 0});
                 if (!ok) w = v4i{0, 0, 0, 0};
                 *(v4i *)(cbuf + q * ROW_PITCH + c * 32 + half * 16) = w;
             });
@@ -277,7 +278,7 @@ hipError_t launch_conv_stem_pool(const ConvArgs &a, int hp, int wp, hipStream_t 
         a.ksteps != (a.KH * 32 + 63) / 64)
         return hipErrorInvalidValue;
     const size_t lds_bytes = (size_t)g.cout_chunks * g.ksteps * kChunkBytes + 2 * (size_t)kStemMaxRows * kStemPitch * 4 +
-                             (size_t)kStemGroups * 32 * (a.Cout + 16) + (size_t)a.Cout * 4;
+                             (size_t)kStemGroups * 32 * (a.Cout + 16) + (size_t)a.Cout * 4 + (a.pc ? (size_t)(a.Cout / 16) * kPcGroupInts * 4 : 0);
     const int slots = 256 * 3;
     const dim3 grid((unsigned)(8 * g.per_xcd < slots ? 8 * g.per_xcd : slots)), block(256);
     auto go = [&](auto kernel) -> hipError_t {
@@ -288,7 +289,8 @@ hipError_t launch_conv_stem_pool(const ConvArgs &a, int hp, int wp, hipStream_t 
         hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, a, g);
         return hipGetLastError();
     };
-    return a.Cout == 64 ? go(conv_stem_pool_kernel<2>) : go(conv_stem_pool_kernel<1>);
+    if (a.pc) return a.Cout == 64 ? go(conv_stem_pool_kernel<2, true>) : go(conv_stem_pool_kernel<1, true>);
+    return a.Cout == 64 ? go(conv_stem_pool_kernel<2, false>) : go(conv_stem_pool_kernel<1, false>);
 }
 
 }  // namespace icnn

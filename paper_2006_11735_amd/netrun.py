@@ -39,6 +39,7 @@ class GpuNet:
         self.fused = []                     # names of int32 skip buffers that are never written
         self.fused_proj = {}                # main conv name -> the projection op fused into it
         self.fused_block = {}               # last conv name -> (first, middle) conv ops fused into its launch
+        self.fused_block_pc = {}            # the same with requantisation per output channel
         self.fused_pool = {}                # first conv name -> the max-pool op fused into its launch
         self.fused_pair = {}                # block-closing conv name -> the next block's opening conv op in its launch
         self.fused_twin = {}                # branch name -> the other branch's op in its launch
@@ -125,23 +126,24 @@ class GpuNet:
         steps, i = [], 0
         while i < len(self.steps):
             pair = self.steps[i:i + 2]
-            if len(pair) == 2 and pair[0][0] == "conv" and pair[1][0] == "maxpool":
+            if len(pair) == 2 and pair[0][0] in ("conv", "conv_pc") and pair[1][0] == "maxpool":
                 oc, op_ = pair[0][1], pair[1][1]
                 if op_["src"] == oc["dst"] and readers.get(oc["dst"]) == [op_] and oc["dst"] not in self.net["outputs"]:
-                    d, x, wp, bias, _res, _y, _ws = pair[0][2]
+                    pc = pair[0][0] == "conv_pc"
+                    d, x, wp, bias = pair[0][2][:4]
                     dd = B.conv_desc(**{k: getattr(d, k) for k, _ in d._fields_})
                     pooled = self.buf[op_["dst"]]
                     dd.out_c_stride, dd.out_c_offset = pooled.shape[3], 0
-                    args = (dd, op_["k"], op_["stride"], op_["pad"], x, wp, bias, pooled)
+                    args = (dd, op_["k"], op_["stride"], op_["pad"], x, wp, bias) + ((pair[0][2][4],) if pc else ()) + (pooled,)
                     try:
-                        B.iconv2d_maxpool_brelu(*args)
+                        (B.iconv2d_maxpool_brelu_pc if pc else B.iconv2d_maxpool_brelu)(*args)
                     except B.IcnnError as e:
                         if e.code != B.ICNN_E_UNSUPPORTED:
                             raise
                     else:
                         self.fused.append(oc["dst"])
                         self.fused_pool[oc["name"]] = op_
-                        steps.append(("convpool", oc, args))
+                        steps.append(("convpool_pc" if pc else "convpool", oc, args))
                         i += 2
                         continue
             steps.append(self.steps[i])
@@ -165,21 +167,26 @@ class GpuNet:
         steps, i = [], 0
         while i < len(self.steps):
             two = self.steps[i:i + 2]
-            if len(two) == 2 and two[0][0] == "conv" and two[1][0] == "conv":
+            if len(two) == 2 and two[0][0] == two[1][0] and two[0][0] in ("conv", "conv_pc"):
+                pc = two[0][0] == "conv_pc"
                 o3, o1 = two[0][1], two[1][1]
-                (d3, t, w3, b3, res, y, _ws3), (d1, _y, w1, b1, _r1, z, _ws1) = two[0][2], two[1][2]
+                d3, t, w3, b3, res, y = self._conv_args(two[0])
+                d1, _y, w1, b1, _r1, z = self._conv_args(two[1])
                 if (o1["src"] == o3["dst"] and o3["kh"] == 1 and o1["kh"] == 1 and o3["dst_c_offset"] == 0 and
                         o1["cout"] == o3["cin"] and o1["cin"] == o3["cout"] and
                         self.PAIR_MIN_PIXELS <= d3.n * d3.h * d3.w <= self.PAIR_MAX_PIXELS and o3["cout"] <= self.PAIR_MAX_WIDE):
-                    args = (d3, t, w3, b3, res, y, d1, w1, b1, z)
+                    if pc:
+                        fn, args = B.iconv2d_pair_brelu_pc, (d3, t, w3, b3, two[0][2][4], res, y, d1, w1, b1, two[1][2][4], z)
+                    else:
+                        fn, args = B.iconv2d_pair_brelu, (d3, t, w3, b3, res, y, d1, w1, b1, z)
                     try:
-                        B.iconv2d_pair_brelu(*args)                # also a warm-up launch
+                        fn(*args)                                  # also a warm-up launch
                     except B.IcnnError as e:
                         if e.code != B.ICNN_E_UNSUPPORTED:
                             raise
                     else:
                         self.fused_pair[o3["name"]] = o1
-                        steps.append(("pair", o3, args))
+                        steps.append(("pair_pc" if pc else "pair", o3, args))
                         i += 2
                         continue
             steps.append(self.steps[i])
@@ -272,6 +279,12 @@ class GpuNet:
             n += 1
         return run[:n] if n > 1 else None
 
+    @staticmethod
+    def _conv_args(step):
+        """descriptor, input, weights, bias, skip operand, output of a "conv" or "conv_pc" step"""
+        args = step[2]
+        return args[:4] + args[4 + (step[0] == "conv_pc"):][:2]
+
     def _readers(self):
         """buffer name -> the ops that read it"""
         readers = {}
@@ -289,7 +302,8 @@ class GpuNet:
         steps, i = [], 0
         while i < len(self.steps):
             trio = self.steps[i:i + 3]
-            if len(trio) == 3 and trio[0][0] == "conv" and trio[1][0] == "conv" and trio[2][0] == "dual":
+            if [st[0] for st in trio] in (["conv", "conv", "dual"], ["conv_pc", "conv_pc", "dual_pc"]):
+                pc = trio[2][0] == "dual_pc"
                 o1, o2, o3 = (st[1] for st in trio)
                 proj = self.fused_proj[o3["name"]]
                 chain = (o2["src"] == o1["dst"] and o3["src"] == o2["dst"] and proj["src"] == o1["src"] and
@@ -297,18 +311,24 @@ class GpuNet:
                          o1["dst"] not in self.net["outputs"] and o2["dst"] not in self.net["outputs"] and
                          o1["dst_c_offset"] == 0 and o2["dst_c_offset"] == 0)
                 if chain:
-                    (d1, x, w1, b1, _r1, _y1, _ws1), (d2, _x2, w2, b2, _r2, _y2, _ws2) = trio[0][2], trio[1][2]
-                    dm, _xm, wm, bm, dp, _xp, wp, bp, y = trio[2][2]
-                    args = (d1, x, w1, b1, d2, w2, b2, dm, wm, bm, dp, wp, bp, y)
+                    d1, x, w1, b1 = trio[0][2][:4]
+                    d2, _x2, w2, b2 = trio[1][2][:4]
+                    if pc:
+                        dm, _xm, wm, bm, pcm, dp, _xp, wp, bp, y = trio[2][2]
+                        fn = B.iconv2d_bottleneck_dual_brelu_pc
+                        args = (d1, x, w1, b1, trio[0][2][4], d2, w2, b2, trio[1][2][4], dm, wm, bm, pcm, dp, wp, bp, y)
+                    else:
+                        dm, _xm, wm, bm, dp, _xp, wp, bp, y = trio[2][2]
+                        fn, args = B.iconv2d_bottleneck_dual_brelu, (d1, x, w1, b1, d2, w2, b2, dm, wm, bm, dp, wp, bp, y)
                     try:
-                        B.iconv2d_bottleneck_dual_brelu(*args)     # also a warm-up launch
+                        fn(*args)                                  # also a warm-up launch
                     except B.IcnnError as e:
                         if e.code != B.ICNN_E_UNSUPPORTED:
                             raise
                     else:
                         self.fused += [o1["dst"], o2["dst"]]
                         self.fused_projblock[o3["name"]] = (o1, o2, proj)
-                        steps.append(("projblock", o3, args))
+                        steps.append(("projblock_pc" if pc else "projblock", o3, args))
                         i += 3
                         continue
             steps.append(self.steps[i])
@@ -325,7 +345,8 @@ class GpuNet:
         steps, i = [], 0
         while i < len(self.steps):
             trio = self.steps[i:i + 3]
-            if len(trio) == 3 and all(st[0] == "conv" for st in trio):
+            if [st[0] for st in trio] in (["conv"] * 3, ["conv_pc"] * 3):
+                pc = trio[0][0] == "conv_pc"
                 o1, o2, o3 = (st[1] for st in trio)
                 chain = (o2["src"] == o1["dst"] and o3["src"] == o2["dst"] and o3["res"] == o1["src"] and
                          readers.get(o1["dst"]) == [o2] and readers.get(o2["dst"]) == [o3] and
@@ -333,18 +354,21 @@ class GpuNet:
                          o1["dst_c_offset"] == 0 and o2["dst_c_offset"] == 0)
                 d1 = trio[0][2][0]
                 if chain and (o1["cout"] != 128 or d1.n * d1.h * d1.w >= self.BLOCK128_MIN_PIXELS):
-                    (d1, x, w1, b1, _r1, _y1, _ws1), (d2, _x2, w2, b2, _r2, _y2, _ws2), (d3, _x3, w3, b3, res, y, _ws3) = (
-                        st[2] for st in trio)
-                    args = (d1, x, w1, b1, d2, w2, b2, d3, w3, b3, res, y)
+                    (d1, x, w1, b1, _r1, _y1), (d2, _x2, w2, b2, _r2, _y2), (d3, _x3, w3, b3, res, y) = (self._conv_args(st) for st in trio)
+                    if pc:
+                        pc1, pc2, pc3 = (st[2][4] for st in trio)
+                        fn, args = B.iconv2d_bottleneck_brelu_pc, (d1, x, w1, b1, pc1, d2, w2, b2, pc2, d3, w3, b3, pc3, res, y)
+                    else:
+                        fn, args = B.iconv2d_bottleneck_brelu, (d1, x, w1, b1, d2, w2, b2, d3, w3, b3, res, y)
                     try:
-                        B.iconv2d_bottleneck_brelu(*args)          # also a warm-up launch
+                        fn(*args)                                  # also a warm-up launch
                     except B.IcnnError as e:
                         if e.code != B.ICNN_E_UNSUPPORTED:
                             raise
                     else:
                         self.fused += [o1["dst"], o2["dst"]]
-                        self.fused_block[o3["name"]] = (o1, o2)
-                        steps.append(("block", o3, args))
+                        (self.fused_block_pc if pc else self.fused_block)[o3["name"]] = (o1, o2)
+                        steps.append(("block_pc" if pc else "block", o3, args))
                         i += 3
                         continue
             steps.append(self.steps[i])
@@ -436,30 +460,13 @@ class GpuNet:
 
     def run_step(self, i, stream=None):
         kind, _, args = self.steps[i]
-        if kind == "conv":
-            B.iconv2d_brelu(*args, stream=stream)
-        elif kind == "conv_pc":
-            B.iconv2d_brelu_pc(*args, stream=stream)
-        elif kind == "dual":
-            B.iconv2d_dual_brelu(*args, stream=stream)
-        elif kind == "dual_pc":
-            B.iconv2d_dual_brelu_pc(*args, stream=stream)
-        elif kind == "pair":
-            B.iconv2d_pair_brelu(*args, stream=stream)
-        elif kind == "twin":
-            B.iconv2d_twin_brelu(*args, stream=stream)
-        elif kind == "chain":
-            B.iconv2d_chain_brelu(*args, stream=stream)
-        elif kind == "projblock":
-            B.iconv2d_bottleneck_dual_brelu(*args, stream=stream)
-        elif kind == "block":
-            B.iconv2d_bottleneck_brelu(*args, stream=stream)
-        elif kind == "convpool":
-            B.iconv2d_maxpool_brelu(*args, stream=stream)
-        elif kind == "maxpool":
-            B.imaxpool2d_u8(*args, stream=stream)
-        else:
-            B.iavgpool_global_u8(*args, stream=stream)
+        self._FUNCTIONS[kind](*args, stream=stream)
+
+    _FUNCTIONS = {"conv": B.iconv2d_brelu, "conv_pc": B.iconv2d_brelu_pc, "dual": B.iconv2d_dual_brelu, "dual_pc": B.iconv2d_dual_brelu_pc,
+                  "pair": B.iconv2d_pair_brelu, "pair_pc": B.iconv2d_pair_brelu_pc, "twin": B.iconv2d_twin_brelu, "chain": B.iconv2d_chain_brelu,
+                  "projblock": B.iconv2d_bottleneck_dual_brelu, "projblock_pc": B.iconv2d_bottleneck_dual_brelu_pc,
+                  "block": B.iconv2d_bottleneck_brelu, "block_pc": B.iconv2d_bottleneck_brelu_pc, "convpool": B.iconv2d_maxpool_brelu,
+                  "convpool_pc": B.iconv2d_maxpool_brelu_pc, "maxpool": B.imaxpool2d_u8, "avgpool": B.iavgpool_global_u8}
 
     def result(self, name):
         return self.buf[name].cpu().numpy()

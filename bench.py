@@ -39,7 +39,7 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def layer_work(net, op, images, fused_proj=None, fused_block=None, fused_pool=None, fused_pair=None, fused_projblock=None, fused_twin=None, fused_chain=None):
+def layer_work(net, op, images, fused_proj=None, fused_block=None, fused_pool=None, fused_pair=None, fused_projblock=None, fused_twin=None, fused_chain=None, fused_twin_last=None):
     """Algorithmic ops and bytes of one conv launch (true sizes, input counted once).  With a
     projection fused into the launch, its ops, input and weights are added and the int32 skip
     tensor is not counted (it never exists).  With a whole bottleneck block in the launch: the ops of its
@@ -62,6 +62,13 @@ def layer_work(net, op, images, fused_proj=None, fused_block=None, fused_pool=No
             opsi, bi, mi, ki = layer_work(net, o, images)
             ops, byts, k = ops + opsi, byts + bi - 2 * mi * o["cout"], k + ki
         return ops, byts, m, k
+    if fused_twin_last is not None:
+        # two branches and the layer behind them in one launch: the three layers' ops and weights, the branches' input once, the last
+        # layer's skip operand and output (the tensor between them never exists)
+        oa, ob = fused_twin_last
+        opsa, ba, m, ka = layer_work(net, oa, images, fused_twin=ob)
+        opsc, bc, _, kc = layer_work(net, op, images)
+        return opsa + opsc, ba + bc - m * (oa["cout"] + ob["cout"] + op["cin"]), m, ka + kc
     if fused_twin is not None:
         # two branches of one input in one launch: both layers' ops, weights and outputs; the input once
         opsa, ba, m, ka = layer_work(net, op, images)
@@ -466,7 +473,7 @@ def main():
     rows = []
     for step, ms in zip(g.steps, layer_ms):
         kind, op = step[0], step[1]
-        if kind not in ("conv", "conv_pc", "dual", "dual_pc", "block", "convpool", "pair", "projblock", "twin", "chain"):
+        if kind not in ("conv", "conv_pc", "dual", "dual_pc", "block", "convpool", "pair", "projblock", "twin", "twin_last", "chain"):
             other_ms += ms
             rows.append({"name": op["dst"], "kind": kind, "ms": ms})
             continue
@@ -476,14 +483,15 @@ def main():
                                      g.fused_pair.get(op["name"]) if kind == "pair" else None,
                                      g.fused_projblock.get(op["name"]) if kind == "projblock" else None,
                                      g.fused_twin.get(op["name"]) if kind == "twin" else None,
-                                     g.fused_chain.get(op["name"]) if kind == "chain" else None)
+                                     g.fused_chain.get(op["name"]) if kind == "chain" else None,
+                                     g.fused_twin_last.get(op["name"]) if kind == "twin_last" else None)
         conv_ops += ops
         conv_ms += ms
         conv_bytes += byts
         tops = ops / (ms * 1e-3) / 1e12
         attain = min(INT8_MFMA_PEAK_TOPS, ops / byts * HBM_PEAK_GBS / 1e3)
         rows.append({"name": (op["name"][:-3] + "_block" if kind == "block" else op["name"]) + ("+proj" if kind in ("dual", "dual_pc") else "") +
-                             ("+pool" if kind == "convpool" else "") + ("+next_c1" if kind == "pair" else "") + ("+" + g.fused_twin[op["name"]]["name"] if kind == "twin" else "") + ("_chain%d" % (len(g.fused_chain[op["name"]]) + 1) if kind == "chain" else "") + ("_block+proj" if kind == "projblock" else ""), "kind": "conv", "M": m, "N": op["cout"] + (g.fused_twin[op["name"]]["cout"] if kind == "twin" else 0), "K": k, "ms": ms,
+                             ("+pool" if kind == "convpool" else "") + ("+next_c1" if kind == "pair" else "") + ("+" + g.fused_twin[op["name"]]["name"] if kind == "twin" else "") + ("+".join([""] + [o["name"] for o in g.fused_twin_last[op["name"]]]) if kind == "twin_last" else "") + ("_chain%d" % (len(g.fused_chain[op["name"]]) + 1) if kind == "chain" else "") + ("_block+proj" if kind == "projblock" else ""), "kind": "conv", "M": m, "N": op["cout"] + (g.fused_twin[op["name"]]["cout"] if kind == "twin" else 0), "K": k, "ms": ms,
                      "tops": tops, "pct_mfma_peak": 100 * tops / INT8_MFMA_PEAK_TOPS,
                      "pct_attainable": 100 * tops / attain, "gbs": byts / (ms * 1e-3) / 1e9})
     for r in rows:

@@ -372,6 +372,22 @@ int iconv2d_twin_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_p
                        const icnn_conv_desc *cb, const void *wb_packed, const int32_t *bias_b, void *yb, void *stream);
 
 /*
+ * Two branches of one input and the single-channel layer behind them as one launch: the end of a picture-to-picture network (Section 3.1
+ * for each layer, Section 4.1 for the concatenation).  Result: exactly that of
+ *     iconv2d_twin_brelu(ca, x, wa_packed, bias_a, t, cb, wb_packed, bias_b, t, ...);
+ *     iconv2d_brelu(cc, t, wc_packed, bias_c, res, y, ...);
+ * without the tensor t ever existing.  Every argument is a device pointer; y must not overlap x.  Shapes it takes: stride 1, "same"
+ * padding, ca 3x3 with 16 outputs and cb 1x1 with 32, both of 48 input channels, their channel ranges (out_c_offset) filling 48 channels
+ * between them; cc 3x3, 48 input channels, one output, any output and skip operand kind.  Inputs ICNN_IN_U8_LE127, the branches
+ * store unsigned bytes up to 127 and take no skip operand; x and in_c_stride 16-byte aligned; tensors below 2 GiB.  The pitches of
+ * t (ca's and cb's out_c_stride, cc's in_c_stride) are not used.  Anything else returns ICNN_E_UNSUPPORTED having launched nothing, and
+ * the caller issues the layers separately.
+ */
+int iconv2d_twin_last_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_packed, const int32_t *bias_a,
+                            const icnn_conv_desc *cb, const void *wb_packed, const int32_t *bias_b,
+                            const icnn_conv_desc *cc, const void *wc_packed, const int32_t *bias_c, const void *res, void *y, void *stream);
+
+/*
  * A run of 3x3 layers as one launch: the body of a picture-to-picture network (Section 3.1 for each layer).  Result: exactly
  * that of
  *     iconv2d_brelu(descs[0], x,  w_packed[0], bias[0], NULL, t0, ...);
@@ -400,7 +416,8 @@ int iconv2d_chain_split(int32_t n_layers, const icnn_conv_desc *const *descs, in
 typedef enum {
     ICNN_CALL_CONV = 0, ICNN_CALL_CONV_PC = 1, ICNN_CALL_DUAL = 2, ICNN_CALL_DUAL_PC = 3, ICNN_CALL_CONV_MAXPOOL = 4, ICNN_CALL_BOTTLENECK = 5,
     ICNN_CALL_BOTTLENECK_DUAL = 6, ICNN_CALL_PAIR = 7, ICNN_CALL_TWIN = 8, ICNN_CALL_CHAIN = 9, ICNN_CALL_MAXPOOL = 10, ICNN_CALL_AVGPOOL = 11,
-    ICNN_CALL_CONV_MAXPOOL_PC = 12, ICNN_CALL_BOTTLENECK_PC = 13, ICNN_CALL_BOTTLENECK_DUAL_PC = 14, ICNN_CALL_PAIR_PC = 15
+    ICNN_CALL_CONV_MAXPOOL_PC = 12, ICNN_CALL_BOTTLENECK_PC = 13, ICNN_CALL_BOTTLENECK_DUAL_PC = 14, ICNN_CALL_PAIR_PC = 15,
+    ICNN_CALL_TWIN_LAST = 16
 } icnn_call_kind;
 typedef struct {
     int32_t kind;                  /* icnn_call_kind */

@@ -44,7 +44,7 @@ class icnn_call(C.Structure):
 
 (ICNN_CALL_CONV, ICNN_CALL_CONV_PC, ICNN_CALL_DUAL, ICNN_CALL_DUAL_PC, ICNN_CALL_CONV_MAXPOOL, ICNN_CALL_BOTTLENECK, ICNN_CALL_BOTTLENECK_DUAL,
  ICNN_CALL_PAIR, ICNN_CALL_TWIN, ICNN_CALL_CHAIN, ICNN_CALL_MAXPOOL, ICNN_CALL_AVGPOOL, ICNN_CALL_CONV_MAXPOOL_PC, ICNN_CALL_BOTTLENECK_PC,
- ICNN_CALL_BOTTLENECK_DUAL_PC, ICNN_CALL_PAIR_PC) = range(16)
+ ICNN_CALL_BOTTLENECK_DUAL_PC, ICNN_CALL_PAIR_PC, ICNN_CALL_TWIN_LAST) = range(17)
 
 
 class IcnnError(RuntimeError):
@@ -88,6 +88,7 @@ _lib.iconv2d_maxpool_brelu_pc.argtypes = [_descp, _i32, _i32, _i32, _vp, _vp, _v
 _lib.iconv2d_bottleneck_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp] + [_descp, _vp, _vp, _vp] * 2 + [_vp, _vp, _vp]
 _lib.iconv2d_bottleneck_dual_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp] + [_descp, _vp, _vp, _vp] * 2 + [_descp, _vp, _vp, _vp, _vp]
 _lib.iconv2d_pair_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp, _vp, _vp, _descp, _vp, _vp, _vp, _vp, _vp]
+_lib.iconv2d_twin_last_brelu.argtypes = [_descp, _vp, _vp, _vp] + [_descp, _vp, _vp] * 2 + [_vp, _vp, _vp]
 _lib.iconv2d_chain_brelu.argtypes = [_i32, C.POINTER(_descp), _vp, C.POINTER(_vp), C.POINTER(_vp), _vp, _vp]
 _lib.iconv2d_chain_split.argtypes = [_i32, C.POINTER(_descp), C.POINTER(_i32), C.POINTER(_i32)]
 _lib.icnn_run_calls.argtypes = [_i32, C.POINTER(icnn_call), _vp]
@@ -106,7 +107,7 @@ _lib.icnn_peak_copy.argtypes = [_vp, _vp, C.c_size_t, _vp]
 EXPORTS = ["icnn_version", "icnn_last_error", "icnn_set_tuning", "iconv2d_validate", "iconv2d_out_hw",
            "iconv2d_workspace_bytes", "iconv2d_packed_weight_bytes", "iconv2d_prepack_weights",
            "iconv2d_brelu", "iconv2d_brelu_static_ws", "iconv2d_packed_channel_params_bytes", "iconv2d_prepack_channel_params", "iconv2d_brelu_pc",
-           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_maxpool_brelu_pc", "iconv2d_bottleneck_brelu_pc", "iconv2d_bottleneck_dual_brelu_pc", "iconv2d_pair_brelu_pc", "iconv2d_twin_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "icnn_run_calls", "icnn_lanes_create", "icnn_lanes_destroy", "icnn_run_lanes", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
+           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_maxpool_brelu_pc", "iconv2d_bottleneck_brelu_pc", "iconv2d_bottleneck_dual_brelu_pc", "iconv2d_pair_brelu_pc", "iconv2d_twin_brelu", "iconv2d_twin_last_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "icnn_run_calls", "icnn_lanes_create", "icnn_lanes_destroy", "icnn_run_lanes", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
            "irenormalize_u8", "icnn_peak_mfma_i8", "icnn_peak_copy"]
 
 
@@ -298,6 +299,11 @@ def iconv2d_twin_brelu(ca, x, wa_packed, bias_a, ya, cb, wb_packed, bias_b, yb, 
                                           _ptr(wb_packed), _ptr(bias_b), _ptr(yb), _stream(stream)))
 
 
+def iconv2d_twin_last_brelu(ca, x, wa_packed, bias_a, cb, wb_packed, bias_b, cc, wc_packed, bias_c, res, y, stream=None):
+    return _check(_lib.iconv2d_twin_last_brelu(C.byref(ca), _ptr(x), _ptr(wa_packed), _ptr(bias_a), C.byref(cb), _ptr(wb_packed), _ptr(bias_b),
+                                               C.byref(cc), _ptr(wc_packed), _ptr(bias_c), _ptr(res), _ptr(y), _stream(stream)))
+
+
 def iconv2d_chain_brelu(descs, x, w_packed, bias, y, stream=None):
     n = len(descs)
     dp = (_descp * n)(*[C.pointer(d) for d in descs])
@@ -340,7 +346,7 @@ class Calls:
         # (kind, integers in the argument list before the first pointer or after the first descriptor)
         c.kind, ints = {"conv": (ICNN_CALL_CONV, 0), "conv_pc": (ICNN_CALL_CONV_PC, 0), "dual": (ICNN_CALL_DUAL, 0),
                         "dual_pc": (ICNN_CALL_DUAL_PC, 0), "convpool": (ICNN_CALL_CONV_MAXPOOL, 3), "block": (ICNN_CALL_BOTTLENECK, 0),
-                        "projblock": (ICNN_CALL_BOTTLENECK_DUAL, 0), "pair": (ICNN_CALL_PAIR, 0), "twin": (ICNN_CALL_TWIN, 0),
+                        "projblock": (ICNN_CALL_BOTTLENECK_DUAL, 0), "pair": (ICNN_CALL_PAIR, 0), "twin": (ICNN_CALL_TWIN, 0), "twin_last": (ICNN_CALL_TWIN_LAST, 0),
                         "convpool_pc": (ICNN_CALL_CONV_MAXPOOL_PC, 3), "block_pc": (ICNN_CALL_BOTTLENECK_PC, 0),
                         "projblock_pc": (ICNN_CALL_BOTTLENECK_DUAL_PC, 0), "pair_pc": (ICNN_CALL_PAIR_PC, 0),
                         "maxpool": (ICNN_CALL_MAXPOOL, 7), "avgpool": (ICNN_CALL_AVGPOOL, 7)}[kind]

@@ -814,8 +814,9 @@ int iconv2d_pair_brelu_pc(const icnn_conv_desc *c3, const void *t, const void *w
     return pair_layers(c3, t, w3_packed, bias3, pc3_packed, res, y, c1, w1_packed, bias1, pc1_packed, z, stream, "iconv2d_pair_brelu_pc");
 }
 
-int iconv2d_twin_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_packed, const int32_t *bias_a, void *ya,
-                       const icnn_conv_desc *cb, const void *wb_packed, const int32_t *bias_b, void *yb, void *stream)
+// Geometry and arguments of two branches of one input
+static int twin_layers(const icnn_conv_desc *ca, const void *x, const void *wa_packed, const int32_t *bias_a, void *ya,
+                       const icnn_conv_desc *cb, const void *wb_packed, const int32_t *bias_b, void *yb, ConvArgs &a, ConvArgs &b)
 {
     ConvGeom ga, gb;
     int rc = check_conv(ca, &ga);
@@ -828,13 +829,42 @@ int iconv2d_twin_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_p
         return fail(ICNN_E_UNSUPPORTED, "twin layers take no skip operands");
     if (ca->in_signed != ICNN_IN_U8_LE127 || ca->in_sub128) return fail(ICNN_E_UNSUPPORTED, "twin layers take unsigned inputs up to 127 only");
     if (!aligned16(x)) return fail(ICNN_E_UNSUPPORTED, "twin layers need a 16-byte aligned input");
-    ConvArgs a, b;
     if ((rc = fill_conv_args(ca, ga, x, wa_packed, bias_a, nullptr, ya, a))) return rc;
     if ((rc = fill_conv_args(cb, gb, x, wb_packed, bias_b, nullptr, yb, b))) return rc;
     if (!conv_plane_twin_ok(a, b))
         return fail(ICNN_E_UNSUPPORTED, "twin layers: a 5x5 layer of 64 channels beside a 3x3, or a 3x3 layer of 48 or 64 channels beside a 1x1, "
                                         "stride 1, \"same\" padding, at most 32 output channels each, tensors below 2 GiB");
+    return ICNN_OK;
+}
+
+int iconv2d_twin_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_packed, const int32_t *bias_a, void *ya,
+                       const icnn_conv_desc *cb, const void *wb_packed, const int32_t *bias_b, void *yb, void *stream)
+{
+    ConvArgs a, b;
+    const int rc = twin_layers(ca, x, wa_packed, bias_a, ya, cb, wb_packed, bias_b, yb, a, b);
+    if (rc) return rc;
     return launched(launch_conv_plane_twin(a, b, (hipStream_t)stream), "iconv2d_twin_brelu");
+}
+
+int iconv2d_twin_last_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_packed, const int32_t *bias_a,
+                            const icnn_conv_desc *cb, const void *wb_packed, const int32_t *bias_b,
+                            const icnn_conv_desc *cc, const void *wc_packed, const int32_t *bias_c, const void *res, void *y, void *stream)
+{
+    ConvArgs a, b, c;
+    int32_t dummy[4] = {0, 0, 0, 0};           // the branches' outputs never reach memory
+    int rc = twin_layers(ca, x, wa_packed, bias_a, dummy, cb, wb_packed, bias_b, dummy, a, b);
+    if (rc) return rc;
+    ConvGeom gc;
+    if ((rc = check_conv(cc, &gc))) return rc;
+    for (const icnn_conv_desc *d : {ca, cb})
+        if ((d->out_mode != ICNN_OUT_BRELU_U8 && d->out_mode != ICNN_OUT_CLAMP_U8) || (d->out_mode == ICNN_OUT_BRELU_U8 ? d->bound_q : d->hi) > 127)
+            return fail(ICNN_E_UNSUPPORTED, "the two branches must store unsigned bytes up to 127");
+    if (cc->in_signed != ICNN_IN_U8_LE127 || cc->in_sub128) return fail(ICNN_E_UNSUPPORTED, "the last layer takes unsigned inputs up to 127 only");
+    if ((rc = fill_conv_args(cc, gc, dummy, wc_packed, bias_c, res, y, c))) return rc;
+    if (!conv_tail_ok(a, b, c))
+        return fail(ICNN_E_UNSUPPORTED, "branches and last layer: 3x3 with 16 outputs beside 1x1 with 32, both of 48 channels and filling 48 between them, then "
+                                        "3x3 with one output, stride 1, \"same\" padding");
+    return launched(launch_conv_tail(a, b, c, (hipStream_t)stream), "iconv2d_twin_last_brelu");
 }
 
 // What every layer of a chain has to be; g: its geometry
@@ -1055,6 +1085,9 @@ static int run_call(int32_t k, const icnn_call &c, void *stream)
         break;
     case ICNN_CALL_PAIR: rc = iconv2d_pair_brelu(d[0], p[0], p[1], b(2), p[3], o(4), d[1], p[5], b(6), o(7), stream); break;
     case ICNN_CALL_TWIN: rc = iconv2d_twin_brelu(d[0], p[0], p[1], b(2), o(3), d[1], p[4], b(5), o(6), stream); break;
+    case ICNN_CALL_TWIN_LAST:
+        rc = iconv2d_twin_last_brelu(d[0], p[0], p[1], b(2), d[1], p[3], b(4), d[2], p[5], b(6), p[7], o(8), stream);
+        break;
     case ICNN_CALL_CHAIN:
         rc = iconv2d_chain_brelu(i[0], (const icnn_conv_desc *const *)c.list[0], p[0], (const void *const *)c.list[1],
                                  (const int32_t *const *)c.list[2], o(1), stream);

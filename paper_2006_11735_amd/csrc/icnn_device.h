@@ -223,6 +223,8 @@ bool conv_plane_applies(const ConvArgs &a);
 hipError_t launch_conv_plane(const ConvArgs &a, hipStream_t st);
 bool conv_plane_twin_ok(const ConvArgs &a, const ConvArgs &b);
 hipError_t launch_conv_plane_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st);
+bool conv_tail_ok(const ConvArgs &a, const ConvArgs &b, const ConvArgs &c);
+hipError_t launch_conv_tail(const ConvArgs &a, const ConvArgs &b, const ConvArgs &c, hipStream_t st);
 bool conv_deep_applies(const ConvArgs &a);
 hipError_t launch_conv_deep(const ConvArgs &a, hipStream_t st);
 int conv_chain_split(int N, int H, int W, int n, int *len);

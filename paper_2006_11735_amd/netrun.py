@@ -43,6 +43,7 @@ class GpuNet:
         self.fused_pool = {}                # first conv name -> the max-pool op fused into its launch
         self.fused_pair = {}                # block-closing conv name -> the next block's opening conv op in its launch
         self.fused_twin = {}                # branch name -> the other branch's op in its launch
+        self.fused_twin_last = {}           # last conv name -> the ops of the two branches before it in its launch
         self.fused_chain = {}               # last conv name -> the conv ops before it in its launch
         self.fused_projblock = {}           # last conv name -> (first, middle, projection) conv ops fused into its launch
         self._packed = {}                   # conv name -> its packed weights, bias and per-channel parameters, shared by the parts
@@ -116,6 +117,7 @@ class GpuNet:
             self._fuse_projection_blocks()
             self._fuse_first_layer()
             self._fuse_pairs()
+            self._fuse_twin_last()
             self._fuse_twins()
             self._fuse_chains()
 
@@ -188,6 +190,41 @@ class GpuNet:
                         self.fused_pair[o3["name"]] = o1
                         steps.append(("pair_pc" if pc else "pair", o3, args))
                         i += 2
+                        continue
+            steps.append(self.steps[i])
+            i += 1
+        self.steps = steps
+
+    # On fewer pixels than a few of the fused kernel's tiles the layers spread better over the chip than one launch does.
+    TWIN_LAST_MIN_PIXELS = 64 * 64
+
+    def _fuse_twin_last(self):
+        """Two branches of one input and the single-channel convolution of their concatenation, nothing else reading that: one
+        iconv2d_twin_last_brelu launch where the library accepts it (the concatenation's buffer then stays untouched)."""
+        readers = self._readers()
+        steps, i = [], 0
+        while i < len(self.steps):
+            trio = self.steps[i:i + 3]
+            if [st[0] for st in trio] == ["conv"] * 3:
+                a, b, (dc, _t, wc, bc, rc, y, _ws) = (st[2] for st in trio)
+                oa, ob, oc = (st[1] for st in trio)
+                if oa["kh"] < ob["kh"]:
+                    a, b, oa, ob = b, a, ob, oa
+                (da, x, wa, ba, ra), (db, _x, wb, bb, rb) = a[:5], b[:5]
+                if (oa["src"] == ob["src"] and oa["dst"] == ob["dst"] == oc["src"] and readers.get(oa["dst"]) == [oc] and ra is None and rb is None and
+                        oa["dst"] not in self.net["outputs"] and oc["dst"] != oa["src"] and
+                        da.n * da.h * da.w >= self.TWIN_LAST_MIN_PIXELS):
+                    args = (da, x, wa, ba, db, wb, bb, dc, wc, bc, rc, y)
+                    try:
+                        B.iconv2d_twin_last_brelu(*args)           # also a warm-up launch
+                    except B.IcnnError as e:
+                        if e.code != B.ICNN_E_UNSUPPORTED:
+                            raise
+                    else:
+                        self.fused.append(oa["dst"])
+                        self.fused_twin_last[oc["name"]] = (oa, ob)
+                        steps.append(("twin_last", oc, args))
+                        i += 3
                         continue
             steps.append(self.steps[i])
             i += 1
@@ -463,7 +500,7 @@ class GpuNet:
         self._FUNCTIONS[kind](*args, stream=stream)
 
     _FUNCTIONS = {"conv": B.iconv2d_brelu, "conv_pc": B.iconv2d_brelu_pc, "dual": B.iconv2d_dual_brelu, "dual_pc": B.iconv2d_dual_brelu_pc,
-                  "pair": B.iconv2d_pair_brelu, "pair_pc": B.iconv2d_pair_brelu_pc, "twin": B.iconv2d_twin_brelu, "chain": B.iconv2d_chain_brelu,
+                  "pair": B.iconv2d_pair_brelu, "pair_pc": B.iconv2d_pair_brelu_pc, "twin": B.iconv2d_twin_brelu, "twin_last": B.iconv2d_twin_last_brelu, "chain": B.iconv2d_chain_brelu,
                   "projblock": B.iconv2d_bottleneck_dual_brelu, "projblock_pc": B.iconv2d_bottleneck_dual_brelu_pc,
                   "block": B.iconv2d_bottleneck_brelu, "block_pc": B.iconv2d_bottleneck_brelu_pc, "convpool": B.iconv2d_maxpool_brelu,
                   "convpool_pc": B.iconv2d_maxpool_brelu_pc, "maxpool": B.imaxpool2d_u8, "avgpool": B.iavgpool_global_u8}

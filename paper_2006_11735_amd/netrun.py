@@ -137,12 +137,7 @@ class GpuNet:
                     pooled = self.buf[op_["dst"]]
                     dd.out_c_stride, dd.out_c_offset = pooled.shape[3], 0
                     args = (dd, op_["k"], op_["stride"], op_["pad"], x, wp, bias) + ((pair[0][2][4],) if pc else ()) + (pooled,)
-                    try:
-                        (B.iconv2d_maxpool_brelu_pc if pc else B.iconv2d_maxpool_brelu)(*args)
-                    except B.IcnnError as e:
-                        if e.code != B.ICNN_E_UNSUPPORTED:
-                            raise
-                    else:
+                    if self._accepts(B.iconv2d_maxpool_brelu_pc if pc else B.iconv2d_maxpool_brelu, args):
                         self.fused.append(oc["dst"])
                         self.fused_pool[oc["name"]] = op_
                         steps.append(("convpool_pc" if pc else "convpool", oc, args))
@@ -181,12 +176,7 @@ class GpuNet:
                         fn, args = B.iconv2d_pair_brelu_pc, (d3, t, w3, b3, two[0][2][4], res, y, d1, w1, b1, two[1][2][4], z)
                     else:
                         fn, args = B.iconv2d_pair_brelu, (d3, t, w3, b3, res, y, d1, w1, b1, z)
-                    try:
-                        fn(*args)                                  # also a warm-up launch
-                    except B.IcnnError as e:
-                        if e.code != B.ICNN_E_UNSUPPORTED:
-                            raise
-                    else:
+                    if self._accepts(fn, args):
                         self.fused_pair[o3["name"]] = o1
                         steps.append(("pair_pc" if pc else "pair", o3, args))
                         i += 2
@@ -216,12 +206,7 @@ class GpuNet:
                         oa["dst"] not in self.net["outputs"] and oc["dst"] != oa["src"] and
                         da.n * da.h * da.w >= self.TWIN_LAST_MIN_PIXELS):
                     args = (da, x, wa, ba, db, wb, bb, dc, wc, bc, rc, y)
-                    try:
-                        B.iconv2d_twin_last_brelu(*args)           # also a warm-up launch
-                    except B.IcnnError as e:
-                        if e.code != B.ICNN_E_UNSUPPORTED:
-                            raise
-                    else:
+                    if self._accepts(B.iconv2d_twin_last_brelu, args):
                         self.fused.append(oa["dst"])
                         self.fused_twin_last[oc["name"]] = (oa, ob)
                         steps.append(("twin_last", oc, args))
@@ -250,12 +235,7 @@ class GpuNet:
                 if (oa["src"] == ob["src"] and oa["kh"] == ob["kh"] + 2 and ra is None and rb is None and
                         oa["dst"] != oa["src"] and ob["dst"] != ob["src"] and da.n * da.h * da.w >= self.TWIN_MIN_PIXELS):
                     args = (da, xa, wa, ba, ya, db, wb, bb, yb)
-                    try:
-                        B.iconv2d_twin_brelu(*args)                # also a warm-up launch
-                    except B.IcnnError as e:
-                        if e.code != B.ICNN_E_UNSUPPORTED:
-                            raise
-                    else:
+                    if self._accepts(B.iconv2d_twin_brelu, args):
                         self.fused_twin[oa["name"]] = ob
                         steps.append(("twin", oa, args))
                         i += 2
@@ -293,7 +273,9 @@ class GpuNet:
                     steps.append(part[0])
                     continue
                 args = ([st[2][0] for st in part], part[0][2][1], [st[2][2] for st in part], [st[2][3] for st in part], part[-1][2][5])
-                B.iconv2d_chain_brelu(*args)                       # also a warm-up launch
+                if not self._accepts(B.iconv2d_chain_brelu, args):
+                    steps += part
+                    continue
                 self.fused += [st[1]["dst"] for st in part[:-1]]
                 self.fused_chain[part[-1][1]["name"]] = [st[1] for st in part[:-1]]
                 steps.append(("chain", part[-1][1], args))
@@ -317,6 +299,17 @@ class GpuNet:
                 break
             n += 1
         return run[:n] if n > 1 else None
+
+    @staticmethod
+    def _accepts(fn, args):
+        """Issues a fused call, which is also its warm-up launch; False if the library does not take it."""
+        try:
+            fn(*args)
+        except B.IcnnError as e:
+            if e.code != B.ICNN_E_UNSUPPORTED:
+                raise
+            return False
+        return True
 
     @staticmethod
     def _conv_args(step):
@@ -359,12 +352,7 @@ class GpuNet:
                     else:
                         dm, _xm, wm, bm, dp, _xp, wp, bp, y = trio[2][2]
                         fn, args = B.iconv2d_bottleneck_dual_brelu, (d1, x, w1, b1, d2, w2, b2, dm, wm, bm, dp, wp, bp, y)
-                    try:
-                        fn(*args)                                  # also a warm-up launch
-                    except B.IcnnError as e:
-                        if e.code != B.ICNN_E_UNSUPPORTED:
-                            raise
-                    else:
+                    if self._accepts(fn, args):
                         self.fused += [o1["dst"], o2["dst"]]
                         self.fused_projblock[o3["name"]] = (o1, o2, proj)
                         steps.append(("projblock_pc" if pc else "projblock", o3, args))
@@ -399,12 +387,7 @@ class GpuNet:
                         fn, args = B.iconv2d_bottleneck_brelu_pc, (d1, x, w1, b1, pc1, d2, w2, b2, pc2, d3, w3, b3, pc3, res, y)
                     else:
                         fn, args = B.iconv2d_bottleneck_brelu, (d1, x, w1, b1, d2, w2, b2, d3, w3, b3, res, y)
-                    try:
-                        fn(*args)                                  # also a warm-up launch
-                    except B.IcnnError as e:
-                        if e.code != B.ICNN_E_UNSUPPORTED:
-                            raise
-                    else:
+                    if self._accepts(fn, args):
                         self.fused += [o1["dst"], o2["dst"]]
                         (self.fused_block_pc if pc else self.fused_block)[o3["name"]] = (o1, o2)
                         steps.append(("block_pc" if pc else "block", o3, args))
@@ -481,13 +464,7 @@ class GpuNet:
         else:
             dm, xm, wm, bm, _res, y, _ws = main[2]
             kind, fn, args = "dual", B.iconv2d_dual_brelu, (dm, xm, wm, bm, dp, xp, wp, bp, y)
-        try:
-            fn(*args)                       # also a warm-up launch
-        except B.IcnnError as e:
-            if e.code == B.ICNN_E_UNSUPPORTED:
-                return None
-            raise
-        return (kind, main[1], args)
+        return (kind, main[1], args) if self._accepts(fn, args) else None
 
     def set_input(self, x_raw=None):
         if x_raw is None:

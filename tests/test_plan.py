@@ -1,0 +1,54 @@
+"""What `netrun` plans for networks other than the stored configurations: channel slices, buffers that are used again, pitches the fused
+launches do not take.  Every plan is run on the CPU (tests/cpu_library.py) and has to give the oracle's bytes."""
+import pytest
+import torch
+
+import cpu_library
+from oracle import calibrate as K
+from workloads import nets as W
+
+pytestmark = pytest.mark.skipif(torch.cuda.is_available(), reason="plans are run without a GPU")
+
+
+@pytest.fixture(autouse=True)
+def library(monkeypatch):
+    return cpu_library.install(monkeypatch)
+
+
+def builder(n, h, w, c, top=W.ACT_MAX):
+    b = W._Builder("net", n, h, w, c, n)
+    b.net["input_range"] = [0, top]
+    return b
+
+
+def integers(net):
+    """Requantisation that keeps outputs spread over their range, without a calibration run: uniform bytes times uniform weights"""
+    conv = {}
+    for op in W.conv_ops(net):
+        sigma = 127 * 127 / 3 * (op["kh"] * op["kw"] * op["cin"]) ** 0.5
+        mul, shift = K.bound_params(int(2 * sigma), K.MAX_INT)
+        conv[op["name"]] = dict(mul=mul, shift=shift, bound_q=K.MAX_INT, lo=0, hi=255, res_mul=20000, res_shift=15 if op["res_dtype"] == "s32" else 5)
+    pool = {op["dst"]: dict(mul=K.mul_shift(64, 1)[0], shift=K.mul_shift(64, 1)[1], bound_q=K.MAX_INT) for op in net["ops"] if op["op"] == "avgpool"}
+    return {"conv": conv, "avgpool": pool, "max_int": K.MAX_INT}
+
+
+def straight(layers, last_total=None):
+    b = builder(1, 64, 64, 64)
+    cur = "raw"
+    for i in range(layers):
+        last = i + 1 == layers
+        cur = b.conv("c%d" % i, cur, "out" if last else "t%d" % i, 64, 3, dst_c_total=last_total if last else None)
+    b.net["outputs"] = ["out"]
+    return b.net
+
+
+def test_a_run_of_layers_is_one_chain():
+    net = straight(3)
+    g = cpu_library.check(net, integers(net))
+    assert [st[0] for st in g.steps] == ["chain"]
+
+
+def test_a_chain_the_library_refuses_runs_layer_by_layer():
+    net = straight(3, last_total=72)                   # the last layer writes 64 of 72 channels: no 16-byte pitch
+    g = cpu_library.check(net, integers(net))
+    assert [st[0] for st in g.steps] == ["conv"] * 3 and not g.fused and not g.fused_chain

@@ -394,7 +394,7 @@ int iconv2d_twin_last_brelu(const icnn_conv_desc *ca, const void *x, const void 
  *     iconv2d_brelu(descs[1], t0, w_packed[1], bias[1], NULL, t1, ...);    ...    the last one writing y
  * without the middle tensors ever existing (every workgroup takes a tile of the picture through all layers and recomputes
  * the borders it needs).  The arrays are host memory holding host pointers to descriptors and device pointers to the
- * layers' packed weights and biases; y must not overlap x.  Shapes it takes: 1 to 6 layers, all 3x3 / stride 1 / padding 1 with
+ * layers' packed weights and biases; y must not overlap x (disjoint channel ranges of one buffer do not).  Shapes it takes: 1 to 6 layers, all 3x3 / stride 1 / padding 1 with
  * 64 input and 64 output channels, unsigned inputs (up to 127, or full range), unsigned 8-bit outputs, no skip operands;
  * x, y and their pitches 16-byte aligned; tensors below 2 GiB.  The pitches and offsets of the middle tensors are not used.  Anything
  * else returns ICNN_E_UNSUPPORTED having launched nothing, and the caller issues the layers separately.

@@ -124,6 +124,38 @@ int launched(hipError_t e, const char *what)
 
 int dtype_bytes(int dt) { return dt == ICNN_S32 ? 4 : 1; }
 
+// The bytes of a channel slice: `width` bytes at every multiple of `pitch` from `at`, up to `end`
+struct Slice {
+    uintptr_t at, end;
+    unsigned long long pitch, width;
+};
+
+Slice slice_of(const void *p, long long pixels, int c_stride, int c_offset, int c, int item)
+{
+    Slice s;
+    s.pitch = (unsigned long long)c_stride * item;
+    s.width = (unsigned long long)c * item;
+    s.at = (uintptr_t)p + (uintptr_t)c_offset * item;
+    s.end = s.at + (uintptr_t)(pixels - 1) * s.pitch + s.width;
+    return s;
+}
+
+Slice input_slice(const icnn_conv_desc *d, const void *x) { return slice_of(x, (long long)d->n * d->h * d->w, d->in_c_stride, 0, d->cin, 1); }
+
+Slice output_slice(const icnn_conv_desc *d, const ConvGeom &g, const void *y)
+{
+    return slice_of(y, g.M, d->out_c_stride, d->out_c_offset, d->cout, d->out_mode == ICNN_OUT_RAW_S32 ? 4 : 1);
+}
+
+// Do two slices share a byte?  Disjoint channel ranges of one buffer do not; address ranges that interleave with different pitches count as shared.
+bool overlap(const Slice &a, const Slice &b)
+{
+    if (a.at >= b.end || b.at >= a.end) return false;
+    if (a.pitch != b.pitch) return true;
+    const unsigned long long d = b.at >= a.at ? (b.at - a.at) % a.pitch : (a.pitch - (a.at - b.at) % a.pitch) % a.pitch;
+    return !(d >= a.width && d + b.width <= a.pitch);
+}
+
 }  // namespace
 
 extern "C" {
@@ -899,6 +931,7 @@ int iconv2d_chain_brelu(int32_t n_layers, const icnn_conv_desc *const *descs, co
     if (n_layers < 1) return fail(ICNN_E_SHAPE, "a chain has at least one layer");
     if (n_layers > kChainMaxLayers) return fail(ICNN_E_UNSUPPORTED, "one launch takes at most %d layers (iconv2d_chain_split)", kChainMaxLayers);
     ChainArgs c;
+    Slice in = {0, 0, 0, 0};
     for (int i = 0; i < n_layers; ++i) {
         const icnn_conv_desc *d = descs[i];
         ConvGeom g;
@@ -914,8 +947,11 @@ int iconv2d_chain_brelu(int32_t n_layers, const icnn_conv_desc *const *descs, co
             if (a.x_bytes >= 0x7fffff00u || g.M > 0x7fffffffLL) return fail(ICNN_E_UNSUPPORTED, "a chain needs tensors below 2 GiB");
             c.x = a.x; c.x_bytes = a.x_bytes; c.in_cs = d->in_c_stride;
             c.N = d->n; c.H = d->h; c.W = d->w; c.L = n_layers;
+            in = input_slice(d, x);
         }
         if (i + 1 == n_layers) {
+            // (a workgroup reads borders that others write)
+            if (overlap(in, output_slice(d, g, y))) return fail(ICNN_E_UNSUPPORTED, "a chain's output must not overlap its input");
             if (!a.vec_out) return fail(ICNN_E_UNSUPPORTED, "a chain needs a 16-byte aligned output");
             c.out = (uint8_t *)y; c.out_cs = d->out_c_stride; c.out_co = d->out_c_offset;
         }

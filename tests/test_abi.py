@@ -153,6 +153,26 @@ def test_twin_layers_are_refused_on_the_host_where_the_fused_kernel_does_not_tak
     assert e.value.code == B.ICNN_E_UNSUPPORTED                                              # misaligned input
 
 
+def test_a_chain_refuses_an_output_over_its_input():
+    B = binding()
+    x, w, bias = 1 << 20, 1 << 30, 1 << 31
+    size = 16 * 16 * 64
+
+    def code(y, in_pitch=64, out_pitch=64, offset=0):
+        first, last = good(B, h=16, w=16, in_c_stride=in_pitch), good(B, h=16, w=16, out_c_stride=out_pitch, out_c_offset=offset)
+        with pytest.raises(B.IcnnError) as e:
+            B.iconv2d_chain_brelu([first, last], x, [w] * 2, [bias] * 2, y, stream=0)
+        return e.value.code
+    overlapping = [(x,), (x + size - 64,), (x - size + 64,), (x, 128, 128, 0), (x, 128, 128, 32), (x + 32, 128, 128, 0), (x - 16, 128, 128, 0),
+                   (x, 128, 192, 64)]
+    for case in overlapping:
+        assert code(*case) == B.ICNN_E_UNSUPPORTED, case
+    import torch
+    if not torch.cuda.is_available():                    # accepted: the launch itself fails where there is no GPU
+        for case in [(x + size,), (x - size,), (x, 128, 128, 64), (x + 64, 128, 128, 0), (x - 64, 128, 128, 0), (x, 192, 192, 112)]:
+            assert code(*case) == B.ICNN_E_LAUNCH, case
+
+
 def test_tuning_overrides_are_validated():
     B = binding()
     try:

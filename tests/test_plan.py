@@ -52,3 +52,14 @@ def test_a_chain_the_library_refuses_runs_layer_by_layer():
     net = straight(3, last_total=72)                   # the last layer writes 64 of 72 channels: no 16-byte pitch
     g = cpu_library.check(net, integers(net))
     assert [st[0] for st in g.steps] == ["conv"] * 3 and not g.fused and not g.fused_chain
+
+
+def test_buffers_used_in_turn():
+    # a -> b, b -> a, a -> out: a chain from a to a would write what its other workgroups read
+    b = builder(1, 64, 64, 64)
+    b.conv("c0", "raw", "a", 64, 3)
+    b.conv("c1", "a", "b", 64, 3)
+    b.conv("c2", "b", "a", 64, 3)
+    b.conv("c3", "a", "out", 64, 3)
+    b.net["outputs"] = ["out"]
+    cpu_library.check(b.net, integers(b.net))

@@ -257,8 +257,7 @@ class GpuNet:
             run = [self.steps[i]]
             while i + len(run) < len(self.steps):
                 a, b = run[-1], self.steps[i + len(run)]
-                if (a[0] != "conv" or b[0] != "conv" or b[1]["src"] != a[1]["dst"] or readers.get(a[1]["dst"]) != [b[1]] or
-                        a[1]["dst"] in self.net["outputs"]):
+                if a[0] != "conv" or b[0] != "conv" or not self._only_feeds(a[1], b[1], readers):
                     break
                 run.append(b)
             run = self._chain_part(run)
@@ -325,6 +324,13 @@ class GpuNet:
             if op.get("res") is not None:
                 readers.setdefault(op["res"], []).append(op)
         return readers
+
+    def _only_feeds(self, a, b, readers):
+        """Whether op b reads what op a writes, all of it and nothing beside it, and nothing else ever does: the tensor between
+        them may stay on chip."""
+        width = self.net["buffers"][a["dst"]]["shape"][3]
+        return (b["src"] == a["dst"] and readers.get(a["dst"]) == [b] and a["dst"] not in self.net["outputs"] and
+                a["dst_c_offset"] == 0 and a["cout"] == b.get("cin", width))
 
     def _fuse_projection_blocks(self):
         """A stage's opening bottleneck block whose last layer already runs with its projection as one dual step: the

@@ -63,3 +63,23 @@ def test_buffers_used_in_turn():
     b.conv("c3", "a", "out", 64, 3)
     b.net["outputs"] = ["out"]
     cpu_library.check(b.net, integers(b.net))
+
+
+def test_a_layer_that_reads_another_slice_than_the_last_one_written():
+    # p fills cat[0:64], q cat[64:128], r reads cat[0:64]: r follows q in the list and takes nothing from it
+    b = builder(1, 64, 64, 64)
+    b.conv("p", "raw", "cat", 64, 3, dst_c_total=128)
+    b.conv("q", "raw", "cat", 64, 3, dst_c_total=128, dst_c_offset=64)
+    b.conv("r", "cat", "out", 64, 3, src_c=64)
+    b.net["outputs"] = ["out"]
+    g = cpu_library.check(b.net, integers(b.net))
+    assert not g.fused_chain
+
+
+def test_a_layer_that_reads_more_than_the_last_one_wrote():
+    b = builder(1, 64, 64, 64)
+    b.conv("p", "raw", "cat", 64, 3, dst_c_total=128, dst_c_offset=64)
+    b.conv("q", "raw", "cat", 64, 3, dst_c_total=128)
+    b.conv("r", "cat", "out", 64, 3)                   # all 128 channels
+    b.net["outputs"] = ["out"]
+    cpu_library.check(b.net, integers(b.net))

@@ -130,7 +130,7 @@ class GpuNet:
             pair = self.steps[i:i + 2]
             if len(pair) == 2 and pair[0][0] in ("conv", "conv_pc") and pair[1][0] == "maxpool":
                 oc, op_ = pair[0][1], pair[1][1]
-                if op_["src"] == oc["dst"] and readers.get(oc["dst"]) == [op_] and oc["dst"] not in self.net["outputs"]:
+                if self._only_feeds(oc, op_, readers):
                     pc = pair[0][0] == "conv_pc"
                     d, x, wp, bias = pair[0][2][:4]
                     dd = B.conv_desc(**{k: getattr(d, k) for k, _ in d._fields_})
@@ -344,10 +344,7 @@ class GpuNet:
                 pc = trio[2][0] == "dual_pc"
                 o1, o2, o3 = (st[1] for st in trio)
                 proj = self.fused_proj[o3["name"]]
-                chain = (o2["src"] == o1["dst"] and o3["src"] == o2["dst"] and proj["src"] == o1["src"] and
-                         readers.get(o1["dst"]) == [o2] and readers.get(o2["dst"]) == [o3] and
-                         o1["dst"] not in self.net["outputs"] and o2["dst"] not in self.net["outputs"] and
-                         o1["dst_c_offset"] == 0 and o2["dst_c_offset"] == 0)
+                chain = proj["src"] == o1["src"] and self._only_feeds(o1, o2, readers) and self._only_feeds(o2, o3, readers)
                 if chain:
                     d1, x, w1, b1 = trio[0][2][:4]
                     d2, _x2, w2, b2 = trio[1][2][:4]
@@ -381,10 +378,7 @@ class GpuNet:
             if [st[0] for st in trio] in (["conv"] * 3, ["conv_pc"] * 3):
                 pc = trio[0][0] == "conv_pc"
                 o1, o2, o3 = (st[1] for st in trio)
-                chain = (o2["src"] == o1["dst"] and o3["src"] == o2["dst"] and o3["res"] == o1["src"] and
-                         readers.get(o1["dst"]) == [o2] and readers.get(o2["dst"]) == [o3] and
-                         o1["dst"] not in self.net["outputs"] and o2["dst"] not in self.net["outputs"] and
-                         o1["dst_c_offset"] == 0 and o2["dst_c_offset"] == 0)
+                chain = o3["res"] == o1["src"] and self._only_feeds(o1, o2, readers) and self._only_feeds(o2, o3, readers)
                 d1 = trio[0][2][0]
                 if chain and (o1["cout"] != 128 or d1.n * d1.h * d1.w >= self.BLOCK128_MIN_PIXELS):
                     (d1, x, w1, b1, _r1, _y1), (d2, _x2, w2, b2, _r2, _y2), (d3, _x3, w3, b3, res, y) = (self._conv_args(st) for st in trio)

@@ -83,3 +83,18 @@ def test_a_layer_that_reads_more_than_the_last_one_wrote():
     b.conv("r", "cat", "out", 64, 3)                   # all 128 channels
     b.net["outputs"] = ["out"]
     cpu_library.check(b.net, integers(b.net))
+
+
+def test_a_pool_over_more_channels_than_the_layer_before_it_wrote():
+    b = builder(1, 32, 32, 3, 255)
+    b.conv("side", "raw", "cat", 32, 7, stride=2, pad=3, in_sub128=True, dst_c_total=64, dst_c_offset=32)
+    b.conv("stem", "raw", "cat", 32, 7, stride=2, pad=3, in_sub128=True, dst_c_total=64)
+    b.maxpool("cat", "pool")
+    b.net["outputs"] = ["pool"]
+    g = cpu_library.check(b.net, integers(b.net))
+    assert not g.fused_pool
+    b = builder(1, 32, 32, 3, 255)
+    b.conv("stem", "raw", "t", 32, 7, stride=2, pad=3, in_sub128=True)
+    b.maxpool("t", "pool")
+    b.net["outputs"] = ["pool"]
+    assert cpu_library.check(b.net, integers(b.net)).fused_pool

@@ -301,11 +301,12 @@ class GpuNet:
 
     @staticmethod
     def _accepts(fn, args):
-        """Issues a fused call, which is also its warm-up launch; False if the library does not take it."""
+        """Issues a fused call, which is also its warm-up launch; False if the library does not take it: layers that are valid by
+        themselves (their workspace has been asked for) and do not fit together are refused as a shape or a parameter, too."""
         try:
             fn(*args)
         except B.IcnnError as e:
-            if e.code != B.ICNN_E_UNSUPPORTED:
+            if e.code not in (B.ICNN_E_UNSUPPORTED, B.ICNN_E_SHAPE, B.ICNN_E_PARAM):
                 raise
             return False
         return True

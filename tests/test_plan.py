@@ -98,3 +98,29 @@ def test_a_pool_over_more_channels_than_the_layer_before_it_wrote():
     b.maxpool("t", "pool")
     b.net["outputs"] = ["pool"]
     assert cpu_library.check(b.net, integers(b.net)).fused_pool
+
+
+def block(middle=None, pad=0, inplace=False, projection=None, res_mode="pre"):
+    """An identity (or, with a projection, opening) bottleneck block of 64 channels.  middle: the second layer reads that many channels;
+    pad: of the first layer, taken back by the second"""
+    b = builder(1, 16, 16, 64)
+    b.conv("c0", "raw", "x", 64, 1)
+    if middle:
+        b.conv("side", "raw", "t", middle - 64, 1, dst_c_total=middle, dst_c_offset=64)
+    b.conv("c1", "x", "t", 64, 1, pad=pad, dst_c_total=middle)
+    b.conv("c2", "t", "u", 64, 3, pad=1 - pad)
+    skip = "x"
+    if projection:
+        skip = b.conv("proj", "x", "sk", projection, 1, out_mode="raw_s32", role="projection")
+    b.conv("c3", "u", "x" if inplace else "y", projection or 64, 1, res=skip, res_mode=res_mode)
+    b.net["outputs"] = ["x" if inplace else "y"]
+    return b.net
+
+
+@pytest.mark.parametrize("kw, kinds", [
+    (dict(), ["conv", "block"]), (dict(middle=128), ["conv"] * 5), (dict(pad=1), ["conv"] * 4), (dict(projection=256), ["conv", "projblock"]),
+    (dict(projection=256, res_mode="post"), ["conv"] * 5), (dict(projection=256, pad=1), ["conv"] * 3 + ["dual"]),
+], ids=str)
+def test_bottleneck_blocks_of_other_forms(kw, kinds):
+    net = block(**kw)
+    assert [st[0] for st in cpu_library.check(net, integers(net)).steps] == kinds

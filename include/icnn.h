@@ -14,6 +14,10 @@
  *   - Activations are NHWC, 8 bits per element.  "Channel pitch" (c_stride) is
  *     the number of elements between consecutive pixels; it may exceed the
  *     channel count so that a layer can read or write a slice of a wider buffer.
+ *   - A fused call (several layers in one launch) whose output overlaps an input
+ *     of its first layers, where the separate calls would have read that input to
+ *     the end before writing, returns ICNN_E_UNSUPPORTED.  Disjoint channel ranges
+ *     of one buffer do not overlap.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Calls enqueue work and return; they never synchronise.
  *   - Return value: 0 on success, a negative icnn_status otherwise.  Arguments

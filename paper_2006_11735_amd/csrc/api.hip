@@ -156,6 +156,13 @@ bool overlap(const Slice &a, const Slice &b)
     return !(d >= a.width && d + b.width <= a.pitch);
 }
 
+// ... of different pixels (both tensors of one geometry): a kernel whose workgroups read all of their pixels before they write them may
+// write over an input in place
+bool overlap_beyond_pixels(const Slice &a, const void *a_base, const Slice &b, const void *b_base)
+{
+    return overlap(a, b) && !(a_base == b_base && a.pitch == b.pitch);
+}
+
 }  // namespace
 
 extern "C" {
@@ -532,6 +539,8 @@ static int dual_layer(const icnn_conv_desc *m, const void *x_main, const void *w
         return fail(ICNN_E_UNSUPPORTED, "fused block needs 16-byte aligned tensors");
     if (!merged_sum_fits(gm.K, gp.K, m->res_mul, m->res_shift))
         return fail(ICNN_E_UNSUPPORTED, "cannot prove that the merged sum stays inside int32 for these sizes");
+    if (overlap(output_slice(m, gm, y), input_slice(m, x_main)) || overlap(output_slice(m, gm, y), input_slice(p, x_proj)))
+        return fail(ICNN_E_UNSUPPORTED, "the fused block's output must not overlap its inputs");
     ConvArgs a, b;
     // the main layer's arguments without its skip operand (the projection is accumulated in registers)
     icnn_conv_desc m0 = *m;
@@ -607,6 +616,8 @@ static int maxpool_layer(const icnn_conv_desc *d, int32_t pool_k, int32_t pool_s
     if (xb > 0x7fffffffull || g.M > 0x7fffffffLL) return fail(ICNN_E_UNSUPPORTED, "fused first layer needs tensors below 2 GiB");
     if (xb < 4) return fail(ICNN_E_UNSUPPORTED, "fused first layer reads the picture four bytes at a time: it needs at least four");
     const int hp = (g.ho + 2 * pool_pad - pool_k) / pool_stride + 1, wp = (g.wo + 2 * pool_pad - pool_k) / pool_stride + 1;
+    if (overlap(slice_of(y, (long long)d->n * hp * wp, d->out_c_stride, d->out_c_offset, d->cout, 1), input_slice(d, x)))
+        return fail(ICNN_E_UNSUPPORTED, "the pooled output must not overlap the picture");
     return launched(launch_conv_stem_pool(a, hp, wp, (hipStream_t)stream), what);
 }
 
@@ -663,6 +674,7 @@ static int bottleneck(const icnn_conv_desc *c1, const void *x, const void *w1_pa
     if ((rc = fill_conv_args(c3, g3, x, w3_packed, bias3, res, y, a3))) return rc;
     if ((rc = take_pc(a1, pc1)) || (rc = take_pc(a2, pc2)) || (rc = take_pc(a3, pc3))) return rc;
     if (!a3.epi_vec) return fail(ICNN_E_UNSUPPORTED, "fused block needs 16-byte aligned output and skip tensors");
+    if (overlap(output_slice(c3, g3, y), input_slice(c1, x))) return fail(ICNN_E_UNSUPPORTED, "the fused block's output must not overlap its input");
     if (!a1.vec_bias || !a2.vec_bias || !a3.vec_bias) return fail(ICNN_E_UNSUPPORTED, "fused block needs 16-byte aligned bias arrays");
     if (a1.x_bytes >= 0x7fffff00u || a1.wp_bytes >= 0x7fffff00u || a2.wp_bytes >= 0x7fffff00u || a3.wp_bytes >= 0x7fffff00u)
         return fail(ICNN_E_UNSUPPORTED, "fused block needs tensors below 2 GiB");
@@ -749,6 +761,7 @@ static int bottleneck_dual(const icnn_conv_desc *c1, const void *x, const void *
     if ((rc = fill_conv_args(cp, gp, x, wp_packed, biasp, nullptr, &dummy, ap))) return rc;
     if ((rc = take_pc(a1, pc1)) || (rc = take_pc(a2, pc2)) || (rc = take_pc(a3, pc3))) return rc;
     if (!a3.epi_vec) return fail(ICNN_E_UNSUPPORTED, "fused block needs a 16-byte aligned output");
+    if (overlap(output_slice(c3, g3, y), input_slice(c1, x))) return fail(ICNN_E_UNSUPPORTED, "the fused block's output must not overlap its input");
     if (!a1.vec_bias || !a2.vec_bias || !a3.vec_bias || !ap.vec_bias) return fail(ICNN_E_UNSUPPORTED, "fused block needs 16-byte aligned bias arrays");
     if (a1.x_bytes >= 0x7fffff00u || g1.M > 0x7fffffffLL) return fail(ICNN_E_UNSUPPORTED, "fused block needs tensors below 2 GiB");
     ProjArgs q = {};
@@ -828,6 +841,15 @@ static int pair_layers(const icnn_conv_desc *c3, const void *t, const void *w3_p
         (unsigned long long)g3.M * c3->out_c_stride >= 0x7fffff00ull ||
         (c3->res_mode != ICNN_RES_NONE && (unsigned long long)g3.M * c3->res_c_stride >= 0x7fffff00ull))
         return fail(ICNN_E_UNSUPPORTED, "fused pair needs tensors below 2 GiB");
+    {
+        const Slice st = input_slice(c3, t), sy = output_slice(c3, g3, y), sz = output_slice(c1, g1, z);
+        bool clash = overlap(sy, sz) || overlap_beyond_pixels(sy, y, st, t) || overlap_beyond_pixels(sz, z, st, t);
+        if (c3->res_mode != ICNN_RES_NONE) {
+            const Slice sr = slice_of(res, g3.M, c3->res_c_stride, 0, c3->cout, 1);
+            clash = clash || overlap_beyond_pixels(sy, y, sr, res) || overlap_beyond_pixels(sz, z, sr, res);
+        }
+        if (clash) return fail(ICNN_E_UNSUPPORTED, "the outputs of a fused pair must not overlap each other or other pixels' inputs");
+    }
     if (conv_pair_lds_bytes(c3->cout, c1->cout, pc3 != nullptr) > 160 * 1024) return fail(ICNN_E_UNSUPPORTED, "the tile of the wide tensor does not fit the on-chip memory");
     return launched(launch_conv_pair(a3, a1, g3.M, (hipStream_t)stream), what);
 }
@@ -873,8 +895,12 @@ int iconv2d_twin_brelu(const icnn_conv_desc *ca, const void *x, const void *wa_p
                        const icnn_conv_desc *cb, const void *wb_packed, const int32_t *bias_b, void *yb, void *stream)
 {
     ConvArgs a, b;
-    const int rc = twin_layers(ca, x, wa_packed, bias_a, ya, cb, wb_packed, bias_b, yb, a, b);
-    if (rc) return rc;
+    ConvGeom ga, gb;
+    int rc = twin_layers(ca, x, wa_packed, bias_a, ya, cb, wb_packed, bias_b, yb, a, b);
+    if (rc || (rc = check_conv(ca, &ga)) || (rc = check_conv(cb, &gb))) return rc;
+    const Slice in = input_slice(ca, x), oa = output_slice(ca, ga, ya), ob = output_slice(cb, gb, yb);
+    if (overlap(in, oa) || overlap(in, ob) || overlap(oa, ob))
+        return fail(ICNN_E_UNSUPPORTED, "the outputs of twin layers must not overlap each other or their input");
     return launched(launch_conv_plane_twin(a, b, (hipStream_t)stream), "iconv2d_twin_brelu");
 }
 
@@ -893,6 +919,7 @@ int iconv2d_twin_last_brelu(const icnn_conv_desc *ca, const void *x, const void 
             return fail(ICNN_E_UNSUPPORTED, "the two branches must store unsigned bytes up to 127");
     if (cc->in_signed != ICNN_IN_U8_LE127 || cc->in_sub128) return fail(ICNN_E_UNSUPPORTED, "the last layer takes unsigned inputs up to 127 only");
     if ((rc = fill_conv_args(cc, gc, dummy, wc_packed, bias_c, res, y, c))) return rc;
+    if (overlap(input_slice(ca, x), output_slice(cc, gc, y))) return fail(ICNN_E_UNSUPPORTED, "the last layer's output must not overlap the branches' input");
     if (!conv_tail_ok(a, b, c))
         return fail(ICNN_E_UNSUPPORTED, "branches and last layer: 3x3 with 16 outputs beside 1x1 with 32, both of 48 channels and filling 48 between them, then "
                                         "3x3 with one output, stride 1, \"same\" padding");

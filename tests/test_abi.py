@@ -173,6 +173,66 @@ def test_a_chain_refuses_an_output_over_its_input():
             assert code(*case) == B.ICNN_E_LAUNCH, case
 
 
+def test_fused_launches_refuse_outputs_over_what_other_workgroups_read():
+    B = binding()
+    import torch
+    accepted = None if torch.cuda.is_available() else B.ICNN_E_LAUNCH      # the launch itself fails where there is no GPU
+    x, t, y, z, w, bias = (k << 24 for k in range(1, 7))
+
+    def code(fn, *args):
+        with pytest.raises(B.IcnnError) as e:
+            fn(*args, stream=0)
+        return e.value.code
+
+    def one(cin, cout, **kw):
+        return good(B, **{**dict(h=16, w=16, cin=cin, in_c_stride=cin, cout=cout, kh=1, kw=1, pad_h=0, pad_w=0, out_c_stride=cout), **kw})
+    mid = good(B, h=16, w=16)
+    skip = dict(res_mode=B.ICNN_RES_PRE, res_c_stride=64, res_mul=3, res_shift=5)
+    proj = dict(res_mode=B.ICNN_RES_PRE, res_dtype=B.ICNN_S32, res_c_stride=256, res_mul=3, res_shift=12)
+    raw = one(64, 256, out_mode=B.ICNN_OUT_RAW_S32)
+    last = one(64, 256, **proj)
+    wide = one(256, 1024, res_mode=B.ICNN_RES_PRE, res_c_stride=1024, res_mul=3, res_shift=5)
+    pix = 16 * 16
+    cases = [
+        # (overlapping?, call)
+        (True, (B.iconv2d_bottleneck_brelu, one(64, 64), x, w, bias, mid, w, bias, one(64, 64, **skip), w, bias, x, x)),
+        (False, (B.iconv2d_bottleneck_brelu, one(64, 64), x, w, bias, mid, w, bias, one(64, 64, **skip), w, bias, x, y)),
+        (True, (B.iconv2d_bottleneck_dual_brelu, one(64, 64), x, w, bias, mid, w, bias, last, w, bias, raw, w, bias, x - pix * 255)),
+        (False, (B.iconv2d_bottleneck_dual_brelu, one(64, 64), x, w, bias, mid, w, bias, last, w, bias, raw, w, bias, x - pix * 256)),
+        (True, (B.iconv2d_dual_brelu, last, t, w, bias, raw, x, w, bias, x)),
+        (True, (B.iconv2d_dual_brelu, last, t, w, bias, raw, x, w, bias, t)),
+        (False, (B.iconv2d_dual_brelu, last, t, w, bias, raw, x, w, bias, y)),
+        # a pair may write over its own pixels' inputs, not over its other output or another pixel's input
+        (False, (B.iconv2d_pair_brelu, wide, t, w, bias, x, y, one(1024, 256), w, bias, t)),
+        (False, (B.iconv2d_pair_brelu, wide, t, w, bias, x, x, one(1024, 256), w, bias, z)),
+        (True, (B.iconv2d_pair_brelu, wide, t, w, bias, x, y, one(1024, 256), w, bias, t + 256)),
+        (True, (B.iconv2d_pair_brelu, wide, t, w, bias, x, y, one(1024, 256), w, bias, y)),
+        (True, (B.iconv2d_pair_brelu, wide, t, w, bias, x, y, one(1024, 256), w, bias, x + 1024 * 16)),
+        (True, (B.iconv2d_maxpool_brelu, good(B, h=32, w=32, cin=3, in_c_stride=3, kh=7, kw=7, stride_h=2, stride_w=2, pad_h=3, pad_w=3, in_sub128=1), 3, 2, 1,
+                x, w, bias, x + 16)),
+        (False, (B.iconv2d_maxpool_brelu, good(B, h=32, w=32, cin=3, in_c_stride=3, kh=7, kw=7, stride_h=2, stride_w=2, pad_h=3, pad_w=3, in_sub128=1), 3, 2, 1,
+                 x, w, bias, y)),
+    ]
+
+    def branch(k, cout, offset, **kw):
+        return good(B, **{**dict(h=32, w=64, cout=cout, kh=k, kw=k, pad_h=k // 2, pad_w=k // 2, out_c_stride=48, out_c_offset=offset), **kw})
+    cases += [
+        (False, (B.iconv2d_twin_brelu, branch(5, 32, 0), x, w, bias, y, branch(3, 16, 32), w, bias, y)),
+        (True, (B.iconv2d_twin_brelu, branch(5, 32, 0), x, w, bias, y, branch(3, 16, 16), w, bias, y)),
+        (True, (B.iconv2d_twin_brelu, branch(5, 32, 0), x, w, bias, x, branch(3, 16, 32), w, bias, y)),
+        (True, (B.iconv2d_twin_brelu, branch(5, 32, 0), x, w, bias, y, branch(3, 16, 32), w, bias, x + 64 * 64)),
+    ]
+    narrow = dict(cin=48, in_c_stride=48)
+    tail = good(B, h=32, w=64, cout=1, out_c_stride=1, **narrow)
+    for at, over in ((y, False), (x, True), (x + 32 * 64 * 48 - 1, True), (x + 32 * 64 * 48, False)):
+        cases.append((over, (B.iconv2d_twin_last_brelu, branch(3, 16, 0, **narrow), x, w, bias, branch(1, 32, 16, **narrow), w, bias, tail, w, bias, None, at)))
+    for over, call in cases:
+        if over:
+            assert code(*call) == B.ICNN_E_UNSUPPORTED, call
+        elif accepted is not None:
+            assert code(*call) == accepted, call
+
+
 def test_tuning_overrides_are_validated():
     B = binding()
     try:

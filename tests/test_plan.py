@@ -119,8 +119,40 @@ def block(middle=None, pad=0, inplace=False, projection=None, res_mode="pre"):
 
 @pytest.mark.parametrize("kw, kinds", [
     (dict(), ["conv", "block"]), (dict(middle=128), ["conv"] * 5), (dict(pad=1), ["conv"] * 4), (dict(projection=256), ["conv", "projblock"]),
-    (dict(projection=256, res_mode="post"), ["conv"] * 5), (dict(projection=256, pad=1), ["conv"] * 3 + ["dual"]),
+    (dict(projection=256, res_mode="post"), ["conv"] * 5), (dict(inplace=True), ["conv"] * 4), (dict(projection=256, pad=1), ["conv"] * 3 + ["dual"]),
 ], ids=str)
 def test_bottleneck_blocks_of_other_forms(kw, kinds):
     net = block(**kw)
     assert [st[0] for st in cpu_library.check(net, integers(net)).steps] == kinds
+
+
+def test_a_merge_that_overwrites_what_its_projection_reads():
+    b = builder(1, 16, 16, 64)
+    b.conv("c0", "raw", "x", 64, 1)
+    b.conv("c1", "x", "t", 64, 1)
+    b.conv("proj", "x", "sk", 64, 1, out_mode="raw_s32", role="projection")
+    b.conv("c2", "t", "x", 64, 1, res="sk", res_mode="pre")
+    b.net["outputs"] = ["x"]
+    cpu_library.check(b.net, integers(b.net))
+
+
+def test_two_branches_on_one_channel_range():
+    # the second branch overwrites the first one's channels
+    b = builder(1, 64, 64, 64)
+    b.conv("a", "raw", "t", 32, 5, dst_c_total=48)
+    b.conv("b", "raw", "t", 16, 3, dst_c_total=48, dst_c_offset=16)
+    b.conv("c", "t", "out", 16, 1, src_c=32)
+    b.net["outputs"] = ["out"]
+    g, want = cpu_library.planned(b.net, integers(b.net))
+    assert (g.result("out") == want["out"]).all() and [st[0] for st in g.steps] == ["conv"] * 3
+
+
+def test_a_pair_that_returns_to_its_first_buffer():
+    # t -> y -> t: every workgroup has read its own pixels of t before it writes them
+    b = builder(1, 48, 48, 64)
+    b.conv("c0", "raw", "t", 64, 1)
+    b.conv("c1", "t", "y", 256, 1)
+    b.conv("c2", "y", "t", 64, 1)
+    b.net["outputs"] = ["y", "t"]
+    g = cpu_library.check(b.net, integers(b.net))
+    assert [st[0] for st in g.steps] == ["conv", "pair"]

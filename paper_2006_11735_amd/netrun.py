@@ -84,10 +84,11 @@ class GpuNet:
         net, calib = self.net, self.calib
         self.steps = []
         pending = {}                        # skip buffer name -> prepared projection step
-        for op in net["ops"]:
+        readers = self._readers()
+        for at, op in enumerate(net["ops"]):
             if op["op"] == "conv":
                 step = self._prep_conv(op)
-                if fuse and op["role"] == "projection" and op["out_mode"] == "raw_s32":
+                if fuse and op["role"] == "projection" and op["out_mode"] == "raw_s32" and self._can_wait(at, readers):
                     pending[op["dst"]] = step
                     continue
                 if op["res"] in pending:
@@ -120,6 +121,16 @@ class GpuNet:
             self._fuse_twin_last()
             self._fuse_twins()
             self._fuse_chains()
+
+    def _can_wait(self, at, readers):
+        """Whether op `at` may be issued with the one op that reads its result, a later merge: nothing between them writes what it reads
+        or writes, and nobody else sees the result."""
+        ops = self.net["ops"]
+        op, use = ops[at], readers.get(ops[at]["dst"], [])
+        if len(use) != 1 or use[0].get("res") != op["dst"] or op["dst"] in self.net["outputs"] or op["dst_c_offset"] != 0:
+            return False
+        merge = [i for i, o in enumerate(ops) if o is use[0]][0]
+        return merge > at and not any(o["dst"] in (op["src"], op["dst"]) for o in ops[at + 1:merge])
 
     def _fuse_first_layer(self):
         """A picture convolution followed by the max-pool of its output, nothing else reading that output: one

@@ -156,3 +156,27 @@ def test_a_pair_that_returns_to_its_first_buffer():
     b.net["outputs"] = ["y", "t"]
     g = cpu_library.check(b.net, integers(b.net))
     assert [st[0] for st in g.steps] == ["conv", "pair"]
+
+
+def merges(second_reader=False, output=False, overwrite=False, unread=False):
+    """x -> projection -> sk and x -> t -> merge with sk.  second_reader: another merge reads sk; output: sk is a result; overwrite: x is
+    written again before the merge; unread: no merge at all"""
+    b = builder(1, 16, 16, 64)
+    b.conv("c0", "raw", "x", 64, 1)
+    b.conv("c1", "x", "t", 64, 1)
+    b.conv("proj", "x", "sk", 64, 1, out_mode="raw_s32", role="projection")
+    if overwrite:
+        b.conv("again", "t", "x", 64, 1)
+    if not unread:
+        b.conv("c2", "t", "y", 64, 1, res="sk", res_mode="pre")
+    if second_reader:
+        b.conv("c3", "y", "z", 64, 1, res="sk", res_mode="pre")
+    b.net["outputs"] = ["z" if second_reader else "t" if unread else "y"] + (["sk"] if output else [])
+    return b.net
+
+
+@pytest.mark.parametrize("kw", [{}, dict(second_reader=True), dict(output=True), dict(overwrite=True), dict(unread=True, output=True), dict(unread=True)], ids=str)
+def test_projections_and_who_reads_them(kw):
+    net = merges(**kw)
+    g = cpu_library.check(net, integers(net))
+    assert bool(g.fused_proj) == (not kw)

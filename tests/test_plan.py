@@ -5,6 +5,7 @@ import torch
 
 import cpu_library
 from oracle import calibrate as K
+from oracle import net as ONet
 from workloads import nets as W
 
 pytestmark = pytest.mark.skipif(torch.cuda.is_available(), reason="plans are run without a GPU")
@@ -180,3 +181,18 @@ def test_projections_and_who_reads_them(kw):
     net = merges(**kw)
     g = cpu_library.check(net, integers(net))
     assert bool(g.fused_proj) == (not kw)
+
+
+@pytest.mark.parametrize("make, per_channel, kinds", [
+    (lambda: W.vdsr(64, 72, depth=9), False, {"conv", "chain"}),
+    (lambda: W.vrcnn(64, 72), False, {"conv", "twin", "twin_last"}),
+    (lambda: W.resnet(2, [2, 1, 1, 1], "tiny", image=64, calib_images=2, classes=10), False, {"convpool", "projblock", "block", "dual", "conv", "avgpool"}),
+    (lambda: W.resnet(2, [2, 1, 1, 1], "tiny", image=64, calib_images=2, classes=10), True,
+     {"convpool_pc", "projblock_pc", "block_pc", "dual_pc", "conv", "conv_pc", "avgpool"}),
+    (lambda: W.resnet_basic(2, [1, 1, 1, 1], "tiny18", image=64, calib_images=2, classes=10), False, {"convpool", "conv", "avgpool"}),
+], ids=["vdsr", "vrcnn", "bottleneck", "bottleneck_pc", "basic"])
+def test_small_networks_of_every_kind(make, per_channel, kinds):
+    net = make()
+    calib, _ = ONet.calibrate(net, 0, per_channel=per_channel)
+    g = cpu_library.check(net, calib)
+    assert {st[0] for st in g.steps} == kinds

@@ -129,6 +129,7 @@ const char *icnn_last_error(void);
  *   "tile"        -1 library's choice; 0..4 force that tile shape of the tap-by-tap convolution kernel
  *   "stages"      0 library's choice; 2..6 LDS ring depth of that kernel
  *   "no_narrow", "no_lat", "no_halo", "no_stream", "no_block64", "no_deep", "no_plane", "no_pic"   1 keeps layers off the respective special kernel
+ *   "no_fc"       1 keeps the classifier's kind of layer (pointwise, at most 64 pixels, cin >= 512) off the kernel that "no_lat" is about
  *   "lat"         1 lets the kernel for few pixels (waves split K straight from global memory) take every layer whose shape it accepts
  *   "halo_tile"   0 library's choice; 1 = 128 x 128, 2 = 64 x 256 tiles of the patch-resident 3x3 kernel
  *   "halo_always" 1 lets the patch-resident kernel take layers with several tiles per workgroup

@@ -177,7 +177,7 @@ int icnn_set_tuning(const char *name, int32_t value)
     struct Entry { const char *name; int Tuning::*field; int lo, hi; };
     static const Entry table[] = {
         {"tile", &Tuning::tile, -1, 4},         {"stages", &Tuning::stages, 0, 6},
-        {"no_narrow", &Tuning::no_narrow, 0, 1}, {"lat", &Tuning::lat, 0, 1}, {"no_lat", &Tuning::no_lat, 0, 1},
+        {"no_narrow", &Tuning::no_narrow, 0, 1}, {"lat", &Tuning::lat, 0, 1}, {"no_lat", &Tuning::no_lat, 0, 1}, {"no_fc", &Tuning::no_fc, 0, 1},
         {"no_halo", &Tuning::no_halo, 0, 1},     {"halo_tile", &Tuning::halo_tile, 0, 2},
         {"halo_always", &Tuning::halo_always, 0, 1}, {"no_stream", &Tuning::no_stream, 0, 1},
         {"ksplit", &Tuning::ksplit, 0, 8}, {"no_block64", &Tuning::no_block64, 0, 1},

@@ -241,6 +241,7 @@ static bool lat_worth(const ConvArgs &a, int frags)
 bool conv_lat_applies(const ConvArgs &a)
 {
     if (!lat_shape_ok(a) || g_tuning.no_lat) return false;
+    if (g_tuning.no_fc && a.KH == 1 && a.KW == 1 && a.sh == 1 && a.sw == 1 && a.M <= 64 && a.Cin >= 512) return false;
     const bool forced = g_tuning.tile >= 0 || g_tuning.ksplit || g_tuning.deep_always || g_tuning.halo_always || g_tuning.halo_tile || g_tuning.plane_always;
     return g_tuning.lat || (!forced && lat_worth(a, a.KH * a.KW * a.Cin / 32));
 }

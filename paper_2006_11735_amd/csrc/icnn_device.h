@@ -187,6 +187,7 @@ struct Tuning {
     int no_narrow = 0;     // keep one-to-four-channel layers on the tile kernels
     int lat = 0;           // few-pixel kernel for every layer whose shape it accepts
     int no_lat = 0;        // keep layers on few pixels off the kernel whose waves split the K axis straight from global memory
+    int no_fc = 0;         // the same for the classifier's kind of layer only: pointwise on at most 64 pixels with K >= 512
     int no_halo = 0;       // keep 3x3 layers on the tap-by-tap kernel
     int halo_tile = 0;     // patch-resident kernel: 1 = 128 x 128, 2 = 64 x 256
     int halo_always = 0;   // patch-resident kernel also with several tiles per workgroup and short K loops
@@ -200,7 +201,7 @@ struct Tuning {
     int deep_always = 0;   // that kernel for every layer whose shape it accepts
     int block_any_form = 0; // LDS-ring block kernel: the instantiation that holds every epilogue form, also where one form would do
     int no_block64 = 0;    // fused bottleneck blocks with 64 middle channels: the LDS-ring kernel instead of the register-resident one
-    int ksplit = 0;        // 0 library's choice; 1 never split the K axis; 2..8 this split where it divides the K steps
+    int ksplit = 0;        // 0, 1 the K axis stays whole (the library's choice); 2..8 this split where it divides the K steps
 };
 extern Tuning g_tuning;
 

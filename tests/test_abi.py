@@ -233,6 +233,25 @@ def test_fused_launches_refuse_outputs_over_what_other_workgroups_read():
             assert code(*call) == accepted, call
 
 
+def test_every_tuning_name_of_the_header_is_known():
+    B = binding()
+    text = open(os.path.join(ROOT, "include", "icnn.h")).read()
+    part = text[text.index("Kernel-selection override"):text.index("int icnn_set_tuning")]
+    names = set(re.findall(r'"([a-z0-9_]+)"', part)) - {"reset"}
+    assert {"tile", "no_fc", "no_lat", "lat", "ksplit", "no_pic"} <= names
+    try:
+        for name in sorted(names):
+            B.icnn_set_tuning(name, 0)
+            with pytest.raises(B.IcnnError) as e:
+                B.icnn_set_tuning(name, 99)
+            assert e.value.code == B.ICNN_E_PARAM and "outside" in str(e.value), name
+        with pytest.raises(B.IcnnError) as e:
+            B.icnn_set_tuning("colour", 1)
+        assert "unknown" in str(e.value)
+    finally:
+        B.icnn_set_tuning("reset")
+
+
 def test_tuning_overrides_are_validated():
     B = binding()
     try:

@@ -44,6 +44,17 @@ def test_shapes(lat, shape):
     check(sum(shape), *shape)
 
 
+@pytest.mark.parametrize("name", ["no_fc", "no_lat"])
+def test_the_classifier_off_this_kernel(name):
+    from paper_2006_11735_amd import binding as B
+    B.icnn_set_tuning(name, 1)
+    try:
+        check(21, 9, 1, 1, 512, 1000, 1, out_mode="raw_s32")
+        check(22, 64, 1, 1, 2048, 40, 1)
+    finally:
+        B.icnn_set_tuning("reset")
+
+
 def test_skip_operands_modes_and_inputs(lat):
     check(1, 1, 9, 9, 128, 64, 3, res_kind="u8", res_mode="pre")
     check(2, 1, 9, 9, 128, 64, 3, res_kind="u8", res_mode="post")

@@ -113,6 +113,41 @@ def layer_work(net, op, images, fused_proj=None, fused_block=None, fused_pool=No
     return ops, byts, m, k
 
 
+# kind of a convolution launch (without the "_pc" of per-channel requantisation) -> layer_work's argument for what the launch holds beside the layer
+FUSED_KINDS = {"conv": None, "dual": "fused_proj", "block": "fused_block", "convpool": "fused_pool", "pair": "fused_pair", "projblock": "fused_projblock",
+               "twin": "fused_twin", "chain": "fused_chain", "twin_last": "fused_twin_last"}
+
+
+def step_work(g, i):
+    """layer_work of step i of a GpuNet over the images of its part of the batch; None for a step without a convolution."""
+    kind, op, _ = g.steps[i]
+    base, pc = (kind[:-3], True) if kind.endswith("_pc") else (kind, False)
+    if base not in FUSED_KINDS:
+        return None
+    arg = FUSED_KINDS[base]
+    fused = {}
+    if arg is not None:
+        table = g.fused_block_pc if base == "block" and pc else getattr(g, arg)
+        fused[arg] = table[op["name"]]
+    return layer_work(g.net, op, g.step_images[i], **fused)
+
+
+def step_name(g, i):
+    kind, op, _ = g.steps[i]
+    base = kind[:-3] if kind.endswith("_pc") else kind
+    name = op["name"]
+    tail = {"block": "", "projblock": "_block+proj", "dual": "+proj", "convpool": "+pool", "pair": "+next_c1"}.get(base, "")
+    if base == "block":
+        name = name[:-3] + "_block"
+    elif base == "twin":
+        tail = "+" + g.fused_twin[name]["name"]
+    elif base == "twin_last":
+        tail = "".join("+" + o["name"] for o in g.fused_twin_last[name])
+    elif base == "chain":
+        tail = "_chain%d" % (len(g.fused_chain[name]) + 1)
+    return name + tail
+
+
 def cpu_baseline(net, calib, seed, budget_s=20.0):
     """The oracle as it stands, timed on this host: images/s on a bounded sample."""
     from oracle import net as ONet
@@ -464,35 +499,34 @@ def main():
             acc[i] += ev[i].elapsed_time(ev[i + 1])
     layer_ms = [a / reps for a in acc]
     # an event between two launches costs a little stream time itself: the per-launch intervals add
-    # up to more than the step measured above without events; spread that excess evenly
-    excess = max(0.0, (sum(layer_ms) - ms_per_step) / nsteps)
+    # up to more than the same launches one after the other without events; spread that excess evenly.
+    # (A large batch runs as two lists side by side: its step is shorter than its launches in a row.)
+    serial_ms = ms_per_step
+    if g.parts > 1:
+        from paper_2006_11735_amd import binding as B
+        row = B.Calls([(kind, args) for kind, _, args in g.steps])
+        serial_ms = _time_us(torch, row.run, reps) / 1e3
+    excess = max(0.0, (sum(layer_ms) - serial_ms) / nsteps)
     layer_ms = [max(m - excess, 1e-4) for m in layer_ms]
 
     conv_ops = conv_ms = conv_bytes = 0.0
     other_ms = 0.0
     rows = []
-    for step, ms in zip(g.steps, layer_ms):
+    for i, (step, ms) in enumerate(zip(g.steps, layer_ms)):
         kind, op = step[0], step[1]
-        if kind not in ("conv", "conv_pc", "dual", "dual_pc", "block", "convpool", "pair", "projblock", "twin", "twin_last", "chain"):
+        work = step_work(g, i)
+        if work is None:
             other_ms += ms
             rows.append({"name": op["dst"], "kind": kind, "ms": ms})
             continue
-        ops, byts, m, k = layer_work(net, op, images, g.fused_proj.get(op["name"]) if kind in ("dual", "dual_pc") else None,
-                                     g.fused_block.get(op["name"]) if kind == "block" else None,
-                                     g.fused_pool.get(op["name"]) if kind == "convpool" else None,
-                                     g.fused_pair.get(op["name"]) if kind == "pair" else None,
-                                     g.fused_projblock.get(op["name"]) if kind == "projblock" else None,
-                                     g.fused_twin.get(op["name"]) if kind == "twin" else None,
-                                     g.fused_chain.get(op["name"]) if kind == "chain" else None,
-                                     g.fused_twin_last.get(op["name"]) if kind == "twin_last" else None)
+        ops, byts, m, k = work
         conv_ops += ops
         conv_ms += ms
         conv_bytes += byts
         tops = ops / (ms * 1e-3) / 1e12
         attain = min(INT8_MFMA_PEAK_TOPS, ops / byts * HBM_PEAK_GBS / 1e3)
-        rows.append({"name": (op["name"][:-3] + "_block" if kind == "block" else op["name"]) + ("+proj" if kind in ("dual", "dual_pc") else "") +
-                             ("+pool" if kind == "convpool" else "") + ("+next_c1" if kind == "pair" else "") + ("+" + g.fused_twin[op["name"]]["name"] if kind == "twin" else "") + ("+".join([""] + [o["name"] for o in g.fused_twin_last[op["name"]]]) if kind == "twin_last" else "") + ("_chain%d" % (len(g.fused_chain[op["name"]]) + 1) if kind == "chain" else "") + ("_block+proj" if kind == "projblock" else ""), "kind": "conv", "M": m, "N": op["cout"] + (g.fused_twin[op["name"]]["cout"] if kind == "twin" else 0), "K": k, "ms": ms,
-                     "tops": tops, "pct_mfma_peak": 100 * tops / INT8_MFMA_PEAK_TOPS,
+        rows.append({"name": step_name(g, i), "kind": "conv", "M": m, "N": op["cout"] + (g.fused_twin[op["name"]]["cout"] if kind == "twin" else 0),
+                     "K": k, "ms": ms, "tops": tops, "pct_mfma_peak": 100 * tops / INT8_MFMA_PEAK_TOPS,
                      "pct_attainable": 100 * tops / attain, "gbs": byts / (ms * 1e-3) / 1e9})
     for r in rows:
         if r["kind"] == "conv":
@@ -503,8 +537,8 @@ def main():
             log("%-12s %-8s %8.1f us" % (r["name"], r["kind"], r["ms"] * 1e3))
     conv_tops = conv_ops / (conv_ms * 1e-3) / 1e12
     n_conv = sum(1 for r in rows if r["kind"] == "conv")
-    log("conv launches: %d, %.3f ms per step (events, excess %.2f us/launch removed; whole step %.3f ms wall), %.1f TOP/s" % (
-        n_conv, conv_ms, excess * 1e3, ms_per_step, conv_tops))
+    log("conv launches: %d, %.3f ms per step (events, excess %.2f us/launch removed; launches in a row %.3f ms, whole step %.3f ms wall), %.1f TOP/s" % (
+        n_conv, conv_ms, excess * 1e3, serial_ms, ms_per_step, conv_tops))
 
     traffic, traffic_stale = None, None
     tpath = os.path.join(ROOT, "profiles", "traffic_%s.json" % args.config)
@@ -531,7 +565,7 @@ def main():
         "conv_tops": conv_tops,
         "pct_int8_mfma_peak": 100 * conv_tops / INT8_MFMA_PEAK_TOPS,
         "whole_step_tops": conv_ops / (ms_per_step * 1e-3) / 1e12,
-        "roofline": {"kernel": "conv kernels (all %d conv launches of a step: conv_dlds / conv_halo / conv_deep / conv_plane / conv_pic / conv_narrow / conv_dual / conv_block / conv_block64 / conv_pair / conv_stem_pool, every tile shape)" % n_conv,
+        "roofline": {"kernel": "conv kernels (all %d conv launches of a step: conv_dlds / conv_greg / conv_lat / conv_halo / conv_deep / conv_plane / conv_rows / conv_tail / conv_chain / conv_pic / conv_narrow / conv_dual / conv_block / conv_block64 / conv_pair / conv_stem_pool, every tile shape)" % n_conv,
                      "bound": "mfma", "achieved": conv_tops, "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s",
                      "frac": conv_tops / INT8_MFMA_PEAK_TOPS, "traffic": traffic, "traffic_stale": traffic_stale,
                      "peak_measured": peak_tops, "frac_of_peak_measured": conv_tops / peak_tops,
@@ -569,7 +603,7 @@ def main():
             ms2, images / (ms2 * 1e-3), same))
         del g2, pair
     if args.per_channel:
-        result["config"]["workload"] += "; per-output-channel requantisation (iconv2d_brelu_pc, iconv2d_dual_brelu_pc)"
+        result["config"]["workload"] += "; per-output-channel requantisation (the _pc entry points)"
     elif os.path.exists(pc_path) and args.config == "cfg3" and not args.main_only:
         # the same network with one (mul, shift) and skip rescale per output channel, on both stored calibrations:
         # channels without a positive calibration value keep the layer's pair ("layer"), or get the wide pair of
@@ -593,8 +627,8 @@ def main():
             log("per-channel variant (%s): %.3f ms per step (%d launches)" % (label, ms_pc, len(g_pc.steps)))
             del g_pc
         result["per_channel_variant"] = dict(variants.get("layer", {}), floor_channels_own=variants.get("own"),
-                                             note="iconv2d_brelu_pc on every BReLU layer, iconv2d_dual_brelu_pc on the four "
-                                                  "projection blocks; the top-level figures are for the calibration in which a "
+                                             note="one multiplier and shift per output channel in every BReLU layer, layer by layer "
+                                                  "and in the fused launches; the top-level figures are for the calibration in which a "
                                                   "channel without a positive calibration value keeps the layer's pair, "
                                                   "floor_channels_own for the one in which it gets the pair of its own statistic")
     result["hbm_copy_measured_gbs"] = copy_gbs

@@ -56,7 +56,9 @@ class GpuNet:
             self._build(fuse, blocks)
             lists.append(self.steps)
         self.buf = full
+        self.parts = len(parts)
         self.steps = [st for part in lists for st in part]
+        self.step_images = [images for images, part in zip(parts, lists) for _ in part]       # images that step i works on
         self.fused = list(dict.fromkeys(self.fused))
         calls = [B.Calls([(kind, args) for kind, _, args in part]) for part in lists]
         with torch.cuda.device(self.device):

@@ -3,6 +3,7 @@ launches do not take.  Every plan is run on the CPU (tests/cpu_library.py) and h
 import pytest
 import torch
 
+import bench
 import cpu_library
 from oracle import calibrate as K
 from oracle import net as ONet
@@ -191,8 +192,17 @@ def test_projections_and_who_reads_them(kw):
      {"convpool_pc", "projblock_pc", "block_pc", "dual_pc", "conv", "conv_pc", "avgpool"}),
     (lambda: W.resnet_basic(2, [1, 1, 1, 1], "tiny18", image=64, calib_images=2, classes=10), False, {"convpool", "conv", "avgpool"}),
 ], ids=["vdsr", "vrcnn", "bottleneck", "bottleneck_pc", "basic"])
-def test_small_networks_of_every_kind(make, per_channel, kinds):
+def test_small_networks_of_every_kind(make, per_channel, kinds, monkeypatch):
     net = make()
     calib, _ = ONet.calibrate(net, 0, per_channel=per_channel)
     g = cpu_library.check(net, calib)
     assert {st[0] for st in g.steps} == kinds
+    # the benchmark counts every convolution once: in any launch it is part of, also when the batch runs as two halves
+    monkeypatch.setattr(type(g), "HALVES_MIN_PIXELS", 0)
+    halves = cpu_library.planned(net, calib)[0]
+    assert halves.parts == min(2, net["buffers"]["raw"]["shape"][0])
+    for q in (g, halves):
+        work = [bench.step_work(q, i) for i in range(len(q.steps))]
+        assert sum(w[0] for w in work if w is not None) == 2 * W.conv_macs(net)
+        assert {st[0] for st, w in zip(q.steps, work) if w is None} <= {"maxpool", "avgpool"}
+        assert all(bench.step_name(q, i).startswith(q.steps[i][1]["name"][:4]) for i, w in enumerate(work) if w is not None)

@@ -228,14 +228,20 @@ static bool lat_shape_ok(const ConvArgs &a)
            a.ksteps == (a.KH * a.KW * a.Cin + 63) / 64;
 }
 
-// Worth it while the work units (32 channels x 32 pixels) are at most about two per compute unit: beyond, re-reading the weights per
-// 32 pixels costs more than the tile kernels' serial K axis.  Measured against them over the layers of the 50-layer residual network at
-// 1 to 24 images: 448 units win with 4 to 72 fragments of K (3x3 of 256 channels on 9 x 14 x 14: 9.7 -> 8.4 us; on one image
-// 9.0 -> 5.1), 784 lose everywhere, and with 144 fragments 224 units win (11.8 -> 8.3 us) and 400 do not (11.9, 12.4 us).
-static bool lat_worth(const ConvArgs &a, int frags)
+// Worth it while all work units (32 channels x 32 pixels) are on the chip at once: two workgroups of eight waves fit a compute unit, and a
+// launch costs by whole units per compute unit.  Microseconds here / in the tile kernels, over layers of residual networks at 1 to 24
+// images: 3x3 of 256 channels on 14 x 14, 248 units 6.1 / 9.4, 448 units 8.2 / 9.4, 496 units 8.3 / 9.5, 544 units 10.8 / 9.5;
+// 1024 -> 256 there, 496 units 6.8 / 7.4, 544 units 8.7 / 7.3; 3x3 / 2 of 512 channels, 496 units 14.3 / 18.4, 592 units 19.0 / 18.4;
+// 512 -> 2048 on 7 x 7, 448 units 5.6 / 6.0, 512 units 5.9 / 5.9, 640 units 7.3 / 6.2.
+// The kernel whose waves split K over a patch in LDS (conv_deep.hip) is nearer where it applies: two units per compute unit lose to it
+// with 144 fragments of K (3x3 of 512 channels on 7 x 7: 256 units 8.2 / 11.4, 272 units 12.0 / 11.5) and win with 72 (the first line).
+// With a projection: 12 fragments, 400 units 6.8 / 6.5 on its own and 1 % of a one-image step the other way; 24, 416 units 7.9 / 7.9, 608
+// units 10.4 / 7.8; 48, 512 units 9.0 / 9.9, 640 units 11.8 / 10.1.
+constexpr int kLatOnePerCu = 256, kLatTwoPerCu = 512;
+static bool lat_worth(int M, int Cout, int frags, int most_units)
 {
-    const long long units = (long long)((a.Cout + 31) / 32) * ((a.M + 31) / 32);
-    return frags >= 4 && units <= 448 && (a.M <= 64 || units * frags <= 50000);
+    const long long units = (long long)((Cout + 31) / 32) * ((M + 31) / 32);
+    return frags >= 4 && units <= most_units;
 }
 
 bool conv_lat_applies(const ConvArgs &a)
@@ -243,7 +249,9 @@ bool conv_lat_applies(const ConvArgs &a)
     if (!lat_shape_ok(a) || g_tuning.no_lat) return false;
     if (g_tuning.no_fc && a.KH == 1 && a.KW == 1 && a.sh == 1 && a.sw == 1 && a.M <= 64 && a.Cin >= 512) return false;
     const bool forced = g_tuning.tile >= 0 || g_tuning.ksplit || g_tuning.deep_always || g_tuning.halo_always || g_tuning.halo_tile || g_tuning.plane_always;
-    return g_tuning.lat || (!forced && lat_worth(a, a.KH * a.KW * a.Cin / 32));
+    const int frags = a.KH * a.KW * a.Cin / 32;
+    const bool nearer = frags > 96 && !g_tuning.no_deep && conv_deep_applies(a);
+    return g_tuning.lat || (!forced && lat_worth(a.M, a.Cout, frags, nearer ? kLatOnePerCu : kLatTwoPerCu));
 }
 
 static hipError_t launch_lat(const ConvArgs &a, const ProjArgs *q, hipStream_t st)
@@ -286,7 +294,7 @@ hipError_t launch_conv_lat(const ConvArgs &a, hipStream_t st)
 bool conv_lat_dual_applies(const ConvArgs &a, const ProjArgs &q)
 {
     if (!lat_shape_ok(a) || g_tuning.no_lat || q.Cin % 32 || q.in_cs % 16 || ((uintptr_t)q.x & 15) || a.frag_xor) return false;
-    return g_tuning.lat || lat_worth(a, (a.Cin + q.Cin) / 32);
+    return g_tuning.lat || lat_worth(a.M, a.Cout, (a.Cin + q.Cin) / 32, kLatTwoPerCu);
 }
 hipError_t launch_conv_lat_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st)
 {

@@ -55,6 +55,13 @@ def test_the_classifier_off_this_kernel(name):
         B.icnn_set_tuning("reset")
 
 
+@pytest.mark.parametrize("shape", [(1, 32, 32, 128, 512, 1), (1, 33, 32, 128, 512, 1), (10, 7, 7, 512, 512, 3), (11, 7, 7, 512, 512, 3), (10, 14, 14, 256, 256, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_on_either_side_of_what_is_on_the_chip_at_once(shape):
+    # 512 and 528 work units; 256 and 272 where the kernel that splits K over a patch is nearer; 496 where it is not
+    check(sum(shape), *shape)
+
+
 def test_skip_operands_modes_and_inputs(lat):
     check(1, 1, 9, 9, 128, 64, 3, res_kind="u8", res_mode="pre")
     check(2, 1, 9, 9, 128, 64, 3, res_kind="u8", res_mode="post")

@@ -164,9 +164,16 @@ class GpuNet:
     # fit the chip in about one round and the wide tensor is at most 1024 channels (measured at batch 64: 17.6 us
     # against 23.8 us for 12544 pixels of 256 -> 1024 -> 256; level at 50176 pixels of 128 -> 512 -> 128; a loss,
     # 22.9 us against 19.0 us, at 3136 pixels of 512 -> 2048 -> 512).
-    # Below the other bound the two layers by themselves are the faster choice (a few tiles of 64 pixels against work units all over
-    # the chip: one image of 256 -> 1024 -> 256 takes 13.2 us fused and 8.5 us in two launches, nine 13.7 and 13.1 us).
-    PAIR_MIN_PIXELS = 1800
+    # Below the other bound (by narrow width and whether requantisation is per channel) the two layers by themselves are the faster
+    # choice: the fused time hardly depends on the tiles as long as each has a compute unit of its own, the layers' does.
+    #   256 -> 1024 -> 256: 13.2 us fused; apart 12.0 at 784 pixels, 13.1 at 1960, 14.0 at 2156, 14.6 at 3920: up to 2048 pixels the second
+    #   layer's work units are all on the chip at once (conv_lat.hip).  50-layer network, its five pairs fused / apart: 8 images 332 / 327 us,
+    #   10: 351 / 348, 11: 387 / 387, 16: 399 / 402, 64: 748 / 774.
+    #   Per channel: 18.7 us fused at few pixels; the same network: 16 images 500 / 490 us, 40: 726 / 711, 48: 826 / 842, 64: 904 / 919.  Up to
+    #   8192 pixels the first layer by itself is one round of two 128 x 128 tiles per compute unit.
+    #   128 -> 512 -> 128: 7.4 us fused and 9.7 apart at 784 pixels already; per channel two of them gain 5 us at one image only when apart
+    #   (784 pixels), are level at 1568 pixels and gain 6 us fused at 7056.
+    PAIR_MIN_PIXELS = {(256, False): 2049, (256, True): 8193, (128, True): 1536}
     PAIR_MAX_PIXELS = 64 * 512
     PAIR_MAX_WIDE = 1024
 
@@ -184,7 +191,7 @@ class GpuNet:
                 d1, _y, w1, b1, _r1, z = self._conv_args(two[1])
                 if (o1["src"] == o3["dst"] and o3["kh"] == 1 and o1["kh"] == 1 and o3["dst_c_offset"] == 0 and
                         o1["cout"] == o3["cin"] and o1["cin"] == o3["cout"] and
-                        self.PAIR_MIN_PIXELS <= d3.n * d3.h * d3.w <= self.PAIR_MAX_PIXELS and o3["cout"] <= self.PAIR_MAX_WIDE):
+                        self.PAIR_MIN_PIXELS.get((o3["cin"], pc), 0) <= d3.n * d3.h * d3.w <= self.PAIR_MAX_PIXELS and o3["cout"] <= self.PAIR_MAX_WIDE):
                     if pc:
                         fn, args = B.iconv2d_pair_brelu_pc, (d3, t, w3, b3, two[0][2][4], res, y, d1, w1, b1, two[1][2][4], z)
                     else:

@@ -386,9 +386,12 @@ class GpuNet:
             i += 1
         self.steps = steps
 
-    # With 128 middle channels a block is a chain of 22 us whatever its tiles are fewer than the compute units; its three layers
-    # spread over the chip instead (one image: 12.7 us, four 17.6, nine 21).  64 middle channels stay fused: 10.6 us for one image.
-    BLOCK128_MIN_PIXELS = 7100
+    # With 128 middle channels a block is a chain of 22 us while its tiles are fewer than the compute units; its three layers spread over
+    # the chip instead (one image: 12.7 us, four 17.6).  They are the faster choice while each of them runs in one round, 64 pixels to a
+    # compute unit: the 50-layer network with its three such blocks fused / layer by layer takes 363 / 352 us at 10 images, 437 / 427 at 20
+    # (15680 pixels), 460 / 464 at 21 (16464), 463 / 470 at 24, 522 / 534 at 32; on 36 x 36 maps 438 / 433 at 12 images (15552), 464 / 474 at
+    # 14 (18144); on 20 x 20 maps 439 / 431 at 40 (16000).  64 middle channels stay fused: 10.6 us for one image.
+    BLOCK128_MIN_PIXELS = 16385
 
     def _fuse_blocks(self):
         """Replaces every run of three per-layer conv steps that forms an identity bottleneck block by one fused step."""

@@ -405,7 +405,8 @@ int iconv2d_twin_last_brelu(const icnn_conv_desc *ca, const void *x, const void 
  * else returns ICNN_E_UNSUPPORTED having launched nothing, and the caller issues the layers separately.
  *
  * iconv2d_chain_split (host only) cuts a run of n_layers such layers into launches: lengths[i] (room for n_layers entries) is the number
- * of layers of launch i, *n_launches their count.  More layers per launch recompute more border, fewer cost more launches.
+ * of layers of launch i, *n_launches their count.  More layers per launch recompute more border, fewer cost more launches.  A launch of one
+ * layer is meant as iconv2d_brelu (large planes are cut into such launches altogether).
  */
 int iconv2d_chain_brelu(int32_t n_layers, const icnn_conv_desc *const *descs, const void *x, const void *const *w_packed,
                         const int32_t *const *bias, void *y, void *stream);

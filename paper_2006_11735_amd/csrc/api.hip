@@ -943,11 +943,13 @@ int iconv2d_chain_split(int32_t n_layers, const icnn_conv_desc *const *descs, in
 {
     if (!descs || !lengths || !n_launches) return fail(ICNN_E_NULL, "descs, lengths and n_launches must not be NULL");
     if (n_layers < 1 || n_layers > 256) return fail(ICNN_E_SHAPE, "a chain has 1 to 256 layers");
+    bool full[256];
     for (int i = 0; i < n_layers; ++i) {
         int rc = check_conv(descs[i], nullptr);
         if (rc || (rc = chain_layer_ok(descs[i], descs[0]))) return rc;
+        full[i] = descs[i]->in_signed == ICNN_IN_U8_FULL;
     }
-    *n_launches = conv_chain_split(descs[0]->n, descs[0]->h, descs[0]->w, n_layers, lengths);
+    *n_launches = conv_chain_split(descs[0]->n, descs[0]->h, descs[0]->w, n_layers, full, lengths);
     return ICNN_OK;
 }
 

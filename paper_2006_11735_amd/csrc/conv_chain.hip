@@ -228,9 +228,9 @@ __global__ __launch_bounds__(512, 1) void conv_chain_kernel(const ChainArgs g)
 
 // ------------------------------------------------------------------ dispatch
 // Estimated microseconds of a launch of L layers on TH x TW tiles: the launch itself, then per round of workgroups (one per
-// compute unit) a prologue and, per layer, rounds of four pixel groups and what a layer costs whatever its size (weights
-// to registers, barrier, latencies).  Fitted to 1 to 6 layers on planes of 96 x 96 to 384 x 384 (256 x 256: 5.7, 8.9, 12.2
-// and 16.5 us for 1 to 4 layers).
+// compute unit) a prologue (from the second round on it waits for memory that other workgroups are using) and, per layer, rounds of four
+// pixel groups and what a layer costs whatever its size (weights to registers, barrier, latencies).  Within a tenth of what 2 to 6 layers
+// take on planes of 64 x 64 to 1600 x 2560 (256 x 256: 9.3, 12.7 and 16.8 us for 2 to 4 layers, 720 x 1280: 93, 153 and 217).
 static double chain_cost(long long tiles, int L, int th, int tw)
 {
     double per_tile = 1.5;
@@ -238,7 +238,21 @@ static double chain_cost(long long tiles, int L, int th, int tw)
         const int ng = ((th + 2 * b) * (tw + 2 * b) + 31) / 32;
         per_tile += 0.65 * ((ng + 3) / 4) + 1.0;
     }
-    return 2.0 + per_tile * (double)((tiles + 255) / 256);
+    const double rounds = (double)((tiles + 255) / 256);
+    return 2.0 + per_tile * rounds + 1.2 * (rounds - 1);
+}
+
+// Microseconds of one layer by itself, in the kernel that iconv2d_brelu takes for it; full: inputs up to 255.  Measured / estimated:
+// 64 x 64 4.4 / 4.5, 128 x 128 7.0 / 7.5 (inputs up to 255: 7.7), 256 x 256 6.1 / 6.0 (10.4 / 9.7), 480 x 640 14.9 / 15.0 (26.8 / 26.8),
+// 720 x 1280 34.5 / 35.7 (65.2 / 70.4).
+static double layer_cost(int N, int H, int W, bool full)
+{
+    const long long pixels = (long long)N * H * W;
+    if (pixels <= 8192) return pixels <= 4096 ? 4.5 : 5.5;           // conv_lat.hip, one or two work units per compute unit
+    const double plane = full ? 0 : conv_plane_cost(N, H, W);
+    if (plane > 0) return plane;
+    const double tiles = 5.0 + 7.1e-5 * (double)pixels;              // the tile kernels
+    return tiles > 7.5 ? tiles : 7.5;
 }
 
 // best tile for L layers
@@ -255,23 +269,31 @@ static double chain_tile(int N, int H, int W, int L, int &th, int &tw)
     return best;
 }
 
-// Cuts n layers into launches of len[0], len[1], ... layers (at most n entries); returns their number.
-int conv_chain_split(int N, int H, int W, int n, int *len)
+// Cuts n layers into launches of len[0], len[1], ... layers (at most n entries); returns their number.  A piece of one layer is not a chain:
+// iconv2d_brelu computes it.  full[i]: layer i's inputs go up to 255.
+// 18 layers as cut here / one by one: 64 x 64 43 / 78 us, 256 x 256 76 / 110, 384 x 384 156 / 188; on 384 x 512 and above the layers
+// by themselves are the faster choice (720 x 1280: 621 us, in nine chains of two 836).  With inputs up to 255: 256 x 256 79 / 187,
+// 256 x 384 139 / 219, 720 x 1280 876 / 1173.
+int conv_chain_split(int N, int H, int W, int n, const bool *full, int *len)
 {
     double cost[kChainMaxLayers + 1];
     int th, tw;
-    for (int L = 1; L <= kChainMaxLayers; ++L) cost[L] = chain_tile(N, H, W, L, th, tw);
+    const double single[2] = {layer_cost(N, H, W, false), layer_cost(N, H, W, true)};
+    for (int L = 2; L <= kChainMaxLayers; ++L) cost[L] = chain_tile(N, H, W, L, th, tw);
     // shortest path over the number of layers done
     double best[257];
     int from[257];
     best[0] = 0;
     for (int i = 1; i <= n; ++i) {
         best[i] = 1e300;
-        for (int L = 1; L <= kChainMaxLayers && L <= i; ++L)
-            if (best[i - L] + cost[L] < best[i]) { best[i] = best[i - L] + cost[L]; from[i] = L; }
+        for (int L = 1; L <= kChainMaxLayers && L <= i; ++L) {
+            const double c = best[i - L] + (L == 1 ? single[full[i - 1]] : cost[L]);
+            if (c < best[i]) { best[i] = c; from[i] = L; }
+        }
     }
     int k = 0;
-    for (int i = n; i > 0; i -= from[i]) len[k++] = from[i];
+    for (int i = n; i > 0; i -= from[i]) ++k;
+    for (int i = n, j = k; i > 0; i -= from[i]) len[--j] = from[i];
     return k;
 }
 

@@ -477,17 +477,30 @@ static bool plane_shape_ok(const ConvArgs &a)
 }
 
 // Tile rows per wave: 2 (tiles of 16 x 32 pixels) where the picture gives every compute unit several tiles, else 1 for
-// the 3x3 layers of 64 channels; 0: the layer is not worth this kernel.
-static int plane_rpw(const ConvArgs &a)
+// the 3x3 layers of 64 channels (one_row); 0: the layer is not worth this kernel.
+static int plane_rpw(int N, int H, int W, bool one_row, bool always)
 {
-    const int tx = (a.W + kPlaneTW - 1) / kPlaneTW;
-    const long long tiles8 = (long long)a.N * ((a.H + 7) / 8) * tx;
+    const int tx = (W + kPlaneTW - 1) / kPlaneTW;
+    const long long tiles8 = (long long)N * ((H + 7) / 8) * tx;
     // tiles hang over the right and bottom edges of pictures that are no multiples of them: not where that is more than
     // a quarter of the work
-    if (!g_tuning.plane_always && (a.W * 4 < tx * kPlaneTW * 3 || a.H < 8)) return 0;
-    if (tiles8 >= 2048 || (g_tuning.plane_always && !(a.KH == 3 && a.Cin == 64 && tiles8 < 512))) return 2;
-    if (a.KH == 3 && a.Cin == 64 && (tiles8 >= 192 || g_tuning.plane_always)) return 1;
-    return g_tuning.plane_always ? 2 : 0;
+    if (!always && (W * 4LL < (long long)tx * kPlaneTW * 3 || H < 8)) return 0;
+    if (tiles8 >= 2048 || (always && !(one_row && tiles8 < 512))) return 2;
+    if (one_row && (tiles8 >= 192 || always)) return 1;
+    return always ? 2 : 0;
+}
+
+static int plane_rpw(const ConvArgs &a) { return plane_rpw(a.N, a.H, a.W, a.KH == 3 && a.Cin == 64, g_tuning.plane_always); }
+
+double conv_plane_cost(int N, int H, int W)
+{
+    const long long tx = (W + kPlaneTW - 1) / kPlaneTW;
+    auto rounds = [&](int rows) { return (double)((N * tx * ((H + rows - 1) / rows) + 255) / 256); };
+    switch (plane_rpw(N, H, W, true, false)) {
+    case 1: return 3.7 + 2.25 * rounds(8);
+    case 2: return 0.5 + 4.4 * rounds(16);
+    default: return 0;
+    }
 }
 
 bool conv_plane_applies(const ConvArgs &a)

@@ -221,6 +221,7 @@ hipError_t launch_conv_halo(const ConvArgs &a, hipStream_t st);
 bool conv_rows_twin_applies(const ConvArgs &a, const ConvArgs &b);
 hipError_t launch_conv_rows_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st);
 bool conv_plane_applies(const ConvArgs &a);
+double conv_plane_cost(int N, int H, int W);     // estimated microseconds of a 3x3 layer of 64 channels there; 0: not a layer for it
 hipError_t launch_conv_plane(const ConvArgs &a, hipStream_t st);
 bool conv_plane_twin_ok(const ConvArgs &a, const ConvArgs &b);
 hipError_t launch_conv_plane_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st);
@@ -228,7 +229,7 @@ bool conv_tail_ok(const ConvArgs &a, const ConvArgs &b, const ConvArgs &c);
 hipError_t launch_conv_tail(const ConvArgs &a, const ConvArgs &b, const ConvArgs &c, hipStream_t st);
 bool conv_deep_applies(const ConvArgs &a);
 hipError_t launch_conv_deep(const ConvArgs &a, hipStream_t st);
-int conv_chain_split(int N, int H, int W, int n, int *len);
+int conv_chain_split(int N, int H, int W, int n, const bool *full, int *len);
 hipError_t launch_conv_chain(ChainArgs &g, hipStream_t st);
 hipError_t launch_conv_pic(const ConvArgs &a, hipStream_t st);
 hipError_t launch_conv_stem_pool(const ConvArgs &a, int hp, int wp, hipStream_t st);

@@ -173,6 +173,26 @@ def test_a_chain_refuses_an_output_over_its_input():
             assert code(*case) == B.ICNN_E_LAUNCH, case
 
 
+def test_chain_split_by_plane_size():
+    # what the launches have been timed at (18 layers of 3x3 x 64): few pixels in long chains, large planes layer by layer where the kernel
+    # with two-dimensional tiles takes them, in chains where inputs go up to 255
+    B = binding()
+
+    def split(h, w, full=False, n=18):
+        kind = B.ICNN_IN_U8_FULL if full else B.ICNN_IN_U8_LE127
+        return B.iconv2d_chain_split([good(B, h=h, w=w, in_signed=kind, bound_q=255 if full else 127)] * n)
+    assert split(64, 64) == [6, 6, 6] and split(320, 320) == [2] * 9 and max(split(256, 256)) == 4
+    for h, w in ((384, 512), (480, 640), (720, 1280), (1600, 2560)):
+        assert split(h, w) == [1] * 18, (h, w)
+        assert min(split(h, w, full=True)) >= 2, (h, w)
+    assert max(split(256, 384)) > 1 and min(split(256, 384, full=True)) > 1
+    # inputs that go up to 255 from the second layer on: only those layers change their own cost
+    d = [good(B, h=720, w=1280)] * 4 + [good(B, h=720, w=1280, in_signed=B.ICNN_IN_U8_FULL)] * 4
+    assert B.iconv2d_chain_split(d) == [1, 1, 1, 1, 2, 2]
+    for n in (1, 2, 7, 255):
+        assert sum(split(100, 130, n=n)) == n
+
+
 def test_fused_launches_refuse_outputs_over_what_other_workgroups_read():
     B = binding()
     import torch

@@ -280,13 +280,13 @@ class GpuNet:
                 if a[0] != "conv" or b[0] != "conv" or not self._only_feeds(a[1], b[1], readers):
                     break
                 run.append(b)
-            run = self._chain_part(run)
-            if run is None:
+            run, lengths = self._chain_part(run)
+            if len(run) < 2:
                 steps.append(self.steps[i])
                 i += 1
                 continue
             at = 0
-            for n in B.iconv2d_chain_split([st[2][0] for st in run]):
+            for n in lengths:
                 part, at = run[at:at + n], at + n
                 if n == 1:
                     steps.append(part[0])
@@ -302,22 +302,25 @@ class GpuNet:
         self.steps = steps
 
     def _chain_part(self, run):
-        """The leading layers of a run that one chain can hold, or None."""
-        if run[0][0] != "conv":
-            return None
-        d = run[0][2][0]
-        if d.n * d.h * d.w < self.CHAIN_MIN_PIXELS:
-            return None
-        n = 0
-        while n < len(run):
+        """The leading layers of a run that chains can hold (none: an empty list), and how many of them each launch takes."""
+        d = run[0][2][0] if run[0][0] == "conv" else None
+        if d is None or d.n * d.h * d.w < self.CHAIN_MIN_PIXELS:
+            return [], []
+
+        def split(part):
             try:
-                B.iconv2d_chain_split([st[2][0] for st in run[:n + 1]])
+                return B.iconv2d_chain_split([st[2][0] for st in part])
             except B.IcnnError as e:
                 if e.code not in (B.ICNN_E_UNSUPPORTED, B.ICNN_E_SHAPE):
                     raise
-                break
-            n += 1
-        return run[:n] if n > 1 else None
+                return None
+        if split(run[:1]) is None:
+            return [], []
+        while True:                                    # (what does not fit is the last layer of a run, if any)
+            lengths = split(run)
+            if lengths is not None:
+                return run, lengths
+            run = run[:-1]
 
     @staticmethod
     def _accepts(fn, args):

@@ -6,7 +6,7 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
-#include <vector>
+#include <new>
 
 using namespace icnn;
 
@@ -1185,9 +1185,11 @@ int icnn_run_calls(int32_t n, const icnn_call *calls, void *stream)
 }
 
 namespace {
+constexpr int kMaxLists = 16;
 struct Lanes {
-    std::vector<hipStream_t> streams;       // of lists 1, 2, ...
-    std::vector<hipEvent_t> done;           // a list's last call
+    int lists = 0;
+    hipStream_t streams[kMaxLists] = {};    // of lists 1, 2, ... (0: the caller's)
+    hipEvent_t done[kMaxLists] = {};        // a list's last call
     hipEvent_t start = nullptr;
 };
 }  // namespace
@@ -1196,26 +1198,25 @@ void icnn_lanes_destroy(void *lanes)
 {
     Lanes *const l = (Lanes *)lanes;
     if (!l) return;
-    for (hipEvent_t e : l->done) (void)hipEventDestroy(e);
-    for (hipStream_t s : l->streams) (void)hipStreamDestroy(s);
+    for (hipEvent_t e : l->done)
+        if (e) (void)hipEventDestroy(e);
+    for (hipStream_t s : l->streams)
+        if (s) (void)hipStreamDestroy(s);
     if (l->start) (void)hipEventDestroy(l->start);
     delete l;
 }
 
 int icnn_lanes_create(int32_t lists, void **lanes)
 {
-    if (lists < 1 || lists > 16) return fail(ICNN_E_SHAPE, "lists must be in [1, 16]");
+    if (lists < 1 || lists > kMaxLists) return fail(ICNN_E_SHAPE, "lists must be in [1, %d]", kMaxLists);
     if (!lanes) return fail(ICNN_E_NULL, "lanes is NULL");
-    Lanes *const l = new Lanes;
+    Lanes *const l = new (std::nothrow) Lanes;
+    if (!l) return fail(ICNN_E_LAUNCH, "icnn_lanes_create: out of host memory");
+    l->lists = lists;
     hipError_t e = hipEventCreateWithFlags(&l->start, hipEventDisableTiming);
     for (int32_t k = 1; k < lists && e == hipSuccess; ++k) {
-        hipStream_t s;
-        e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
-        if (e != hipSuccess) break;
-        l->streams.push_back(s);
-        hipEvent_t d;
-        e = hipEventCreateWithFlags(&d, hipEventDisableTiming);
-        if (e == hipSuccess) l->done.push_back(d);
+        e = hipStreamCreateWithFlags(&l->streams[k], hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&l->done[k], hipEventDisableTiming);
     }
     if (e != hipSuccess) {
         icnn_lanes_destroy(l);
@@ -1229,7 +1230,7 @@ int icnn_run_lanes(void *lanes, int32_t lists, const int32_t *n, const icnn_call
 {
     Lanes *const l = (Lanes *)lanes;
     if (!l || !n || !calls) return fail(ICNN_E_NULL, "lanes, n and calls must not be NULL");
-    if (lists < 1 || lists > (int32_t)l->streams.size() + 1) return fail(ICNN_E_SHAPE, "%d lists: the lanes hold %d", lists, (int)l->streams.size() + 1);
+    if (lists < 1 || lists > l->lists) return fail(ICNN_E_SHAPE, "%d lists: the lanes hold %d", lists, l->lists);
     int32_t most = 0;
     for (int32_t q = 0; q < lists; ++q) {
         if (n[q] < 0) return fail(ICNN_E_SHAPE, "n must be >= 0");
@@ -1237,15 +1238,15 @@ int icnn_run_lanes(void *lanes, int32_t lists, const int32_t *n, const icnn_call
         most = n[q] > most ? n[q] : most;
     }
     hipError_t e = hipEventRecord(l->start, (hipStream_t)stream);
-    for (int32_t q = 1; q < lists && e == hipSuccess; ++q) e = hipStreamWaitEvent(l->streams[q - 1], l->start, 0);
+    for (int32_t q = 1; q < lists && e == hipSuccess; ++q) e = hipStreamWaitEvent(l->streams[q], l->start, 0);
     if (e != hipSuccess) return launched(e, "icnn_run_lanes");
     int rc = ICNN_OK;
     for (int32_t k = 0; k < most && !rc; ++k)
         for (int32_t q = 0; q < lists && !rc; ++q)
-            if (k < n[q]) rc = run_call(k, calls[q][k], q ? (void *)l->streams[q - 1] : stream);
+            if (k < n[q]) rc = run_call(k, calls[q][k], q ? (void *)l->streams[q] : stream);
     for (int32_t q = 1; q < lists; ++q) {
-        e = hipEventRecord(l->done[q - 1], l->streams[q - 1]);
-        if (e == hipSuccess) e = hipStreamWaitEvent((hipStream_t)stream, l->done[q - 1], 0);
+        e = hipEventRecord(l->done[q], l->streams[q]);
+        if (e == hipSuccess) e = hipStreamWaitEvent((hipStream_t)stream, l->done[q], 0);
         if (e != hipSuccess && !rc) rc = launched(e, "icnn_run_lanes");
     }
     return rc;

@@ -21,7 +21,6 @@
 
 #include <mutex>
 #include <type_traits>
-#include <vector>
 
 namespace icnn {
 
@@ -631,12 +630,13 @@ __global__ __launch_bounds__(256) void conv_greg_kernel(const ConvArgs a)
 hipError_t allow_large_lds(const void *kernel)
 {
     static std::mutex lock;
-    static std::vector<const void *> done;
+    static const void *done[256];                    // (more kernels than the library has; beyond, the attribute is set anew)
+    static int n = 0;
     std::lock_guard<std::mutex> g(lock);
-    for (const void *k : done)
-        if (k == kernel) return hipSuccess;
+    for (int i = 0; i < n; ++i)
+        if (done[i] == kernel) return hipSuccess;
     const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e == hipSuccess) done.push_back(kernel);
+    if (e == hipSuccess && n < 256) done[n++] = kernel;
     return e;
 }
 

@@ -22,9 +22,7 @@
 // Every input byte crosses the memory system once (plus the patch overlap), and what bounds the loop is LDS: 1 + NCH
 // fragment reads of 1 KiB per 2 NCH matrix instructions and wave.  Accumulator layout, packed weights and epilogue
 // are those of the other kernels, so the results are the same bit for bit.
-#include "conv_common.h"
-
-#include <type_traits>
+#include "conv_patch.h"
 
 namespace icnn {
 
@@ -40,12 +38,6 @@ __device__ unsigned long long g_plane_trace[256];
 #else
 #define PLANE_TR(k)
 #endif
-
-struct PlaneArgs {
-    int tiles_x, tiles_per_img, n_tiles;
-    int per_xcd;                // tiles handed to each of the 8 XCDs
-    FastDiv div_tpi, div_tx;    // / tiles_per_img, / tiles_x
-};
 
 // Twin layers: a second convolution `b` of the same input whose kernel is the centre (KS - 2) x (KS - 2) of this one's
 // (the 3x3 branch beside a 5x5 branch, the 1x1 beside a 3x3 of the restoration network's two-branch layers).  Its
@@ -73,31 +65,22 @@ constexpr int twin_frag(int f)
 // as the loop, and because the barrier per tile keeps the two waves of a SIMD in step, both multiplied and then both
 // ran epilogues: 2.1 k clocks of matrix work, then 2.9 k of vector work, per tile.
 template <int KS, int CIN, int NCH, int NB, int RPW, bool PIPE>
-__global__ __launch_bounds__(512, 1) void conv_plane_kernel(const ConvArgs a, const ConvArgs b, const PlaneArgs g)
+__global__ __launch_bounds__(512, 1) void conv_plane_kernel(const ConvArgs a, const ConvArgs b, const TileWalk g)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the buffer-resource type exists in the device pass only
-    constexpr unsigned OOB = 0x80000000u;            // beyond any buffer this kernel accepts (< 2 GiB)
-    constexpr int PAD = KS / 2;
     constexpr int TH = 8 * RPW;
-    constexpr int PH = TH + KS - 1, PW = kPlaneTW + KS - 1;
-    constexpr int PWL = (PW + 3) & ~3;               // pixels per patch row in LDS: whole groups of four
-    constexpr int PPT = CIN / 16;                    // 16-byte pieces per pixel (= per tap)
-    constexpr int ROWB = PWL * CIN;                  // bytes per patch row
+    using Patch = TilePatch<KS, CIN, TH, kPlaneTW, 8>;
+    constexpr int PPT = Patch::PPT, ROWB = Patch::ROWB, CPW = Patch::CPW, PATCH = Patch::BYTES;
     constexpr int K = KS * KS * CIN;
     constexpr int KSTEPS = (K + 63) / 64;
     constexpr int F = 2 * KSTEPS;                    // fragments of 32 k-values, the zero-padded tail included
-    constexpr int PIECES = PH * PWL * PPT;
-    constexpr int NCOPY = (PIECES + 63) / 64;        // wave-wide 1 KiB copies per patch
-    constexpr int CPW = (NCOPY + 7) / 8;             // per wave
-    constexpr int PATCH = NCOPY * 1024;
     constexpr int WBYTES = NCH * KSTEPS * kChunkBytes;
     constexpr int KSB = KS - 2;
     constexpr int KSTEPSB = NB ? (KSB * KSB * CIN + 63) / 64 : 0, FB = 2 * KSTEPSB;
     constexpr int WBYTESB = NB * KSTEPSB * kChunkBytes;
-    static_assert(CIN == 48 || CIN == 64, "row layouts exist for 48 and 64 channels");
     static_assert(NB == 0 || CIN == 64 || KS == 3, "twin_frag() covers 64 channels, and 48 channels at 3x3 beside 1x1");
     static_assert(WBYTES + WBYTESB + 2 * PATCH <= 160 * 1024, "LDS");
-    static_assert((PH + 1) * ROWB < 65536, "fragment reads address rows and taps through the instruction's 16-bit offset");
+    static_assert((Patch::PH + 1) * ROWB < 65536, "fragment reads address rows and taps through the instruction's 16-bit offset");
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     uint8_t *const wbuf = lds;
@@ -109,83 +92,23 @@ __global__ __launch_bounds__(512, 1) void conv_plane_kernel(const ConvArgs a, co
     [[maybe_unused]] int trn = 0;
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.x_bytes, 0x00020000);
 
-    // Work slot v (blockIdx.x, + gridDim.x, ...; the grid is a multiple of 8) is tile (v & 7) * per_xcd + (v >> 3): the
-    // workgroups of an XCD walk a contiguous range of tiles, so the patch borders neighbouring tiles share meet in one L2.
-    auto tile_of = [&](int v) { return (v & 7) * g.per_xcd + (v >> 3); };
-    auto valid = [&](int v) { return (v >> 3) < g.per_xcd && tile_of(v) < g.n_tiles; };
-    auto tile_origin = [&](int v, int &n, int &y0, int &x0) {
-        const int t = tile_of(v);
-        n = fast_div(t, g.div_tpi);
-        const int r = t - n * g.tiles_per_img;
-        const int ty = fast_div(r, g.div_tx);
-        y0 = ty * TH;
-        x0 = (r - ty * g.tiles_x) * kPlaneTW;
-    };
-
-    // Patch layout in LDS: pixel (py, px) at (py * PWL + px) * CIN.  64-byte pixels: the 16-byte piece c of a pixel lives in
-    // slot c ^ ((px >> 2) & 3), so that the fragment reads of 16 consecutive pixels hit every bank once (rows are whole
-    // multiples of 256 bytes, so the row does not enter); 48-byte pixels spread over the banks by themselves.
-    // Copy e of a patch covers LDS bytes [1024 e, 1024 e + 1024): what this lane fetches for each of its copies does not
-    // depend on the tile but for the origin: the piece's offset from the patch's first pixel, and (py, px) for the
-    // check against the picture's borders (a lane beyond the patch gets py = 0x7fff, which never passes it).
-    int p_rel[CPW], p_yx[CPW];
-#pragma unroll
-    for (int i = 0; i < CPW; ++i) {
-        const int q = (wave + 8 * i) * 64 + lane;
-        const int pix = q / PPT, slot = q - pix * PPT;
-        const int py = pix / PWL, px = pix - py * PWL;
-        const int logical = CIN == 64 ? slot ^ ((px >> 2) & 3) : slot;
-        const bool in_patch = q < PIECES && px < PW;
-        p_rel[i] = (py * a.W + px) * a.in_cs + logical * 16;
-        p_yx[i] = ((in_patch ? py : 0x7fff) << 16) | px;
-    }
-    // copy i of this wave for the patch whose first pixel is picture pixel (n, y0 - PAD, x0 - PAD), into buffer b
+    Patch patch;
+    patch.locate(a, wave, lane);
     auto issue_copy = [&](auto i_tag, int base, int y0, int x0, int b) {
-        constexpr int i = decltype(i_tag)::value;
-        const int e = wave + 8 * i;
-        if (e < NCOPY) {                             // wave-uniform
-            const int iy = y0 - PAD + (p_yx[i] >> 16), ix = x0 - PAD + (p_yx[i] & 0xffff);
-            const bool ok = ((unsigned)iy < (unsigned)a.H) & ((unsigned)ix < (unsigned)a.W);
-            const unsigned off = ok ? (unsigned)(base + p_rel[i]) : OOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(pbuf + b * PATCH + e * 1024), 16, off,
-                                                     0, 0, 0);
-        }
+        patch.template issue<decltype(i_tag)::value>(rs_x, a, pbuf + b * PATCH, wave, base, y0, x0);
     };
-    // byte offset of that first pixel (may be negative: only pixels inside the picture use it)
-    auto patch_base = [&](int n, int y0, int x0) { return ((n * a.H + y0 - PAD) * a.W + x0 - PAD) * a.in_cs; };
     auto issue_patch = [&](int v, int b) {
         int n, y0, x0;
-        tile_origin(v, n, y0, x0);
-        const int base = patch_base(n, y0, x0);
+        g.template origin<TH, kPlaneTW>(v, n, y0, x0);
+        const int base = Patch::base(a, n, y0, x0);
         static_for<CPW>([&](auto i_tag) { issue_copy(i_tag, base, y0, x0, b); });
     };
 
-    if (valid(blockIdx.x)) issue_patch(blockIdx.x, 0);
+    if (g.valid(blockIdx.x)) issue_patch(blockIdx.x, 0);
     PLANE_TR(0);
     // weights: a straight copy of the first NCH chunks (the packed order is the fragment order)
-    // (direct-to-LDS copies as well, 1 KiB per wave and copy, all in flight together with the first patch: through
-    // registers the copy loop waited out one memory latency per 8 KiB, five of them for a 3x3 layer of 64 channels, which
-    // is most of the kernel's time on a picture with one tile per workgroup)
-    {
-        const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)a.wp, 0, a.wp_bytes, 0x00020000);
-#pragma unroll
-        for (int e0 = 0; e0 < WBYTES / 1024; e0 += 8) {
-            const int e = e0 + wave;
-            if (e < WBYTES / 1024)                   // wave-uniform
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, (__attribute__((address_space(3))) void *)(wbuf + e * 1024), 16,
-                                                         (unsigned)(e * 1024 + lane * 16), 0, 0, 0);
-        }
-        if constexpr (NB > 0) {
-            const __amdgpu_buffer_rsrc_t rs_wb = __builtin_amdgcn_make_buffer_rsrc((void *)b.wp, 0, b.wp_bytes, 0x00020000);
-#pragma unroll
-            for (int e0 = 0; e0 < WBYTESB / 1024; e0 += 8) {
-                const int e = e0 + wave;
-                if (e < WBYTESB / 1024)
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_wb, (__attribute__((address_space(3))) void *)(wbufB + e * 1024), 16,
-                                                             (unsigned)(e * 1024 + lane * 16), 0, 0, 0);
-            }
-        }
-    }
+    copy_packed_weights<8, WBYTES>(a.wp, a.wp_bytes, wbuf, wave, lane);
+    if constexpr (NB > 0) copy_packed_weights<8, WBYTESB>(b.wp, b.wp_bytes, wbufB, wave, lane);
     v16i bias[NCH];
     load_bias_rows<NCH>(a, 0, half, bias);
     [[maybe_unused]] v16i biasB[NB ? NB : 1];
@@ -236,18 +159,18 @@ __global__ __launch_bounds__(512, 1) void conv_plane_kernel(const ConvArgs a, co
     [[maybe_unused]] const bool quickB = NB && b.epi_vec && b.out_mode <= 1 && b.epi_mode / 4 == 0 && (b.Cout & 15) == 0;
 
     int buf = 0;
-    for (int v = blockIdx.x; valid(v); v += gridDim.x) {
+    for (int v = blockIdx.x; g.valid(v); v += gridDim.x) {
         PLANE_TR(1);
         int n, y0, x0;
-        tile_origin(v, n, y0, x0);
+        g.template origin<TH, kPlaneTW>(v, n, y0, x0);
         // The next tile's patch travels during this tile.  (A third buffer, i.e. two patches in flight per workgroup, measured
         // no faster: at these sizes the layers with short K loops run at what the memory system gives this access
         // pattern, 3.2 TB/s.)  Its copies are issued one by one between the K steps: issued together at the tile's start
         // they fill the memory pipeline's queue and every wave sits on them for ~ 900 clocks.
-        const bool more = valid(v + (int)gridDim.x);
+        const bool more = g.valid(v + (int)gridDim.x);
         int nn = 0, ny0 = 0, nx0 = 0;
-        if (more) tile_origin(v + (int)gridDim.x, nn, ny0, nx0);
-        const int nbase = patch_base(nn, ny0, nx0);
+        if (more) g.template origin<TH, kPlaneTW>(v + (int)gridDim.x, nn, ny0, nx0);
+        const int nbase = Patch::base(a, nn, ny0, nx0);
         PLANE_TR(2);
         const uint8_t *const P = pbuf + buf * PATCH;
 
@@ -514,20 +437,11 @@ bool conv_plane_applies(const ConvArgs &a)
 template <int KS, int CIN, int NCH, int NB = 0, int RPW = 2, bool PIPE = false>
 static hipError_t launch_plane(const ConvArgs &a, const ConvArgs &b, hipStream_t st)
 {
-    PlaneArgs g;
-    g.tiles_x = (a.W + kPlaneTW - 1) / kPlaneTW;
-    g.tiles_per_img = g.tiles_x * ((a.H + 8 * RPW - 1) / (8 * RPW));
-    const long long tiles = (long long)g.tiles_per_img * a.N;
-    if (tiles < 1 || tiles > 0x7ffffff0LL) return hipErrorInvalidValue;
-    g.n_tiles = (int)tiles;
-    g.per_xcd = (int)((tiles + 7) / 8);
-    g.div_tpi = make_fast_div((unsigned)g.tiles_per_img);
-    g.div_tx = make_fast_div((unsigned)g.tiles_x);
-    constexpr int PH = 8 * RPW + KS - 1, PW = kPlaneTW + KS - 1;
-    constexpr int NCOPY = (PH * ((PW + 3) & ~3) * (CIN / 16) + 63) / 64;
+    TileWalk g;
+    if (!tile_walk(g, a.N, a.H, a.W, 8 * RPW, kPlaneTW)) return hipErrorInvalidValue;
     constexpr int KSTEPS = (KS * KS * CIN + 63) / 64;
     constexpr int KSTEPSB = NB ? ((KS - 2) * (KS - 2) * CIN + 63) / 64 : 0;
-    const size_t lds_bytes = (size_t)(NCH * KSTEPS + NB * KSTEPSB) * kChunkBytes + 2 * (size_t)NCOPY * 1024;
+    const size_t lds_bytes = (size_t)(NCH * KSTEPS + NB * KSTEPSB) * kChunkBytes + 2 * (size_t)TilePatch<KS, CIN, 8 * RPW, kPlaneTW, 8>::BYTES;
     const auto kernel = conv_plane_kernel<KS, CIN, NCH, NB, RPW, PIPE>;
     if (lds_bytes > 64 * 1024) {
         const hipError_t e = allow_large_lds((const void *)kernel);

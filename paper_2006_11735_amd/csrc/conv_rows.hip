@@ -11,23 +11,15 @@
 //            one activation fragment of an input row is multiplied into every output row it reaches (up to five, and three of the
 //            twin), with the step's five (+ three) weight fragments in registers.  0.6 KiB of LDS per matrix instruction instead of 1.2.
 //   epilogue of the tile before, dealt out between this tile's matrix instructions (two sets of accumulators, used in turn)
-//   patch, weights, copies, tile walk: as in conv_plane.hip
+//   patch, weights, copies, tile walk: as in conv_plane.hip (conv_patch.h)
 //
 // Straight-line code for a tile: 272 matrix instructions per wave, everything else in their shadow.
 // Measured on 2560 x 1600, 64 -> 32 + 16: see launch_conv_rows_twin().
-#include "conv_common.h"
-
-#include <type_traits>
+#include "conv_patch.h"
 
 namespace icnn {
 
 constexpr int kRowsTW = 32, kRowsTH = 16;
-
-struct RowsArgs {
-    int tiles_x, tiles_per_img, n_tiles;
-    int per_xcd;                // tiles handed to each of the 8 XCDs
-    FastDiv div_tpi, div_tx;    // / tiles_per_img, / tiles_x
-};
 
 // Matrix instructions of a tile before product dy of fragment i (step i / 8, input row i % 8): the order of the loop below
 constexpr int rows_products_before(int i, int dy)
@@ -46,16 +38,14 @@ static_assert(kRowsProducts == 4 * (50 + 18), "products of four rows");
 
 // FORM: the requantisation form of both layers, 3 or 4 of requant16
 template <int FORM>
-__global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a, const ConvArgs b, const RowsArgs g)
+__global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a, const ConvArgs b, const TileWalk g)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the buffer-resource type exists in the device pass only
-    constexpr unsigned OOB = 0x80000000u;            // beyond any buffer this kernel accepts (< 2 GiB)
-    constexpr int KS = 5, KSB = 3, CIN = 64, PAD = 2, RPW = 4;
-    constexpr int PH = kRowsTH + KS - 1, PW = kRowsTW + KS - 1, PPT = CIN / 16, ROWB = PW * CIN;
+    constexpr int KS = 5, KSB = 3, CIN = 64, RPW = 4;
+    using Patch = TilePatch<KS, CIN, kRowsTH, kRowsTW, 4>;
+    constexpr int ROWB = Patch::ROWB, CPW = Patch::CPW, PATCH = Patch::BYTES;
     constexpr int F = KS * KS * 2, FB = KSB * KSB * 2;                   // weight fragments of 32 k-values
-    constexpr int PIECES = PH * PW * PPT, NCOPY = (PIECES + 63) / 64, CPW = (NCOPY + 3) / 4, PATCH = NCOPY * 1024;
     constexpr int WBYTES = F * 1024, WBYTESB = FB * 1024;
-    static_assert(PW % 4 == 0, "patch rows are whole groups of four pixels");
     static_assert(WBYTES + WBYTESB + 2 * PATCH <= 160 * 1024, "LDS");
 
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
@@ -67,51 +57,21 @@ __global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.x_bytes, 0x00020000);
 
-    auto tile_of = [&](int v) { return (v & 7) * g.per_xcd + (v >> 3); };
-    auto valid = [&](int v) { return (v >> 3) < g.per_xcd && tile_of(v) < g.n_tiles; };
-    auto tile_origin = [&](int v, int &n, int &y0, int &x0) {
-        const int t = tile_of(v);
-        n = fast_div(t, g.div_tpi);
-        const int r = t - n * g.tiles_per_img;
-        const int ty = fast_div(r, g.div_tx);
-        y0 = ty * kRowsTH;
-        x0 = (r - ty * g.tiles_x) * kRowsTW;
-    };
-    // (patch layout and copies: see conv_plane.hip)
-    int p_rel[CPW], p_yx[CPW];
-#pragma unroll
-    for (int i = 0; i < CPW; ++i) {
-        const int q = (wave + 4 * i) * 64 + lane;
-        const int pix = q / PPT, slot = q - pix * PPT;
-        const int py = pix / PW, px = pix - py * PW;
-        p_rel[i] = (py * a.W + px) * a.in_cs + (slot ^ ((px >> 2) & 3)) * 16;
-        p_yx[i] = ((q < PIECES ? py : 0x7fff) << 16) | px;
-    }
+    Patch patch;
+    patch.locate(a, wave, lane);
     auto issue_copy = [&](auto i_tag, int base, int y0, int x0, int buf) {
-        constexpr int i = decltype(i_tag)::value;
-        const int e = wave + 4 * i;
-        if (e < NCOPY) {                             // wave-uniform
-            const int iy = y0 - PAD + (p_yx[i] >> 16), ix = x0 - PAD + (p_yx[i] & 0xffff);
-            const bool ok = ((unsigned)iy < (unsigned)a.H) & ((unsigned)ix < (unsigned)a.W);
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(pbuf + buf * PATCH + e * 1024), 16,
-                                                     ok ? (unsigned)(base + p_rel[i]) : OOB, 0, 0, 0);
-        }
+        patch.template issue<decltype(i_tag)::value>(rs_x, a, pbuf + buf * PATCH, wave, base, y0, x0);
     };
-    auto patch_base = [&](int n, int y0, int x0) { return ((n * a.H + y0 - PAD) * a.W + x0 - PAD) * a.in_cs; };
 
     const int v0 = blockIdx.x;
-    if (!valid(v0)) return;                          // (the whole workgroup: it has no tile at all)
+    if (!g.valid(v0)) return;                          // (the whole workgroup: it has no tile at all)
     {
         int n, y0, x0;
-        tile_origin(v0, n, y0, x0);
-        const int base = patch_base(n, y0, x0);
+        g.template origin<kRowsTH, kRowsTW>(v0, n, y0, x0);
+        const int base = Patch::base(a, n, y0, x0);
         static_for<CPW>([&](auto i_tag) { issue_copy(i_tag, base, y0, x0, 0); });
-        const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)a.wp, 0, a.wp_bytes, 0x00020000);
-        const __amdgpu_buffer_rsrc_t rs_wb = __builtin_amdgcn_make_buffer_rsrc((void *)b.wp, 0, b.wp_bytes, 0x00020000);
-        for (int e = wave; e < F; e += 4)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, (__attribute__((address_space(3))) void *)(wbuf + e * 1024), 16, (unsigned)(e * 1024 + lane * 16), 0, 0, 0);
-        for (int e = wave; e < FB; e += 4)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_wb, (__attribute__((address_space(3))) void *)(wbufB + e * 1024), 16, (unsigned)(e * 1024 + lane * 16), 0, 0, 0);
+        copy_packed_weights<4, WBYTES>(a.wp, a.wp_bytes, wbuf, wave, lane);
+        copy_packed_weights<4, WBYTESB>(b.wp, b.wp_bytes, wbufB, wave, lane);
     }
     v16i bias[1], biasB[1];
     load_bias_rows<1>(a, 0, half, bias);
@@ -137,13 +97,13 @@ __global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a
     auto tile = [&](auto prev_tag, int v, int buf, v16i (&acc)[RPW], v16i (&accB)[RPW], const v16i (&old)[RPW], const v16i (&oldB)[RPW], const Done &was, Done &now) {
         constexpr bool PREV = decltype(prev_tag)::value;
         int n, y0, x0;
-        tile_origin(v, n, y0, x0);
+        g.template origin<kRowsTH, kRowsTW>(v, n, y0, x0);
         now.pix = (n * a.H + y0 + RPW * wave) * a.W + x0 + col;
         now.rows = x0 + col < a.W ? min(RPW, a.H - y0 - RPW * wave) : 0;
-        const bool more = valid(v + (int)gridDim.x);
+        const bool more = g.valid(v + (int)gridDim.x);
         int nn = 0, ny0 = 0, nx0 = 0;
-        if (more) tile_origin(v + (int)gridDim.x, nn, ny0, nx0);
-        const int nbase = patch_base(nn, ny0, nx0);
+        if (more) g.template origin<kRowsTH, kRowsTW>(v + (int)gridDim.x, nn, ny0, nx0);
+        const int nbase = Patch::base(a, nn, ny0, nx0);
         const uint8_t *const P = pbuf + buf * PATCH;
 
         constexpr int ROWS = RPW + KS - 1;           // input rows under the wave's output rows
@@ -233,10 +193,10 @@ __global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a
     tile(std::false_type{}, v, 0, acc0, accB0, acc1, accB1, d1, d0);
     for (;;) {
         v += gridDim.x;
-        if (!valid(v)) { finish(acc0, accB0, d0); break; }
+        if (!g.valid(v)) { finish(acc0, accB0, d0); break; }
         tile(std::true_type{}, v, 1, acc1, accB1, acc0, accB0, d0, d1);
         v += gridDim.x;
-        if (!valid(v)) { finish(acc1, accB1, d1); break; }
+        if (!g.valid(v)) { finish(acc1, accB1, d1); break; }
         tile(std::true_type{}, v, 0, acc0, accB0, acc1, accB1, d1, d0);
     }
 #endif
@@ -255,17 +215,9 @@ bool conv_rows_twin_applies(const ConvArgs &a, const ConvArgs &b)
 
 hipError_t launch_conv_rows_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st)
 {
-    RowsArgs g;
-    g.tiles_x = (a.W + kRowsTW - 1) / kRowsTW;
-    g.tiles_per_img = g.tiles_x * ((a.H + kRowsTH - 1) / kRowsTH);
-    const long long tiles = (long long)g.tiles_per_img * a.N;
-    if (tiles < 1 || tiles > 0x7ffffff0LL / 8) return hipErrorInvalidValue;
-    g.n_tiles = (int)tiles;
-    g.per_xcd = (int)((tiles + 7) / 8);
-    g.div_tpi = make_fast_div((unsigned)g.tiles_per_img);
-    g.div_tx = make_fast_div((unsigned)g.tiles_x);
-    constexpr int NCOPY = ((kRowsTH + 4) * (kRowsTW + 4) * 4 + 63) / 64;
-    constexpr size_t lds_bytes = (50 + 18) * 1024 + 2 * (size_t)NCOPY * 1024;
+    TileWalk g;
+    if (!tile_walk(g, a.N, a.H, a.W, kRowsTH, kRowsTW)) return hipErrorInvalidValue;
+    constexpr size_t lds_bytes = (50 + 18) * 1024 + 2 * (size_t)TilePatch<5, 64, kRowsTH, kRowsTW, 4>::BYTES;
     const auto kernel = a.rqh && b.rqh ? conv_rows_twin_kernel<4> : conv_rows_twin_kernel<3>;
     const hipError_t e = allow_large_lds((const void *)kernel);
     if (e != hipSuccess) return e;

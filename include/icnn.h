@@ -153,13 +153,13 @@ int iconv2d_validate(const icnn_conv_desc *desc);
 /* Output height and width of the layer (host only). */
 int iconv2d_out_hw(const icnn_conv_desc *desc, int32_t *ho, int32_t *wo);
 
-/* Bytes of device workspace iconv2d_brelu uses for this layer (may be 0): the padded copy of a layer with cin <= 4,
- * or the partial sums of a layer whose K axis is split over workgroups.  The caller zero-fills a workspace once after
- * allocating it (its first 4096 bytes are counters that every call leaves at zero); one workspace of the largest size
- * may serve all layers that run one after the other on a stream.  Layers that split K also run without a workspace
- * (NULL): then the K axis stays whole.  A layer with cin <= 4 always needs its workspace passed, although the
- * stride-1 forms that the library convolves straight off the picture (8-bit output, 32 or 64 channels, kernel up to
- * 8 x 8, no skip operand) leave it untouched. */
+/* Bytes of device workspace iconv2d_brelu uses for this layer (may be 0): the padded copy of a layer with cin <= 4.
+ * (Under the "ksplit" override of icnn_set_tuning also the partial sums of a layer whose K axis it splits over workgroups;
+ * the library does not split by itself, and such a layer also runs without a workspace, its K axis whole.)  The caller
+ * zero-fills a workspace once after allocating it (its first 4096 bytes are counters that every call leaves at zero);
+ * one workspace of the largest size may serve all layers that run one after the other on a stream.  A layer with
+ * cin <= 4 always needs its workspace passed, although the stride-1 forms that the library convolves straight off the
+ * picture (8-bit output, 32 or 64 channels, kernel up to 8 x 8, no skip operand) leave it untouched. */
 int iconv2d_workspace_bytes(const icnn_conv_desc *desc, size_t *bytes);
 
 /* Bytes of the library's packed weight format for this layer. */

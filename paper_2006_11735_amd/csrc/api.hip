@@ -405,7 +405,7 @@ static int conv_layer(const icnn_conv_desc *d, const void *x, const void *w_pack
         return launched(launch_conv(a, true, true, (hipStream_t)stream), what);
     }
     const bool vec_in = aligned16(x) && d->cin % 16 == 0 && d->in_c_stride % 16 == 0;
-    // layers with few tiles and a long K axis split it over workgroups when the caller brought the workspace
+    // under the "ksplit" override a layer splits its K axis over workgroups when the caller brought the workspace
     // iconv2d_workspace_bytes asked for (a workspace passed to a layer that asked for none is not touched)
     if (workspace && conv_split_bytes(a, vec_in) != 0) {
         a.ws_cnt = (unsigned *)workspace;

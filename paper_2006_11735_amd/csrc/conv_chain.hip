@@ -16,6 +16,10 @@
 //            reads one activation fragment (1 KiB of LDS) per matrix instruction.
 //   work     layer l's pixels in groups of 32 (row-major over the region); wave w takes groups (w >> 1), + 4, ...
 //   barrier  one per layer
+//
+// Measured on 256 x 256: a launch of four layers 15 to 16 us, four launches 24 us; under rocprofv3 the matrix cores are busy 22 % of the GPU-active
+// cycles (28 % of the kernel's own time at 2.4 GHz, recomputed borders included), LDS bank conflicts hold 11 % of the clocks (pixel groups
+// that straddle rows).  The rest is the chain patch -> layer -> barrier -> layer with eight waves on a compute unit.
 #include "conv_common.h"
 
 #include <type_traits>

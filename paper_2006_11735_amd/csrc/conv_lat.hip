@@ -11,6 +11,8 @@
 //   weights      the packed order is the fragment order: 1 KiB of consecutive bytes per wave and fragment
 //   activations  a lane's fragment is 16 consecutive channels of its pixel's tap; borders and the K tail of a wave come as
 //                zeros from the buffer descriptors' range checks
+//   measured     33 of the 42 launches of one image through the 50-layer network, 5.6 us each (kernel trace), of which the matrix cores work
+//                1 %: launch, one latency of the memory side (weights from beyond L2), the meeting in LDS
 //   order        work units are dealt channel-major to the XCDs, so that each L2 fetches an eighth of the weights
 //
 // DUAL: a residual block's last layer with its projection (see conv_dual.hip): both contractions have accumulators and

@@ -91,7 +91,7 @@ def test_config3_per_channel_full_batch_sampled_images(floor_channels):
                 continue
             got = g.result(name)[img:img + 1]
             assert (got == want[name]).all(), (img, name)
-    assert len(g.fused_proj) == 4 and not g.fused_block       # per-channel layers are not taken by the block kernel
+    assert len(g.fused_proj) == 4 and not g.fused_block       # (per-channel blocks are listed in fused_block_pc)
 
 
 def stored(cfg):
@@ -200,7 +200,7 @@ def test_converted_float_networks(per_channel):
 
 
 def test_config5_resnet18_full_batch_sampled_images():
-    # basic blocks: 3x3 convs with the skip merge in their epilogue, int32 projections unfused
+    # basic blocks: 3x3 convs with the skip merge in their epilogue; the merge is a 3x3 layer, so its projection stays a launch of its own
     from paper_2006_11735_amd.netrun import GpuNet
     net, calib = W.CONFIGS["cfg5"](), stored("cfg5")
     g = GpuNet(net, 0, calib)

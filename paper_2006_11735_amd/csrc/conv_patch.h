@@ -98,17 +98,21 @@ struct TilePatch {
 #if defined(__HIP_DEVICE_COMPILE__)
 // A layer's packed weights (BYTES of them, whole KiB) to LDS as they are, by WAVES waves: direct copies of 1 KiB per wave, all in flight together
 // with the first patch.  (Through registers the copy loop waited out one memory latency per 8 KiB, five of them for a 3x3 layer of
-// 64 channels, which is most of the kernel's time on a picture with one tile per workgroup.)
-template <int WAVES, int BYTES>
+// 64 channels, which is most of the kernel's time on a picture with one tile per workgroup.)  UNROLL: not where a wave has many copies and the
+// tile loop behind them all the registers: unrolled, the addresses of seventeen copies are held across it.
+template <int WAVES, int BYTES, bool UNROLL = true>
 __device__ __forceinline__ void copy_packed_weights(const uint8_t *wp, unsigned wp_bytes, uint8_t *dst, int wave, int lane)
 {
     const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)wp, 0, wp_bytes, 0x00020000);
+    auto copy = [&](int e) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, (__attribute__((address_space(3))) void *)(dst + e * 1024), 16, (unsigned)(e * 1024 + lane * 16), 0, 0, 0);
+    };
+    if constexpr (UNROLL) {
 #pragma unroll
-    for (int e0 = 0; e0 < BYTES / 1024; e0 += WAVES) {
-        const int e = e0 + wave;
-        if (e < BYTES / 1024)                        // wave-uniform
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_w, (__attribute__((address_space(3))) void *)(dst + e * 1024), 16, (unsigned)(e * 1024 + lane * 16), 0,
-                                                     0, 0);
+        for (int e0 = 0; e0 < BYTES / 1024; e0 += WAVES)
+            if (e0 + wave < BYTES / 1024) copy(e0 + wave);      // wave-uniform
+    } else {
+        for (int e = wave; e < BYTES / 1024; e += WAVES) copy(e);
     }
 }
 #endif

@@ -73,8 +73,8 @@ __global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a
         g.template origin<kRowsTH, kRowsTW>(v0, n, y0, x0);
         const int base = Patch::base(a, n, y0, x0);
         static_for<CPW>([&](auto i_tag) { issue_copy(i_tag, base, y0, x0, 0); });
-        copy_packed_weights<4, WBYTES>(a.wp, a.wp_bytes, wbuf, wave, lane);
-        copy_packed_weights<4, WBYTESB>(b.wp, b.wp_bytes, wbufB, wave, lane);
+        copy_packed_weights<4, WBYTES, false>(a.wp, a.wp_bytes, wbuf, wave, lane);
+        copy_packed_weights<4, WBYTESB, false>(b.wp, b.wp_bytes, wbufB, wave, lane);
     }
     v16i bias[1], biasB[1];
     load_bias_rows<1>(a, 0, half, bias);

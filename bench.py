@@ -39,7 +39,7 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def layer_work(net, op, images, fused_proj=None, fused_block=None, fused_pool=None, fused_pair=None, fused_projblock=None, fused_twin=None, fused_chain=None, fused_twin_last=None):
+def layer_work(net, op, images, fused_proj=None, fused_block=None, fused_pool=None, fused_pair=None, fused_projblock=None, fused_twin=None, fused_chain=None, fused_twin_last=None, fused_triple=None):
     """Algorithmic ops and bytes of one conv launch (true sizes, input counted once).  With a
     projection fused into the launch, its ops, input and weights are added and the int32 skip
     tensor is not counted (it never exists).  With a whole bottleneck block in the launch: the ops of its
@@ -75,6 +75,13 @@ def layer_work(net, op, images, fused_proj=None, fused_block=None, fused_pool=No
         opsb, bb, _, kb = layer_work(net, fused_twin, images)
         _, h, w, _ = net["buffers"][op["src"]]["shape"]
         return opsa + opsb, ba + bb - images * h * w * op["cin"], m, ka + kb
+    if fused_triple is not None:
+        # a 3x3 layer, the layer that closes its block and the next block's first in one launch: all layers' ops, weights and outputs, the
+        # first one's input and the skip operand (the others' inputs are not read back from memory)
+        o2, o1 = fused_triple
+        ops2, b2, m, k2 = layer_work(net, o2, images)
+        ops3, b3, _, k3 = layer_work(net, op, images, fused_pair=o1)
+        return ops2 + ops3, b2 + b3 - m * op["cin"], m, k2 + k3
     if fused_pair is not None:
         # two pointwise layers in one launch: both layers' ops; the first layer's input, skip operand and output, both
         # layers' weights, the second layer's output (the second layer's input is not read back from memory)
@@ -115,7 +122,7 @@ def layer_work(net, op, images, fused_proj=None, fused_block=None, fused_pool=No
 
 # kind of a convolution launch (without the "_pc" of per-channel requantisation) -> layer_work's argument for what the launch holds beside the layer
 FUSED_KINDS = {"conv": None, "dual": "fused_proj", "block": "fused_block", "convpool": "fused_pool", "pair": "fused_pair", "projblock": "fused_projblock",
-               "twin": "fused_twin", "chain": "fused_chain", "twin_last": "fused_twin_last"}
+               "twin": "fused_twin", "chain": "fused_chain", "twin_last": "fused_twin_last", "triple": "fused_triple"}
 
 
 def step_work(g, i):
@@ -143,6 +150,9 @@ def step_name(g, i):
         tail = "+" + g.fused_twin[name]["name"]
     elif base == "twin_last":
         tail = "".join("+" + o["name"] for o in g.fused_twin_last[name])
+    elif base == "triple":
+        o2, o1 = g.fused_triple[name]
+        name, tail = o2["name"], "+c3" + ("+next_c1" if o1 is not None else "")
     elif base == "chain":
         tail = "_chain%d" % (len(g.fused_chain[name]) + 1)
     return name + tail
@@ -565,7 +575,7 @@ def main():
         "conv_tops": conv_tops,
         "pct_int8_mfma_peak": 100 * conv_tops / INT8_MFMA_PEAK_TOPS,
         "whole_step_tops": conv_ops / (ms_per_step * 1e-3) / 1e12,
-        "roofline": {"kernel": "conv kernels (all %d conv launches of a step: conv_dlds / conv_greg / conv_lat / conv_halo / conv_deep / conv_plane / conv_rows / conv_tail / conv_chain / conv_pic / conv_narrow / conv_dual / conv_block / conv_block64 / conv_pair / conv_stem_pool, every tile shape)" % n_conv,
+        "roofline": {"kernel": "conv kernels (all %d conv launches of a step: conv_dlds / conv_greg / conv_lat / conv_halo / conv_deep / conv_plane / conv_rows / conv_tail / conv_chain / conv_pic / conv_narrow / conv_dual / conv_block / conv_block64 / conv_pair / conv_tri / conv_stem_pool, every tile shape)" % n_conv,
                      "bound": "mfma", "achieved": conv_tops, "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s",
                      "frac": conv_tops / INT8_MFMA_PEAK_TOPS, "traffic": traffic, "traffic_stale": traffic_stale,
                      "peak_measured": peak_tops, "frac_of_peak_measured": conv_tops / peak_tops,

@@ -138,6 +138,7 @@ const char *icnn_last_error(void);
  *   "plane_always" 1 lets the kernel with two-dimensional tiles (few channels, large pictures) take every layer it accepts
  *   "deep_always" 1 lets the 3x3 kernel whose waves split the K axis take every layer whose shape it accepts
  *   "deep_plain_walk" 1 gives that kernel the tile order of the other kernels (pixel tiles, not channel tiles, per XCD)
+ *   "tri_tile"    0 library's choice; 1..4 = tiles of 32, 64, 96 or 112 pixels in the 3x3 + 1x1 + 1x1 kernel
  *   "ksplit"      0, 1 never split the K axis over workgroups (the library's choice); 2..8 that split where it divides the K steps
  *   "reset"       (value ignored) back to the library's choices
  * Unknown names and values outside these ranges return ICNN_E_PARAM and change nothing. */
@@ -360,6 +361,30 @@ int iconv2d_pair_brelu_pc(const icnn_conv_desc *c3, const void *t, const void *w
                           const void *pc1_packed, void *z, void *stream);
 
 /*
+ * The second half of one bottleneck block and the first layer of the next as one launch: the 3x3 convolution, the 1x1 convolution
+ * that closes the block (skip operand merged in its epilogue, Section 4.1; Section 3.1 for each layer) and the 1x1 convolution that
+ * opens the next block.  Result: exactly that of
+ *     iconv2d_brelu(c2, t,  w2_packed, bias2, NULL, t2, ...);     // 3x3, stride 1, padding 1
+ *     iconv2d_brelu(c3, t2, w3_packed, bias3, res,  y,  ...);     // 1x1, stride 1, no padding
+ *     iconv2d_brelu(c1, y,  w1_packed, bias1, NULL, z,  ...);     // 1x1, stride 1, no padding
+ * c1 = NULL leaves the last layer away (w1_packed, bias1 and z are then not read); t2 = NULL leaves the middle tensor unwritten (c3's
+ * in_c_stride and, with c1, c1's are not used).  lanes (at least 1): how many such launches the program runs side by side (the parts of a
+ * batch); it changes the launch's shape, never a result.  Shapes it takes: 256 -> 256 -> 1024 (-> 256) channels, images up to 196 pixels wide; c2 and, with c1, c3 store unsigned bytes bounded by
+ * at most 127 from a lower clamp of 0, c3 without c1 any unsigned bytes; c1 likewise; c3 takes no skip operand or an unsigned 8-bit one
+ * joined before requantisation whose rescale fits 32 bits, c2 and c1 none; inputs ICNN_IN_U8_LE127; tensors, bias arrays and pitches
+ * 16-byte aligned, tensors below 2 GiB; no output overlaps t, another output, or res (y may be res itself).  Anything else returns
+ * ICNN_E_UNSUPPORTED having launched nothing, and the caller issues the layers separately.
+ */
+int iconv2d_triple_brelu(const icnn_conv_desc *c2, const void *t, const void *w2_packed, const int32_t *bias2, void *t2,
+                         const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *res, void *y,
+                         const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, void *z, int32_t lanes, void *stream);
+/* ... per output channel, as three iconv2d_brelu_pc calls (an unsigned 8-bit skip operand may have any rescale) */
+int iconv2d_triple_brelu_pc(const icnn_conv_desc *c2, const void *t, const void *w2_packed, const int32_t *bias2, const void *pc2_packed, void *t2,
+                            const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3_packed, const void *res,
+                            void *y, const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, const void *pc1_packed, void *z,
+                            int32_t lanes, void *stream);
+
+/*
  * Two branches of one input as one launch: the layers of different kernel sizes whose outputs are concatenated
  * (Section 4.1, zero-copy concatenation: each branch is calibrated to the shared bound and writes its channel range
  * of the common buffer; Section 3.1 for each layer).  Result: exactly that of
@@ -417,13 +442,14 @@ int iconv2d_chain_split(int32_t n_layers, const icnn_conv_desc *const *descs, in
  * entry point that its kind names (the first error ends the list and is returned).  For programs that issue the same calls again
  * and again, whose cost on the host is then one call's marshalling and not n.  Which fields a kind reads, in the order of
  * the entry point's own arguments: d its descriptors, i its integers, p its device pointers (absent ones NULL);
- * ICNN_CALL_CHAIN: i[0] layers, list[0..2] the host arrays descs, w_packed and bias, p[0] = x, p[1] = y.
+ * ICNN_CALL_CHAIN: i[0] layers, list[0..2] the host arrays descs, w_packed and bias, p[0] = x, p[1] = y;
+ * ICNN_CALL_TRIPLE: i[0] lanes; ICNN_CALL_TRIPLE_PC: list[0..2] the channel parameters pc2_packed, pc3_packed and pc1_packed, i, p and d as ICNN_CALL_TRIPLE.
  */
 typedef enum {
     ICNN_CALL_CONV = 0, ICNN_CALL_CONV_PC = 1, ICNN_CALL_DUAL = 2, ICNN_CALL_DUAL_PC = 3, ICNN_CALL_CONV_MAXPOOL = 4, ICNN_CALL_BOTTLENECK = 5,
     ICNN_CALL_BOTTLENECK_DUAL = 6, ICNN_CALL_PAIR = 7, ICNN_CALL_TWIN = 8, ICNN_CALL_CHAIN = 9, ICNN_CALL_MAXPOOL = 10, ICNN_CALL_AVGPOOL = 11,
     ICNN_CALL_CONV_MAXPOOL_PC = 12, ICNN_CALL_BOTTLENECK_PC = 13, ICNN_CALL_BOTTLENECK_DUAL_PC = 14, ICNN_CALL_PAIR_PC = 15,
-    ICNN_CALL_TWIN_LAST = 16
+    ICNN_CALL_TWIN_LAST = 16, ICNN_CALL_TRIPLE = 17, ICNN_CALL_TRIPLE_PC = 18
 } icnn_call_kind;
 typedef struct {
     int32_t kind;                  /* icnn_call_kind */

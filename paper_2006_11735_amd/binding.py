@@ -44,7 +44,7 @@ class icnn_call(C.Structure):
 
 (ICNN_CALL_CONV, ICNN_CALL_CONV_PC, ICNN_CALL_DUAL, ICNN_CALL_DUAL_PC, ICNN_CALL_CONV_MAXPOOL, ICNN_CALL_BOTTLENECK, ICNN_CALL_BOTTLENECK_DUAL,
  ICNN_CALL_PAIR, ICNN_CALL_TWIN, ICNN_CALL_CHAIN, ICNN_CALL_MAXPOOL, ICNN_CALL_AVGPOOL, ICNN_CALL_CONV_MAXPOOL_PC, ICNN_CALL_BOTTLENECK_PC,
- ICNN_CALL_BOTTLENECK_DUAL_PC, ICNN_CALL_PAIR_PC, ICNN_CALL_TWIN_LAST) = range(17)
+ ICNN_CALL_BOTTLENECK_DUAL_PC, ICNN_CALL_PAIR_PC, ICNN_CALL_TWIN_LAST, ICNN_CALL_TRIPLE, ICNN_CALL_TRIPLE_PC) = range(19)
 
 
 class IcnnError(RuntimeError):
@@ -88,6 +88,8 @@ _lib.iconv2d_maxpool_brelu_pc.argtypes = [_descp, _i32, _i32, _i32, _vp, _vp, _v
 _lib.iconv2d_bottleneck_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp] + [_descp, _vp, _vp, _vp] * 2 + [_vp, _vp, _vp]
 _lib.iconv2d_bottleneck_dual_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp] + [_descp, _vp, _vp, _vp] * 2 + [_descp, _vp, _vp, _vp, _vp]
 _lib.iconv2d_pair_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp, _vp, _vp, _descp, _vp, _vp, _vp, _vp, _vp]
+_lib.iconv2d_triple_brelu.argtypes = [_descp, _vp, _vp, _vp, _vp, _descp, _vp, _vp, _vp, _vp, _descp, _vp, _vp, _vp, _i32, _vp]
+_lib.iconv2d_triple_brelu_pc.argtypes = [_descp, _vp, _vp, _vp, _vp, _vp, _descp, _vp, _vp, _vp, _vp, _vp, _descp, _vp, _vp, _vp, _vp, _i32, _vp]
 _lib.iconv2d_twin_last_brelu.argtypes = [_descp, _vp, _vp, _vp] + [_descp, _vp, _vp] * 2 + [_vp, _vp, _vp]
 _lib.iconv2d_chain_brelu.argtypes = [_i32, C.POINTER(_descp), _vp, C.POINTER(_vp), C.POINTER(_vp), _vp, _vp]
 _lib.iconv2d_chain_split.argtypes = [_i32, C.POINTER(_descp), C.POINTER(_i32), C.POINTER(_i32)]
@@ -107,7 +109,7 @@ _lib.icnn_peak_copy.argtypes = [_vp, _vp, C.c_size_t, _vp]
 EXPORTS = ["icnn_version", "icnn_last_error", "icnn_set_tuning", "iconv2d_validate", "iconv2d_out_hw",
            "iconv2d_workspace_bytes", "iconv2d_packed_weight_bytes", "iconv2d_prepack_weights",
            "iconv2d_brelu", "iconv2d_brelu_static_ws", "iconv2d_packed_channel_params_bytes", "iconv2d_prepack_channel_params", "iconv2d_brelu_pc",
-           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_maxpool_brelu_pc", "iconv2d_bottleneck_brelu_pc", "iconv2d_bottleneck_dual_brelu_pc", "iconv2d_pair_brelu_pc", "iconv2d_twin_brelu", "iconv2d_twin_last_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "icnn_run_calls", "icnn_lanes_create", "icnn_lanes_destroy", "icnn_run_lanes", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
+           "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu", "iconv2d_bottleneck_dual_brelu", "iconv2d_pair_brelu", "iconv2d_maxpool_brelu_pc", "iconv2d_bottleneck_brelu_pc", "iconv2d_bottleneck_dual_brelu_pc", "iconv2d_pair_brelu_pc", "iconv2d_triple_brelu", "iconv2d_triple_brelu_pc", "iconv2d_twin_brelu", "iconv2d_twin_last_brelu", "iconv2d_maxpool_brelu", "iconv2d_chain_brelu", "iconv2d_chain_split", "icnn_run_calls", "icnn_lanes_create", "icnn_lanes_destroy", "icnn_run_lanes", "iadd_rescale", "iconcat", "imaxpool2d_u8", "iavgpool_global_u8",
            "irenormalize_u8", "icnn_peak_mfma_i8", "icnn_peak_copy"]
 
 
@@ -294,6 +296,20 @@ def iconv2d_pair_brelu_pc(c3, t, w3_packed, bias3, pc3, res, y, c1, w1_packed, b
                                              _ptr(w1_packed), _ptr(bias1), _ptr(pc1), _ptr(z), _stream(stream)))
 
 
+def iconv2d_triple_brelu(c2, t, w2_packed, bias2, t2, c3, w3_packed, bias3, res, y, c1, w1_packed, bias1, z, lanes=1, stream=None):
+    """c1, w1_packed, bias1, z: None without the third layer; t2: None leaves the middle tensor unwritten; lanes: such launches side by side"""
+    return _check(_lib.iconv2d_triple_brelu(C.byref(c2), _ptr(t), _ptr(w2_packed), _ptr(bias2), _ptr(t2), C.byref(c3), _ptr(w3_packed), _ptr(bias3),
+                                            _ptr(res), _ptr(y), None if c1 is None else C.byref(c1), _ptr(w1_packed), _ptr(bias1), _ptr(z),
+                                            int(lanes), _stream(stream)))
+
+
+def iconv2d_triple_brelu_pc(c2, t, w2_packed, bias2, pc2, t2, c3, w3_packed, bias3, pc3, res, y, c1, w1_packed, bias1, pc1, z, lanes=1, stream=None):
+    return _check(_lib.iconv2d_triple_brelu_pc(C.byref(c2), _ptr(t), _ptr(w2_packed), _ptr(bias2), _ptr(pc2), _ptr(t2), C.byref(c3),
+                                               _ptr(w3_packed), _ptr(bias3), _ptr(pc3), _ptr(res), _ptr(y),
+                                               None if c1 is None else C.byref(c1), _ptr(w1_packed), _ptr(bias1), _ptr(pc1), _ptr(z),
+                                               int(lanes), _stream(stream)))
+
+
 def iconv2d_twin_brelu(ca, x, wa_packed, bias_a, ya, cb, wb_packed, bias_b, yb, stream=None):
     return _check(_lib.iconv2d_twin_brelu(C.byref(ca), _ptr(x), _ptr(wa_packed), _ptr(bias_a), _ptr(ya), C.byref(cb),
                                           _ptr(wb_packed), _ptr(bias_b), _ptr(yb), _stream(stream)))
@@ -342,6 +358,19 @@ class Calls:
             c.kind, c.i[0] = ICNN_CALL_CHAIN, n
             c.list[0], c.list[1], c.list[2] = C.addressof(dp), C.addressof(wp), C.addressof(bp)
             c.p[0], c.p[1] = _ptr(x), _ptr(y)
+            return
+        if kind in ("triple", "triple_pc"):
+            args = list(args)
+            if kind == "triple_pc":                                # the packed channel parameters of c2, c3 and c1
+                for k, at in ((2, 15), (1, 9), (0, 4)):
+                    c.list[k] = _ptr(args.pop(at))
+            c2, t, w2, b2, t2, c3, w3, b3, res, y, c1, w1, b1, z, c.i[0] = args
+            c.kind = ICNN_CALL_TRIPLE if kind == "triple" else ICNN_CALL_TRIPLE_PC
+            for k, d in enumerate((c2, c3, c1)):
+                if d is not None:
+                    c.d[k] = C.pointer(d)
+            for k, q in enumerate((t, w2, b2, t2, w3, b3, res, y, w1, b1, z)):
+                c.p[k] = _ptr(q)
             return
         # (kind, integers in the argument list before the first pointer or after the first descriptor)
         c.kind, ints = {"conv": (ICNN_CALL_CONV, 0), "conv_pc": (ICNN_CALL_CONV_PC, 0), "dual": (ICNN_CALL_DUAL, 0),

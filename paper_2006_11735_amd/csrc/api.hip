@@ -182,7 +182,7 @@ int icnn_set_tuning(const char *name, int32_t value)
         {"halo_always", &Tuning::halo_always, 0, 1}, {"no_stream", &Tuning::no_stream, 0, 1},
         {"ksplit", &Tuning::ksplit, 0, 8}, {"no_block64", &Tuning::no_block64, 0, 1},
         {"no_plane", &Tuning::no_plane, 0, 1}, {"no_pic", &Tuning::no_pic, 0, 1}, {"block_any_form", &Tuning::block_any_form, 0, 1}, {"plane_no_pipe", &Tuning::plane_no_pipe, 0, 1}, {"plane_always", &Tuning::plane_always, 0, 1},
-        {"no_deep", &Tuning::no_deep, 0, 1}, {"deep_always", &Tuning::deep_always, 0, 1}, {"deep_plain_walk", &Tuning::deep_plain_walk, 0, 1},
+        {"no_deep", &Tuning::no_deep, 0, 1}, {"deep_always", &Tuning::deep_always, 0, 1}, {"deep_plain_walk", &Tuning::deep_plain_walk, 0, 1}, {"tri_tile", &Tuning::tri_tile, 0, 4},
     };
     if (!strcmp(name, "reset")) {
         g_tuning = Tuning();
@@ -868,6 +868,89 @@ int iconv2d_pair_brelu_pc(const icnn_conv_desc *c3, const void *t, const void *w
     return pair_layers(c3, t, w3_packed, bias3, pc3_packed, res, y, c1, w1_packed, bias1, pc1_packed, z, stream, "iconv2d_pair_brelu_pc");
 }
 
+static int triple_layers(const icnn_conv_desc *c2, const void *t, const void *w2_packed, const int32_t *bias2, const void *pc2, void *t2,
+                         const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3, const void *res, void *y,
+                         const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, const void *pc1, void *z, int32_t lanes,
+                         void *stream, const char *what)
+{
+    ConvGeom g2, g3, g1;
+    int rc = check_conv(c2, &g2);
+    if (rc) return rc;
+    if ((rc = check_conv(c3, &g3))) return rc;
+    if (c1 && (rc = check_conv(c1, &g1))) return rc;
+    if (lanes < 1) return fail(ICNN_E_PARAM, "lanes must be >= 1");
+    for (const icnn_conv_desc *d : {c2, c3, c1}) {
+        if (!d) continue;
+        if (d->n != c2->n || d->h != c2->h || d->w != c2->w) return fail(ICNN_E_SHAPE, "the layers must share n, h, w");
+        const int k = d == c2 ? 3 : 1;
+        if (d->kh != k || d->kw != k || d->pad_h != k / 2 || d->pad_w != k / 2 || d->stride_h != 1 || d->stride_w != 1)
+            return fail(ICNN_E_UNSUPPORTED, "fused run is a 3x3 layer with padding 1 and one or two 1x1 layers, all of stride 1");
+        if (d->in_signed != ICNN_IN_U8_LE127 || d->in_sub128) return fail(ICNN_E_UNSUPPORTED, "fused run takes unsigned inputs up to 127 only");
+        if ((d->out_mode != ICNN_OUT_BRELU_U8 && d->out_mode != ICNN_OUT_CLAMP_U8) || (d->out_mode == ICNN_OUT_CLAMP_U8 && d->lo != 0))
+            return fail(ICNN_E_UNSUPPORTED, "the layers of a fused run store unsigned bytes from a lower clamp of 0");
+        if (d != c3 && d->res_mode != ICNN_RES_NONE) return fail(ICNN_E_UNSUPPORTED, "only the middle layer of a fused run takes a skip operand");
+        // what another layer of the launch multiplies has to be a signed byte as well
+        if ((d == c2 || (d == c3 && c1)) && (d->out_mode == ICNN_OUT_BRELU_U8 ? d->bound_q : d->hi) > 127)
+            return fail(ICNN_E_UNSUPPORTED, "the inner results of a fused run must be bytes in 0..127");
+    }
+    if (c3->cin != c2->cout || (c1 && c1->cin != c3->cout)) return fail(ICNN_E_SHAPE, "the widths of the layers do not match");
+    if (c2->cin != kTriMid || c2->cout != kTriMid || c3->cout != kTriWide || (c1 && c1->cout != kTriMid))
+        return fail(ICNN_E_UNSUPPORTED, "fused run is 256 -> 256 -> 1024 (-> 256) channels");
+    if (!aligned16(t) || c2->in_c_stride % 16 != 0) return fail(ICNN_E_UNSUPPORTED, "fused run needs a 16-byte aligned input");
+    ConvArgs a2, a3, a1;
+    alignas(16) int32_t dummy[4] = {0, 0, 0, 0};        // stands for a middle tensor that never reaches memory
+    if ((rc = fill_conv_args(c2, g2, t, w2_packed, bias2, nullptr, t2 ? t2 : dummy, a2))) return rc;
+    if ((rc = fill_conv_args(c3, g3, t, w3_packed, bias3, res, y, a3))) return rc;
+    if (c1 && (rc = fill_conv_args(c1, g1, y, w1_packed, bias1, nullptr, z, a1))) return rc;
+    if ((rc = take_pc(a2, pc2)) || (rc = take_pc(a3, pc3)) || (c1 && (rc = take_pc(a1, pc1)))) return rc;
+    if (!a2.epi_vec || !a3.epi_vec || (c1 && !a1.epi_vec)) return fail(ICNN_E_UNSUPPORTED, "fused run needs 16-byte aligned output and skip tensors");
+    if (!a2.vec_bias || !a3.vec_bias || (c1 && !a1.vec_bias)) return fail(ICNN_E_UNSUPPORTED, "fused run needs 16-byte aligned bias arrays");
+    if (pc3 ? c3->res_mode == ICNN_RES_POST || (c3->res_mode == ICNN_RES_PRE && c3->res_dtype != ICNN_U8) : a3.epi_mode / 4 == 2)
+        return fail(ICNN_E_UNSUPPORTED, "fused run takes an unsigned 8-bit skip operand joined before requantisation");
+    if (!t2) a2.out = nullptr;
+    const bool skip = c3->res_mode != ICNN_RES_NONE;
+    // (pixel indices and the copies' byte offsets are 32 bits)
+    const unsigned long long res_bytes = skip ? (unsigned long long)(g3.M - 1) * c3->res_c_stride + c3->cout : 0;
+    if (a2.x_bytes >= 0x7fffff00u || res_bytes >= 0x7fffff00ull || g2.M > 0x7fffffffLL)
+        return fail(ICNN_E_UNSUPPORTED, "fused run needs tensors below 2 GiB");
+    {
+        const Slice in[2] = {input_slice(c2, t), skip ? slice_of(res, g3.M, c3->res_c_stride, 0, c3->cout, 1) : input_slice(c2, t)};
+        Slice out[3];
+        int n = 0;
+        if (t2) out[n++] = output_slice(c2, g2, t2);
+        if (c1) out[n++] = output_slice(c1, g1, z);
+        out[n++] = output_slice(c3, g3, y);
+        bool clash = false;
+        for (int i = 0; i < n; ++i) {
+            clash = clash || overlap(out[i], in[0]) || (i + 1 == n && skip ? overlap_beyond_pixels(out[i], y, in[1], res) : overlap(out[i], in[1]));
+            for (int j = 0; j < i; ++j) clash = clash || overlap(out[i], out[j]);
+        }
+        if (clash) return fail(ICNN_E_UNSUPPORTED, "the outputs of a fused run must not overlap each other or its inputs");
+    }
+    TriArgs q = {};
+    if (!conv_tri_plan(g2.M, c2->w, lanes, q)) return fail(ICNN_E_UNSUPPORTED, "the image is too wide for a tile's patch");
+    q.res_bytes = (unsigned)res_bytes;
+    return launched(launch_conv_tri(q, a2, a3, c1 ? &a1 : nullptr, (hipStream_t)stream), what);
+}
+
+int iconv2d_triple_brelu(const icnn_conv_desc *c2, const void *t, const void *w2_packed, const int32_t *bias2, void *t2,
+                         const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *res, void *y,
+                         const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, void *z, int32_t lanes, void *stream)
+{
+    return triple_layers(c2, t, w2_packed, bias2, nullptr, t2, c3, w3_packed, bias3, nullptr, res, y, c1, w1_packed, bias1, nullptr, z, lanes,
+                         stream, "iconv2d_triple_brelu");
+}
+
+int iconv2d_triple_brelu_pc(const icnn_conv_desc *c2, const void *t, const void *w2_packed, const int32_t *bias2, const void *pc2_packed, void *t2,
+                            const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3_packed, const void *res,
+                            void *y, const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, const void *pc1_packed, void *z,
+                            int32_t lanes, void *stream)
+{
+    if (!pc2_packed || !pc3_packed || (c1 && !pc1_packed)) return fail(ICNN_E_NULL, "packed channel parameters are NULL");
+    return triple_layers(c2, t, w2_packed, bias2, pc2_packed, t2, c3, w3_packed, bias3, pc3_packed, res, y, c1, w1_packed, bias1, pc1_packed, z,
+                         lanes, stream, "iconv2d_triple_brelu_pc");
+}
+
 // Geometry and arguments of two branches of one input
 static int twin_layers(const icnn_conv_desc *ca, const void *x, const void *wa_packed, const int32_t *bias_a, void *ya,
                        const icnn_conv_desc *cb, const void *wb_packed, const int32_t *bias_b, void *yb, ConvArgs &a, ConvArgs &b)
@@ -1166,6 +1249,13 @@ static int run_call(int32_t k, const icnn_call &c, void *stream)
                                               stream);
         break;
     case ICNN_CALL_PAIR_PC: rc = iconv2d_pair_brelu_pc(d[0], p[0], p[1], b(2), p[3], p[4], o(5), d[1], p[6], b(7), p[8], o(9), stream); break;
+    case ICNN_CALL_TRIPLE:
+        rc = iconv2d_triple_brelu(d[0], p[0], p[1], b(2), o(3), d[1], p[4], b(5), p[6], o(7), d[2], p[8], b(9), o(10), i[0], stream);
+        break;
+    case ICNN_CALL_TRIPLE_PC:
+        rc = iconv2d_triple_brelu_pc(d[0], p[0], p[1], b(2), c.list[0], o(3), d[1], p[4], b(5), c.list[1], p[6], o(7), d[2], p[8], b(9), c.list[2],
+                                     o(10), i[0], stream);
+        break;
     case ICNN_CALL_MAXPOOL: rc = imaxpool2d_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
     case ICNN_CALL_AVGPOOL: rc = iavgpool_global_u8(i[0], i[1], i[2], i[3], i[4], i[5], i[6], p[0], o(1), stream); break;
     default: rc = fail(ICNN_E_PARAM, "call %d: unknown kind %d", k, c.kind);

@@ -588,6 +588,57 @@ __device__ __forceinline__ void epilogue_rq24_slice(const P &a, const v16i &acc,
         else shift_into_byte(w[r >> 2], x, FORM == 4 ? 1 : sh_v, r & 3);
     }
 }
+// Outputs R0 .. R0 + N - 1 (N even) of epilogue_bytes16<RES, 1>: a layer with a.rq_fast whose skip operand's rescale, if any, is sk.  Five and
+// three quarter instructions per output, two and three quarters without the operand (the 32-bit form takes seven and three): every one of
+// them issues in the same four to five clocks on this chip, wide multiplies included (v_mad_i64_i32 4.6, v_mul_hi_u32 4.8, v_mad_u32_u24
+// 4.8 with two waves per SIMD and matrix instructions between them), so a product whose high word is the result wants no shift behind it.
+// Step by step for the N values together, so that none waits for the instruction just before it.
+// w: the words of the sixteen bytes, which the caller collects over its slices; a word's lower half is kept in it until the upper one comes.
+template <int RES, int R0, int N, class P>
+__device__ __forceinline__ void epilogue_hi_slice(const P &a, const SkipMul &sk, const v16i &acc, const v4i &res8, int (&w)[4])
+{
+    static_assert(N % 2 == 0 && R0 % 2 == 0, "whole pairs");
+    int t[N];
+    const int lo_v = a.lo;
+    if constexpr (RES == 1) {
+        uint32_t x[N];
+        // byte in the top bits, the rounding constant below it
+#pragma unroll
+        for (int e = 0; e < N; ++e)
+            x[e] = __builtin_amdgcn_perm((uint32_t)res8[(R0 + e) >> 2], sk.rnd, 0x00020100u | (uint32_t)(4 + ((R0 + e) & 3)) << 24);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < N; ++e) x[e] = __umulhi(x[e], sk.k);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < N; ++e) t[e] = __builtin_elementwise_add_sat(acc[R0 + e], (int)x[e]);
+        __builtin_amdgcn_sched_barrier(0);
+    } else {
+#pragma unroll
+        for (int e = 0; e < N; ++e) t[e] = acc[R0 + e];
+    }
+#pragma unroll
+    for (int e = 0; e < N; ++e) t[e] = (int)(((int64_t)t[e] * a.mul_hi + 0x80000000LL) >> 32);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < N; ++e) t[e] = med3_vvs(t[e], lo_v, a.hi);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < N; e += 2) {
+        const uint32_t two = __builtin_amdgcn_perm((uint32_t)t[e + 1], (uint32_t)t[e], 0x0c0c0400u);
+        if (((R0 + e) & 2) == 0) w[(R0 + e) >> 2] = (int)two;
+        else w[(R0 + e) >> 2] = (int)__builtin_amdgcn_perm(two, (uint32_t)w[(R0 + e) >> 2], 0x05040100u);
+    }
+}
+template <int RES, class P>
+__device__ __forceinline__ v4i epilogue_hi16(const P &a, const SkipMul &sk, const v16i &acc, const v4i &res8)
+{
+    int w[4];
+    epilogue_hi_slice<RES, 0, 8>(a, sk, acc, res8, w);
+    __builtin_amdgcn_sched_barrier(0);
+    epilogue_hi_slice<RES, 8, 8>(a, sk, acc, res8, w);
+    return v4i{w[0], w[1], w[2], w[3]};
+}
 // Between the last v_mfma of an accumulation and the first instruction that reads the accumulator.  The compiler's
 // hazard recogniser does not always keep the two apart (seen in a kernel whose epilogue starts two instructions after
 // the last MFMA, behind a branch: the reads returned the sums without the last product, now and then), and the

@@ -1,0 +1,468 @@
+// The second half of one bottleneck block and the first layer of the next as ONE kernel: 3x3 convolution (256 -> 256
+// channels), 1x1 convolution (256 -> 1024, skip operand merged in its epilogue, Section 4.1) and the 1x1 convolution
+// (1024 -> 256) that opens the next block and reads nothing but that result.  Cut this way, between a block's first two
+// layers instead of between blocks, nothing is computed twice: the only neighbours' values a tile needs are the 3x3
+// layer's input, which is in memory, and the two pointwise layers stay on the tile.
+//
+//   tile     PX consecutive pixels of the flattened N*H*W axis (32, 64, 96 or 112); patch: these and the W + 1 pixels
+//            before and behind them, so that tap (kh, kw) of a pixel is the patch row (kh - 1) * W + kw - 1 away; a tap
+//            beyond the image's edge reads a row of zeros instead, chosen by a mask of nine bits per pixel
+//   phase 1  b = BReLU/requant(W2 (*) t + b2) on the tile, from the patch in LDS; b replaces the patch
+//   phase 2  y = epilogue(W3 b + b3, skip), 256 of the 1024 channels at a time; the skip operand's tile was copied to LDS
+//            meanwhile and every lane replaces the sixteen bytes it has merged by its result
+//   phase 3  z = BReLU/requant(W1 y + b1) from y in LDS, while y goes to memory in whole rows
+//
+// Every wave owns 32 of the 256 output channels of a phase, on all the tile's pixels, so a weight byte is needed by one
+// wave of the workgroup only and goes from memory straight into that wave's registers, in packed order (which is the
+// fragment order), eight K steps ahead of its products and across the phases.  No K loop has a barrier.  LDS rows are
+// padded by 16 bytes: consecutive rows start one bank group apart, so the fragment reads of any 16 consecutive pixels are
+// free of conflicts and a row's channels are constant offsets from one address.
+#include "conv_common.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace icnn {
+
+// FORM: 1 all layers requantise as a product's high word (rq_fast), the skip operand rescaled likewise (g.sk), the block's last layer between matrix instructions; 0 any form,
+// chosen at run time; 2 per output channel.  NEXT: the next block's first layer is included.
+template <int NP, bool NEXT, int FORM>                 // NP: pixel groups of 32 (the fourth one half used)
+__global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const ConvArgs a2, const ConvArgs a3, const ConvArgs a1)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr unsigned OOB = 0x80000000u;
+    constexpr int MID = kTriMid, C = kTriWide, PX = tri_pixels(NP);
+    constexpr int AP = MID + 16, YP = C + 16;          // row pitches of the patch (later b) and of the skip operand (later y)
+    constexpr int S2 = 9 * 4, S1 = 16;                 // K steps of 64 of a wave's chunk: 3x3 layer, next block's layer (last layer: 4 per chunk)
+
+    // LDS: patch, then b | skip operand, then y | biases: [256] 3x3 layer, [1024] last, [256] next
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    const int yb = g.patch_bytes;
+    int32_t *const btab = (int32_t *)(lds + yb + PX * YP);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
+
+    // XCD-contiguous walk, as in the other fused kernels
+    auto tile_of = [&](int v) { return (v & 7) * g.per_xcd + (v >> 3); };
+    auto valid = [&](int v) { return (v >> 3) < g.per_xcd && tile_of(v) < g.n_tiles; };
+    // every LDS access of this wave is over before the others go on (fragment reads in flight included)
+    auto sync = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    // ---- copies global -> LDS, 1 KiB per wave-wide copy
+    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)a2.x, 0, a2.x_bytes, 0x00020000);
+    const bool has_res = a3.res_mode != 0;
+    const __amdgpu_buffer_rsrc_t rs_r =
+        __builtin_amdgcn_make_buffer_rsrc(has_res ? (void *)a3.res : (void *)a3.out, 0, has_res ? g.res_bytes : 0, 0x00020000);
+    // 16-byte piece i of the patch region is piece i % 17 of row i / 17; the seventeenth is padding.  Row r is pixel p0 - W - 1 + r; pixels
+    // outside the tensor, the padding and the rows behind the last one (the first of them is the row of zeros) get zeros.
+    auto issue_patch = [&](int p0) {
+        int l = lane;
+        asm volatile("" : "+v"(l));                    // (worked out here: left alone, the compiler keeps it all in registers)
+        const int first = p0 - g.W - 1;
+#pragma unroll 1
+        for (int c = wave; c < g.patch_bytes / 1024; c += 8) {
+            const int i = c * 64 + l;
+            const int row = (int)(((unsigned)i * 61681u) >> 20), piece = i - row * 17;         // / 17, exact below 2^16
+            const int p = first + row;
+            const unsigned off = piece < 16 && row < g.rows && (unsigned)p < (unsigned)a2.M ? (unsigned)p * (unsigned)a2.in_cs + piece * 16 : OOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + c * 1024), 16, off, 0, 0, 0);
+        }
+    };
+    // a pixel's whole skip operand per copy
+    auto issue_skip = [&](int p0) {
+        const int n = min(PX, a2.M - p0);
+#pragma unroll 1
+        for (int q = wave; q < n; q += 8)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_r, (__attribute__((address_space(3))) void *)(lds + yb + q * YP), 16, lane * 16,
+                                                     (unsigned)(p0 + q) * (unsigned)a3.res_cs, 0, 0);
+    };
+
+    // ---- weights: this wave's 32-channel chunk of every layer, two fragments per K step, a ring of eight steps
+    const uint8_t *const w2 = a2.wp + (size_t)wave * (S2 * kChunkBytes);
+    const uint8_t *const w3 = a3.wp + (size_t)wave * (4 * kChunkBytes);        // channels ch * 256 + ...: + ch * 32 steps
+    const uint8_t *const w1 = NEXT ? a1.wp + (size_t)wave * (S1 * kChunkBytes) : w2;
+    v4i ring[8][2];                                    // two groups of four steps
+    // (through a descriptor of the four steps at p: the address costs scalar instructions only, 36 clocks per matrix instruction of a SIMD in
+    // the K loops against 45 with 64-bit vector addresses)
+    auto steps_at = [&](const uint8_t *p) { return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 4 * kChunkBytes, 0x00020000); };
+    const int lane16 = lane * 16;
+    // fragment f of the ring (its steps' two fragments in order), from the group of four steps behind rs
+    auto load_frag = [&](auto f_tag, __amdgpu_buffer_rsrc_t rs) __attribute__((always_inline)) {
+        constexpr int f = decltype(f_tag)::value;
+        ring[f >> 1][f & 1] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane16 + (f & 1) * 1024, ((f >> 1) & 3) * kChunkBytes, 0);
+    };
+
+    // The launch's weights come from beyond the XCD's L2, and one workgroup's eight steps in flight do not cover that distance: at the start
+    // every wave touches its share of them, a 128-byte line per lane, workgroups without a tile included (the 152-layer network 1289 -> 1085 us
+    // at 32 images, 1690 -> 1600 at 64).  Not with launches side by side, which find them there: 2048 -> 2150 at two halves of 96.
+    // (in flight before the patch's copies, so they are over when those are; what they fetch lands in the skip operand's place before it does)
+    auto touch_weights = [&]() {
+        constexpr int N2 = 8 * S2 * kChunkBytes / 8192, N3 = 32 * 4 * kChunkBytes / 8192, N1 = NEXT ? 8 * S1 * kChunkBytes / 8192 : 0;
+        for (int i = (int)(blockIdx.x >> 3) * 8 + wave; i < N2 + N3 + N1; i += (int)gridDim.x) {
+            const uint8_t *const p = i < N2 ? a2.wp + i * 8192 : i < N2 + N3 ? a3.wp + (i - N2) * 8192 : a1.wp + (i - N2 - N3) * 8192;
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 8192, 0x00020000);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(lds + yb + wave * 256), 4, lane * 128, 0, 0, 0);
+        }
+    };
+
+    // ---- this lane's pixels q = 32 j + col of the tile; slots beyond the tile stay on its last pixel and are never stored
+    auto slot = [&](int j) { return min(32 * j + col, PX - 1); };
+    const int co = wave * 32 + half * 16;              // its sixteen channels inside the 256 of a phase
+    auto init = [&](v16i &c, const int32_t *tab) __attribute__((always_inline)) { c = bias16(tab + co); };
+
+    v16i acc[NP];
+    // half steps (32 channels) whose fragments are in flight: a half step is 32 NP clocks of matrix work, twice that beside the SIMD's other wave
+    constexpr int NB = NP >= 3 ? 2 : NP == 2 ? 4 : 8, AHEAD = NB - 1;
+    v4i bf[NB][NP];
+    auto read_frag = [&](auto h_tag, auto j_tag, const int (&ad)[NP]) __attribute__((always_inline)) {
+        constexpr int h = decltype(h_tag)::value, j = decltype(j_tag)::value;
+        bf[h % NB][j] = *(const v4i *)(lds + ad[j] + h * 32);
+    };
+    auto first_frags = [&](const int (&ad)[NP]) __attribute__((always_inline)) {
+        static_for<AHEAD>([&](auto h_tag) __attribute__((always_inline)) {
+            static_for<NP>([&](auto j_tag) __attribute__((always_inline)) { read_frag(h_tag, j_tag, ad); });
+        });
+    };
+    // Four K steps = 256 channels of the rows at ad: behind every matrix instruction, in its shadow, one fragment of the half step AHEAD of it is
+    // read (beyond the group: of the next group, at nad), behind every half step one weight fragment fetched from nx, eight steps on.
+    auto group = [&](auto half_tag, const int (&ad)[NP], const int (&nad)[NP], const uint8_t *nx) __attribute__((always_inline)) {
+        constexpr int R0 = 4 * decltype(half_tag)::value;       // the ring's half that this group multiplies
+        const __amdgpu_buffer_rsrc_t rs = steps_at(nx);
+        static_for<8>([&](auto h_tag) __attribute__((always_inline)) {
+            constexpr int h = decltype(h_tag)::value;
+            static_for<NP>([&](auto j_tag) __attribute__((always_inline)) {
+                constexpr int j = decltype(j_tag)::value, hn = h + AHEAD;
+                acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ring[R0 + (h >> 1)][h & 1], bf[h % NB][j], acc[j], 0, 0, 0);
+                asm volatile("" : "+v"(acc[j]));       // here, not wherever the sums are needed
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (hn < 8) read_frag(std::integral_constant<int, hn>{}, j_tag, ad);
+                else read_frag(std::integral_constant<int, hn - 8>{}, j_tag, nad);
+                if constexpr (j == NP - 1) load_frag(std::integral_constant<int, R0 * 2 + h>{}, rs);
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
+    };
+    using H0 = std::integral_constant<int, 0>;
+    using H1 = std::integral_constant<int, 1>;
+
+    // sixteen bytes of layer a at this lane's pixel, RES: with a skip operand
+    auto finish = [&](const ConvArgs &a, auto res_tag, const v16i &c, const v4i &r8, const int32_t *pc) __attribute__((always_inline)) {
+        constexpr int RES = decltype(res_tag)::value;
+        if constexpr (FORM == 2) return epilogue_pc_bytes16<RES>(a, c, r8, pc);
+        else if constexpr (FORM == 1) return epilogue_hi16<RES>(a, g.sk, c, r8);
+        else return epilogue_bytes16<RES>(a, c, r8);
+    };
+
+    if (!valid(blockIdx.x)) {
+        if (g.touch) touch_weights();
+        asm volatile("" ::: "memory");
+        ICNN_WAIT_VMCNT(0);
+        return;
+    }
+    {
+        int bv[3];                                     // requested before the patch, written to the table behind the ring's loads
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int i = tid + q * 512;
+            bv[q] = i < MID ? a2.bias[i] : (i < MID + C ? a3.bias[i - MID] : NEXT ? a1.bias[i - MID - C] : 0);
+        }
+        asm volatile("" ::: "memory");
+        if (g.touch) touch_weights();
+        issue_patch(tile_of(blockIdx.x) * PX);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        const __amdgpu_buffer_rsrc_t rs0 = steps_at(w2), rs1 = steps_at(w2 + 4 * kChunkBytes);
+        static_for<16>([&](auto f_tag) __attribute__((always_inline)) { load_frag(f_tag, decltype(f_tag)::value < 8 ? rs0 : rs1); });
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) btab[tid + q * 512] = bv[q];
+        asm volatile("" ::: "memory");
+    }
+
+    for (int v = blockIdx.x; valid(v); v += gridDim.x) {
+        const int p0 = tile_of(v) * PX;
+        int taps[NP];                                  // bit t: tap t of the pixel lies in its image
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const int p = min(p0 + 32 * j + col, a2.M - 1);
+            const int r = p - fast_div(p, a2.div_howo) * (a2.H * a2.W);
+            const int y = fast_div(r, a2.div_wo), x = r - y * a2.W;
+            const int cols = (x > 0 ? 1 : 0) | 2 | (x + 1 < a2.W ? 4 : 0);
+            taps[j] = (y > 0 ? cols : 0) | cols << 3 | (y + 1 < a2.H ? cols << 6 : 0);
+        }
+        asm volatile("" ::: "memory");
+        ICNN_WAIT_VMCNT(16);                           // this wave's copies of the patch have landed: sixteen younger loads at least are the ring's
+        sync();                                        // ... everybody's; and nobody reads the last tile's y any more
+        if (has_res) issue_skip(p0);
+
+        // ---------------- phase 1: 3x3
+#pragma unroll
+        for (int j = 0; j < NP; ++j) init(acc[j], btab);
+        {
+            const int zero = g.rows * AP + half * 16;
+            int centre[NP], ad[NP], nad[NP];
+#pragma unroll
+            for (int j = 0; j < NP; ++j) centre[j] = (slot(j) + a2.W + 1) * AP + half * 16;
+            auto tap = [&](int (&d)[NP], int t, int off) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < NP; ++j) d[j] = (taps[j] >> t) & 1 ? centre[j] + off : zero;
+            };
+            int off = -(a2.W + 1) * AP, kw = 0;
+            tap(ad, 0, off);
+            first_frags(ad);
+            auto one = [&](auto half_tag, int t) __attribute__((always_inline)) {
+                const int tn = t < 8 ? t + 1 : 8;      // (after the last tap: itself, read and not used)
+                if (t < 8) {
+                    off += AP;
+                    if (++kw == 3) { kw = 0; off += (a2.W - 3) * AP; }
+                }
+                tap(nad, tn, off);
+                group(half_tag, ad, nad, t < 7 ? w2 + (t + 2) * (4 * kChunkBytes) : w3 + (t - 7) * (32 * kChunkBytes));
+#pragma unroll
+                for (int j = 0; j < NP; ++j) ad[j] = nad[j];
+            };
+#pragma unroll 1
+            for (int t = 0; t < 8; t += 2) {
+                one(H0{}, t);
+                one(H1{}, t + 1);
+            }
+            one(H0{}, 8);
+        }
+        asm volatile("" ::: "memory");
+        ICNN_WAIT_VMCNT(16);                           // the skip operand's copies (all older than the ring's loads) have landed
+        sync();                                        // ... everybody's, and every wave has its last fragments of the patch: b may overwrite it
+        mfma_drain(acc);
+        static_for<NP>([&](auto jc) __attribute__((always_inline)) {
+            constexpr int j = decltype(jc)::value;
+            const v4i w = finish(a2, H0{}, acc[j], v4i{0, 0, 0, 0}, a2.pc + (2 * wave + half) * kPcGroupInts);
+            if (32 * j + 31 < PX || 32 * j + col < PX) *(v4i *)(lds + (32 * j + col) * AP + co) = w;
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        sync();
+
+        // ---------------- phase 2: 1x1, 256 output channels at a time, one pixel group of a chunk after the other
+        {
+            int ad[NP];
+#pragma unroll
+            for (int j = 0; j < NP; ++j) ad[j] = slot(j) * AP + half * 16;
+            const int at0 = yb + co;                   // this lane's bytes of chunk ch at pixel q: + q * YP + ch * 256
+            // the next fragments of b: four half steps in flight, across the groups
+            v4i fr[4];
+            v16i c2[2];                                // the group being multiplied, the one being finished
+            v4i r8[2];
+            int w[4];
+#pragma unroll
+            for (int h = 0; h < 3; ++h) fr[h] = *(const v4i *)(lds + ad[0] + h * 32);
+            // group J of chunk ch (PAR: the parity of its number); the one before it (OJ, of chunk och) is finished meanwhile
+            auto item = [&](auto half_tag, auto j_tag, auto par_tag, auto first_tag, int ch) __attribute__((always_inline)) {
+                constexpr int R0 = 4 * decltype(half_tag)::value, j = decltype(j_tag)::value, PAR = decltype(par_tag)::value;
+                constexpr int oj = j == 0 ? NP - 1 : j - 1, nj = j + 1 < NP ? j + 1 : 0;
+                const bool old = !decltype(first_tag)::value || ch > 0;        // there is a group before it
+                init(c2[PAR], btab + MID + ch * MID);
+                const __amdgpu_buffer_rsrc_t rs = steps_at(ch + 2 < C / MID ? w3 + (ch + 2) * (32 * kChunkBytes) : w1 + (ch + 2 - C / MID) * (4 * kChunkBytes));
+                static_for<8>([&](auto h_tag) __attribute__((always_inline)) {
+                    constexpr int h = decltype(h_tag)::value, hn = h + 3;
+                    c2[PAR] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ring[R0 + (h >> 1)][h & 1], fr[h & 3], c2[PAR], 0, 0, 0);
+                    asm volatile("" : "+v"(c2[PAR]));
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (hn < 8) fr[hn & 3] = *(const v4i *)(lds + ad[j] + hn * 32);
+                    else fr[hn & 3] = *(const v4i *)(lds + ad[nj] + (hn - 8) * 32);
+                    if constexpr (j == NP - 1) load_frag(std::integral_constant<int, R0 * 2 + h>{}, rs);
+                    if constexpr (h == 4) r8[PAR] = *(const v4i *)(lds + at0 + slot(j) * YP + ch * MID);
+                    if constexpr (FORM == 1)
+                        if (old) epilogue_hi_slice<1, 2 * h, 2>(a3, g.sk, c2[PAR ^ 1], r8[PAR ^ 1], w);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if constexpr (FORM == 1) {
+                    if (old && (32 * oj + 31 < PX || 32 * oj + col < PX))
+                        *(v4i *)(lds + at0 + (32 * oj + col) * YP + (j == 0 ? ch - 1 : ch) * MID) = v4i{w[0], w[1], w[2], w[3]};
+                    mfma_drain(c2[PAR]);
+                } else {
+                    mfma_drain(c2[PAR]);
+                    const int32_t *pc = a3.pc + ((ch * 8 + wave) * 2 + half) * kPcGroupInts;
+                    const v4i o = has_res ? finish(a3, H1{}, c2[PAR], r8[PAR], pc) : finish(a3, H0{}, c2[PAR], r8[PAR], pc);
+                    if (32 * j + 31 < PX || 32 * j + col < PX) *(v4i *)(lds + at0 + (32 * j + col) * YP + ch * MID) = o;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto chunk = [&](auto half_tag, auto odd_tag, auto first_tag, int ch) __attribute__((always_inline)) {
+                constexpr int P0 = decltype(odd_tag)::value * NP;
+                // b goes to memory as well: four pixels per wave-wide store, dealt over waves and chunks
+                if (a2.out) {
+                    int l = lane;
+                    asm volatile("" : "+v"(l));
+                    const int q = (wave + 8 * ch) * 4 + (l >> 4), piece = (l & 15) * 16;
+                    if (ch < NP && q < PX && p0 + q < a2.M)
+                        *(v4i *)((uint8_t *)a2.out + (size_t)(p0 + q) * a2.out_cs + a2.out_co + piece) = *(const v4i *)(lds + q * AP + piece);
+                }
+                static_for<NP>([&](auto j_tag) __attribute__((always_inline)) {
+                    constexpr int j = decltype(j_tag)::value;
+                    item(half_tag, j_tag, std::integral_constant<int, (P0 + j) & 1>{}, std::integral_constant<bool, decltype(first_tag)::value && j == 0>{}, ch);
+                });
+            };
+#pragma unroll
+            for (int ch = 0; ch < C / MID; ch += 2) {  // (nine groups of the ring so far)
+                chunk(H1{}, H0{}, std::true_type{}, ch);
+                chunk(H0{}, H1{}, std::false_type{}, ch + 1);
+            }
+            if constexpr (FORM == 1) {
+                constexpr int PAR = (2 * NP - 1) & 1;
+                const v4i o = finish(a3, H1{}, c2[PAR], r8[PAR], nullptr);
+                if (32 * NP - 1 < PX || 32 * (NP - 1) + col < PX) *(v4i *)(lds + at0 + (32 * (NP - 1) + col) * YP + 3 * MID) = o;
+            }
+        }
+        sync();                                        // y is complete; nobody reads b any more
+
+        // y leaves LDS one pixel's whole row per store
+        auto store_y = [&](int q) __attribute__((always_inline)) {
+            if (q < PX && p0 + q < a2.M)
+                *(v4i *)((uint8_t *)a3.out + (size_t)(p0 + q) * a3.out_cs + a3.out_co + lane16) = *(const v4i *)(lds + yb + q * YP + lane16);
+        };
+        const int vn = v + (int)gridDim.x;
+        if constexpr (NEXT) {
+            if (valid(vn)) issue_patch(tile_of(vn) * PX);      // travels during this phase
+            // ---------------- phase 3: 1x1, K = 1024
+            int ad[NP], nad[NP];
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                ad[j] = yb + slot(j) * YP + half * 16;
+                init(acc[j], btab + MID + C);
+            }
+            first_frags(ad);
+            auto quarter = [&](auto half_tag, int k) __attribute__((always_inline)) {
+#pragma unroll
+                for (int j = 0; j < NP; ++j) nad[j] = k < 3 ? ad[j] + 256 : ad[j];
+                constexpr int PER = (PX + 31) / 32;
+                for (int c = k * PER; c < (k + 1) * PER; ++c) store_y(wave + 8 * c);
+                group(half_tag, ad, nad, (k < 2 ? w1 : w2 - 4 * (4 * kChunkBytes)) + (k + 2) * (4 * kChunkBytes));
+#pragma unroll
+                for (int j = 0; j < NP; ++j) ad[j] = nad[j];
+            };
+#pragma unroll 1
+            for (int k = 0; k < 4; k += 2) {
+                quarter(H1{}, k);
+                quarter(H0{}, k + 1);
+            }
+            mfma_drain(acc);
+            static_for<NP>([&](auto jc) __attribute__((always_inline)) {
+                constexpr int j = decltype(jc)::value;
+                const v4i w = finish(a1, H0{}, acc[j], v4i{0, 0, 0, 0}, a1.pc + (2 * wave + half) * kPcGroupInts);
+                const int q = 32 * j + col;
+                if (q < PX && p0 + q < a2.M) *(v4i *)((uint8_t *)a1.out + (size_t)(p0 + q) * a1.out_cs + a1.out_co + co) = w;
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        } else {
+#pragma unroll 2
+            for (int c = 0; c < (PX + 7) / 8; ++c) store_y(wave + 8 * c);
+            if (valid(vn)) {
+                issue_patch(tile_of(vn) * PX);         // (b is no longer read)
+                asm volatile("" ::: "memory");
+                ICNN_WAIT_VMCNT(0);
+            }
+        }
+        if (!valid(vn)) break;
+        // an odd number of groups: the next tile's first four steps are in the ring's other half
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                const v4i w = ring[r][f];
+                ring[r][f] = ring[r + 4][f];
+                ring[r + 4][f] = w;
+            }
+    }
+#endif
+}
+
+// ------------------------------------------------------------------ dispatch
+namespace {
+size_t tri_lds_bytes(const TriArgs &g) { return (size_t)g.patch_bytes + (size_t)tri_pixels(g.np) * (kTriWide + 16) + (2 * kTriMid + kTriWide) * 4; }
+
+bool tri_shape(long long M, int W, int np, TriArgs &g)
+{
+    const int px = tri_pixels(np);
+    g.np = np;
+    g.W = W;
+    g.rows = px + 2 * (W + 1);
+    g.patch_bytes = ((g.rows + 1) * 17 + 63) / 64 * 1024;
+    if (g.rows > 1024 || tri_lds_bytes(g) > 160 * 1024) return false;
+    const long long tiles = (M + px - 1) / px;
+    g.n_tiles = (int)tiles;
+    g.per_xcd = (int)((tiles + 7) / 8);
+    return true;
+}
+}  // namespace
+
+// Which tile.  One round of tiles on the 256 compute units takes 14, 19, 25 or 31 us by tile (28 for two rounds of the smallest), whatever their
+// number: the cheapest in rounds.  The 152-layer network, 32 / 64 / 96 / 112 pixels: 937 / 1057 / 1264 / 1454 us at 16 images, 1295 / 1375 / 1561 / 1748
+// at 40, 1671 / 1444 / 1627 / 1814 at 48, 1752 / 1603 / 1711 / 1896 at 64.  With several launches side by side, the smallest of the first three
+// tiles that gives all of them a compute unit each (two halves of 84 images: 1997 / 2050 / 1909 / 2077, of 96: 2189 / 2169 / 2115 / 2241), and
+// where none does the same rule as alone (of 128: 2817 / 2615 / 2780 / 2754).
+bool conv_tri_plan(long long M, int W, int lanes, TriArgs &g)
+{
+    if (M < 1 || M > 0x7fffffffLL - 256 || W > 1000) return false;
+    g.touch = lanes == 1;
+    if (g_tuning.tri_tile) return tri_shape(M, W, g_tuning.tri_tile, g);
+    static const int cost[5] = {0, 14, 19, 25, 31};
+    long long best = -1;
+    TriArgs t = g;
+    for (int np = 1; np <= 4; ++np) {
+        if (!tri_shape(M, W, np, t)) break;
+        if (lanes > 1 && np < 4 && (long long)t.n_tiles * lanes <= 256) {
+            g = t;
+            return true;
+        }
+        const long long c = ((long long)t.n_tiles + 255) / 256 * cost[np];
+        if (best < 0 || c < best) {
+            best = c;
+            g = t;
+        }
+    }
+    return best >= 0;
+}
+
+// a1: the next block's first layer, or null.  The caller has checked widths (256 -> 256 -> 1024 -> 256), kinds and alignment.
+hipError_t launch_conv_tri(const TriArgs &g, const ConvArgs &a2, const ConvArgs &a3, const ConvArgs *a1, hipStream_t st)
+{
+    if (a2.Cin != kTriMid || a2.Cout != kTriMid || a3.Cin != kTriMid || a3.Cout != kTriWide || (a1 && (a1->Cin != kTriWide || a1->Cout != kTriMid)) ||
+        g.n_tiles < 1 || g.np < 1 || g.np > 4 || g.W != a2.W || g.rows != tri_pixels(g.np) + 2 * (g.W + 1) ||
+        (long long)g.n_tiles * tri_pixels(g.np) < a2.M || tri_lds_bytes(g) > 160 * 1024)
+        return hipErrorInvalidValue;
+    // (17 workgroups per XCD touch all of the weights at once; more without a tile would only wait for compute units)
+    const int slots = std::min(256, std::max(8 * g.per_xcd, g.touch ? 136 : 0));
+    ConvArgs b2 = a2;
+    TriArgs q = g;
+    q.sk = a3.res_mode ? make_skip_mul(a3.res_mul, a3.res_shift) : SkipMul{0, 0, 0};      // (without an operand the arithmetic runs on zeros)
+    b2.div_howo = make_fast_div((unsigned)(a2.H * a2.W));
+    b2.div_wo = make_fast_div((unsigned)a2.W);
+    const int form = a3.pc ? 2 : a2.rq_fast && a3.rq_fast && (!a3.res_mode || q.sk.ok) && (!a1 || a1->rq_fast) ? 1 : 0;
+    auto go = [&](auto kernel) -> hipError_t {
+        const hipError_t e = allow_large_lds((const void *)kernel);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)slots), dim3(512), tri_lds_bytes(g), st, q, b2, a3, a1 ? *a1 : a2);
+        return hipGetLastError();
+    };
+    auto by_form = [&](auto np_tag, auto next_tag) {
+        constexpr int NP = decltype(np_tag)::value;
+        constexpr bool NEXT = decltype(next_tag)::value;
+        return form == 2 ? go(conv_tri_kernel<NP, NEXT, 2>) : form == 1 ? go(conv_tri_kernel<NP, NEXT, 1>) : go(conv_tri_kernel<NP, NEXT, 0>);
+    };
+    auto by_next = [&](auto np_tag) { return a1 ? by_form(np_tag, std::true_type{}) : by_form(np_tag, std::false_type{}); };
+    switch (g.np) {
+    case 1: return by_next(std::integral_constant<int, 1>{});
+    case 2: return by_next(std::integral_constant<int, 2>{});
+    case 3: return by_next(std::integral_constant<int, 3>{});
+    default: return by_next(std::integral_constant<int, 4>{});
+    }
+}
+
+}  // namespace icnn

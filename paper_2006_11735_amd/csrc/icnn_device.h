@@ -82,6 +82,25 @@ struct ConvArgs {
     int32_t *ws_part;
 };
 
+// An unsigned 8-bit skip operand's rescale as the high word of one product: [x * mul / 2^shift] = high 32 bits of (x << 24 | rnd) * k for every
+// byte x.  (x << 24 | rnd) * (m << (8 - s)) / 2^32 = x m / 2^s + rnd * m 2^(8-s) / 2^32, and the smallest rnd that makes the second term one
+// half exceeds it by less than the 2^-s between two values of the first (m <= 2^24): the floor is that of x m / 2^s + 1/2.
+// All zero: adds nothing (no skip operand).  ok = 0: the pair does not fit.
+struct SkipMul {
+    int ok;
+    uint32_t k, rnd;
+};
+static inline SkipMul make_skip_mul(long long mul, int shift)
+{
+    SkipMul r = {0, 0, 0};
+    while (shift > 8 && mul != 0 && (mul & 1) == 0) { mul /= 2; --shift; }
+    if (mul < 1 || mul > (1 << 24) || shift < 0 || shift > 8) return r;
+    const long long k = mul << (8 - shift), rnd = shift == 0 ? 0 : ((1LL << 31) + k - 1) / k;
+    if (k > 0xffffffffLL || rnd >= (1 << 24)) return r;
+    r.ok = 1; r.k = (uint32_t)k; r.rnd = (uint32_t)rnd;
+    return r;
+}
+
 // Workspace layout of a convolution call: counters first (zero-filled by the caller once, left zero by every call),
 // then data (the padded copy of a small-cin layer, or the partial accumulators of a split K axis).
 constexpr size_t kWsCounterBytes = 4096;
@@ -123,6 +142,19 @@ struct BlockArgs {
     unsigned inv_tw, inv_pw;      // q / TW = q * inv_tw >> 16 for q < 128; row / PW likewise for row < 160
     int k1;                       // K steps of the first layer: C / 64
     int nchunk3;                  // output channel chunks of the last layer: C / MID
+};
+
+// A 3x3 layer, the 1x1 layer that closes its block and the next block's first layer (see conv_tri.hip)
+constexpr int kTriMid = 256, kTriWide = 1024;
+constexpr int tri_pixels(int np) { return np == 4 ? 112 : 32 * np; }      // pixels of a tile by its groups of 32 (four whole groups do not fit LDS)
+struct TriArgs {
+    int np, W;                    // pixel groups; image width
+    int rows;                     // of the patch: the tile's pixels and W + 1 on either side
+    int patch_bytes;              // of it in LDS: rows + 1 (zeros) of 272 bytes, in whole KiB
+    int n_tiles, per_xcd;
+    int touch;                    // the workgroups touch the launch's weights first
+    unsigned res_bytes;
+    SkipMul sk;
 };
 
 // A run of 3x3 layers of 64 channels as one launch (see conv_chain.hip)
@@ -201,6 +233,7 @@ struct Tuning {
     int deep_always = 0;   // that kernel for every layer whose shape it accepts
     int block_any_form = 0; // LDS-ring block kernel: the instantiation that holds every epilogue form, also where one form would do
     int no_block64 = 0;    // fused bottleneck blocks with 64 middle channels: the LDS-ring kernel instead of the register-resident one
+    int tri_tile = 0;      // 3x3 + 1x1 + 1x1 kernel: 1..4 = tiles of 32, 64, 96 or 112 pixels
     int ksplit = 0;        // 0, 1 the K axis stays whole (the library's choice); 2..8 this split where it divides the K steps
 };
 extern Tuning g_tuning;
@@ -241,6 +274,8 @@ bool conv_block64_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &
 bool conv_block64_proj_takes(const ConvArgs &a1, const ConvArgs &a3, const ProjArgs &pj);
 hipError_t launch_conv_block64(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, const ProjArgs *pj,
                                hipStream_t st);
+bool conv_tri_plan(long long M, int W, int lanes, TriArgs &g);
+hipError_t launch_conv_tri(const TriArgs &g, const ConvArgs &a2, const ConvArgs &a3, const ConvArgs *a1, hipStream_t st);
 size_t conv_pair_lds_bytes(int c, int mid2, bool pc);
 hipError_t launch_conv_pair(const ConvArgs &a3, const ConvArgs &a1, long long pixels, hipStream_t st);
 bool conv_narrow_applies(const ConvArgs &a);

@@ -42,6 +42,7 @@ class GpuNet:
         self.fused_block_pc = {}            # the same with requantisation per output channel
         self.fused_pool = {}                # first conv name -> the max-pool op fused into its launch
         self.fused_pair = {}                # block-closing conv name -> the next block's opening conv op in its launch
+        self.fused_triple = {}              # block-closing conv name -> (3x3 conv op before it, next block's opening conv op or None) in its launch
         self.fused_twin = {}                # branch name -> the other branch's op in its launch
         self.fused_twin_last = {}           # last conv name -> the ops of the two branches before it in its launch
         self.fused_chain = {}               # last conv name -> the conv ops before it in its launch
@@ -49,6 +50,7 @@ class GpuNet:
         self._packed = {}                   # conv name -> its packed weights, bias and per-channel parameters, shared by the parts
         blocks = fuse if fuse_blocks is None else fuse_blocks
         full, parts, at = self.buf, self._parts(), 0
+        self.parts = len(parts)
         lists = []
         for images in parts:
             self.buf = {name: t[at:at + images] for name, t in full.items()}
@@ -56,7 +58,6 @@ class GpuNet:
             self._build(fuse, blocks)
             lists.append(self.steps)
         self.buf = full
-        self.parts = len(parts)
         self.steps = [st for part in lists for st in part]
         self.step_images = [images for images, part in zip(parts, lists) for _ in part]       # images that step i works on
         self.fused = list(dict.fromkeys(self.fused))
@@ -119,6 +120,7 @@ class GpuNet:
             self._fuse_blocks()
             self._fuse_projection_blocks()
             self._fuse_first_layer()
+            self._fuse_triples()
             self._fuse_pairs()
             self._fuse_twin_last()
             self._fuse_twins()
@@ -155,6 +157,50 @@ class GpuNet:
                         self.fused_pool[oc["name"]] = op_
                         steps.append(("convpool_pc" if pc else "convpool", oc, args))
                         i += 2
+                        continue
+            steps.append(self.steps[i])
+            i += 1
+        self.steps = steps
+
+    # By whether requantisation is per channel: below these the three layers by themselves, which spread their weights over the whole chip,
+    # are level or faster (50-layer network, fused / apart: one image 240 / 236 us, two 250 / 252, nine 310 / 334, 32 469 / 515; per channel four
+    # images 339 / 326, six 379 / 392, 32 623 / 640).
+    TRIPLE_MIN_PIXELS = {False: 256, True: 1024}
+
+    def _fuse_triples(self):
+        """A block's 3x3 convolution, the 1x1 convolution that closes the block and, where it follows, the 1x1 convolution that opens the
+        next one: one iconv2d_triple_brelu launch where the library accepts it.  All three outputs are written (the 3x3 layer's too: its
+        buffer has other readers, or somebody looks at it)."""
+        steps, i = [], 0
+        while i < len(self.steps):
+            run = self.steps[i:i + 3]
+            kinds = [st[0] for st in run]
+            if len(run) >= 2 and kinds[0] == kinds[1] and kinds[0] in ("conv", "conv_pc") and run[0][1]["kh"] == 3:
+                pc = kinds[0] == "conv_pc"
+                o2, o3 = run[0][1], run[1][1]
+                if np.prod(self.buf[o2["dst"]].shape[:3]) >= self.TRIPLE_MIN_PIXELS[kinds[0] == "conv_pc"] and o3["src"] == o2["dst"] and o3["kh"] == 1 and o2["dst_c_offset"] == 0 and o2["cout"] == o3["cin"]:
+                    d2, t, w2, b2, r2, t2 = self._conv_args(run[0])
+                    d3, _t2, w3, b3, res, y = self._conv_args(run[1])
+                    head = (d2, t, w2, b2) + ((run[0][2][4],) if pc else ()) + (t2, d3, w3, b3) + ((run[1][2][4],) if pc else ()) + (res, y)
+                    fn = B.iconv2d_triple_brelu_pc if pc else B.iconv2d_triple_brelu
+                    tails = [(None, (None,) * (5 if pc else 4) + (self.parts,))]
+                    if len(run) == 3 and kinds[2] == kinds[0]:
+                        o1 = run[2][1]
+                        if o1["src"] == o3["dst"] and o1["kh"] == 1 and o3["dst_c_offset"] == 0 and o1["cin"] == o3["cout"] and o1["cout"] == o3["cin"]:
+                            d1, _y, w1, b1, _r1, z = self._conv_args(run[2])
+                            tails.insert(0, (o1, (d1, w1, b1) + ((run[2][2][4],) if pc else ()) + (z, self.parts)))
+                    took = None
+                    for o1, tail in tails:
+                        if r2 is None and self._accepts(fn, head + tail):
+                            took = o1, head + tail
+                            break
+                    if took is not None:
+                        o1, args = took
+                        self.fused_triple[o3["name"]] = (o2, o1)
+                        if o1 is not None:
+                            self.fused_pair[o3["name"]] = o1
+                        steps.append(("triple_pc" if pc else "triple", o3, args))
+                        i += 2 if o1 is None else 3
                         continue
             steps.append(self.steps[i])
             i += 1
@@ -506,7 +552,8 @@ class GpuNet:
         self._FUNCTIONS[kind](*args, stream=stream)
 
     _FUNCTIONS = {"conv": B.iconv2d_brelu, "conv_pc": B.iconv2d_brelu_pc, "dual": B.iconv2d_dual_brelu, "dual_pc": B.iconv2d_dual_brelu_pc,
-                  "pair": B.iconv2d_pair_brelu, "pair_pc": B.iconv2d_pair_brelu_pc, "twin": B.iconv2d_twin_brelu, "twin_last": B.iconv2d_twin_last_brelu, "chain": B.iconv2d_chain_brelu,
+                  "pair": B.iconv2d_pair_brelu, "pair_pc": B.iconv2d_pair_brelu_pc, "triple": B.iconv2d_triple_brelu,
+                  "triple_pc": B.iconv2d_triple_brelu_pc, "twin": B.iconv2d_twin_brelu, "twin_last": B.iconv2d_twin_last_brelu, "chain": B.iconv2d_chain_brelu,
                   "projblock": B.iconv2d_bottleneck_dual_brelu, "projblock_pc": B.iconv2d_bottleneck_dual_brelu_pc,
                   "block": B.iconv2d_bottleneck_brelu, "block_pc": B.iconv2d_bottleneck_brelu_pc, "convpool": B.iconv2d_maxpool_brelu,
                   "convpool_pc": B.iconv2d_maxpool_brelu_pc, "maxpool": B.imaxpool2d_u8, "avgpool": B.iavgpool_global_u8}

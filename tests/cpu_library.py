@@ -40,7 +40,7 @@ class CpuLibrary:
 
     NAMES = ("iconv2d_brelu", "iconv2d_brelu_pc", "iconv2d_dual_brelu", "iconv2d_dual_brelu_pc", "iconv2d_bottleneck_brelu",
              "iconv2d_bottleneck_brelu_pc", "iconv2d_bottleneck_dual_brelu", "iconv2d_bottleneck_dual_brelu_pc", "iconv2d_pair_brelu",
-             "iconv2d_pair_brelu_pc", "iconv2d_twin_brelu", "iconv2d_twin_last_brelu", "iconv2d_maxpool_brelu", "iconv2d_maxpool_brelu_pc",
+             "iconv2d_pair_brelu_pc", "iconv2d_triple_brelu", "iconv2d_triple_brelu_pc", "iconv2d_twin_brelu", "iconv2d_twin_last_brelu", "iconv2d_maxpool_brelu", "iconv2d_maxpool_brelu_pc",
              "iconv2d_chain_brelu", "imaxpool2d_u8", "iavgpool_global_u8")
 
     # ---- what a GpuNet prepares
@@ -118,6 +118,21 @@ class CpuLibrary:
 
     def iconv2d_pair_brelu_pc(self, d3, t, w3, b3, p3, res, y, d1, w1, b1, p1, z):
         self.iconv2d_pair_brelu(d3, t, w3, b3, res, y, d1, w1, b1, z, (p3, p1))
+
+    def iconv2d_triple_brelu(self, d2, t, w2, b2, t2, d3, w3, b3, res, y, d1, w1, b1, z, lanes=1, pcs=(None, None, None)):
+        outs = ([] if t2 is None else [self.writes(d2, t2)]) + [self.writes(d3, y)] + ([] if d1 is None else [self.writes(d1, z)])
+        self.no_race(outs, [self.reads(d2, t)])
+        if res is not None:
+            self.no_race(outs, [_bytes_of(res, d3.res_c_stride, 0, d3.cout, 1)], in_place=True)
+        for k, o in enumerate(outs):
+            self.no_race([o], outs[:k])
+        mid = self.layer(d2, t.numpy(), w2, b2, out=None if t2 is None else t2.numpy(), pc=pcs[0])
+        wide = self.layer(d3, mid[..., d2.out_c_offset if t2 is not None else 0:][..., :d2.cout], w3, b3, None if res is None else res.numpy(), y.numpy(), pcs[1])
+        if d1 is not None:
+            self.layer(d1, wide[..., d3.out_c_offset:d3.out_c_offset + d3.cout], w1, b1, out=z.numpy(), pc=pcs[2])
+
+    def iconv2d_triple_brelu_pc(self, d2, t, w2, b2, p2, t2, d3, w3, b3, p3, res, y, d1, w1, b1, p1, z, lanes=1):
+        self.iconv2d_triple_brelu(d2, t, w2, b2, t2, d3, w3, b3, res, y, d1, w1, b1, z, lanes, (p2, p3, p1))
 
     def iconv2d_twin_brelu(self, da, x, wa, ba, ya, db, wb, bb, yb):
         self.no_race([self.writes(da, ya), self.writes(db, yb)], [self.reads(da, x)])

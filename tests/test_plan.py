@@ -160,6 +160,25 @@ def test_a_pair_that_returns_to_its_first_buffer():
     assert [st[0] for st in g.steps] == ["conv", "pair"]
 
 
+@pytest.mark.parametrize("next_dst, height, kinds", [("v", 16, ["conv", "conv", "triple"]), (None, 16, ["conv", "conv", "triple"]),
+                                                     ("t", 16, ["conv", "conv", "triple", "conv"]), ("u", 16, ["conv", "conv", "triple", "conv"]),
+                                                     ("v", 15, ["conv", "conv", "conv", "conv", "conv"])], ids=str)
+def test_a_block_boundary_of_256_channels(next_dst, height, kinds):
+    # the 3x3 layer's input has neighbours' readers, and its output is written too: the next block's first layer stays outside if it goes there
+    b = builder(1, height, 16, 64)
+    b.conv("c0", "raw", "x", 1024, 1)
+    b.conv("c1", "x", "t", 256, 1)
+    b.conv("c2", "t", "u", 256, 3)
+    b.conv("c3", "u", "y", 1024, 1, res="x", res_mode="pre")
+    if next_dst:
+        b.conv("d1", "y", next_dst, 256, 1)
+    b.net["outputs"] = ["y"] + ([next_dst] if next_dst else [])
+    g, want = cpu_library.planned(b.net, integers(b.net))
+    assert [st[0] for st in g.steps] == kinds
+    for name in ["y"] + ([next_dst] if next_dst else ["u"]):
+        assert (g.result(name) == want[name]).all(), name
+
+
 def merges(second_reader=False, output=False, overwrite=False, unread=False):
     """x -> projection -> sk and x -> t -> merge with sk.  second_reader: another merge reads sk; output: sk is a result; overwrite: x is
     written again before the merge; unread: no merge at all"""

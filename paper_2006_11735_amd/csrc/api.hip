@@ -180,7 +180,7 @@ int icnn_set_tuning(const char *name, int32_t value)
         {"no_narrow", &Tuning::no_narrow, 0, 1}, {"lat", &Tuning::lat, 0, 1}, {"no_lat", &Tuning::no_lat, 0, 1}, {"no_fc", &Tuning::no_fc, 0, 1},
         {"no_halo", &Tuning::no_halo, 0, 1},     {"halo_tile", &Tuning::halo_tile, 0, 2},
         {"halo_always", &Tuning::halo_always, 0, 1}, {"no_stream", &Tuning::no_stream, 0, 1},
-        {"ksplit", &Tuning::ksplit, 0, 8}, {"no_block64", &Tuning::no_block64, 0, 1},
+        {"ksplit", &Tuning::ksplit, 0, 8}, {"no_block64", &Tuning::no_block64, 0, 1}, {"no_block128", &Tuning::no_block128, 0, 1},
         {"no_plane", &Tuning::no_plane, 0, 1}, {"no_pic", &Tuning::no_pic, 0, 1}, {"block_any_form", &Tuning::block_any_form, 0, 1}, {"plane_no_pipe", &Tuning::plane_no_pipe, 0, 1}, {"plane_always", &Tuning::plane_always, 0, 1},
         {"no_deep", &Tuning::no_deep, 0, 1}, {"deep_always", &Tuning::deep_always, 0, 1}, {"deep_plain_walk", &Tuning::deep_plain_walk, 0, 1}, {"tri_tile", &Tuning::tri_tile, 0, 4},
     };
@@ -681,7 +681,7 @@ static int bottleneck(const icnn_conv_desc *c1, const void *x, const void *w1_pa
     BlockArgs b;
     b.x = (const uint8_t *)x; b.x_bytes = a1.x_bytes; b.x_cs = c1->in_c_stride;
     b.N = c1->n; b.H = c1->h; b.W = c1->w;
-    if (!conv_block_tile(b.H, b.W, b)) return fail(ICNN_E_UNSUPPORTED, "no tile shape for this image");
+    if (!conv_block_tile(b.H, b.W, kBlockPix, kBlockRows, b)) return fail(ICNN_E_UNSUPPORTED, "no tile shape for this image");
     const long long tiles = (long long)b.tiles_per_img * b.N;
     if (tiles > 0x7fffffffLL || g1.M > 0x7fffffffLL) return fail(ICNN_E_SHAPE, "too many tiles");
     b.n_tiles = (int)tiles;
@@ -691,6 +691,7 @@ static int bottleneck(const icnn_conv_desc *c1, const void *x, const void *w1_pa
     if ((pc3 || !g_tuning.no_block64) && conv_block64_takes(b, a1, a3) && conv_block64_lds_bytes(c, c, false, pc3 != nullptr) <= 160 * 1024)
         return launched(launch_conv_block64(b, a1, a2, a3, nullptr, (hipStream_t)stream), what);
     if (pc3) return fail(ICNN_E_UNSUPPORTED, "fused block with channel parameters needs a middle width of 64, outer widths of 64, 128 or 256, an 8-bit output and the block input as skip operand");
+    if (!g_tuning.no_block128 && conv_block128_takes(b, a1, a3)) return launched(launch_conv_block128(b, a1, a2, a3, (hipStream_t)stream), what);
     return launched(launch_conv_block(b, a1, a2, a3, (hipStream_t)stream), what);
 }
 
@@ -772,7 +773,7 @@ static int bottleneck_dual(const icnn_conv_desc *c1, const void *x, const void *
     BlockArgs b;
     b.x = (const uint8_t *)x; b.x_bytes = a1.x_bytes; b.x_cs = c1->in_c_stride;
     b.N = c1->n; b.H = c1->h; b.W = c1->w;
-    if (!conv_block_tile(b.H, b.W, b)) return fail(ICNN_E_UNSUPPORTED, "no tile shape for this image");
+    if (!conv_block_tile(b.H, b.W, kBlockPix, kBlockRows, b)) return fail(ICNN_E_UNSUPPORTED, "no tile shape for this image");
     const long long tiles = (long long)b.tiles_per_img * b.N;
     if (tiles > 0x7fffffffLL) return fail(ICNN_E_SHAPE, "too many tiles");
     b.n_tiles = (int)tiles;

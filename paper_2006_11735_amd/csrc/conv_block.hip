@@ -32,8 +32,8 @@
 
 namespace icnn {
 
-constexpr int kBlkRows = 160;        // patch rows: five pixel groups of 32
-constexpr int kBlkPix = 128;         // output pixel slots of a tile: four groups
+constexpr int kBlkRows = kBlockRows; // patch rows: five pixel groups of 32
+constexpr int kBlkPix = kBlockPix;   // output pixel slots of a tile: four groups
 constexpr int kBlkStages = 6;        // weight ring
 [[maybe_unused]] constexpr int kBlkDepth = kBlkStages - 1;      // stages issued ahead of the step being multiplied
 
@@ -547,14 +547,14 @@ size_t conv_block_lds_bytes(int mid, int c)
     return (size_t)kBlkStages * mg * 2048 + (size_t)k1 * kBlkRows * 64 + (size_t)s2 * kBlkRows * 64 + (size_t)(2 * mid + c) * 4;
 }
 
-// Output tile TH x TW with TH * TW <= 128 and (TH + 2) * (TW + 2) <= 160 that covers the image with the fewest tiles
-// (ties: the widest).  Also the two multiply-shift divisors the kernel uses, checked over their whole ranges.
-bool conv_block_tile(int H, int W, BlockArgs &g)
+// Output tile TH x TW with TH * TW <= pix and (TH + 2) * (TW + 2) <= rows that covers the image with the fewest tiles
+// (ties: the widest).  Also the two multiply-shift divisors the kernels use, checked over their whole ranges.
+bool conv_block_tile(int H, int W, int pix, int rows, BlockArgs &g)
 {
     long long best = -1;
-    for (int th = 1; th <= 126; ++th)
-        for (int tw = 1; tw <= 126; ++tw) {
-            if (th * tw > kBlkPix || (th + 2) * (tw + 2) > kBlkRows) continue;
+    for (int th = 1; th <= pix; ++th)
+        for (int tw = 1; tw <= pix; ++tw) {
+            if (th * tw > pix || (th + 2) * (tw + 2) > rows) continue;
             const long long tiles = (long long)((H + th - 1) / th) * ((W + tw - 1) / tw);
             if (best < 0 || tiles < best || (tiles == best && tw > g.TW)) {
                 best = tiles;
@@ -568,9 +568,9 @@ bool conv_block_tile(int H, int W, BlockArgs &g)
     g.tiles_per_img = g.tiles_x * ((H + g.TH - 1) / g.TH);
     g.inv_tw = 65536u / (unsigned)g.TW + 1;
     g.inv_pw = 65536u / (unsigned)g.PW + 1;
-    for (unsigned q = 0; q < (unsigned)kBlkPix; ++q)
+    for (unsigned q = 0; q < (unsigned)pix; ++q)
         if (((q * g.inv_tw) >> 16) != q / (unsigned)g.TW) return false;
-    for (unsigned r = 0; r < (unsigned)kBlkRows; ++r)
+    for (unsigned r = 0; r < (unsigned)rows; ++r)
         if (((r * g.inv_pw) >> 16) != r / (unsigned)g.PW) return false;
     return true;
 }

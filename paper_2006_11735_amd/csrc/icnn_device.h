@@ -232,6 +232,7 @@ struct Tuning {
     int deep_plain_walk = 0;   // that kernel with the tile order of the other kernels (measurement)
     int deep_always = 0;   // that kernel for every layer whose shape it accepts
     int block_any_form = 0; // LDS-ring block kernel: the instantiation that holds every epilogue form, also where one form would do
+    int no_block128 = 0;   // fused bottleneck blocks of 512 -> 128 -> 512 channels: the LDS-ring kernel instead of the one of small workgroups
     int no_block64 = 0;    // fused bottleneck blocks with 64 middle channels: the LDS-ring kernel instead of the register-resident one
     int tri_tile = 0;      // 3x3 + 1x1 + 1x1 kernel: 1..4 = tiles of 32, 64, 96 or 112 pixels
     int ksplit = 0;        // 0, 1 the K axis stays whole (the library's choice); 2..8 this split where it divides the K steps
@@ -266,9 +267,12 @@ int conv_chain_split(int N, int H, int W, int n, const bool *full, int *len);
 hipError_t launch_conv_chain(ChainArgs &g, hipStream_t st);
 hipError_t launch_conv_pic(const ConvArgs &a, hipStream_t st);
 hipError_t launch_conv_stem_pool(const ConvArgs &a, int hp, int wp, hipStream_t st);
-bool conv_block_tile(int H, int W, BlockArgs &g);
+constexpr int kBlockPix = 128, kBlockRows = 160;       // output pixels of a tile and rows of its patch, at most (conv_block.hip, conv_block64.hip)
+bool conv_block_tile(int H, int W, int pix, int rows, BlockArgs &g);
 size_t conv_block_lds_bytes(int mid, int c);
 hipError_t launch_conv_block(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st);
+bool conv_block128_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a3);
+hipError_t launch_conv_block128(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st);
 size_t conv_block64_lds_bytes(int c_in, int c_out, bool proj, bool pc);
 bool conv_block64_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a3);
 bool conv_block64_proj_takes(const ConvArgs &a1, const ConvArgs &a3, const ProjArgs &pj);

@@ -133,6 +133,7 @@ const char *icnn_last_error(void);
  *   "lat"         1 lets the kernel for few pixels (waves split K straight from global memory) take every layer whose shape it accepts
  *   "halo_tile"   0 library's choice; 1 = 128 x 128, 2 = 64 x 256 tiles of the patch-resident 3x3 kernel
  *   "halo_always" 1 lets the patch-resident kernel take layers with several tiles per workgroup
+ *   "no_block64s" 1 keeps fused bottleneck blocks of 256 -> 64 -> 256 channels on the kernel with resident weights
  *   "no_block128" 1 keeps fused bottleneck blocks of 512 -> 128 -> 512 channels on the kernel that streams weights through LDS
  *   "block_any_form" 1 keeps fused bottleneck blocks on the instantiation that holds every epilogue form
  *   "plane_no_pipe" 1 keeps that kernel off its instantiations with the software-pipelined epilogue

@@ -180,7 +180,7 @@ int icnn_set_tuning(const char *name, int32_t value)
         {"no_narrow", &Tuning::no_narrow, 0, 1}, {"lat", &Tuning::lat, 0, 1}, {"no_lat", &Tuning::no_lat, 0, 1}, {"no_fc", &Tuning::no_fc, 0, 1},
         {"no_halo", &Tuning::no_halo, 0, 1},     {"halo_tile", &Tuning::halo_tile, 0, 2},
         {"halo_always", &Tuning::halo_always, 0, 1}, {"no_stream", &Tuning::no_stream, 0, 1},
-        {"ksplit", &Tuning::ksplit, 0, 8}, {"no_block64", &Tuning::no_block64, 0, 1}, {"no_block128", &Tuning::no_block128, 0, 1},
+        {"ksplit", &Tuning::ksplit, 0, 8}, {"no_block64", &Tuning::no_block64, 0, 1}, {"no_block128", &Tuning::no_block128, 0, 1}, {"no_block64s", &Tuning::no_block64s, 0, 1},
         {"no_plane", &Tuning::no_plane, 0, 1}, {"no_pic", &Tuning::no_pic, 0, 1}, {"block_any_form", &Tuning::block_any_form, 0, 1}, {"plane_no_pipe", &Tuning::plane_no_pipe, 0, 1}, {"plane_always", &Tuning::plane_always, 0, 1},
         {"no_deep", &Tuning::no_deep, 0, 1}, {"deep_always", &Tuning::deep_always, 0, 1}, {"deep_plain_walk", &Tuning::deep_plain_walk, 0, 1}, {"tri_tile", &Tuning::tri_tile, 0, 4},
     };
@@ -688,6 +688,8 @@ static int bottleneck(const icnn_conv_desc *c1, const void *x, const void *w1_pa
     b.per_xcd = 0;              // set by the launcher
     b.k1 = c / 64;
     b.nchunk3 = c3->cout / mid;
+    if (!g_tuning.no_block64 && !g_tuning.no_block64s && conv_block64s_takes(b, a1, a2, a3))
+        return launched(launch_conv_block64s(b, a1, a2, a3, (hipStream_t)stream), what);
     if ((pc3 || !g_tuning.no_block64) && conv_block64_takes(b, a1, a3) && conv_block64_lds_bytes(c, c, false, pc3 != nullptr) <= 160 * 1024)
         return launched(launch_conv_block64(b, a1, a2, a3, nullptr, (hipStream_t)stream), what);
     if (pc3) return fail(ICNN_E_UNSUPPORTED, "fused block with channel parameters needs a middle width of 64, outer widths of 64, 128 or 256, an 8-bit output and the block input as skip operand");

@@ -1,0 +1,307 @@
+// The identity bottleneck block of a network's first stage (1x1 conv from 256 to 64 channels, 3x3 conv, 1x1 conv back to 256
+// with the block input as skip operand, Section 4.1) as one kernel of small workgroups: four waves take tiles of at most 64
+// pixels through the three layers, and two workgroups share a compute unit, so that one's loads and barriers run beside the
+// other's arithmetic.
+//
+//   tile     TH x TW output pixels (at most 64), patch (TH+2) x (TW+2) input pixels (at most 96); two patch buffers, the next
+//            tile's patch is copied global -> LDS while this tile runs
+//   phase 1  a = BReLU/requant(W1 x + b1) on the patch: six (chunk, pixel group) items over four waves; patch pixels
+//            outside the image become zeros (the 3x3 layer's padding)
+//   phase 2  b = BReLU/requant(W2 (*) a + b2) on the tile, one item per wave; b replaces a
+//   phase 3  y = epilogue(W3 b + b3, skip): two of the eight chunks of 32 channels per wave; the skip operand is the block input,
+//            in LDS already, and every lane replaces the sixteen bytes it has merged by its result; y leaves in whole rows
+//
+// A wave's share of the three layers' weights is 30 fragments = 120 registers, loaded once for the workgroup's whole life.
+//
+// What bounds it: vector work.  The last layer's epilogue is 368 instructions per wave and tile, the other two 132, and what
+// is left for positions has been taken out of the tile: where a patch's rows lie in memory is worked out by one thread per
+// row into a table in LDS, where a copy's and a store's pieces lie in a tile once per workgroup.  64 x 56 x 56 pixels: 46 us with
+// eight waves on tiles of 128 pixels (conv_block64.hip), 46 with three workgroups per compute unit that fetch their weights per
+// tile (9 of a tile's 19 k clocks), 41 now.
+#include "conv_common.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace icnn {
+
+constexpr int kB64sMid = 64, kB64sWide = 256;
+constexpr int kB64sRows = 96, kB64sPix = 64;           // patch rows, output pixel slots
+constexpr int kB64sXP = kB64sWide + 16, kB64sAP = kB64sMid + 16;      // row pitches: padded as in conv_tri.hip
+constexpr int kB64sXBytes = (kB64sRows * (kB64sXP / 16) + 63) / 64 * 1024;
+
+// The three layers requantise as a product's high word (rq_fast) and the skip operand is rescaled likewise (sk)
+__global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const BlockArgs g, const SkipMul sk, const ConvArgs a1, const ConvArgs a2,
+                                                               const ConvArgs a3)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr unsigned OOB = 0x80000000u;
+    constexpr int MID = kB64sMid, C = kB64sWide, XP = kB64sXP, AP = kB64sAP;
+
+    // LDS: two patches of x (in the end y on the tile's rows) | a on the patch, then b on the tile | biases [64] [64] [256] | two tables of patch rows
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    uint8_t *const abuf = lds + 2 * kB64sXBytes;
+    int32_t *const btab = (int32_t *)(abuf + kB64sRows * AP);
+    unsigned *const rtab = (unsigned *)(btab + 2 * MID + C);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
+
+    auto sync = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+
+    // XCD-contiguous walk, as in the other fused kernels
+    auto tile_of = [&](int v) { return (v & 7) * g.per_xcd + (v >> 3); };
+    auto valid = [&](int v) { return (v >> 3) < g.per_xcd && tile_of(v) < g.n_tiles; };
+    auto tile_origin = [&](int v, int &n, int &y0, int &x0) {
+        const int t = tile_of(v);
+        n = t / g.tiles_per_img;
+        const int r = t - n * g.tiles_per_img;
+        const int ty = r / g.tiles_x;
+        y0 = ty * g.TH;
+        x0 = (r - ty * g.tiles_x) * g.TW;
+    };
+    if (!valid(blockIdx.x)) return;
+
+    // ---- the patch of a tile.  Table: the offset of every row in memory, one thread per row (one more stands for the padding behind the last).
+    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)g.x, 0, g.x_bytes, 0x00020000);
+    auto write_rows = [&](int v, int b) __attribute__((always_inline)) {
+        if (tid <= kB64sRows) {
+            int n, y0, x0;
+            tile_origin(v, n, y0, x0);
+            const int py = (int)(((unsigned)tid * g.inv_pw) >> 16), px = tid - py * g.PW;
+            const int iy = y0 - 1 + py, ix = x0 - 1 + px;
+            const bool ok = py < g.TH + 2 && (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
+            rtab[b * 128 + tid] = ok ? (unsigned)(((n * g.H + iy) * g.W + ix) * g.x_cs) : OOB;
+        }
+    };
+    // Copies of 1 KiB: 16-byte piece i of the region is piece i % 17 of row i / 17; the last one is padding, which takes any bytes (an offset
+    // of 1 GiB beside the row: inside the tensor or read as zeros).
+    constexpr int COPIES = kB64sXBytes / 1024, CPW = (COPIES + 3) / 4;
+    int c_row[CPW], c_off[CPW];                        // of this lane's piece of copy wave + 4 q: table entry, offset in the row
+#pragma unroll
+    for (int q = 0; q < CPW; ++q) {
+        const int i = (wave + 4 * q) * 64 + lane;
+        const int row = (int)(((unsigned)i * 61681u) >> 20), piece = i - row * 17;             // / 17, exact below 2^16
+        c_row[q] = min(row, kB64sRows);
+        c_off[q] = piece < 16 ? piece * 16 : 0x40000000;
+    }
+    auto issue_patch = [&](int b) __attribute__((always_inline)) {
+        unsigned off[CPW];
+#pragma unroll
+        for (int q = 0; q < CPW; ++q) off[q] = rtab[b * 128 + c_row[q]] + (unsigned)c_off[q];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int q = 0; q < CPW; ++q)
+            if (wave + 4 * q < COPIES)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + b * kB64sXBytes + (wave + 4 * q) * 1024), 16,
+                                                         off[q], 0, 0, 0);
+    };
+
+    // ---- biases and this wave's weights, for the workgroup's whole life
+    const int c12 = wave & 1, pg = (wave >> 1) ^ (int)((blockIdx.x >> 8) & 1);          // chunk of layers 1 and 2; pixel group in phase 2 and first one in
+                                                       // phase 1, where group 0's waves take a second one (the other waves of the second workgroup on a compute unit)
+    v4i w1[8], w2[18], w3[2][2];
+    int bv[2];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int i = tid + q * 256;
+        bv[q] = i < MID ? a1.bias[i] : (i < 2 * MID ? a2.bias[i - MID] : i < 2 * MID + C ? a3.bias[i - 2 * MID] : 0);
+    }
+    write_rows(blockIdx.x, 0);
+    if (valid(blockIdx.x + (int)gridDim.x)) write_rows(blockIdx.x + (int)gridDim.x, 1);
+    sync();
+    issue_patch(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        const int l16 = lane * 16;
+        const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void *)(a1.wp + (size_t)c12 * 4 * kChunkBytes), 0, 4 * kChunkBytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void *)(a2.wp + (size_t)c12 * 9 * kChunkBytes), 0, 9 * kChunkBytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t r3 = __builtin_amdgcn_make_buffer_rsrc((void *)(a3.wp + (size_t)wave * 2 * kChunkBytes), 0, 2 * kChunkBytes, 0x00020000);
+#pragma unroll
+        for (int f = 0; f < 8; ++f) w1[f] = __builtin_amdgcn_raw_buffer_load_b128(r1, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
+#pragma unroll
+        for (int f = 0; f < 18; ++f) w2[f] = __builtin_amdgcn_raw_buffer_load_b128(r2, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) w3[f >> 1][f & 1] = __builtin_amdgcn_raw_buffer_load_b128(r3, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+        if (tid + q * 256 < 2 * MID + C) btab[tid + q * 256] = bv[q];
+
+    // patch row of this lane's pixels q = 32 j + col (slots beyond the tile: of pixel 0)
+    int prow[2];
+    bool in[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int q = 32 * j + col;
+        in[j] = q < g.TH * g.TW;
+        const int ty = in[j] ? (int)(((unsigned)q * g.inv_tw) >> 16) : 0;
+        prow[j] = (ty + 1) * g.PW + (in[j] ? q - ty * g.TW : 0) + 1;
+    }
+    // where this lane's pieces of y lie: four pixels' whole rows per store
+    int s_lds[4], s_out[4];
+    short s_y[4], s_x[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int q = (wave + 4 * c) * 4 + (lane >> 4);
+        const int ty = (int)(((unsigned)q * g.inv_tw) >> 16), tx = q - ty * g.TW;
+        s_lds[c] = ((ty + 1) * g.PW + tx + 1) * XP + (lane & 15) * 16;
+        s_y[c] = (short)(q < g.TH * g.TW ? ty : 0x4000);
+        s_x[c] = (short)tx;
+        s_out[c] = (ty * g.W + tx) * a3.out_cs + (lane & 15) * 16;
+    }
+
+    int buf = 0;
+    for (int v = blockIdx.x; valid(v); v += gridDim.x, buf ^= 1) {
+    int n, y0, x0;
+    tile_origin(v, n, y0, x0);
+    uint8_t *const xb = lds + buf * kB64sXBytes;
+    asm volatile("" ::: "memory");
+    if (v == (int)blockIdx.x) ICNN_WAIT_VMCNT(30);     // this wave's copies of the patch have landed: thirty younger loads are the weights',
+    else ICNN_WAIT_VMCNT(4);                           // ... or the last tile's four stores
+    sync();                                            // ... everybody's; and nobody reads the last tile's y or b any more
+    {
+        const int v1 = v + (int)gridDim.x, v2 = v1 + (int)gridDim.x;
+        if (valid(v1)) issue_patch(buf ^ 1);
+        if (valid(v2)) write_rows(v2, buf);            // (this tile's table has been used up)
+    }
+
+    // ---------------- phase 1: a = requant(W1 x + b1) on patch rows 32 pg .. + 32, and on the last 32 for the waves of group 0
+#pragma unroll
+    for (int rep = 0; rep < 2; ++rep) {
+        if (rep && pg) break;
+        const int row = 32 * (rep ? 2 : pg) + col;
+        const uint8_t *const xr = xb + row * XP + half * 16;
+        v4i bf[4];
+#pragma unroll
+        for (int h = 0; h < 4; ++h) bf[h] = *(const v4i *)(xr + h * 32);
+        v16i acc = bias16(btab + c12 * 32 + half * 16);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<8>([&](auto h_tag) __attribute__((always_inline)) {
+            constexpr int h = decltype(h_tag)::value;
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w1[h], bf[h & 3], acc, 0, 0, 0);
+            asm volatile("" : "+v"(acc));
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (h < 4) bf[h] = *(const v4i *)(xr + (h + 4) * 32);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        mfma_drain(acc);
+        const int py = (int)(((unsigned)row * g.inv_pw) >> 16), px = row - py * g.PW;
+        const int iy = y0 - 1 + py, ix = x0 - 1 + px;
+        v4i w = epilogue_hi16<0>(a1, sk, acc, v4i{0, 0, 0, 0});
+        if (!((unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W)) w = v4i{0, 0, 0, 0};
+        *(v4i *)(abuf + row * AP + c12 * 32 + half * 16) = w;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    sync();
+
+    // ---------------- phase 2: b = requant(W2 (*) a + b2) on output slots 32 pg .. + 32
+    {
+        const uint8_t *const ar = abuf + (pg ? prow[1] : prow[0]) * AP + half * 16;
+        v4i bf[6];
+        auto frag = [&](auto f_tag) __attribute__((always_inline)) {
+            constexpr int f = decltype(f_tag)::value, t = f >> 1;
+            bf[f % 6] = *(const v4i *)(ar + ((t / 3 - 1) * g.PW + t % 3 - 1) * AP + (f & 1) * 32);
+        };
+        static_for<6>(frag);
+        v16i acc = bias16(btab + MID + c12 * 32 + half * 16);
+        __builtin_amdgcn_sched_barrier(0);
+        static_for<18>([&](auto f_tag) __attribute__((always_inline)) {
+            constexpr int f = decltype(f_tag)::value;
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w2[f], bf[f % 6], acc, 0, 0, 0);
+            asm volatile("" : "+v"(acc));
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (f + 6 < 18) frag(std::integral_constant<int, f + 6>{});
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        sync();                                        // every wave has its last fragments of a: b may overwrite it
+        mfma_drain(acc);
+        *(v4i *)(abuf + (32 * pg + col) * AP + c12 * 32 + half * 16) = epilogue_hi16<0>(a2, sk, acc, v4i{0, 0, 0, 0});   // slots beyond the tile hold values nobody stores
+    }
+    sync();
+
+    // ---------------- phase 3: y = epilogue(W3 b + b3, skip) on chunks 2 wave and 2 wave + 1
+    {
+        v4i bf[2][2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) bf[j][h] = *(const v4i *)(abuf + (32 * j + col) * AP + half * 16 + h * 32);
+        v16i acc[2];
+        v4i r8[2];
+        // item i: chunk i >> 1, pixel group i & 1; its products are issued before the epilogue of the item before it
+        auto multiply = [&](auto i_tag) __attribute__((always_inline)) {
+            constexpr int c = decltype(i_tag)::value >> 1, j = decltype(i_tag)::value & 1;
+            acc[j] = bias16(btab + 2 * MID + (2 * wave + c) * 32 + half * 16);
+            r8[j] = *(const v4i *)(xb + prow[j] * XP + (2 * wave + c) * 32 + half * 16);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w3[c][h], bf[j][h], acc[j], 0, 0, 0);
+            asm volatile("" : "+v"(acc[j]));
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        multiply(std::integral_constant<int, 0>{});
+        static_for<4>([&](auto i_tag) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_tag)::value, c = i >> 1, j = i & 1;
+            if constexpr (i < 3) multiply(std::integral_constant<int, i + 1>{});
+            mfma_drain(acc[j]);
+            const v4i o = epilogue_hi16<1>(a3, sk, acc[j], r8[j]);
+            if (in[j]) *(v4i *)(xb + prow[j] * XP + (2 * wave + c) * 32 + half * 16) = o;
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    }
+    sync();                                            // y is complete
+
+    // y leaves LDS
+    {
+        // (through a descriptor of the tile's own: pieces outside the image are dropped there, so the stores are always four)
+        const __amdgpu_buffer_rsrc_t rs_y = __builtin_amdgcn_make_buffer_rsrc(
+            (uint8_t *)a3.out + (size_t)(unsigned)((n * g.H + y0) * g.W + x0) * a3.out_cs + a3.out_co, 0, 0x7fffff00, 0x00020000);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const v4i o = *(const v4i *)(xb + s_lds[c]);
+            const bool ok = y0 + s_y[c] < g.H && x0 + s_x[c] < g.W;
+            __builtin_amdgcn_raw_buffer_store_b128(o, rs_y, ok ? (unsigned)s_out[c] : OOB, 0, 0);
+        }
+    }
+    }
+#endif
+}
+
+// ------------------------------------------------------------------ dispatch
+// 256 -> 64 -> 64 -> 256 channels, per-layer requantisation, an 8-bit output, the block input itself as skip operand (unsigned 8-bit, joined
+// before requantisation) or none
+bool conv_block64s_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3)
+{
+    if (a1.Cin != kB64sWide || a1.Cout != kB64sMid || a3.Cout != kB64sWide || a3.pc) return false;
+    if (a3.out_mode == 3 || !a3.epi_vec || a3.epi_mode / 4 == 2 || !a1.rq_fast || !a2.rq_fast || !a3.rq_fast) return false;
+    if (a3.res_mode == 0) return true;
+    return (const uint8_t *)a3.res == g.x && a3.res_cs == g.x_cs && make_skip_mul(a3.res_mul, a3.res_shift).ok;
+}
+
+hipError_t launch_conv_block64s(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st)
+{
+    if (!conv_block64s_takes(g, a1, a2, a3)) return hipErrorInvalidValue;
+    BlockArgs gx = g;
+    if (!conv_block_tile(g.H, g.W, kB64sPix, kB64sRows, gx)) return hipErrorInvalidValue;
+    const long long tiles = (long long)gx.tiles_per_img * g.N;
+    if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
+    gx.n_tiles = (int)tiles;
+    gx.per_xcd = (int)((tiles + 7) / 8);
+    const size_t lds_bytes = 2 * kB64sXBytes + kB64sRows * kB64sAP + (2 * kB64sMid + kB64sWide) * 4 + 2 * 128 * 4;
+    static_assert(2 * kB64sXBytes + kB64sRows * kB64sAP + (2 * kB64sMid + kB64sWide) * 4 + 2 * 128 * 4 <= 64 * 1024, "no permission needed");
+    const SkipMul sk = a3.res_mode ? make_skip_mul(a3.res_mul, a3.res_shift) : SkipMul{0, 0, 0};     // (without an operand: adds zero)
+    hipLaunchKernelGGL(conv_block64s_kernel, dim3((unsigned)std::min(8 * gx.per_xcd, 512)), dim3(256), lds_bytes, st, gx, sk, a1, a2, a3);
+    return hipGetLastError();
+}
+
+}  // namespace icnn

@@ -233,6 +233,7 @@ struct Tuning {
     int deep_always = 0;   // that kernel for every layer whose shape it accepts
     int block_any_form = 0; // LDS-ring block kernel: the instantiation that holds every epilogue form, also where one form would do
     int no_block128 = 0;   // fused bottleneck blocks of 512 -> 128 -> 512 channels: the LDS-ring kernel instead of the one of small workgroups
+    int no_block64s = 0;   // fused bottleneck blocks of 256 -> 64 -> 256 channels: the kernel with resident weights instead of the one of small workgroups
     int no_block64 = 0;    // fused bottleneck blocks with 64 middle channels: the LDS-ring kernel instead of the register-resident one
     int tri_tile = 0;      // 3x3 + 1x1 + 1x1 kernel: 1..4 = tiles of 32, 64, 96 or 112 pixels
     int ksplit = 0;        // 0, 1 the K axis stays whole (the library's choice); 2..8 this split where it divides the K steps
@@ -273,6 +274,8 @@ size_t conv_block_lds_bytes(int mid, int c);
 hipError_t launch_conv_block(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st);
 bool conv_block128_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a3);
 hipError_t launch_conv_block128(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st);
+bool conv_block64s_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3);
+hipError_t launch_conv_block64s(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st);
 size_t conv_block64_lds_bytes(int c_in, int c_out, bool proj, bool pc);
 bool conv_block64_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a3);
 bool conv_block64_proj_takes(const ConvArgs &a1, const ConvArgs &a3, const ProjArgs &pj);

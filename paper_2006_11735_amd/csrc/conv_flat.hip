@@ -1,0 +1,268 @@
+// A 3x3 or 1x1 layer of stride 1 whose weights go from memory straight into the registers of the one wave of a workgroup that
+// multiplies them, and whose input crosses the compute unit's memory path once per 128 output channels.
+//
+//   tile     PX consecutive pixels of the flattened N*H*W axis; patch (3x3): these and the W + 1 pixels before and behind
+//            them, so that tap (kh, kw) of a pixel is the patch row (kh - 1) * W + kw - 1 away; a tap beyond the image's edge
+//            reads a row of zeros instead, chosen by a mask of nine bits per pixel.  The whole patch, all channels, lies in
+//            LDS before the K loop begins, rows padded by 16 bytes (any 16 consecutive rows start in different banks)
+//   waves    four: WC along the output channels, 32 each; 4 / WC along the pixels, 64 each
+//   K loop   groups of G steps of 64; every group of weights is fetched eight K steps ahead; no barrier
+//
+// Two or three workgroups share a compute unit: one's copies and epilogue run beside another's matrix instructions.  What bounds it is the
+// compute unit's memory path (64 to 72 bytes a clock): a 3x3 of 256 channels takes 295 KB of weights and 30 KB of patch per 64 pixels x 128
+// channels, 4608 clocks of matrix instructions on its four units.
+#include "conv_common.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace icnn {
+
+struct FlatArgs {
+    int rows, patch_bytes;        // patch rows; bytes of it in LDS with the row of zeros behind, in whole KiB
+    unsigned inv_pieces;          // i / (pieces of a row) = i * inv_pieces >> 22
+    SkipMul sk;
+};
+
+// KK: kernel size; NG groups of G steps: cin = 64 G NG / KK^2.  FORM: 1 requantisation as a product's high word (rq_fast), an unsigned 8-bit skip
+// operand before it rescaled likewise (g.sk) or none, 8-bit output; 0 any form of one pair per layer; 2 per output channel.
+template <int KK, int NG, int G, int WC, int FORM>
+__global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, const FlatArgs g)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr unsigned OOB = 0x80000000u;
+    constexpr int CIN = 64 * G * NG / (KK * KK), GP = NG / (KK * KK);      // groups per tap
+    constexpr int AP = CIN + 16, PIECES = AP / 16, PX = 64 * (4 / WC), NS = 8 / G;
+    constexpr int T = NG * G;                          // K steps
+
+    // LDS: patch | biases of the tile's channels
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    int32_t *const btab = (int32_t *)(lds + g.patch_bytes);
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
+
+    int ct, pt;
+    if (!tile_of_block(a, ct, pt)) return;
+    const int p0 = pt * PX;
+    const int wc = wave % WC, pw = p0 + (wave / WC) * 64;                  // this wave's channels in the tile, first pixel
+    const int co_tile = ct * (WC * 32), co_wave = co_tile + wc * 32;
+
+    // ---- weights: group k of this wave's chunk in slot k % NS of the ring
+    const uint8_t *const wp = a.wp + (size_t)(co_wave >> 5) * (T * kChunkBytes);
+    v4i ring[NS][2 * G];
+    const int lane16 = lane * 16;
+    auto load_frag = [&](auto k_tag, auto f_tag) __attribute__((always_inline)) {
+        constexpr int k = decltype(k_tag)::value, f = decltype(f_tag)::value;
+        if constexpr (k < NG) {
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)(wp + k * (G * kChunkBytes)), 0, G * kChunkBytes, 0x00020000);
+            ring[k % NS][f] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
+        }
+    };
+
+    // ---- prologue: biases, patch and the ring's first groups in flight together
+    const int bv = a.bias[co_tile + min(tid, WC * 32 - 1)];
+    asm volatile("" ::: "memory");
+    {
+        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.x_bytes, 0x00020000);
+        const int first = KK == 3 ? p0 - a.W - 1 : p0;
+        // 16-byte piece i of the patch region is piece i % PIECES of row i / PIECES, the last of a row padding; pixels outside the tensor, the
+        // padding and the rows behind the last one (the first of them is the row of zeros) get zeros
+        int i = tid;
+        int row = (int)(((unsigned)i * g.inv_pieces) >> 22), piece = i - row * PIECES;
+        for (int c = wave; c < g.patch_bytes / 1024; c += 4) {
+            const int p = first + row;
+            const unsigned off = piece < PIECES - 1 && row < g.rows && (unsigned)p < (unsigned)a.M ? (unsigned)p * (unsigned)a.in_cs + piece * 16 : OOB;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + c * 1024), 16, off, 0, 0, 0);
+            row += 256 / PIECES;
+            piece += 256 % PIECES;
+            if (piece >= PIECES) { piece -= PIECES; ++row; }
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        constexpr int FIRST = NS < NG ? NS : NG;
+        static_for<FIRST * 2 * G>([&](auto i_tag) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_tag)::value;
+            load_frag(std::integral_constant<int, i / (2 * G)>{}, std::integral_constant<int, i % (2 * G)>{});
+        });
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if (tid < WC * 32) btab[tid] = bv;
+    }
+    // this lane's pixels
+    int taps[2], q[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        q[j] = (wave / WC) * 64 + 32 * j + col;
+        if constexpr (KK == 3) {
+            const int p = min(p0 + q[j], a.M - 1);
+            const int r = p - fast_div(p, a.div_howo) * (a.H * a.W);
+            const int y = fast_div(r, a.div_wo), x = r - y * a.W;
+            const int cols = (x > 0 ? 1 : 0) | 2 | (x + 1 < a.W ? 4 : 0);
+            taps[j] = (y > 0 ? cols : 0) | cols << 3 | (y + 1 < a.H ? cols << 6 : 0);
+        }
+    }
+    v4i res8[1][2];
+    if constexpr (FORM == 1) {
+        if (a.res_mode != 0) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                res8[0][j] = p0 + q[j] < a.M ? *(const v4i *)((const uint8_t *)a.res + ((size_t)(p0 + q[j]) * a.res_cs + co_wave + half * 16)) : v4i{0, 0, 0, 0};
+        }
+    } else {
+        prefetch_res8<1, 2>(a, co_wave, pw, lane, res8);
+    }
+    asm volatile("" ::: "memory");
+    ICNN_WAIT_VMCNT(2 * G * (NS < NG ? NS : NG));      // this wave's copies of the patch have landed: as many younger loads at least are the ring's
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();                      // ... everybody's
+    asm volatile("" ::: "memory");
+
+    // ---- K loop
+    v16i acc[1][2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[0][j] = bias16(btab + wc * 32 + half * 16);
+    {
+        constexpr int NB = 2 * G < 4 ? 2 * G : 4, AHEAD = NB - 1, H = 2 * G;       // fragments in flight; half steps (32 channels) of a group
+        v4i bf[NB][2];
+        const int zero = g.rows * AP + half * 16;
+        int ad[2], nad[2];
+        auto tap = [&](auto t_tag, int (&d)[2]) __attribute__((always_inline)) {
+            constexpr int t = decltype(t_tag)::value;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int at = (q[j] + (KK == 3 ? (t / 3) * a.W + t % 3 : 0)) * AP + half * 16;
+                d[j] = KK == 1 || (taps[j] >> t) & 1 ? at : zero;
+            }
+        };
+        tap(std::integral_constant<int, 0>{}, ad);
+#pragma unroll
+        for (int h = 0; h < AHEAD; ++h)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) bf[h][j] = *(const v4i *)(lds + ad[j] + h * 32);
+        static_for<NG>([&](auto k_tag) __attribute__((always_inline)) {
+            constexpr int k = decltype(k_tag)::value, part = KK == 3 ? k % GP : k, next = KK == 3 ? (k + 1) % GP : k + 1;
+            constexpr int AT = part * (G * 64), NAT = k + 1 < NG ? next * (G * 64) : AT;
+            if constexpr (KK == 3 && next == 0 && k + 1 < NG) tap(std::integral_constant<int, (k + 1) / GP>{}, nad);
+            else {
+                nad[0] = ad[0];
+                nad[1] = ad[1];
+            }
+            static_for<H>([&](auto h_tag) __attribute__((always_inline)) {
+                constexpr int h = decltype(h_tag)::value, hn = h + AHEAD;
+                static_for<2>([&](auto j_tag) __attribute__((always_inline)) {
+                    constexpr int j = decltype(j_tag)::value;
+                    acc[0][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ring[k % NS][h], bf[h % NB][j], acc[0][j], 0, 0, 0);
+                    asm volatile("" : "+v"(acc[0][j]));        // here, not wherever the sums are needed
+                    __builtin_amdgcn_sched_barrier(0);
+                    bf[hn % NB][j] = *(const v4i *)(lds + (hn < H ? ad[j] + AT + hn * 32 : nad[j] + NAT + (hn - H) * 32));
+                    if constexpr (j == 1) load_frag(std::integral_constant<int, k + NS>{}, h_tag);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            });
+            ad[0] = nad[0];
+            ad[1] = nad[1];
+        });
+    }
+    mfma_drain(acc);
+    if constexpr (FORM == 1) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const v4i w = a.res_mode != 0 ? epilogue_hi16<1>(a, g.sk, acc[0][j], res8[0][j]) : epilogue_hi16<0>(a, g.sk, acc[0][j], v4i{0, 0, 0, 0});
+            if (p0 + q[j] < a.M) *(v4i *)((uint8_t *)a.out + (size_t)(p0 + q[j]) * a.out_cs + a.out_co + co_wave + half * 16) = w;
+        }
+    } else if constexpr (FORM == 2) {
+        epilogue_pc_tiles<1, 2>(a, acc, co_wave, pw, lane, res8, a.pc, 0);
+    } else {
+        epilogue_tiles<1, 2>(a, acc, co_wave, pw, lane, res8);
+    }
+#endif
+}
+
+// ------------------------------------------------------------------ dispatch
+namespace {
+bool flat_shape(const ConvArgs &a, FlatArgs &g)
+{
+    const int wc = a.Cout == 64 ? 2 : 4, px = 64 * (4 / wc), pieces = a.Cin / 16 + 1;
+    g.rows = px + (a.KH == 3 ? 2 * (a.W + 1) : 0);
+    g.patch_bytes = ((g.rows + 1) * pieces + 63) / 64 * 1024;
+    g.inv_pieces = (1u << 22) / (unsigned)pieces + 1;           // exact for i below 256 = the only ones divided
+    return g.patch_bytes + 512 <= 80 * 1024;
+}
+}  // namespace
+
+static bool flat_takes(const ConvArgs &a, bool direct_ok)
+{
+    FlatArgs g;
+    if (!direct_ok || a.frag_xor || a.in_xor || a.sh != 1 || a.sw != 1 || a.KH != a.KW || a.ph != a.KH / 2 || a.pw != a.KW / 2 || !a.vec_bias) return false;
+    if (a.x_bytes >= 0x7fffff00u || a.wp_bytes >= 0x7fffff00u || a.M > 0x7fffffff - 256) return false;
+    if (a.KH == 3) {
+        if (a.Cin == 64 ? a.Cout != 64 && a.Cout % 128 != 0 : (a.Cin != 128 && a.Cin != 256 && a.Cin != 512) || a.Cout % 128 != 0) return false;
+    } else if (a.KH != 1 || (a.Cin != 256 && a.Cin != 512 && a.Cin != 1024) || a.Cout % 128 != 0) {
+        return false;
+    }
+    return flat_shape(a, g);
+}
+
+// Every layer it takes but two kinds (microseconds the other kernel / this one, weights and maps cold in L2).  Up to 256 units of 32 channels x
+// 32 pixels the few-pixel kernel's are on the chip at once, one to a compute unit: 3x3 of 256 channels on 14 x 14, 248 units 5.9 / 6.5, 296 units
+// 8.3 / 6.5; of 512 on 7 x 7, 208 units 8.2 / 9.3, 400 units 11.7 / 9.3; of 128 on 28 x 28, 196 units 4.8 / 5.3, 296 units 6.3 / 5.3; 1024 -> 256 on
+// 14 x 14, 248 units 5.2 / 5.1, 296 units 6.5 / 5.1; 512 -> 2048 on 7 x 7, 256 units 4.3 / 4.1, 320 units 5.2 / 4.3.  Layers of 64 channels on large
+// pictures are level with the two-dimensional tiles that keep weights and patch in LDS (16 / 32 / 64 images of 56 x 56: 6.2 / 6.2, 9.2 / 9.9,
+// 14.7 / 14.6; with a skip operand 64 images 17.5 / 16.1).  The others: 3x3 of 256 channels on 14 x 14, 16 / 32 / 64 / 128 images 9.9 / 6.8, 11.4 / 7.4,
+// 13.2 / 10.8, 22.5 / 18.9; of 512 on 7 x 7, 64 images 14.3 / 10.7; of 128 on 28 x 28, 9 / 64 images 8.4 / 5.5, 16.1 / 12.6; 256 -> 1024 on 14 x 14,
+// 9 / 64 images 5.4 / 3.9, 13.0 / 9.5; 512 -> 256 on 28 x 28, 9 / 64 images 6.1 / 4.6, 16.1 / 14.1; 1024 -> 512 and 512 -> 128 within 4 % where they have
+// 12544 and 50176 pixels, 9 % faster at 9408.
+bool conv_flat_applies(const ConvArgs &a, bool direct_ok)
+{
+    if (g_tuning.flat == 2 || !flat_takes(a, direct_ok)) return false;
+    if (g_tuning.flat == 1) return true;
+    if (g_tuning.tile >= 0 || g_tuning.stages || g_tuning.ksplit || g_tuning.deep_always || g_tuning.halo_always || g_tuning.halo_tile ||
+        g_tuning.plane_always || g_tuning.lat)
+        return false;
+    if ((long long)(a.Cout / 32) * ((a.M + 31) / 32) <= 256 && !g_tuning.no_lat) return false;
+    return a.pc || a.res_mode != 0 || g_tuning.no_plane || !conv_plane_applies(a);
+}
+
+hipError_t launch_conv_flat(const ConvArgs &args, hipStream_t st)
+{
+    ConvArgs a = args;
+    FlatArgs g;
+    if (!flat_takes(a, true) || !flat_shape(a, g)) return hipErrorInvalidValue;
+    const bool narrow = a.Cout == 64;
+    if (!finish_args(a, narrow ? 64 : 128, narrow ? 128 : 64)) return hipErrorInvalidValue;
+    a.div_howo = make_fast_div((unsigned)(a.Ho * a.Wo));
+    a.div_wo = make_fast_div((unsigned)a.Wo);
+    g.sk = SkipMul{0, 0, 0};
+    if (a.res_mode == 1 && a.res_dtype == 0) g.sk = make_skip_mul(a.res_mul, a.res_shift);
+    const int form = a.pc ? 2 : a.rq_fast && a.epi_vec && (a.res_mode == 0 || g.sk.ok) ? 1 : 0;
+    const size_t lds_bytes = g.patch_bytes + 512;
+    auto go = [&](auto kernel) -> hipError_t {
+        if (lds_bytes > 64 * 1024) {
+            const hipError_t e = allow_large_lds((const void *)kernel);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * a.per_xcd)), dim3(256), lds_bytes, st, a, g);
+        return hipGetLastError();
+    };
+#define ICNN_FLAT(KK, NG, G, WC) (form == 1 ? go(conv_flat_kernel<KK, NG, G, WC, 1>) : form == 2 ? go(conv_flat_kernel<KK, NG, G, WC, 2>) : go(conv_flat_kernel<KK, NG, G, WC, 0>))
+    if (a.KH == 3) {
+        switch (a.Cin) {
+        case 64: return narrow ? ICNN_FLAT(3, 9, 1, 2) : ICNN_FLAT(3, 9, 1, 4);
+        case 128: return ICNN_FLAT(3, 9, 2, 4);
+        case 256: return ICNN_FLAT(3, 9, 4, 4);
+        default: return ICNN_FLAT(3, 18, 4, 4);
+        }
+    }
+    switch (a.Cin) {
+    case 256: return ICNN_FLAT(1, 1, 4, 4);
+    case 512: return ICNN_FLAT(1, 2, 4, 4);
+    default: return ICNN_FLAT(1, 4, 4, 4);
+    }
+#undef ICNN_FLAT
+}
+
+}  // namespace icnn

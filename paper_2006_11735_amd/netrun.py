@@ -68,9 +68,10 @@ class GpuNet:
 
     # A layer of 16384 pixels gives each of the 256 compute units one tile of 64; a layer with a few more runs two rounds, the second nearly
     # empty, and the next layer waits for it.  Beyond that size a batch therefore runs as two halves side by side on two streams,
-    # one half's last rounds filled with the other's next layer: 2.77 ms become 2.23 for the 152-layer network at batch 84, 3.24 become 2.82
-    # at 128, 1.04 become 0.94 for the 50-layer one at 84, 0.46 become 0.43 for the 18-layer one at 96.  At and below it (80 and
-    # 64 pictures: level to 5 % slower) there is no second round to fill.  Pictures of restoration networks are hundreds of rounds each.
+    # one half's last rounds filled with the other's next layer (halves / whole, us): 50-layer network 751 / 805 at batch 84, 977 / 1072 at 128;
+    # the 152-layer one 1818 / 1832 at 84, 2223 / 2506 at 128; per channel 1042 / 1071 at 84; the 18-layer one 317 / 357 at 84.  Below it the
+    # networks differ: the 152-layer one loses 3 % at 68 and is level at 76, the 50-layer one gains 2 % at 64, the 18-layer one 6 % from 44 on.
+    # Pictures of restoration networks are hundreds of rounds each.
     HALVES_MIN_PIXELS = 256 * 64
     HALVES_MAX_MAP = 32 * 32
 
@@ -163,9 +164,9 @@ class GpuNet:
         self.steps = steps
 
     # By whether requantisation is per channel: below these the three layers by themselves, which spread their weights over the whole chip,
-    # are level or faster (50-layer network, fused / apart: one image 240 / 236 us, two 250 / 252, nine 310 / 334, 32 469 / 515; per channel four
-    # images 339 / 326, six 379 / 392, 32 623 / 640).
-    TRIPLE_MIN_PIXELS = {False: 256, True: 1024}
+    # are level or faster (50-layer network, fused / apart: one image 232 / 231 us, three 252 / 252, four 255 / 257, nine 278 / 286, 32 449 / 476;
+    # per channel nine images 357 / 350, 16 418 / 413, 24 508 / 509, 32 601 / 610).
+    TRIPLE_MIN_PIXELS = {False: 256, True: 4704}
 
     def _fuse_triples(self):
         """A block's 3x3 convolution, the 1x1 convolution that closes the block and, where it follows, the 1x1 convolution that opens the
@@ -435,12 +436,10 @@ class GpuNet:
             i += 1
         self.steps = steps
 
-    # With 128 middle channels a block is a chain of 22 us while its tiles are fewer than the compute units; its three layers spread over
-    # the chip instead (one image: 12.7 us, four 17.6).  They are the faster choice while each of them runs in one round, 64 pixels to a
-    # compute unit: the 50-layer network with its three such blocks fused / layer by layer takes 363 / 352 us at 10 images, 437 / 427 at 20
-    # (15680 pixels), 460 / 464 at 21 (16464), 463 / 470 at 24, 522 / 534 at 32; on 36 x 36 maps 438 / 433 at 12 images (15552), 464 / 474 at
-    # 14 (18144); on 20 x 20 maps 439 / 431 at 40 (16000).  64 middle channels stay fused: 10.6 us for one image.
-    BLOCK128_MIN_PIXELS = 16385
+    # With 128 middle channels a block is one workgroup after another's worth of weights per 64 pixels; its three layers spread them over the
+    # chip.  The 50-layer network with its three such blocks fused / layer by layer: 225 / 231 us at one image of 28 x 28 (13 workgroups),
+    # 265 / 278 at nine, 443 / 472 at 32, 650 / 685 at 64.  Fewer pixels than that were not looked at and stay apart.
+    BLOCK128_MIN_PIXELS = 784
 
     def _fuse_blocks(self):
         """Replaces every run of three per-layer conv steps that forms an identity bottleneck block by one fused step."""

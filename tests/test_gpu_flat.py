@@ -1,0 +1,94 @@
+"""The stride-1 3x3 and 1x1 kernel whose weights go straight into registers (iconv2d_brelu, iconv2d_brelu_pc), at the edges of its tiles and in
+every form it takes, against the oracle; and the library's choice against the kernel it would take otherwise."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def flat():
+    from paper_2006_11735_amd import binding as B
+    B.icnn_set_tuning("flat", 1)
+    yield
+    B.icnn_set_tuning("reset")
+
+
+def layer(seed, n, h, w, cin, cout, k, pitch=0, signed=False):
+    g = np.random.default_rng(seed)
+    shape = (n, h, w, cin + pitch)
+    x = g.integers(-128, 128, size=shape).astype(np.int8) if signed else g.integers(0, 128, size=shape).astype(np.uint8)
+    wt = g.integers(-127, 128, size=(cout, k, k, cin), dtype=np.int8)
+    return g, x, wt, g.integers(-4096, 4097, size=cout).astype(np.int32)
+
+
+def check(x, wt, b, **kw):
+    from gpu_util import gpu_conv2d
+    kw.setdefault("mul", 20000)
+    kw.setdefault("shift", 25)
+    got = gpu_conv2d(x, wt, b, pad=wt.shape[1] // 2, **kw)
+    kw.pop("misalign", None)
+    want = O.conv2d(x, wt, b, pad=wt.shape[1] // 2, cin=wt.shape[3], **kw)
+    assert want.max() > want.min() and (got == want).all()
+
+
+# one pixel, one row, one column, a last tile of one pixel, of 63, pictures smaller and larger than a tile, every channel count it is built for
+@pytest.mark.parametrize("shape", [(1, 1, 1, 64, 64, 3), (1, 1, 129, 64, 64, 3), (1, 65, 1, 128, 128, 3), (3, 5, 13, 64, 128, 3), (5, 7, 7, 512, 128, 3),
+                                   (2, 14, 14, 256, 256, 3), (1, 9, 47, 256, 128, 3), (1, 3, 200, 64, 64, 3), (127, 1, 1, 256, 128, 1), (1, 1, 1, 512, 256, 1),
+                                   (1, 13, 5, 1024, 128, 1), (2, 8, 8, 1024, 384, 1), (1, 2, 2, 128, 128, 3), (300, 2, 3, 64, 64, 3)],
+                         ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("skip", [False, True], ids=["plain", "skip"])
+def test_tiles(flat, shape, skip):
+    g, x, wt, b = layer(sum(shape), *shape)
+    kw = dict(res=g.integers(0, 128, size=shape[:3] + shape[4:5], dtype=np.uint8), res_mode="pre", res_mul=20000, res_shift=5) if skip else {}
+    check(x, wt, b, mul=32767, shift=25, **kw)
+
+
+@pytest.mark.parametrize("kw", [dict(out_mode="raw_s32"), dict(out_mode="linear_s8"), dict(out_mode="clamp_u8", lo=3, hi=250), dict(bound_q=15), dict(mul=20001, shift=24),
+                                dict(mul=2**31 - 1, shift=43), dict(mul=1, shift=9)], ids=str)
+@pytest.mark.parametrize("res", [None, "u8", "s8", "s32", "post"])
+@pytest.mark.parametrize("shape", [(1, 9, 11, 64, 64, 3), (1, 9, 11, 256, 128, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_modes(flat, shape, res, kw):
+    g, x, wt, b = layer(5, *shape)
+    out = shape[:3] + shape[4:5]
+    if res == "post" and kw.get("out_mode") == "raw_s32":
+        res = "u8"                     # a raw accumulator has no requantised output to add to
+    r = {None: None, "u8": g.integers(0, 128, size=out, dtype=np.uint8), "post": g.integers(0, 128, size=out, dtype=np.uint8),
+         "s8": g.integers(-128, 128, size=out).astype(np.int8), "s32": g.integers(-300000, 300000, size=out).astype(np.int32)}[res]
+    more = {} if r is None else dict(res=r, res_mode="post" if res == "post" else "pre", res_mul=20000, res_shift=15 if res == "s32" else 5)
+    check(x, wt, b, **{**kw, **more})
+
+
+def test_inputs_pitches_and_channel_parameters(flat):
+    from test_gpu_conv import channel_params
+    for shape in ((1, 10, 11, 128, 128, 3), (2, 6, 6, 512, 128, 1)):
+        g, x, wt, b = layer(7, *shape, pitch=48)
+        res = g.integers(0, 128, size=shape[:3] + shape[4:5], dtype=np.uint8)
+        check(x, wt, b, out=np.zeros(shape[:3] + (shape[4] + 48,), np.uint8), out_c_offset=32)
+        check(x, wt, b, misalign=1)                      # unaligned addresses stay on a kernel that takes them
+        check(x, wt, b, res=res, res_mode="pre", **channel_params(8, shape[4], res=True))
+        check(x, wt, b, out_mode="linear_s8", **channel_params(9, shape[4]))
+        _g, x, wt, b = layer(10, *shape, signed=True)
+        check(x, wt, b)
+        check(x.view(np.uint8), wt, b)                   # bytes up to 255
+
+
+@pytest.mark.parametrize("shape", [(6, 14, 14, 256, 256, 3), (5, 14, 14, 256, 256, 3), (17, 7, 7, 512, 512, 3), (3, 28, 28, 128, 128, 3), (2, 28, 28, 512, 128, 1),
+                                   (9, 14, 14, 1024, 256, 1), (2, 56, 56, 64, 64, 3), (2, 30, 30, 256, 1024, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_the_librarys_choice(shape):
+    # on either side of 256 units of 32 channels x 32 pixels, with and without a skip operand
+    from gpu_util import gpu_conv2d
+    from paper_2006_11735_amd import binding as B
+    g, x, wt, b = layer(11, *shape)
+    res = g.integers(0, 128, size=shape[:3] + shape[4:5], dtype=np.uint8)
+    for kw in ({}, dict(res=res, res_mode="pre", res_mul=20000, res_shift=5)):
+        got = []
+        for how in (0, 1, 2):
+            B.icnn_set_tuning("flat", how)
+            try:
+                got.append(gpu_conv2d(x, wt, b, pad=shape[5] // 2, mul=20000, shift=25, **kw))
+            finally:
+                B.icnn_set_tuning("reset")
+        assert got[0].max() > 0 and (got[0] == got[1]).all() and (got[0] == got[2]).all()

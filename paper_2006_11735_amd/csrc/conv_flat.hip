@@ -1,9 +1,11 @@
-// A 3x3 or 1x1 layer of stride 1 whose weights go from memory straight into the registers of the one wave of a workgroup that
+// A 3x3 or 1x1 layer of stride 1 or 2 whose weights go from memory straight into the registers of the one wave of a workgroup that
 // multiplies them, and whose input crosses the compute unit's memory path once per 128 output channels.
 //
-//   tile     PX consecutive pixels of the flattened N*H*W axis; patch (3x3): these and the W + 1 pixels before and behind
+//   tile     PX consecutive pixels of the flattened N*Ho*Wo axis; patch (3x3): these and the W + 1 pixels before and behind
 //            them, so that tap (kh, kw) of a pixel is the patch row (kh - 1) * W + kw - 1 away; a tap beyond the image's edge
-//            reads a row of zeros instead, chosen by a mask of nine bits per pixel.  The whole patch, all channels, lies in
+//            reads a row of zeros instead, chosen by a mask of nine bits per pixel.  Stride 2: the input as four planes of the output's
+//            size, the pixels of even and odd rows and columns; the tile's pixels in the first, with one, Wo and Wo + 1 more before them
+//            in the others, and a tap is a row's distance again.  The whole patch, all channels, lies in
 //            LDS before the K loop begins, rows padded by 16 bytes (any 16 consecutive rows start in different banks)
 //   waves    four: WC along the output channels, 32 each; 4 / WC along the pixels, 64 each
 //   K loop   groups of G steps of 64; every group of weights is fetched eight K steps ahead; no barrier
@@ -21,12 +23,14 @@ namespace icnn {
 struct FlatArgs {
     int rows, patch_bytes;        // patch rows; bytes of it in LDS with the row of zeros behind, in whole KiB
     unsigned inv_pieces;          // i / (pieces of a row) = i * inv_pieces >> 22
+    int n_pt;                     // pixel tiles, if neighbouring workgroups share channels; 0: they share pixels
     SkipMul sk;
 };
 
 // KK: kernel size; NG groups of G steps: cin = 64 G NG / KK^2.  FORM: 1 requantisation as a product's high word (rq_fast), an unsigned 8-bit skip
 // operand before it rescaled likewise (g.sk) or none, 8-bit output; 0 any form of one pair per layer; 2 per output channel.
-template <int KK, int NG, int G, int WC, int FORM>
+// S: stride, both ways.
+template <int KK, int NG, int G, int WC, int FORM, int S>
 __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, const FlatArgs g)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -35,9 +39,12 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
     constexpr int AP = CIN + 16, PIECES = AP / 16, PX = 64 * (4 / WC), NS = 8 / G;
     constexpr int T = NG * G;                          // K steps
 
-    // LDS: patch | biases of the tile's channels
+    // LDS: patch | biases of the tile's channels | stride 2: where each patch row is in the input
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     int32_t *const btab = (int32_t *)(lds + g.patch_bytes);
+    unsigned *const rtab = (unsigned *)(lds + g.patch_bytes + 512);
+    // stride 2: first patch rows of the pixels of odd columns, odd rows, both
+    const int eo = PX, oe = 2 * PX + 1, oo = 3 * PX + 1 + a.Wo;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -46,6 +53,11 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
 
     int ct, pt;
     if (!tile_of_block(a, ct, pt)) return;
+    if (g.n_pt) {
+        const int logical = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
+        ct = logical / g.n_pt;
+        pt = logical - ct * g.n_pt;
+    }
     const int p0 = pt * PX;
     const int wc = wave % WC, pw = p0 + (wave / WC) * 64;                  // this wave's channels in the tile, first pixel
     const int co_tile = ct * (WC * 32), co_wave = co_tile + wc * 32;
@@ -65,6 +77,20 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
     // ---- prologue: biases, patch and the ring's first groups in flight together
     const int bv = a.bias[co_tile + min(tid, WC * 32 - 1)];
     asm volatile("" ::: "memory");
+    if constexpr (S == 2) {
+        for (int r = tid; r < g.rows; r += 256) {
+            const int odd_y = KK == 3 && r >= oe, odd_x = KK == 3 && (r >= oo || (r >= eo && r < oe));
+            const int p = p0 + (KK == 1 || r < eo ? r : r < oe ? r - eo - 1 : r < oo ? r - oe - a.Wo : r - oo - a.Wo - 1);
+            unsigned off = OOB;
+            if ((unsigned)p < (unsigned)a.M) {
+                const int n = fast_div(p, a.div_howo), at = p - n * (a.Ho * a.Wo), y = fast_div(at, a.div_wo);
+                const int iy = 2 * y + odd_y, ix = 2 * (at - y * a.Wo) + odd_x;
+                if (iy < a.H && ix < a.W) off = (unsigned)((n * a.H + iy) * a.W + ix) * (unsigned)a.in_cs;
+            }
+            rtab[r] = off;
+        }
+        __syncthreads();
+    }
     {
         const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.x_bytes, 0x00020000);
         const int first = KK == 3 ? p0 - a.W - 1 : p0;
@@ -73,8 +99,13 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
         int i = tid;
         int row = (int)(((unsigned)i * g.inv_pieces) >> 22), piece = i - row * PIECES;
         for (int c = wave; c < g.patch_bytes / 1024; c += 4) {
-            const int p = first + row;
-            const unsigned off = piece < PIECES - 1 && row < g.rows && (unsigned)p < (unsigned)a.M ? (unsigned)p * (unsigned)a.in_cs + piece * 16 : OOB;
+            unsigned off;
+            if constexpr (S == 2) {
+                off = piece < PIECES - 1 && row < g.rows ? rtab[min(row, g.rows - 1)] + piece * 16 : OOB;
+            } else {
+                const int p = first + row;
+                off = piece < PIECES - 1 && row < g.rows && (unsigned)p < (unsigned)a.M ? (unsigned)p * (unsigned)a.in_cs + piece * 16 : OOB;
+            }
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + c * 1024), 16, off, 0, 0, 0);
             row += 256 / PIECES;
             piece += 256 % PIECES;
@@ -98,10 +129,10 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
         q[j] = (wave / WC) * 64 + 32 * j + col;
         if constexpr (KK == 3) {
             const int p = min(p0 + q[j], a.M - 1);
-            const int r = p - fast_div(p, a.div_howo) * (a.H * a.W);
-            const int y = fast_div(r, a.div_wo), x = r - y * a.W;
-            const int cols = (x > 0 ? 1 : 0) | 2 | (x + 1 < a.W ? 4 : 0);
-            taps[j] = (y > 0 ? cols : 0) | cols << 3 | (y + 1 < a.H ? cols << 6 : 0);
+            const int r = p - fast_div(p, a.div_howo) * (a.Ho * a.Wo);
+            const int y = fast_div(r, a.div_wo), x = r - y * a.Wo;
+            const int cols = (x > 0 ? 1 : 0) | 2 | (S * x + 1 < a.W ? 4 : 0);
+            taps[j] = (y > 0 ? cols : 0) | cols << 3 | (S * y + 1 < a.H ? cols << 6 : 0);
         }
     }
     v4i res8[1][2];
@@ -131,10 +162,12 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
         const int zero = g.rows * AP + half * 16;
         int ad[2], nad[2];
         auto tap = [&](auto t_tag, int (&d)[2]) __attribute__((always_inline)) {
-            constexpr int t = decltype(t_tag)::value;
+            constexpr int t = decltype(t_tag)::value, kh = t / 3, kw = t % 3;
+            const int from = KK == 1 ? 0 : S == 1 ? kh * a.W + kw :
+                             (kh == 1 ? kw == 1 ? 0 : eo : (kw == 1 ? oe : oo) + (kh == 2 ? a.Wo : 0)) + (kw == 2 ? 1 : 0);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                const int at = (q[j] + (KK == 3 ? (t / 3) * a.W + t % 3 : 0)) * AP + half * 16;
+                const int at = (q[j] + from) * AP + half * 16;
                 d[j] = KK == 1 || (taps[j] >> t) & 1 ? at : zero;
             }
         };
@@ -184,27 +217,27 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
 
 // ------------------------------------------------------------------ dispatch
 namespace {
-bool flat_shape(const ConvArgs &a, FlatArgs &g)
+bool flat_shape(const ConvArgs &a, FlatArgs &g, size_t &lds_bytes)
 {
     const int wc = a.Cout == 64 ? 2 : 4, px = 64 * (4 / wc), pieces = a.Cin / 16 + 1;
-    g.rows = px + (a.KH == 3 ? 2 * (a.W + 1) : 0);
+    g.rows = a.KH == 1 ? px : a.sh == 1 ? px + 2 * (a.W + 1) : 4 * px + 2 * (a.Wo + 1);
     g.patch_bytes = ((g.rows + 1) * pieces + 63) / 64 * 1024;
     g.inv_pieces = (1u << 22) / (unsigned)pieces + 1;           // exact for i below 256 = the only ones divided
-    return g.patch_bytes + 512 <= 80 * 1024;
+    lds_bytes = g.patch_bytes + 512 + (a.sh == 2 ? (g.rows * 4 + 511) / 512 * 512 : 0);
+    return lds_bytes <= 160 * 1024;
 }
 }  // namespace
 
 static bool flat_takes(const ConvArgs &a, bool direct_ok)
 {
     FlatArgs g;
-    if (!direct_ok || a.frag_xor || a.in_xor || a.sh != 1 || a.sw != 1 || a.KH != a.KW || a.ph != a.KH / 2 || a.pw != a.KW / 2 || !a.vec_bias) return false;
-    if (a.x_bytes >= 0x7fffff00u || a.wp_bytes >= 0x7fffff00u || a.M > 0x7fffffff - 256) return false;
-    if (a.KH == 3) {
-        if (a.Cin == 64 ? a.Cout != 64 && a.Cout % 128 != 0 : (a.Cin != 128 && a.Cin != 256 && a.Cin != 512) || a.Cout % 128 != 0) return false;
-    } else if (a.KH != 1 || (a.Cin != 256 && a.Cin != 512 && a.Cin != 1024) || a.Cout % 128 != 0) {
-        return false;
-    }
-    return flat_shape(a, g);
+    size_t lds_bytes;
+    if (!direct_ok || a.frag_xor || a.in_xor || a.sh < 1 || a.sh > 2 || a.sw != a.sh || a.KH != a.KW || a.ph != a.KH / 2 || a.pw != a.KW / 2 || !a.vec_bias) return false;
+    if (a.x_bytes >= 0x7fffff00u || a.wp_bytes >= 0x7fffff00u || a.M > 0x7fffffff - 256 || a.W > 4096) return false;
+    if (a.Cout % 128 != 0 && !(a.Cout == 64 && a.Cin == 64 && a.KH == 3 && a.sh == 1)) return false;
+    const int c = a.Cin;
+    if (a.KH == 3 ? c != 64 && c != 128 && c != 256 && c != 512 : a.KH != 1 || (c != 128 && c != 256 && c != 512 && (a.sh == 1 ? c != 1024 && c != 2048 : c != 64))) return false;
+    return flat_shape(a, g, lds_bytes);
 }
 
 // Every layer it takes but two kinds (microseconds the other kernel / this one, weights and maps cold in L2).  Up to 256 units of 32 channels x
@@ -214,8 +247,11 @@ static bool flat_takes(const ConvArgs &a, bool direct_ok)
 // pictures are level with the two-dimensional tiles that keep weights and patch in LDS (16 / 32 / 64 images of 56 x 56: 6.2 / 6.2, 9.2 / 9.9,
 // 14.7 / 14.6; with a skip operand 64 images 17.5 / 16.1).  The others: 3x3 of 256 channels on 14 x 14, 16 / 32 / 64 / 128 images 9.9 / 6.8, 11.4 / 7.4,
 // 13.2 / 10.8, 22.5 / 18.9; of 512 on 7 x 7, 64 images 14.3 / 10.7; of 128 on 28 x 28, 9 / 64 images 8.4 / 5.5, 16.1 / 12.6; 256 -> 1024 on 14 x 14,
-// 9 / 64 images 5.4 / 3.9, 13.0 / 9.5; 512 -> 256 on 28 x 28, 9 / 64 images 6.1 / 4.6, 16.1 / 14.1; 1024 -> 512 and 512 -> 128 within 4 % where they have
-// 12544 and 50176 pixels, 9 % faster at 9408.
+// 9 / 64 images 5.4 / 3.9, 13.0 / 9.5; 512 -> 256 on 28 x 28, 9 / 64 images 6.1 / 4.6, 16.1 / 14.1; 128 -> 512, 15.6 / 11.2; 1024 -> 512 and 512 -> 128
+// within 4 % where they have 12544 and 50176 pixels, 9 % faster at 9408.  Stride 2, 64 images: 3x3 of 128 channels on 56 x 56 16.1 / 15.3, of 256 on
+// 28 x 28 16.5 / 12.1, of 512 on 14 x 14 19.6 / 12.8 (and 128 images 26.6 / 23.9); 128 -> 256 on 28 x 28 11.2 / 8.2, 256 -> 512 on 14 x 14 12.4 / 8.6;
+// 1x1, 64 -> 128 on 56 x 56 14.5 / 13.4, 256 -> 512 on 14 x 14 7.6 / 6.1.  A 1x1 patch of 2048 channels leaves room for one workgroup on a compute
+// unit: 64 / 80 / 96 / 128 images of 7 x 7 (196, 248, 300, 392 workgroups) 10.4 / 8.0, 10.8 / 8.4, 14.4 / 13.7, 12.5 / 14.1: one round of them only.
 bool conv_flat_applies(const ConvArgs &a, bool direct_ok)
 {
     if (g_tuning.flat == 2 || !flat_takes(a, direct_ok)) return false;
@@ -224,6 +260,7 @@ bool conv_flat_applies(const ConvArgs &a, bool direct_ok)
         g_tuning.plane_always || g_tuning.lat)
         return false;
     if ((long long)(a.Cout / 32) * ((a.M + 31) / 32) <= 256 && !g_tuning.no_lat) return false;
+    if (a.Cin == 2048 && (long long)(a.Cout / 128) * ((a.M + 63) / 64) > 256) return false;
     return a.pc || a.res_mode != 0 || g_tuning.no_plane || !conv_plane_applies(a);
 }
 
@@ -231,15 +268,19 @@ hipError_t launch_conv_flat(const ConvArgs &args, hipStream_t st)
 {
     ConvArgs a = args;
     FlatArgs g;
-    if (!flat_takes(a, true) || !flat_shape(a, g)) return hipErrorInvalidValue;
+    size_t lds_bytes;
+    if (!flat_takes(a, true) || !flat_shape(a, g, lds_bytes)) return hipErrorInvalidValue;
     const bool narrow = a.Cout == 64;
     if (!finish_args(a, narrow ? 64 : 128, narrow ? 128 : 64)) return hipErrorInvalidValue;
     a.div_howo = make_fast_div((unsigned)(a.Ho * a.Wo));
     a.div_wo = make_fast_div((unsigned)a.Wo);
+    // What the eight L2s fetch: weights eight times and the input once, or the other way round as far as the channel tiles go.  (3x3 of 512
+    // channels on 64 images of 7 x 7, 20.5 MB against 11 MB.)
+    const double wt = a.wp_bytes, in = a.x_bytes;
+    g.n_pt = a.n_ct > 1 && wt * 8 + in > wt * std::max(8 / a.n_ct, 1) + in * std::min(a.n_ct, 8) ? a.n_tiles / a.n_ct : 0;
     g.sk = SkipMul{0, 0, 0};
     if (a.res_mode == 1 && a.res_dtype == 0) g.sk = make_skip_mul(a.res_mul, a.res_shift);
     const int form = a.pc ? 2 : a.rq_fast && a.epi_vec && (a.res_mode == 0 || g.sk.ok) ? 1 : 0;
-    const size_t lds_bytes = g.patch_bytes + 512;
     auto go = [&](auto kernel) -> hipError_t {
         if (lds_bytes > 64 * 1024) {
             const hipError_t e = allow_large_lds((const void *)kernel);
@@ -248,19 +289,38 @@ hipError_t launch_conv_flat(const ConvArgs &args, hipStream_t st)
         hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * a.per_xcd)), dim3(256), lds_bytes, st, a, g);
         return hipGetLastError();
     };
-#define ICNN_FLAT(KK, NG, G, WC) (form == 1 ? go(conv_flat_kernel<KK, NG, G, WC, 1>) : form == 2 ? go(conv_flat_kernel<KK, NG, G, WC, 2>) : go(conv_flat_kernel<KK, NG, G, WC, 0>))
+#define ICNN_FLAT(KK, NG, G, WC, S) \
+    (form == 1 ? go(conv_flat_kernel<KK, NG, G, WC, 1, S>) : form == 2 ? go(conv_flat_kernel<KK, NG, G, WC, 2, S>) : go(conv_flat_kernel<KK, NG, G, WC, 0, S>))
+    if (a.KH == 3 && a.sh == 1) {
+        switch (a.Cin) {
+        case 64: return narrow ? ICNN_FLAT(3, 9, 1, 2, 1) : ICNN_FLAT(3, 9, 1, 4, 1);
+        case 128: return ICNN_FLAT(3, 9, 2, 4, 1);
+        case 256: return ICNN_FLAT(3, 9, 4, 4, 1);
+        default: return ICNN_FLAT(3, 18, 4, 4, 1);
+        }
+    }
     if (a.KH == 3) {
         switch (a.Cin) {
-        case 64: return narrow ? ICNN_FLAT(3, 9, 1, 2) : ICNN_FLAT(3, 9, 1, 4);
-        case 128: return ICNN_FLAT(3, 9, 2, 4);
-        case 256: return ICNN_FLAT(3, 9, 4, 4);
-        default: return ICNN_FLAT(3, 18, 4, 4);
+        case 64: return ICNN_FLAT(3, 9, 1, 4, 2);
+        case 128: return ICNN_FLAT(3, 9, 2, 4, 2);
+        case 256: return ICNN_FLAT(3, 9, 4, 4, 2);
+        default: return ICNN_FLAT(3, 18, 4, 4, 2);
+        }
+    }
+    if (a.sh == 1) {
+        switch (a.Cin) {
+        case 128: return ICNN_FLAT(1, 1, 2, 4, 1);
+        case 256: return ICNN_FLAT(1, 1, 4, 4, 1);
+        case 512: return ICNN_FLAT(1, 2, 4, 4, 1);
+        case 1024: return ICNN_FLAT(1, 4, 4, 4, 1);
+        default: return ICNN_FLAT(1, 8, 4, 4, 1);
         }
     }
     switch (a.Cin) {
-    case 256: return ICNN_FLAT(1, 1, 4, 4);
-    case 512: return ICNN_FLAT(1, 2, 4, 4);
-    default: return ICNN_FLAT(1, 4, 4, 4);
+    case 64: return ICNN_FLAT(1, 1, 1, 4, 2);
+    case 128: return ICNN_FLAT(1, 1, 2, 4, 2);
+    case 256: return ICNN_FLAT(1, 1, 4, 4, 2);
+    default: return ICNN_FLAT(1, 2, 4, 4, 2);
     }
 #undef ICNN_FLAT
 }

@@ -1,4 +1,4 @@
-"""The stride-1 3x3 and 1x1 kernel whose weights go straight into registers (iconv2d_brelu, iconv2d_brelu_pc), at the edges of its tiles and in
+"""The 3x3 and 1x1 kernel of strides 1 and 2 whose weights go straight into registers (iconv2d_brelu, iconv2d_brelu_pc), at the edges of its tiles and in
 every form it takes, against the oracle; and the library's choice against the kernel it would take otherwise."""
 import numpy as np
 import pytest
@@ -37,13 +37,28 @@ def check(x, wt, b, **kw):
 # one pixel, one row, one column, a last tile of one pixel, of 63, pictures smaller and larger than a tile, every channel count it is built for
 @pytest.mark.parametrize("shape", [(1, 1, 1, 64, 64, 3), (1, 1, 129, 64, 64, 3), (1, 65, 1, 128, 128, 3), (3, 5, 13, 64, 128, 3), (5, 7, 7, 512, 128, 3),
                                    (2, 14, 14, 256, 256, 3), (1, 9, 47, 256, 128, 3), (1, 3, 200, 64, 64, 3), (127, 1, 1, 256, 128, 1), (1, 1, 1, 512, 256, 1),
-                                   (1, 13, 5, 1024, 128, 1), (2, 8, 8, 1024, 384, 1), (1, 2, 2, 128, 128, 3), (300, 2, 3, 64, 64, 3)],
+                                   (1, 13, 5, 1024, 128, 1), (2, 8, 8, 1024, 384, 1), (1, 2, 2, 128, 128, 3), (300, 2, 3, 64, 64, 3),
+                                   (1, 5, 13, 2048, 128, 1), (1, 63, 1, 128, 128, 1)],
                          ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("skip", [False, True], ids=["plain", "skip"])
 def test_tiles(flat, shape, skip):
     g, x, wt, b = layer(sum(shape), *shape)
     kw = dict(res=g.integers(0, 128, size=shape[:3] + shape[4:5], dtype=np.uint8), res_mode="pre", res_mul=20000, res_shift=5) if skip else {}
     check(x, wt, b, mul=32767, shift=25, **kw)
+
+
+# stride 2: one pixel, even and odd pictures, rows and columns of one, pictures smaller and larger than a tile
+@pytest.mark.parametrize("shape", [(1, 1, 1, 64, 128, 3), (3, 7, 9, 64, 128, 3), (2, 28, 28, 256, 128, 3), (5, 8, 7, 128, 128, 3), (1, 1, 131, 128, 128, 3),
+                                   (1, 131, 1, 64, 256, 3), (9, 2, 2, 256, 128, 3), (6, 14, 14, 512, 128, 3), (130, 1, 1, 128, 128, 3), (2, 13, 30, 64, 128, 1),
+                                   (1, 9, 15, 128, 256, 1), (3, 7, 7, 256, 128, 1), (1, 17, 17, 512, 128, 1)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("form", ["plain", "skip", "raw", "per channel"])
+def test_stride_2(flat, shape, form):
+    from test_gpu_conv import channel_params
+    g, x, wt, b = layer(sum(shape), *shape)
+    n, h, w = shape[:3]
+    res = g.integers(0, 128, size=(n, (h + 1) // 2, (w + 1) // 2, shape[4]), dtype=np.uint8)
+    check(x, wt, b, stride=2, **{"plain": {}, "skip": dict(res=res, res_mode="pre", res_mul=20000, res_shift=5), "raw": dict(out_mode="raw_s32"),
+                                 "per channel": channel_params(3, shape[4])}[form])
 
 
 @pytest.mark.parametrize("kw", [dict(out_mode="raw_s32"), dict(out_mode="linear_s8"), dict(out_mode="clamp_u8", lo=3, hi=250), dict(bound_q=15), dict(mul=20001, shift=24),
@@ -76,7 +91,7 @@ def test_inputs_pitches_and_channel_parameters(flat):
 
 
 @pytest.mark.parametrize("shape", [(6, 14, 14, 256, 256, 3), (5, 14, 14, 256, 256, 3), (17, 7, 7, 512, 512, 3), (3, 28, 28, 128, 128, 3), (2, 28, 28, 512, 128, 1),
-                                   (9, 14, 14, 1024, 256, 1), (2, 56, 56, 64, 64, 3), (2, 30, 30, 256, 1024, 1)], ids=lambda s: "x".join(map(str, s)))
+                                   (9, 14, 14, 1024, 256, 1), (2, 56, 56, 64, 64, 3), (2, 30, 30, 256, 1024, 1), (16, 7, 7, 2048, 512, 1), (90, 7, 7, 2048, 512, 1)], ids=lambda s: "x".join(map(str, s)))
 def test_the_librarys_choice(shape):
     # on either side of 256 units of 32 channels x 32 pixels, with and without a skip operand
     from gpu_util import gpu_conv2d

@@ -308,7 +308,13 @@ static hipError_t launch_dual_cfg(const ConvArgs &a0, const ProjArgs &q, hipStre
 
 hipError_t launch_conv_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st)
 {
-    if (conv_lat_dual_applies(a, q)) return launch_conv_lat_dual(a, q, st);
+    // Where the projection has twice the closing layer's channels: weights straight into registers, except where the few-pixel kernel has no more
+    // work units than the chip has compute units (us few-pixel / this one: 224 units 5.7 / 5.6, 256 units 6.4 / 7.8, 416 units 7.9 / 5.6, 448 units
+    // 9.0 / 7.8).  Against the kernel below, 64 images: 128 + 256 -> 512 channels on 28 x 28 28.7 / 20.9, 256 + 512 -> 1024 on 14 x 14 23.7 / 18.1,
+    // 512 + 1024 -> 2048 on 7 x 7 19.1 / 19.1 (128 images 35.6 / 30.3); per channel 33.2 / 25.6, 25.7 / 20.5, 20.5 / 22.0 (37.3 / 33.9).
+    const bool flat = conv_flat_dual_applies(a, q), many = (long long)((a.Cout + 31) / 32) * ((a.M + 31) / 32) > 256;
+    if (conv_lat_dual_applies(a, q) && !(flat && many && !g_tuning.lat)) return launch_conv_lat_dual(a, q, st);
+    if (flat) return launch_conv_flat_dual(a, q, st);
     // narrow pixel tiles when the wide ones would leave most CUs without work
     const long long wide = (long long)((a.Cout + 127) / 128) * ((a.M + 127) / 128);
     if (a.pc) {

@@ -263,6 +263,8 @@ bool conv_plane_twin_ok(const ConvArgs &a, const ConvArgs &b);
 hipError_t launch_conv_plane_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st);
 bool conv_tail_ok(const ConvArgs &a, const ConvArgs &b, const ConvArgs &c);
 hipError_t launch_conv_tail(const ConvArgs &a, const ConvArgs &b, const ConvArgs &c, hipStream_t st);
+bool conv_flat_dual_applies(const ConvArgs &a, const ProjArgs &q);
+hipError_t launch_conv_flat_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st);
 bool conv_flat_applies(const ConvArgs &a, bool direct_ok);
 hipError_t launch_conv_flat(const ConvArgs &a, hipStream_t st);
 bool conv_deep_applies(const ConvArgs &a);

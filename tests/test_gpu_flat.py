@@ -107,3 +107,54 @@ def test_the_librarys_choice(shape):
             finally:
                 B.icnn_set_tuning("reset")
         assert got[0].max() > 0 and (got[0] == got[1]).all() and (got[0] == got[2]).all()
+
+
+# one tile, one pixel, the last tile of one pixel and of 63, strides 1 and 2 on even and odd pictures, every channel count it is built for
+@pytest.mark.parametrize("shape", [(1, 1, 1, 128, 128, 2), (1, 13, 5, 128, 256, 2), (3, 7, 9, 256, 128, 2), (1, 9, 7, 512, 128, 1), (127, 1, 1, 256, 128, 1),
+                                   (1, 1, 130, 128, 128, 2), (5, 7, 7, 512, 384, 2), (9, 14, 14, 256, 256, 1)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("form", ["plain", "wide", "s8", "per channel"])
+def test_closing_layer_with_projection(shape, form):
+    import torch
+    from gpu_util import dev
+    from paper_2006_11735_amd import binding as B
+    n, h, w, cm, cout, stride = shape
+    hp, wp = h * stride, (w - 1) * stride + 1                               # at stride 2 even heights, odd widths
+    g = np.random.default_rng(sum(shape))
+    xm, xp = g.integers(0, 128, size=(n, h, w, cm), dtype=np.uint8), g.integers(0, 128, size=(n, hp, wp, 2 * cm), dtype=np.uint8)
+    wm, wq = g.integers(-127, 128, size=(cout, 1, 1, cm), dtype=np.int8), g.integers(-127, 128, size=(cout, 1, 1, 2 * cm), dtype=np.int8)
+    bm, bq = (g.integers(-4096, 4097, size=cout).astype(np.int32) for _ in range(2))
+    kw = dict(mul=23187, shift=27, res_mul=20011, res_shift=15)
+    if form == "wide":
+        kw.update(mul=2**31 - 1, shift=43, res_mul=1, res_shift=0)
+    if form == "s8":
+        kw["out_mode"] = "linear_s8"
+    pc = {}
+    if form == "per channel":
+        pc = dict(mul_c=g.integers(1 << 14, 1 << 15, size=cout).astype(np.int32), shift_c=g.integers(24, 29, size=cout).astype(np.int32),
+                  res_mul_c=g.integers(1 << 14, 20011, size=cout).astype(np.int32), res_shift_c=g.integers(15, 17, size=cout).astype(np.int32))
+    want = O.conv2d(xm, wm, bm, bound_q=127, res=O.conv2d(xp, wq, bq, stride=stride, out_mode="raw_s32"), res_mode="pre", **kw, **pc)
+    out_mode = B.ICNN_OUT_LINEAR_S8 if form == "s8" else B.ICNN_OUT_BRELU_U8
+    dm = B.conv_desc(n=n, h=h, w=w, cin=cm, in_c_stride=cm, cout=cout, kh=1, kw=1, out_c_stride=cout, mul=kw["mul"], shift=kw["shift"], bound_q=127, out_mode=out_mode,
+                     res_mode=B.ICNN_RES_PRE, res_dtype=B.ICNN_S32, res_c_stride=cout, res_mul=kw["res_mul"], res_shift=kw["res_shift"])
+    dp = B.conv_desc(n=n, h=hp, w=wp, cin=2 * cm, in_c_stride=2 * cm, cout=cout, kh=1, kw=1, stride_h=stride, stride_w=stride, out_c_stride=cout,
+                     out_mode=B.ICNN_OUT_RAW_S32)
+    packs = []
+    for d, wt in ((dm, wm), (dp, wq)):
+        packs.append(torch.zeros(B.iconv2d_packed_weight_bytes(d), dtype=torch.uint8, device="cuda:0"))
+        B.iconv2d_prepack_weights(d, dev(wt), packs[-1])
+    args = dev(xm), packs[0], dev(bm)
+    if pc:
+        arrs = [dev(pc[k]) for k in ("mul_c", "shift_c", "res_mul_c", "res_shift_c")]
+        pcp = torch.zeros(B.iconv2d_packed_channel_params_bytes(dm), dtype=torch.uint8, device="cuda:0")
+        B.iconv2d_prepack_channel_params(dm, B.channel_params(*arrs), pcp)
+        args += (pcp,)
+    other = dev(xp), packs[1], dev(bq)
+    fn = B.iconv2d_dual_brelu_pc if pc else B.iconv2d_dual_brelu
+    for name, value in (("no_lat", 1), ("flat", 2)):                        # this kernel, the others
+        y = torch.full((n, h, w, cout), 99, dtype=torch.int8 if form == "s8" else torch.uint8, device="cuda:0")
+        B.icnn_set_tuning(name, value)
+        try:
+            fn(dm, *args, dp, *other, y)
+        finally:
+            B.icnn_set_tuning("reset")
+        assert want.max() > 0 and (y.cpu().numpy() == want).all()

@@ -112,6 +112,15 @@ def test_twin_with_outputs_of_their_own_and_a_clamped_branch():
         assert yb.dtype == np.int32 and (ya == wa).all() and (yb == wb).all()
 
 
+# the 5x5 layer beside a 3x3 one of 16 channels (two output rows to an accumulator) and of others: pictures whose last rows leave one, two or three
+# of a wave's four, an odd pair, fewer rows than a tile
+@pytest.mark.parametrize("n, h, w", [(1, 1, 40), (1, 17, 33), (2, 18, 64), (1, 35, 31), (1, 16, 160), (1, 3, 3)])
+@pytest.mark.parametrize("cout_a, cout_b, mode_b", [(32, 16, "brelu"), (16, 16, "brelu"), (32, 32, "brelu"), (16, 32, "brelu"), (32, 16, "clamp_u8")])
+def test_twin_of_5x5_and_3x3(n, h, w, cout_a, cout_b, mode_b):
+    got, want = run_twin(n + h + w, n, h, w, 64, 5, cout_a, cout_b, mode_b=mode_b)
+    assert (got == want).all()
+
+
 def test_twin_refuses_what_it_does_not_take():
     from gpu_util import dev
     from paper_2006_11735_amd import binding as B

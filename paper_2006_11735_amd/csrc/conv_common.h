@@ -639,6 +639,54 @@ __device__ __forceinline__ v4i epilogue_hi16(const P &a, const SkipMul &sk, cons
     epilogue_hi_slice<RES, 8, 8>(a, sk, acc, res8, w);
     return v4i{w[0], w[1], w[2], w[3]};
 }
+// The same per output channel, from tables of a factor (pc_prepack_kernel's A) and of the skip rescale's multiplier and byte position (pc_hi_channel):
+// five and three quarter instructions per output, two and three quarters without the operand.  A, K: those of outputs R0, R0 + 1; P: the positions
+// of the four outputs that R0 is among, a byte each.
+typedef int v2i __attribute__((ext_vector_type(2)));
+template <int RES, int R0>
+__device__ __forceinline__ void epilogue_pc_hi_pair(const ConvArgs &a, v2i A, v2i K, uint32_t P, const v16i &acc, const v4i &res8, int (&w)[4])
+{
+    int t[2];
+    const int lo_v = a.lo;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        t[e] = acc[R0 + e];
+        if constexpr (RES == 1) {
+            // [x * mul / 2^shift] = high 32 bits of (x << (32 - shift)) * mul + 2^31
+            const int byte = 8 * ((R0 + e) & 3);
+            const uint32_t x = (((uint32_t)res8[(R0 + e) >> 2] >> byte) & 0xffu) << ((P >> byte) & 0xffu);
+            t[e] = __builtin_elementwise_add_sat(t[e], (int)(((uint64_t)x * (uint32_t)K[e] + 0x80000000ull) >> 32));
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 2; ++e) t[e] = med3_vvs((int)(((int64_t)t[e] * A[e] + 0x80000000LL) >> 32), lo_v, a.hi);
+    const uint32_t two = __builtin_amdgcn_perm((uint32_t)t[1], (uint32_t)t[0], 0x0c0c0400u);
+    if constexpr ((R0 & 2) == 0) w[R0 >> 2] = (int)two;
+    else w[R0 >> 2] = (int)__builtin_amdgcn_perm(two, (uint32_t)w[R0 >> 2], 0x05040100u);
+}
+// sixteen of them, tables in LDS
+template <int RES>
+__device__ __forceinline__ v4i epilogue_pc_hi16(const ConvArgs &a, const int32_t *A, const int32_t *K, const uint8_t *P, const v16i &acc, const v4i &res8)
+{
+    int w[4];
+    static_for<8>([&](auto h_tag) __attribute__((always_inline)) {
+        constexpr int R0 = 2 * decltype(h_tag)::value;
+        epilogue_pc_hi_pair<RES, R0>(a, *(const v2i *)(A + R0), RES ? *(const v2i *)(K + R0) : v2i{0, 0}, RES ? *(const uint32_t *)(P + (R0 & ~3)) : 0u, acc, res8, w);
+    });
+    return v4i{w[0], w[1], w[2], w[3]};
+}
+// A channel's table entries from the packed parameters; returns whether that form is exact for it (the factor needs no shift or clamp around
+// it, the rescale of an unsigned byte stays in int32).  skip: the layer has such an operand.
+__device__ __forceinline__ bool pc_hi_channel(const int32_t *pc, int channel, bool skip, int &A, int &K, int &P)
+{
+    const int32_t *const g = pc + (channel >> 4) * kPcGroupInts;
+    const int r = channel & 15, flags = g[kPcFlags], rm = g[kPcResMul + r], rs = g[kPcResShift + r];
+    A = g[kPcA + r];
+    // (flag bit 0: shifts of 0 to 30, 255 * rm below 2^31; with a shift below 8 the byte goes to the top and the multiplier up by the rest)
+    P = 32 - max(rs & 31, 8);
+    K = skip ? rm << max(8 - (rs & 31), 0) : 0;
+    return (flags & 2) && (!skip || (flags & 1));
+}
 // Between the last v_mfma of an accumulation and the first instruction that reads the accumulator.  The compiler's
 // hazard recogniser does not always keep the two apart (seen in a kernel whose epilogue starts two instructions after
 // the last MFMA, behind a branch: the reads returned the sums without the last product, now and then), and the

@@ -25,16 +25,16 @@ __global__ __launch_bounds__(256, 2) void conv_flat_dual_kernel(const ConvArgs a
     constexpr int CH = 64 * G, AP = CH + 16, PIECES = AP / 16, PX = 64, NS = 8 / G, ALL = PS + MS;
     constexpr int BUF = PX * AP;                       // a whole number of KiB: 64 rows of PIECES pieces
 
-    // LDS: two buffers | the projection's biases | the closing layer's | where each pixel is in the projection's input | FORM 2: rescale factors, shifts
-    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-    int32_t *const tab = (int32_t *)(lds + 2 * BUF);
-    unsigned *const rtab = (unsigned *)(tab + 256);
-    int32_t *const rescale = tab + 256 + PX;
-
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
+
+    // LDS: two buffers | the projection's biases | the closing layer's | where each pixel is in the projection's input | FORM 2: rescale factors, shifts, factors
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    int32_t *const tab = (int32_t *)(lds + 2 * BUF);
+    unsigned *const rtab = (unsigned *)(tab + 256);
+    int32_t *const rescale = tab + 256 + PX, *const factors = rescale + 256 + wave * 32;
 
     int ct, pt;
     if (!tile_of_block(a, ct, pt)) return;
@@ -58,11 +58,18 @@ __global__ __launch_bounds__(256, 2) void conv_flat_dual_kernel(const ConvArgs a
             ring[k % NS][f] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
         }
     };
+    [[maybe_unused]] bool one_product = false;
     // ---- prologue: tables, then the projection's segments and the ring's first groups in flight together
     {
         const int co = co_tile + (tid & 127);
         tab[tid] = tid < 128 ? q.bias[co] : a.bias[co];
         if constexpr (FORM == 2) rescale[tid] = a.pc[(co >> 4) * kPcGroupInts + (tid < 128 ? kPcResMul : kPcResShift) + (co & 15)];
+        if constexpr (FORM == 2) {
+            int factor, none, position;
+            const bool ok = pc_hi_channel(a.pc, co_wave + col, false, factor, none, position);
+            one_product = a.pc_fast_ok && __builtin_amdgcn_ballot_w64(!ok) == 0;
+            if (half == 0) factors[col] = factor;
+        }
         if (tid < PX) {
             const int p = p0 + tid;
             unsigned off = OOB;
@@ -180,12 +187,14 @@ __global__ __launch_bounds__(256, 2) void conv_flat_dual_kernel(const ConvArgs a
 
     mfma_drain(acc);
     const int pw = p0;
-    if constexpr (FORM == 1) {
+    if (FORM == 1 || (FORM == 2 && one_product)) {
         const SkipMul none = {0, 0, 0};
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int p = pw + 32 * j + col;
-            const v4i w = epilogue_hi16<0>(a, none, acc[0][j], v4i{0, 0, 0, 0});
+            v4i w;
+            if constexpr (FORM == 2) w = epilogue_pc_hi16<0>(a, factors + half * 16, factors, nullptr, acc[0][j], v4i{0, 0, 0, 0});
+            else w = epilogue_hi16<0>(a, none, acc[0][j], v4i{0, 0, 0, 0});
             if (p < a.M) *(v4i *)((uint8_t *)a.out + (size_t)p * a.out_cs + a.out_co + co_wave + half * 16) = w;
         }
     } else {
@@ -211,7 +220,7 @@ hipError_t launch_conv_flat_dual(const ConvArgs &args, const ProjArgs &q, hipStr
     a.div_wo = make_fast_div((unsigned)a.Wo);
     const double wt = (double)a.wp_bytes + q.wp_bytes, in = (double)a.x_bytes + (double)a.M * q.Cin;       // as in conv_flat.hip
     const int n_pt = a.n_ct > 1 && wt * 8 + in > wt * (a.n_ct < 8 ? 8 / a.n_ct : 1) + in * (a.n_ct < 8 ? a.n_ct : 8) ? a.n_tiles / a.n_ct : 0;
-    const size_t lds_bytes = 2 * 64 * ((a.Cin == 128 ? 128 : 256) + 16) + (256 + 64 + (a.pc ? 256 : 0)) * 4;
+    const size_t lds_bytes = 2 * 64 * ((a.Cin == 128 ? 128 : 256) + 16) + (256 + 64 + (a.pc ? 384 : 0)) * 4;
     auto go = [&](auto kernel) -> hipError_t {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * a.per_xcd)), dim3(256), lds_bytes, st, a, q, n_pt);
         return hipGetLastError();

@@ -165,8 +165,9 @@ class GpuNet:
 
     # By whether requantisation is per channel: below these the three layers by themselves, which spread their weights over the whole chip,
     # are level or faster (50-layer network, fused / apart: one image 232 / 231 us, three 252 / 252, four 255 / 257, nine 278 / 286, 32 449 / 476;
-    # per channel nine images 357 / 350, 16 418 / 413, 24 508 / 509, 32 601 / 610).
-    TRIPLE_MIN_PIXELS = {False: 256, True: 4704}
+    # per channel nine images 317 / 292, 16 359 / 336, 32 486 / 487, 48 638 / 645, 64 714 / 725, 76 782 / 794; with two launches side by side
+    # the layers are: 96 images 929 / 885).
+    TRIPLE_MIN_PIXELS = {False: 256, True: 6272}
 
     def _fuse_triples(self):
         """A block's 3x3 convolution, the 1x1 convolution that closes the block and, where it follows, the 1x1 convolution that opens the
@@ -179,7 +180,7 @@ class GpuNet:
             if len(run) >= 2 and kinds[0] == kinds[1] and kinds[0] in ("conv", "conv_pc") and run[0][1]["kh"] == 3:
                 pc = kinds[0] == "conv_pc"
                 o2, o3 = run[0][1], run[1][1]
-                if np.prod(self.buf[o2["dst"]].shape[:3]) >= self.TRIPLE_MIN_PIXELS[kinds[0] == "conv_pc"] and o3["src"] == o2["dst"] and o3["kh"] == 1 and o2["dst_c_offset"] == 0 and o2["cout"] == o3["cin"]:
+                if np.prod(self.buf[o2["dst"]].shape[:3]) >= self.TRIPLE_MIN_PIXELS[pc] and not (pc and self.parts > 1) and o3["src"] == o2["dst"] and o3["kh"] == 1 and o2["dst_c_offset"] == 0 and o2["cout"] == o3["cin"]:
                     d2, t, w2, b2, r2, t2 = self._conv_args(run[0])
                     d3, _t2, w3, b3, res, y = self._conv_args(run[1])
                     head = (d2, t, w2, b2) + ((run[0][2][4],) if pc else ()) + (t2, d3, w3, b3) + ((run[1][2][4],) if pc else ()) + (res, y)
@@ -218,10 +219,10 @@ class GpuNet:
     #   10: 351 / 348, 11: 387 / 387, 16: 399 / 402, 64: 748 / 774.
     #   Per channel: 18.7 us fused at few pixels; the same network: 16 images 500 / 490 us, 40: 726 / 711, 48: 826 / 842, 64: 904 / 919.  Up to
     #   8192 pixels the first layer by itself is one round of two 128 x 128 tiles per compute unit.
-    #   128 -> 512 -> 128: 7.4 us fused and 9.7 apart at 784 pixels already; per channel two of them gain 5 us at one image only when apart
-    #   (784 pixels), are level at 1568 pixels and gain 6 us fused at 7056.
-    PAIR_MIN_PIXELS = {(256, False): 2049, (256, True): 8193, (128, True): 1536}
+    #   128 -> 512 -> 128: 7.4 us fused and 9.7 apart at 784 pixels already; per channel never (the 50-layer network fused / apart: one image 263 / 265,
+    #   nine 292 / 285, 16 337 / 332, 32 489 / 477).
     PAIR_MAX_PIXELS = 64 * 512
+    PAIR_MIN_PIXELS = {(256, False): 2049, (256, True): 8193, (128, True): PAIR_MAX_PIXELS + 1}
     PAIR_MAX_WIDE = 1024
 
     def _fuse_pairs(self):

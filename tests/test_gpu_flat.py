@@ -90,6 +90,25 @@ def test_inputs_pitches_and_channel_parameters(flat):
         check(x.view(np.uint8), wt, b)                   # bytes up to 255
 
 
+# per channel: factors and skip rescales that are one product each (shifts 0 to 30, the largest multipliers among them), and a last wave where one is not
+@pytest.mark.parametrize("odd", [None, "factor", "shift", "multiplier"])
+@pytest.mark.parametrize("shape", [(1, 9, 11, 64, 64, 3), (1, 9, 11, 256, 256, 1), (2, 7, 9, 128, 128, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_per_channel_products(flat, shape, odd):
+    g, x, wt, b = layer(12, *shape)
+    cout = shape[4]
+    rs = g.integers(0, 31, size=cout)
+    rm = np.where(np.arange(cout) % 5 == 0, (2**31 - 1 - ((1 << rs) >> 1)) // 255, g.integers(1, 1 << 15, size=cout))
+    pc = dict(mul_c=g.integers(1 << 14, 1 << 15, size=cout).astype(np.int32), shift_c=g.integers(21, 33, size=cout).astype(np.int32),
+              res_mul_c=rm.astype(np.int32), res_shift_c=rs.astype(np.int32))
+    if odd:
+        name, value = {"factor": ("shift_c", 33), "shift": ("res_shift_c", 31), "multiplier": ("res_mul_c", 2**31 - 1)}[odd]
+        pc[name][cout - 7] = value
+    res = g.integers(0, 256, size=shape[:4][:3] + (cout,), dtype=np.uint8)
+    check(x, wt, b, res=res, res_mode="pre", **pc)
+    check(x, wt, b, res=res, res_mode="pre", out_mode="linear_s8", **pc)
+    check(x, wt, b, mul_c=pc["mul_c"], shift_c=pc["shift_c"])
+
+
 @pytest.mark.parametrize("shape", [(6, 14, 14, 256, 256, 3), (5, 14, 14, 256, 256, 3), (17, 7, 7, 512, 512, 3), (3, 28, 28, 128, 128, 3), (2, 28, 28, 512, 128, 1),
                                    (9, 14, 14, 1024, 256, 1), (2, 56, 56, 64, 64, 3), (2, 30, 30, 256, 1024, 1), (16, 7, 7, 2048, 512, 1), (90, 7, 7, 2048, 512, 1)], ids=lambda s: "x".join(map(str, s)))
 def test_the_librarys_choice(shape):

@@ -16,7 +16,8 @@
 //            a 32-channel chunk of the MID2 outputs per wave.
 //
 // What bounds it is the compute unit's path from L2: a 64-pixel tile pulls both layers' packed weights (512 KB at
-// 256 <-> 1024 channels) plus its skip operands through it, at the 25-35 bytes per clock that path delivers, while the
+// 256 <-> 1024 channels) plus its skip operands through it, at 25-35 bytes per clock with 64-bit addresses (64-72 through descriptors, as
+// conv_tri.hip has it, which takes these pairs together with the 3x3 layer before them where it applies), while the
 // matrix cores need a quarter of that time; hence one tile per workgroup and nothing fetched twice.
 //
 // Every product runs on v_mfma_i32_32x32x32_i8 with the accumulator layout, packed weights and epilogue arithmetic

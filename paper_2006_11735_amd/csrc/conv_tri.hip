@@ -39,6 +39,11 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int yb = g.patch_bytes;
     int32_t *const btab = (int32_t *)(lds + yb + PX * YP);
+    // FORM 2 with g.table (epilogue_pc_hi16): factors in the same order, skip multipliers and byte positions of the last layer, a word per wave: all of
+    // its channels take that form.  (12544 pixels, per channel: 33 us with the packed parameters fetched from memory for every 32 pixels, 27.5 so.)
+    int32_t *const atab = btab + 2 * MID + C, *const ktab = atab + 2 * MID + C, *const votes = ktab + C;
+    uint8_t *const ptab = (uint8_t *)(votes + 8);
+    [[maybe_unused]] bool one_product = false;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -154,9 +159,13 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
     using H1 = std::integral_constant<int, 1>;
 
     // sixteen bytes of layer a at this lane's pixel, RES: with a skip operand
-    auto finish = [&](const ConvArgs &a, auto res_tag, const v16i &c, const v4i &r8, const int32_t *pc) __attribute__((always_inline)) {
+    // (FORM 2: its packed parameters, its place in atab; only the last layer, at MID of it, has an operand)
+    auto finish = [&](const ConvArgs &a, auto res_tag, const v16i &c, const v4i &r8, [[maybe_unused]] const int32_t *pc, [[maybe_unused]] int at) __attribute__((always_inline)) {
         constexpr int RES = decltype(res_tag)::value;
-        if constexpr (FORM == 2) return epilogue_pc_bytes16<RES>(a, c, r8, pc);
+        if constexpr (FORM == 2) {
+            if (one_product) return epilogue_pc_hi16<RES>(a, atab + at, ktab + (at - MID), ptab + (at - MID), c, r8);
+            return epilogue_pc_bytes16<RES>(a, c, r8, pc);
+        }
         else if constexpr (FORM == 1) return epilogue_hi16<RES>(a, g.sk, c, r8);
         else return epilogue_bytes16<RES>(a, c, r8);
     };
@@ -174,6 +183,19 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
             const int i = tid + q * 512;
             bv[q] = i < MID ? a2.bias[i] : (i < MID + C ? a3.bias[i - MID] : NEXT ? a1.bias[i - MID - C] : 0);
         }
+        [[maybe_unused]] int factor[3] = {0, 0, 0}, rescale[3] = {0, 0, 0}, position[3] = {0, 0, 0};
+        [[maybe_unused]] bool mine = true;
+        if constexpr (FORM == 2) {
+            if (g.table) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int i = tid + q * 512;
+                    if (i < MID) mine &= pc_hi_channel(a2.pc, i, false, factor[q], rescale[q], position[q]);
+                    else if (i < MID + C) mine &= pc_hi_channel(a3.pc, i - MID, has_res, factor[q], rescale[q], position[q]);
+                    else if (NEXT) mine &= pc_hi_channel(a1.pc, i - MID - C, false, factor[q], rescale[q], position[q]);
+                }
+            }
+        }
         asm volatile("" ::: "memory");
         if (g.touch) touch_weights();
         issue_patch(tile_of(blockIdx.x) * PX);
@@ -185,6 +207,21 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int q = 0; q < 3; ++q) btab[tid + q * 512] = bv[q];
+        if constexpr (FORM == 2) {
+            if (g.table) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int i = tid + q * 512;
+                    atab[i] = factor[q];
+                    if (i >= MID && i < MID + C) {
+                        ktab[i - MID] = rescale[q];
+                        ptab[i - MID] = (uint8_t)position[q];
+                    }
+                }
+                const bool all = __builtin_amdgcn_ballot_w64(!mine) == 0;
+                if (lane == 0) votes[wave] = all;
+            }
+        }
         asm volatile("" ::: "memory");
     }
 
@@ -203,6 +240,14 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
         ICNN_WAIT_VMCNT(16);                           // this wave's copies of the patch have landed: sixteen younger loads at least are the ring's
         sync();                                        // ... everybody's; and nobody reads the last tile's y any more
         if (has_res) issue_skip(p0);
+        if constexpr (FORM == 2) {
+            if (g.table) {
+                int all = 1;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) all &= votes[k];
+                one_product = __builtin_amdgcn_readfirstlane(all) != 0;
+            }
+        }
 
         // ---------------- phase 1: 3x3
 #pragma unroll
@@ -243,7 +288,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
         mfma_drain(acc);
         static_for<NP>([&](auto jc) __attribute__((always_inline)) {
             constexpr int j = decltype(jc)::value;
-            const v4i w = finish(a2, H0{}, acc[j], v4i{0, 0, 0, 0}, a2.pc + (2 * wave + half) * kPcGroupInts);
+            const v4i w = finish(a2, H0{}, acc[j], v4i{0, 0, 0, 0}, a2.pc + (2 * wave + half) * kPcGroupInts, co);
             if (32 * j + 31 < PX || 32 * j + col < PX) *(v4i *)(lds + (32 * j + col) * AP + co) = w;
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -289,7 +334,8 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
                 } else {
                     mfma_drain(c2[PAR]);
                     const int32_t *pc = a3.pc + ((ch * 8 + wave) * 2 + half) * kPcGroupInts;
-                    const v4i o = has_res ? finish(a3, H1{}, c2[PAR], r8[PAR], pc) : finish(a3, H0{}, c2[PAR], r8[PAR], pc);
+                    const int at = MID + ch * MID + co;
+                    const v4i o = has_res ? finish(a3, H1{}, c2[PAR], r8[PAR], pc, at) : finish(a3, H0{}, c2[PAR], r8[PAR], pc, at);
                     if (32 * j + 31 < PX || 32 * j + col < PX) *(v4i *)(lds + at0 + (32 * j + col) * YP + ch * MID) = o;
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -316,7 +362,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
             }
             if constexpr (FORM == 1) {
                 constexpr int PAR = (2 * NP - 1) & 1;
-                const v4i o = finish(a3, H1{}, c2[PAR], r8[PAR], nullptr);
+                const v4i o = finish(a3, H1{}, c2[PAR], r8[PAR], nullptr, 0);
                 if (32 * NP - 1 < PX || 32 * (NP - 1) + col < PX) *(v4i *)(lds + at0 + (32 * (NP - 1) + col) * YP + 3 * MID) = o;
             }
         }
@@ -355,7 +401,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
             mfma_drain(acc);
             static_for<NP>([&](auto jc) __attribute__((always_inline)) {
                 constexpr int j = decltype(jc)::value;
-                const v4i w = finish(a1, H0{}, acc[j], v4i{0, 0, 0, 0}, a1.pc + (2 * wave + half) * kPcGroupInts);
+                const v4i w = finish(a1, H0{}, acc[j], v4i{0, 0, 0, 0}, a1.pc + (2 * wave + half) * kPcGroupInts, MID + C + co);
                 const int q = 32 * j + col;
                 if (q < PX && p0 + q < a2.M) *(v4i *)((uint8_t *)a1.out + (size_t)(p0 + q) * a1.out_cs + a1.out_co + co) = w;
                 __builtin_amdgcn_sched_barrier(0);
@@ -444,11 +490,15 @@ hipError_t launch_conv_tri(const TriArgs &g, const ConvArgs &a2, const ConvArgs 
     q.sk = a3.res_mode ? make_skip_mul(a3.res_mul, a3.res_shift) : SkipMul{0, 0, 0};      // (without an operand the arithmetic runs on zeros)
     b2.div_howo = make_fast_div((unsigned)(a2.H * a2.W));
     b2.div_wo = make_fast_div((unsigned)a2.W);
+    // (the biggest tile leaves no room for the tables)
+    const size_t tables = (2 * kTriMid + 2 * kTriWide + 8) * 4 + kTriWide;
+    q.table = a3.pc && tri_lds_bytes(g) + tables <= 160 * 1024;
+    const size_t lds_bytes = tri_lds_bytes(g) + (q.table ? tables : 0);
     const int form = a3.pc ? 2 : a2.rq_fast && a3.rq_fast && (!a3.res_mode || q.sk.ok) && (!a1 || a1->rq_fast) ? 1 : 0;
     auto go = [&](auto kernel) -> hipError_t {
         const hipError_t e = allow_large_lds((const void *)kernel);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)slots), dim3(512), tri_lds_bytes(g), st, q, b2, a3, a1 ? *a1 : a2);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)slots), dim3(512), lds_bytes, st, q, b2, a3, a1 ? *a1 : a2);
         return hipGetLastError();
     };
     auto by_form = [&](auto np_tag, auto next_tag) {

@@ -154,6 +154,7 @@ struct TriArgs {
     int n_tiles, per_xcd;
     int touch;                    // the workgroups touch the launch's weights first
     unsigned res_bytes;
+    int table;                    // per channel: there is room for the tables of the one-product form
     SkipMul sk;
 };
 

@@ -165,8 +165,8 @@ class GpuNet:
 
     # By whether requantisation is per channel: below these the three layers by themselves, which spread their weights over the whole chip,
     # are level or faster (50-layer network, fused / apart: one image 232 / 231 us, three 252 / 252, four 255 / 257, nine 278 / 286, 32 449 / 476;
-    # per channel nine images 317 / 292, 16 359 / 336, 32 486 / 487, 48 638 / 645, 64 714 / 725, 76 782 / 794; with two launches side by side
-    # the layers are: 96 images 929 / 885).
+    # per channel nine images 293 / 284, 16 341 / 332, 32 475 / 475, 48 645 / 682, 64 736 / 775, 76 811 / 852; with two launches side by side
+    # the layers are level or faster: 96 images 947 / 944).
     TRIPLE_MIN_PIXELS = {False: 256, True: 6272}
 
     def _fuse_triples(self):

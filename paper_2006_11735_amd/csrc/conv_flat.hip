@@ -278,12 +278,12 @@ static bool flat_takes(const ConvArgs &a, bool direct_ok)
 // unit: 64 / 80 / 96 / 128 images of 7 x 7 (196, 248, 300, 392 workgroups) 10.4 / 8.0, 10.8 / 8.4, 14.4 / 13.7, 12.5 / 14.1: one round of them only.
 bool conv_flat_applies(const ConvArgs &a, bool direct_ok)
 {
-    if (g_tuning.flat == 2 || !flat_takes(a, direct_ok)) return false;
-    if (g_tuning.flat == 1) return true;
-    if (g_tuning.tile >= 0 || g_tuning.stages || g_tuning.ksplit || g_tuning.deep_always || g_tuning.halo_always || g_tuning.halo_tile ||
-        g_tuning.plane_always || g_tuning.lat)
-        return false;
+    if (g_tuning.flat == 2) return false;
+    if (g_tuning.flat == 1) return flat_takes(a, direct_ok);
     if ((long long)(a.Cout / 32) * ((a.M + 31) / 32) <= 256 && !g_tuning.no_lat) return false;
+    if (g_tuning.tile >= 0 || g_tuning.stages || g_tuning.ksplit || g_tuning.deep_always || g_tuning.halo_always || g_tuning.halo_tile ||
+        g_tuning.plane_always || g_tuning.lat || !flat_takes(a, direct_ok))
+        return false;
     if (a.Cin == 2048 && (long long)(a.Cout / 128) * ((a.M + 63) / 64) > 256) return false;
     return a.pc || a.res_mode != 0 || g_tuning.no_plane || !conv_plane_applies(a);
 }

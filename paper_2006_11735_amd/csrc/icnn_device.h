@@ -85,6 +85,7 @@ struct ConvArgs {
 // An unsigned 8-bit skip operand's rescale as the high word of one product: [x * mul / 2^shift] = high 32 bits of (x << 24 | rnd) * k for every
 // byte x.  (x << 24 | rnd) * (m << (8 - s)) / 2^32 = x m / 2^s + rnd * m 2^(8-s) / 2^32, and the smallest rnd that makes the second term one
 // half exceeds it by less than the 2^-s between two values of the first (m <= 2^24): the floor is that of x m / 2^s + 1/2.
+// The kernels add that word as an int32, saturating: the rescaled 255 has to be one (at s = 0 multipliers from 8421505 on are not).
 // All zero: adds nothing (no skip operand).  ok = 0: the pair does not fit.
 struct SkipMul {
     int ok;
@@ -94,7 +95,7 @@ static inline SkipMul make_skip_mul(long long mul, int shift)
 {
     SkipMul r = {0, 0, 0};
     while (shift > 8 && mul != 0 && (mul & 1) == 0) { mul /= 2; --shift; }
-    if (mul < 1 || mul > (1 << 24) || shift < 0 || shift > 8) return r;
+    if (mul < 1 || mul > (1 << 24) || shift < 0 || shift > 8 || (255 * mul + ((1LL << shift) >> 1)) >> shift > 0x7fffffffLL) return r;
     const long long k = mul << (8 - shift), rnd = shift == 0 ? 0 : ((1LL << 31) + k - 1) / k;
     if (k > 0xffffffffLL || rnd >= (1 << 24)) return r;
     r.ok = 1; r.k = (uint32_t)k; r.rnd = (uint32_t)rnd;

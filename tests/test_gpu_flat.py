@@ -109,6 +109,17 @@ def test_per_channel_products(flat, shape, odd):
     check(x, wt, b, mul_c=pc["mul_c"], shift_c=pc["shift_c"])
 
 
+# rescales of the skip operand's 255 on both sides of int32, by the library's own choice of kernel.  The output's ratio is 2^-24, so that a
+# sum's top bits are what is stored; (255 * 16777215 / 2 is an int32, twice that is not)
+@pytest.mark.parametrize("rescale", [(8421504, 0), (8421505, 0), (10000000, 0), (16777215, 0), (16777215, 1), (2**31 - 1, 0)], ids=str)
+@pytest.mark.parametrize("shape", [(1, 46, 46, 128, 128, 1), (1, 70, 60, 64, 64, 3), (1, 46, 46, 128, 128, 3)], ids=lambda s: "x".join(map(str, s)))
+def test_skip_rescales_at_the_end_of_int32(shape, rescale):
+    g, x, wt, b = layer(13, *shape)
+    res = g.integers(0, 256, size=shape[:3] + shape[4:5], dtype=np.uint8)
+    res[0, 5:9] = 255
+    check(x, wt, b, res=res, res_mode="pre", res_mul=rescale[0], res_shift=rescale[1], mul=1, shift=24)
+
+
 @pytest.mark.parametrize("shape", [(6, 14, 14, 256, 256, 3), (5, 14, 14, 256, 256, 3), (17, 7, 7, 512, 512, 3), (3, 28, 28, 128, 128, 3), (2, 28, 28, 512, 128, 1),
                                    (9, 14, 14, 1024, 256, 1), (2, 56, 56, 64, 64, 3), (2, 30, 30, 256, 1024, 1), (16, 7, 7, 2048, 512, 1), (90, 7, 7, 2048, 512, 1)], ids=lambda s: "x".join(map(str, s)))
 def test_the_librarys_choice(shape):

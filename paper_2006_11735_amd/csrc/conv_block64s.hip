@@ -148,17 +148,19 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const BlockArgs g
         const int ty = in[j] ? (int)(((unsigned)q * g.inv_tw) >> 16) : 0;
         prow[j] = (ty + 1) * g.PW + (in[j] ? q - ty * g.TW : 0) + 1;
     }
-    // where this lane's pieces of y lie: four pixels' whole rows per store
-    int s_lds[4], s_out[4];
+    // where this lane's pieces of y lie: four pixels' whole rows per store (slots beyond the tile: nowhere, whatever the picture's height)
+    int s_lds[4];
+    unsigned s_out[4];
     short s_y[4], s_x[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         const int q = (wave + 4 * c) * 4 + (lane >> 4);
-        const int ty = (int)(((unsigned)q * g.inv_tw) >> 16), tx = q - ty * g.TW;
+        const bool slot = q < g.TH * g.TW;
+        const int ty = slot ? (int)(((unsigned)q * g.inv_tw) >> 16) : 0, tx = slot ? q - ty * g.TW : 0;
         s_lds[c] = ((ty + 1) * g.PW + tx + 1) * XP + (lane & 15) * 16;
-        s_y[c] = (short)(q < g.TH * g.TW ? ty : 0x4000);
+        s_y[c] = (short)ty;
         s_x[c] = (short)tx;
-        s_out[c] = (ty * g.W + tx) * a3.out_cs + (lane & 15) * 16;
+        s_out[c] = slot ? (unsigned)((ty * g.W + tx) * a3.out_cs + (lane & 15) * 16) : OOB;
     }
 
     int buf = 0;
@@ -270,7 +272,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const BlockArgs g
         for (int c = 0; c < 4; ++c) {
             const v4i o = *(const v4i *)(xb + s_lds[c]);
             const bool ok = y0 + s_y[c] < g.H && x0 + s_x[c] < g.W;
-            __builtin_amdgcn_raw_buffer_store_b128(o, rs_y, ok ? (unsigned)s_out[c] : OOB, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b128(o, rs_y, ok ? s_out[c] : OOB, 0, 0);
         }
     }
     }

@@ -13,6 +13,12 @@ def test_tiles(shape):
     assert (got == want).all(), "%d of %d bytes differ" % (int((got != want).sum()), want.size)
 
 
+def test_a_picture_taller_than_16384_rows():
+    # tiles of 8 x 7 = 56 of 64 pixel slots: the other eight belong to nobody, at any height
+    got, want = run_block(3, 1, 16500, 7, 256, 64)
+    assert (got == want).all(), "%d of %d bytes differ" % (int((got != want).sum()), want.size)
+
+
 @pytest.mark.parametrize("kw", [dict(skip=None), dict(skip="s32"), dict(c3_mode="linear_s8", skip=None), dict(c3_mode="raw_s32"), dict(forms=("hi", "hi")),
                                 dict(forms=("wide", "hi")), dict(bound12=15), dict(cbuf=320)], ids=str)
 def test_output_and_skip_modes(kw):

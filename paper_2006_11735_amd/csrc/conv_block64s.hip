@@ -280,12 +280,23 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const BlockArgs g
 }
 
 // ------------------------------------------------------------------ dispatch
+// The stores' offsets from a tile's first pixel are 32 bits, up to the descriptor's 0x7fffff00 bytes.  A tile has at most 64 rows: the
+// tile itself is asked for only where that many could pass it (at a pitch of 256 pictures from 133000 columns on).
+static bool block64s_stores_fit(const BlockArgs &g, const ConvArgs &a3)
+{
+    const long long limit = 0x7fffff00LL - kB64sWide;
+    if (((kB64sPix - 1LL) * g.W + kB64sPix) * a3.out_cs <= limit) return true;
+    BlockArgs t = g;
+    return conv_block_tile(g.H, g.W, kB64sPix, kB64sRows, t) && ((t.TH - 1LL) * g.W + t.TW - 1) * a3.out_cs <= limit;
+}
+
 // 256 -> 64 -> 64 -> 256 channels, per-layer requantisation, an 8-bit output, the block input itself as skip operand (unsigned 8-bit, joined
 // before requantisation) or none
 bool conv_block64s_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3)
 {
     if (a1.Cin != kB64sWide || a1.Cout != kB64sMid || a3.Cout != kB64sWide || a3.pc) return false;
     if (a3.out_mode == 3 || !a3.epi_vec || a3.epi_mode / 4 == 2 || !a1.rq_fast || !a2.rq_fast || !a3.rq_fast) return false;
+    if (!block64s_stores_fit(g, a3)) return false;
     if (a3.res_mode == 0) return true;
     return (const uint8_t *)a3.res == g.x && a3.res_cs == g.x_cs && make_skip_mul(a3.res_mul, a3.res_shift).ok;
 }

@@ -15,9 +15,10 @@ def rnd(seed):
     return np.random.default_rng(seed)
 
 
-def run_block(seed, n, h, w, c, mid, *, skip="x", c3_mode="brelu", forms=("auto", "auto"), bound12=127, cbuf=None):
+def run_block(seed, n, h, w, c, mid, *, skip="x", c3_mode="brelu", forms=("auto", "auto"), bound12=127, cbuf=None, pitch=None):
     """Returns (gpu output, oracle output).  forms: how the first two layers requantise: "auto" = calibrated
-    15-bit multiplier (the 32-bit form), "hi" = a pair only the one-multiply form takes, "wide" = only the general form."""
+    15-bit multiplier (the 32-bit form), "hi" = a pair only the one-multiply form takes, "wide" = only the general form.
+    pitch: channels from one output pixel to the next (default: c)."""
     from gpu_util import dev
     from paper_2006_11735_amd import binding as B
     g = rnd(seed)
@@ -64,7 +65,7 @@ def run_block(seed, n, h, w, c, mid, *, skip="x", c3_mode="brelu", forms=("auto"
     d1 = B.conv_desc(n=n, h=h, w=w, cin=c, in_c_stride=cbuf, cout=mid, kh=1, kw=1, out_c_stride=mid, mul=m1, shift=s1, bound_q=bound12)
     d2 = B.conv_desc(n=n, h=h, w=w, cin=mid, in_c_stride=mid, cout=mid, kh=3, kw=3, pad_h=1, pad_w=1, out_c_stride=mid, mul=m2,
                      shift=s2, bound_q=bound12)
-    d3 = B.conv_desc(n=n, h=h, w=w, cin=mid, in_c_stride=mid, cout=c, kh=1, kw=1, out_c_stride=c, mul=m3, shift=s3, bound_q=127,
+    d3 = B.conv_desc(n=n, h=h, w=w, cin=mid, in_c_stride=mid, cout=c, kh=1, kw=1, out_c_stride=pitch or c, mul=m3, shift=s3, bound_q=127,
                      out_mode=om)
     if res is not None:
         d3.res_mode, d3.res_c_stride = B.ICNN_RES_PRE, c
@@ -76,12 +77,12 @@ def run_block(seed, n, h, w, c, mid, *, skip="x", c3_mode="brelu", forms=("auto"
         B.iconv2d_prepack_weights(d, dev(wt), pk)
         packs.append(pk)
     tdt = {np.dtype(np.uint8): torch.uint8, np.dtype(np.int8): torch.int8, np.dtype(np.int32): torch.int32}[want.dtype]
-    y = torch.zeros(want.shape, dtype=tdt, device="cuda:0")
+    y = torch.zeros((n, h, w, pitch or c), dtype=tdt, device="cuda:0")
     xd = dev(x)
     rd = None if res is None else (dev(res) if (skip != "x" or cbuf != c) else xd)
     B.iconv2d_bottleneck_brelu(d1, xd, packs[0], dev(b1), d2, packs[1], dev(b2), d3, packs[2], dev(b3), rd, y)
     torch.cuda.synchronize()
-    return y.cpu().numpy(), want
+    return y[..., :c].cpu().numpy(), want
 
 
 BLOCKS = [

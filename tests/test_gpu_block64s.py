@@ -19,6 +19,13 @@ def test_a_picture_taller_than_16384_rows():
     assert (got == want).all(), "%d of %d bytes differ" % (int((got != want).sum()), want.size)
 
 
+# tiles of 4 x 14: first and last pixel 253 apart, 2 GiB at 8.49 million channels from pixel to pixel; on either side of it
+@pytest.mark.parametrize("pitch", [8488064, 8488080, 9437184])
+def test_a_tile_over_two_gib_of_output(pitch):
+    got, want = run_block(4, 1, 4, 80, 256, 64, pitch=pitch)
+    assert (got == want).all(), "%d of %d bytes differ" % (int((got != want).sum()), want.size)
+
+
 @pytest.mark.parametrize("kw", [dict(skip=None), dict(skip="s32"), dict(c3_mode="linear_s8", skip=None), dict(c3_mode="raw_s32"), dict(forms=("hi", "hi")),
                                 dict(forms=("wide", "hi")), dict(bound12=15), dict(cbuf=320)], ids=str)
 def test_output_and_skip_modes(kw):

@@ -1,5 +1,5 @@
 // The two-branch layer of the restoration network on large pictures: a 5x5 layer of 64 channels and, in the same launch, the 3x3 layer
-// of the same input (at most 32 output channels each, stride 1, "same" padding, bytes by one product each).
+// of the same input (at most 32 output channels each, stride 1, "same" padding, unsigned bytes by one 32-bit or 24-bit product each).
 //
 // conv_plane.hip runs it with two waves per SIMD that own two tile rows each: 51 % of the matrix cores' rate, because every
 // product needs a fresh fragment from LDS (1.34 MB per tile, 7.5 k clocks of LDS against 8.7 k of matrix work), and because the barrier
@@ -45,9 +45,11 @@ struct RowsProducts {
 };
 static_assert(RowsProducts<false>::ALL == 4 * (50 + 18) && RowsProducts<true>::ALL == 4 * 50 + 2 * 24, "products of four rows");
 
-// Both layers requantise by a product's high word (ConvArgs::rq_fast).  PAIR: the twin has 16 channels; an accumulator tile of it holds two
+// FORM: both layers requantise by that form of requant16: 1 a product's high word (ConvArgs::rq_fast); 3 or 4 where that does not apply to both, at ratios
+// of one half and more or a shift of 33 (2560 x 1600, 64 -> 32 + 16, one layer by itself: ratio 1 235 us here, 267 with two-dimensional tiles; shift 33
+// 234 and 288; 238 in form 1).  PAIR: the twin has 16 channels; an accumulator tile of it holds two
 // output rows, the second in the lanes and weight rows that the channels 16 to 31 would have: 248 products of four rows instead of 272.
-template <bool PAIR>
+template <bool PAIR, int FORM>
 __global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a, const ConvArgs b, const TileWalk g)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the buffer-resource type exists in the device pass only
@@ -151,7 +153,9 @@ __global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a
                     constexpr int o = (LO + decltype(q_tag)::value) * 2, k = o % 16, group = Products::EACH + 1, u = o / 16 / group, t = o / 16 % group;
                     constexpr bool twin = t == Products::EACH;
                     constexpr int j = twin ? u : u * Products::EACH + t;
-                    epilogue_hi_slice<0, k, 2>(twin ? b : a, SkipMul{0, 0, 0}, twin ? oldB[twin ? j : 0] : old[twin ? 0 : j], v4i{0, 0, 0, 0}, wd);
+                    const v16i &sums = twin ? oldB[twin ? j : 0] : old[twin ? 0 : j];
+                    if constexpr (FORM == 1) epilogue_hi_slice<0, k, 2>(twin ? b : a, SkipMul{0, 0, 0}, sums, v4i{0, 0, 0, 0}, wd);
+                    else epilogue_rq24_slice<0, k, 2, FORM>(twin ? b : a, sums, v4i{0, 0, 0, 0}, wd);
                     if constexpr (k == 14) {
                         const ConvArgs &c = twin ? b : a;
                         const int row = PAIR && twin ? 2 * j + half : j, co = PAIR && twin ? 0 : half * 16;
@@ -204,13 +208,13 @@ __global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a
         static_for<RPW>([&](auto j_tag) {
             constexpr int j = decltype(j_tag)::value;
             if (j >= was.rows || !storeA) return;
-            *(v4i *)((uint8_t *)a.out + (size_t)(was.pix + j * a.W) * a.out_cs + a.out_co + half * 16) = epilogue_bytes16<0, 1>(a, acc[j], v4i{0, 0, 0, 0});
+            *(v4i *)((uint8_t *)a.out + (size_t)(was.pix + j * a.W) * a.out_cs + a.out_co + half * 16) = epilogue_bytes16<0, FORM>(a, acc[j], v4i{0, 0, 0, 0});
         });
         static_for<UNITS>([&](auto j_tag) {
             constexpr int j = decltype(j_tag)::value;
             const int row = PAIR ? 2 * j + half : j;
             if (row >= was.rows || !storeB) return;
-            *(v4i *)((uint8_t *)b.out + (size_t)(was.pix + row * a.W) * b.out_cs + b.out_co + (PAIR ? 0 : half * 16)) = epilogue_bytes16<0, 1>(b, accB[j], v4i{0, 0, 0, 0});
+            *(v4i *)((uint8_t *)b.out + (size_t)(was.pix + row * a.W) * b.out_cs + b.out_co + (PAIR ? 0 : half * 16)) = epilogue_bytes16<0, FORM>(b, accB[j], v4i{0, 0, 0, 0});
         });
     };
 
@@ -237,11 +241,16 @@ __global__ __launch_bounds__(256, 1) void conv_rows_twin_kernel(const ConvArgs a
 // what the kernel assumes of a layer beyond its shape (conv_plane_twin_ok)
 static bool rows_layer_ok(const ConvArgs &a)
 {
-    return a.rq_fast && a.epi_vec && a.out_mode <= 1 && a.res_mode == 0 && (a.Cout & 15) == 0 && a.Cout <= 32;
+    return a.epi_vec && a.out_mode <= 1 && a.res_mode == 0 && (a.Cout & 15) == 0 && a.Cout <= 32;
+}
+// the cheapest form of the kernel that both layers' parameters allow; 0: none
+static int rows_form(const ConvArgs &a, const ConvArgs &b)
+{
+    return a.rq_fast && b.rq_fast ? 1 : a.rq24 && b.rq24 ? 3 : a.rqh && b.rqh ? 4 : 0;
 }
 bool conv_rows_twin_applies(const ConvArgs &a, const ConvArgs &b)
 {
-    return a.KH == 5 && a.Cin == 64 && rows_layer_ok(a) && rows_layer_ok(b) && !g_tuning.plane_no_pipe;
+    return a.KH == 5 && a.Cin == 64 && rows_layer_ok(a) && rows_layer_ok(b) && rows_form(a, b) != 0 && !g_tuning.plane_no_pipe;
 }
 
 hipError_t launch_conv_rows_twin(const ConvArgs &a, const ConvArgs &b, hipStream_t st)
@@ -249,11 +258,19 @@ hipError_t launch_conv_rows_twin(const ConvArgs &a, const ConvArgs &b, hipStream
     TileWalk g;
     if (!tile_walk(g, a.N, a.H, a.W, kRowsTH, kRowsTW)) return hipErrorInvalidValue;
     constexpr size_t lds_bytes = (50 + 18) * 1024 + 2 * (size_t)TilePatch<5, 64, kRowsTH, kRowsTW, 4>::BYTES;
-    const auto kernel = b.Cout == 16 ? conv_rows_twin_kernel<true> : conv_rows_twin_kernel<false>;
-    const hipError_t e = allow_large_lds((const void *)kernel);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * g.per_xcd < 256 ? 8 * g.per_xcd : 256)), dim3(256), lds_bytes, st, a, b, g);
-    return hipGetLastError();
+    auto go = [&](auto kernel) -> hipError_t {
+        const hipError_t e = allow_large_lds((const void *)kernel);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * g.per_xcd < 256 ? 8 * g.per_xcd : 256)), dim3(256), lds_bytes, st, a, b, g);
+        return hipGetLastError();
+    };
+    const bool pair = b.Cout == 16;
+    switch (rows_form(a, b)) {
+    case 1: return pair ? go(conv_rows_twin_kernel<true, 1>) : go(conv_rows_twin_kernel<false, 1>);
+    case 3: return pair ? go(conv_rows_twin_kernel<true, 3>) : go(conv_rows_twin_kernel<false, 3>);
+    case 4: return pair ? go(conv_rows_twin_kernel<true, 4>) : go(conv_rows_twin_kernel<false, 4>);
+    default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace icnn

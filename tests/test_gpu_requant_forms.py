@@ -59,8 +59,10 @@ PRODUCT = [(32767, 23, 127), (16385, 23, 255), (16385, 20, 127), (3, 1, 255), (3
 
 
 @pytest.mark.parametrize("a, b", [(p, q) for form in (HIGH_HALF, PRODUCT) for p, q in zip(form, form[1:] + form[:1])], ids=str)
-def test_two_branch_forms(a, b):
-    # a 5x5 layer of 32 channels beside a 3x3 layer of 16: both forms of conv_rows_twin_kernel, each branch with parameters of its own
+@pytest.mark.parametrize("cout_b", [16, 32])
+def test_two_branch_forms(a, b, cout_b):
+    # a 5x5 layer of 32 channels beside a 3x3 layer of 16 (two output rows to an accumulator) or 32, each branch with parameters of its own:
+    # conv_rows_twin_kernel in these two forms where a branch's shift is 33 or its ratio one half and more, with one wide product elsewhere
     from gpu_util import dev
     from paper_2006_11735_amd import binding as B
     high = [mul << (33 - shift) < 1 << 24 for mul, shift, _ in (a, b)]
@@ -71,8 +73,8 @@ def test_two_branch_forms(a, b):
     steps = [rounding_accumulators(*p) for p in (a, b)]
     x = torch.zeros((1, h, w, 64), dtype=torch.uint8, device="cuda:0")
     rng = np.random.default_rng(1)
-    couts, ks, offs = (32, 16), (5, 3), (0, 32)
-    descs = [B.conv_desc(n=1, h=h, w=w, cin=64, in_c_stride=64, cout=c, kh=k, kw=k, pad_h=k // 2, pad_w=k // 2, out_c_stride=48, out_c_offset=o,
+    couts, ks, offs = (32, cout_b), (5, 3), (0, 32)
+    descs = [B.conv_desc(n=1, h=h, w=w, cin=64, in_c_stride=64, cout=c, kh=k, kw=k, pad_h=k // 2, pad_w=k // 2, out_c_stride=32 + cout_b, out_c_offset=o,
                          mul=p[0], shift=p[1], bound_q=p[2]) for p, c, k, o in zip((a, b), couts, ks, offs)]
     packs = []
     for d in descs:
@@ -80,7 +82,7 @@ def test_two_branch_forms(a, b):
         B.iconv2d_prepack_weights(d, dev(rng.integers(-127, 128, size=(d.cout, d.kh, d.kw, 64), dtype=np.int8)), packs[-1])
     for at in range(0, max(-(-len(s) // c) for s, c in zip(steps, couts))):
         bias = [np.array([s[(at * c + i) % len(s)] for i in range(c)], dtype=np.int32) for s, c in zip(steps, couts)]
-        y = torch.full((1, h, w, 48), 99, dtype=torch.uint8, device="cuda:0")
+        y = torch.full((1, h, w, 32 + cout_b), 99, dtype=torch.uint8, device="cuda:0")
         B.iconv2d_twin_brelu(descs[0], x, packs[0], dev(bias[0]), y, descs[1], packs[1], dev(bias[1]), y)
         torch.cuda.synchronize()
         want = np.array([exact(t, *p) for p, v in zip((a, b), bias) for t in v], dtype=np.uint8)

@@ -22,7 +22,7 @@ class Layer:
         # a ratio per channel that leaves most results inside the clamp: 127 / (about three standard deviations of the sums)
         ratio = gain * 127.0 / (3 * 73 * 64 * np.sqrt(cin * k * k)) * g.uniform(0.5, 2.0, size=cout)
         shift = g.integers(22, 27, size=cout)
-        if form != "plain":                          # shifts beyond 32 and, now and then, a ratio above one half
+        if form in FORMS[1:]:                        # shifts beyond 32 and, now and then, a ratio above one half
             shift = np.where(np.arange(cout) % 3 == 0, g.integers(33, 40, size=cout), shift)
             ratio = np.where(np.arange(cout) % 17 == 5, 1.5, ratio)
         mul = np.clip(np.round(ratio * 2.0 ** shift), 1, 2 ** 31 - 1)
@@ -34,7 +34,18 @@ class Layer:
             if skip != "u8":
                 rs = rs + 10
             arrs += [np.minimum(np.round(rr * 2.0 ** rs), 2 ** 31 - 1), rs]
+            if form not in FORMS and skip == "u8":   # rescales that are one product each: shifts 0 to 30, the largest multipliers among them
+                rs = g.integers(0, 31, size=cout)
+                top = (2 ** 31 - 1 - ((1 << rs) >> 1)) // 255
+                arrs[2:] = [np.where(np.arange(cout) % 5 == 0, top, np.minimum(np.round(rr * 2.0 ** rs), top)), rs]
             self.d.res_mul, self.d.res_shift = (1, 0) if skip == "u8" else (3, 1)
+        at = cout - 7                                # one channel of the last group, or none, that is not one product
+        if form == "one factor":
+            arrs[1][at] = 33
+        elif form == "one shift" and skip == "u8":
+            arrs[3][at] = 31
+        elif form == "one multiplier" and skip == "u8":
+            arrs[2][at] = 2 ** 31 - 1
         self.pc = torch.zeros(B.iconv2d_packed_channel_params_bytes(self.d), dtype=torch.uint8, device="cuda:0")
         keep = [dev(a.astype(np.int32)) for a in arrs]
         B.iconv2d_prepack_channel_params(self.d, B.channel_params(*keep), self.pc)
@@ -67,6 +78,13 @@ def test_bottleneck_block(shape, form):
         B.iconv2d_bottleneck_brelu_pc(l1.d, x, l1.wp, l1.bias, l1.pc, l2.d, l2.wp, l2.bias, l2.pc, l3.d, l3.wp, l3.bias, l3.pc, res, got)
         assert torch.equal(got, want), (skip, int((got != want).sum()))
         assert 3 < len(torch.unique(want))
+
+
+# one product per output with the skip operand, in the waves all of whose channels allow it: all of them, all but the last group's
+@pytest.mark.parametrize("form", ["products", "one factor", "one shift", "one multiplier"])
+@pytest.mark.parametrize("shape", [(1, 17, 23, 256), (1, 9, 14, 128), (2, 5, 6, 64)], ids=lambda s: "x".join(map(str, s)))
+def test_bottleneck_block_with_a_channel_of_another_form(shape, form):
+    test_bottleneck_block(shape, form)
 
 
 @pytest.mark.parametrize("form", FORMS)

@@ -189,6 +189,22 @@ def csrc_digest():
     return h.hexdigest()[:16]
 
 
+def summary_stamp(summary):
+    """Hash of a byte-counter summary's own fields: it no longer matches where a field was changed afterwards, the digest among them."""
+    fields = {k: v for k, v in summary.items() if k != "stamp"}
+    return hashlib.sha256(json.dumps(fields, sort_keys=True).encode()).hexdigest()[:16]
+
+
+def byte_counters(path):
+    """(HBM bytes per conv launch of a rocprofv3 --pmc summary, whether they belong to other kernel sources than these); (None, None) without one."""
+    if not os.path.exists(path):
+        return None, None
+    with open(path) as f:
+        summary = json.load(f)
+    own = summary.get("stamp") == summary_stamp(summary) and summary.get("csrc_digest") == csrc_digest()
+    return summary.get("conv_hbm_bytes_per_launch"), not own
+
+
 def _time_us(torch, fns, reps=20):
     """Average duration of a call.  fns: one callable, or several that are called in turn (the same kernel on
     different buffers, so that no call finds its operands in the 256 MB last-level cache)."""
@@ -344,8 +360,10 @@ def summarise_pmc(config, fetch_csv, write_csv):
            "fetch_size_scale": scale["fetch"], "write_size_scale": scale["write"], "csrc_digest": csrc_digest(),
            "kernels_kib_per_dispatch": {k: [len(f[k]), sum(f[k]) / len(f[k]), sum(w.get(k, [0])) / max(1, len(w.get(k, [0])))]
                                         for k in sorted(f) if f[k] and any(t in k for t in ("conv_", "pool", "pad_", "stream_copy"))}}
+    out["stamp"] = summary_stamp(out)
     path = os.path.join(ROOT, "profiles", "traffic_%s.json" % config)
-    json.dump(out, open(path, "w"), indent=1)
+    with open(path, "w") as file:
+        json.dump(out, file, indent=1)
     print(json.dumps(out, indent=1))
     print("written", path)
 
@@ -550,14 +568,10 @@ def main():
     log("conv launches: %d, %.3f ms per step (events, excess %.2f us/launch removed; launches in a row %.3f ms, whole step %.3f ms wall), %.1f TOP/s" % (
         n_conv, conv_ms, excess * 1e3, serial_ms, ms_per_step, conv_tops))
 
-    traffic, traffic_stale = None, None
     tpath = os.path.join(ROOT, "profiles", "traffic_%s.json" % args.config)
-    if os.path.exists(tpath):          # HBM bytes per conv launch from the committed rocprofv3 --pmc summary
-        tj = json.load(open(tpath))
-        traffic = tj.get("conv_hbm_bytes_per_launch")
-        traffic_stale = tj.get("csrc_digest") != csrc_digest()     # counters were taken on other kernel sources
-        if traffic_stale:
-            log("note: %s was measured on other kernel sources than this build (traffic_stale)" % tpath)
+    traffic, traffic_stale = byte_counters(tpath)      # from the committed rocprofv3 --pmc summary
+    if traffic_stale:
+        log("note: %s was measured on other kernel sources than this build (traffic_stale)" % tpath)
 
     peak_tops, copy_gbs = measured_peaks(torch)
 

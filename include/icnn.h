@@ -372,7 +372,7 @@ int iconv2d_pair_brelu_pc(const icnn_conv_desc *c3, const void *t, const void *w
  *     iconv2d_brelu(c1, y,  w1_packed, bias1, NULL, z,  ...);     // 1x1, stride 1, no padding
  * c1 = NULL leaves the last layer away (w1_packed, bias1 and z are then not read); t2 = NULL leaves the middle tensor unwritten (c3's
  * in_c_stride and, with c1, c1's are not used).  lanes (at least 1): how many such launches the program runs side by side (the parts of a
- * batch); it changes the launch's shape, never a result.  Shapes it takes: 256 -> 256 -> 1024 (-> 256) channels, images up to 196 pixels wide; c2 and, with c1, c3 store unsigned bytes bounded by
+ * batch); it changes the launch's shape, never a result.  Shapes it takes: 256 -> 256 -> 1024 (-> 256) channels, images up to 210 pixels wide; c2 and, with c1, c3 store unsigned bytes bounded by
  * at most 127 from a lower clamp of 0, c3 without c1 any unsigned bytes; c1 likewise; c3 takes no skip operand or an unsigned 8-bit one
  * joined before requantisation whose rescale fits 32 bits, c2 and c1 none; inputs ICNN_IN_U8_LE127; tensors, bias arrays and pitches
  * 16-byte aligned, tensors below 2 GiB; no output overlaps t, another output, or res (y may be res itself).  Anything else returns

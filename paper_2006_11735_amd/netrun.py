@@ -171,8 +171,7 @@ class GpuNet:
 
     def _fuse_triples(self):
         """A block's 3x3 convolution, the 1x1 convolution that closes the block and, where it follows, the 1x1 convolution that opens the
-        next one: one iconv2d_triple_brelu launch where the library accepts it.  All three outputs are written (the 3x3 layer's too: its
-        buffer has other readers, or somebody looks at it)."""
+        next one: one iconv2d_triple_brelu launch where the library accepts it.  All three outputs are written, the 3x3 layer's too."""
         steps, i = [], 0
         while i < len(self.steps):
             run = self.steps[i:i + 3]
@@ -208,6 +207,8 @@ class GpuNet:
             i += 1
         self.steps = steps
 
+    # What the three-layer launches and the blocks leave: per channel the 256 -> 1024 -> 256 boundaries of a batch in two halves, per layer those whose
+    # 3x3 layer _fuse_triples does not take (no stored network has one).  The figures are those of the 50-layer network without these launches.
     # The fused pair streams both layers' weights through every workgroup's 64-pixel tile: it wins where the tiles
     # fit the chip in about one round and the wide tensor is at most 1024 channels (measured at batch 64: 17.6 us
     # against 23.8 us for 12544 pixels of 256 -> 1024 -> 256; level at 50176 pixels of 128 -> 512 -> 128; a loss,

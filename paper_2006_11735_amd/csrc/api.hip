@@ -177,7 +177,7 @@ int icnn_set_tuning(const char *name, int32_t value)
     struct Entry { const char *name; int Tuning::*field; int lo, hi; };
     static const Entry table[] = {
         {"tile", &Tuning::tile, -1, 4},         {"stages", &Tuning::stages, 0, 6},
-        {"no_narrow", &Tuning::no_narrow, 0, 1}, {"lat", &Tuning::lat, 0, 1}, {"no_lat", &Tuning::no_lat, 0, 1}, {"no_fc", &Tuning::no_fc, 0, 1},
+        {"no_narrow", &Tuning::no_narrow, 0, 1}, {"lat", &Tuning::lat, 0, 4}, {"no_lat", &Tuning::no_lat, 0, 1}, {"no_fc", &Tuning::no_fc, 0, 1},
         {"no_halo", &Tuning::no_halo, 0, 1},     {"halo_tile", &Tuning::halo_tile, 0, 2},
         {"halo_always", &Tuning::halo_always, 0, 1}, {"no_stream", &Tuning::no_stream, 0, 1},
         {"ksplit", &Tuning::ksplit, 0, 8}, {"no_block64", &Tuning::no_block64, 0, 1}, {"no_block128", &Tuning::no_block128, 0, 1}, {"no_block64s", &Tuning::no_block64s, 0, 1},
@@ -871,6 +871,10 @@ int iconv2d_pair_brelu_pc(const icnn_conv_desc *c3, const void *t, const void *w
     return pair_layers(c3, t, w3_packed, bias3, pc3_packed, res, y, c1, w1_packed, bias1, pc1_packed, z, stream, "iconv2d_pair_brelu_pc");
 }
 
+// Below this many pixels a run of three layers is three launches of layers that spread their weights over the whole chip (50-layer network, its five runs
+// in one launch each / apart, us: two images 202 / 183, four 219 / 213, five 223 / 220, six = 1176 pixels 240 / 241, nine 247 / 253).
+constexpr long long kTriMinPixels = 1176;
+
 static int triple_layers(const icnn_conv_desc *c2, const void *t, const void *w2_packed, const int32_t *bias2, const void *pc2, void *t2,
                          const icnn_conv_desc *c3, const void *w3_packed, const int32_t *bias3, const void *pc3, const void *res, void *y,
                          const icnn_conv_desc *c1, const void *w1_packed, const int32_t *bias1, const void *pc1, void *z, int32_t lanes,
@@ -912,6 +916,7 @@ static int triple_layers(const icnn_conv_desc *c2, const void *t, const void *w2
         return fail(ICNN_E_UNSUPPORTED, "fused run takes an unsigned 8-bit skip operand joined before requantisation");
     if (!t2) a2.out = nullptr;
     const bool skip = c3->res_mode != ICNN_RES_NONE;
+    bool in_place = false;
     // (pixel indices and the copies' byte offsets are 32 bits)
     const unsigned long long res_bytes = skip ? (unsigned long long)(g3.M - 1) * c3->res_c_stride + c3->cout : 0;
     if (a2.x_bytes >= 0x7fffff00u || res_bytes >= 0x7fffff00ull || g2.M > 0x7fffffffLL)
@@ -928,11 +933,21 @@ static int triple_layers(const icnn_conv_desc *c2, const void *t, const void *w2
             clash = clash || overlap(out[i], in[0]) || (i + 1 == n && skip ? overlap_beyond_pixels(out[i], y, in[1], res) : overlap(out[i], in[1]));
             for (int j = 0; j < i; ++j) clash = clash || overlap(out[i], out[j]);
         }
+        in_place = skip && overlap(out[n - 1], in[1]);
         if (clash) return fail(ICNN_E_UNSUPPORTED, "the outputs of a fused run must not overlap each other or its inputs");
     }
     TriArgs q = {};
     if (!conv_tri_plan(g2.M, c2->w, lanes, q)) return fail(ICNN_E_UNSUPPORTED, "the image is too wide for a tile's patch");
     q.res_bytes = (unsigned)res_bytes;
+    // (layers by themselves read what the one before has stored: where it stands as they have it)
+    const bool chained = c2->out_c_offset == 0 && c3->in_c_stride == c2->out_c_stride && (!c1 || (c3->out_c_offset == 0 && c1->in_c_stride == c3->out_c_stride));
+    if (g2.M < kTriMinPixels && t2 && !pc2 && !in_place && chained && !g_tuning.tri_tile) {
+        if ((rc = fill_conv_args(c3, g3, t2, w3_packed, bias3, res, y, a3))) return rc;
+        hipError_t e = launch_conv(a2, true, true, (hipStream_t)stream);
+        if (e == hipSuccess) e = launch_conv(a3, true, true, (hipStream_t)stream);
+        if (e == hipSuccess && c1) e = launch_conv(a1, true, true, (hipStream_t)stream);
+        return launched(e, what);
+    }
     return launched(launch_conv_tri(q, a2, a3, c1 ? &a1 : nullptr, (hipStream_t)stream), what);
 }
 

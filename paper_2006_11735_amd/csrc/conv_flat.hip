@@ -280,7 +280,7 @@ bool conv_flat_applies(const ConvArgs &a, bool direct_ok)
 {
     if (g_tuning.flat == 2) return false;
     if (g_tuning.flat == 1) return flat_takes(a, direct_ok);
-    if ((long long)(a.Cout / 32) * ((a.M + 31) / 32) <= 256 && !g_tuning.no_lat) return false;
+    if (conv_lat_before_flat(a)) return false;
     if (g_tuning.tile >= 0 || g_tuning.stages || g_tuning.ksplit || g_tuning.deep_always || g_tuning.halo_always || g_tuning.halo_tile ||
         g_tuning.plane_always || g_tuning.lat || !flat_takes(a, direct_ok))
         return false;

@@ -219,7 +219,7 @@ struct Tuning {
     int tile = -1;         // force tile shape 0..4 of the direct-to-LDS kernel (also keeps 3x3 layers off the patch kernel)
     int stages = 0;        // force the LDS ring depth of the direct-to-LDS kernel (2..6)
     int no_narrow = 0;     // keep one-to-four-channel layers on the tile kernels
-    int lat = 0;           // few-pixel kernel for every layer whose shape it accepts
+    int lat = 0;           // few-pixel kernel for every layer whose shape it accepts; 2, 3, 4: with tiles of 16 x 16, 32 x 16, 32 x 32
     int no_lat = 0;        // keep layers on few pixels off the kernel whose waves split the K axis straight from global memory
     int no_fc = 0;         // the same for the classifier's kind of layer only: pointwise on at most 64 pixels with K >= 512
     int no_halo = 0;       // keep 3x3 layers on the tap-by-tap kernel
@@ -251,6 +251,7 @@ size_t conv_split_bytes(const ConvArgs &a, bool direct_ok);
 hipError_t launch_conv_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st);
 hipError_t allow_large_lds(const void *kernel);   // > 64 KiB of dynamic LDS, once per kernel function
 bool conv_lat_applies(const ConvArgs &a);
+bool conv_lat_before_flat(const ConvArgs &a);
 hipError_t launch_conv_lat(const ConvArgs &a, hipStream_t st);
 bool conv_lat_dual_applies(const ConvArgs &a, const ProjArgs &q);
 hipError_t launch_conv_lat_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st);

@@ -164,7 +164,7 @@ class GpuNet:
         self.steps = steps
 
     # By whether requantisation is per channel: below these the three layers by themselves, which spread their weights over the whole chip,
-    # are level or faster (50-layer network, fused / apart: one image 232 / 231 us, three 252 / 252, four 255 / 257, nine 278 / 286, 32 449 / 476;
+    # are level or faster (50-layer network, fused / apart, us: per layer the library itself takes them apart below 1176 pixels; one image 169 / 169;
     # per channel nine images 293 / 284, 16 341 / 332, 32 475 / 475, 48 645 / 682, 64 736 / 775, 76 811 / 852; with two launches side by side
     # the layers are level or faster: 96 images 947 / 944).
     TRIPLE_MIN_PIXELS = {False: 256, True: 6272}

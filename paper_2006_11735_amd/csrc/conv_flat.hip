@@ -26,9 +26,19 @@ namespace icnn {
 
 struct FlatArgs {
     int rows, patch_bytes;        // patch rows; bytes of it in LDS with the row of zeros behind, in whole KiB
-    unsigned inv_pieces;          // i / (pieces of a row) = i * inv_pieces >> 22
-    int n_pt;                     // pixel tiles, if neighbouring workgroups share channels; 0: they share pixels
     SkipMul sk;
+};
+// What the patch's copies, the biases and the weights need, passed as single arguments, which are in registers when a wave starts; the other arguments
+// come by scalar loads and are waited for behind those requests.  (86 instructions at some 9 clocks and two rounds of scalar loads before the first
+// request, 157 and four before the first weights; us at 64 images, before / now: 1024 -> 256 on 14 x 14 8.8 / 8.0, 2048 -> 512 on 7 x 7 9.9 / 8.8, 512 -> 2048
+// 10.5 / 9.8, 3x3 of 512 channels 13.2 / 12.5, at stride 2 16.3 / 15.6; launches of several rounds gain less, 128 -> 512 on 28 x 28 per channel 16.6 / 15.9.)
+struct FlatFirst {
+    const uint8_t *x, *wp;
+    const int32_t *bias, *pc;
+    int M, in_cs;
+    unsigned shape;               // patch rows (11 bits), KiB of it (8), image width (13)
+    unsigned div_mul;             // a workgroup's number by channel tiles, or by pixel tiles where neighbouring workgroups share channels
+    unsigned tiles;               // channel tiles (16 bits), that division's shifts (8, 6), whether it is by pixel tiles, whether there is a skip operand
 };
 
 constexpr int kFlatTables = 4 * 72 * 4;                // of four waves' 32 channels
@@ -37,7 +47,9 @@ constexpr int kFlatTables = 4 * 72 * 4;                // of four waves' 32 chan
 // operand before it rescaled likewise (g.sk) or none, 8-bit output; 0 any form of one pair per layer; 2 per output channel.
 // S: stride, both ways.
 template <int KK, int NG, int G, int WC, int FORM, int S>
-__global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, const FlatArgs g)
+__global__ __launch_bounds__(256, 2) void conv_flat_kernel(const uint8_t *x, const uint8_t *weights, const int32_t *bias, const int32_t *pc, const int M,
+                                                           const int in_cs, const unsigned shape, const unsigned div_mul, const unsigned tiles,
+                                                           const ConvArgs a, const FlatArgs g)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr unsigned OOB = 0x80000000u;
@@ -50,27 +62,27 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
 
+    const int rows = (int)(shape & 0x7ff), patch_bytes = (int)(shape >> 11 & 0xff) * 1024, W = (int)(shape >> 19);
+
     // LDS: patch | biases of the tile's channels | FORM 2: factors, skip multipliers | stride 2: where each patch row is in the input
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-    int32_t *const btab = (int32_t *)(lds + g.patch_bytes);
+    int32_t *const btab = (int32_t *)(lds + patch_bytes);
     int32_t *const ptab = btab + 128 + wave * 72;                          // FORM 2: this wave's 32 factors, 32 skip multipliers and positions
-    unsigned *const rtab = (unsigned *)(lds + g.patch_bytes + 512 + (FORM == 2 ? kFlatTables : 0));
-    // stride 2: first patch rows of the pixels of odd columns, odd rows, both
-    const int eo = PX, oe = 2 * PX + 1, oo = 3 * PX + 1 + a.Wo;
+    unsigned *const rtab = (unsigned *)(lds + patch_bytes + 512 + (FORM == 2 ? kFlatTables : 0));
 
-    int ct, pt;
-    if (!tile_of_block(a, ct, pt)) return;
-    if (g.n_pt) {
-        const int logical = (blockIdx.x & 7) * a.per_xcd + (blockIdx.x >> 3);
-        ct = logical / g.n_pt;
-        pt = logical - ct * g.n_pt;
-    }
+    // (as tile_of_block; the division by pixel tiles where the host found neighbours sharing channels the better order)
+    const int n_ct = (int)(tiles & 0xffff), n_pt = (int)(((unsigned)M + PX - 1) / PX), n_tiles = n_ct * n_pt;
+    const int logical = (int)(blockIdx.x & 7) * ((n_tiles + 7) >> 3) + (int)(blockIdx.x >> 3);
+    if (logical >= n_tiles) return;
+    const bool by_pt = tiles >> 30 & 1;
+    const int major = fast_div_packed(logical, div_mul, tiles >> 16 & 0xff, tiles >> 24 & 0x3f), minor = logical - major * (by_pt ? n_pt : n_ct);
+    const int ct = by_pt ? major : minor, pt = by_pt ? minor : major;
     const int p0 = pt * PX;
     const int wc = wave % WC, pw = p0 + (wave / WC) * 64;                  // this wave's channels in the tile, first pixel
     const int co_tile = ct * (WC * 32), co_wave = co_tile + wc * 32;
 
     // ---- weights: group k of this wave's chunk in slot k % NS of the ring
-    const uint8_t *const wp = a.wp + (size_t)(co_wave >> 5) * (T * kChunkBytes);
+    const uint8_t *const wp = weights + (size_t)(co_wave >> 5) * (T * kChunkBytes);
     v4i ring[NS][2 * G];
     const int lane16 = lane * 16;
     auto load_frag = [&](auto k_tag, auto f_tag) __attribute__((always_inline)) {
@@ -81,61 +93,75 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
         }
     };
 
-    // ---- prologue: biases, patch and the ring's first groups in flight together
-    const int bv = a.bias[co_tile + min(tid, WC * 32 - 1)];
-    [[maybe_unused]] int factor = 0, rescale = 0, position = 0;
-    [[maybe_unused]] bool one_product = false;
-    if constexpr (FORM == 2) one_product = pc_hi_channel(a.pc, co_wave + col, a.res_mode != 0, factor, rescale, position);
-    asm volatile("" ::: "memory");
-    if constexpr (S == 2) {
-        for (int r = tid; r < g.rows; r += 256) {
-            const int odd_y = KK == 3 && r >= oe, odd_x = KK == 3 && (r >= oo || (r >= eo && r < oe));
-            const int p = p0 + (KK == 1 || r < eo ? r : r < oe ? r - eo - 1 : r < oo ? r - oe - a.Wo : r - oo - a.Wo - 1);
-            unsigned off = OOB;
-            if ((unsigned)p < (unsigned)a.M) {
-                const int n = fast_div(p, a.div_howo), at = p - n * (a.Ho * a.Wo), y = fast_div(at, a.div_wo);
-                const int iy = 2 * y + odd_y, ix = 2 * (at - y * a.Wo) + odd_x;
-                if (iy < a.H && ix < a.W) off = (unsigned)((n * a.H + iy) * a.W + ix) * (unsigned)a.in_cs;
-            }
-            rtab[r] = off;
-        }
-        __syncthreads();
-    }
-    {
-        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)a.x, 0, a.x_bytes, 0x00020000);
-        const int first = KK == 3 ? p0 - a.W - 1 : p0;
-        // 16-byte piece i of the patch region is piece i % PIECES of row i / PIECES, the last of a row padding; pixels outside the tensor, the
-        // padding and the rows behind the last one (the first of them is the row of zeros) get zeros
-        int i = tid;
-        int row = (int)(((unsigned)i * g.inv_pieces) >> 22), piece = i - row * PIECES;
-        for (int c = wave; c < g.patch_bytes / 1024; c += 4) {
-            unsigned off;
-            if constexpr (S == 2) {
-                off = piece < PIECES - 1 && row < g.rows ? rtab[min(row, g.rows - 1)] + piece * 16 : OOB;
-            } else {
-                const int p = first + row;
-                off = piece < PIECES - 1 && row < g.rows && (unsigned)p < (unsigned)a.M ? (unsigned)p * (unsigned)a.in_cs + piece * 16 : OOB;
-            }
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + c * 1024), 16, off, 0, 0, 0);
-            row += 256 / PIECES;
-            piece += 256 % PIECES;
-            if (piece >= PIECES) { piece -= PIECES; ++row; }
-        }
+    // ---- prologue: patch, biases and the ring's first groups in flight together.  Stride 2, whose patch rows take the other arguments to find: the ring first
+    constexpr int FIRST = NS < NG ? NS : NG;
+    auto start_ring = [&]() __attribute__((always_inline)) {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        constexpr int FIRST = NS < NG ? NS : NG;
         static_for<FIRST * 2 * G>([&](auto i_tag) __attribute__((always_inline)) {
             constexpr int i = decltype(i_tag)::value;
             load_frag(std::integral_constant<int, i / (2 * G)>{}, std::integral_constant<int, i % (2 * G)>{});
         });
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        if (tid < WC * 32) btab[tid] = bv;
-        if constexpr (FORM == 2) {
-            ptab[lane] = half ? rescale : factor;
-            if (half == 0) ((uint8_t *)(ptab + 64))[col] = (uint8_t)position;
-            one_product = a.pc_fast_ok && __builtin_amdgcn_ballot_w64(!one_product) == 0;
+    };
+    // stride 2: first patch rows of the pixels of odd columns, odd rows, both
+    [[maybe_unused]] int eo = 0, oe = 0, oo = 0;
+    if constexpr (S == 2) {
+        start_ring();
+        in_registers(a.Ho, a.Wo, a.H, a.div_howo.mul, a.div_howo.s1, a.div_howo.s2, a.div_wo.mul, a.div_wo.s1, a.div_wo.s2);
+        eo = PX; oe = 2 * PX + 1; oo = 3 * PX + 1 + a.Wo;
+        for (int r = tid; r < rows; r += 256) {
+            const int odd_y = KK == 3 && r >= oe, odd_x = KK == 3 && (r >= oo || (r >= eo && r < oe));
+            const int p = p0 + (KK == 1 || r < eo ? r : r < oe ? r - eo - 1 : r < oo ? r - oe - a.Wo : r - oo - a.Wo - 1);
+            unsigned off = OOB;
+            if ((unsigned)p < (unsigned)M) {
+                const int n = fast_div(p, a.div_howo), at = p - n * (a.Ho * a.Wo), y = fast_div(at, a.div_wo);
+                const int iy = 2 * y + odd_y, ix = 2 * (at - y * a.Wo) + odd_x;
+                if (iy < a.H && ix < W) off = (unsigned)((n * a.H + iy) * W + ix) * (unsigned)in_cs;
+            }
+            rtab[r] = off;
         }
+        // (the barrier is for the table alone: the ring's loads stay in flight)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xC07F);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
+    {
+        // (every place inside the tensor lies below 2 GiB, OOB above)
+        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, 0x7fffff00, 0x00020000);
+        const int first = KK == 3 ? p0 - W - 1 : p0;
+        // 16-byte piece i of the patch region is piece i % PIECES of row i / PIECES, the last of a row padding; pixels outside the tensor, the
+        // padding and the rows behind the last one (the first of them is the row of zeros) get zeros
+        int row = tid / PIECES, piece = tid - row * PIECES;
+        for (int c = wave; c < patch_bytes / 1024; c += 4) {
+            unsigned off;
+            if constexpr (S == 2) {
+                off = piece < PIECES - 1 && row < rows ? rtab[min(row, rows - 1)] + piece * 16 : OOB;
+            } else {
+                const int p = first + row;
+                off = piece < PIECES - 1 && row < rows && (unsigned)p < (unsigned)M ? (unsigned)p * (unsigned)in_cs + piece * 16 : OOB;
+            }
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + c * 1024), 16, off, 0, 0, 0);
+            row += 256 / PIECES;
+            piece += 256 % PIECES;
+            if (piece >= PIECES) { piece -= PIECES; ++row; }
+        }
+    }
+    const int bv = bias[co_tile + min(tid, WC * 32 - 1)];
+    [[maybe_unused]] int factor = 0, rescale = 0, position = 0;
+    [[maybe_unused]] bool one_product = false;
+    if constexpr (FORM == 2) one_product = pc_hi_channel(pc, co_wave + col, tiles >> 31, factor, rescale, position);
+    if constexpr (S == 1) start_ring();
+    in_registers(a.Ho, a.Wo, a.H, a.div_howo.mul, a.div_howo.s1, a.div_howo.s2, a.div_wo.mul, a.div_wo.s1, a.div_wo.s2, a.res_mode, a.res, a.res_cs, a.out, a.out_cs,
+                 a.out_co, a.lo, a.hi);
+    if constexpr (FORM == 1) in_registers(a.mul_hi, g.sk.k, g.sk.rnd);
+    if (tid < WC * 32) btab[tid] = bv;
+    if constexpr (FORM == 2) {
+        ptab[lane] = half ? rescale : factor;
+        if (half == 0) ((uint8_t *)(ptab + 64))[col] = (uint8_t)position;
+        one_product = a.pc_fast_ok && __builtin_amdgcn_ballot_w64(!one_product) == 0;
     }
     // this lane's pixels
     int taps[2], q[2];
@@ -143,10 +169,10 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
     for (int j = 0; j < 2; ++j) {
         q[j] = (wave / WC) * 64 + 32 * j + col;
         if constexpr (KK == 3) {
-            const int p = min(p0 + q[j], a.M - 1);
+            const int p = min(p0 + q[j], M - 1);
             const int r = p - fast_div(p, a.div_howo) * (a.Ho * a.Wo);
             const int y = fast_div(r, a.div_wo), x = r - y * a.Wo;
-            const int cols = (x > 0 ? 1 : 0) | 2 | (S * x + 1 < a.W ? 4 : 0);
+            const int cols = (x > 0 ? 1 : 0) | 2 | (S * x + 1 < W ? 4 : 0);
             taps[j] = (y > 0 ? cols : 0) | cols << 3 | (S * y + 1 < a.H ? cols << 6 : 0);
         }
     }
@@ -155,13 +181,13 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
         if (a.res_mode != 0) {
 #pragma unroll
             for (int j = 0; j < 2; ++j)
-                res8[0][j] = p0 + q[j] < a.M ? *(const v4i *)((const uint8_t *)a.res + ((size_t)(p0 + q[j]) * a.res_cs + co_wave + half * 16)) : v4i{0, 0, 0, 0};
+                res8[0][j] = p0 + q[j] < M ? *(const v4i *)((const uint8_t *)a.res + ((size_t)(p0 + q[j]) * a.res_cs + co_wave + half * 16)) : v4i{0, 0, 0, 0};
         }
     } else {
         prefetch_res8<1, 2>(a, co_wave, pw, lane, res8);
     }
     asm volatile("" ::: "memory");
-    ICNN_WAIT_VMCNT(2 * G * (NS < NG ? NS : NG));      // this wave's copies of the patch have landed: as many younger loads at least are the ring's
+    ICNN_WAIT_VMCNT((S == 1 ? 2 * G * FIRST : 0));     // this wave's copies of the patch have landed: as many younger loads at least are the ring's
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0xC07F);
     __builtin_amdgcn_s_barrier();                      // ... everybody's
@@ -174,11 +200,11 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
     {
         constexpr int NB = 2 * G < 4 ? 2 * G : 4, AHEAD = NB - 1, H = 2 * G;       // fragments in flight; half steps (32 channels) of a group
         v4i bf[NB][2];
-        const int zero = g.rows * AP + half * 16;
+        const int zero = rows * AP + half * 16;
         int ad[2], nad[2];
         auto tap = [&](auto t_tag, int (&d)[2]) __attribute__((always_inline)) {
             constexpr int t = decltype(t_tag)::value, kh = t / 3, kw = t % 3;
-            const int from = KK == 1 ? 0 : S == 1 ? kh * a.W + kw :
+            const int from = KK == 1 ? 0 : S == 1 ? kh * W + kw :
                              (kh == 1 ? kw == 1 ? 0 : eo : (kw == 1 ? oe : oo) + (kh == 2 ? a.Wo : 0)) + (kw == 2 ? 1 : 0);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
@@ -220,7 +246,7 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const v4i w = a.res_mode != 0 ? epilogue_hi16<1>(a, g.sk, acc[0][j], res8[0][j]) : epilogue_hi16<0>(a, g.sk, acc[0][j], v4i{0, 0, 0, 0});
-            if (p0 + q[j] < a.M) *(v4i *)((uint8_t *)a.out + (size_t)(p0 + q[j]) * a.out_cs + a.out_co + co_wave + half * 16) = w;
+            if (p0 + q[j] < M) *(v4i *)((uint8_t *)a.out + (size_t)(p0 + q[j]) * a.out_cs + a.out_co + co_wave + half * 16) = w;
         }
     } else if constexpr (FORM == 2) {
         if (one_product) {
@@ -228,10 +254,10 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const ConvArgs a, con
             for (int j = 0; j < 2; ++j) {
                 const v4i w = a.res_mode != 0 ? epilogue_pc_hi16<1>(a, ptab + half * 16, ptab + 32 + half * 16, (const uint8_t *)(ptab + 64) + half * 16, acc[0][j], res8[0][j])
                                               : epilogue_pc_hi16<0>(a, ptab + half * 16, ptab, nullptr, acc[0][j], v4i{0, 0, 0, 0});
-                if (p0 + q[j] < a.M) *(v4i *)((uint8_t *)a.out + (size_t)(p0 + q[j]) * a.out_cs + a.out_co + co_wave + half * 16) = w;
+                if (p0 + q[j] < M) *(v4i *)((uint8_t *)a.out + (size_t)(p0 + q[j]) * a.out_cs + a.out_co + co_wave + half * 16) = w;
             }
         } else {
-            epilogue_pc_tiles<1, 2>(a, acc, co_wave, pw, lane, res8, a.pc, 0);
+            epilogue_pc_tiles<1, 2>(a, acc, co_wave, pw, lane, res8, pc, 0);
         }
     } else {
         epilogue_tiles<1, 2>(a, acc, co_wave, pw, lane, res8);
@@ -246,9 +272,8 @@ bool flat_shape(const ConvArgs &a, FlatArgs &g, size_t &lds_bytes)
     const int wc = a.Cout == 64 ? 2 : 4, px = 64 * (4 / wc), pieces = a.Cin / 16 + 1;
     g.rows = a.KH == 1 ? px : a.sh == 1 ? px + 2 * (a.W + 1) : 4 * px + 2 * (a.Wo + 1);
     g.patch_bytes = ((g.rows + 1) * pieces + 63) / 64 * 1024;
-    g.inv_pieces = (1u << 22) / (unsigned)pieces + 1;           // exact for i below 256 = the only ones divided
     lds_bytes = g.patch_bytes + 512 + (a.pc ? kFlatTables : 0) + (a.sh == 2 ? (g.rows * 4 + 511) / 512 * 512 : 0);
-    return lds_bytes <= 160 * 1024;
+    return lds_bytes <= 160 * 1024 && g.rows <= 0x7ff;
 }
 }  // namespace
 
@@ -257,7 +282,7 @@ static bool flat_takes(const ConvArgs &a, bool direct_ok)
     FlatArgs g;
     size_t lds_bytes;
     if (!direct_ok || a.frag_xor || a.in_xor || a.sh < 1 || a.sh > 2 || a.sw != a.sh || a.KH != a.KW || a.ph != a.KH / 2 || a.pw != a.KW / 2 || !a.vec_bias) return false;
-    if (a.x_bytes >= 0x7fffff00u || a.wp_bytes >= 0x7fffff00u || a.M > 0x7fffffff - 256 || a.W > 4096) return false;
+    if (a.x_bytes >= 0x7fffff00u || a.wp_bytes >= 0x7fffff00u || a.M > 0x7fffffff - 256 || a.W > 4096 || a.Cout / 64 > 0xffff) return false;
     if (a.Cout % 128 != 0 && !(a.Cout == 64 && a.Cin == 64 && a.KH == 3 && a.sh == 1)) return false;
     const int c = a.Cin;
     if (a.KH == 3 ? c != 64 && c != 128 && c != 256 && c != 512 : a.KH != 1 || (c != 128 && c != 256 && c != 512 && (a.sh == 1 ? c != 1024 && c != 2048 : c != 64))) return false;
@@ -301,16 +326,19 @@ hipError_t launch_conv_flat(const ConvArgs &args, hipStream_t st)
     // What the eight L2s fetch: weights eight times and the input once, or the other way round as far as the channel tiles go.  (3x3 of 512
     // channels on 64 images of 7 x 7, 20.5 MB against 11 MB.)
     const double wt = a.wp_bytes, in = a.x_bytes;
-    g.n_pt = a.n_ct > 1 && wt * 8 + in > wt * std::max(8 / a.n_ct, 1) + in * std::min(a.n_ct, 8) ? a.n_tiles / a.n_ct : 0;
+    const bool by_pt = a.n_ct > 1 && wt * 8 + in > wt * std::max(8 / a.n_ct, 1) + in * std::min(a.n_ct, 8);
     g.sk = SkipMul{0, 0, 0};
     if (a.res_mode == 1 && a.res_dtype == 0) g.sk = make_skip_mul(a.res_mul, a.res_shift);
     const int form = a.pc ? 2 : a.rq_fast && a.epi_vec && (a.res_mode == 0 || g.sk.ok) ? 1 : 0;
+    const FastDiv by = make_fast_div((unsigned)(by_pt ? a.n_tiles / a.n_ct : a.n_ct));
+    const FlatFirst f = {a.x, a.wp, a.bias, a.pc, a.M, a.in_cs, (unsigned)g.rows | (unsigned)(g.patch_bytes / 1024) << 11 | (unsigned)a.W << 19, by.mul,
+                         (unsigned)a.n_ct | by.s1 << 16 | by.s2 << 24 | (by_pt ? 1u << 30 : 0u) | (a.res_mode ? 1u << 31 : 0u)};
     auto go = [&](auto kernel) -> hipError_t {
         if (lds_bytes > 64 * 1024) {
             const hipError_t e = allow_large_lds((const void *)kernel);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * a.per_xcd)), dim3(256), lds_bytes, st, a, g);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * a.per_xcd)), dim3(256), lds_bytes, st, f.x, f.wp, f.bias, f.pc, f.M, f.in_cs, f.shape, f.div_mul, f.tiles, a, g);
         return hipGetLastError();
     };
 #define ICNN_FLAT(KK, NG, G, WC, S) \

@@ -76,18 +76,6 @@ struct LatMore<true, TAPS> {
     LatProj p;
 };
 
-// Scalars that have to be in registers here.  The compiler asks for a kernel argument where it is first used, one round of scalar loads after
-// the other (six of them, 200 to 500 clocks each, before the last request of this kernel was out).
-__device__ __forceinline__ void in_registers() {}
-template <class T, class... R>
-__device__ __forceinline__ void in_registers(T v, R... rest)
-{
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" ::"s"(v));
-#endif
-    in_registers(rest...);
-}
-
 __device__ __forceinline__ int half_div(int n, unsigned mul)      // see mul_div
 {
     return (int)__umulhi(2u * (unsigned)n, mul);

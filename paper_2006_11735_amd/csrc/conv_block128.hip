@@ -30,8 +30,10 @@ constexpr int kB128XBytes = (kB128Rows * (kB128XP / 16) + 63) / 64 * 1024;
 // HI: the three layers requantise as a product's high word (rq_fast) and the skip operand is rescaled likewise (g.sk), the last layer's
 // epilogue dealt out between matrix instructions; else any 8-bit form
 template <bool HI>
-__global__ __launch_bounds__(256, 2) void conv_block128_kernel(const BlockArgs g, const SkipMul sk, const ConvArgs a1, const ConvArgs a2,
-                                                               const ConvArgs a3)
+__global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x, const uint8_t *w1_packed, const unsigned hw, const unsigned shape, const int x_cs,
+                                                               const int n_tiles, const int tiles_per_img, const unsigned mul_tpi, const int tiles_x,
+                                                               const unsigned mul_tx, const unsigned shifts, const unsigned inv_pw, const BlockArgs ga,
+                                                               const SkipMul sk, const ConvArgs a1, const ConvArgs a2, const ConvArgs a3)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr unsigned OOB = 0x80000000u;
@@ -55,20 +57,22 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const BlockArgs g
         asm volatile("" ::: "memory");
     };
 
+    struct { int H, W, TH, TW, PW, x_cs; unsigned inv_tw, inv_pw; } g = {(int)(hw & 0xffff), (int)(hw >> 16), (int)(shape & 0xff), (int)(shape >> 8 & 0xff),
+                                                                        (int)(shape >> 16), x_cs, 0, inv_pw};
     // XCD x takes a contiguous range of tiles, so that the halos neighbouring patches share meet in one L2
-    const int tile = (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= g.per_xcd || tile >= g.n_tiles) return;
-    const int n = tile / g.tiles_per_img;
+    const int tile = (int)(blockIdx.x & 7) * ((n_tiles + 7) >> 3) + (int)(blockIdx.x >> 3);
+    if (tile >= n_tiles) return;
+    const int n = fast_div_packed(tile, mul_tpi, shifts & 0xff, shifts >> 8 & 0xff);
     int y0, x0;
     {
-        const int r = tile - n * g.tiles_per_img;
-        const int ty = r / g.tiles_x;
+        const int r = tile - n * tiles_per_img;
+        const int ty = fast_div_packed(r, mul_tx, shifts >> 16 & 0xff, shifts >> 24);
         y0 = ty * g.TH;
-        x0 = (r - ty * g.tiles_x) * g.TW;
+        x0 = (r - ty * tiles_x) * g.TW;
     }
 
     // ---- weights: group k of this wave's chunk (its 32 channels), two K steps of two fragments, in slot k & 3 of the ring
-    const uint8_t *const w1 = a1.wp + (size_t)wave * (8 * kChunkBytes);
+    const uint8_t *const w1 = w1_packed + (size_t)wave * (8 * kChunkBytes);
     const uint8_t *const w2 = a2.wp + (size_t)wave * (18 * kChunkBytes);
     const uint8_t *const w3 = a3.wp + (size_t)wave * (2 * kChunkBytes);        // channels ch * 128 + ...: + ch * 8 steps
     v4i ring[4][4];
@@ -84,16 +88,10 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const BlockArgs g
             ring[k & 3][f] = __builtin_amdgcn_raw_buffer_load_b128(group_at(k_tag), lane16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
     };
 
-    // ---- prologue: biases, patch and the ring's first groups in flight together
+    // ---- prologue: patch, biases and the ring's first groups in flight together; what the patch and the ring need are leading arguments, which are in
+    // registers when a wave starts, and the other arguments arrive meanwhile
     {
-        int bv[3];
-#pragma unroll
-        for (int q = 0; q < 3; ++q) {
-            const int i = tid + q * 256;
-            bv[q] = i < MID ? a1.bias[i] : (i < 2 * MID ? a2.bias[i - MID] : a3.bias[i - 2 * MID]);
-        }
-        asm volatile("" ::: "memory");
-        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)g.x, 0, g.x_bytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, 0x7fffff00, 0x00020000);     // (every place inside the tensor lies below 2 GiB, OOB above)
         // 16-byte piece i of the patch region is piece i % 33 of row i / 33; the last one is padding
 #pragma unroll 2
         for (int c = wave; c < kB128XBytes / 1024; c += 4) {
@@ -104,6 +102,17 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const BlockArgs g
             const bool ok = piece < 32 && py < g.TH + 2 && (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
             const unsigned off = ok ? (unsigned)(((n * g.H + iy) * g.W + ix) * g.x_cs) + piece * 16 : OOB;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + c * 1024), 16, off, 0, 0, 0);
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        in_registers(a1.bias, a2.bias, a3.bias, a2.wp, a3.wp, a3.res_mode, a3.out, a3.out_cs, a3.out_co, ga.inv_tw);
+        if constexpr (HI) in_registers(sk.k, sk.rnd, a1.mul_hi, a1.lo, a1.hi, a2.mul_hi, a2.lo, a2.hi, a3.mul_hi, a3.lo, a3.hi);
+        g.inv_tw = ga.inv_tw;
+        int bv[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const int i = tid + q * 256;
+            bv[q] = i < MID ? a1.bias[i] : (i < 2 * MID ? a2.bias[i - MID] : a3.bias[i - 2 * MID]);
         }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
@@ -280,6 +289,7 @@ bool conv_block128_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs 
 {
     if (a1.Cin != kB128Wide || a1.Cout != kB128Mid || a3.Cout != kB128Wide || a3.pc) return false;
     if (a3.out_mode == 3 || !a3.epi_vec || a3.epi_mode / 4 == 2) return false;
+    if (g.H > 0xffff || g.W > 0xffff || g.x_bytes >= 0x7fffff00u) return false;
     return a3.res_mode == 0 || ((const uint8_t *)a3.res == g.x && a3.res_cs == g.x_cs);
 }
 
@@ -297,7 +307,10 @@ hipError_t launch_conv_block128(const BlockArgs &g, const ConvArgs &a1, const Co
     auto go = [&](auto kernel) -> hipError_t {
         const hipError_t e = allow_large_lds((const void *)kernel);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * gx.per_xcd)), dim3(256), lds_bytes, st, gx, sk, a1, a2, a3);
+        const FastDiv tpi = make_fast_div((unsigned)gx.tiles_per_img), tx = make_fast_div((unsigned)gx.tiles_x);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * gx.per_xcd)), dim3(256), lds_bytes, st, g.x, a1.wp, (unsigned)gx.H | (unsigned)gx.W << 16,
+                           (unsigned)gx.TH | (unsigned)gx.TW << 8 | (unsigned)gx.PW << 16, gx.x_cs, gx.n_tiles, gx.tiles_per_img, tpi.mul, gx.tiles_x, tx.mul,
+                           tpi.s1 | tpi.s2 << 8 | tx.s1 << 16 | tx.s2 << 24, gx.inv_pw, gx, sk, a1, a2, a3);
         return hipGetLastError();
     };
     const bool hi = a1.rq_fast && a2.rq_fast && a3.rq_fast && (a3.res_mode == 0 || sk.ok) && !g_tuning.block_any_form;

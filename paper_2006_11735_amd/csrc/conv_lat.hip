@@ -427,7 +427,8 @@ static bool lat_worth(int M, int Cout, int frags, int most_units)
 }
 
 // Against the kernel with weights straight into registers (conv_flat.hip), which has one workgroup per 128 channels x 64 pixels: here up to cost 6, and up
-// to 12 where that kernel's few workgroups have long K loops to themselves.  Microseconds here / there, costs in brackets: 3x3 of 256 channels on
+// to 9 where that kernel's few workgroups have long K loops to themselves (at 12 the two are level, and between other layers this one loses: nine images in
+// the 50-layer network, 3x3 of 256 channels at stride 2 9.0 / 8.2, 1024 -> 256 5.5 / 5.2).  Microseconds here / there, costs in brackets: 3x3 of 256 channels on
 // 14 x 14 (6) 4.8 / 6.2, (9) 6.6 / 6.3; of 128 on 28 x 28 (6) 3.9 / 4.4, (9) 4.9 / 4.4; of 64 on 56 x 56 (6) 2.8 / 3.8, (12) 3.5 / 3.8, (18) 4.2 / 3.9;
 // stride 2, 256 channels on 28 x 28 (9) 6.7 / 7.7, (12) 7.5 / 7.7, (15) 10.3 / 7.8; 512 channels on 14 x 14 (6) 8.0 / 11.5, (9) 11.5 / 11.3;
 // 1024 -> 256 (9) 3.9 / 4.9, (12) 4.4 / 4.9, (15) 5.5 / 5.0; 2048 -> 512 (6) 5.2 / 7.3, (9) 7.0 / 7.3; 512 -> 2048 (9) 3.2 / 3.8, (12) 3.4 / 3.8, (15) 4.2 / 3.9;
@@ -437,7 +438,7 @@ bool conv_lat_before_flat(const ConvArgs &a)
     if (!lat_shape_ok(a) || g_tuning.no_lat) return false;
     const long long cost = lat_tile(a.M, a.Cout, a.ksteps).cost;
     const bool longer = a.KH == 1 && a.sh == 1 ? a.ksteps >= 8 : (a.sh == 2 ? a.ksteps <= 36 : a.ksteps <= 9) && a.KH == 3;
-    return cost <= (longer ? 12 : 6);
+    return cost <= (longer ? 9 : 6);
 }
 
 bool conv_lat_applies(const ConvArgs &a)

@@ -27,7 +27,9 @@ namespace icnn {
 // FORM: 1 all layers requantise as a product's high word (rq_fast), the skip operand rescaled likewise (g.sk), the block's last layer between matrix instructions; 0 any form,
 // chosen at run time; 2 per output channel.  NEXT: the next block's first layer is included.
 template <int NP, bool NEXT, int FORM>                 // NP: pixel groups of 32 (the fourth one half used)
-__global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const ConvArgs a2, const ConvArgs a3, const ConvArgs a1)
+__global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, const uint8_t *w2_packed, const uint8_t *w3_packed, const uint8_t *w1_packed, const int M,
+                                                          const int in_cs, const unsigned shape, const unsigned tiles, const int grid, const TriArgs ga, const ConvArgs a2,
+                                                          const ConvArgs a3, const ConvArgs a1)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr unsigned OOB = 0x80000000u;
@@ -35,11 +37,14 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
     constexpr int AP = MID + 16, YP = C + 16;          // row pitches of the patch (later b) and of the skip operand (later y)
     constexpr int S2 = 9 * 4, S1 = 16;                 // K steps of 64 of a wave's chunk: 3x3 layer, next block's layer (last layer: 4 per chunk)
 
+    // what the weights' touch, the patch and the ring need are leading arguments: in registers when a wave starts, the others arrive meanwhile
+    struct { int W, rows, patch_bytes, n_tiles, per_xcd, touch; } g = {(int)(shape & 0x3ff), (int)(shape >> 10 & 0x7ff), (int)(shape >> 21 & 0xff) * 1024,
+                                                                       (int)(tiles), (int)((tiles + 7) >> 3), (int)(shape >> 29 & 1)};
     // LDS: patch, then b | skip operand, then y | biases: [256] 3x3 layer, [1024] last, [256] next
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int yb = g.patch_bytes;
     int32_t *const btab = (int32_t *)(lds + yb + PX * YP);
-    // FORM 2 with g.table (epilogue_pc_hi16): factors in the same order, skip multipliers and byte positions of the last layer, a word per wave: all of
+    // FORM 2 with ga.table (epilogue_pc_hi16): factors in the same order, skip multipliers and byte positions of the last layer, a word per wave: all of
     // its channels take that form.  (12544 pixels, per channel: 33 us with the packed parameters fetched from memory for every 32 pixels, 27.5 so.)
     int32_t *const atab = btab + 2 * MID + C, *const ktab = atab + 2 * MID + C, *const votes = ktab + C;
     uint8_t *const ptab = (uint8_t *)(votes + 8);
@@ -62,10 +67,10 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
     };
 
     // ---- copies global -> LDS, 1 KiB per wave-wide copy
-    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)a2.x, 0, a2.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, 0x7fffff00, 0x00020000);      // (every place inside the tensor lies below 2 GiB, OOB above)
     const bool has_res = a3.res_mode != 0;
     const __amdgpu_buffer_rsrc_t rs_r =
-        __builtin_amdgcn_make_buffer_rsrc(has_res ? (void *)a3.res : (void *)a3.out, 0, has_res ? g.res_bytes : 0, 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc(has_res ? (void *)a3.res : (void *)a3.out, 0, has_res ? ga.res_bytes : 0, 0x00020000);
     // 16-byte piece i of the patch region is piece i % 17 of row i / 17; the seventeenth is padding.  Row r is pixel p0 - W - 1 + r; pixels
     // outside the tensor, the padding and the rows behind the last one (the first of them is the row of zeros) get zeros.
     auto issue_patch = [&](int p0) {
@@ -77,13 +82,13 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
             const int i = c * 64 + l;
             const int row = (int)(((unsigned)i * 61681u) >> 20), piece = i - row * 17;         // / 17, exact below 2^16
             const int p = first + row;
-            const unsigned off = piece < 16 && row < g.rows && (unsigned)p < (unsigned)a2.M ? (unsigned)p * (unsigned)a2.in_cs + piece * 16 : OOB;
+            const unsigned off = piece < 16 && row < g.rows && (unsigned)p < (unsigned)M ? (unsigned)p * (unsigned)in_cs + piece * 16 : OOB;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + c * 1024), 16, off, 0, 0, 0);
         }
     };
     // a pixel's whole skip operand per copy
     auto issue_skip = [&](int p0) {
-        const int n = min(PX, a2.M - p0);
+        const int n = min(PX, M - p0);
 #pragma unroll 1
         for (int q = wave; q < n; q += 8)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_r, (__attribute__((address_space(3))) void *)(lds + yb + q * YP), 16, lane * 16,
@@ -91,9 +96,9 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
     };
 
     // ---- weights: this wave's 32-channel chunk of every layer, two fragments per K step, a ring of eight steps
-    const uint8_t *const w2 = a2.wp + (size_t)wave * (S2 * kChunkBytes);
-    const uint8_t *const w3 = a3.wp + (size_t)wave * (4 * kChunkBytes);        // channels ch * 256 + ...: + ch * 32 steps
-    const uint8_t *const w1 = NEXT ? a1.wp + (size_t)wave * (S1 * kChunkBytes) : w2;
+    const uint8_t *const w2 = w2_packed + (size_t)wave * (S2 * kChunkBytes);
+    const uint8_t *const w3 = w3_packed + (size_t)wave * (4 * kChunkBytes);        // channels ch * 256 + ...: + ch * 32 steps
+    const uint8_t *const w1 = NEXT ? w1_packed + (size_t)wave * (S1 * kChunkBytes) : w2;
     v4i ring[8][2];                                    // two groups of four steps
     // (through a descriptor of the four steps at p: the address costs scalar instructions only, 36 clocks per matrix instruction of a SIMD in
     // the K loops against 45 with 64-bit vector addresses)
@@ -111,8 +116,8 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
     // (in flight before the patch's copies, so they are over when those are; what they fetch lands in the skip operand's place before it does)
     auto touch_weights = [&]() {
         constexpr int N2 = 8 * S2 * kChunkBytes / 8192, N3 = 32 * 4 * kChunkBytes / 8192, N1 = NEXT ? 8 * S1 * kChunkBytes / 8192 : 0;
-        for (int i = (int)(blockIdx.x >> 3) * 8 + wave; i < N2 + N3 + N1; i += (int)gridDim.x) {
-            const uint8_t *const p = i < N2 ? a2.wp + i * 8192 : i < N2 + N3 ? a3.wp + (i - N2) * 8192 : a1.wp + (i - N2 - N3) * 8192;
+        for (int i = (int)(blockIdx.x >> 3) * 8 + wave; i < N2 + N3 + N1; i += grid) {
+            const uint8_t *const p = i < N2 ? w2_packed + i * 8192 : i < N2 + N3 ? w3_packed + (i - N2) * 8192 : w1_packed + (i - N2 - N3) * 8192;
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, 8192, 0x00020000);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(lds + yb + wave * 256), 4, lane * 128, 0, 0, 0);
         }
@@ -166,7 +171,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
             if (one_product) return epilogue_pc_hi16<RES>(a, atab + at, ktab + (at - MID), ptab + (at - MID), c, r8);
             return epilogue_pc_bytes16<RES>(a, c, r8, pc);
         }
-        else if constexpr (FORM == 1) return epilogue_hi16<RES>(a, g.sk, c, r8);
+        else if constexpr (FORM == 1) return epilogue_hi16<RES>(a, ga.sk, c, r8);
         else return epilogue_bytes16<RES>(a, c, r8);
     };
 
@@ -177,7 +182,14 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
         return;
     }
     {
-        int bv[3];                                     // requested before the patch, written to the table behind the ring's loads
+        if (g.touch) touch_weights();
+        issue_patch(tile_of(blockIdx.x) * PX);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        in_registers(a2.bias, a3.bias, a3.res_mode, a2.H, a2.W, a2.div_howo.mul, a2.div_howo.s1, a2.div_howo.s2, a2.div_wo.mul, a2.div_wo.s1, a2.div_wo.s2, a3.res,
+                     a3.res_cs, ga.res_bytes);
+        if constexpr (NEXT) in_registers(a1.bias);
+        int bv[3];                                     // requested before the ring, written to the table behind the ring's loads
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             const int i = tid + q * 512;
@@ -186,7 +198,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
         [[maybe_unused]] int factor[3] = {0, 0, 0}, rescale[3] = {0, 0, 0}, position[3] = {0, 0, 0};
         [[maybe_unused]] bool mine = true;
         if constexpr (FORM == 2) {
-            if (g.table) {
+            if (ga.table) {
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
                     const int i = tid + q * 512;
@@ -197,9 +209,6 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
             }
         }
         asm volatile("" ::: "memory");
-        if (g.touch) touch_weights();
-        issue_patch(tile_of(blockIdx.x) * PX);
-        asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         const __amdgpu_buffer_rsrc_t rs0 = steps_at(w2), rs1 = steps_at(w2 + 4 * kChunkBytes);
         static_for<16>([&](auto f_tag) __attribute__((always_inline)) { load_frag(f_tag, decltype(f_tag)::value < 8 ? rs0 : rs1); });
@@ -208,7 +217,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
 #pragma unroll
         for (int q = 0; q < 3; ++q) btab[tid + q * 512] = bv[q];
         if constexpr (FORM == 2) {
-            if (g.table) {
+            if (ga.table) {
 #pragma unroll
                 for (int q = 0; q < 3; ++q) {
                     const int i = tid + q * 512;
@@ -225,7 +234,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
         asm volatile("" ::: "memory");
     }
 
-    for (int v = blockIdx.x; valid(v); v += gridDim.x) {
+    for (int v = blockIdx.x; valid(v); v += grid) {
         const int p0 = tile_of(v) * PX;
         int taps[NP];                                  // bit t: tap t of the pixel lies in its image
 #pragma unroll
@@ -241,7 +250,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
         sync();                                        // ... everybody's; and nobody reads the last tile's y any more
         if (has_res) issue_skip(p0);
         if constexpr (FORM == 2) {
-            if (g.table) {
+            if (ga.table) {
                 int all = 1;
 #pragma unroll
                 for (int k = 0; k < 8; ++k) all &= votes[k];
@@ -324,7 +333,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
                     if constexpr (j == NP - 1) load_frag(std::integral_constant<int, R0 * 2 + h>{}, rs);
                     if constexpr (h == 4) r8[PAR] = *(const v4i *)(lds + at0 + slot(j) * YP + ch * MID);
                     if constexpr (FORM == 1)
-                        if (old) epilogue_hi_slice<1, 2 * h, 2>(a3, g.sk, c2[PAR ^ 1], r8[PAR ^ 1], w);
+                        if (old) epilogue_hi_slice<1, 2 * h, 2>(a3, ga.sk, c2[PAR ^ 1], r8[PAR ^ 1], w);
                     __builtin_amdgcn_sched_barrier(0);
                 });
                 if constexpr (FORM == 1) {
@@ -373,7 +382,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const TriArgs g, const
             if (q < PX && p0 + q < a2.M)
                 *(v4i *)((uint8_t *)a3.out + (size_t)(p0 + q) * a3.out_cs + a3.out_co + lane16) = *(const v4i *)(lds + yb + q * YP + lane16);
         };
-        const int vn = v + (int)gridDim.x;
+        const int vn = v + grid;
         if constexpr (NEXT) {
             if (valid(vn)) issue_patch(tile_of(vn) * PX);      // travels during this phase
             // ---------------- phase 3: 1x1, K = 1024
@@ -498,7 +507,9 @@ hipError_t launch_conv_tri(const TriArgs &g, const ConvArgs &a2, const ConvArgs 
     auto go = [&](auto kernel) -> hipError_t {
         const hipError_t e = allow_large_lds((const void *)kernel);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)slots), dim3(512), lds_bytes, st, q, b2, a3, a1 ? *a1 : a2);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)slots), dim3(512), lds_bytes, st, a2.x, a2.wp, a3.wp, a1 ? a1->wp : a2.wp, a2.M, a2.in_cs,
+                           (unsigned)g.W | (unsigned)g.rows << 10 | (unsigned)(g.patch_bytes / 1024) << 21 | (g.touch ? 1u << 29 : 0u), (unsigned)g.n_tiles, slots, q, b2, a3,
+                           a1 ? *a1 : a2);
         return hipGetLastError();
     };
     auto by_form = [&](auto np_tag, auto next_tag) {

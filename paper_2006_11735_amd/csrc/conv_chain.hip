@@ -11,15 +11,18 @@
 //            sixteen consecutive pixels hit every bank once, and every tap of a fragment read is an immediate offset
 //            from one address per lane).  Layer 0 reads the patch copied straight from memory, every later layer what the
 //            layer before wrote; pixels outside the picture are stored as zeros = the next layer's padding.
-//   weights  36 KiB per layer, double-buffered: the next layer's travel while this one is multiplied.  A wave multiplies one
+//   weights  36 KiB per layer, double-buffered, copied a layer ahead.  A wave multiplies one
 //            32-channel chunk (wave & 1) and keeps its 18 weight fragments in registers for the layer, so the K loop
-//            reads one activation fragment (1 KiB of LDS) per matrix instruction.
+//            reads one activation fragment (1 KiB of LDS) per matrix instruction; behind each product of its last group it reads the
+//            next layer's fragment into the place of the one just used.
 //   work     layer l's pixels in groups of 32 (row-major over the region); wave w takes groups (w >> 1), + 4, ...
 //   barrier  one per layer
 //
-// Measured on 256 x 256: a launch of four layers 15 to 16 us, four launches 24 us; under rocprofv3 the matrix cores are busy 22 % of the GPU-active
-// cycles (28 % of the kernel's own time at 2.4 GHz, recomputed borders included), LDS bank conflicts hold 11 % of the clocks (pixel groups
-// that straddle rows).  The rest is the chain patch -> layer -> barrier -> layer with eight waves on a compute unit.
+// Measured on 256 x 256: a launch of four layers 14.5 us (16.8 before the layers' parameters left the loop: a scalar load in it was waited for with the
+// fragments; before the next layer's weights came behind the last products, 1000 clocks a layer; and before the next group's first fragments came
+// behind the last products of the one before), one of two 8.2.  Of 31 k clocks 4.5 pass before the first layer, 7.3 in a layer of 16 groups: 36 matrix
+// instructions a round of groups and SIMD at 50 clocks, 33 without the rest of the loop; seven other instructions to each.  Unrolling the loop by two
+// saves sixteen moves a group and is slower (14.5 / 15.5 us: more code than the instruction buffers of eight waves take).
 #include "conv_common.h"
 
 #include <type_traits>
@@ -36,35 +39,37 @@ constexpr int kChainB = (kChainRP - 2) * kChainRow;
 constexpr int kChainLds = 2 * kChainWBytes + kChainA + kChainB + kChainMaxLayers * 64 * 4;
 static_assert(kChainLds <= 160 * 1024, "LDS");
 
-// PIPE: every layer has the 32-bit requantisation form (ConvArgs::rq24; the host checks).  A wave then deals the requantisation of
+// PIPE: every layer requantises as a product's high word (ConvArgs::rq_fast; the host checks).  A wave then deals the requantisation of
 // its previous pixel group out between the matrix instructions of the next: the barrier per layer keeps the two waves of a SIMD in
 // step, so both multiplied and then both requantised (a round of groups took 2.3 k clocks for 1.15 k of matrix work).
 template <bool PIPE>
-__global__ __launch_bounds__(512, 1) void conv_chain_kernel(const ChainArgs g)
+__global__ __launch_bounds__(512, 1) void conv_chain_kernel(const uint8_t *x, const uint8_t *first_weights, const int H, const int W, const int in_cs, const unsigned shape,
+                                                            const int n_tiles, const int tiles_per_img, const unsigned mul_tpi, const int tiles_x,
+                                                            const unsigned mul_tx, const unsigned shifts, const ChainArgs g)
 {
 #if defined(__HIP_DEVICE_COMPILE__)   // the buffer-resource type exists in the device pass only
     constexpr unsigned OOB = 0x80000000u;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     uint8_t *const wbuf = lds;
     uint8_t *const bufA = lds + 2 * kChainWBytes;
-    uint8_t *const bufB = bufA + kChainA;
-    int32_t *const btab = (int32_t *)(bufB + kChainB);
+    int32_t *const btab = (int32_t *)(bufA + kChainA + kChainB);      // (the other buffer begins at kChainA)
 
     const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, col = lane & 31;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int chunk = wave & 1;
 
     // the workgroups of an XCD (dealt round-robin) take a contiguous range of tiles: shared patch borders meet in one L2
-    const int t = (int)(blockIdx.x & 7) * g.per_xcd + (int)(blockIdx.x >> 3);
-    if (t >= g.n_tiles) return;
-    const int n = fast_div(t, g.div_tpi);
-    const int r = t - n * g.tiles_per_img;
-    const int ty = fast_div(r, g.div_tx);
-    const int y0 = ty * g.TH, x0 = (r - ty * g.tiles_x) * g.TW;
-    const int L = g.L;
+    // (what the patch and the first layer's weights need are leading arguments, which are in registers when a wave starts)
+    const int t = (int)(blockIdx.x & 7) * ((n_tiles + 7) >> 3) + (int)(blockIdx.x >> 3);
+    if (t >= n_tiles) return;
+    const int TH = (int)(shape & 0xff), TW = (int)(shape >> 8 & 0xff), L = (int)(shape >> 16);
+    const int n = fast_div_packed(t, mul_tpi, shifts & 0xff, shifts >> 8 & 0xff);
+    const int r = t - n * tiles_per_img;
+    const int ty = fast_div_packed(r, mul_tx, shifts >> 16 & 0xff, shifts >> 24);
+    const int y0 = ty * TH, x0 = (r - ty * tiles_x) * TW;
 
-    auto issue_weights = [&](int l) {
-        const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)g.l[l].wp, 0, kChainWBytes, 0x00020000);
+    auto issue_weights = [&](int l, const uint8_t *wp) {
+        const __amdgpu_buffer_rsrc_t rs_w = __builtin_amdgcn_make_buffer_rsrc((void *)wp, 0, kChainWBytes, 0x00020000);
         uint8_t *const dst = wbuf + (l & 1) * kChainWBytes;
 #pragma unroll
         for (int i = 0; i < (kChainWBytes / 1024 + 7) / 8; ++i) {
@@ -76,11 +81,12 @@ __global__ __launch_bounds__(512, 1) void conv_chain_kernel(const ChainArgs g)
     };
 
     // the first layer's patch: LDS piece q (16 bytes) is slot q % 5 of buffer pixel q / 5; slot 4 is the pixel's padding
-    const int ph = g.TH + 2 * L, pw = g.TW + 2 * L;
+    const int ph = TH + 2 * L, pw = TW + 2 * L;
     const int ncopy = (ph * kChainRow + 1023) / 1024;
     constexpr int CPW = (kChainA / 1024 + 7) / 8;
     {
-        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)g.x, 0, g.x_bytes, 0x00020000);
+        // (every place inside the tensor lies below 2 GiB, OOB above)
+        const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, 0x7fffff00, 0x00020000);
 #pragma unroll
         for (int i = 0; i < CPW; ++i) {
             const int e = wave + 8 * i;
@@ -88,13 +94,13 @@ __global__ __launch_bounds__(512, 1) void conv_chain_kernel(const ChainArgs g)
             const int pix = q / 5, slot = q - pix * 5;
             const int py = pix / kChainRP, px = pix - py * kChainRP;
             const int iy = y0 - L + py, ix = x0 - L + px;
-            const bool ok = slot < 4 && py < ph && px < pw && (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
-            const unsigned off = ok ? (unsigned)(((n * g.H + iy) * g.W + ix) * g.in_cs + slot * 16) : OOB;
+            const bool ok = slot < 4 && py < ph && px < pw && (unsigned)iy < (unsigned)H && (unsigned)ix < (unsigned)W;
+            const unsigned off = ok ? (unsigned)(((n * H + iy) * W + ix) * in_cs + slot * 16) : OOB;
             if (e < ncopy)                          // wave-uniform
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(bufA + e * 1024), 16, off, 0, 0, 0);
         }
     }
-    issue_weights(0);
+    issue_weights(0, first_weights);
     if (wave < L) {                                 // wave l: layer l's biases (and what inputs up to 255 add to them)
         int b = g.l[wave].bias[lane];
         if (g.l[wave].xin) b += 128 * g.l[wave].wsum[lane];
@@ -103,6 +109,7 @@ __global__ __launch_bounds__(512, 1) void conv_chain_kernel(const ChainArgs g)
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0x0070);             // vmcnt(0), lgkmcnt(0)
     asm volatile("" ::: "memory");
+    if (L > 1) issue_weights(1, g.l[1].wp);
     if (g.l[0].xin) {
         // inputs up to 255: the matrix cores take x - 128 (see ConvArgs::frag_xor); every lane flips the pieces it fetched
 #pragma unroll
@@ -118,132 +125,139 @@ __global__ __launch_bounds__(512, 1) void conv_chain_kernel(const ChainArgs g)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 
-    for (int l = 0; l < L; ++l) {
-        const ChainLayer &a = g.l[l];
-        const bool last = l + 1 == L;
-        if (!last) issue_weights(l + 1);
-        const uint8_t *const src = (l & 1) ? bufB : bufA;
-        uint8_t *const dst = (l & 1) ? bufA : bufB;
-        v4i w[kChainF];
+    v4i w[kChainF];                                 // this wave's fragments of the layer
 #pragma unroll
-        for (int f = 0; f < kChainF; ++f) w[f] = *(const v4i *)(wbuf + (l & 1) * kChainWBytes + (chunk * kChainF + f) * 1024 + lane * 16);
+    for (int f = 0; f < kChainF; ++f) w[f] = *(const v4i *)(wbuf + (chunk * kChainF + f) * 1024 + lane * 16);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    // One layer.  Nothing of it is an argument of the kernel any more once its groups begin: a scalar load in there is waited for together with the
+    // fragments on their way.  LAST: the tile goes to memory, else to the other buffer.
+    auto layer = [&](auto last_tag, const int l) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last_tag)::value;
+        struct { int mul, shift, lo, hi, rq_fast, mul_hi, rq24, t_hi, rnd, rqh; } a = {g.l[l].mul, g.l[l].shift, g.l[l].lo, g.l[l].hi, g.l[l].rq_fast,
+                                                                                     g.l[l].mul_hi, g.l[l].rq24, g.l[l].t_hi, g.l[l].rnd, g.l[l].rqh};
+        unsigned inv = g.inv[l], xout = LAST ? 0u : g.l[l + 1].xin;
+        asm volatile("" : "+s"(a.lo), "+s"(a.hi), "+s"(a.mul_hi), "+s"(inv), "+s"(xout));
+        if (l + 2 < L) issue_weights(l + 2, g.l[l + 2].wp);        // (its place's weights are in every wave's registers since the last barrier)
+        auto next_weight = [&](int f) { return *(const v4i *)(wbuf + ((l + 1) & 1) * kChainWBytes + (chunk * kChainF + f) * 1024 + lane * 16); };
+        const int src = (l & 1) ? kChainA : 0, dst = (l & 1) ? 0 : kChainA;      // bytes behind bufA
         const v16i bias = bias16(btab + l * 64 + chunk * 32 + half * 16);
         const int border = L - 1 - l;               // this layer's region reaches so far beyond the tile
-        const int rw = g.TW + 2 * border, cnt = rw * (g.TH + 2 * border);
+        const int rw = TW + 2 * border, cnt = rw * (TH + 2 * border);
         const int ng = (cnt + 31) >> 5;
-        const uint32_t xout = last ? 0u : g.l[l + 1].xin;
+        uint8_t *const out = g.out + g.out_co + chunk * 32 + half * 16;
+        const size_t out_cs = (size_t)g.out_cs;
 
-        // pixel of this lane in group gr
+        // pixel of this lane in group gr (idx below 2^9, inv below 2^16)
         auto locate = [&](int gr, int &oy, int &ox) {
             const int idx = min(gr * 32 + col, cnt - 1);
-            oy = (int)((unsigned)idx * g.inv[l] >> 16);
-            ox = idx - oy * rw;
+            oy = (int)(__umul24((unsigned)idx, inv) >> 16);
+            ox = idx - __mul24(oy, rw);
         };
         constexpr int RING = 6;
         v4i bf[RING];
-        const uint8_t *p = src;
-        auto fetch = [&](auto f_tag) {
+        const uint8_t *p = bufA;
+        auto fetch = [&](const uint8_t *from, auto f_tag, auto slot_tag) __attribute__((always_inline)) {
             constexpr int f = decltype(f_tag)::value, T = f / 2;
-            bf[f % RING] = *(const v4i *)(p + (T / 3) * kChainRow + (T % 3) * kChainPix + (f & 1) * 32);
+            bf[decltype(slot_tag)::value % RING] = *(const v4i *)(from + (T / 3) * kChainRow + (T % 3) * kChainPix + (f & 1) * 32);
         };
-        // group gr's place, and its first fragments on their way
-        auto start = [&](int gr, int &oy, int &ox) {
-            locate(gr, oy, ox);
-            p = src + oy * kChainRow + ox * kChainPix + half * 16;
-            static_for<RING - 1>([&](auto f_tag) { fetch(f_tag); });
-        };
-        auto store = [&](int gr, int oy, int ox, v4i o) {
+        auto at = [&](int oy, int ox) { return (const uint8_t *)bufA + (src + half * 16 + __mul24(oy, kChainRow) + __mul24(ox, kChainPix)); };
+        auto store = [&](int gr, int oy, int ox, v4i o) __attribute__((always_inline)) {
             const int iy = y0 - border + oy, ix = x0 - border + ox;
-            const bool valid = gr * 32 + col < cnt;
-            const bool inside = (unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W;
-            if (last) {
-                if (valid && inside)
-                    *(v4i *)(g.out + (size_t)((n * g.H + iy) * g.W + ix) * g.out_cs + g.out_co + chunk * 32 + half * 16) = o;
-            } else if (valid) {
+            const bool valid = (unsigned)(gr * 32 + col) < (unsigned)cnt;
+            const bool inside = ((unsigned)iy < (unsigned)H) & ((unsigned)ix < (unsigned)W);
+            if constexpr (LAST) {
+                if (valid & inside) *(v4i *)(out + (size_t)((n * H + iy) * W + ix) * out_cs) = o;
+            } else {
                 if (!inside) o = v4i{0, 0, 0, 0};
-                *(v4i *)(dst + oy * kChainRow + ox * kChainPix + chunk * 32 + half * 16) = o ^ (int)xout;
+                if (valid) *(v4i *)(bufA + (dst + chunk * 32 + half * 16 + __mul24(oy, kChainRow) + __mul24(ox, kChainPix))) = o ^ (int)xout;
             }
         };
-        auto finish = [&](int gr, int oy, int ox, const v16i &acc) {
-            int tv[16];
+        const SkipMul none = {0, 0, 0};
+        auto finish = [&](int gr, int oy, int ox, v16i &acc) __attribute__((always_inline)) {
+            mfma_drain(acc);
+            if constexpr (PIPE) {
+                store(gr, oy, ox, epilogue_hi16<0>(a, none, acc, v4i{0, 0, 0, 0}));
+            } else {
+                int tv[16];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) tv[q] = acc[q];
-            store(gr, oy, ox, PIPE ? requant16<3>(a, tv) : requant16_any(a, tv));
+                for (int q = 0; q < 16; ++q) tv[q] = acc[q];
+                store(gr, oy, ox, requant16_any(a, tv));
+            }
         };
-        // Multiplies group gr, whose first fragments are on their way, into acc; then starts the group after it.  PREV: group
-        // gr - 4, whose sums are in old, is requantised in slices between the matrix instructions and stored.
-        auto step = [&](auto prev_tag, int gr, int &oy, int &ox, v16i &acc, const v16i &old, int old_y, int old_x) {
-            constexpr bool PREV = decltype(prev_tag)::value;
+        // Multiplies group gr, whose first fragments are on their way, into acc.  Behind its matrix instructions: the fragments to come, in the end those of
+        // the group after it, at (oy, ox) then (behind the last group: read and not used); PIPE: the requantisation of group gr - 4, whose sums are in old,
+        // and its store.
+        auto step = [&](auto reload_tag, int gr, int &oy, int &ox, v16i &acc, v16i &old, int old_y, int old_x) __attribute__((always_inline)) {
+            constexpr bool RELOAD = decltype(reload_tag)::value;
             [[maybe_unused]] int ow[4] = {0, 0, 0, 0};
-            static_for<kChainF>([&](auto f_tag) {
-                constexpr int f = decltype(f_tag)::value;
-                if constexpr (f + RING - 1 < kChainF) fetch(std::integral_constant<int, f + RING - 1>{});
+            const uint8_t *next = p;
+            static_for<kChainF>([&](auto f_tag) __attribute__((always_inline)) {
+                constexpr int f = decltype(f_tag)::value, g5 = f + RING - 1;
                 if constexpr (f == 0) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[f], bf[f % RING], bias, 0, 0, 0);
                 else acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[f], bf[f % RING], acc, 0, 0, 0);
-                if constexpr (PREV && f >= 1 && f < 17) {
-                    epilogue_rq24_slice<0, f - 1, 1>(a, old, v4i{0, 0, 0, 0}, ow);
-                    __builtin_amdgcn_sched_barrier(0);
+                asm volatile("" : "+v"(acc));      // here, not wherever the sums are needed
+                if constexpr (RELOAD) w[f] = next_weight(f);
+                if constexpr (g5 < kChainF) fetch(p, std::integral_constant<int, g5>{}, std::integral_constant<int, g5>{});
+                else fetch(next, std::integral_constant<int, g5 - kChainF>{}, std::integral_constant<int, g5>{});
+                if constexpr (PIPE && f == 1) mfma_drain(old);
+                if constexpr (PIPE && f >= 2 && f < 10) epilogue_hi_slice<0, 2 * (f - 2), 2>(a, none, old, v4i{0, 0, 0, 0}, ow);
+                if constexpr (PIPE && f == 10) store(gr - 4, old_y, old_x, v4i{ow[0], ow[1], ow[2], ow[3]});
+                if constexpr (f == 11) {
+                    locate(gr + 4, oy, ox);
+                    next = at(oy, ox);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             });
-            int ny = 0, nx = 0;
-            if (gr + 4 < ng) start(gr + 4, ny, nx);
-            if constexpr (PREV) store(gr - 4, old_y, old_x, v4i{ow[0], ow[1], ow[2], ow[3]});
-            mfma_drain(acc);
-            oy = ny;
-            ox = nx;
+            p = next;
         };
-        const int gr0 = wave >> 1;
-        int oy = 0, ox = 0;
-        if (gr0 < ng) {
-            start(gr0, oy, ox);
-            v16i acc0 = bias, acc1 = bias;
-            if constexpr (PIPE) {
-                int py = oy, px = ox, gr = gr0;
-                step(std::false_type{}, gr, oy, ox, acc0, acc1, 0, 0);
-                for (;;) {
-                    gr += 4;
-                    if (gr >= ng) { finish(gr - 4, py, px, acc0); break; }
-                    int cy = oy, cx = ox;
-                    step(std::true_type{}, gr, oy, ox, acc1, acc0, py, px);
-                    py = cy; px = cx;
-                    gr += 4;
-                    if (gr >= ng) { finish(gr - 4, py, px, acc1); break; }
-                    cy = oy; cx = ox;
-                    step(std::true_type{}, gr, oy, ox, acc0, acc1, py, px);
-                    py = cy; px = cx;
-                }
-            } else {
-                for (int gr = gr0; gr < ng; gr += 4) {
-                    const int cy = oy, cx = ox;
-                    step(std::false_type{}, gr, oy, ox, acc0, acc1, 0, 0);
-                    finish(gr, cy, cx, acc0);
-                }
-            }
+        static_assert(kChainF % RING == 0, "the next group's fragments take the first slots");
+        // This wave's groups, the last one apart: it takes the next layer's weights behind its products.  (A wave without any goes through one whose pixels are
+        // none; the first group's predecessor is none either.  One body in a loop and one behind it: with more of them the weights move between registers.)
+        int gr = wave >> 1, oy, ox, py = 0, px = 0;
+        locate(gr, oy, ox);
+        p = at(oy, ox);
+        static_for<RING - 1>([&](auto f_tag) __attribute__((always_inline)) { fetch(p, f_tag, f_tag); });
+        v16i acc, old = bias;
+        for (; gr + 4 < ng; gr += 4) {
+            const int cy = oy, cx = ox;
+            step(std::false_type{}, gr, oy, ox, acc, old, py, px);
+            if constexpr (PIPE) old = acc;
+            else finish(gr, cy, cx, acc);
+            py = cy; px = cx;
         }
-        if (!last) {
+        const int cy = oy, cx = ox;
+        step(std::integral_constant<bool, !LAST>{}, gr, oy, ox, acc, old, py, px);
+        finish(gr, cy, cx, acc);
+        if constexpr (!LAST) {
             asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(0x0070);     // the next layer's weights have landed; this wave's pixels are in LDS
+            __builtin_amdgcn_s_waitcnt(0x0070);     // the weights of the layer after the next have landed; this wave's pixels are in LDS
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
         }
-    }
+    };
+    for (int l = 0; l + 1 < L; ++l) layer(std::false_type{}, l);
+    layer(std::true_type{}, L - 1);
 #endif
 }
 
 // ------------------------------------------------------------------ dispatch
 // Estimated microseconds of a launch of L layers on TH x TW tiles: the launch itself, then per round of workgroups (one per
 // compute unit) a prologue (from the second round on it waits for memory that other workgroups are using) and, per layer, rounds of four
-// pixel groups and what a layer costs whatever its size (weights to registers, barrier, latencies).  Within a tenth of what 2 to 6 layers
-// take on planes of 64 x 64 to 1600 x 2560 (256 x 256: 9.3, 12.7 and 16.8 us for 2 to 4 layers, 720 x 1280: 93, 153 and 217).
+// pixel groups and what a layer costs whatever its size (barrier, latencies, a last epilogue).  Within a tenth of what 2 to 6 layers
+// take on planes of 64 x 64 to 480 x 640 (256 x 256: 8.2, 11.0 and 14.5 us for 2 to 4 layers, 480 x 640: 27.7 and 46.2 for 2 and 3).
 static double chain_cost(long long tiles, int L, int th, int tw)
 {
-    double per_tile = 1.5;
+    double per_tile = 1.7;
     for (int b = 0; b < L; ++b) {
         const int ng = ((th + 2 * b) * (tw + 2 * b) + 31) / 32;
-        per_tile += 0.65 * ((ng + 3) / 4) + 1.0;
+        per_tile += 0.6 * ((ng + 3) / 4) + 0.75;
     }
     const double rounds = (double)((tiles + 255) / 256);
-    return 2.0 + per_tile * rounds + 1.2 * (rounds - 1);
+    return 2.0 + per_tile * rounds + 2.1 * (rounds - 1);
 }
 
 // Microseconds of one layer by itself, in the kernel that iconv2d_brelu takes for it; full: inputs up to 255.  Measured / estimated:
@@ -252,7 +266,7 @@ static double chain_cost(long long tiles, int L, int th, int tw)
 static double layer_cost(int N, int H, int W, bool full)
 {
     const long long pixels = (long long)N * H * W;
-    if (pixels <= 8192) return pixels <= 4096 ? 4.5 : 5.5;           // conv_lat.hip, one or two work units per compute unit
+    if (pixels <= 8192) return pixels <= 4096 ? 3.4 : 4.2;           // conv_lat.hip, one or two work units per compute unit
     const double plane = full ? 0 : conv_plane_cost(N, H, W);
     if (plane > 0) return plane;
     const double tiles = 5.0 + 7.1e-5 * (double)pixels;              // the tile kernels
@@ -327,11 +341,14 @@ hipError_t launch_conv_chain(ChainArgs &g, hipStream_t st)
         g.inv[l] = (65536 + rw - 1) / rw;           // idx * inv >> 16 = idx / rw: idx < 22 * 22 and inv * rw - 65536 < 24
     }
     bool pipe = true;
-    for (int l = 0; l < g.L; ++l) pipe = pipe && g.l[l].rq24;
+    for (int l = 0; l < g.L; ++l) pipe = pipe && g.l[l].rq_fast;
     const auto kernel = pipe ? conv_chain_kernel<true> : conv_chain_kernel<false>;
     const hipError_t e = allow_large_lds((const void *)kernel);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * g.per_xcd)), dim3(512), kChainLds, st, g);
+    const FastDiv &tpi = g.div_tpi, &tx = g.div_tx;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(8 * g.per_xcd)), dim3(512), kChainLds, st, g.x, g.l[0].wp, g.H, g.W, g.in_cs,
+                       (unsigned)g.TH | (unsigned)g.TW << 8 | (unsigned)g.L << 16, g.n_tiles, g.tiles_per_img, tpi.mul, g.tiles_x, tx.mul,
+                       tpi.s1 | tpi.s2 << 8 | tx.s1 << 16 | tx.s2 << 24, g);
     return hipGetLastError();
 }
 

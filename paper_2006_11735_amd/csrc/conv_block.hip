@@ -28,6 +28,7 @@
 // it they refill the slot of stage g - 1, whose fragments every multiply wave has multiplied.  The input waves wait
 // for everything they issued before a tile's first barrier; they start overwriting the patch only after the
 // barrier that follows phase 1's epilogue.
+#include "block_tile.h"
 #include "conv_common.h"
 
 namespace icnn {
@@ -547,32 +548,16 @@ size_t conv_block_lds_bytes(int mid, int c)
     return (size_t)kBlkStages * mg * 2048 + (size_t)k1 * kBlkRows * 64 + (size_t)s2 * kBlkRows * 64 + (size_t)(2 * mid + c) * 4;
 }
 
-// Output tile TH x TW with TH * TW <= pix and (TH + 2) * (TW + 2) <= rows that covers the image with the fewest tiles
-// (ties: the widest).  Also the two multiply-shift divisors the kernels use, checked over their whole ranges.
+// The block's output tiles, and the two multiply-shift divisors the kernels use, exact over their whole ranges.
 bool conv_block_tile(int H, int W, int pix, int rows, BlockArgs &g)
 {
-    long long best = -1;
-    for (int th = 1; th <= pix; ++th)
-        for (int tw = 1; tw <= pix; ++tw) {
-            if (th * tw > pix || (th + 2) * (tw + 2) > rows) continue;
-            const long long tiles = (long long)((H + th - 1) / th) * ((W + tw - 1) / tw);
-            if (best < 0 || tiles < best || (tiles == best && tw > g.TW)) {
-                best = tiles;
-                g.TH = th;
-                g.TW = tw;
-            }
-        }
-    if (best < 0) return false;
+    if (!fewest_tiles(H, W, pix, rows, g.TH, g.TW)) return false;
     g.PW = g.TW + 2;
     g.tiles_x = (W + g.TW - 1) / g.TW;
     g.tiles_per_img = g.tiles_x * ((H + g.TH - 1) / g.TH);
     g.inv_tw = 65536u / (unsigned)g.TW + 1;
     g.inv_pw = 65536u / (unsigned)g.PW + 1;
-    for (unsigned q = 0; q < (unsigned)pix; ++q)
-        if (((q * g.inv_tw) >> 16) != q / (unsigned)g.TW) return false;
-    for (unsigned r = 0; r < (unsigned)rows; ++r)
-        if (((r * g.inv_pw) >> 16) != r / (unsigned)g.PW) return false;
-    return true;
+    return inverse16_exact((unsigned)g.TW, g.inv_tw, (unsigned)pix) && inverse16_exact((unsigned)g.PW, g.inv_pw, (unsigned)rows);
 }
 
 hipError_t launch_conv_block(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st)

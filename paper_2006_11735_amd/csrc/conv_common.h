@@ -566,6 +566,30 @@ __device__ __forceinline__ void copy_pc_groups(int32_t *dst, const int32_t *src,
 {
     for (int i = tid; i < n_groups * (kPcGroupInts / 4); i += THREADS) ((v4i *)dst)[i] = ((const v4i *)src)[i];
 }
+// Sixteen outputs of a layer with rq_fast that joins an int32 skip operand before requantisation, where skip_s32_fits below holds: 32 bits of
+// (r * res_mul + half + t * 2^shift) >> shift are the rescaled operand r and the sum t together, two multiply-adds, and an overflow is kept at
+// int32's ends by its high word alone: what is left below that is too little to leave the output's range.  Six and three quarter
+// instructions per output, some 25 in the general form.
+__device__ __forceinline__ v4i epilogue_skip_s32(const ConvArgs &a, const v16i &acc, const v4i (&res)[4])
+{
+    int t[16];
+    const int sh = a.res_shift, ends = 1 << (sh - 1);
+    const int lowest = -ends;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int64_t sum = (int64_t)acc[r] * (1 << sh) + ((int64_t)res[r >> 2][r & 3] * a.res_mul + ends);
+        const int high = med3_vvs((int)(sum >> 32), lowest, ends - 1);
+        t[r] = (int)__builtin_amdgcn_alignbit((uint32_t)high, (uint32_t)sum, (uint32_t)sh);
+    }
+    return requant16<1>(a, t);
+}
+static inline bool skip_s32_fits(const ConvArgs &a)
+{
+    if (a.res_mode != 1 || a.res_dtype != 2 || !a.rq_fast || !a.epi_vec || a.res_shift < 2 || a.res_shift > 30) return false;
+    const long long left = 1LL << (32 - a.res_shift);        // an overflow ends up to this much (less one) inside int32's ends
+    auto out = [&](long long v) { return (v * a.mul_hi + 0x80000000LL) >> 32; };
+    return out(0x7fffffffLL + 1 - left) >= a.hi && out(-0x80000000LL + left - 1) <= a.lo;
+}
 // Outputs R0 .. R0 + N - 1 of epilogue_bytes16<RES, 3> (the 32-bit requantisation form, a.rq24): their bytes go into
 // the words w[R0 / 4 ..], which the caller collects over the sixteen outputs.  For callers that deal the epilogue out
 // in slices between matrix instructions.  R0 and N are multiples of... any; a word is started by its output 4 q.

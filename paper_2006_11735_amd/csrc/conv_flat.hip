@@ -42,6 +42,7 @@ struct FlatFirst {
 };
 
 constexpr int kFlatTables = 4 * 72 * 4;                // of four waves' 32 channels
+constexpr int kFlatSums = 4 * 32 * (32 * 4 + 16);      // 32 pixels' int32 sums of four waves
 
 // KK: kernel size; NG groups of G steps: cin = 64 G NG / KK^2.  FORM: 1 requantisation as a product's high word (rq_fast), an unsigned 8-bit skip
 // operand before it rescaled likewise (g.sk) or none, 8-bit output; 0 any form of one pair per layer; 2 per output channel; 3 as 1 with an int32
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const uint8_t *x, con
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                res32[j][i] = *(const v4i *)((const int32_t *)a.res + ((size_t)min(p0 + q[j], M - 1) * a.res_cs + co_wave + half * 16 + 4 * i));
+                res32[j][i] = *(const v4i *)((const int32_t *)a.res + ((size_t)min(pw + 32 * j + 8 * i + (lane >> 3), M - 1) * a.res_cs + co_wave + 4 * (lane & 7)));
     } else if constexpr (FORM == 1) {
         if (a.res_mode != 0) {
 #pragma unroll
@@ -250,12 +251,12 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const uint8_t *x, con
         });
     }
     mfma_drain(acc);
+    // int32 sums, stored (FORM 4) or joined (FORM 3): a pixel's 32 are 128 bytes, of which a lane has half in its accumulators.  They pass through LDS, so
+    // that an access to memory has eight whole lines and not a quarter of 64 halves.  (A region of the wave's own; its LDS accesses keep their order.)
+    constexpr int SP = 32 * 4 + 16;
+    [[maybe_unused]] uint8_t *const sums = lds + patch_bytes + 512 + (S == 2 ? (rows * 4 + 511) / 512 * 512 : 0) + wave * (32 * SP);
+    [[maybe_unused]] const int px = lane >> 3, piece = (lane & 7) * 16;
     if constexpr (FORM == 4) {
-        // A pixel's 32 sums are 128 bytes, of which a lane has half: through LDS, so that a store fills eight whole lines and not a quarter of 64
-        // halves.  (A region of the wave's own; its LDS accesses keep their order.)
-        constexpr int SP = 32 * 4 + 16;
-        uint8_t *const sums = lds + patch_bytes + 512 + (S == 2 ? (rows * 4 + 511) / 512 * 512 : 0) + wave * (32 * SP);
-        const int px = lane >> 3, piece = (lane & 7) * 16;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
 #pragma unroll
@@ -275,7 +276,16 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const uint8_t *x, con
     } else if constexpr (FORM == 3) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const v4i w = epilogue_skip_s32(a, acc[0][j], res32[j]);
+            v4i r[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) *(v4i *)(sums + (8 * i + px) * SP + piece) = res32[j][i];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) r[i] = *(const v4i *)(sums + col * SP + half * 64 + i * 16);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const v4i w = epilogue_skip_s32(a, acc[0][j], r);
             if (p0 + q[j] < M) *(v4i *)((uint8_t *)a.out + (size_t)(p0 + q[j]) * a.out_cs + a.out_co + co_wave + half * 16) = w;
         }
     } else if constexpr (FORM == 1) {
@@ -380,8 +390,10 @@ hipError_t launch_conv_flat(const ConvArgs &args, hipStream_t st)
 #define ICNN_FLAT(KK, NG, G, WC, S) \
     (form == 1 ? go(conv_flat_kernel<KK, NG, G, WC, 1, S>) : form == 2 ? go(conv_flat_kernel<KK, NG, G, WC, 2, S>) : go(conv_flat_kernel<KK, NG, G, WC, 0, S>))
     // The closing layer of a basic block beside its projection's int32 sums: two products in place of the general 64-bit steps, and the sums requested
-    // before the K loop (64 images, 128 channels on 28 x 28 18.4 -> 15.7 us, 256 on 14 x 14 13.9 -> 12.8, 512 on 7 x 7 14.0 -> 11.4).
-    if (a.KH == 3 && a.sh == 1 && !narrow && !a.pc && skip_s32_fits(a)) {
+    // before the K loop in whole lines (64 images, 128 channels on 28 x 28 18.4 -> 15.6 us, 256 on 14 x 14 13.9 -> 11.6, 512 on 7 x 7 14.0 -> 11.4;
+    // with each lane asking for its own half lines 15.7, 12.8 and 11.4).
+    if (a.KH == 3 && a.sh == 1 && !narrow && !a.pc && skip_s32_fits(a) && lds_bytes + kFlatSums <= 160 * 1024) {
+        lds_bytes += kFlatSums;
         switch (a.Cin) {
         case 64: return go(conv_flat_kernel<3, 9, 1, 4, 3, 1>);
         case 128: return go(conv_flat_kernel<3, 9, 2, 4, 3, 1>);
@@ -417,7 +429,7 @@ hipError_t launch_conv_flat(const ConvArgs &args, hipStream_t st)
     // A projection's int32 sums, stored in whole lines (64 images: 64 -> 128 channels on 56 x 56 13.3 -> 7.3 us, 128 -> 256 on 28 x 28 8.8 -> 6.2,
     // 256 -> 512 on 14 x 14 6.3 -> 5.6).
     if (a.out_mode == 3 && a.res_mode == 0 && a.epi_vec && !a.pc) {
-        lds_bytes += 4 * 32 * (32 * 4 + 16);
+        lds_bytes += kFlatSums;
         switch (a.Cin) {
         case 64: return go(conv_flat_kernel<1, 1, 1, 4, 4, 2>);
         case 128: return go(conv_flat_kernel<1, 1, 2, 4, 4, 2>);

@@ -335,10 +335,8 @@ static bool flat_takes(const ConvArgs &a, bool direct_ok)
     return flat_shape(a, g, lds_bytes);
 }
 
-// Every layer it takes but two kinds (microseconds the other kernel / this one, weights and maps cold in L2).  Up to 256 units of 32 channels x
-// 32 pixels the few-pixel kernel's are on the chip at once, one to a compute unit: 3x3 of 256 channels on 14 x 14, 248 units 5.9 / 6.5, 296 units
-// 8.3 / 6.5; of 512 on 7 x 7, 208 units 8.2 / 9.3, 400 units 11.7 / 9.3; of 128 on 28 x 28, 196 units 4.8 / 5.3, 296 units 6.3 / 5.3; 1024 -> 256 on
-// 14 x 14, 248 units 5.2 / 5.1, 296 units 6.5 / 5.1; 512 -> 2048 on 7 x 7, 256 units 4.3 / 4.1, 320 units 5.2 / 4.3.  Layers of 64 channels on large
+// Every layer it takes but two kinds (microseconds the other kernel / this one, weights and maps cold in L2).  Those of few enough pixels for the
+// few-pixel kernel: the rule and its figures stand beside it (conv_lat_before_flat).  Layers of 64 channels on large
 // pictures are level with the two-dimensional tiles that keep weights and patch in LDS (16 / 32 / 64 images of 56 x 56: 6.2 / 6.2, 9.2 / 9.9,
 // 14.7 / 14.6; with a skip operand 64 images 17.5 / 16.1).  The others: 3x3 of 256 channels on 14 x 14, 16 / 32 / 64 / 128 images 9.9 / 6.8, 11.4 / 7.4,
 // 13.2 / 10.8, 22.5 / 18.9; of 512 on 7 x 7, 64 images 14.3 / 10.7; of 128 on 28 x 28, 9 / 64 images 8.4 / 5.5, 16.1 / 12.6; 256 -> 1024 on 14 x 14,

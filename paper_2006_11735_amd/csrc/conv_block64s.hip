@@ -17,7 +17,8 @@
 // is left for positions has been taken out of the tile: where a patch's rows lie in memory is worked out by one thread per
 // row into a table in LDS, where a copy's and a store's pieces lie in a tile once per workgroup.  64 x 56 x 56 pixels: 46 us with
 // eight waves on tiles of 128 pixels (conv_block64.hip), 46 with three workgroups per compute unit that fetch their weights per
-// tile (9 of a tile's 19 k clocks), 41 now.
+// tile (9 of a tile's 19 k clocks), 41 now.  Biases and weights are requested before anything else, from arguments that the hardware puts into registers:
+// behind the tile's arguments and the first patch they came some 1500 clocks later (7.2 -> 6.9 us at one picture, 42.6 -> 41.9 at 64).
 #include "conv_common.h"
 
 #include <algorithm>
@@ -31,8 +32,10 @@ constexpr int kB64sXP = kB64sWide + 16, kB64sAP = kB64sMid + 16;      // row pit
 constexpr int kB64sXBytes = (kB64sRows * (kB64sXP / 16) + 63) / 64 * 1024;
 
 // The three layers requantise as a product's high word (rq_fast) and the skip operand is rescaled likewise (sk)
-__global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const BlockArgs g, const SkipMul sk, const ConvArgs a1, const ConvArgs a2,
-                                                               const ConvArgs a3)
+__global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *const x, const uint8_t *const wp1, const uint8_t *const wp2,
+                                                               const uint8_t *const wp3, const int32_t *const bias1, const int32_t *const bias2,
+                                                               const int32_t *const bias3, const BlockArgs g, const SkipMul sk, const ConvArgs a1,
+                                                               const ConvArgs a2, const ConvArgs a3)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr unsigned OOB = 0x80000000u;
@@ -48,6 +51,32 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const BlockArgs g
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
+
+    // ---- biases and this wave's weights, for the workgroup's whole life: requested first, from arguments that arrive in registers
+    const int c12 = wave & 1, pg = (wave >> 1) ^ (int)((blockIdx.x >> 8) & 1);          // chunk of layers 1 and 2; pixel group in phase 2 and first one in
+                                                       // phase 1, where group 0's waves take a second one (the other waves of the second workgroup on a compute unit)
+    v4i w1[8], w2[18], w3[2][2];
+    int bv[2];
+    static_assert(MID == 64, "a wave's biases are one layer's");
+    bv[0] = (wave == 0 ? bias1 : wave == 1 ? bias2 : bias3 + 64 * (wave - 2))[lane];
+    bv[1] = bias3[min(tid + 2 * MID, C - 1)];
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    {
+        const int l16 = lane * 16;
+        const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void *)(wp1 + (size_t)c12 * 4 * kChunkBytes), 0, 4 * kChunkBytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void *)(wp2 + (size_t)c12 * 9 * kChunkBytes), 0, 9 * kChunkBytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t r3 = __builtin_amdgcn_make_buffer_rsrc((void *)(wp3 + (size_t)wave * 2 * kChunkBytes), 0, 2 * kChunkBytes, 0x00020000);
+#pragma unroll
+        for (int f = 0; f < 8; ++f) w1[f] = __builtin_amdgcn_raw_buffer_load_b128(r1, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
+#pragma unroll
+        for (int f = 0; f < 18; ++f) w2[f] = __builtin_amdgcn_raw_buffer_load_b128(r2, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) w3[f >> 1][f & 1] = __builtin_amdgcn_raw_buffer_load_b128(r3, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
+    }
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    in_registers(g.per_xcd, g.n_tiles, g.tiles_per_img, g.tiles_x, g.TH, g.TW, g.PW, g.inv_pw, g.inv_tw, g.H, g.W, g.x_cs, g.x_bytes, g.k1, a3.out_cs, a3.out_co, a3.out);
 
     auto sync = [&]() {
         asm volatile("" ::: "memory");
@@ -70,7 +99,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const BlockArgs g
     if (!valid(blockIdx.x)) return;
 
     // ---- the patch of a tile.  Table: the offset of every row in memory, one thread per row (one more stands for the padding behind the last).
-    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)g.x, 0, g.x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, g.x_bytes, 0x00020000);
     auto write_rows = [&](int v, int b) __attribute__((always_inline)) {
         if (tid <= kB64sRows) {
             int n, y0, x0;
@@ -104,36 +133,10 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const BlockArgs g
                                                          off[q], 0, 0, 0);
     };
 
-    // ---- biases and this wave's weights, for the workgroup's whole life
-    const int c12 = wave & 1, pg = (wave >> 1) ^ (int)((blockIdx.x >> 8) & 1);          // chunk of layers 1 and 2; pixel group in phase 2 and first one in
-                                                       // phase 1, where group 0's waves take a second one (the other waves of the second workgroup on a compute unit)
-    v4i w1[8], w2[18], w3[2][2];
-    int bv[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int i = tid + q * 256;
-        bv[q] = i < MID ? a1.bias[i] : (i < 2 * MID ? a2.bias[i - MID] : i < 2 * MID + C ? a3.bias[i - 2 * MID] : 0);
-    }
     write_rows(blockIdx.x, 0);
     if (valid(blockIdx.x + (int)gridDim.x)) write_rows(blockIdx.x + (int)gridDim.x, 1);
     sync();
     issue_patch(0);
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    {
-        const int l16 = lane * 16;
-        const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void *)(a1.wp + (size_t)c12 * 4 * kChunkBytes), 0, 4 * kChunkBytes, 0x00020000);
-        const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void *)(a2.wp + (size_t)c12 * 9 * kChunkBytes), 0, 9 * kChunkBytes, 0x00020000);
-        const __amdgpu_buffer_rsrc_t r3 = __builtin_amdgcn_make_buffer_rsrc((void *)(a3.wp + (size_t)wave * 2 * kChunkBytes), 0, 2 * kChunkBytes, 0x00020000);
-#pragma unroll
-        for (int f = 0; f < 8; ++f) w1[f] = __builtin_amdgcn_raw_buffer_load_b128(r1, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
-#pragma unroll
-        for (int f = 0; f < 18; ++f) w2[f] = __builtin_amdgcn_raw_buffer_load_b128(r2, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
-#pragma unroll
-        for (int f = 0; f < 4; ++f) w3[f >> 1][f & 1] = __builtin_amdgcn_raw_buffer_load_b128(r3, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
-    }
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int q = 0; q < 2; ++q)
         if (tid + q * 256 < 2 * MID + C) btab[tid + q * 256] = bv[q];
@@ -169,8 +172,8 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const BlockArgs g
     tile_origin(v, n, y0, x0);
     uint8_t *const xb = lds + buf * kB64sXBytes;
     asm volatile("" ::: "memory");
-    if (v == (int)blockIdx.x) ICNN_WAIT_VMCNT(30);     // this wave's copies of the patch have landed: thirty younger loads are the weights',
-    else ICNN_WAIT_VMCNT(4);                           // ... or the last tile's four stores
+    if (v == (int)blockIdx.x) ICNN_WAIT_VMCNT(0);      // this wave's copies of the patch have landed (the weights, requested before them, too);
+    else ICNN_WAIT_VMCNT(4);                           // younger are the last tile's four stores
     sync();                                            // ... everybody's; and nobody reads the last tile's y or b any more
     {
         const int v1 = v + (int)gridDim.x, v2 = v1 + (int)gridDim.x;
@@ -313,7 +316,8 @@ hipError_t launch_conv_block64s(const BlockArgs &g, const ConvArgs &a1, const Co
     const size_t lds_bytes = 2 * kB64sXBytes + kB64sRows * kB64sAP + (2 * kB64sMid + kB64sWide) * 4 + 2 * 128 * 4;
     static_assert(2 * kB64sXBytes + kB64sRows * kB64sAP + (2 * kB64sMid + kB64sWide) * 4 + 2 * 128 * 4 <= 64 * 1024, "no permission needed");
     const SkipMul sk = a3.res_mode ? make_skip_mul(a3.res_mul, a3.res_shift) : SkipMul{0, 0, 0};     // (without an operand: adds zero)
-    hipLaunchKernelGGL(conv_block64s_kernel, dim3((unsigned)std::min(8 * gx.per_xcd, 512)), dim3(256), lds_bytes, st, gx, sk, a1, a2, a3);
+    hipLaunchKernelGGL(conv_block64s_kernel, dim3((unsigned)std::min(8 * gx.per_xcd, 512)), dim3(256), lds_bytes, st, gx.x, a1.wp, a2.wp, a3.wp, a1.bias, a2.bias, a3.bias, gx,
+                       sk, a1, a2, a3);
     return hipGetLastError();
 }
 

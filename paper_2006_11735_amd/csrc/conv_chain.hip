@@ -11,7 +11,8 @@
 //            sixteen consecutive pixels hit every bank once, and every tap of a fragment read is an immediate offset
 //            from one address per lane).  Layer 0 reads the patch copied straight from memory, every later layer what the
 //            layer before wrote; pixels outside the picture are stored as zeros = the next layer's padding.
-//   weights  36 KiB per layer, double-buffered, copied a layer ahead.  A wave multiplies one
+//   weights  36 KiB per layer, double-buffered, copied two layers ahead: layer 1's in the prologue, waited for at its last barrier; layer l + 2's from
+//            the start of layer l on, into the place of layer l's, waited for at the barrier that ends layer l.  A wave multiplies one
 //            32-channel chunk (wave & 1) and keeps its 18 weight fragments in registers for the layer, so the K loop
 //            reads one activation fragment (1 KiB of LDS) per matrix instruction; behind each product of its last group it reads the
 //            next layer's fragment into the place of the one just used.
@@ -129,7 +130,8 @@ __global__ __launch_bounds__(512, 1) void conv_chain_kernel(const uint8_t *x, co
 #pragma unroll
     for (int f = 0; f < kChainF; ++f) w[f] = *(const v4i *)(wbuf + (chunk * kChainF + f) * 1024 + lane * 16);
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0xC07F);
+    // vmcnt(0), lgkmcnt(0): behind the barrier layer 1's weights are there for every wave, as layer 0's last groups read them
+    __builtin_amdgcn_s_waitcnt(0x0070);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 

@@ -135,6 +135,12 @@ __global__ __launch_bounds__(256, 2) void conv_stem_pool_kernel(const uint8_t *x
             }
         }
     };
+    // The unit keeps the order of a wave's LDS accesses; this keeps the compiler to it where lanes read what other lanes have stored.
+    auto wave_order = [&]() {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
 #pragma unroll
     for (int b = 0; b < 4; ++b) fetch(word[b], inner[b], b);
 
@@ -158,6 +164,7 @@ __global__ __launch_bounds__(256, 2) void conv_stem_pool_kernel(const uint8_t *x
 
 #pragma unroll
     for (int b = 0; b < 3; ++b) store(word[b], inner[b], b);
+    wave_order();
 
     // fragment of picture row r (of four groups from b on): eight pixels from column 2 col on, this half of the wave four of them
     const uint8_t *const pix = ring + 8 * col + 16 * half;
@@ -256,10 +263,7 @@ __global__ __launch_bounds__(256, 2) void conv_stem_pool_kernel(const uint8_t *x
             if (out_ok) *(v4i *)(mine + c * 32) = w;
         }
         if (s + 1 < n_rows) store(w_put, in_put, s + 3);
-        // the wave's LDS accesses keep their order
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_order();
     };
     // weights and biases are here before the loop: its first product would wait for the picture rows just requested too
 #pragma unroll

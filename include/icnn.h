@@ -130,7 +130,8 @@ const char *icnn_last_error(void);
  *   "stages"      0 library's choice; 2..6 LDS ring depth of that kernel
  *   "no_narrow", "no_lat", "no_halo", "no_stream", "no_block64", "no_deep", "no_plane", "no_pic"   1 keeps layers off the respective special kernel
  *   "no_fc"       1 keeps the classifier's kind of layer (pointwise, at most 64 pixels, cin >= 512) off the kernel that "no_lat" is about
- *   "lat"         1 lets the kernel for few pixels (waves split K straight from global memory) take every layer whose shape it accepts
+ *   "lat"         1 lets the kernel for few pixels (waves split K straight from global memory) take every layer whose shape it accepts; 2, 3, 4: so,
+ *                 in tiles of 16 x 16, 32 x 16, 32 x 32 channels x pixels
  *   "halo_tile"   0 library's choice; 1 = 128 x 128, 2 = 64 x 256 tiles of the patch-resident 3x3 kernel
  *   "halo_always" 1 lets the patch-resident kernel take layers with several tiles per workgroup
  *   "no_block64s" 1 keeps fused bottleneck blocks of 256 -> 64 -> 256 channels on the kernel with resident weights
@@ -141,7 +142,7 @@ const char *icnn_last_error(void);
  *   "deep_always" 1 lets the 3x3 kernel whose waves split the K axis take every layer whose shape it accepts
  *   "deep_plain_walk" 1 gives that kernel the tile order of the other kernels (pixel tiles, not channel tiles, per XCD)
  *   "flat"        0 library's choice; 1 / 2: every / no layer whose shape it takes on the kernel that streams weights into registers
- *   "tri_tile"    0 library's choice; 1..4 = tiles of 32, 64, 96 or 112 pixels in the 3x3 + 1x1 + 1x1 kernel
+ *   "tri_tile"    0 library's choice; 1..4 = the 3x3 + 1x1 + 1x1 kernel at any size, in tiles of 32, 64, 96 or 112 pixels
  *   "ksplit"      0, 1 never split the K axis over workgroups (the library's choice); 2..8 that split where it divides the K steps
  *   "reset"       (value ignored) back to the library's choices
  * Unknown names and values outside these ranges return ICNN_E_PARAM and change nothing. */
@@ -364,16 +365,18 @@ int iconv2d_pair_brelu_pc(const icnn_conv_desc *c3, const void *t, const void *w
                           const void *pc1_packed, void *z, void *stream);
 
 /*
- * The second half of one bottleneck block and the first layer of the next as one launch: the 3x3 convolution, the 1x1 convolution
+ * The second half of one bottleneck block and the first layer of the next as one call: the 3x3 convolution, the 1x1 convolution
  * that closes the block (skip operand merged in its epilogue, Section 4.1; Section 3.1 for each layer) and the 1x1 convolution that
- * opens the next block.  Result: exactly that of
+ * opens the next block.  One launch; a small call of one multiplier and shift per layer (fewer than 1176 pixels) is a launch per layer where each can
+ * read in memory what the one before has stored (t2 given, c2's and, with c1, c3's out_c_offset 0, c3's and c1's in_c_stride the pitch that is stored, y
+ * not res itself), which is faster there.  Result: exactly that of
  *     iconv2d_brelu(c2, t,  w2_packed, bias2, NULL, t2, ...);     // 3x3, stride 1, padding 1
  *     iconv2d_brelu(c3, t2, w3_packed, bias3, res,  y,  ...);     // 1x1, stride 1, no padding
  *     iconv2d_brelu(c1, y,  w1_packed, bias1, NULL, z,  ...);     // 1x1, stride 1, no padding
- * c1 = NULL leaves the last layer away (w1_packed, bias1 and z are then not read); t2 = NULL leaves the middle tensor unwritten (c3's
- * in_c_stride and, with c1, c1's are not used).  lanes (at least 1): how many such launches the program runs side by side (the parts of a
- * batch); it changes the launch's shape, never a result.  Shapes it takes: 256 -> 256 -> 1024 (-> 256) channels, images up to 210 pixels wide; c2 and, with c1, c3 store unsigned bytes bounded by
- * at most 127 from a lower clamp of 0, c3 without c1 any unsigned bytes; c1 likewise; c3 takes no skip operand or an unsigned 8-bit one
+ * c1 = NULL leaves the last layer away (w1_packed, bias1 and z are then not read); t2 = NULL leaves the middle tensor unwritten.  No
+ * result depends on c3's in_c_stride or, with c1, on c1's.  lanes (at least 1): how many such launches the program runs side by side (the parts
+ * of a batch); it may change the one launch's shape, never a result.  Shapes it takes: 256 -> 256 -> 1024 (-> 256) channels, images up to 210 pixels
+ * wide; c2 and, with c1, c3 store unsigned bytes bounded by at most 127 from a lower clamp of 0, c3 without c1 any unsigned bytes; c1 likewise; c3 takes no skip operand or an unsigned 8-bit one
  * joined before requantisation whose rescale fits 32 bits, c2 and c1 none; inputs ICNN_IN_U8_LE127; tensors, bias arrays and pitches
  * 16-byte aligned, tensors below 2 GiB; no output overlaps t, another output, or res (y may be res itself).  Anything else returns
  * ICNN_E_UNSUPPORTED having launched nothing, and the caller issues the layers separately.

@@ -171,7 +171,8 @@ class GpuNet:
 
     def _fuse_triples(self):
         """A block's 3x3 convolution, the 1x1 convolution that closes the block and, where it follows, the 1x1 convolution that opens the
-        next one: one iconv2d_triple_brelu launch where the library accepts it.  All three outputs are written, the 3x3 layer's too."""
+        next one: one iconv2d_triple_brelu call where the library accepts it (one launch, or one per layer where it takes a small call
+        apart).  All three outputs are written, the 3x3 layer's too."""
         steps, i = [], 0
         while i < len(self.steps):
             run = self.steps[i:i + 3]

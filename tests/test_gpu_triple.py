@@ -1,5 +1,6 @@
-"""A 3x3 layer, the 1x1 layer that closes its block and the 1x1 layer that opens the next one as one launch (iconv2d_triple_brelu): the
-same bytes as the three layers one by one, which have their own tests against the oracle, at the edges of tiles and images."""
+"""A 3x3 layer, the 1x1 layer that closes its block and the 1x1 layer that opens the next one as one call (iconv2d_triple_brelu).  The fused kernel (a
+forced tile): the same bytes as the three layers one by one, which have their own tests against the oracle, at the edges of tiles and images.  The
+library's own choice, which takes the layers of small calls apart: against the oracle, on both sides of each of its conditions."""
 import numpy as np
 import pytest
 import torch
@@ -25,8 +26,10 @@ class Layer:
                                  out_c_stride=pitch or cout, out_c_offset=0, mul=mul, shift=shift, bound_q=127)
         self.pc = None
         self.wp = torch.zeros(B.iconv2d_packed_weight_bytes(d), dtype=torch.uint8, device="cuda:0")
-        B.iconv2d_prepack_weights(d, dev(g.integers(-127, 128, size=(cout, k, k, cin), dtype=np.int8)), self.wp)
-        self.bias = dev(g.integers(-4096, 4097, size=cout).astype(np.int32))
+        self.w_host = g.integers(-127, 128, size=(cout, k, k, cin), dtype=np.int8)
+        B.iconv2d_prepack_weights(d, dev(self.w_host), self.wp)
+        self.bias_host = g.integers(-4096, 4097, size=cout).astype(np.int32)
+        self.bias = dev(self.bias_host)
         if skip:
             d.res_mode, d.res_dtype, d.res_c_stride, d.res_mul, d.res_shift = (B.ICNN_RES_PRE, B.ICNN_U8, cout) + rescale
         if form.startswith("pc"):
@@ -51,6 +54,13 @@ class Layer:
         else:
             B.iconv2d_brelu(self.d, x, self.wp, self.bias, res, y, None)
         return y
+
+
+    def oracle(self, x, res=None):
+        from oracle import oracle as O
+        d = self.d
+        skip = {} if res is None else dict(res=res, res_mode="pre", res_mul=d.res_mul, res_shift=d.res_shift)
+        return O.conv2d(x, self.w_host, self.bias_host, pad=d.pad_h, mul=d.mul, shift=d.shift, bound_q=127, **skip)
 
 
 def picture(g, *shape):
@@ -117,12 +127,24 @@ def test_more_tiles_than_workgroups(tile):
     check(n * 4, 7, 7, third=False)
 
 
-def test_the_widest_image():
+@pytest.fixture
+def smallest_tile():
     from paper_2006_11735_amd import binding as B
+    B.icnn_set_tuning("tri_tile", 1)
+    yield
+    B.icnn_set_tuning("reset")
+
+
+def test_the_widest_image(smallest_tile):
+    from paper_2006_11735_amd import binding as B
+    assert fits(1, 210) and not fits(1, 211)
     check(1, 3, 210)
-    with pytest.raises(B.IcnnError) as e:
-        check(1, 3, 211)
-    assert e.value.code == B.ICNN_E_UNSUPPORTED
+    for forced in (True, False):
+        if not forced:
+            B.icnn_set_tuning("reset")
+        with pytest.raises(B.IcnnError) as e:
+            check(1, 3, 211)
+        assert e.value.code == B.ICNN_E_UNSUPPORTED
 
 
 @pytest.mark.parametrize("form", ["hi", "wide", "pc", "pc_mixed"])
@@ -146,14 +168,61 @@ def test_skip_operand_pitches_and_in_place(tile):
 
 # the skip operand's rescale as one product's high word: the ends of its range, ties at every shift, pairs that reduce to it, pairs it does not take
 @pytest.mark.parametrize("rescale", [(1, 0), (30000, 0), (1, 1), (3, 1), (32767, 4), (8000000, 8), (129, 8), (1, 8), (20000 << 4, 10), (20001, 9), (6000000, 30)], ids=str)
-def test_skip_rescales(rescale):
+def test_skip_rescales(rescale, smallest_tile):
     check(1, 14, 14, rescale=rescale)
 
 
 def test_the_librarys_choice_of_tiles():
-    for n in (1, 48, 84, 128):
+    for n in (6, 48, 84, 128):                       # six: the first that is not taken apart
         check(n, 14, 14)
         check(n, 14, 14, lanes=2)
+
+
+# below 1176 pixels the library takes the layers apart where each finds in memory what it reads: t2 is stored, at c2's offset 0 and with the pitch that c3
+# reads, y likewise for c1, and y is not res.  Every other call is one launch, and in_c_stride of c3 and c1 means nothing there.
+@pytest.mark.parametrize("shape", [(1, 25, 47), (1, 24, 49), (6, 14, 14), (1, 7, 7)], ids=lambda s: "x".join(map(str, s)))
+def test_on_both_sides_of_the_bound(shape):
+    against_oracle(*shape)
+    against_oracle(*shape, lanes=2, third=False)
+
+
+@pytest.mark.parametrize("how", [dict(), dict(pitches=(32, 64, 16)), dict(in_pitch3=272), dict(in_pitch1=1056), dict(offset2=32), dict(offset3=64, third=False),
+                                 dict(offset3=64), dict(in_place=True), dict(in_place=True, third=False), dict(middle=False), dict(skip=False),
+                                 dict(third=False, in_pitch3=512), dict(middle=False, in_pitch3=272, in_pitch1=1040)], ids=str)
+def test_what_a_small_call_needs_to_be_taken_apart(how):
+    against_oracle(2, 9, 11, **how)
+
+
+def against_oracle(n, h, w, skip=True, third=True, middle=True, pitches=(0, 0, 0), in_pitch3=None, in_pitch1=None, offset2=0, offset3=0, in_place=False, lanes=1):
+    """pitches: beyond what the channels and their offset take; in_pitch3, in_pitch1: in_c_stride of c3 and c1 (default: what is stored)"""
+    from gpu_util import dev
+    from paper_2006_11735_amd import binding as B
+    g = np.random.default_rng([n, h, w, lanes])
+    mid, wide = 256, 1024
+    stored = [mid + offset2 + pitches[0], wide + offset3 + pitches[1], mid + pitches[2]]
+    l2 = Layer(g, n, h, w, mid, mid, 3, pitch=stored[0])
+    l3 = Layer(g, n, h, w, mid, wide, skip=skip, pitch=stored[1], in_pitch=in_pitch3 or stored[0])
+    l1 = Layer(g, n, h, w, wide, mid, pitch=stored[2], in_pitch=in_pitch1 or stored[1])
+    l2.d.out_c_offset, l3.d.out_c_offset = offset2, offset3
+    t = g.integers(0, 128, size=(n, h, w, mid), dtype=np.uint8)
+    res = g.integers(0, 256, size=(n, h, w, wide), dtype=np.uint8) if skip else None
+    b = l2.oracle(t)
+    y = l3.oracle(b, res)
+    z = l1.oracle(y)
+    gb, gy, gz = (torch.full((n, h, w, c), 99, dtype=torch.uint8, device="cuda:0") for c in stored)
+    gres = dev(res) if skip else None
+    if in_place:
+        assert stored[1] == wide
+        gy = gres
+    tail = (l1.d, l1.wp, l1.bias, gz) if third else (None,) * 4
+    B.iconv2d_triple_brelu(l2.d, dev(t), l2.wp, l2.bias, gb if middle else None, l3.d, l3.wp, l3.bias, gres, gy, *tail, lanes=lanes)
+    torch.cuda.synchronize()
+    for got, want, at, written in ((gb, b, offset2, middle), (gy, y, offset3, True), (gz, z, 0, third)):
+        whole = np.full(got.shape, 99, dtype=np.uint8)
+        if written:
+            whole[..., at:at + want.shape[3]] = want
+        assert (got.cpu().numpy() == whole).all()
+    assert len(np.unique(y)) > 3 and len(np.unique(z)) > 3
 
 
 def test_refused_calls_launch_nothing():

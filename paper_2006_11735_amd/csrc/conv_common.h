@@ -781,7 +781,7 @@ __device__ __forceinline__ void epilogue_tiles(const ConvArgs &a, const v16i (&a
     prefetch_res8<TM, TP>(a, co_wave, pix_wave, lane, res8);
     epilogue_tiles<TM, TP>(a, acc, co_wave, pix_wave, lane, res8);
 }
-// Maps the hardware workgroup id to a tile.  Workgroups are dealt round-robin to the
+
 // Scalars that have to be in registers here.  The compiler asks for a kernel argument where it is first used, one round of scalar loads after
 // the other, some 1000 clocks for the first and 200 to 500 for each of the others (six of them before the last request of conv_lat.hip was out).
 __device__ __forceinline__ void in_registers() {}
@@ -801,6 +801,7 @@ __device__ __forceinline__ int fast_div_packed(int n, unsigned mul, unsigned s1,
     return (int)((t + (((unsigned)n - t) >> s1)) >> s2);
 }
 
+// Maps the hardware workgroup id to a tile.  Workgroups are dealt round-robin to the
 // 8 XCDs (each with its own L2); giving XCD x the contiguous tile range
 // [x*per_xcd, (x+1)*per_xcd) keeps the cout tiles of one pixel tile, and neighbouring
 // pixel tiles (shared halo rows), in one L2.  Returns false for padding workgroups.

@@ -872,7 +872,7 @@ int iconv2d_pair_brelu_pc(const icnn_conv_desc *c3, const void *t, const void *w
 }
 
 // Below this many pixels a run of three layers is three launches of layers that spread their weights over the whole chip (50-layer network, its five runs
-// in one launch each / apart, us: two images 202 / 183, four 219 / 213, five 223 / 220, six = 1176 pixels 240 / 241, nine 247 / 253).
+// in one launch each / apart, us: two images 192 / 177, three 203 / 195, four 207 / 206, five 213 / 210, six = 1176 pixels 226 / 227, nine 232 / 233, 16 267 / 283).
 constexpr long long kTriMinPixels = 1176;
 
 static int triple_layers(const icnn_conv_desc *c2, const void *t, const void *w2_packed, const int32_t *bias2, const void *pc2, void *t2,

@@ -19,9 +19,10 @@
 //   work     layer l's pixels in groups of 32 (row-major over the region); wave w takes groups (w >> 1), + 4, ...
 //   barrier  one per layer
 //
-// Measured on 256 x 256: a launch of four layers 14.5 us (16.8 before the layers' parameters left the loop: a scalar load in it was waited for with the
+// Measured on 256 x 256: a launch of four layers of the network 14 to 15 us (16.8 before the layers' parameters left the loop: a scalar load in it was waited for with the
 // fragments; before the next layer's weights came behind the last products, 1000 clocks a layer; and before the next group's first fragments came
-// behind the last products of the one before), one of two 8.2.  Of 31 k clocks 4.5 pass before the first layer, 7.3 in a layer of 16 groups: 36 matrix
+// behind the last products of the one before); on uniform random bytes, which are slower, two, three and four layers
+// 8.9, 12.3 and 16.1.  That the prologue waits for layer 1's weights as well changes none of these.  Of 31 k clocks 4.5 pass before the first layer, 7.3 in a layer of 16 groups: 36 matrix
 // instructions a round of groups and SIMD at 50 clocks, 33 without the rest of the loop; seven other instructions to each.  Unrolling the loop by two
 // saves sixteen moves a group and is slower (14.5 / 15.5 us: more code than the instruction buffers of eight waves take).
 #include "conv_common.h"
@@ -249,8 +250,10 @@ __global__ __launch_bounds__(512, 1) void conv_chain_kernel(const uint8_t *x, co
 // ------------------------------------------------------------------ dispatch
 // Estimated microseconds of a launch of L layers on TH x TW tiles: the launch itself, then per round of workgroups (one per
 // compute unit) a prologue (from the second round on it waits for memory that other workgroups are using) and, per layer, rounds of four
-// pixel groups and what a layer costs whatever its size (barrier, latencies, a last epilogue).  Within a tenth of what 2 to 6 layers
-// take on planes of 64 x 64 to 480 x 640 (256 x 256: 8.2, 11.0 and 14.5 us for 2 to 4 layers, 480 x 640: 27.7 and 46.2 for 2 and 3).
+// pixel groups and what a layer costs whatever its size (barrier, latencies, a last epilogue).  Measured / estimated, launches of 2 to 6 layers on
+// uniform random bytes: one round of workgroups 256 x 256 8.9 / 8.2, 12.3 / 11.3 and 16.1 / 14.5 for 2 to 4 layers (inputs up to 255 add 5 %), 64 x 64 6.3 / 6.4,
+// 8.5 / 8.4, 10.9 / 10.3, 13.5 / 11.7, 15.0 / 13.6; several rounds 480 x 640 28.1 / 30.2, 47.2 / 50.5, 65.0 / 69.9; from 0.81 to 1.18 over all sizes tried (64 x 64
+// to 1600 x 2560, one to 16 pictures), low for five and six layers in one round, high for two in many.
 static double chain_cost(long long tiles, int L, int th, int tw)
 {
     double per_tile = 1.7;
@@ -263,8 +266,9 @@ static double chain_cost(long long tiles, int L, int th, int tw)
 }
 
 // Microseconds of one layer by itself, in the kernel that iconv2d_brelu takes for it; full: inputs up to 255.  Measured / estimated:
-// 64 x 64 4.4 / 4.5, 128 x 128 7.0 / 7.5 (inputs up to 255: 7.7), 256 x 256 6.1 / 6.0 (10.4 / 9.7), 480 x 640 14.9 / 15.0 (26.8 / 26.8),
-// 720 x 1280 34.5 / 35.7 (65.2 / 70.4).
+// 64 x 64 3.7 / 3.4 (inputs up to 255: 3.7 / 3.4), two of them 4.1 / 4.2 (4.8 / 4.2), 96 x 96 4.2 / 7.5 (7.0 / 7.5), 128 x 128 4.4 / 7.5
+// (7.1 / 7.5), 256 x 256 6.0 / 6.0 (9.6 / 9.7), 480 x 640 15.4 / 15.0 (26.8 / 26.8), 720 x 1280 34.2 / 35.7 (64.8 / 70.4).  (What stands at 7.5 goes to
+// conv_flat.hip with inputs up to 127; chains are ahead there by more: 128 x 128 48 us for 18 layers, 75 one by one.)
 static double layer_cost(int N, int H, int W, bool full)
 {
     const long long pixels = (long long)N * H * W;
@@ -291,9 +295,10 @@ static double chain_tile(int N, int H, int W, int L, int &th, int &tw)
 
 // Cuts n layers into launches of len[0], len[1], ... layers (at most n entries); returns their number.  A piece of one layer is not a chain:
 // iconv2d_brelu computes it.  full[i]: layer i's inputs go up to 255.
-// 18 layers as cut here / one by one: 64 x 64 43 / 78 us, 256 x 256 76 / 110, 384 x 384 156 / 188; on 384 x 512 and above the layers
-// by themselves are the faster choice (720 x 1280: 621 us, in nine chains of two 836).  With inputs up to 255: 256 x 256 79 / 187,
-// 256 x 384 139 / 219, 720 x 1280 876 / 1173.
+// 18 layers as cut here / one by one: 64 x 64 42 / 62 us, 256 x 256 71 / 103, 384 x 384 142 / 183; 720 x 1280 one by one 612, in nine chains of two 695;
+// with inputs up to 255: 256 x 256 74 / 170, 256 x 384 128 / 204, 720 x 1280 741 / 1169.  Against the best split by the pieces' own times, 22 sizes of 64 x 64
+// to 1600 x 2560 in both kinds: within 2 %, but for 480 x 640 with inputs up to 127, which goes one by one (273) where chains of two take 250: each is
+// 28.1 us, two layers by themselves 30.8, estimated at 30.2 and 30.0.
 int conv_chain_split(int N, int H, int W, int n, const bool *full, int *len)
 {
     double cost[kChainMaxLayers + 1];

@@ -549,6 +549,10 @@ static hipError_t launch_lat(const ConvArgs &a, const ProjArgs *q, hipStream_t s
     g.res_shift = q ? q->res_shift : a.res_shift;
     g.fast = a.rq24 && !a.pc && (a.res_mode == 0 || (a.res_mode == 1 && a.res_fast));
     g.t_hi = a.t_hi; g.rnd = a.rnd;
+    // As many loads in flight as the waves have steps: a missing one is still requested and multiplied.  One image, its layers replayed as a graph over 16 sets
+    // of weights, us with the next larger number / as here, 16 x 16, 32 x 16 and 32 x 32: one step (256 -> 1024) 4.2 / 3.2, 3.5 / 2.9, 3.6 / 3.1; two (1024 -> 256)
+    // 2.9 / 2.7, 3.1 / 2.8, 3.9 / 3.4; three (3x3 of 128 channels) 4.8 / 3.8, 3.9 / 3.3, 5.1 / 4.0.  Nine steps (3x3 of 512) at once where they have the registers, in
+    // 16 x 16: 4.8 / 4.6 against rounds of five.
     if (p.ch == 1) {
         if (p.steps <= 1) return pick_taps<1, 1, 1, false>(p, g, st);
         if (p.steps <= 2) return pick_taps<1, 1, 2, false>(p, g, st);

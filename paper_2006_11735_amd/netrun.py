@@ -164,9 +164,9 @@ class GpuNet:
         self.steps = steps
 
     # By whether requantisation is per channel: below these the three layers by themselves, which spread their weights over the whole chip,
-    # are level or faster (50-layer network, fused / apart, us: per layer the library itself takes them apart below 1176 pixels; one image 169 / 169;
-    # per channel nine images 293 / 284, 16 341 / 332, 32 475 / 475, 48 645 / 682, 64 736 / 775, 76 811 / 852; with two launches side by side
-    # the layers are level or faster: 96 images 947 / 944).
+    # are level or faster (50-layer network, fused / apart, us: per layer the library itself takes them apart below 1176 pixels, six images 226 / 227, 16 267 / 283,
+    # 64 526 / 559; per channel four images 249 / 237, nine 272 / 266, 16 314 / 309, 24 360 / 355, 32 = 6272 pixels 423 / 425, 48 560 / 600, 64 630 / 674; with two
+    # launches side by side the layers are level or faster: 88 images 819 / 794, 96 863 / 847, 128 1074 / 1076).
     TRIPLE_MIN_PIXELS = {False: 256, True: 6272}
 
     def _fuse_triples(self):
@@ -209,7 +209,9 @@ class GpuNet:
         self.steps = steps
 
     # What the three-layer launches and the blocks leave: per channel the 256 -> 1024 -> 256 boundaries of a batch in two halves, per layer those whose
-    # 3x3 layer _fuse_triples does not take (no stored network has one).  The figures are those of the 50-layer network without these launches.
+    # 3x3 layer _fuse_triples does not take (no stored network has one).  The figures are those of the 50-layer network without these launches, from when the
+    # layers by themselves were the tile kernels; in two halves per channel, the one case left in a stored network, the pairs are now behind (fused / apart: 88
+    # images 835 / 794 us, 96 884 / 847, 128 1134 / 1076).
     # The fused pair streams both layers' weights through every workgroup's 64-pixel tile: it wins where the tiles
     # fit the chip in about one round and the wide tensor is at most 1024 channels (measured at batch 64: 17.6 us
     # against 23.8 us for 12544 pixels of 256 -> 1024 -> 256; level at 50176 pixels of 128 -> 512 -> 128; a loss,
@@ -440,8 +442,8 @@ class GpuNet:
         self.steps = steps
 
     # With 128 middle channels a block is one workgroup after another's worth of weights per 64 pixels; its three layers spread them over the
-    # chip.  The 50-layer network with its three such blocks fused / layer by layer: 225 / 231 us at one image of 28 x 28 (13 workgroups),
-    # 265 / 278 at nine, 443 / 472 at 32, 650 / 685 at 64.  Fewer pixels than that were not looked at and stay apart.
+    # chip, but are three launches.  The 50-layer network with its three such blocks fused / layer by layer: 165 / 173 us at one image of 28 x 28 (13
+    # workgroups), 177 / 184 at two, 205 / 214 at four, 232 / 241 at nine, 341 / 367 at 32, 527 / 545 at 64.  Fewer pixels than that were not looked at and stay apart.
     BLOCK128_MIN_PIXELS = 784
 
     def _fuse_blocks(self):

@@ -794,6 +794,23 @@ __device__ __forceinline__ void in_registers(T v, R... rest)
     in_registers(rest...);
 }
 
+// A kernel's argument that is read here and not where the compiler would have it, which is at the kernel's start: there it holds registers through phases
+// that do not use it, and where they run out it is waited for at once to be put aside.  at: its place among the kernel's arguments (their
+// order in a struct of the same members).
+template <class T>
+__device__ __forceinline__ T late_argument(unsigned at)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    using Args = const __attribute__((address_space(4))) char *;
+    Args p = (Args)__builtin_amdgcn_kernarg_segment_ptr() + at;
+    asm volatile("" : "+s"(p));
+    return *(const T *)p;
+#else
+    (void)at;
+    return T{};
+#endif
+}
+
 // fast_div with its parts as they come in scalar arguments
 __device__ __forceinline__ int fast_div_packed(int n, unsigned mul, unsigned s1, unsigned s2)
 {

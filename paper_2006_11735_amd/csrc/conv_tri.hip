@@ -24,12 +24,24 @@
 
 namespace icnn {
 
+// The kernel's arguments in their order (late_argument)
+struct TriKernelArgs {
+    const uint8_t *x, *w2;
+    const int32_t *bias2, *bias3, *bias1;
+    int M, in_cs;
+    unsigned shape, tiles;
+    int grid;
+    const uint8_t *w3, *w1;
+    TriArgs ga;
+    ConvArgs a2, a3, a1;
+};
+
 // FORM: 1 all layers requantise as a product's high word (rq_fast), the skip operand rescaled likewise (g.sk), the block's last layer between matrix instructions; 0 any form,
 // chosen at run time; 2 per output channel.  NEXT: the next block's first layer is included.
 template <int NP, bool NEXT, int FORM>                 // NP: pixel groups of 32 (the fourth one half used)
-__global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, const uint8_t *w2_packed, const uint8_t *w3_packed, const uint8_t *w1_packed, const int M,
-                                                          const int in_cs, const unsigned shape, const unsigned tiles, const int grid, const TriArgs ga, const ConvArgs a2,
-                                                          const ConvArgs a3, const ConvArgs a1)
+__global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, const uint8_t *w2_packed, const int32_t *bias2, const int32_t *bias3, const int32_t *bias1,
+                                                          const int M, const int in_cs, const unsigned shape, const unsigned tiles, const int grid,
+                                                          const uint8_t *w3_packed, const uint8_t *w1_packed, const TriArgs, const ConvArgs, const ConvArgs, const ConvArgs)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr unsigned OOB = 0x80000000u;
@@ -37,9 +49,9 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
     constexpr int AP = MID + 16, YP = C + 16;          // row pitches of the patch (later b) and of the skip operand (later y)
     constexpr int S2 = 9 * 4, S1 = 16;                 // K steps of 64 of a wave's chunk: 3x3 layer, next block's layer (last layer: 4 per chunk)
 
-    // what the weights' touch, the patch and the ring need are leading arguments: in registers when a wave starts, the others arrive meanwhile
+    // what the patch, the biases and the ring need are leading arguments: in registers when a wave starts, the others arrive meanwhile
     struct { int W, rows, patch_bytes, n_tiles, per_xcd, touch; } g = {(int)(shape & 0x3ff), (int)(shape >> 10 & 0x7ff), (int)(shape >> 21 & 0xff) * 1024,
-                                                                       (int)(tiles), (int)((tiles + 7) >> 3), (int)(shape >> 29 & 1)};
+                                                                       (int)(tiles), (int)((tiles + 7) >> 3), NP == 1 ? (int)(shape >> 29 & 1) : 0};
     // LDS: patch, then b | skip operand, then y | biases: [256] 3x3 layer, [1024] last, [256] next
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int yb = g.patch_bytes;
@@ -68,9 +80,9 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
 
     // ---- copies global -> LDS, 1 KiB per wave-wide copy
     const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, 0x7fffff00, 0x00020000);      // (every place inside the tensor lies below 2 GiB, OOB above)
-    const bool has_res = a3.res_mode != 0;
-    const __amdgpu_buffer_rsrc_t rs_r =
-        __builtin_amdgcn_make_buffer_rsrc(has_res ? (void *)a3.res : (void *)a3.out, 0, has_res ? ga.res_bytes : 0, 0x00020000);
+    TriArgs ga;
+    ConvArgs a2, a3, a1;                               // read behind the first requests, the last two behind the 3x3 layer
+    bool has_res = false;
     // 16-byte piece i of the patch region is piece i % 17 of row i / 17; the seventeenth is padding.  Row r is pixel p0 - W - 1 + r; pixels
     // outside the tensor, the padding and the rows behind the last one (the first of them is the row of zeros) get zeros.
     auto issue_patch = [&](int p0) {
@@ -89,6 +101,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
     // a pixel's whole skip operand per copy
     auto issue_skip = [&](int p0) {
         const int n = min(PX, M - p0);
+        const __amdgpu_buffer_rsrc_t rs_r = __builtin_amdgcn_make_buffer_rsrc((void *)a3.res, 0, ga.res_bytes, 0x00020000);
 #pragma unroll 1
         for (int q = wave; q < n; q += 8)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_r, (__attribute__((address_space(3))) void *)(lds + yb + q * YP), 16, lane * 16,
@@ -96,9 +109,16 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
     };
 
     // ---- weights: this wave's 32-channel chunk of every layer, two fragments per K step, a ring of eight steps
+    // An XCD's workgroups start together and would ask its L2 for the same lines, which come from beyond it, all at once.  So each begins at another
+    // tap and goes round, and at another quarter of the next block's layer (another order of the last layer's chunks changed nothing).  Tiles of 32 pixels,
+    // which need a tap's weights twice as soon, touch them all first instead: every wave its share, a 128-byte line per lane, workgroups without a tile
+    // included.  The 152-layer network, us, touched / from one place / in turn / touched and in turn: 8 images 713 / - / 764 / 718, 16 784 / 943 / 823 / 788,
+    // 32 930 / 1060 / 928 / 920; tiles of 64 pixels, 64 images 1345 / 1475 / 1315 / 1340, 96 1824 / - / 1799 / 1813; launches side by side are not touched for
+    // (2048 -> 2150 at two halves of 96).
+    const int place = NP > 1 ? (int)(blockIdx.x >> 3) : 0, t0 = (int)((unsigned)place % 9u), k0 = place & 3;
+    auto next_tap = [](int t, int n) { return t + n >= 9 ? t + n - 9 : t + n; };
     const uint8_t *const w2 = w2_packed + (size_t)wave * (S2 * kChunkBytes);
-    const uint8_t *const w3 = w3_packed + (size_t)wave * (4 * kChunkBytes);        // channels ch * 256 + ...: + ch * 32 steps
-    const uint8_t *const w1 = NEXT ? w1_packed + (size_t)wave * (S1 * kChunkBytes) : w2;
+    const uint8_t *w3 = nullptr, *w1 = nullptr;        // channels ch * 256 + ... of the last layer: + ch * 32 steps
     v4i ring[8][2];                                    // two groups of four steps
     // (through a descriptor of the four steps at p: the address costs scalar instructions only, 36 clocks per matrix instruction of a SIMD in
     // the K loops against 45 with 64-bit vector addresses)
@@ -110,10 +130,8 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
         ring[f >> 1][f & 1] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane16 + (f & 1) * 1024, ((f >> 1) & 3) * kChunkBytes, 0);
     };
 
-    // The launch's weights come from beyond the XCD's L2, and one workgroup's eight steps in flight do not cover that distance: at the start
-    // every wave touches its share of them, a 128-byte line per lane, workgroups without a tile included (the 152-layer network 1289 -> 1085 us
-    // at 32 images, 1690 -> 1600 at 64).  Not with launches side by side, which find them there: 2048 -> 2150 at two halves of 96.
-    // (in flight before the patch's copies, so they are over when those are; what they fetch lands in the skip operand's place before it does)
+    // (behind the patch's copies and before the ring's, so they are over when the ring's first fragments are here; what they fetch lands in the skip
+    // operand's place before it does)
     auto touch_weights = [&]() {
         constexpr int N2 = 8 * S2 * kChunkBytes / 8192, N3 = 32 * 4 * kChunkBytes / 8192, N1 = NEXT ? 8 * S1 * kChunkBytes / 8192 : 0;
         for (int i = (int)(blockIdx.x >> 3) * 8 + wave; i < N2 + N3 + N1; i += grid) {
@@ -181,20 +199,30 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
         ICNN_WAIT_VMCNT(0);
         return;
     }
+    // The patch, the biases and the ring are requested from arguments that are in registers when a wave starts, and nothing of it waits for the others, which
+    // come some 1500 clocks later: with those asked for in between the patch was requested at 3000 clocks of a tile's 38000 and all of it here
+    // at 7900, now at 900 and 5600.
     {
-        if (g.touch) touch_weights();
         issue_patch(tile_of(blockIdx.x) * PX);
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        in_registers(a2.bias, a3.bias, a3.res_mode, a2.H, a2.W, a2.div_howo.mul, a2.div_howo.s1, a2.div_howo.s2, a2.div_wo.mul, a2.div_wo.s1, a2.div_wo.s2, a3.res,
-                     a3.res_cs, ga.res_bytes);
-        if constexpr (NEXT) in_registers(a1.bias);
         int bv[3];                                     // requested before the ring, written to the table behind the ring's loads
 #pragma unroll
         for (int q = 0; q < 3; ++q) {
             const int i = tid + q * 512;
-            bv[q] = i < MID ? a2.bias[i] : (i < MID + C ? a3.bias[i - MID] : NEXT ? a1.bias[i - MID - C] : 0);
+            bv[q] = i < MID ? bias2[i] : (i < MID + C ? bias3[i - MID] : NEXT ? bias1[i - MID - C] : 0);
         }
+        if (g.touch) touch_weights();
+        auto read_arguments = [&]() __attribute__((always_inline)) {
+            ga = late_argument<TriArgs>(offsetof(TriKernelArgs, ga));
+            a2 = late_argument<ConvArgs>(offsetof(TriKernelArgs, a2));
+            a3 = late_argument<ConvArgs>(offsetof(TriKernelArgs, a3));
+            a1 = late_argument<ConvArgs>(offsetof(TriKernelArgs, a1));
+            has_res = a3.res_mode != 0;
+            w3 = late_argument<const uint8_t *>(offsetof(TriKernelArgs, w3)) + (size_t)wave * (4 * kChunkBytes);
+            w1 = NEXT ? late_argument<const uint8_t *>(offsetof(TriKernelArgs, w1)) + (size_t)wave * (S1 * kChunkBytes) : w2;
+        };
+        if constexpr (FORM == 2) read_arguments();
         [[maybe_unused]] int factor[3] = {0, 0, 0}, rescale[3] = {0, 0, 0}, position[3] = {0, 0, 0};
         [[maybe_unused]] bool mine = true;
         if constexpr (FORM == 2) {
@@ -210,10 +238,12 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
         }
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        const __amdgpu_buffer_rsrc_t rs0 = steps_at(w2), rs1 = steps_at(w2 + 4 * kChunkBytes);
+        const __amdgpu_buffer_rsrc_t rs0 = steps_at(w2 + t0 * (4 * kChunkBytes)), rs1 = steps_at(w2 + next_tap(t0, 1) * (4 * kChunkBytes));
         static_for<16>([&](auto f_tag) __attribute__((always_inline)) { load_frag(f_tag, decltype(f_tag)::value < 8 ? rs0 : rs1); });
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (FORM != 2) read_arguments();
+        in_registers(a3.res_mode, a2.H, a2.div_howo.mul, a2.div_howo.s1, a2.div_howo.s2, a2.div_wo.mul, a2.div_wo.s1, a2.div_wo.s2, a3.res, a3.res_cs, ga.res_bytes);
 #pragma unroll
         for (int q = 0; q < 3; ++q) btab[tid + q * 512] = bv[q];
         if constexpr (FORM == 2) {
@@ -239,10 +269,10 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
         int taps[NP];                                  // bit t: tap t of the pixel lies in its image
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
-            const int p = min(p0 + 32 * j + col, a2.M - 1);
-            const int r = p - fast_div(p, a2.div_howo) * (a2.H * a2.W);
-            const int y = fast_div(r, a2.div_wo), x = r - y * a2.W;
-            const int cols = (x > 0 ? 1 : 0) | 2 | (x + 1 < a2.W ? 4 : 0);
+            const int p = min(p0 + 32 * j + col, M - 1);
+            const int r = p - fast_div(p, a2.div_howo) * (a2.H * g.W);
+            const int y = fast_div(r, a2.div_wo), x = r - y * g.W;
+            const int cols = (x > 0 ? 1 : 0) | 2 | (x + 1 < g.W ? 4 : 0);
             taps[j] = (y > 0 ? cols : 0) | cols << 3 | (y + 1 < a2.H ? cols << 6 : 0);
         }
         asm volatile("" ::: "memory");
@@ -265,22 +295,23 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
             const int zero = g.rows * AP + half * 16;
             int centre[NP], ad[NP], nad[NP];
 #pragma unroll
-            for (int j = 0; j < NP; ++j) centre[j] = (slot(j) + a2.W + 1) * AP + half * 16;
+            for (int j = 0; j < NP; ++j) centre[j] = (slot(j) + g.W + 1) * AP + half * 16;
             auto tap = [&](int (&d)[NP], int t, int off) __attribute__((always_inline)) {
 #pragma unroll
                 for (int j = 0; j < NP; ++j) d[j] = (taps[j] >> t) & 1 ? centre[j] + off : zero;
             };
-            int off = -(a2.W + 1) * AP, kw = 0;
-            tap(ad, 0, off);
+            int kw = t0 % 3, tc = t0;
+            int off = ((t0 / 3 - 1) * g.W + kw - 1) * AP;
+            tap(ad, t0, off);
             first_frags(ad);
             auto one = [&](auto half_tag, int t) __attribute__((always_inline)) {
-                const int tn = t < 8 ? t + 1 : 8;      // (after the last tap: itself, read and not used)
                 if (t < 8) {
                     off += AP;
-                    if (++kw == 3) { kw = 0; off += (a2.W - 3) * AP; }
+                    if (++kw == 3) { kw = 0; off += (g.W - 3) * AP; }
+                    if (++tc == 9) { tc = 0; off = -(g.W + 1) * AP; }
                 }
-                tap(nad, tn, off);
-                group(half_tag, ad, nad, t < 7 ? w2 + (t + 2) * (4 * kChunkBytes) : w3 + (t - 7) * (32 * kChunkBytes));
+                tap(nad, tc, off);
+                group(half_tag, ad, nad, t < 7 ? w2 + next_tap(t0, t + 2) * (4 * kChunkBytes) : w3 + (t - 7) * (32 * kChunkBytes));
 #pragma unroll
                 for (int j = 0; j < NP; ++j) ad[j] = nad[j];
             };
@@ -289,6 +320,9 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
                 one(H0{}, t);
                 one(H1{}, t + 1);
             }
+            // (what the next phases want of the arguments: read here, under the last tap's products)
+            a3 = late_argument<ConvArgs>(offsetof(TriKernelArgs, a3));
+            a1 = late_argument<ConvArgs>(offsetof(TriKernelArgs, a1));
             one(H0{}, 8);
         }
         asm volatile("" ::: "memory");
@@ -322,7 +356,8 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
                 constexpr int oj = j == 0 ? NP - 1 : j - 1, nj = j + 1 < NP ? j + 1 : 0;
                 const bool old = !decltype(first_tag)::value || ch > 0;        // there is a group before it
                 init(c2[PAR], btab + MID + ch * MID);
-                const __amdgpu_buffer_rsrc_t rs = steps_at(ch + 2 < C / MID ? w3 + (ch + 2) * (32 * kChunkBytes) : w1 + (ch + 2 - C / MID) * (4 * kChunkBytes));
+                const __amdgpu_buffer_rsrc_t rs = steps_at(ch + 2 < C / MID ? w3 + (ch + 2) * (32 * kChunkBytes) : NEXT ? w1 + ((k0 + ch + 2 - C / MID) & 3) * (4 * kChunkBytes) :
+                                                            w2 + next_tap(t0, ch + 2 - C / MID) * (4 * kChunkBytes));
                 static_for<8>([&](auto h_tag) __attribute__((always_inline)) {
                     constexpr int h = decltype(h_tag)::value, hn = h + 3;
                     c2[PAR] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ring[R0 + (h >> 1)][h & 1], fr[h & 3], c2[PAR], 0, 0, 0);
@@ -356,7 +391,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
                     int l = lane;
                     asm volatile("" : "+v"(l));
                     const int q = (wave + 8 * ch) * 4 + (l >> 4), piece = (l & 15) * 16;
-                    if (ch < NP && q < PX && p0 + q < a2.M)
+                    if (ch < NP && q < PX && p0 + q < M)
                         *(v4i *)((uint8_t *)a2.out + (size_t)(p0 + q) * a2.out_cs + a2.out_co + piece) = *(const v4i *)(lds + q * AP + piece);
                 }
                 static_for<NP>([&](auto j_tag) __attribute__((always_inline)) {
@@ -379,7 +414,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
 
         // y leaves LDS one pixel's whole row per store
         auto store_y = [&](int q) __attribute__((always_inline)) {
-            if (q < PX && p0 + q < a2.M)
+            if (q < PX && p0 + q < M)
                 *(v4i *)((uint8_t *)a3.out + (size_t)(p0 + q) * a3.out_cs + a3.out_co + lane16) = *(const v4i *)(lds + yb + q * YP + lane16);
         };
         const int vn = v + grid;
@@ -389,16 +424,16 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
             int ad[NP], nad[NP];
 #pragma unroll
             for (int j = 0; j < NP; ++j) {
-                ad[j] = yb + slot(j) * YP + half * 16;
+                ad[j] = yb + slot(j) * YP + half * 16 + k0 * 256;
                 init(acc[j], btab + MID + C);
             }
             first_frags(ad);
             auto quarter = [&](auto half_tag, int k) __attribute__((always_inline)) {
 #pragma unroll
-                for (int j = 0; j < NP; ++j) nad[j] = k < 3 ? ad[j] + 256 : ad[j];
+                for (int j = 0; j < NP; ++j) nad[j] = k + k0 == 3 ? ad[j] - 768 : ad[j] + 256;
                 constexpr int PER = (PX + 31) / 32;
                 for (int c = k * PER; c < (k + 1) * PER; ++c) store_y(wave + 8 * c);
-                group(half_tag, ad, nad, (k < 2 ? w1 : w2 - 4 * (4 * kChunkBytes)) + (k + 2) * (4 * kChunkBytes));
+                group(half_tag, ad, nad, k < 2 ? w1 + ((k + k0 + 2) & 3) * (4 * kChunkBytes) : w2 + next_tap(t0, k - 2) * (4 * kChunkBytes));
 #pragma unroll
                 for (int j = 0; j < NP; ++j) ad[j] = nad[j];
             };
@@ -412,7 +447,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
                 constexpr int j = decltype(jc)::value;
                 const v4i w = finish(a1, H0{}, acc[j], v4i{0, 0, 0, 0}, a1.pc + (2 * wave + half) * kPcGroupInts, MID + C + co);
                 const int q = 32 * j + col;
-                if (q < PX && p0 + q < a2.M) *(v4i *)((uint8_t *)a1.out + (size_t)(p0 + q) * a1.out_cs + a1.out_co + co) = w;
+                if (q < PX && p0 + q < M) *(v4i *)((uint8_t *)a1.out + (size_t)(p0 + q) * a1.out_cs + a1.out_co + co) = w;
                 __builtin_amdgcn_sched_barrier(0);
             });
         } else {
@@ -446,6 +481,7 @@ bool tri_shape(long long M, int W, int np, TriArgs &g)
 {
     const int px = tri_pixels(np);
     g.np = np;
+    g.touch = 0;
     g.W = W;
     g.rows = px + 2 * (W + 1);
     g.patch_bytes = ((g.rows + 1) * 17 + 63) / 64 * 1024;
@@ -465,8 +501,8 @@ bool tri_shape(long long M, int W, int np, TriArgs &g)
 bool conv_tri_plan(long long M, int W, int lanes, TriArgs &g)
 {
     if (M < 1 || M > 0x7fffffffLL - 256 || W > 1000) return false;
-    g.touch = lanes == 1;
-    if (g_tuning.tri_tile) return tri_shape(M, W, g_tuning.tri_tile, g);
+    auto touch = [&]() { g.touch = lanes == 1 && g.np == 1; return true; };
+    if (g_tuning.tri_tile) return tri_shape(M, W, g_tuning.tri_tile, g) && touch();
     static const int cost[5] = {0, 14, 19, 25, 31};
     long long best = -1;
     TriArgs t = g;
@@ -482,7 +518,7 @@ bool conv_tri_plan(long long M, int W, int lanes, TriArgs &g)
             g = t;
         }
     }
-    return best >= 0;
+    return best >= 0 && touch();
 }
 
 // a1: the next block's first layer, or null.  The caller has checked widths (256 -> 256 -> 1024 -> 256), kinds and alignment.
@@ -507,9 +543,9 @@ hipError_t launch_conv_tri(const TriArgs &g, const ConvArgs &a2, const ConvArgs 
     auto go = [&](auto kernel) -> hipError_t {
         const hipError_t e = allow_large_lds((const void *)kernel);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)slots), dim3(512), lds_bytes, st, a2.x, a2.wp, a3.wp, a1 ? a1->wp : a2.wp, a2.M, a2.in_cs,
-                           (unsigned)g.W | (unsigned)g.rows << 10 | (unsigned)(g.patch_bytes / 1024) << 21 | (g.touch ? 1u << 29 : 0u), (unsigned)g.n_tiles, slots, q, b2, a3,
-                           a1 ? *a1 : a2);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)slots), dim3(512), lds_bytes, st, a2.x, a2.wp, a2.bias, a3.bias, a1 ? a1->bias : a2.bias, a2.M, a2.in_cs,
+                           (unsigned)g.W | (unsigned)g.rows << 10 | (unsigned)(g.patch_bytes / 1024) << 21 | (g.touch ? 1u << 29 : 0u), (unsigned)g.n_tiles, slots, a3.wp,
+                           a1 ? a1->wp : a2.wp, q, b2, a3, a1 ? *a1 : a2);
         return hipGetLastError();
     };
     auto by_form = [&](auto np_tag, auto next_tag) {

@@ -135,6 +135,15 @@ def smallest_tile():
     B.icnn_set_tuning("reset")
 
 
+# workgroups that begin at different taps, one to all nine of them and more (the last block has no next layer: what it fetches ahead is its own next
+# tile's first taps)
+@pytest.mark.parametrize("tiles", [1, 8, 9, 72, 73, 255, 257, 300])
+def test_where_the_weights_begin(tiles, tile):
+    check(1, tiles * PIXELS[tile] // 16, 16)
+    if tiles > 255:
+        check(1, tiles * PIXELS[tile] // 16, 16, third=False)
+
+
 def test_the_widest_image(smallest_tile):
     from paper_2006_11735_amd import binding as B
     assert fits(1, 210) and not fits(1, 211)

@@ -141,6 +141,7 @@ const char *icnn_last_error(void);
  *   "plane_always" 1 lets the kernel with two-dimensional tiles (few channels, large pictures) take every layer it accepts
  *   "deep_always" 1 lets the 3x3 kernel whose waves split the K axis take every layer whose shape it accepts
  *   "deep_plain_walk" 1 gives that kernel the tile order of the other kernels (pixel tiles, not channel tiles, per XCD)
+ *   "keep"        0 library's choice; 1 / 2: every / no layer whose shape it takes on the 3x3 kernel that keeps 64 channels' weights in registers
  *   "flat"        0 library's choice; 1 / 2: every / no layer whose shape it takes on the kernel that streams weights into registers
  *   "tri_tile"    0 library's choice; 1..4 = the 3x3 + 1x1 + 1x1 kernel at any size, in tiles of 32, 64, 96 or 112 pixels
  *   "ksplit"      0, 1 never split the K axis over workgroups (the library's choice); 2..8 that split where it divides the K steps

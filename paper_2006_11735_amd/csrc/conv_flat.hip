@@ -335,10 +335,20 @@ static bool flat_takes(const ConvArgs &a, bool direct_ok)
     return flat_shape(a, g, lds_bytes);
 }
 
+// A layer of 64 channels whose tiles are all on the chip at once, three to a compute unit.  Against two-dimensional tiles (there / here; smaller layers are level): 16, 20, 24
+// and 31 images of 56 x 56 5.8 / 5.1, 8.1 / 5.6, 8.5 / 6.8, 8.8 / 7.0; 256 x 256 6.4 / 6.2, two of 200 x 200 8.5 / 7.1; with two to a unit, 300 x 300, 8.6 / 8.9; in two rounds
+// 400 x 400 11.7 / 13.8.
+static bool flat_one_round(const ConvArgs &a)
+{
+    FlatArgs g;
+    size_t lds_bytes;
+    return a.Cout == 64 && a.M > 45056 && a.M <= 768 * 128 && flat_shape(a, g, lds_bytes) && 3 * lds_bytes <= 160 * 1024;
+}
+
 // Every layer it takes but two kinds (microseconds the other kernel / this one, weights and maps cold in L2).  Those of few enough pixels for the
 // few-pixel kernel: the rule and its figures stand beside it (conv_lat_before_flat).  Layers of 64 channels on large
-// pictures are level with the two-dimensional tiles that keep weights and patch in LDS (16 / 32 / 64 images of 56 x 56: 6.2 / 6.2, 9.2 / 9.9,
-// 14.7 / 14.6; with a skip operand 64 images 17.5 / 16.1).  The others: 3x3 of 256 channels on 14 x 14, 16 / 32 / 64 / 128 images 9.9 / 6.8, 11.4 / 7.4,
+// pictures go to the kernel that keeps their weights (conv_keep_applies) or to two-dimensional tiles, but for one round of this kernel's workgroups
+// (flat_one_round).  The others: 3x3 of 256 channels on 14 x 14, 16 / 32 / 64 / 128 images 9.9 / 6.8, 11.4 / 7.4,
 // 13.2 / 10.8, 22.5 / 18.9; of 512 on 7 x 7, 64 images 14.3 / 10.7; of 128 on 28 x 28, 9 / 64 images 8.4 / 5.5, 16.1 / 12.6; 256 -> 1024 on 14 x 14,
 // 9 / 64 images 5.4 / 3.9, 13.0 / 9.5; 512 -> 256 on 28 x 28, 9 / 64 images 6.1 / 4.6, 16.1 / 14.1; 128 -> 512, 15.6 / 11.2; 1024 -> 512 and 512 -> 128
 // within 4 % where they have 12544 and 50176 pixels, 9 % faster at 9408.  Stride 2, 64 images: 3x3 of 128 channels on 56 x 56 16.1 / 15.3, of 256 on
@@ -354,7 +364,7 @@ bool conv_flat_applies(const ConvArgs &a, bool direct_ok)
         g_tuning.plane_always || g_tuning.lat || !flat_takes(a, direct_ok))
         return false;
     if (a.Cin == 2048 && (long long)(a.Cout / 128) * ((a.M + 63) / 64) > 256) return false;
-    return a.pc || a.res_mode != 0 || g_tuning.no_plane || !conv_plane_applies(a);
+    return a.pc || a.res_mode != 0 || g_tuning.no_plane || !conv_plane_applies(a) || flat_one_round(a);
 }
 
 hipError_t launch_conv_flat(const ConvArgs &args, hipStream_t st)

@@ -808,6 +808,7 @@ hipError_t launch_conv(const ConvArgs &a, bool vec_in, bool direct_ok, hipStream
     if (direct_ok && conv_narrow_applies(a) && !g_tuning.no_narrow)
         return launch_conv_narrow(a, st);
     // weights straight into registers, the input's patch in LDS
+    if (direct && conv_keep_applies(a, direct_ok)) return launch_conv_keep(a, st);
     if (direct && conv_flat_applies(a, direct_ok)) return launch_conv_flat(a, st);
     // few pixels: the waves split the K axis straight from global memory
     if (direct && conv_lat_applies(a)) return launch_conv_lat(a, st);

@@ -237,6 +237,7 @@ struct Tuning {
     int no_block128 = 0;   // fused bottleneck blocks of 512 -> 128 -> 512 channels: the LDS-ring kernel instead of the one of small workgroups
     int no_block64s = 0;   // fused bottleneck blocks of 256 -> 64 -> 256 channels: the kernel with resident weights instead of the one of small workgroups
     int no_block64 = 0;    // fused bottleneck blocks with 64 middle channels: the LDS-ring kernel instead of the register-resident one
+    int keep = 0;          // 3x3 layers of 64 channels with their weights kept in registers: 1 every layer that kernel accepts, 2 none
     int flat = 0;          // kernel with register-fed weights: 1 every layer whose shape it accepts, 2 none
     int tri_tile = 0;      // 3x3 + 1x1 + 1x1 kernel: 1..4 = tiles of 32, 64, 96 or 112 pixels
     int ksplit = 0;        // 0, 1 the K axis stays whole (the library's choice); 2..8 this split where it divides the K steps
@@ -268,6 +269,8 @@ bool conv_tail_ok(const ConvArgs &a, const ConvArgs &b, const ConvArgs &c);
 hipError_t launch_conv_tail(const ConvArgs &a, const ConvArgs &b, const ConvArgs &c, hipStream_t st);
 bool conv_flat_dual_applies(const ConvArgs &a, const ProjArgs &q);
 hipError_t launch_conv_flat_dual(const ConvArgs &a, const ProjArgs &q, hipStream_t st);
+bool conv_keep_applies(const ConvArgs &a, bool direct_ok);
+hipError_t launch_conv_keep(const ConvArgs &a, hipStream_t st);
 bool conv_flat_applies(const ConvArgs &a, bool direct_ok);
 hipError_t launch_conv_flat(const ConvArgs &a, hipStream_t st);
 bool conv_deep_applies(const ConvArgs &a);

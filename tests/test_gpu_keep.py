@@ -1,0 +1,66 @@
+"""The 3x3 kernel of 64 -> 64 channels that keeps its weights in registers, at the edges of its rounds, tiles and pictures and in the forms it takes, against
+the oracle; calls that it leaves to the others; and the library's choice."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from test_gpu_flat import check, layer
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture
+def keep():
+    from paper_2006_11735_amd import binding as B
+    B.icnn_set_tuning("keep", 1)
+    yield
+    B.icnn_set_tuning("reset")
+
+
+def skip_of(g, n, h, w):
+    return dict(res=g.integers(0, 128, size=(n, h, w, 64), dtype=np.uint8), res_mode="pre", res_mul=20000, res_shift=5)
+
+
+# one pixel, rounds of 128 pixels less and more one, a row, a column, many small pictures, rows of all widths up to the widest it takes, several rounds and
+# tiles a workgroup and some with one more than the others
+@pytest.mark.parametrize("shape", [(1, 1, 1), (1, 1, 126), (1, 127, 1), (1, 16, 8), (1, 43, 3), (300, 2, 3), (130, 1, 1), (5, 7, 7), (3, 14, 14), (2, 28, 28), (1, 56, 56),
+                                   (3, 9, 126), (2, 31, 57), (1, 112, 112), (11, 56, 56), (700, 7, 7), (90, 28, 29)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("skip", [False, True], ids=["plain", "skip"])
+def test_tiles(keep, shape, skip):
+    g, x, wt, b = layer(sum(shape), *shape, 64, 64, 3)
+    check(x, wt, b, mul=32767, shift=25, **(skip_of(g, *shape) if skip else {}))
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(out_mode="linear_s8"), dict(out_mode="clamp_u8", lo=3, hi=250), dict(bound_q=15), dict(mul=20001, shift=24), dict(mul=1, shift=9)], ids=str)
+@pytest.mark.parametrize("skip", [False, True], ids=["plain", "skip"])
+@pytest.mark.parametrize("inputs", ["unsigned", "signed", "pitch"])
+def test_forms(keep, kw, skip, inputs):
+    g, x, wt, b = layer(7, 2, 19, 23, 64, 64, 3, pitch=32 if inputs == "pitch" else 0, signed=inputs == "signed")
+    check(x, wt, b, **kw, **(skip_of(g, 2, 19, 23) if skip else {}))
+
+
+# what it does not take goes where it went before: too wide a picture, int32 sums, other operands, a wide multiplier, parameters per channel, inputs up to 255
+@pytest.mark.parametrize("how", ["wide", "raw", "s8", "post", "multiplier", "channels"])
+def test_left_to_the_others(keep, how):
+    from test_gpu_conv import channel_params
+    n, h, w = (1, 5, 127) if how == "wide" else (2, 11, 13)
+    g, x, wt, b = layer(3, n, h, w, 64, 64, 3)
+    more = {"wide": {}, "raw": dict(out_mode="raw_s32"), "multiplier": dict(mul=2**31 - 1, shift=43), "channels": channel_params(3, 64),
+            "s8": dict(res=g.integers(-128, 128, size=(n, h, w, 64)).astype(np.int8), res_mode="pre", res_mul=20000, res_shift=5),
+            "post": dict(res=g.integers(0, 128, size=(n, h, w, 64), dtype=np.uint8), res_mode="post", res_mul=20000, res_shift=15)}[how]
+    check(x, wt, b, **more)
+
+
+# the library's choice on both sides of its lines: one round of another kernel's workgroups, and beyond
+@pytest.mark.parametrize("shape", [(44, 32, 32), (45, 32, 32), (96, 32, 32), (97, 32, 32), (1, 400, 246), (1, 262, 263)], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("skip", [False, True], ids=["plain", "skip"])
+def test_the_librarys_choice(shape, skip):
+    from gpu_util import gpu_conv2d
+    from paper_2006_11735_amd import binding as B
+    g, x, wt, b = layer(2, *shape, 64, 64, 3)
+    kw = dict(pad=1, mul=20000, shift=25, **(skip_of(g, *shape) if skip else {}))
+    got = gpu_conv2d(x, wt, b, **kw)
+    B.icnn_set_tuning("tile", 1)                       # the tap-by-tap kernel
+    want = gpu_conv2d(x, wt, b, **kw)
+    B.icnn_set_tuning("reset")
+    assert got.max() > got.min() and (got == want).all()

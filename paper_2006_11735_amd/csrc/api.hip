@@ -334,6 +334,7 @@ static int fill_conv_args(const icnn_conv_desc *d, const ConvGeom &g, const void
         a.rq_fast = 1;
         a.mul_hi = (int)((long long)a.mul << (32 - a.shift));
     }
+    a.rq_byte = requant_fits_byte(a);
     a.rq24 = a.t_hi = a.rnd = a.rqh = 0;
     if (d->out_mode != ICNN_OUT_RAW_S32 && a.lo == 0 && a.hi >= 0 && a.shift >= 1 && a.shift <= 33 && a.mul >= 1 &&
         a.mul < (1 << 24)) {

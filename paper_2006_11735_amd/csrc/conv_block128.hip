@@ -28,8 +28,8 @@ constexpr int kB128XP = kB128Wide + 16, kB128AP = kB128Mid + 16;
 constexpr int kB128XBytes = (kB128Rows * (kB128XP / 16) + 63) / 64 * 1024;
 
 // HI: the three layers requantise as a product's high word (rq_fast) and the skip operand is rescaled likewise (g.sk), the last layer's
-// epilogue dealt out between matrix instructions; else any 8-bit form
-template <bool HI>
+// epilogue dealt out between matrix instructions; else any 8-bit form.  BYTE: HI, and all of them to bytes (requant_fits_byte)
+template <bool HI, bool BYTE>
 __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x, const uint8_t *w1_packed, const unsigned hw, const unsigned shape, const int x_cs,
                                                                const int n_tiles, const int tiles_per_img, const unsigned mul_tpi, const int tiles_x,
                                                                const unsigned mul_tx, const unsigned shifts, const unsigned inv_pw, const BlockArgs ga,
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
 
     const int co = wave * 32 + half * 16;              // this lane's sixteen channels inside the 128 of a phase
     auto finish = [&](const ConvArgs &a, const v16i &c) __attribute__((always_inline)) {
-        if constexpr (HI) return epilogue_hi16<0>(a, sk, c, v4i{0, 0, 0, 0});
+        if constexpr (HI) return epilogue_hi16<0, BYTE>(a, sk, c, v4i{0, 0, 0, 0});
         else return epilogue_bytes16<0>(a, c, v4i{0, 0, 0, 0});
     };
     // Group K of the ring on NJ pixel groups: row addresses ad, the group's 128 channels at `at` bytes into the row; behind every matrix
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
                 __builtin_amdgcn_sched_barrier(0);
                 fr[hn & 3] = *(const v4i *)(lds + ad0 + (hn < 4 ? j : j ^ 1) * (32 * AP) + (hn & 3) * 32);
                 if constexpr (h == 1) r8[j] = *(const v4i *)(lds + prow[j] * XP + ch * MID + co);
-                if constexpr (HI && i > 0) epilogue_hi_slice<1, 4 * h, 4>(a3, sk, c2[j ^ 1], r8[j ^ 1], w);
+                if constexpr (HI && i > 0) epilogue_hi_slice<1, 4 * h, 4, BYTE>(a3, sk, c2[j ^ 1], r8[j ^ 1], w);
                 __builtin_amdgcn_sched_barrier(0);
             });
             if constexpr (HI) {
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
             __builtin_amdgcn_sched_barrier(0);
         });
         if constexpr (HI) {
-            const v4i o = epilogue_hi16<1>(a3, sk, c2[1], r8[1]);
+            const v4i o = epilogue_hi16<1, BYTE>(a3, sk, c2[1], r8[1]);
             if (in[1]) *(v4i *)(lds + prow[1] * XP + 3 * MID + co) = o;
         }
     }
@@ -314,7 +314,8 @@ hipError_t launch_conv_block128(const BlockArgs &g, const ConvArgs &a1, const Co
         return hipGetLastError();
     };
     const bool hi = a1.rq_fast && a2.rq_fast && a3.rq_fast && (a3.res_mode == 0 || sk.ok) && !g_tuning.block_any_form;
-    return hi ? go(conv_block128_kernel<true>) : go(conv_block128_kernel<false>);
+    if (hi && requant_fits_byte(a1) && requant_fits_byte(a2) && requant_fits_byte(a3)) return go(conv_block128_kernel<true, true>);
+    return hi ? go(conv_block128_kernel<true, false>) : go(conv_block128_kernel<false, false>);
 }
 
 }  // namespace icnn

@@ -31,7 +31,8 @@ constexpr int kB64sRows = 96, kB64sPix = 64;           // patch rows, output pix
 constexpr int kB64sXP = kB64sWide + 16, kB64sAP = kB64sMid + 16;      // row pitches: padded as in conv_tri.hip
 constexpr int kB64sXBytes = (kB64sRows * (kB64sXP / 16) + 63) / 64 * 1024;
 
-// The three layers requantise as a product's high word (rq_fast) and the skip operand is rescaled likewise (sk)
+// The three layers requantise as a product's high word (rq_fast) and the skip operand is rescaled likewise (sk).  BYTE: all of them to bytes (requant_fits_byte)
+template <bool BYTE>
 __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *const x, const uint8_t *const wp1, const uint8_t *const wp2,
                                                                const uint8_t *const wp3, const int32_t *const bias1, const int32_t *const bias2,
                                                                const int32_t *const bias3, const BlockArgs g, const SkipMul sk, const ConvArgs a1,
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
         mfma_drain(acc);
         const int py = (int)(((unsigned)row * g.inv_pw) >> 16), px = row - py * g.PW;
         const int iy = y0 - 1 + py, ix = x0 - 1 + px;
-        v4i w = epilogue_hi16<0>(a1, sk, acc, v4i{0, 0, 0, 0});
+        v4i w = epilogue_hi16<0, BYTE>(a1, sk, acc, v4i{0, 0, 0, 0});
         if (!((unsigned)iy < (unsigned)g.H && (unsigned)ix < (unsigned)g.W)) w = v4i{0, 0, 0, 0};
         *(v4i *)(abuf + row * AP + c12 * 32 + half * 16) = w;
         __builtin_amdgcn_sched_barrier(0);
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
         });
         sync();                                        // every wave has its last fragments of a: b may overwrite it
         mfma_drain(acc);
-        *(v4i *)(abuf + (32 * pg + col) * AP + c12 * 32 + half * 16) = epilogue_hi16<0>(a2, sk, acc, v4i{0, 0, 0, 0});   // slots beyond the tile hold values nobody stores
+        *(v4i *)(abuf + (32 * pg + col) * AP + c12 * 32 + half * 16) = epilogue_hi16<0, BYTE>(a2, sk, acc, v4i{0, 0, 0, 0});   // slots beyond the tile hold values nobody stores
     }
     sync();
 
@@ -259,7 +260,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
             constexpr int i = decltype(i_tag)::value, c = i >> 1, j = i & 1;
             if constexpr (i < 3) multiply(std::integral_constant<int, i + 1>{});
             mfma_drain(acc[j]);
-            const v4i o = epilogue_hi16<1>(a3, sk, acc[j], r8[j]);
+            const v4i o = epilogue_hi16<1, BYTE>(a3, sk, acc[j], r8[j]);
             if (in[j]) *(v4i *)(xb + prow[j] * XP + (2 * wave + c) * 32 + half * 16) = o;
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -316,7 +317,8 @@ hipError_t launch_conv_block64s(const BlockArgs &g, const ConvArgs &a1, const Co
     const size_t lds_bytes = 2 * kB64sXBytes + kB64sRows * kB64sAP + (2 * kB64sMid + kB64sWide) * 4 + 2 * 128 * 4;
     static_assert(2 * kB64sXBytes + kB64sRows * kB64sAP + (2 * kB64sMid + kB64sWide) * 4 + 2 * 128 * 4 <= 64 * 1024, "no permission needed");
     const SkipMul sk = a3.res_mode ? make_skip_mul(a3.res_mul, a3.res_shift) : SkipMul{0, 0, 0};     // (without an operand: adds zero)
-    hipLaunchKernelGGL(conv_block64s_kernel, dim3((unsigned)std::min(8 * gx.per_xcd, 512)), dim3(256), lds_bytes, st, gx.x, a1.wp, a2.wp, a3.wp, a1.bias, a2.bias, a3.bias, gx,
+    const auto kernel = requant_fits_byte(a1) && requant_fits_byte(a2) && requant_fits_byte(a3) ? conv_block64s_kernel<true> : conv_block64s_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(8 * gx.per_xcd, 512)), dim3(256), lds_bytes, st, gx.x, a1.wp, a2.wp, a3.wp, a1.bias, a2.bias, a3.bias, gx,
                        sk, a1, a2, a3);
     return hipGetLastError();
 }

@@ -140,8 +140,8 @@ __global__ __launch_bounds__(512, 1) void conv_chain_kernel(const uint8_t *x, co
     // fragments on their way.  LAST: the tile goes to memory, else to the other buffer.
     auto layer = [&](auto last_tag, const int l) __attribute__((always_inline)) {
         constexpr bool LAST = decltype(last_tag)::value;
-        struct { int mul, shift, lo, hi, rq_fast, mul_hi, rq24, t_hi, rnd, rqh; } a = {g.l[l].mul, g.l[l].shift, g.l[l].lo, g.l[l].hi, g.l[l].rq_fast,
-                                                                                     g.l[l].mul_hi, g.l[l].rq24, g.l[l].t_hi, g.l[l].rnd, g.l[l].rqh};
+        struct { int mul, shift, lo, hi, rq_fast, mul_hi, rq24, t_hi, rnd, rqh, rq_byte; } a = {g.l[l].mul, g.l[l].shift, g.l[l].lo, g.l[l].hi, g.l[l].rq_fast,
+                                                                                     g.l[l].mul_hi, g.l[l].rq24, g.l[l].t_hi, g.l[l].rnd, g.l[l].rqh, 0};
         unsigned inv = g.inv[l], xout = LAST ? 0u : g.l[l + 1].xin;
         asm volatile("" : "+s"(a.lo), "+s"(a.hi), "+s"(a.mul_hi), "+s"(inv), "+s"(xout));
         if (l + 2 < L) issue_weights(l + 2, g.l[l + 2].wp);        // (its place's weights are in every wave's registers since the last barrier)

@@ -125,7 +125,8 @@ __device__ __forceinline__ void shift_into_byte(int &w, uint32_t x, int sh_v, in
 // (Section 3.2.1).  RQ as in epilogue_vec: 1 one 32x32->64 multiply-add whose high word is the result;
 // 2 general 64-bit multiply, add, shift; 3 in 32 bits after clamping t to [0, t_hi] (see ConvArgs::rq24); 4 likewise with the
 // high half of a 24-bit product (see ConvArgs::rqh).  (Form 4 in place of form 1 in every kernel measured slower, the nine-image
-// network 341 -> 354 us; it serves kernels that deal an epilogue out between matrix instructions, where form 1's word pairs do not fit.)
+// network 341 -> 354 us; it serves kernels that deal an epilogue out between matrix instructions, where form 1's word pairs do not fit.)  5 bytes
+// (requant_fits_byte), as in epilogue_hi_slice.
 // (P: ConvArgs, or any struct with the same requantisation fields)
 template <int RQ, class P>
 __device__ __forceinline__ v4i requant16(const P &a, const int (&t)[16])
@@ -154,6 +155,19 @@ __device__ __forceinline__ v4i requant16(const P &a, const int (&t)[16])
         }
         return v4i{w[0], w[1], w[2], w[3]};
     }
+    if (RQ == 5) {
+        typedef short i16x2 __attribute__((ext_vector_type(2)));
+        const int m = a.mul_hi << 8;
+        uint32_t two[8];
+#pragma unroll
+        for (int r = 0; r < 16; r += 2)
+            two[r / 2] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, __builtin_amdgcn_cvt_pk_i16((int)(((int64_t)t[r] * m + 0x8000000000LL) >> 32),
+                                                                                    (int)(((int64_t)t[r + 1] * m + 0x8000000000LL) >> 32))), i16x2{0, 0}));
+        v4i w;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[q] = (int)__builtin_amdgcn_perm(two[2 * q + 1], two[2 * q], 0x07050301u);
+        return w;
+    }
     int v[16];
     const int lo_v = a.lo;
 #pragma unroll
@@ -173,6 +187,7 @@ __device__ __forceinline__ v4i requant16(const P &a, const int (&t)[16])
 template <class P>
 __device__ __forceinline__ v4i requant16_any(const P &a, const int (&t)[16])
 {
+    if (a.rq_byte) return requant16<5>(a, t);
     if (a.rq24) return requant16<3>(a, t);
     if (a.rq_fast) return requant16<1>(a, t);
     return requant16<2>(a, t);
@@ -618,12 +633,15 @@ __device__ __forceinline__ void epilogue_rq24_slice(const P &a, const v16i &acc,
 // 4.8 with two waves per SIMD and matrix instructions between them), so a product whose high word is the result wants no shift behind it.
 // Step by step for the N values together, so that none waits for the instruction just before it.
 // w: the words of the sixteen bytes, which the caller collects over its slices; a word's lower half is kept in it until the upper one comes.
-template <int RES, int R0, int N, class P>
+// BYTE (requant_fits_byte): bytes from 0 to 127 by a multiplier below 2^23.  The product is taken 2^8 times as large, so that the saturating conversion to 16 bits is
+// the upper clamp, one packed maximum the lower one of two outputs, and the result the upper byte: two and a quarter instructions in place of
+// two and three quarters.
+template <int RES, int R0, int N, bool BYTE = false, class P>
 __device__ __forceinline__ void epilogue_hi_slice(const P &a, const SkipMul &sk, const v16i &acc, const v4i &res8, int (&w)[4])
 {
     static_assert(N % 2 == 0 && R0 % 2 == 0, "whole pairs");
     int t[N];
-    const int lo_v = a.lo;
+    [[maybe_unused]] const int lo_v = a.lo;
     if constexpr (RES == 1) {
         uint32_t x[N];
         // byte in the top bits, the rounding constant below it
@@ -641,6 +659,26 @@ __device__ __forceinline__ void epilogue_hi_slice(const P &a, const SkipMul &sk,
 #pragma unroll
         for (int e = 0; e < N; ++e) t[e] = acc[R0 + e];
     }
+    if constexpr (BYTE) {
+        typedef short i16x2 __attribute__((ext_vector_type(2)));
+        const int m = a.mul_hi << 8;
+#pragma unroll
+        for (int e = 0; e < N; ++e) t[e] = (int)(((int64_t)t[e] * m + 0x8000000000LL) >> 32);
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t two[N / 2];
+#pragma unroll
+        for (int e = 0; e < N; e += 2) two[e / 2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pk_i16(t[e], t[e + 1]));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < N; e += 2) two[e / 2] = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, two[e / 2]), i16x2{0, 0}));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < N; e += 2) {
+            if (((R0 + e) & 2) == 0) w[(R0 + e) >> 2] = (int)two[e / 2];
+            else w[(R0 + e) >> 2] = (int)__builtin_amdgcn_perm(two[e / 2], (uint32_t)w[(R0 + e) >> 2], 0x07050301u);
+        }
+        return;
+    }
 #pragma unroll
     for (int e = 0; e < N; ++e) t[e] = (int)(((int64_t)t[e] * a.mul_hi + 0x80000000LL) >> 32);
     __builtin_amdgcn_sched_barrier(0);
@@ -654,13 +692,13 @@ __device__ __forceinline__ void epilogue_hi_slice(const P &a, const SkipMul &sk,
         else w[(R0 + e) >> 2] = (int)__builtin_amdgcn_perm(two, (uint32_t)w[(R0 + e) >> 2], 0x05040100u);
     }
 }
-template <int RES, class P>
+template <int RES, bool BYTE = false, class P>
 __device__ __forceinline__ v4i epilogue_hi16(const P &a, const SkipMul &sk, const v16i &acc, const v4i &res8)
 {
     int w[4];
-    epilogue_hi_slice<RES, 0, 8>(a, sk, acc, res8, w);
+    epilogue_hi_slice<RES, 0, 8, BYTE>(a, sk, acc, res8, w);
     __builtin_amdgcn_sched_barrier(0);
-    epilogue_hi_slice<RES, 8, 8>(a, sk, acc, res8, w);
+    epilogue_hi_slice<RES, 8, 8, BYTE>(a, sk, acc, res8, w);
     return v4i{w[0], w[1], w[2], w[3]};
 }
 // The same per output channel, from tables of a factor (pc_prepack_kernel's A) and of the skip rescale's multiplier and byte position (pc_hi_channel):

@@ -45,7 +45,7 @@ constexpr int kFlatTables = 4 * 72 * 4;                // of four waves' 32 chan
 constexpr int kFlatSums = 4 * 32 * (32 * 4 + 16);      // 32 pixels' int32 sums of four waves
 
 // KK: kernel size; NG groups of G steps: cin = 64 G NG / KK^2.  FORM: 1 requantisation as a product's high word (rq_fast), an unsigned 8-bit skip
-// operand before it rescaled likewise (g.sk) or none, 8-bit output; 0 any form of one pair per layer; 2 per output channel; 3 as 1 with an int32
+// operand before it rescaled likewise (g.sk) or none, 8-bit output; 5 as 1, to bytes (requant_fits_byte); 0 any form of one pair per layer; 2 per output channel; 3 as 1 with an int32
 // skip operand; 4 int32 sums.
 // S: stride, both ways.
 template <int KK, int NG, int G, int WC, int FORM, int S>
@@ -58,6 +58,7 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const uint8_t *x, con
     constexpr int CIN = 64 * G * NG / (KK * KK), GP = NG / (KK * KK);      // groups per tap
     constexpr int AP = CIN + 16, PIECES = AP / 16, PX = 64 * (4 / WC), NS = 8 / G;
     constexpr int T = NG * G;                          // K steps
+    constexpr bool HI = FORM == 1 || FORM == 5, BYTE = FORM == 5;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const uint8_t *x, con
     if constexpr (S == 1) start_ring();
     in_registers(a.Ho, a.Wo, a.H, a.div_howo.mul, a.div_howo.s1, a.div_howo.s2, a.div_wo.mul, a.div_wo.s1, a.div_wo.s2, a.res_mode, a.res, a.res_cs, a.out, a.out_cs,
                  a.out_co, a.lo, a.hi);
-    if constexpr (FORM == 1) in_registers(a.mul_hi, g.sk.k, g.sk.rnd);
+    if constexpr (HI) in_registers(a.mul_hi, g.sk.k, g.sk.rnd);
     if (tid < WC * 32) btab[tid] = bv;
     if constexpr (FORM == 2) {
         ptab[lane] = half ? rescale : factor;
@@ -186,7 +187,7 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const uint8_t *x, con
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 res32[j][i] = *(const v4i *)((const int32_t *)a.res + ((size_t)min(pw + 32 * j + 8 * i + (lane >> 3), M - 1) * a.res_cs + co_wave + 4 * (lane & 7)));
-    } else if constexpr (FORM == 1) {
+    } else if constexpr (HI) {
         if (a.res_mode != 0) {
 #pragma unroll
             for (int j = 0; j < 2; ++j)
@@ -288,10 +289,10 @@ __global__ __launch_bounds__(256, 2) void conv_flat_kernel(const uint8_t *x, con
             const v4i w = epilogue_skip_s32(a, acc[0][j], r);
             if (p0 + q[j] < M) *(v4i *)((uint8_t *)a.out + (size_t)(p0 + q[j]) * a.out_cs + a.out_co + co_wave + half * 16) = w;
         }
-    } else if constexpr (FORM == 1) {
+    } else if constexpr (HI) {
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-            const v4i w = a.res_mode != 0 ? epilogue_hi16<1>(a, g.sk, acc[0][j], res8[0][j]) : epilogue_hi16<0>(a, g.sk, acc[0][j], v4i{0, 0, 0, 0});
+            const v4i w = a.res_mode != 0 ? epilogue_hi16<1, BYTE>(a, g.sk, acc[0][j], res8[0][j]) : epilogue_hi16<0, BYTE>(a, g.sk, acc[0][j], v4i{0, 0, 0, 0});
             if (p0 + q[j] < M) *(v4i *)((uint8_t *)a.out + (size_t)(p0 + q[j]) * a.out_cs + a.out_co + co_wave + half * 16) = w;
         }
     } else if constexpr (FORM == 2) {
@@ -383,7 +384,7 @@ hipError_t launch_conv_flat(const ConvArgs &args, hipStream_t st)
     const bool by_pt = a.n_ct > 1 && wt * 8 + in > wt * std::max(8 / a.n_ct, 1) + in * std::min(a.n_ct, 8);
     g.sk = SkipMul{0, 0, 0};
     if (a.res_mode == 1 && a.res_dtype == 0) g.sk = make_skip_mul(a.res_mul, a.res_shift);
-    const int form = a.pc ? 2 : a.rq_fast && a.epi_vec && (a.res_mode == 0 || g.sk.ok) ? 1 : 0;
+    const int form = a.pc ? 2 : a.rq_fast && a.epi_vec && (a.res_mode == 0 || g.sk.ok) ? requant_fits_byte(a) ? 5 : 1 : 0;
     const FastDiv by = make_fast_div((unsigned)(by_pt ? a.n_tiles / a.n_ct : a.n_ct));
     const FlatFirst f = {a.x, a.wp, a.bias, a.pc, a.M, a.in_cs, (unsigned)g.rows | (unsigned)(g.patch_bytes / 1024) << 11 | (unsigned)a.W << 19, by.mul,
                          (unsigned)a.n_ct | by.s1 << 16 | by.s2 << 24 | (by_pt ? 1u << 30 : 0u) | (a.res_mode ? 1u << 31 : 0u)};
@@ -396,7 +397,7 @@ hipError_t launch_conv_flat(const ConvArgs &args, hipStream_t st)
         return hipGetLastError();
     };
 #define ICNN_FLAT(KK, NG, G, WC, S) \
-    (form == 1 ? go(conv_flat_kernel<KK, NG, G, WC, 1, S>) : form == 2 ? go(conv_flat_kernel<KK, NG, G, WC, 2, S>) : go(conv_flat_kernel<KK, NG, G, WC, 0, S>))
+    (form == 5 ? go(conv_flat_kernel<KK, NG, G, WC, 5, S>) : form == 1 ? go(conv_flat_kernel<KK, NG, G, WC, 1, S>) : form == 2 ? go(conv_flat_kernel<KK, NG, G, WC, 2, S>) : go(conv_flat_kernel<KK, NG, G, WC, 0, S>))
     // The closing layer of a basic block beside its projection's int32 sums: two products in place of the general 64-bit steps, and the sums requested
     // before the K loop in whole lines (64 images, 128 channels on 28 x 28 18.4 -> 15.6 us, 256 on 14 x 14 13.9 -> 11.6, 512 on 7 x 7 14.0 -> 11.4;
     // with each lane asking for its own half lines 15.7, 12.8 and 11.4).

@@ -17,7 +17,7 @@ namespace icnn {
 
 // The leading arguments are in registers when a wave starts (as in conv_flat.hip): a workgroup's place, where a pixel lies in the projection's input (image, row,
 // pixel: bytes from one to the next); the others arrive while the first copies are requested.  (64 images, 128 + 256 -> 512 channels on 28 x 28: 22.6 -> 21.9 us.)
-// PS segments of the projection, MS of the closing layer, G steps of 64 each.  FORM: 1 requantisation as a product's high word (rq_fast), 8-bit output; 0 any form of one
+// PS segments of the projection, MS of the closing layer, G steps of 64 each.  FORM: 1 requantisation as a product's high word (rq_fast), 8-bit output; 3 as 1, to bytes (requant_fits_byte); 0 any form of one
 // pair per layer; 2 per output channel.
 template <int G, int PS, int MS, int FORM>
 __global__ __launch_bounds__(256, 2) void conv_flat_dual_kernel(const uint8_t *proj_x, const int M, const unsigned div_mul, const unsigned tiles, const int howo,
@@ -96,7 +96,7 @@ __global__ __launch_bounds__(256, 2) void conv_flat_dual_kernel(const uint8_t *p
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     in_registers(q.bias, a.bias, q.wp, a.wp, a.x, a.x_bytes, a.in_cs, q.res_mul, q.res_shift, a.out, a.out_cs, a.out_co, a.lo, a.hi);
-    if constexpr (FORM == 1) in_registers(a.mul_hi);
+    if constexpr (FORM == 1 || FORM == 3) in_registers(a.mul_hi);
     {
         const int co = co_tile + (tid & 127);
         tab[tid] = tid < 128 ? q.bias[co] : a.bias[co];
@@ -196,14 +196,14 @@ __global__ __launch_bounds__(256, 2) void conv_flat_dual_kernel(const uint8_t *p
 
     mfma_drain(acc);
     const int pw = p0;
-    if (FORM == 1 || (FORM == 2 && one_product)) {
+    if (FORM == 1 || FORM == 3 || (FORM == 2 && one_product)) {
         const SkipMul none = {0, 0, 0};
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int p = pw + 32 * j + col;
             v4i w;
             if constexpr (FORM == 2) w = epilogue_pc_hi16<0>(a, factors + half * 16, factors, nullptr, acc[0][j], v4i{0, 0, 0, 0});
-            else w = epilogue_hi16<0>(a, none, acc[0][j], v4i{0, 0, 0, 0});
+            else w = epilogue_hi16<0, FORM == 3>(a, none, acc[0][j], v4i{0, 0, 0, 0});
             if (p < M) *(v4i *)((uint8_t *)a.out + (size_t)p * a.out_cs + a.out_co + co_wave + half * 16) = w;
         }
     } else {
@@ -238,7 +238,7 @@ hipError_t launch_conv_flat_dual(const ConvArgs &args, const ProjArgs &q, hipStr
         return hipGetLastError();
     };
 #define ICNN_FLAT_DUAL(G, PS, MS) \
-    (a.pc ? go(conv_flat_dual_kernel<G, PS, MS, 2>) : a.rq_fast && a.epi_vec ? go(conv_flat_dual_kernel<G, PS, MS, 1>) : go(conv_flat_dual_kernel<G, PS, MS, 0>))
+    (a.pc ? go(conv_flat_dual_kernel<G, PS, MS, 2>) : a.rq_fast && a.epi_vec ? requant_fits_byte(a) ? go(conv_flat_dual_kernel<G, PS, MS, 3>) : go(conv_flat_dual_kernel<G, PS, MS, 1>) : go(conv_flat_dual_kernel<G, PS, MS, 0>))
     return a.Cin == 128 ? ICNN_FLAT_DUAL(2, 2, 1) : a.Cin == 256 ? ICNN_FLAT_DUAL(4, 2, 1) : ICNN_FLAT_DUAL(4, 4, 2);
 #undef ICNN_FLAT_DUAL
 }

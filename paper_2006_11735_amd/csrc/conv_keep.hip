@@ -50,10 +50,11 @@ __device__ __forceinline__ void keep_mfma_first(v16i &sum, const v4i &w, const v
 #endif
 }
 
-// RES: an unsigned 8-bit skip operand joined before requantisation (g.sk).  The layer requantises as a product's high word (rq_fast).
+// RES: an unsigned 8-bit skip operand joined before requantisation (g.sk).  The layer requantises as a product's high word (rq_fast); BYTE: to bytes
+// (requant_fits_byte).
 // hw: H | W << 16; geo: KiB of a patch row | rounds of a tile << 4 | KiB of a buffer << 8 | workgroups / 8 << 16 | rounds of the first tile << 24; share: rounds of a
 // workgroup << 8 | workgroups with one more; shifts: of the divisions by W (two) and H (two), a byte each.
-template <bool RES>
+template <bool RES, bool BYTE>
 __global__ __launch_bounds__(256, 1) void conv_keep_kernel(const uint8_t *x, const uint8_t *wp, const int32_t *bias, const int M, const int in_cs, const unsigned hw,
                                                            const unsigned geo, const unsigned share, const unsigned mul_w, const unsigned mul_h, const unsigned shifts,
                                                            const ConvArgs a, const KeepArgs g)
@@ -196,6 +197,9 @@ __global__ __launch_bounds__(256, 1) void conv_keep_kernel(const uint8_t *x, con
             for (int c = 0; c < 2; ++c) s.r8[c] = __builtin_amdgcn_raw_buffer_load_b128(rs_r, at + c * 32, 0, 0);
         }
     };
+    auto high = [&](int t) __attribute__((always_inline)) {
+        return BYTE ? (int)(((int64_t)t * (a.mul_hi << 8) + 0x8000000000LL) >> 32) : (int)(((int64_t)t * a.mul_hi + 0x80000000LL) >> 32);
+    };
     // Multiplies group q, whose first fragments are on their way, into cur.  Between its products: the fragments to come, in the end those of group
     // j (of a tile's last: its own again, not used), and the requantisation and store of the group before, whose place takes group j's skip operand then.
     auto step = [&](const Tile &t, int b_, int j, Group &q, Sums &cur, Sums &old) __attribute__((always_inline)) {
@@ -220,20 +224,25 @@ __global__ __launch_bounds__(256, 1) void conv_keep_kernel(const uint8_t *x, con
                         const uint32_t x = __builtin_amdgcn_perm((uint32_t)old.r8[oc][(R0 + e) >> 2], g.sk.rnd, 0x00020100u | (uint32_t)(4 + ((R0 + e) & 3)) << 24);
                         sum[e] = __builtin_elementwise_add_sat(sum[e], (int)__umulhi(x, g.sk.k));
                     } else {
-                        sum[e] = (int)(((int64_t)sum[e] * a.mul_hi + 0x80000000LL) >> 32);
+                        sum[e] = high(sum[e]);
                     }
                 }
             }
             if constexpr (pair >= 0 && pair < 16 && c == 1) {
-                const int lo_v = a.lo;
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    if constexpr (RES) sum[e] = (int)(((int64_t)sum[e] * a.mul_hi + 0x80000000LL) >> 32);
-                    sum[e] = med3_vvs(sum[e], lo_v, a.hi);
+                if constexpr (RES) {
+                    sum[0] = high(sum[0]);
+                    sum[1] = high(sum[1]);
                 }
-                const uint32_t two = __builtin_amdgcn_perm((uint32_t)sum[1], (uint32_t)sum[0], 0x0c0c0400u);
+                uint32_t two;
+                if constexpr (BYTE) {                  // as in epilogue_hi_slice
+                    typedef short i16x2 __attribute__((ext_vector_type(2)));
+                    two = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, __builtin_amdgcn_cvt_pk_i16(sum[0], sum[1])), i16x2{0, 0}));
+                } else {
+                    const int lo_v = a.lo;
+                    two = __builtin_amdgcn_perm((uint32_t)med3_vvs(sum[1], lo_v, a.hi), (uint32_t)med3_vvs(sum[0], lo_v, a.hi), 0x0c0c0400u);
+                }
                 if constexpr ((R0 & 2) == 0) o[R0 >> 2] = (int)two;
-                else o[R0 >> 2] = (int)__builtin_amdgcn_perm(two, (uint32_t)o[R0 >> 2], 0x05040100u);
+                else o[R0 >> 2] = (int)__builtin_amdgcn_perm(two, (uint32_t)o[R0 >> 2], BYTE ? 0x07050301u : 0x05040100u);
                 if constexpr (pair % 8 == 7) store(old.p, oc, o);
             }
             if constexpr (c == 1) {
@@ -289,7 +298,7 @@ __global__ __launch_bounds__(256, 1) void conv_keep_kernel(const uint8_t *x, con
     mfma_drain(s1.s);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        const v4i o = epilogue_hi16<RES ? 1 : 0>(a, g.sk, s1.s[c], s1.r8[c]);
+        const v4i o = epilogue_hi16<RES ? 1 : 0, BYTE>(a, g.sk, s1.s[c], s1.r8[c]);
         const int p[4] = {o[0], o[1], o[2], o[3]};
         store(s1.p, c, p);
     }
@@ -345,7 +354,8 @@ hipError_t launch_conv_keep(const ConvArgs &a, hipStream_t st)
     g.sk = a.res_mode ? make_skip_mul(a.res_mul, a.res_shift) : SkipMul{0, 0, 0};
     g.out_bytes = (unsigned)(((long long)a.M - 1) * a.out_cs + a.out_co + 64);
     g.res_bytes = a.res_mode ? (unsigned)(((long long)a.M - 1) * a.res_cs + 64) : 0u;
-    const auto kernel = a.res_mode ? conv_keep_kernel<true> : conv_keep_kernel<false>;
+    const bool byte = requant_fits_byte(a);
+    const auto kernel = a.res_mode ? byte ? conv_keep_kernel<true, true> : conv_keep_kernel<true, false> : byte ? conv_keep_kernel<false, true> : conv_keep_kernel<false, false>;
     const hipError_t e = allow_large_lds((const void *)kernel);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(256), (size_t)(2 * buf), st, a.x, a.wp, a.bias, a.M, a.in_cs, (unsigned)a.H | (unsigned)a.W << 16,

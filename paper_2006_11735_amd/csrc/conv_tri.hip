@@ -36,8 +36,8 @@ struct TriKernelArgs {
     ConvArgs a2, a3, a1;
 };
 
-// FORM: 1 all layers requantise as a product's high word (rq_fast), the skip operand rescaled likewise (g.sk), the block's last layer between matrix instructions; 0 any form,
-// chosen at run time; 2 per output channel.  NEXT: the next block's first layer is included.
+// FORM: 1 all layers requantise as a product's high word (rq_fast), the skip operand rescaled likewise (g.sk), the block's last layer between matrix instructions; 3 as 1, all
+// layers to bytes (requant_fits_byte); 0 any form, chosen at run time; 2 per output channel.  NEXT: the next block's first layer is included.
 template <int NP, bool NEXT, int FORM>                 // NP: pixel groups of 32 (the fourth one half used)
 __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, const uint8_t *w2_packed, const int32_t *bias2, const int32_t *bias3, const int32_t *bias1,
                                                           const int M, const int in_cs, const unsigned shape, const unsigned tiles, const int grid,
@@ -46,6 +46,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr unsigned OOB = 0x80000000u;
     constexpr int MID = kTriMid, C = kTriWide, PX = tri_pixels(NP);
+    constexpr bool HI = FORM == 1 || FORM == 3, BYTE = FORM == 3;
     constexpr int AP = MID + 16, YP = C + 16;          // row pitches of the patch (later b) and of the skip operand (later y)
     constexpr int S2 = 9 * 4, S1 = 16;                 // K steps of 64 of a wave's chunk: 3x3 layer, next block's layer (last layer: 4 per chunk)
 
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
             if (one_product) return epilogue_pc_hi16<RES>(a, atab + at, ktab + (at - MID), ptab + (at - MID), c, r8);
             return epilogue_pc_bytes16<RES>(a, c, r8, pc);
         }
-        else if constexpr (FORM == 1) return epilogue_hi16<RES>(a, ga.sk, c, r8);
+        else if constexpr (HI) return epilogue_hi16<RES, BYTE>(a, ga.sk, c, r8);
         else return epilogue_bytes16<RES>(a, c, r8);
     };
 
@@ -367,11 +368,11 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
                     else fr[hn & 3] = *(const v4i *)(lds + ad[nj] + (hn - 8) * 32);
                     if constexpr (j == NP - 1) load_frag(std::integral_constant<int, R0 * 2 + h>{}, rs);
                     if constexpr (h == 4) r8[PAR] = *(const v4i *)(lds + at0 + slot(j) * YP + ch * MID);
-                    if constexpr (FORM == 1)
-                        if (old) epilogue_hi_slice<1, 2 * h, 2>(a3, ga.sk, c2[PAR ^ 1], r8[PAR ^ 1], w);
+                    if constexpr (HI)
+                        if (old) epilogue_hi_slice<1, 2 * h, 2, BYTE>(a3, ga.sk, c2[PAR ^ 1], r8[PAR ^ 1], w);
                     __builtin_amdgcn_sched_barrier(0);
                 });
-                if constexpr (FORM == 1) {
+                if constexpr (HI) {
                     if (old && (32 * oj + 31 < PX || 32 * oj + col < PX))
                         *(v4i *)(lds + at0 + (32 * oj + col) * YP + (j == 0 ? ch - 1 : ch) * MID) = v4i{w[0], w[1], w[2], w[3]};
                     mfma_drain(c2[PAR]);
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
                 chunk(H1{}, H0{}, std::true_type{}, ch);
                 chunk(H0{}, H1{}, std::false_type{}, ch + 1);
             }
-            if constexpr (FORM == 1) {
+            if constexpr (HI) {
                 constexpr int PAR = (2 * NP - 1) & 1;
                 const v4i o = finish(a3, H1{}, c2[PAR], r8[PAR], nullptr, 0);
                 if (32 * NP - 1 < PX || 32 * (NP - 1) + col < PX) *(v4i *)(lds + at0 + (32 * (NP - 1) + col) * YP + 3 * MID) = o;
@@ -539,7 +540,8 @@ hipError_t launch_conv_tri(const TriArgs &g, const ConvArgs &a2, const ConvArgs 
     const size_t tables = (2 * kTriMid + 2 * kTriWide + 8) * 4 + kTriWide;
     q.table = a3.pc && tri_lds_bytes(g) + tables <= 160 * 1024;
     const size_t lds_bytes = tri_lds_bytes(g) + (q.table ? tables : 0);
-    const int form = a3.pc ? 2 : a2.rq_fast && a3.rq_fast && (!a3.res_mode || q.sk.ok) && (!a1 || a1->rq_fast) ? 1 : 0;
+    int form = a3.pc ? 2 : a2.rq_fast && a3.rq_fast && (!a3.res_mode || q.sk.ok) && (!a1 || a1->rq_fast) ? 1 : 0;
+    if (form == 1 && requant_fits_byte(a2) && requant_fits_byte(a3) && (!a1 || requant_fits_byte(*a1))) form = 3;
     auto go = [&](auto kernel) -> hipError_t {
         const hipError_t e = allow_large_lds((const void *)kernel);
         if (e != hipSuccess) return e;
@@ -551,7 +553,7 @@ hipError_t launch_conv_tri(const TriArgs &g, const ConvArgs &a2, const ConvArgs 
     auto by_form = [&](auto np_tag, auto next_tag) {
         constexpr int NP = decltype(np_tag)::value;
         constexpr bool NEXT = decltype(next_tag)::value;
-        return form == 2 ? go(conv_tri_kernel<NP, NEXT, 2>) : form == 1 ? go(conv_tri_kernel<NP, NEXT, 1>) : go(conv_tri_kernel<NP, NEXT, 0>);
+        return form == 2 ? go(conv_tri_kernel<NP, NEXT, 2>) : form == 3 ? go(conv_tri_kernel<NP, NEXT, 3>) : form == 1 ? go(conv_tri_kernel<NP, NEXT, 1>) : go(conv_tri_kernel<NP, NEXT, 0>);
     };
     auto by_next = [&](auto np_tag) { return a1 ? by_form(np_tag, std::true_type{}) : by_form(np_tag, std::false_type{}); };
     switch (g.np) {

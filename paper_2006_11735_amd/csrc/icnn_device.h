@@ -58,6 +58,7 @@ struct ConvArgs {
     int vec_bias; // bias is 16-byte aligned and cout % 16 == 0
     int rq_fast;  // requantisation as one 32x32->64 multiply-add (mul_hi = mul << (32 - shift))
     int mul_hi;
+    int rq_byte;  // that, to bytes from 0 to 127 by a multiplier below 2^23 (requant_fits_byte)
     // requantisation in 32 bits: with lo = 0, clamping t to [0, t_hi] first (t_hi: the smallest t whose result is
     // hi) leaves the result unchanged, and then t * mul + 2^(shift-1) fits 32 bits unsigned with both factors
     // below 2^24, so one full-rate multiply-add and a shift finish it and no clamp of the result is needed
@@ -81,6 +82,13 @@ struct ConvArgs {
     unsigned *ws_cnt;
     int32_t *ws_part;
 };
+
+// A layer that stores bytes from 0 to 127 and whose product, taken 2^8 times as large, still fits 64 bits with a 32-bit factor: see epilogue_hi_slice
+template <class P>
+static inline bool requant_fits_byte(const P &a)
+{
+    return a.rq_fast && a.lo == 0 && a.hi == 127 && a.mul_hi < (1 << 23);
+}
 
 // An unsigned 8-bit skip operand's rescale as the high word of one product: [x * mul / 2^shift] = high 32 bits of (x << 24 | rnd) * k for every
 // byte x.  (x << 24 | rnd) * (m << (8 - s)) / 2^32 = x m / 2^s + rnd * m 2^(8-s) / 2^32, and the smallest rnd that makes the second term one

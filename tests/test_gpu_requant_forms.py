@@ -87,3 +87,40 @@ def test_two_branch_forms(a, b, cout_b):
         torch.cuda.synchronize()
         want = np.array([exact(t, *p) for p, v in zip((a, b), bias) for t in v], dtype=np.uint8)
         assert (y.cpu().numpy() == want).all()
+
+
+# bytes by a product 2^8 times as large: multipliers on both sides of 2^23 (mul * 2^(32 - shift)), sums at int32's ends, with a skip operand that saturates them
+@pytest.mark.parametrize("mul, shift", [(32767, 24), (32767, 23), (16385, 24), (1, 10), (1, 9), (3, 32), (8388607, 32), (5000001, 32)])
+@pytest.mark.parametrize("kernel, cin, cout, k", [("flat", 128, 128, 1), ("keep", 64, 64, 3), ("lat", 64, 64, 1), ("tile", 64, 64, 3)])
+@pytest.mark.parametrize("skip", [None, (20000, 5), (255, 0), (8388608, 1)], ids=str)
+def test_byte_form(mul, shift, kernel, cin, cout, k, skip):
+    from gpu_util import dev
+    from paper_2006_11735_amd import binding as B
+    rng = np.random.default_rng([mul, shift])
+    steps = rounding_accumulators(mul, shift, 127) + [2 ** 31 - 1, -2 ** 31, 2 ** 31 - 2, -2 ** 31 + 1, 0]
+    rm, rs = skip or (0, 0)
+    n, px = (len(steps) + cout - 1) // cout, 70
+    res = rng.integers(0, 256, size=(px, cout), dtype=np.uint8)
+    res[:4] = np.array([[0], [1], [127], [255]], np.uint8)
+    d = B.conv_desc(n=1, h=px, w=1, cin=cin, in_c_stride=cin, cout=cout, kh=k, kw=k, pad_h=k // 2, pad_w=k // 2, out_c_stride=cout, mul=mul, shift=shift, bound_q=127)
+    if skip:
+        d.res_mode, d.res_dtype, d.res_c_stride, d.res_mul, d.res_shift = B.ICNN_RES_PRE, B.ICNN_U8, cout, rm, rs
+    wp = torch.zeros(B.iconv2d_packed_weight_bytes(d), dtype=torch.uint8, device="cuda:0")
+    B.iconv2d_prepack_weights(d, dev(rng.integers(-127, 128, size=(cout, k, k, cin), dtype=np.int8)), wp)
+    x = torch.zeros((px, cin), dtype=torch.uint8, device="cuda:0")
+    for at in range(n):
+        bias = np.array([steps[(at * cout + i) % len(steps)] for i in range(cout)], dtype=np.int64)
+        if skip:                                           # (half of them so that the sum, not the bias, is at the step)
+            bias[::2] = np.clip(bias[::2] - ((int(res[2, 0]) * rm + ((1 << rs) >> 1)) >> rs), -2 ** 31, 2 ** 31 - 1)
+        y = torch.zeros((px, cout), dtype=torch.uint8, device="cuda:0")
+        B.icnn_set_tuning(kernel, 1)
+        try:
+            B.iconv2d_brelu(d, x, wp, dev(bias.astype(np.int32)), dev(res) if skip else None, y)
+            torch.cuda.synchronize()
+        finally:
+            B.icnn_set_tuning("reset")
+        t = np.broadcast_to(bias, (px, cout)).astype(object)
+        if skip:
+            t = np.clip(t + ((res.astype(object) * rm + ((1 << rs) >> 1)) >> rs), -2 ** 31, 2 ** 31 - 1)
+        want = np.clip((t * mul + (1 << (shift - 1))) >> shift, 0, 127).astype(np.uint8)
+        assert (y.cpu().numpy() == want).all()

@@ -3,7 +3,7 @@
 // most 64 pixels through the three layers, and two workgroups share a compute unit, so that one's loads, barriers and
 // vector work run beside the other's matrix instructions.
 //
-//   tile     TH x TW output pixels (at most 64), patch (TH+2) x (TW+2) input pixels (at most 96), copied to LDS once
+//   tile     TH x TW output pixels (at most 64, or 32 where there are few), patch (TH+2) x (TW+2) input pixels (at most 96, 64), copied to LDS once
 //   phase 1  a = BReLU/requant(W1 x + b1) on the patch; patch pixels outside the image become zeros (the 3x3 layer's padding)
 //   phase 2  b = BReLU/requant(W2 (*) a + b2) on the tile, tap = patch row offset; b replaces a
 //   phase 3  y = epilogue(W3 b + b3, skip), 128 of the 512 channels at a time; the skip operand is the block input, in LDS
@@ -23,13 +23,14 @@
 namespace icnn {
 
 constexpr int kB128Mid = 128, kB128Wide = 512;
-constexpr int kB128Rows = 96, kB128Pix = 64;           // patch rows, output pixel slots
+// a tile of OG groups of 32 output pixel slots, patch rows in one group more
 constexpr int kB128XP = kB128Wide + 16, kB128AP = kB128Mid + 16;
-constexpr int kB128XBytes = (kB128Rows * (kB128XP / 16) + 63) / 64 * 1024;
+constexpr int b128_rows(int og) { return 32 * (og + 1); }
+constexpr int b128_x_bytes(int og) { return (b128_rows(og) * (kB128XP / 16) + 63) / 64 * 1024; }
 
 // HI: the three layers requantise as a product's high word (rq_fast) and the skip operand is rescaled likewise (g.sk), the last layer's
 // epilogue dealt out between matrix instructions; else any 8-bit form.  BYTE: HI, and all of them to bytes (requant_fits_byte)
-template <bool HI, bool BYTE>
+template <int OG, bool HI, bool BYTE>
 __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x, const uint8_t *w1_packed, const unsigned hw, const unsigned shape, const int x_cs,
                                                                const int n_tiles, const int tiles_per_img, const unsigned mul_tpi, const int tiles_x,
                                                                const unsigned mul_tx, const unsigned shifts, const unsigned inv_pw, const BlockArgs ga,
@@ -38,12 +39,13 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr unsigned OOB = 0x80000000u;
     constexpr int MID = kB128Mid, C = kB128Wide, XP = kB128XP, AP = kB128AP;
+    constexpr int PG = OG + 1, XBYTES = b128_x_bytes(OG);
     constexpr int NG = 4 + 9 + 4;                      // groups of two K steps: first layer, taps, chunks of the last layer
 
     // LDS: patch of x (in the end y on the tile's rows) | a on the patch, then b on the tile | biases [128] [128] [512]
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-    uint8_t *const abuf = lds + kB128XBytes;
-    int32_t *const btab = (int32_t *)(abuf + kB128Rows * AP);
+    uint8_t *const abuf = lds + XBYTES;
+    int32_t *const btab = (int32_t *)(abuf + b128_rows(OG) * AP);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -94,7 +96,7 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
         const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc((void *)x, 0, 0x7fffff00, 0x00020000);     // (every place inside the tensor lies below 2 GiB, OOB above)
         // 16-byte piece i of the patch region is piece i % 33 of row i / 33; the last one is padding
 #pragma unroll 2
-        for (int c = wave; c < kB128XBytes / 1024; c += 4) {
+        for (int c = wave; c < XBYTES / 1024; c += 4) {
             const int i = c * 64 + lane;
             const int row = (int)(((unsigned)i * 63551u) >> 21), piece = i - row * 33;         // / 33, exact below 6000
             const int py = (int)(((unsigned)row * g.inv_pw) >> 16), px = row - py * g.PW;
@@ -163,11 +165,11 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
 
     // ---------------- phase 1: a = requant(W1 x + b1) on the patch
     {
-        v16i acc[3];
-        v4i bf[2][3];
-        int ad[3];
+        v16i acc[PG];
+        v4i bf[2][PG];
+        int ad[PG];
 #pragma unroll
-        for (int j = 0; j < 3; ++j) {
+        for (int j = 0; j < PG; ++j) {
             ad[j] = (32 * j + col) * XP + half * 16;
             acc[j] = bias16(btab + co);
         }
@@ -177,7 +179,7 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
             group(k_tag, acc, bf, ad, std::integral_constant<int, k * 128>{}, ad, std::integral_constant<int, (k < 3 ? k + 1 : k) * 128>{});
         });
         mfma_drain(acc);
-        static_for<3>([&](auto j_tag) __attribute__((always_inline)) {
+        static_for<PG>([&](auto j_tag) __attribute__((always_inline)) {
             constexpr int j = decltype(j_tag)::value;
             const int row = 32 * j + col;
             const int py = (int)(((unsigned)row * g.inv_pw) >> 16), px = row - py * g.PW;
@@ -191,22 +193,22 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
     sync();
 
     // ---------------- phase 2: b = requant(W2 (*) a + b2) on the tile's pixel slots
-    int prow[2];                                       // patch row of this lane's pixels q = 32 j + col (slots beyond the tile: of pixel 0)
-    bool in[2];
+    int prow[OG];                                      // patch row of this lane's pixels q = 32 j + col (slots beyond the tile: of pixel 0)
+    bool in[OG];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
+    for (int j = 0; j < OG; ++j) {
         const int q = 32 * j + col;
         in[j] = q < g.TH * g.TW;
         const int ty = in[j] ? (int)(((unsigned)q * g.inv_tw) >> 16) : 0;
         prow[j] = (ty + 1) * g.PW + (in[j] ? q - ty * g.TW : 0) + 1;
     }
     {
-        v16i acc[2];
-        v4i bf[4][2];
-        int ad[2], nad[2];
+        v16i acc[OG];
+        v4i bf[4][OG];
+        int ad[OG], nad[OG];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            ad[j] = kB128XBytes + (prow[j] - g.PW - 1) * AP + half * 16;
+        for (int j = 0; j < OG; ++j) {
+            ad[j] = XBYTES + (prow[j] - g.PW - 1) * AP + half * 16;
             acc[j] = bias16(btab + MID + co);
         }
         first_frags(bf, ad);
@@ -214,14 +216,14 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
         static_for<9>([&](auto t_tag) __attribute__((always_inline)) {
             constexpr int t = decltype(t_tag)::value;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) nad[j] = t == 8 ? ad[j] : ad[j] + (t % 3 == 2 ? (g.PW - 2) * AP : AP);
+            for (int j = 0; j < OG; ++j) nad[j] = t == 8 ? ad[j] : ad[j] + (t % 3 == 2 ? (g.PW - 2) * AP : AP);
             group(std::integral_constant<int, 4 + t>{}, acc, bf, ad, Z{}, nad, Z{});
 #pragma unroll
-            for (int j = 0; j < 2; ++j) ad[j] = nad[j];
+            for (int j = 0; j < OG; ++j) ad[j] = nad[j];
         });
         sync();                                        // every wave has its last fragments of a: b may overwrite it
         mfma_drain(acc);
-        static_for<2>([&](auto j_tag) __attribute__((always_inline)) {
+        static_for<OG>([&](auto j_tag) __attribute__((always_inline)) {
             constexpr int j = decltype(j_tag)::value;
             *(v4i *)(abuf + (32 * j + col) * AP + co) = finish(a2, acc[j]);        // slots beyond the tile hold values nobody stores
             __builtin_amdgcn_sched_barrier(0);
@@ -235,43 +237,45 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
         v16i c2[2];                                    // the group being multiplied, the one being finished
         v4i fr[4], r8[2];
         int w[4];
-        const int ad0 = kB128XBytes + col * AP + half * 16;
+        const int ad0 = XBYTES + col * AP + half * 16;
 #pragma unroll
         for (int h = 0; h < 3; ++h) fr[h] = *(const v4i *)(lds + ad0 + h * 32);
-        static_for<8>([&](auto i_tag) __attribute__((always_inline)) {
-            constexpr int i = decltype(i_tag)::value, ch = i >> 1, j = i & 1, K = 13 + ch;
-            c2[j] = bias16(btab + 2 * MID + ch * MID + co);
+        static_for<4 * OG>([&](auto i_tag) __attribute__((always_inline)) {
+            constexpr int i = decltype(i_tag)::value, ch = i / OG, j = i % OG, K = 13 + ch, now = i & 1;
+            constexpr int before = i == 0 ? 0 : (i - 1) % OG, next = (i + 1) % OG;                             // the pixel groups of the items beside it
+            c2[now] = bias16(btab + 2 * MID + ch * MID + co);
             static_for<4>([&](auto h_tag) __attribute__((always_inline)) {
                 constexpr int h = decltype(h_tag)::value, hn = h + 3;
-                c2[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ring[K & 3][h], fr[h], c2[j], 0, 0, 0);
-                asm volatile("" : "+v"(c2[j]));
+                c2[now] = __builtin_amdgcn_mfma_i32_32x32x32_i8(ring[K & 3][h], fr[h], c2[now], 0, 0, 0);
+                asm volatile("" : "+v"(c2[now]));
                 __builtin_amdgcn_sched_barrier(0);
-                fr[hn & 3] = *(const v4i *)(lds + ad0 + (hn < 4 ? j : j ^ 1) * (32 * AP) + (hn & 3) * 32);
-                if constexpr (h == 1) r8[j] = *(const v4i *)(lds + prow[j] * XP + ch * MID + co);
-                if constexpr (HI && i > 0) epilogue_hi_slice<1, 4 * h, 4, BYTE>(a3, sk, c2[j ^ 1], r8[j ^ 1], w);
+                fr[hn & 3] = *(const v4i *)(lds + ad0 + (hn < 4 ? j : next) * (32 * AP) + (hn & 3) * 32);
+                if constexpr (h == 1) r8[now] = *(const v4i *)(lds + prow[j] * XP + ch * MID + co);
+                if constexpr (HI && i > 0) epilogue_hi_slice<1, 4 * h, 4, BYTE>(a3, sk, c2[now ^ 1], r8[now ^ 1], w);
                 __builtin_amdgcn_sched_barrier(0);
             });
             if constexpr (HI) {
                 if constexpr (i > 0)
-                    if (in[j ^ 1]) *(v4i *)(lds + prow[j ^ 1] * XP + ((i - 1) >> 1) * MID + co) = v4i{w[0], w[1], w[2], w[3]};
-                mfma_drain(c2[j]);
+                    if (in[before]) *(v4i *)(lds + prow[before] * XP + ((i - 1) / OG) * MID + co) = v4i{w[0], w[1], w[2], w[3]};
+                mfma_drain(c2[now]);
             } else {
-                mfma_drain(c2[j]);
-                const v4i o = has_res ? epilogue_bytes16<1>(a3, c2[j], r8[j]) : epilogue_bytes16<0>(a3, c2[j], r8[j]);
+                mfma_drain(c2[now]);
+                const v4i o = has_res ? epilogue_bytes16<1>(a3, c2[now], r8[now]) : epilogue_bytes16<0>(a3, c2[now], r8[now]);
                 if (in[j]) *(v4i *)(lds + prow[j] * XP + ch * MID + co) = o;
             }
             __builtin_amdgcn_sched_barrier(0);
         });
         if constexpr (HI) {
-            const v4i o = epilogue_hi16<1, BYTE>(a3, sk, c2[1], r8[1]);
-            if (in[1]) *(v4i *)(lds + prow[1] * XP + 3 * MID + co) = o;
+            constexpr int last = (4 * OG - 1) & 1;
+            const v4i o = epilogue_hi16<1, BYTE>(a3, sk, c2[last], r8[last]);
+            if (in[OG - 1]) *(v4i *)(lds + prow[OG - 1] * XP + 3 * MID + co) = o;
         }
     }
     sync();                                            // y is complete
 
     // y leaves LDS two pixels' whole rows per store
 #pragma unroll 4
-    for (int c = wave; c < kB128Pix / 2; c += 4) {
+    for (int c = wave; c < 16 * OG; c += 4) {
         const int q = 2 * c + half, piece = col * 16;
         const int ty = (int)(((unsigned)q * g.inv_tw) >> 16), tx = q - ty * g.TW;
         const int oy = y0 + ty, ox = x0 + tx;
@@ -283,6 +287,8 @@ __global__ __launch_bounds__(256, 2) void conv_block128_kernel(const uint8_t *x,
 }
 
 // ------------------------------------------------------------------ dispatch
+constexpr long long kB128SmallTiles = 256;
+
 // 512 -> 128 -> 128 -> 512 channels, an 8-bit output, the block input itself as skip operand (unsigned 8-bit, joined before requantisation
 // with a rescale that fits 32 bits) or none
 bool conv_block128_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a3)
@@ -296,13 +302,25 @@ bool conv_block128_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs 
 hipError_t launch_conv_block128(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st)
 {
     if (!conv_block128_takes(g, a1, a3)) return hipErrorInvalidValue;
+    // Tiles of 32 pixels where there is a compute unit for each: a workgroup's own time is what a launch takes then.  50 layers, us, 64 / 32 pixels: one image (28 tiles of 32
+    // pixels) 169.3 / 160.8, four 205.1 / 198.9, nine (252) 238.1 / 231.0, 12 (336) 275.8 / 277.4, 32 384.9 / 397.2.
     BlockArgs gx = g;
-    if (!conv_block_tile(g.H, g.W, kB128Pix, kB128Rows, gx)) return hipErrorInvalidValue;
-    const long long tiles = (long long)gx.tiles_per_img * g.N;
+    long long tiles = 0;
+    const auto tile = [&](int og) {
+        gx = g;
+        if (!conv_block_tile(g.H, g.W, 32 * og, b128_rows(og), gx)) return false;
+        tiles = (long long)gx.tiles_per_img * g.N;
+        return true;
+    };
+    int og = 1;
+    if (g_tuning.block128_tile ? g_tuning.block128_tile == 2 || !tile(1) : !tile(1) || tiles > kB128SmallTiles) {
+        og = 2;
+        if (!tile(2)) return hipErrorInvalidValue;
+    }
     if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
     gx.n_tiles = (int)tiles;
     gx.per_xcd = (int)((tiles + 7) / 8);
-    const size_t lds_bytes = kB128XBytes + kB128Rows * kB128AP + (2 * kB128Mid + kB128Wide) * 4;
+    const size_t lds_bytes = b128_x_bytes(og) + b128_rows(og) * kB128AP + (2 * kB128Mid + kB128Wide) * 4;
     const SkipMul sk = a3.res_mode ? make_skip_mul(a3.res_mul, a3.res_shift) : SkipMul{0, 0, 0};     // (without an operand: adds zero)
     auto go = [&](auto kernel) -> hipError_t {
         const hipError_t e = allow_large_lds((const void *)kernel);
@@ -314,8 +332,12 @@ hipError_t launch_conv_block128(const BlockArgs &g, const ConvArgs &a1, const Co
         return hipGetLastError();
     };
     const bool hi = a1.rq_fast && a2.rq_fast && a3.rq_fast && (a3.res_mode == 0 || sk.ok) && !g_tuning.block_any_form;
-    if (hi && requant_fits_byte(a1) && requant_fits_byte(a2) && requant_fits_byte(a3)) return go(conv_block128_kernel<true, true>);
-    return hi ? go(conv_block128_kernel<true, false>) : go(conv_block128_kernel<false, false>);
+    const bool byte = hi && requant_fits_byte(a1) && requant_fits_byte(a2) && requant_fits_byte(a3);
+    auto by_form = [&](auto og_tag) {
+        constexpr int OG = decltype(og_tag)::value;
+        return byte ? go(conv_block128_kernel<OG, true, true>) : hi ? go(conv_block128_kernel<OG, true, false>) : go(conv_block128_kernel<OG, false, false>);
+    };
+    return og == 1 ? by_form(std::integral_constant<int, 1>{}) : by_form(std::integral_constant<int, 2>{});
 }
 
 }  // namespace icnn

@@ -245,6 +245,7 @@ struct Tuning {
     int no_block128 = 0;   // fused bottleneck blocks of 512 -> 128 -> 512 channels: the LDS-ring kernel instead of the one of small workgroups
     int no_block64s = 0;   // fused bottleneck blocks of 256 -> 64 -> 256 channels: the kernel with resident weights instead of the one of small workgroups
     int no_block64 = 0;    // fused bottleneck blocks with 64 middle channels: the LDS-ring kernel instead of the register-resident one
+    int block128_tile = 0; // blocks of 128 middle channels in tiles of 32 (1) or 64 (2) pixels
     int keep = 0;          // 3x3 layers of 64 channels with their weights kept in registers: 1 every layer that kernel accepts, 2 none
     int flat = 0;          // kernel with register-fed weights: 1 every layer whose shape it accepts, 2 none
     int tri_tile = 0;      // 3x3 + 1x1 + 1x1 kernel: 1..4 = tiles of 32, 64, 96 or 112 pixels

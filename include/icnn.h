@@ -134,7 +134,7 @@ const char *icnn_last_error(void);
  *                 in tiles of 16 x 16, 32 x 16, 32 x 32 channels x pixels
  *   "halo_tile"   0 library's choice; 1 = 128 x 128, 2 = 64 x 256 tiles of the patch-resident 3x3 kernel
  *   "halo_always" 1 lets the patch-resident kernel take layers with several tiles per workgroup
- *   "no_block64s" 1 keeps fused bottleneck blocks of 256 -> 64 -> 256 channels on the kernel with resident weights
+ *   "no_block64s" 1 keeps fused bottleneck blocks of 256 -> 64 -> 256 and 64 -> 64 -> 256 channels on the kernel of large workgroups
  *   "no_block128" 1 keeps fused bottleneck blocks of 512 -> 128 -> 512 channels on the kernel that streams weights through LDS
  *   "block_any_form" 1 keeps fused bottleneck blocks on the instantiation that holds every epilogue form
  *   "plane_no_pipe" 1 keeps that kernel off its instantiations with the software-pipelined epilogue

@@ -690,7 +690,7 @@ static int bottleneck(const icnn_conv_desc *c1, const void *x, const void *w1_pa
     b.k1 = c / 64;
     b.nchunk3 = c3->cout / mid;
     if (!g_tuning.no_block64 && !g_tuning.no_block64s && conv_block64s_takes(b, a1, a2, a3))
-        return launched(launch_conv_block64s(b, a1, a2, a3, (hipStream_t)stream), what);
+        return launched(launch_conv_block64s(b, a1, a2, a3, nullptr, (hipStream_t)stream), what);
     if ((pc3 || !g_tuning.no_block64) && conv_block64_takes(b, a1, a3) && conv_block64_lds_bytes(c, c, false, pc3 != nullptr) <= 160 * 1024)
         return launched(launch_conv_block64(b, a1, a2, a3, nullptr, (hipStream_t)stream), what);
     if (pc3) return fail(ICNN_E_UNSUPPORTED, "fused block with channel parameters needs a middle width of 64, outer widths of 64, 128 or 256, an 8-bit output and the block input as skip operand");
@@ -784,6 +784,8 @@ static int bottleneck_dual(const icnn_conv_desc *c1, const void *x, const void *
     b.k1 = 1;
     b.nchunk3 = 4;
     if (!conv_block64_proj_takes(a1, a3, q)) return fail(ICNN_E_UNSUPPORTED, "fused projection block does not take these layers");
+    if (!g_tuning.no_block64s && conv_block64s_proj_takes(b, a1, a2, a3, q))
+        return launched(launch_conv_block64s(b, a1, a2, a3, &q, (hipStream_t)stream), what);
     return launched(launch_conv_block64(b, a1, a2, a3, &q, (hipStream_t)stream), what);
 }
 

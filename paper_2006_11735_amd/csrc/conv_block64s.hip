@@ -19,6 +19,11 @@
 // eight waves on tiles of 128 pixels (conv_block64.hip), 46 with three workgroups per compute unit that fetch their weights per
 // tile (9 of a tile's 19 k clocks), 41 now.  Biases and weights are requested before anything else, from arguments that the hardware puts into registers:
 // behind the tile's arguments and the first patch they came some 1500 clocks later (7.2 -> 6.9 us at one picture, 42.6 -> 41.9 at 64).
+//
+// PROJ: the block that opens the stage (64 input channels, the skip operand a projection of them, "after convolution").  Its last layer's sums
+// pass through vector instructions twice, once at the projection's ratio; an item's four steps (projection, rescale, products, epilogue) are
+// dealt out so that another item's products are made beside them.  28 weight fragments a wave; y has a region of LDS of its own.
+// 56 x 56 pixels, 1 / 9 / 64 pictures: 10.8 / 12.5 / 45.3 us with eight waves on tiles of 128 pixels (conv_block64.hip), 6.8 / 10.6 / 39.0 here.
 #include "conv_common.h"
 
 #include <algorithm>
@@ -28,25 +33,33 @@ namespace icnn {
 
 constexpr int kB64sMid = 64, kB64sWide = 256;
 constexpr int kB64sRows = 96, kB64sPix = 64;           // patch rows, output pixel slots
-constexpr int kB64sXP = kB64sWide + 16, kB64sAP = kB64sMid + 16;      // row pitches: padded as in conv_tri.hip
-constexpr int kB64sXBytes = (kB64sRows * (kB64sXP / 16) + 63) / 64 * 1024;
+constexpr int kB64sYP = kB64sWide + 16, kB64sAP = kB64sMid + 16;      // row pitches: padded as in conv_tri.hip
+constexpr int b64s_patch_bytes(bool proj) { return (kB64sRows * ((proj ? kB64sAP : kB64sYP) / 16) + 63) / 64 * 1024; }
+constexpr int b64s_lds_bytes(bool proj)
+{
+    return 2 * b64s_patch_bytes(proj) + kB64sRows * kB64sAP + (2 * kB64sMid + (proj ? 2 : 1) * kB64sWide) * 4 + 2 * 128 * 4 + (proj ? kB64sPix * kB64sYP : 0);
+}
 
-// The three layers requantise as a product's high word (rq_fast) and the skip operand is rescaled likewise (sk).  BYTE: all of them to bytes (requant_fits_byte)
-template <bool BYTE>
+// The three layers requantise as a product's high word (rq_fast) and the skip operand is rescaled likewise (sk).  BYTE: all of them to bytes (requant_fits_byte).
+// PROJ: the block that opens the stage: 64 input channels, the skip operand a projection pj of the block input whose rescale shifts by less than 32
+template <bool PROJ, bool BYTE>
 __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *const x, const uint8_t *const wp1, const uint8_t *const wp2,
                                                                const uint8_t *const wp3, const int32_t *const bias1, const int32_t *const bias2,
                                                                const int32_t *const bias3, const BlockArgs g, const SkipMul sk, const ConvArgs a1,
-                                                               const ConvArgs a2, const ConvArgs a3)
+                                                               const ConvArgs a2, const ConvArgs a3, const ProjArgs pj)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr unsigned OOB = 0x80000000u;
-    constexpr int MID = kB64sMid, C = kB64sWide, XP = kB64sXP, AP = kB64sAP;
+    constexpr int MID = kB64sMid, C = kB64sWide, CIN = PROJ ? MID : C, XP = CIN + 16, YP = kB64sYP, AP = kB64sAP;
+    constexpr int XBYTES = b64s_patch_bytes(PROJ);
 
-    // LDS: two patches of x (in the end y on the tile's rows) | a on the patch, then b on the tile | biases [64] [64] [256] | two tables of patch rows
+    // LDS: two patches of x (in the end y on the tile's rows) | a on the patch, then b on the tile | biases [64] [64] [256] (PROJ: [256] of the
+    // projection) | two tables of patch rows | PROJ: y on the tile, which has no room in a patch of 64 channels
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
-    uint8_t *const abuf = lds + 2 * kB64sXBytes;
+    uint8_t *const abuf = lds + 2 * XBYTES;
     int32_t *const btab = (int32_t *)(abuf + kB64sRows * AP);
-    unsigned *const rtab = (unsigned *)(btab + 2 * MID + C);
+    unsigned *const rtab = (unsigned *)(btab + 2 * MID + (PROJ ? 2 : 1) * C);
+    [[maybe_unused]] uint8_t *const ybuf = (uint8_t *)(rtab + 2 * 128);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -56,8 +69,10 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
     // ---- biases and this wave's weights, for the workgroup's whole life: requested first, from arguments that arrive in registers
     const int c12 = wave & 1, pg = (wave >> 1) ^ (int)((blockIdx.x >> 8) & 1);          // chunk of layers 1 and 2; pixel group in phase 2 and first one in
                                                        // phase 1, where group 0's waves take a second one (the other waves of the second workgroup on a compute unit)
-    v4i w1[8], w2[18], w3[2][2];
+    v4i w1[CIN / 32], w2[18], w3[2][2];
+    [[maybe_unused]] v4i wq[2][2];                     // the projection's
     int bv[2];
+    [[maybe_unused]] int bq;
     static_assert(MID == 64, "a wave's biases are one layer's");
     bv[0] = (wave == 0 ? bias1 : wave == 1 ? bias2 : bias3 + 64 * (wave - 2))[lane];
     bv[1] = bias3[min(tid + 2 * MID, C - 1)];
@@ -65,11 +80,11 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
     __builtin_amdgcn_sched_barrier(0);
     {
         const int l16 = lane * 16;
-        const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void *)(wp1 + (size_t)c12 * 4 * kChunkBytes), 0, 4 * kChunkBytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t r1 = __builtin_amdgcn_make_buffer_rsrc((void *)(wp1 + (size_t)c12 * (CIN / 64) * kChunkBytes), 0, CIN / 64 * kChunkBytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t r2 = __builtin_amdgcn_make_buffer_rsrc((void *)(wp2 + (size_t)c12 * 9 * kChunkBytes), 0, 9 * kChunkBytes, 0x00020000);
         const __amdgpu_buffer_rsrc_t r3 = __builtin_amdgcn_make_buffer_rsrc((void *)(wp3 + (size_t)wave * 2 * kChunkBytes), 0, 2 * kChunkBytes, 0x00020000);
 #pragma unroll
-        for (int f = 0; f < 8; ++f) w1[f] = __builtin_amdgcn_raw_buffer_load_b128(r1, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
+        for (int f = 0; f < CIN / 32; ++f) w1[f] = __builtin_amdgcn_raw_buffer_load_b128(r1, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
 #pragma unroll
         for (int f = 0; f < 18; ++f) w2[f] = __builtin_amdgcn_raw_buffer_load_b128(r2, l16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
 #pragma unroll
@@ -77,6 +92,12 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
     }
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (PROJ) {                              // (their arguments come late, with the tile's)
+        bq = pj.bias[tid];
+        const __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void *)(pj.wp + (size_t)wave * 2 * kChunkBytes), 0, 2 * kChunkBytes, 0x00020000);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) wq[f >> 1][f & 1] = __builtin_amdgcn_raw_buffer_load_b128(rq, lane * 16 + (f & 1) * 1024, (f >> 1) * kChunkBytes, 0);
+    }
     in_registers(g.per_xcd, g.n_tiles, g.tiles_per_img, g.tiles_x, g.TH, g.TW, g.PW, g.inv_pw, g.inv_tw, g.H, g.W, g.x_cs, g.x_bytes, g.k1, a3.out_cs, a3.out_co, a3.out);
 
     auto sync = [&]() {
@@ -111,16 +132,16 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
             rtab[b * 128 + tid] = ok ? (unsigned)(((n * g.H + iy) * g.W + ix) * g.x_cs) : OOB;
         }
     };
-    // Copies of 1 KiB: 16-byte piece i of the region is piece i % 17 of row i / 17; the last one is padding, which takes any bytes (an offset
+    // Copies of 1 KiB: 16-byte piece i of the region is piece i % 17 (PROJ: 5) of row i / 17; the last one is padding, which takes any bytes (an offset
     // of 1 GiB beside the row: inside the tensor or read as zeros).
-    constexpr int COPIES = kB64sXBytes / 1024, CPW = (COPIES + 3) / 4;
+    constexpr int COPIES = XBYTES / 1024, CPW = (COPIES + 3) / 4;
     int c_row[CPW], c_off[CPW];                        // of this lane's piece of copy wave + 4 q: table entry, offset in the row
 #pragma unroll
     for (int q = 0; q < CPW; ++q) {
         const int i = (wave + 4 * q) * 64 + lane;
-        const int row = (int)(((unsigned)i * 61681u) >> 20), piece = i - row * 17;             // / 17, exact below 2^16
+        const int row = (int)(((unsigned)i * (PROJ ? 209716u : 61681u)) >> 20), piece = i - row * (XP / 16);       // / 17, / 5: exact below 2^12
         c_row[q] = min(row, kB64sRows);
-        c_off[q] = piece < 16 ? piece * 16 : 0x40000000;
+        c_off[q] = piece < CIN / 16 ? piece * 16 : 0x40000000;
     }
     auto issue_patch = [&](int b) __attribute__((always_inline)) {
         unsigned off[CPW];
@@ -130,7 +151,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
 #pragma unroll
         for (int q = 0; q < CPW; ++q)
             if (wave + 4 * q < COPIES)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + b * kB64sXBytes + (wave + 4 * q) * 1024), 16,
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs_x, (__attribute__((address_space(3))) void *)(lds + b * XBYTES + (wave + 4 * q) * 1024), 16,
                                                          off[q], 0, 0, 0);
     };
 
@@ -141,6 +162,8 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
 #pragma unroll
     for (int q = 0; q < 2; ++q)
         if (tid + q * 256 < 2 * MID + C) btab[tid + q * 256] = bv[q];
+
+    if constexpr (PROJ) btab[2 * MID + C + tid] = bq;
 
     // patch row of this lane's pixels q = 32 j + col (slots beyond the tile: of pixel 0)
     int prow[2];
@@ -161,7 +184,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
         const int q = (wave + 4 * c) * 4 + (lane >> 4);
         const bool slot = q < g.TH * g.TW;
         const int ty = slot ? (int)(((unsigned)q * g.inv_tw) >> 16) : 0, tx = slot ? q - ty * g.TW : 0;
-        s_lds[c] = ((ty + 1) * g.PW + tx + 1) * XP + (lane & 15) * 16;
+        s_lds[c] = (PROJ ? q : (ty + 1) * g.PW + tx + 1) * YP + (lane & 15) * 16;
         s_y[c] = (short)ty;
         s_x[c] = (short)tx;
         s_out[c] = slot ? (unsigned)((ty * g.W + tx) * a3.out_cs + (lane & 15) * 16) : OOB;
@@ -171,7 +194,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
     for (int v = blockIdx.x; valid(v); v += gridDim.x, buf ^= 1) {
     int n, y0, x0;
     tile_origin(v, n, y0, x0);
-    uint8_t *const xb = lds + buf * kB64sXBytes;
+    uint8_t *const xb = lds + buf * XBYTES;
     asm volatile("" ::: "memory");
     if (v == (int)blockIdx.x) ICNN_WAIT_VMCNT(0);      // this wave's copies of the patch have landed (the weights, requested before them, too);
     else ICNN_WAIT_VMCNT(4);                           // younger are the last tile's four stores
@@ -188,17 +211,18 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
         if (rep && pg) break;
         const int row = 32 * (rep ? 2 : pg) + col;
         const uint8_t *const xr = xb + row * XP + half * 16;
-        v4i bf[4];
+        constexpr int NF = CIN / 32, NB = NF < 4 ? NF : 4;
+        v4i bf[NB];
 #pragma unroll
-        for (int h = 0; h < 4; ++h) bf[h] = *(const v4i *)(xr + h * 32);
+        for (int h = 0; h < NB; ++h) bf[h] = *(const v4i *)(xr + h * 32);
         v16i acc = bias16(btab + c12 * 32 + half * 16);
         __builtin_amdgcn_sched_barrier(0);
-        static_for<8>([&](auto h_tag) __attribute__((always_inline)) {
+        static_for<NF>([&](auto h_tag) __attribute__((always_inline)) {
             constexpr int h = decltype(h_tag)::value;
-            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w1[h], bf[h & 3], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(w1[h], bf[h % NB], acc, 0, 0, 0);
             asm volatile("" : "+v"(acc));
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (h < 4) bf[h] = *(const v4i *)(xr + (h + 4) * 32);
+            if constexpr (h + NB < NF) bf[h % NB] = *(const v4i *)(xr + (h + NB) * 32);
             __builtin_amdgcn_sched_barrier(0);
         });
         mfma_drain(acc);
@@ -244,6 +268,50 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
 #pragma unroll
             for (int h = 0; h < 2; ++h) bf[j][h] = *(const v4i *)(abuf + (32 * j + col) * AP + half * 16 + h * 32);
         v16i acc[2];
+        if constexpr (PROJ) {
+            v4i xf[2][2];                              // the pixels' own rows of the patch
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) xf[j][h] = *(const v4i *)(xb + prow[j] * XP + half * 16 + h * 32);
+            // item i: chunk i >> 1, pixel group i & 1, in four steps; while one item's sums are in vector instructions, another's products are made
+            auto project = [&](auto i_tag) __attribute__((always_inline)) {
+                constexpr int c = decltype(i_tag)::value >> 1, j = decltype(i_tag)::value & 1;
+                acc[j] = bias16(btab + 2 * MID + C + (2 * wave + c) * 32 + half * 16);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(wq[c][h], xf[j][h], acc[j], 0, 0, 0);
+                asm volatile("" : "+v"(acc[j]));
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            // the projection's sum at the main path's ratio, on the last layer's bias; that layer's products on top
+            auto rescale = [&](auto i_tag) __attribute__((always_inline)) {
+                constexpr int c = decltype(i_tag)::value >> 1, j = decltype(i_tag)::value & 1;
+                const v16i b3 = bias16(btab + 2 * MID + (2 * wave + c) * 32 + half * 16);
+                mfma_drain(acc[j]);
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[j][r] = rsr64_low((int64_t)acc[j][r] * pj.res_mul, pj.res_shift) + b3[r];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w3[c][h], bf[j][h], acc[j], 0, 0, 0);
+                asm volatile("" : "+v"(acc[j]));
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            auto finish = [&](auto i_tag) __attribute__((always_inline)) {
+                constexpr int c = decltype(i_tag)::value >> 1, j = decltype(i_tag)::value & 1;
+                mfma_drain(acc[j]);
+                *(v4i *)(ybuf + (32 * j + col) * YP + (2 * wave + c) * 32 + half * 16) = epilogue_hi16<0, BYTE>(a3, sk, acc[j], v4i{0, 0, 0, 0});
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            constexpr std::integral_constant<int, 0> i0{};
+            constexpr std::integral_constant<int, 1> i1{};
+            constexpr std::integral_constant<int, 2> i2{};
+            constexpr std::integral_constant<int, 3> i3{};
+            project(i0), project(i1);
+            rescale(i0), rescale(i1);
+            finish(i0), project(i2);
+            finish(i1), project(i3);
+            rescale(i2), rescale(i3);
+            finish(i2), finish(i3);
+        } else {
         v4i r8[2];
         // item i: chunk i >> 1, pixel group i & 1; its products are issued before the epilogue of the item before it
         auto multiply = [&](auto i_tag) __attribute__((always_inline)) {
@@ -264,6 +332,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
             if (in[j]) *(v4i *)(xb + prow[j] * XP + (2 * wave + c) * 32 + half * 16) = o;
             __builtin_amdgcn_sched_barrier(0);
         });
+        }
     }
     sync();                                            // y is complete
 
@@ -274,7 +343,7 @@ __global__ __launch_bounds__(256, 2) void conv_block64s_kernel(const uint8_t *co
             (uint8_t *)a3.out + (size_t)(unsigned)((n * g.H + y0) * g.W + x0) * a3.out_cs + a3.out_co, 0, 0x7fffff00, 0x00020000);
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const v4i o = *(const v4i *)(xb + s_lds[c]);
+            const v4i o = *(const v4i *)((PROJ ? ybuf : xb) + s_lds[c]);
             const bool ok = y0 + s_y[c] < g.H && x0 + s_x[c] < g.W;
             __builtin_amdgcn_raw_buffer_store_b128(o, rs_y, ok ? s_out[c] : OOB, 0, 0);
         }
@@ -305,21 +374,33 @@ bool conv_block64s_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs 
     return (const uint8_t *)a3.res == g.x && a3.res_cs == g.x_cs && make_skip_mul(a3.res_mul, a3.res_shift).ok;
 }
 
-hipError_t launch_conv_block64s(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st)
+// The block that opens the stage, 64 -> 64 -> 64 -> 256 channels with a 64 -> 256 projection, per-layer requantisation and an 8-bit output: every such block
+// whose arithmetic the kernel has, since it is the faster one at any number of pictures (times above).  Shifts of 32 and more: a word of the product
+// alone holds them, in another instruction.
+bool conv_block64s_proj_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, const ProjArgs &pj)
 {
-    if (!conv_block64s_takes(g, a1, a2, a3)) return hipErrorInvalidValue;
+    BlockArgs t = g;
+    return conv_block64_proj_takes(a1, a3, pj) && a1.rq_fast && a2.rq_fast && a3.rq_fast && !a3.pc && pj.res_shift < 32 && block64s_stores_fit(g, a3) &&
+           conv_block_tile(g.H, g.W, kB64sPix, kB64sRows, t);
+}
+
+// pj: the projection of an opening block, else null
+hipError_t launch_conv_block64s(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, const ProjArgs *pj, hipStream_t st)
+{
+    if (!(pj ? conv_block64s_proj_takes(g, a1, a2, a3, *pj) : conv_block64s_takes(g, a1, a2, a3))) return hipErrorInvalidValue;
     BlockArgs gx = g;
     if (!conv_block_tile(g.H, g.W, kB64sPix, kB64sRows, gx)) return hipErrorInvalidValue;
     const long long tiles = (long long)gx.tiles_per_img * g.N;
     if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
     gx.n_tiles = (int)tiles;
     gx.per_xcd = (int)((tiles + 7) / 8);
-    const size_t lds_bytes = 2 * kB64sXBytes + kB64sRows * kB64sAP + (2 * kB64sMid + kB64sWide) * 4 + 2 * 128 * 4;
-    static_assert(2 * kB64sXBytes + kB64sRows * kB64sAP + (2 * kB64sMid + kB64sWide) * 4 + 2 * 128 * 4 <= 64 * 1024, "no permission needed");
+    static_assert(b64s_lds_bytes(false) <= 64 * 1024 && b64s_lds_bytes(true) <= 64 * 1024, "no permission needed");
     const SkipMul sk = a3.res_mode ? make_skip_mul(a3.res_mul, a3.res_shift) : SkipMul{0, 0, 0};     // (without an operand: adds zero)
-    const auto kernel = requant_fits_byte(a1) && requant_fits_byte(a2) && requant_fits_byte(a3) ? conv_block64s_kernel<true> : conv_block64s_kernel<false>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(8 * gx.per_xcd, 512)), dim3(256), lds_bytes, st, gx.x, a1.wp, a2.wp, a3.wp, a1.bias, a2.bias, a3.bias, gx,
-                       sk, a1, a2, a3);
+    const bool byte = requant_fits_byte(a1) && requant_fits_byte(a2) && requant_fits_byte(a3);
+    const auto kernel = pj ? byte ? conv_block64s_kernel<true, true> : conv_block64s_kernel<true, false>
+                           : byte ? conv_block64s_kernel<false, true> : conv_block64s_kernel<false, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min(8 * gx.per_xcd, 512)), dim3(256), b64s_lds_bytes(pj != nullptr), st, gx.x, a1.wp, a2.wp, a3.wp, a1.bias,
+                       a2.bias, a3.bias, gx, sk, a1, a2, a3, pj ? *pj : ProjArgs{});
     return hipGetLastError();
 }
 

@@ -204,6 +204,13 @@ __device__ __forceinline__ int64_t rsr64(int64_t v, int s)
     return (v + ((int64_t(1) << s) >> 1)) >> s;
 }
 
+// Its low 32 bits, for shifts below 32: they straddle the product's two words, which one full-rate instruction shifts together.
+__device__ __forceinline__ int rsr64_low(int64_t v, int s)
+{
+    const uint64_t t = (uint64_t)(v + ((int64_t(1) << s) >> 1));
+    return (int)__builtin_amdgcn_alignbit((uint32_t)(t >> 32), (uint32_t)t, (uint32_t)s);
+}
+
 __device__ __forceinline__ int sat32(int64_t v)
 {
     return v > INT32_MAX ? INT32_MAX : (v < INT32_MIN ? INT32_MIN : (int)v);
@@ -243,7 +250,7 @@ struct Tuning {
     int deep_always = 0;   // that kernel for every layer whose shape it accepts
     int block_any_form = 0; // LDS-ring block kernel: the instantiation that holds every epilogue form, also where one form would do
     int no_block128 = 0;   // fused bottleneck blocks of 512 -> 128 -> 512 channels: the LDS-ring kernel instead of the one of small workgroups
-    int no_block64s = 0;   // fused bottleneck blocks of 256 -> 64 -> 256 channels: the kernel with resident weights instead of the one of small workgroups
+    int no_block64s = 0;   // fused bottleneck blocks of 256 -> 64 -> 256 and 64 -> 64 -> 256 channels: the kernel with resident weights instead of the one of small workgroups
     int no_block64 = 0;    // fused bottleneck blocks with 64 middle channels: the LDS-ring kernel instead of the register-resident one
     int block128_tile = 0; // blocks of 128 middle channels in tiles of 32 (1) or 64 (2) pixels
     int keep = 0;          // 3x3 layers of 64 channels with their weights kept in registers: 1 every layer that kernel accepts, 2 none
@@ -295,7 +302,8 @@ hipError_t launch_conv_block(const BlockArgs &g, const ConvArgs &a1, const ConvA
 bool conv_block128_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a3);
 hipError_t launch_conv_block128(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st);
 bool conv_block64s_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3);
-hipError_t launch_conv_block64s(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, hipStream_t st);
+bool conv_block64s_proj_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, const ProjArgs &pj);
+hipError_t launch_conv_block64s(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, const ProjArgs *pj, hipStream_t st);
 size_t conv_block64_lds_bytes(int c_in, int c_out, bool proj, bool pc);
 bool conv_block64_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a3);
 bool conv_block64_proj_takes(const ConvArgs &a1, const ConvArgs &a3, const ProjArgs &pj);

@@ -14,8 +14,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 
 
 def build(verbose=False, extra=(), only_changed=False):
-    """only_changed: skip sources whose object is newer than the source and every header (development aid;
-    the driver's build check compiles everything)."""
+    """only_changed: skip sources whose object is newer than the source and every header (development aid; by default everything is compiled)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJ, exist_ok=True)
     headers = [os.path.join(CSRC, f) for f in os.listdir(CSRC) if f.endswith(".h")]

@@ -18,6 +18,7 @@
 // projection convolution of the block input, W_p x + b_p, rescaled to the main path's ratio and added before the last
 // layer's products, exactly as the two-GEMM kernel of the projection blocks does; here its two MFMAs per pixel group
 // read the pixel's own patch row, and the last layer's chunk count no longer follows from the input width.
+// (Blocks of 256 outer channels that requantise per layer, with or without a projection, go to conv_block64s.hip where it has their arithmetic.)
 // Four workgroup barriers per tile.  Same MFMA instruction, accumulator layout, packed weights and epilogue
 // arithmetic as the other convolution kernels: the result is that of the three separate layers, bit for bit.
 #include "conv_common.h"

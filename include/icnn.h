@@ -141,6 +141,7 @@ const char *icnn_last_error(void);
  *   "plane_always" 1 lets the kernel with two-dimensional tiles (few channels, large pictures) take every layer it accepts
  *   "deep_always" 1 lets the 3x3 kernel whose waves split the K axis take every layer whose shape it accepts
  *   "deep_plain_walk" 1 gives that kernel the tile order of the other kernels (pixel tiles, not channel tiles, per XCD)
+ *   "block64s_tile" 0 library's choice; 1 / 2: fused bottleneck blocks of 256 -> 64 -> 256 and 64 -> 64 -> 256 channels in tiles of 32 / 64 pixels
  *   "block128_tile" 0 library's choice; 1 / 2: fused bottleneck blocks of 512 -> 128 -> 512 channels in tiles of 32 / 64 pixels
  *   "keep"        0 library's choice; 1 / 2: every / no layer whose shape it takes on the 3x3 kernel that keeps 64 channels' weights in registers
  *   "flat"        0 library's choice; 1 / 2: every / no layer whose shape it takes on the kernel that streams weights into registers

@@ -180,7 +180,7 @@ int icnn_set_tuning(const char *name, int32_t value)
         {"no_narrow", &Tuning::no_narrow, 0, 1}, {"lat", &Tuning::lat, 0, 4}, {"no_lat", &Tuning::no_lat, 0, 1}, {"no_fc", &Tuning::no_fc, 0, 1},
         {"no_halo", &Tuning::no_halo, 0, 1},     {"halo_tile", &Tuning::halo_tile, 0, 2},
         {"halo_always", &Tuning::halo_always, 0, 1}, {"no_stream", &Tuning::no_stream, 0, 1},
-        {"ksplit", &Tuning::ksplit, 0, 8}, {"no_block64", &Tuning::no_block64, 0, 1}, {"no_block128", &Tuning::no_block128, 0, 1}, {"no_block64s", &Tuning::no_block64s, 0, 1},
+        {"ksplit", &Tuning::ksplit, 0, 8}, {"no_block64", &Tuning::no_block64, 0, 1}, {"no_block128", &Tuning::no_block128, 0, 1}, {"no_block64s", &Tuning::no_block64s, 0, 1}, {"block64s_tile", &Tuning::block64s_tile, 0, 2},
         {"no_plane", &Tuning::no_plane, 0, 1}, {"no_pic", &Tuning::no_pic, 0, 1}, {"block_any_form", &Tuning::block_any_form, 0, 1}, {"plane_no_pipe", &Tuning::plane_no_pipe, 0, 1}, {"plane_always", &Tuning::plane_always, 0, 1},
         {"no_deep", &Tuning::no_deep, 0, 1}, {"deep_always", &Tuning::deep_always, 0, 1}, {"deep_plain_walk", &Tuning::deep_plain_walk, 0, 1}, {"tri_tile", &Tuning::tri_tile, 0, 4}, {"flat", &Tuning::flat, 0, 2}, {"keep", &Tuning::keep, 0, 2}, {"block128_tile", &Tuning::block128_tile, 0, 2},
     };

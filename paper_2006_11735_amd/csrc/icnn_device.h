@@ -254,6 +254,7 @@ struct Tuning {
     int block_any_form = 0; // LDS-ring block kernel: the instantiation that holds every epilogue form, also where one form would do
     int no_block128 = 0;   // fused bottleneck blocks of 512 -> 128 -> 512 channels: the LDS-ring kernel instead of the one of small workgroups
     int no_block64s = 0;   // fused bottleneck blocks of 256 -> 64 -> 256 and 64 -> 64 -> 256 channels: the kernel with resident weights instead of the one of small workgroups
+    int block64s_tile = 0; // pixels of a tile of that kernel: 0 library's choice, 1: 32, 2: 64
     int no_block64 = 0;    // fused bottleneck blocks with 64 middle channels: the LDS-ring kernel instead of the register-resident one
     int block128_tile = 0; // blocks of 128 middle channels in tiles of 32 (1) or 64 (2) pixels
     int keep = 0;          // 3x3 layers of 64 channels with their weights kept in registers: 1 every layer that kernel accepts, 2 none

@@ -373,12 +373,18 @@ static bool block64s_small(long long tiles32, long long tiles64)
     return tiles32 <= kB64sUnits || (tiles64 > kB64sUnits && tiles32 <= 3 * kB64sUnits);
 }
 
-// A tile of 32 og pixels, in t, whose stores can be made: their offsets from the tile's first pixel are 32 bits, up to the descriptor's 0x7fffff00
-// bytes (at a pitch of 256 pictures of up to 133000 columns fit whatever their tile)
+// A tile of 32 og pixels, in t, whose stores can be made: their offsets from the tile's first pixel are 32 bits, up to the descriptor's 0x7fffff00 bytes
+constexpr long long kB64sStores = 0x7fffff00LL - kB64sWide;
 static bool block64s_tile(const BlockArgs &g, const ConvArgs &a3, int og, BlockArgs &t)
 {
     t = g;
-    return conv_block_tile(g.H, g.W, 32 * og, b64s_rows(og), t) && ((t.TH - 1LL) * g.W + t.TW - 1) * a3.out_cs <= 0x7fffff00LL - kB64sWide;
+    return conv_block_tile(g.H, g.W, 32 * og, b64s_rows(og), t) && ((t.TH - 1LL) * g.W + t.TW - 1) * a3.out_cs <= kB64sStores;
+}
+// (A tile has at most 64 rows: it is searched for only where that many could pass the limit, at a pitch of 256 pictures from 133000 columns on.)
+static bool block64s_stores_fit(const BlockArgs &g, const ConvArgs &a3)
+{
+    BlockArgs t;
+    return (63LL * g.W + 64) * a3.out_cs <= kB64sStores || block64s_tile(g, a3, 2, t);
 }
 
 // 256 -> 64 -> 64 -> 256 channels, per-layer requantisation, an 8-bit output, the block input itself as skip operand (unsigned 8-bit, joined
@@ -387,8 +393,7 @@ bool conv_block64s_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs 
 {
     if (a1.Cin != kB64sWide || a1.Cout != kB64sMid || a3.Cout != kB64sWide || a3.pc) return false;
     if (a3.out_mode == 3 || !a3.epi_vec || a3.epi_mode / 4 == 2 || !a1.rq_fast || !a2.rq_fast || !a3.rq_fast) return false;
-    BlockArgs t;
-    if (!block64s_tile(g, a3, 2, t)) return false;
+    if (!block64s_stores_fit(g, a3)) return false;
     if (a3.res_mode == 0) return true;
     return (const uint8_t *)a3.res == g.x && a3.res_cs == g.x_cs && make_skip_mul(a3.res_mul, a3.res_shift).ok;
 }
@@ -398,19 +403,23 @@ bool conv_block64s_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs 
 // alone holds them, in another instruction.
 bool conv_block64s_proj_takes(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, const ProjArgs &pj)
 {
-    BlockArgs t;
-    return conv_block64_proj_takes(a1, a3, pj) && a1.rq_fast && a2.rq_fast && a3.rq_fast && !a3.pc && pj.res_shift < 32 && block64s_tile(g, a3, 2, t);
+    return conv_block64_proj_takes(a1, a3, pj) && a1.rq_fast && a2.rq_fast && a3.rq_fast && !a3.pc && pj.res_shift < 32 && block64s_stores_fit(g, a3);
 }
 
 // pj: the projection of an opening block, else null
 hipError_t launch_conv_block64s(const BlockArgs &g, const ConvArgs &a1, const ConvArgs &a2, const ConvArgs &a3, const ProjArgs *pj, hipStream_t st)
 {
     if (!(pj ? conv_block64s_proj_takes(g, a1, a2, a3, *pj) : conv_block64s_takes(g, a1, a2, a3))) return hipErrorInvalidValue;
-    BlockArgs gx;
-    const auto tiles_of = [&](int og) { return block64s_tile(g, a3, og, gx) ? (long long)gx.tiles_per_img * g.N : -1; };
-    const long long tiles64 = tiles_of(2), tiles32 = tiles_of(1);
-    const int og = tiles32 >= 0 && (g_tuning.block64s_tile ? g_tuning.block64s_tile == 1 : block64s_small(tiles32, tiles64)) ? 1 : 2;
-    const long long tiles = tiles_of(og);
+    // (a search takes 0.1 to 0.2 us of the host: as few as the choice needs)
+    BlockArgs gx, large;
+    const auto tiles_of = [&](int og, BlockArgs &t) { return block64s_tile(g, a3, og, t) ? (long long)t.tiles_per_img * g.N : -1; };
+    const int forced = g_tuning.block64s_tile;
+    long long tiles = forced == 2 ? -1 : tiles_of(1, gx);
+    int og = 1;
+    if (tiles < 0 || (!forced && tiles > kB64sUnits)) {
+        const long long tiles64 = tiles_of(2, large);
+        if (tiles < 0 || !block64s_small(tiles, tiles64)) og = 2, gx = large, tiles = tiles64;
+    }
     if (tiles < 0 || tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
     gx.n_tiles = (int)tiles;
     gx.per_xcd = (int)((tiles + 7) / 8);

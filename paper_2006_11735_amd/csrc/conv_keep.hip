@@ -282,13 +282,14 @@ __global__ __launch_bounds__(256, 1) void conv_keep_kernel(const uint8_t *x, con
             }
         }
         if (next_n <= 0) break;
-        // the next tile's rows have landed: younger are two stores a round, and two loads of the skip operand
+        // the next tile's rows have landed: younger are two stores a round.  (And with a skip operand loads of it, but not two a round on every way: those that
+        // nothing reads are left out.  So they do not count)
         asm volatile("" ::: "memory");
         switch (n) {
-        case 1: ICNN_WAIT_VMCNT((RES ? 4 : 2)); break;
-        case 2: ICNN_WAIT_VMCNT((RES ? 8 : 4)); break;
-        case 3: ICNN_WAIT_VMCNT((RES ? 12 : 6)); break;
-        default: ICNN_WAIT_VMCNT((RES ? 16 : 8)); break;
+        case 1: ICNN_WAIT_VMCNT(2); break;
+        case 2: ICNN_WAIT_VMCNT(4); break;
+        case 3: ICNN_WAIT_VMCNT(6); break;
+        default: ICNN_WAIT_VMCNT(8); break;
         }
         sync();                                        // ... everybody's, and nobody reads this tile's any more
         t = next;

@@ -35,8 +35,9 @@ struct KeepArgs {
 };
 
 // Products written out: with more registers than a SIMD's 256 vector ones the compiler keeps the sums among the accumulation registers and moves them for every
-// product and every vector instruction.  Here the weights are there, which nothing else reads.  (sum is read by vector instructions behind
-// mfma_drain only; two products of one sum have another one between them)
+// product and every vector instruction.  Here the weights are there, which nothing else reads.  The compiler does not know them for products and puts no wait states
+// behind them: a round's last two come with the twelve that it gives this product elsewhere, in one statement, and nothing but a vector instruction that this file
+// writes down reads the sums behind it.  (Two products of one sum have another one between them)
 __device__ __forceinline__ void keep_mfma(v16i &sum, const v4i &w, const v4i &x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -47,6 +48,12 @@ __device__ __forceinline__ void keep_mfma_first(v16i &sum, const v4i &w, const v
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     asm volatile("v_mfma_i32_32x32x32_i8 %0, %1, %2, %3" : "=&v"(sum) : "a"(w), "v"(x), "v"(start));
+#endif
+}
+__device__ __forceinline__ void keep_mfma_last(v16i (&sum)[2], const v4i &w0, const v4i &w1, const v4i &x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("v_mfma_i32_32x32x32_i8 %0, %2, %4, %0\n\tv_mfma_i32_32x32x32_i8 %1, %3, %4, %1\n\ts_nop 11" : "+v"(sum[0]), "+v"(sum[1]) : "a"(w0), "a"(w1), "v"(x));
 #endif
 }
 
@@ -210,13 +217,13 @@ __global__ __launch_bounds__(256, 1) void conv_keep_kernel(const uint8_t *x, con
         static_for<2 * kKeepF>([&](auto s_tag) __attribute__((always_inline)) {
             constexpr int s = decltype(s_tag)::value, f = s / 2, c = s & 1, ahead = f + RING - 1;
             if constexpr (f == 0) keep_mfma_first(cur.s[c], w[c][f], bf[f % RING], b[c]);
-            else keep_mfma(cur.s[c], w[c][f], bf[f % RING]);
+            else if constexpr (f < kKeepF - 1) keep_mfma(cur.s[c], w[c][f], bf[f % RING]);
+            else if constexpr (c == 1) keep_mfma_last(cur.s, w[0][f], w[1][f], bf[f % RING]);
             __builtin_amdgcn_sched_barrier(0);
             // a pair of the outputs behind two products, in two halves: a product that follows another one at once waits for the matrix unit, and the
             // wave's vector instructions with it
             constexpr int pair = f - 1, oc = pair / 8, R0 = 2 * (pair % 8);
             if constexpr (pair >= 0 && pair < 16 && c == 0) {
-                if constexpr (pair == 0) mfma_drain(old.s);
 #pragma unroll
                 for (int e = 0; e < 2; ++e) {
                     sum[e] = old.s[oc][R0 + e];
@@ -277,8 +284,12 @@ __global__ __launch_bounds__(256, 1) void conv_keep_kernel(const uint8_t *x, con
             step(t, at, min(j + 1, n - 1), q, s0, s1);
             if (j + 1 < n) step(t, at, min(j + 2, n - 1), q, s1, s0);
             else {
-                mfma_drain(s0.s);
-                s1 = s0;
+                // (not a copy: the compiler makes it in front of the last products, whose sums it then has in s1's place, and without wait states)
+                int zero = 0;
+                asm volatile("" : "+s"(zero));
+#pragma unroll
+                for (int c = 0; c < 2; ++c) s1.s[c] = s0.s[c] + zero, s1.r8[c] = s0.r8[c];
+                s1.p = s0.p;
             }
         }
         if (next_n <= 0) break;
@@ -296,7 +307,6 @@ __global__ __launch_bounds__(256, 1) void conv_keep_kernel(const uint8_t *x, con
         round = next_round;
         n = next_n;
     }
-    mfma_drain(s1.s);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         const v4i o = epilogue_hi16<RES ? 1 : 0, BYTE>(a, g.sk, s1.s[c], s1.r8[c]);

@@ -834,7 +834,7 @@ __device__ __forceinline__ void in_registers(T v, R... rest)
 
 // A kernel's argument that is read here and not where the compiler would have it, which is at the kernel's start: there it holds registers through phases
 // that do not use it, and where they run out it is waited for at once to be put aside.  at: its place among the kernel's arguments (their
-// order in a struct of the same members).
+// order in a struct of the same members, which the kernel's file checks with parameters_of).
 template <class T>
 __device__ __forceinline__ T late_argument(unsigned at)
 {
@@ -848,6 +848,10 @@ __device__ __forceinline__ T late_argument(unsigned at)
     return T{};
 #endif
 }
+template <class... T>
+struct Types {};
+template <class... T>
+Types<T...> parameters_of(void (*)(T...));
 
 // fast_div with its parts as they come in scalar arguments
 __device__ __forceinline__ int fast_div_packed(int n, unsigned mul, unsigned s1, unsigned s2)

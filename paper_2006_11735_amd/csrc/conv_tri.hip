@@ -24,7 +24,7 @@
 
 namespace icnn {
 
-// The kernel's arguments in their order (late_argument)
+// The kernel's arguments in their order (late_argument): a parameter more, or of another type, does not compile (tri_members)
 struct TriKernelArgs {
     const uint8_t *x, *w2;
     const int32_t *bias2, *bias3, *bias1;
@@ -473,6 +473,15 @@ __global__ __launch_bounds__(512, 2) void conv_tri_kernel(const uint8_t *x, cons
     }
 #endif
 }
+
+// TriKernelArgs' members are the kernel's parameters
+inline auto tri_members(TriKernelArgs k)
+{
+    auto [x, w2, bias2, bias3, bias1, M, in_cs, shape, tiles, grid, w3, w1, ga, a2, a3, a1] = k;
+    return Types<decltype(x), decltype(w2), decltype(bias2), decltype(bias3), decltype(bias1), decltype(M), decltype(in_cs), decltype(shape), decltype(tiles), decltype(grid),
+                 decltype(w3), decltype(w1), decltype(ga), decltype(a2), decltype(a3), decltype(a1)>();
+}
+static_assert(std::is_same_v<decltype(tri_members(TriKernelArgs())), decltype(parameters_of(&conv_tri_kernel<1, true, 1>))>, "late_argument reads by this struct");
 
 // ------------------------------------------------------------------ dispatch
 namespace {

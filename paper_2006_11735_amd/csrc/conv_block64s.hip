@@ -23,7 +23,8 @@
 // PROJ: the block that opens the stage (64 input channels, the skip operand a projection of them, "after convolution").  Its last layer's sums
 // pass through vector instructions twice, once at the projection's ratio; an item's four steps (projection, rescale, products, epilogue) are
 // dealt out so that another item's products are made beside them.  28 weight fragments a wave; y has a region of LDS of its own.
-// 56 x 56 pixels, 1 / 9 / 64 pictures: 10.8 / 12.5 / 45.3 us with eight waves on tiles of 128 pixels (conv_block64.hip), 6.8 / 10.6 / 39.0 here, 5.7 at one picture in tiles of 32 pixels.
+// 56 x 56 pixels, 1 / 9 / 64 pictures, launches behind one another: 8.4 / 9.3 / 38.2 us with eight waves on tiles of 128 pixels (conv_block64.hip), 5.8 / 8.2 / 33.5 here, 4.65 at
+// one picture in tiles of 32 pixels (a trace of the network, where each has cold weights, gives 1 to 5 us more to either).
 #include "conv_common.h"
 
 #include <algorithm>

@@ -752,7 +752,8 @@ __device__ __forceinline__ bool pc_hi_channel(const int32_t *pc, int channel, bo
 // Between the last v_mfma of an accumulation and the first instruction that reads the accumulator.  The compiler's
 // hazard recogniser does not always keep the two apart (seen in a kernel whose epilogue starts two instructions after
 // the last MFMA, behind a branch: the reads returned the sums without the last product, now and then), and the
-// hardware does not hold the reader back.  Twenty wait states, what a 16-pass matrix instruction needs; the empty
+// hardware does not hold the reader back.  Twenty wait states, more than the compiler itself takes where it sees the reader (twelve behind the 32x32x32
+// product of eight passes, eight behind the 16x16x64 one of four); the empty
 // statements before and after tie every accumulator tile to the wait, so neither an MFMA nor a reader can cross it.
 #ifdef ICNN_NO_DRAIN            // measurement only: what the wait states and the register pinning cost
 #define ICNN_DRAIN_NOPS ""

@@ -5,17 +5,20 @@
 //            (64 pictures of 56 x 56) in tiles of at most eight; each of its four waves takes 32 pixels of a round, all 64 channels
 //   patch    the picture rows that a tile's pixels lie in and one above and below, W + 2 pixels of 80 bytes each (64 channels and 16 bytes that keep
 //            sixteen consecutive pixels on different banks), zeros outside the picture and in a row between two pictures: a tap is a constant
-//            distance, without masks.  Two buffers, the next tile's rows are copied while this one is multiplied
+//            distance, without masks.  Two buffers, the next tile's rows are asked for before this one is multiplied
 //   weights  36 fragments = 144 registers of a wave that has a SIMD's 512 for itself; they pass through the second buffer's place, so
 //            that memory is asked once per workgroup and not once per wave
 //   K loop   a pixel fragment (1 KiB of LDS) feeds two matrix instructions; between them the fragments to come are read and the group before is
 //            requantised, two outputs at a time, and stored.  No barrier but one per tile
 //
-// What bounds it, 64 x 56 x 56 pixels, clocks of a workgroup (18700 to 21400 at the 1.85 to 2.0 GHz that the chip's power leaves: 9.5 and 10.9 us; conv_flat.hip
-// and conv_plane.hip 13.5 and 16): 5000 until weights and first rows are there, 1800 for the next tile's copies, which pass the unit's 64 bytes a clock, 1300 a round (36
-// matrix instructions at 32 clocks and what they do not hide), 1570 with a skip operand (349 instructions).  Taken back: the next tile's copies dealt out between the products
-// (1530 and 1930 a round: the wave issues an instruction every 5 clocks); a pair of outputs behind every second product (1860 with a skip operand: a product behind another
-// one waits for the unit, and the wave's vector instructions with it).
+// What bounds it, 64 x 56 x 56 pixels in tiles of two and of four rounds, clocks of a workgroup (16400, with a skip operand 17700; 10.7 and 11.1 us a launch, conv_flat.hip
+// and conv_plane.hip 13.5 and 16): 3600 until weights and first rows are there, 1900 until the next tile's are asked for (their copies pass the unit's 64 bytes a clock), 1600 a
+// round (36 matrix instructions at 32 clocks and what they do not hide; with a skip operand, 100 vector instructions more, 1650), 700 between the tiles, 600 for the last group
+// (970).  With a skip operand a round waits for loads that stand behind the next tile's copies, and so for most of those: the first tile's two rounds take 3430
+// then, and 4480 at 128 pictures, whose tiles have four rounds' rows to copy.  Taken back: the next tile's copies dealt out between the products (1930 a round
+// with a skip operand: the wave issues an instruction every 5 clocks); a pair of outputs behind every second product (1860: a product behind another one waits for
+// the unit, and the wave's vector instructions with it); odd tiles that leave their sums where they are, the two sets of registers in turn through all tiles (skip
+// operand 11.1 -> 11.4 to 12.7: where ways meet, the compiler waits for more of the loads than it has to).
 #include "conv_common.h"
 
 #include <algorithm>
@@ -36,8 +39,8 @@ struct KeepArgs {
 
 // Products written out: with more registers than a SIMD's 256 vector ones the compiler keeps the sums among the accumulation registers and moves them for every
 // product and every vector instruction.  Here the weights are there, which nothing else reads.  The compiler does not know them for products and puts no wait states
-// behind them: a round's last two come with the twelve that it gives this product elsewhere, in one statement, and nothing but a vector instruction that this file
-// writes down reads the sums behind it.  (Two products of one sum have another one between them)
+// behind them: a round's last two come with the twelve that it gives this product elsewhere, in one statement.  A copy of the compiler's own could still come in front of
+// it, so tests/test_keep_waits.py looks for one in the built kernel.  (Two products of one sum have another one between them)
 __device__ __forceinline__ void keep_mfma(v16i &sum, const v4i &w, const v4i &x)
 {
 #if defined(__HIP_DEVICE_COMPILE__)

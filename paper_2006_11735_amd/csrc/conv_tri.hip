@@ -504,10 +504,11 @@ bool tri_shape(long long M, int W, int np, TriArgs &g)
 }  // namespace
 
 // Which tile.  One round of tiles on the 256 compute units takes 14, 19, 25 or 31 us by tile (28 for two rounds of the smallest), whatever their
-// number: the cheapest in rounds.  The 152-layer network, 32 / 64 / 96 / 112 pixels: 937 / 1057 / 1264 / 1454 us at 16 images, 1295 / 1375 / 1561 / 1748
-// at 40, 1671 / 1444 / 1627 / 1814 at 48, 1752 / 1603 / 1711 / 1896 at 64.  With several launches side by side, the smallest of the first three
-// tiles that gives all of them a compute unit each (two halves of 84 images: 1997 / 2050 / 1909 / 2077, of 96: 2189 / 2169 / 2115 / 2241), and
-// where none does the same rule as alone (of 128: 2817 / 2615 / 2780 / 2754).
+// number: the cheapest in rounds.  The 152-layer network, us, 32 / 64 / 96 / 112 pixels: 769 / 903 / 1093 / 1260 at 16 images, 842 / 962 / 1146 / 1326 at 24, 1043 / 1108 / 1274 / 1448
+// at 40, 1386 / 1172 / 1337 / 1515 at 48, 1510 / 1308 / 1466 / 1633 at 64, 1447 / 1260 / 1412 / 1597 at 72 (24, 72 and 84 on a faster machine).  With several launches side by side, the
+// smallest of the first three tiles that gives all of them a compute unit each (two halves of 84 images: 1729 / 1460 / 1474 / 1661, of 96: 1897 / 1716 / 1695 / 1836), and
+// where none does the same rule as alone (of 128: 2410 / 1996 / 2201 / 2224).  Every one of these goes to its best tile or within 1.1 % of it; beyond, the figures leave
+// the rule: 168 images 3078 / 2575 / 2709 / 2818 (it takes 96 pixels), 256 4438 / 3796 / 3661 / 3922 (112).
 bool conv_tri_plan(long long M, int W, int lanes, TriArgs &g)
 {
     if (M < 1 || M > 0x7fffffffLL - 256 || W > 1000) return false;
